@@ -54,8 +54,8 @@
  *    regions of three kinds, and the step is at its best when m or v lies in a region of another kind than the
  *    other arrays.  Which region is of which kind depends on the physical addresses an allocation gets;
  *    eco_bandwidth_probe, timed on candidate addresses before anything is stored there, tells.
- *  - One plan over all tensors of a model is one kernel launch per storage format; per-tensor calls pay a
- *    launch each.
+ *  - One plan over all tensors of a model is one kernel launch per quantized format (norm gains and ragged tails ride
+ *    in it); per-tensor calls pay a launch each, 2.6 us of host time and 4-6 us on the device.
  *  - Tensor lengths that are multiples of 512 keep every tile on the unguarded fast path.
  *  - Row-wise scale groups (group_size = the row length) of more than 512 elements run with every lane busy when the
  *    row is a multiple of 512 elements, or when 2, 4 or 8 rows together are (576, 640, 768, 1408, 2304, ...) and the
@@ -174,11 +174,13 @@ eco_status_t eco_plan_destroy(eco_plan_t *plan);
 
 /*
  * eco_step — one ECO step (Alg. 1 with Alg. 3 or Alg. 2) over every tensor of the plan.
- * Asynchronous on `stream`; allocates nothing.  Launches per storage format present: one kernel over the full
- * 512-element tiles of block-scaled tensors, one over their ragged tails if any, one per workgroup size for wide
- * groups, and four for tensors with a single scale (abs-max pass into the plan's scratch, its reduction, apply
- * pass, scale write); a plan with more work than one launch can hold (2^32 threads: about 2^35 elements) has these
- * launched in pieces.  Steps of one plan that use that scratch must not overlap each other on different streams.
+ * Asynchronous on `stream`; allocates nothing.  Launches per quantized format present: one kernel over the full
+ * 512-element tiles of block-scaled tensors, one per workgroup size for wide groups, and four for tensors with a single
+ * scale (abs-max pass into the plan's scratch, its reduction, apply pass, scale write); ragged tails, groups of up to
+ * 512 elements that are no power of two and unquantized tensors ride in one of the first two kinds (large sets of
+ * unquantized tensors get a launch of their own), and up to 44 tensors of together 8 million elements are one launch
+ * beside the tensor-wise ones.  A plan with more work than one launch can hold (2^32 threads: about 2^35 elements) has
+ * these launched in pieces.  Steps of one plan that use that scratch must not overlap each other on different streams.
  * hp->block_size, state_dtype, scale_dtype, opt and mode must equal the plan's, and the device that was current at
  * eco_plan_create must be current (ECO_EINVAL otherwise).
  */
@@ -196,7 +198,9 @@ eco_status_t eco_step_tensors(const eco_tensor_t *tensors, size_t n, const eco_h
  * bit; asynchronous on `stream` (it does not wait for it, unlike eco_step_tensors).  Calls no hipMalloc, hipFree,
  * host-to-device copy or other allocating routine: the tensor descriptors, the launch tables and the abs-max
  * scratch of tensors with a single scale live in one static device array of 8.7 MB (8 732 672 bytes) per GPU,
- * held until the process ends, and the tables are written by a kernel from descriptors passed as kernel arguments.
+ * held until the process ends, and the tables are written by a kernel from descriptors passed as kernel arguments (a
+ * list of up to 44 tensors and 8 million elements without tensor-wise scales needs no tables: its descriptors are
+ * arguments of the step kernel itself).
  * Limits: at most 4096 tensors per call and at most 2^20 launch-table entries in total (one per 512 elements of a
  * tensor, rounded up, plus one per tensor with a ragged tail or a single scale; one per scale group for groups
  * wider than 512 elements) -- about 5.3e8 elements per call; beyond that ECO_EUNSUPPORTED, before anything is
@@ -279,8 +283,8 @@ eco_status_t eco_arith_selftest(int32_t kind, float numerator, uint32_t bits_lo,
 eco_status_t eco_step_constants(const eco_hparams_t *hp, eco_constants_t *out);
 
 /* Launch tuning, host only; never changes results.
- *   option 0: cap on the step kernel's grid, in workgroups per compute unit; the kernel then loops over
- *             tiles (0 = library default: one workgroup per 512-element tile, no cap)
+ *   option 0: cap on the step kernel's grid, in workgroups per compute unit; the tiles are then launched in
+ *             pieces (0 = library default: one workgroup per 512-element tile, no cap)
  *   option 1: bytes of dynamic LDS requested per workgroup of the step kernel (-1 = library default).
  *             The kernel never touches it; the request only caps resident workgroups per compute unit.
  *   option 2: the same per wave of the wide-group and tensor-wise kernels (-1 = library default)

@@ -2,12 +2,13 @@
 // constants, launch plans (device tables mapping tiles to tensors) and kernel dispatch.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -110,18 +111,31 @@ void derive_constants(const eco_hparams_t *hp, eco_constants_t *c) {
   }
 }
 
-struct Group {                           // the tensors of one storage format
-  std::vector<eco::TensorDesc> descs;
-  std::vector<uint32_t> tile_tensor;     // block-scaled: one entry per full tile
-  std::vector<uint32_t> ragged_tensor;   // block-scaled: tensors whose last tile is partial
-  std::vector<uint32_t> wide[eco::MAX_WIDE_WAVES + 1];   // wide groups, by waves per group: one entry per group
-  std::vector<uint32_t> tw_tile_tensor;  // tensor-wise: one entry per tile (full or partial)
+struct Lists {                           // the launch lists of one storage format
+  std::vector<uint32_t> tile;            // block-scaled: one entry per full tile
+  std::vector<uint32_t> extra;           // one-wave units that ride along (ragged tails, short rows, unquantized tensors)
+  std::vector<uint32_t> wide[eco::MAX_WIDE_WAVES + 1];   // wide groups, by waves per unit: one entry per unit
+  std::vector<uint32_t> tw_tile;         // tensor-wise: one entry per tile (full or partial)
   std::vector<uint32_t> tw_tensor;       // tensor-wise: the tensors
-  eco::TensorDesc *d_descs = nullptr;
-  uint32_t *d_tables = nullptr;          // all the lists above, back to back, then the abs-max slots
-  uint32_t *d_tile_max = nullptr;        // scratch of the tensor-wise passes: one entry per tensor-wise tile
-  size_t off_ragged = 0, off_wide[eco::MAX_WIDE_WAVES + 1] = {0}, off_tw_tiles = 0, off_tw_tensor = 0, off_slots = 0;
+  size_t off_tile = 0, off_extra = 0, off_wide[eco::MAX_WIDE_WAVES + 1] = {0}, off_tw_tile = 0, off_tw_tensor = 0, off_slots = 0,
+         off_tile_max = 0;
+  uint64_t tensors = 0;
+  std::unique_ptr<eco::SmallArgs> small; // all but the tensor-wise tensors as one launch, where that is the better way
+  unsigned small_wgs = 0, small_waves = 1;
+  std::vector<uint32_t> &list(int l) {
+    return l == eco::LIST_TILE ? tile : l == eco::LIST_EXTRA ? extra : l == eco::LIST_TW_TILES ? tw_tile : wide[l - eco::LIST_WIDE1 + 1];
+  }
 };
+
+// Unquantized tensors of up to this many 512-element tiles together are one-wave units in the launch of a quantized
+// format; more of them get the kernel that is compiled for them alone.  A launch costs 5-6 us, what 20 MB take; beyond a
+// few thousand tiles the unguarded accesses of that kernel are worth more.
+constexpr uint64_t RIDE_ALONG_TILES = 8192;
+constexpr uint64_t RIDE_ALONG_WAVES = 65536;   // largest wide-group launch that takes them, see home_of_extra
+
+// A step of at most SMALL_TENSORS tensors and this many elements that would be several launches is one launch of the
+// short-list kernel instead.
+constexpr uint64_t SMALL_ELEMENTS = 1ull << 23;
 
 int num_compute_units() {
   int dev = 0, cus = 0;
@@ -150,19 +164,13 @@ uint32_t lds_for_waves(int waves, int granule) {
   return waves > 0 ? static_cast<uint32_t>(163840 / waves / granule * granule) : 0u;
 }
 
-// Default: one workgroup per tile.  The hardware dispatcher then hands out tiles in address order,
-// which keeps the set of DRAM pages in flight compact; grid-stride loops over a resident grid
-// measured 10-15 % slower on MI355X.  Option 0 overrides with a resident grid.
-unsigned grid_for(uint64_t tiles, int cus) {
-  uint64_t g = tiles;
+// Most threads of a full-tile launch.  Default: no limit but the runtime's, one workgroup per tile.  The hardware
+// dispatcher then hands out tiles in address order, which keeps the set of DRAM pages in flight compact; grid-stride
+// loops over a resident grid measured 10-15 % slower on MI355X.  Option 0 caps it to a resident grid, in pieces.
+uint64_t tile_threads(uint64_t most, int cus) {
   const int64_t wgs_per_cu = g_wgs_per_cu.load(std::memory_order_relaxed);
-  if (wgs_per_cu > 0) {
-    const uint64_t cap = static_cast<uint64_t>(cus) * static_cast<uint64_t>(wgs_per_cu);
-    if (g > cap) g = cap;
-  }
-  if (g > 0x7FFFFFFFull) g = 0x7FFFFFFFull;
-  if (g == 0) g = 1;
-  return static_cast<unsigned>(g);
+  if (wgs_per_cu <= 0) return most;
+  return std::min<uint64_t>(most, static_cast<uint64_t>(cus) * static_cast<uint64_t>(wgs_per_cu) * eco::WG_THREADS);
 }
 
 // Validation of one tensor descriptor against the layout part of the hyper-parameters; on success *gsz is the
@@ -212,7 +220,8 @@ eco::KernelVariant variant_for(const eco_hparams_t *hp, int f) {
 }
 
 // The scalar part of the kernel arguments: step constants, random-stream key, launch options.
-void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, eco::StepArgs *a) {
+void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, eco::StepLaunch *sl) {
+  eco::StepArgs *a = &sl->args;
   a->b1 = c.b1; a->omb1 = c.omb1; a->b2 = c.b2; a->omb2 = c.omb2; a->rbc2 = c.rbc2; a->c1 = c.c1; a->eps = c.eps;
   a->kappa = c.kappa; a->lr = c.lr; a->alpha = c.alpha; a->wd = c.wd; a->inv_lr = c.inv_lr; a->inv_lr_beta = c.inv_lr_beta;
   a->seed_lo = static_cast<uint32_t>(hp->seed);
@@ -220,15 +229,15 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   a->step_lo = static_cast<uint32_t>(hp->step);
   a->div_mid = (c.c1 >= 0x1p-40f && c.c1 <= 0x1p40f && c.eps <= 1.0f) ? 1u : 0u;
   const int64_t opt_threads = g_max_launch_threads.load(std::memory_order_relaxed);
-  a->max_launch_threads = opt_threads > 0 ? static_cast<uint64_t>(opt_threads) : eco::MAX_LAUNCH_THREADS;
+  sl->max_launch_threads = opt_threads > 0 ? static_cast<uint64_t>(opt_threads) : eco::MAX_LAUNCH_THREADS;
   a->unit_base = 0;
   const int waves = default_waves(kv);
   const int waves_wide = kv.algo == eco::ALGO_ADAM ? waves : 0;     // measured for Adam only; SGDM ran best uncapped
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
-  a->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(waves, 512);
-  a->lds_bytes_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves_wide, 256);
-  a->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves_wide ? waves_wide + 4 : 0, 256);
+  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(waves, 512);
+  sl->lds_bytes_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves_wide, 256);
+  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves_wide ? waves_wide + 4 : 0, 256);
 }
 
 
@@ -279,7 +288,7 @@ struct BuildArgs {
   eco::TensorDesc desc[BUILD_CHUNK];
   uint32_t list_pos[BUILD_CHUNK];    // index into the tables of the first of this tensor's `units` entries
   uint32_t units[BUILD_CHUNK];       // entries (tiles or groups) the tensor adds to its launch list
-  uint32_t extra_pos[BUILD_CHUNK];   // index of one more entry (ragged-tail list, tensor-wise tensor list), or NO_ENTRY
+  uint32_t extra_pos[BUILD_CHUNK];   // index of one more entry (a ragged tail, tensor-wise tensor list), or NO_ENTRY
   uint32_t first_index;              // descriptor index of desc[0]
   uint32_t count;
   unsigned char *scratch;
@@ -304,31 +313,6 @@ __global__ __launch_bounds__(BUILD_THREADS) void eco_noalloc_build_kernel(const 
     tables[pos + i] = index;
 }
 
-// Launch lists of one storage format, in the order they are laid out in the tables.
-enum : int { L_TILE = 0, L_RAGGED = 1, L_WIDE1 = 2, L_TW_TILES = L_WIDE1 + eco::MAX_WIDE_WAVES, L_TW_TENSORS, L_COUNT };
-
-struct ListOf { int list; int extra; uint64_t units; uint64_t group; };
-// Which lists a tensor enters, and with how many entries (mirrors eco_plan_create).
-ListOf lists_of(const eco_tensor_t &t, uint64_t gsz, int cls) {
-  ListOf r = {L_TILE, -1, 0, 0};
-  if (cls == eco::GROUP_BLOCK) {
-    r.units = t.numel / eco::TILE_ELEMS;
-    if (t.numel % eco::TILE_ELEMS) r.extra = L_RAGGED;
-    r.group = gsz;
-  } else if (cls == eco::GROUP_WIDE) {
-    r.group = gsz < t.numel ? gsz : t.numel;
-    const eco::WideGeometry wg = eco::wide_geometry(t.numel, r.group);
-    r.units = wg.units;
-    r.list = L_WIDE1 + static_cast<int>(wg.waves) - 1;
-  } else {
-    r.group = t.numel;
-    r.units = (t.numel + eco::TILE_ELEMS - 1) / eco::TILE_ELEMS;
-    r.list = L_TW_TILES;
-    r.extra = L_TW_TENSORS;
-  }
-  return r;
-}
-
 }  // namespace noalloc
 
 }  // namespace
@@ -338,8 +322,76 @@ struct eco_plan {
   int32_t state_dtype = 0, scale_dtype = 0, opt = 0, mode = 0;
   int cus = 256;
   int device = 0;    // the device that was current when the plan was created (its tables live there)
-  Group groups[4];   // indexed by eco_format_t
+  Lists lists[4];    // indexed by eco_format_t; unquantized tensors may be in a quantized format's lists
+  eco::TensorDesc *d_descs = nullptr;
+  uint32_t *d_tables = nullptr;          // all lists, back to back, then the abs-max slots and the scratch of the tensor-wise passes
 };
+
+namespace {
+
+// The descriptor of a tensor whose units go to a list from number `first_unit` on.
+eco::TensorDesc describe(const eco_tensor_t &t, const eco_hparams_t *layout, const eco::Placement &p, uint64_t first_unit) {
+  eco::TensorDesc d;
+  std::memset(&d, 0, sizeof d);
+  d.w = t.weights; d.s = t.scales; d.g = t.grad; d.m = t.m; d.v = t.v; d.aux = t.aux;
+  d.numel = t.numel;
+  d.tensor_id = t.tensor_id;
+  const bool plain = p.kind == eco::UNIT_PLAIN_BF16 || p.kind == eco::UNIT_PLAIN_FP32;
+  d.group_size = plain ? layout->block_size : p.group;
+  if (p.kind == eco::UNIT_TILES && p.list != eco::LIST_TW_TILES) d.bs_shift = static_cast<uint16_t>(eco::log2_exact(p.group));
+  d.kind = static_cast<uint16_t>(p.tail ? eco::UNIT_TAIL : p.kind);
+  d.slot = p.rows;
+  d.first_unit = static_cast<uint32_t>(first_unit);
+  return d;
+}
+
+// Which format's launches the unquantized tensors ride in: their own, or a quantized format's of the same step.
+int home_of_plain(const uint64_t (&tensors)[4], const uint64_t (&entries)[4]) {
+  const uint64_t plain = entries[eco::FMT_BF16_PLAIN] + entries[eco::FMT_FP32_ID];
+  if (plain > RIDE_ALONG_TILES) return -1;
+  if (tensors[eco::FMT_FP8]) return eco::FMT_FP8;
+  if (tensors[eco::FMT_INT4]) return eco::FMT_INT4;
+  return -1;
+}
+
+// The short-list arguments of one format's tensors; false if they do not fit one launch of it.
+struct SmallItem { const eco_tensor_t *t; eco::Placement p; };
+bool make_small(const std::vector<SmallItem> &items, const eco_hparams_t *layout, eco::SmallArgs *sa, unsigned *wgs, unsigned *waves) {
+  if (items.empty() || items.size() > static_cast<size_t>(eco::SMALL_TENSORS)) return false;
+  unsigned nw = 1;
+  for (const SmallItem &it : items)
+    if (it.p.kind == eco::UNIT_WIDE) nw = std::max(nw, static_cast<unsigned>(it.p.list - eco::LIST_WIDE1 + 1));
+  uint64_t wg = 0;
+  for (size_t i = 0; i < items.size(); ++i) {
+    eco::Placement p = items[i].p;
+    const uint64_t units = p.units + (p.tail ? 1 : 0);
+    p.tail = false;                                     // whole and partial tiles in one list here
+    sa->first_wg[i] = static_cast<uint32_t>(wg);
+    sa->desc[i] = describe(*items[i].t, layout, p, units);
+    const unsigned per_wg = p.kind == eco::UNIT_WIDE ? nw / static_cast<unsigned>(p.list - eco::LIST_WIDE1 + 1) : nw;
+    wg += (units + per_wg - 1) / per_wg;
+  }
+  sa->num = static_cast<uint32_t>(items.size());
+  *wgs = static_cast<unsigned>(wg);
+  *waves = nw;
+  return true;
+}
+
+// Which launch the one-wave units of a format ride in: the full-tile one (0) where there is one, they are many or every
+// wide-group launch is long, else the wide-group one with the most units.  Riding in a wide-group launch costs 3.6 % of
+// it, a launch of their own 5 us: the two meet at about 35 million elements.
+int home_of_extra(uint64_t tiles, uint64_t extra, const uint32_t (&num_wide)[eco::MAX_WIDE_WAVES + 1]) {
+  int best = 0;
+  uint64_t most = 0;
+  if (tiles || extra > RIDE_ALONG_TILES) return 0;
+  for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
+    const uint64_t waves = static_cast<uint64_t>(num_wide[nw]) * nw;
+    if (waves > most && waves <= RIDE_ALONG_WAVES) { best = nw; most = waves; }
+  }
+  return best;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -394,21 +446,16 @@ eco_status_t eco_step_constants(const eco_hparams_t *hp, eco_constants_t *out) {
 
 eco_status_t eco_plan_destroy(eco_plan_t *plan) {
   if (!plan) return ECO_OK;
-  bool any = false;
-  for (Group &g : plan->groups) any = any || g.d_descs || g.d_tables;
   eco_status_t st = ECO_OK;
-  if (any) {
+  if (plan->d_descs || plan->d_tables) {
     // steps may still be running on the plan's device: wait for that device, whichever is current
     int cur = -1;
     const bool have_cur = hipGetDevice(&cur) == hipSuccess;
     if (have_cur && cur != plan->device) (void)hipSetDevice(plan->device);
     const hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) st = fail_hip(e, "hipDeviceSynchronize");
-    for (Group &g : plan->groups) {
-      if (g.d_descs) (void)hipFree(g.d_descs);
-      if (g.d_tables) (void)hipFree(g.d_tables);
-      if (g.d_tile_max) (void)hipFree(g.d_tile_max);
-    }
+    if (plan->d_descs) (void)hipFree(plan->d_descs);
+    if (plan->d_tables) (void)hipFree(plan->d_tables);
     if (have_cur && cur != plan->device) (void)hipSetDevice(cur);
   }
   delete plan;
@@ -430,93 +477,114 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
   plan->opt = layout->opt;
   plan->mode = layout->mode;
 
+  std::vector<eco::TensorDesc> descs;
+  std::vector<uint32_t> host;
   try {
-    for (size_t i = 0; i < n; ++i) {
+    // validation and placement; how much there is of every list
+    std::vector<eco::Placement> place(n);
+    uint64_t tensors_of[4] = {0}, entries_of[4] = {0}, list_entries[4][eco::LIST_COUNT] = {{0}};
+    for (size_t i = 0; i < n && st == ECO_OK; ++i) {
       const eco_tensor_t &t = tensors[i];
       uint64_t gsz = 0;
       int cls = 0;
       st = check_tensor(t, i, layout, &gsz, &cls);
       if (st != ECO_OK) break;
       const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
-      Group &g = plan->groups[t.fmt];
-      eco::TensorDesc d;
-      std::memset(&d, 0, sizeof d);
-      d.w = t.weights; d.s = t.scales; d.g = t.grad; d.m = t.m; d.v = t.v; d.aux = t.aux;
-      d.numel = t.numel;
-      d.tensor_id = t.tensor_id;
-      const uint32_t idx = static_cast<uint32_t>(g.descs.size());
-      uint64_t units = 0;                 // tiles or groups this tensor adds to its launch list
-      std::vector<uint32_t> *list = nullptr;
-      if (cls == eco::GROUP_BLOCK) {
-        d.group_size = quantized ? gsz : layout->block_size;
-        d.bs_shift = static_cast<uint32_t>(eco::log2_exact(d.group_size));
-        units = t.numel / eco::TILE_ELEMS;              // full tiles
-        list = &g.tile_tensor;
-        if (t.numel % eco::TILE_ELEMS) g.ragged_tensor.push_back(idx);
-      } else if (cls == eco::GROUP_WIDE) {
-        d.group_size = gsz < t.numel ? gsz : t.numel;
-        const eco::WideGeometry wg = eco::wide_geometry(t.numel, d.group_size);
-        d.slot = wg.rows;
-        units = wg.units;
-        list = &g.wide[wg.waves];
-      } else {
-        d.group_size = t.numel;
-        d.slot = static_cast<uint32_t>(g.tw_tensor.size());
-        units = (t.numel + eco::TILE_ELEMS - 1) / eco::TILE_ELEMS;
-        list = &g.tw_tile_tensor;
-        g.tw_tensor.push_back(idx);
-      }
-      if (list->size() + units > 0x7FFFFFF0ull) { st = fail(ECO_EUNSUPPORTED, "plan: more than 2^31 tiles in one launch"); break; }
-      d.first_unit = static_cast<uint32_t>(list->size());
-      list->insert(list->end(), static_cast<size_t>(units), idx);
-      g.descs.push_back(d);
+      place[i] = eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt);
+      tensors_of[t.fmt] += 1;
+      entries_of[t.fmt] += place[i].entries;
+      uint64_t &in_list = list_entries[t.fmt][place[i].list];
+      in_list += place[i].entries;
+      if (in_list > 0x7FFFFFF0ull) st = fail(ECO_EUNSUPPORTED, "plan: more than 2^31 tiles in one launch");
     }
-  } catch (const std::bad_alloc &) {
-    st = fail(ECO_ENOMEM, "plan: host allocation failed");
-  }
-  if (st != ECO_OK) { delete plan; return st; }
+    if (st != ECO_OK) { delete plan; return st; }
+    const int plain_home = home_of_plain(tensors_of, entries_of);
 
-  {
-    const hipError_t e = hipGetDevice(&plan->device);
-    if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
-  }
-  plan->cus = num_compute_units();
-  for (Group &g : plan->groups) {
-    if (g.descs.empty()) continue;
-    // one device buffer: [full tiles | ragged | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots]
-    std::vector<uint32_t> host;
-    try {
-      host = g.tile_tensor;
-      g.off_ragged = host.size();
-      host.insert(host.end(), g.ragged_tensor.begin(), g.ragged_tensor.end());
-      for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
-        g.off_wide[nw] = host.size();
-        host.insert(host.end(), g.wide[nw].begin(), g.wide[nw].end());
+    std::vector<SmallItem> items[4];
+    uint64_t elements[4] = {0};
+    descs.reserve(n);
+    for (size_t i = 0; i < n; ++i) {
+      const eco_tensor_t &t = tensors[i];
+      const eco::Placement &p = place[i];
+      const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
+      const int f = quantized || plain_home < 0 ? t.fmt : plain_home;
+      Lists &g = plan->lists[f];
+      const uint32_t idx = static_cast<uint32_t>(i);
+      std::vector<uint32_t> &list = g.list(p.list);
+      eco::TensorDesc d = describe(t, layout, p, list.size());
+      if (p.list == eco::LIST_TW_TILES) {
+        d.slot = static_cast<uint32_t>(g.tw_tensor.size());
+        g.tw_tensor.push_back(idx);
+      } else {
+        elements[f] += t.numel;
+        if (items[f].size() <= static_cast<size_t>(eco::SMALL_TENSORS)) items[f].push_back(SmallItem{&t, p});
       }
-      g.off_tw_tiles = host.size();
-      host.insert(host.end(), g.tw_tile_tensor.begin(), g.tw_tile_tensor.end());
-      g.off_tw_tensor = host.size();
-      host.insert(host.end(), g.tw_tensor.begin(), g.tw_tensor.end());
+      list.insert(list.end(), static_cast<size_t>(p.units), idx);
+      if (p.tail) g.extra.push_back(idx);
+      g.tensors += 1;
+      descs.push_back(d);
+    }
+    for (int f = 0; f < 2; ++f) {
+      Lists &g = plan->lists[f];
+      int launches = g.tile.empty() ? 0 : 1;
+      for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) launches += !g.wide[nw].empty();
+      if (launches < 2 || elements[f] > SMALL_ELEMENTS) continue;
+      std::unique_ptr<eco::SmallArgs> sa(new eco::SmallArgs());
+      if (make_small(items[f], layout, sa.get(), &g.small_wgs, &g.small_waves)) g.small = std::move(sa);
+    }
+
+    // one device buffer: per format [full tiles | one-wave units | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots | scratch]
+    for (Lists &g : plan->lists) {
+      const auto add = [&host](const std::vector<uint32_t> &l, size_t *off) {
+        *off = host.size();
+        host.insert(host.end(), l.begin(), l.end());
+      };
+      if (!g.tensors) continue;
+      add(g.tile, &g.off_tile);
+      add(g.extra, &g.off_extra);
+      for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) add(g.wide[nw], &g.off_wide[nw]);
+      add(g.tw_tile, &g.off_tw_tile);
+      add(g.tw_tensor, &g.off_tw_tensor);
       g.off_slots = host.size();
       host.insert(host.end(), g.tw_tensor.size() + 1, 0u);      // abs-max slots start at zero
-    } catch (const std::bad_alloc &) {
-      (void)eco_plan_destroy(plan);
-      return fail(ECO_ENOMEM, "plan: host allocation failed");
+      g.off_tile_max = host.size();
+      host.insert(host.end(), g.tw_tile.size(), 0u);
     }
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(&g.d_descs), g.descs.size() * sizeof(eco::TensorDesc));
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&g.d_tables), host.size() * sizeof(uint32_t));
-    if (e == hipSuccess && !g.tw_tile_tensor.empty())
-      e = hipMalloc(reinterpret_cast<void **>(&g.d_tile_max), g.tw_tile_tensor.size() * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMemcpy(g.d_descs, g.descs.data(), g.descs.size() * sizeof(eco::TensorDesc), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(g.d_tables, host.data(), host.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      st = (e == hipErrorOutOfMemory) ? fail(ECO_ENOMEM, "plan: device allocation failed") : fail_hip(e, "plan upload");
-      (void)eco_plan_destroy(plan);
-      return st;
-    }
+  } catch (const std::bad_alloc &) {
+    delete plan;
+    return fail(ECO_ENOMEM, "plan: host allocation failed");
+  }
+
+  hipError_t e = hipGetDevice(&plan->device);
+  if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
+  plan->cus = num_compute_units();
+  e = hipMalloc(reinterpret_cast<void **>(&plan->d_descs), descs.size() * sizeof(eco::TensorDesc));
+  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&plan->d_tables), host.size() * sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMemcpy(plan->d_descs, descs.data(), descs.size() * sizeof(eco::TensorDesc), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(plan->d_tables, host.data(), host.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    st = (e == hipErrorOutOfMemory) ? fail(ECO_ENOMEM, "plan: device allocation failed") : fail_hip(e, "plan upload");
+    (void)eco_plan_destroy(plan);
+    return st;
   }
   *out = plan;
   return ECO_OK;
+}
+
+// Launches the step of one format's lists (sl: everything but the scalars).
+static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, eco::StepLaunch *sl,
+                                  eco::SmallArgs *small, hipStream_t stream) {
+  const eco::KernelVariant kv = variant_for(hp, f);
+  fill_step_scalars(hp, c, kv, sl);
+  sl->extra_in = home_of_extra(sl->args.num_tiles, sl->args.num_extra, sl->num_wide);
+  sl->max_tile_threads = tile_threads(sl->max_launch_threads, cus);
+  // the limit on a launch's threads holds for the one launch of the short-list kernel too (without tables it is the only way)
+  if (small && (!sl->args.tensors || static_cast<uint64_t>(sl->small_wgs) * sl->small_waves * 64 <= sl->max_launch_threads)) {
+    small->step = sl->args;
+    sl->small = small;
+  }
+  const hipError_t e = eco::launch_step(kv, *sl, stream);
+  return e == hipSuccess ? ECO_OK : fail_hip(e, "step kernel launch");
 }
 
 eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
@@ -534,31 +602,32 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
   eco_constants_t c;
   derive_constants(hp, &c);
   for (int f = 0; f < 4; ++f) {
-    Group &g = plan->groups[f];
-    if (g.descs.empty()) continue;
-    if (!g.d_descs || !g.d_tables) return fail(ECO_EINVAL, "step: the plan's device tables are missing");
-    eco::StepArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.tensors = g.d_descs;
-    a.tile_tensor = g.d_tables;
-    a.ragged_tensor = g.d_tables + g.off_ragged;
-    a.num_tiles = static_cast<uint32_t>(g.tile_tensor.size());
-    a.num_ragged = static_cast<uint32_t>(g.ragged_tensor.size());
-    a.wide_base = g.d_tables;
+    Lists &g = plan->lists[f];
+    if (!g.tensors) continue;
+    if (!plan->d_descs || !plan->d_tables) return fail(ECO_EINVAL, "step: the plan's device tables are missing");
+    eco::StepLaunch sl;
+    std::memset(&sl, 0, sizeof sl);
+    eco::StepArgs &a = sl.args;
+    a.tensors = plan->d_descs;
+    a.tile_tensor = plan->d_tables + g.off_tile;
+    a.extra_tensor = plan->d_tables + g.off_extra;
+    a.num_tiles = static_cast<uint32_t>(g.tile.size());
+    a.num_extra = static_cast<uint32_t>(g.extra.size());
+    sl.wide_base = plan->d_tables;
     for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
-      a.wide_offset[nw] = static_cast<uint32_t>(g.off_wide[nw]);
-      a.num_wide[nw] = static_cast<uint32_t>(g.wide[nw].size());
+      sl.wide_offset[nw] = static_cast<uint32_t>(g.off_wide[nw]);
+      sl.num_wide[nw] = static_cast<uint32_t>(g.wide[nw].size());
     }
-    a.tw_tile_tensor = g.d_tables + g.off_tw_tiles;
-    a.tw_tensor = g.d_tables + g.off_tw_tensor;
-    a.slots = g.d_tables + g.off_slots;
-    a.tile_max = g.d_tile_max;
-    a.num_tw_tiles = static_cast<uint32_t>(g.tw_tile_tensor.size());
+    a.tw_tile_tensor = plan->d_tables + g.off_tw_tile;
+    a.tw_tensor = plan->d_tables + g.off_tw_tensor;
+    a.slots = plan->d_tables + g.off_slots;
+    a.tile_max = plan->d_tables + g.off_tile_max;
+    a.num_tw_tiles = static_cast<uint32_t>(g.tw_tile.size());
     a.num_tw_tensors = static_cast<uint32_t>(g.tw_tensor.size());
-    const eco::KernelVariant kv = variant_for(hp, f);
-    fill_step_scalars(hp, c, kv, &a);
-    const hipError_t e = eco::launch_step(kv, a, grid_for(a.num_tiles, plan->cus), static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return fail_hip(e, "step kernel launch");
+    eco::SmallArgs small;                  // a copy: steps of one plan may be enqueued by different calls
+    if (g.small) { small = *g.small; sl.small_wgs = g.small_wgs; sl.small_waves = g.small_waves; }
+    st = launch_format(hp, c, f, plan->cus, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
+    if (st != ECO_OK) return st;
   }
   return ECO_OK;
 }
@@ -587,29 +656,91 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   if (n > MAX_TENSORS)
     return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: %zu tensors, the static scratch holds %u (use a plan)", n, MAX_TENSORS);
 
-  // pass 1: validate, count the entries of every launch list
-  uint64_t count[4][L_COUNT] = {{0}};
-  uint64_t total = 0;
-  for (size_t i = 0; i < n; ++i) {
+  // pass 1: validate, place, count the entries of every launch list
+  constexpr int L_TW_TENSORS = eco::LIST_COUNT, L_COUNT = eco::LIST_COUNT + 1;
+  uint64_t count[4][L_COUNT] = {{0}}, tensors_of[4] = {0}, entries_of[4] = {0};
+  uint64_t total = 0, elements = 0;
+  const auto place = [&](size_t i, eco::Placement *p) {
     uint64_t gsz = 0;
     int cls = 0;
-    st = check_tensor(tensors[i], i, hp, &gsz, &cls);
+    const eco_status_t s = check_tensor(tensors[i], i, hp, &gsz, &cls);
+    const int32_t fmt = tensors[i].fmt;
+    if (s == ECO_OK) *p = eco::place_tensor(tensors[i].numel, gsz, cls, fmt == ECO_FMT_FP8_E4M3 || fmt == ECO_FMT_INT4, fmt);
+    return s;
+  };
+  bool tensorwise = false;
+  for (size_t i = 0; i < n; ++i) {
+    eco::Placement p;
+    st = place(i, &p);
     if (st != ECO_OK) return st;
-    const ListOf lo = lists_of(tensors[i], gsz, cls);
-    if (lo.units > MAX_UNITS) return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: tensor %zu alone exceeds the static scratch", i);
-    count[tensors[i].fmt][lo.list] += lo.units;
-    if (lo.extra >= 0) count[tensors[i].fmt][lo.extra] += 1;
-    total += lo.units + (lo.extra >= 0 ? 1 : 0);
+    if (p.entries > MAX_UNITS) return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: tensor %zu alone exceeds the static scratch", i);
+    tensors_of[tensors[i].fmt] += 1;
+    entries_of[tensors[i].fmt] += p.entries;
+    elements += tensors[i].numel;
+    tensorwise = tensorwise || p.list == eco::LIST_TW_TILES;
+    total += p.entries;
     if (total > MAX_UNITS)
       return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: more than %u launch-table entries (512-element tiles, or scale "
                   "groups wider than 512): the static scratch does not hold them (use a plan)", MAX_UNITS);
+  }
+  const int plain_home = home_of_plain(tensors_of, entries_of);
+  const auto format_of = [&](size_t i) {
+    const int32_t fmt = tensors[i].fmt;
+    return fmt == ECO_FMT_FP8_E4M3 || fmt == ECO_FMT_INT4 || plain_home < 0 ? fmt : plain_home;
+  };
+  (void)hipGetLastError();
+  hipStream_t hs = static_cast<hipStream_t>(stream);
+  eco_constants_t c;
+  derive_constants(hp, &c);
+  const int cus = num_compute_units();
+
+  // a short list of small tensors needs no tables: its descriptors go as kernel arguments, one launch per quantized format
+  if (!tensorwise && elements <= SMALL_ELEMENTS && (plain_home >= 0 || !(tensors_of[2] + tensors_of[3])) && tensors_of[0] + tensors_of[1]) {
+    eco::SmallArgs small[2];
+    eco::StepLaunch sl[2];
+    bool fits = true;
+    std::memset(sl, 0, sizeof sl);
+    try {
+      std::vector<SmallItem> items[2];
+      for (size_t i = 0; i < n && fits; ++i) {
+        eco::Placement p;
+        (void)place(i, &p);
+        items[format_of(i)].push_back(SmallItem{&tensors[i], p});
+        fits = items[format_of(i)].size() <= static_cast<size_t>(eco::SMALL_TENSORS);
+      }
+      for (int f = 0; f < 2 && fits; ++f) {
+        if (items[f].empty()) continue;
+        fits = make_small(items[f], hp, &small[f], &sl[f].small_wgs, &sl[f].small_waves);
+        const int64_t limit = g_max_launch_threads.load(std::memory_order_relaxed);
+        if (limit > 0 && static_cast<uint64_t>(sl[f].small_wgs) * sl[f].small_waves * 64 > static_cast<uint64_t>(limit)) fits = false;
+      }
+    } catch (const std::bad_alloc &) {
+      return fail(ECO_ENOMEM, "step: host allocation failed");
+    }
+    if (fits) {
+      for (int f = 0; f < 2; ++f) {
+        if (!sl[f].small_wgs) continue;
+        st = launch_format(hp, c, f, cus, &sl[f], &small[f], hs);
+        if (st != ECO_OK) return st;
+      }
+      return ECO_OK;
+    }
+  }
+
+  for (size_t i = 0; i < n; ++i) {
+    eco::Placement p;
+    (void)place(i, &p);
+    const int f = format_of(i);
+    count[f][p.list] += p.units;
+    if (p.tail) count[f][eco::LIST_EXTRA] += 1;
+    if (p.list == eco::LIST_TW_TILES) count[f][L_TW_TENSORS] += 1;
   }
   uint32_t start[4][L_COUNT], tw_tile_start[4], tw_tensor_start[4];
   {
     uint32_t pos = 0, tw_tiles = 0, tw_tensors = 0;
     for (int f = 0; f < 4; ++f) {
       for (int l = 0; l < L_COUNT; ++l) { start[f][l] = pos; pos += static_cast<uint32_t>(count[f][l]); }
-      tw_tile_start[f] = tw_tiles; tw_tiles += static_cast<uint32_t>(count[f][L_TW_TILES]);
+      tw_tile_start[f] = tw_tiles; tw_tiles += static_cast<uint32_t>(count[f][eco::LIST_TW_TILES]);
       tw_tensor_start[f] = tw_tensors; tw_tensors += static_cast<uint32_t>(count[f][L_TW_TENSORS]);
     }
   }
@@ -617,8 +748,6 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   unsigned char *sp = nullptr;
   st = scratch_for_current_device(&sp);
   if (st != ECO_OK) return st;
-  (void)hipGetLastError();
-  hipStream_t hs = static_cast<hipStream_t>(stream);
 
   // pass 2: descriptors and tables, BUILD_CHUNK tensors per launch of the builder
   uint32_t fill[4][L_COUNT] = {{0}};
@@ -626,30 +755,21 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   std::memset(&ba, 0, sizeof ba);
   ba.scratch = sp;
   for (size_t i = 0; i < n; ++i) {
-    const eco_tensor_t &t = tensors[i];
-    uint64_t gsz = 0;
-    int cls = 0;
-    (void)check_tensor(t, i, hp, &gsz, &cls);
-    const ListOf lo = lists_of(t, gsz, cls);
+    eco::Placement p;
+    (void)place(i, &p);
+    const int f = format_of(i);
     const uint32_t k = ba.count++;
     if (k == 0) ba.first_index = static_cast<uint32_t>(i);
     eco::TensorDesc &d = ba.desc[k];
-    std::memset(&d, 0, sizeof d);
-    d.w = t.weights; d.s = t.scales; d.g = t.grad; d.m = t.m; d.v = t.v; d.aux = t.aux;
-    d.numel = t.numel;
-    d.tensor_id = t.tensor_id;
-    const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
-    d.group_size = (cls == eco::GROUP_BLOCK && !quantized) ? hp->block_size : lo.group;
-    if (cls == eco::GROUP_BLOCK) d.bs_shift = static_cast<uint32_t>(eco::log2_exact(d.group_size));
-    if (cls == eco::GROUP_WIDE) d.slot = eco::wide_geometry(t.numel, lo.group).rows;
-    d.first_unit = fill[t.fmt][lo.list];
-    ba.list_pos[k] = start[t.fmt][lo.list] + fill[t.fmt][lo.list];
-    ba.units[k] = static_cast<uint32_t>(lo.units);
-    fill[t.fmt][lo.list] += static_cast<uint32_t>(lo.units);
+    d = describe(tensors[i], hp, p, fill[f][p.list]);
+    ba.list_pos[k] = start[f][p.list] + fill[f][p.list];
+    ba.units[k] = static_cast<uint32_t>(p.units);
+    fill[f][p.list] += static_cast<uint32_t>(p.units);
     ba.extra_pos[k] = NO_ENTRY;
-    if (lo.extra >= 0) {
-      if (lo.extra == L_TW_TENSORS) d.slot = fill[t.fmt][lo.extra];
-      ba.extra_pos[k] = start[t.fmt][lo.extra] + fill[t.fmt][lo.extra]++;
+    if (p.tail) ba.extra_pos[k] = start[f][eco::LIST_EXTRA] + fill[f][eco::LIST_EXTRA]++;
+    if (p.list == eco::LIST_TW_TILES) {
+      d.slot = fill[f][L_TW_TENSORS];
+      ba.extra_pos[k] = start[f][L_TW_TENSORS] + fill[f][L_TW_TENSORS]++;
     }
     if (ba.count == BUILD_CHUNK || i + 1 == n) {
       hipLaunchKernelGGL(eco_noalloc_build_kernel, dim3(ba.count, BUILD_BLOCKS_PER_TENSOR), dim3(BUILD_THREADS), 0, hs, ba);
@@ -659,37 +779,33 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     }
   }
 
-  eco_constants_t c;
-  derive_constants(hp, &c);
-  const int cus = num_compute_units();
   const eco::TensorDesc *descs = reinterpret_cast<const eco::TensorDesc *>(sp + OFF_DESCS);
   uint32_t *tables = reinterpret_cast<uint32_t *>(sp + OFF_TABLES);
   for (int f = 0; f < 4; ++f) {
     uint64_t any = 0;
     for (int l = 0; l < L_COUNT; ++l) any += count[f][l];
     if (!any) continue;
-    eco::StepArgs a;
-    std::memset(&a, 0, sizeof a);
+    eco::StepLaunch sl;
+    std::memset(&sl, 0, sizeof sl);
+    eco::StepArgs &a = sl.args;
     a.tensors = descs;
-    a.tile_tensor = tables + start[f][L_TILE];
-    a.ragged_tensor = tables + start[f][L_RAGGED];
-    a.num_tiles = static_cast<uint32_t>(count[f][L_TILE]);
-    a.num_ragged = static_cast<uint32_t>(count[f][L_RAGGED]);
-    a.wide_base = tables;
+    a.tile_tensor = tables + start[f][eco::LIST_TILE];
+    a.extra_tensor = tables + start[f][eco::LIST_EXTRA];
+    a.num_tiles = static_cast<uint32_t>(count[f][eco::LIST_TILE]);
+    a.num_extra = static_cast<uint32_t>(count[f][eco::LIST_EXTRA]);
+    sl.wide_base = tables;
     for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
-      a.wide_offset[nw] = start[f][L_WIDE1 + nw - 1];
-      a.num_wide[nw] = static_cast<uint32_t>(count[f][L_WIDE1 + nw - 1]);
+      sl.wide_offset[nw] = start[f][eco::LIST_WIDE1 + nw - 1];
+      sl.num_wide[nw] = static_cast<uint32_t>(count[f][eco::LIST_WIDE1 + nw - 1]);
     }
-    a.tw_tile_tensor = tables + start[f][L_TW_TILES];
+    a.tw_tile_tensor = tables + start[f][eco::LIST_TW_TILES];
     a.tw_tensor = tables + start[f][L_TW_TENSORS];
     a.slots = reinterpret_cast<uint32_t *>(sp + OFF_SLOTS) + tw_tensor_start[f];
     a.tile_max = reinterpret_cast<uint32_t *>(sp + OFF_TILE_MAX) + tw_tile_start[f];
-    a.num_tw_tiles = static_cast<uint32_t>(count[f][L_TW_TILES]);
+    a.num_tw_tiles = static_cast<uint32_t>(count[f][eco::LIST_TW_TILES]);
     a.num_tw_tensors = static_cast<uint32_t>(count[f][L_TW_TENSORS]);
-    const eco::KernelVariant kv = variant_for(hp, f);
-    fill_step_scalars(hp, c, kv, &a);
-    const hipError_t e = eco::launch_step(kv, a, grid_for(a.num_tiles, cus), hs);
-    if (e != hipSuccess) return fail_hip(e, "step kernel launch");
+    st = launch_format(hp, c, f, cus, &sl, nullptr, hs);
+    if (st != ECO_OK) return st;
   }
   return ECO_OK;
 }

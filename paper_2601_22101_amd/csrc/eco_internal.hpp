@@ -39,6 +39,19 @@ constexpr uint32_t DEFAULT_STEP_LDS_BYTES = 13312;
 constexpr int MAX_WIDE_WAVES = 16;          // widest single-workgroup scale group: 16 waves * 512 = 8192 elements
 constexpr uint64_t MAX_WIDE_GROUP = 8192;
 
+// What a wave does with one of its tensor's units.  Full 512-element tiles of block-scaled tensors and groups of more
+// than 512 elements have launch lists of their own; everything else a step consists of -- the last, partial tile of a
+// block-scaled tensor, groups of up to 512 elements that are no power of two, unquantized tensors -- is a list of
+// one-wave units that ride in the launch of those (StepArgs::extra_tensor).
+enum : int {
+  UNIT_TILES = 0,       // block-scaled: unit u is tile u
+  UNIT_TAIL = 1,        // block-scaled, full tiles elsewhere: the one unit is the partial last tile
+  UNIT_ROWS = 2,        // groups of 8..504 elements, no power of two >= 32: unit u is the groups u * slot .. u * slot + slot - 1
+  UNIT_PLAIN_BF16 = 3,  // unquantized: unit u is tile u
+  UNIT_PLAIN_FP32 = 4,
+  UNIT_WIDE = 5         // groups of 520..8192 elements: a workgroup's unit, see wide_geometry
+};
+
 struct TensorDesc {          // 80 bytes, device table entry
   void *w;                   // weights / codes
   void *s;                   // scales
@@ -48,35 +61,56 @@ struct TensorDesc {          // 80 bytes, device table entry
   void *aux;                 // fp32: stored error (exact injection) or master weights
   uint64_t numel;
   uint64_t group_size;       // elements per scale group
-  uint32_t first_unit;       // index of this tensor's first tile (or first group) in its launch list
+  uint32_t first_unit;       // index of this tensor's first unit (tile, group, bundle of groups) in its launch list
   uint32_t tensor_id;
-  uint32_t bs_shift;         // log2(group_size) for power-of-two groups of 32..512 elements
-  uint32_t slot;             // tensor-wise scaling: index of the tensor's abs-max slot; wide groups: groups per workgroup
+  uint16_t bs_shift;         // log2(group_size) for power-of-two groups of 32..512 elements
+  uint16_t kind;             // UNIT_*: what a unit of the list the tensor is in stands for
+  uint32_t slot;             // tensor-wise scaling: index of the tensor's abs-max slot; wide groups and UNIT_ROWS: groups per unit
 };
 static_assert(sizeof(TensorDesc) == 80, "TensorDesc layout");
 
 struct StepArgs {            // by-value kernel argument: everything wave-uniform
   const TensorDesc *tensors;
   const uint32_t *tile_tensor;     // block-scaled tensors: full tile -> index into tensors
-  const uint32_t *ragged_tensor;   //   ... tensors that end in a partial tile
+  const uint32_t *extra_tensor;    // one-wave units that ride in this launch: unit -> index into tensors
   const uint32_t *wide_tensor;     // wide groups of the launch in flight: group -> index into tensors
   const uint32_t *tw_tile_tensor;  // tensor-wise scaling: tile (full or partial) -> index into tensors
   const uint32_t *tw_tensor;       //   ... the tensors themselves
   uint32_t *slots;                 //   ... one abs-max slot (fp32 bit pattern) per such tensor
   uint32_t *tile_max;              //   ... scratch: the abs-max of every such tile, written and consumed within a step
-  uint32_t num_tiles, num_ragged, num_tw_tiles, num_tw_tensors;
+  uint32_t num_tiles, num_extra, num_tw_tiles, num_tw_tensors;
   float b1, omb1, b2, omb2, rbc2, c1, eps, kappa, lr, alpha, wd, inv_lr, inv_lr_beta;
   uint32_t seed_lo, seed_hi, step_lo;
   uint32_t div_mid;                // c1 and eps allow the short division (see div_rn_midrange) after a short square root
   uint32_t unit_base;              // first work item (group, tile, tensor) of the launch in flight, see launch_in_chunks
-  // host side only
+  uint32_t num_units;              // wide-group launch: work items before the extra ones
+};
+
+// A list of at most SMALL_TENSORS tensors, carried by value in the kernel arguments (4 KB): the step of a short list
+// needs no table in device memory and is one launch whatever classes of scale group it holds.
+constexpr int SMALL_TENSORS = 44;
+struct SmallArgs {
+  StepArgs step;
+  uint32_t num;                        // tensors
+  uint32_t first_wg[SMALL_TENSORS];    // the first workgroup of each
+  TensorDesc desc[SMALL_TENSORS];      // first_unit: the number of the tensor's units here
+};
+static_assert(sizeof(SmallArgs) <= 4096, "kernel arguments are limited to 4 KB");
+
+// What one format's step launches, host side.
+struct StepLaunch {
+  StepArgs args;
   uint64_t max_launch_threads;     // most threads one launch may have (the runtime's limit, or a smaller one set for tests)
+  uint64_t max_tile_threads;       // the same for the full-tile kernel (a tuning option may cap it further)
   uint32_t lds_bytes;              // dynamic LDS per workgroup of the full-tile kernel (occupancy cap)
   uint32_t lds_bytes_wave;         // the same per wave of the wide-group kernel
   uint32_t lds_bytes_tw;           // the same per (one-wave) workgroup of the two tensor-wise passes
   const uint32_t *wide_base;       // wide-group lists, one per workgroup size, back to back
   uint32_t wide_offset[MAX_WIDE_WAVES + 1];
   uint32_t num_wide[MAX_WIDE_WAVES + 1];
+  int extra_in;                    // which launch the one-wave units ride in: 0 the full-tile one, n the wide groups of n waves
+  const SmallArgs *small;          // if set, one launch of the short-list kernel ...
+  unsigned small_wgs, small_waves; //   ... with this geometry stands for all of the above but the tensor-wise passes
 };
 
 struct KernelVariant {
@@ -88,7 +122,7 @@ struct KernelVariant {
 };
 
 // Each launcher enqueues its kernels on `stream`, checks every launch, and returns the first error.
-hipError_t launch_step(const KernelVariant &kv, const StepArgs &args, unsigned grid, hipStream_t stream);
+hipError_t launch_step(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream);
 hipError_t launch_quantize_init(const void *src, int src_bf16, uint64_t numel, int fmt, uint64_t group_size,
                                 int scale_bf16, void *weights, void *scales, hipStream_t stream);
 hipError_t launch_dequantize(const void *weights, const void *scales, uint64_t numel, int fmt, uint64_t group_size,
@@ -142,6 +176,57 @@ inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = 
   }
   return w;
 }
+// Groups of up to 512 elements that are no power of two in [32, 512] (rows of 48, 96, 384, ...): as many whole groups to
+// a wave as its 512 elements hold, instead of one.
+inline uint32_t rows_per_wave(uint64_t g) { return static_cast<uint32_t>(TILE_ELEMS / g); }
+
+// What a step does with one tensor: the launch list it enters, the kind of its units there and how many they are.
+enum : int { LIST_TILE = 0, LIST_EXTRA = 1, LIST_WIDE1 = 2, LIST_TW_TILES = LIST_WIDE1 + MAX_WIDE_WAVES, LIST_COUNT };
+struct Placement {
+  int list;              // LIST_*; LIST_WIDE1 + n - 1: groups that take a workgroup of n waves
+  int kind;              // UNIT_*
+  uint64_t units;
+  bool tail;             // one more unit, of kind UNIT_TAIL, in LIST_EXTRA
+  uint64_t group;        // elements per scale group
+  uint32_t rows;         // groups per unit (wide groups, UNIT_ROWS)
+  uint64_t entries;      // what the tensor counts towards the limits on launch tables: a unit per tile or per group
+};
+inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool quantized, int fmt) {
+  Placement p = {LIST_TILE, UNIT_TILES, 0, false, group_size, 1, 0};
+  if (cls == GROUP_BLOCK) {
+    const bool rest = numel % TILE_ELEMS != 0;
+    p.entries = numel / TILE_ELEMS + (rest ? 1 : 0);
+    if (!quantized) {
+      p.list = LIST_EXTRA;
+      p.kind = fmt == FMT_BF16_PLAIN ? UNIT_PLAIN_BF16 : UNIT_PLAIN_FP32;
+      p.units = p.entries;
+    } else {
+      p.units = numel / TILE_ELEMS;
+      p.tail = rest;
+    }
+  } else if (cls == GROUP_WIDE) {
+    p.group = group_size < numel ? group_size : numel;
+    if (p.group <= static_cast<uint64_t>(TILE_ELEMS)) {
+      p.list = LIST_EXTRA;
+      p.kind = UNIT_ROWS;
+      p.rows = rows_per_wave(p.group);
+      p.entries = (numel + p.group - 1) / p.group;
+      p.units = (p.entries + p.rows - 1) / p.rows;
+    } else {
+      const WideGeometry w = wide_geometry(numel, p.group);
+      p.list = LIST_WIDE1 + static_cast<int>(w.waves) - 1;
+      p.kind = UNIT_WIDE;
+      p.rows = w.rows;
+      p.units = p.entries = w.units;
+    }
+  } else {
+    p.group = numel;
+    p.list = LIST_TW_TILES;
+    p.units = (numel + TILE_ELEMS - 1) / TILE_ELEMS;
+    p.entries = p.units + 1;
+  }
+  return p;
+}
 inline int log2_exact(uint64_t x) {
   for (int s = 0; s < 64; ++s)
     if ((1ull << s) == x) return s;
@@ -151,10 +236,10 @@ hipError_t launch_philox_fill(uint64_t seed, uint64_t step, uint32_t tensor_id, 
                               uint32_t *dst, hipStream_t stream);
 
 // per-(fmt, state) translation units of the quantized step kernel
-hipError_t launch_step_fp8_f32(const KernelVariant &, const StepArgs &, unsigned, hipStream_t);
-hipError_t launch_step_fp8_bf16(const KernelVariant &, const StepArgs &, unsigned, hipStream_t);
-hipError_t launch_step_int4_f32(const KernelVariant &, const StepArgs &, unsigned, hipStream_t);
-hipError_t launch_step_int4_bf16(const KernelVariant &, const StepArgs &, unsigned, hipStream_t);
-hipError_t launch_step_plain(const KernelVariant &, const StepArgs &, unsigned, hipStream_t);
+hipError_t launch_step_fp8_f32(const KernelVariant &, const StepLaunch &, hipStream_t);
+hipError_t launch_step_fp8_bf16(const KernelVariant &, const StepLaunch &, hipStream_t);
+hipError_t launch_step_int4_f32(const KernelVariant &, const StepLaunch &, hipStream_t);
+hipError_t launch_step_int4_bf16(const KernelVariant &, const StepLaunch &, hipStream_t);
+hipError_t launch_step_plain(const KernelVariant &, const StepLaunch &, hipStream_t);
 
 }  // namespace eco

@@ -8,63 +8,20 @@
 namespace eco {
 
 // ------------------------------------------------------------------------ plain optimizer step
-// Adam / SGDM on weights that are not quantized.  FMT_BF16_PLAIN: bf16 weights, result rounded to
-// nearest even, no injection (the method is applied to linear layers only; norm weights take the
-// ordinary optimizer).  FMT_FP32_ID: fp32 weights under the identity quantizer, for which the
-// quantization error is zero and Alg. 2/3 add nothing to the momentum.
-template <int FMT, bool STATE_BF16, bool ADAM, int ACC>
-__device__ __forceinline__ void plain_tile(const StepArgs &a, const TensorDesc &td, uint64_t e0) {
-  const int nvalid = ACC == ACC_FULL ? 8 : valid_from(e0, td.numel);
-  float w[8], g[8], m[8], v[8];
-  load_state8<FMT == FMT_BF16_PLAIN, ACC>(td.w, e0, nvalid, w);
-  load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
-  load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
-  if (ADAM) load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    float wj = w[j];
-    m[j] = fmaf(a.b1, m[j], a.omb1 * g[j]);
-    float u;
-    if (ADAM) {
-      v[j] = fmaf(a.b2, v[j], a.omb2 * (g[j] * g[j]));
-      const float d = sqrtf(v[j] * a.rbc2) + a.eps;
-      u = (a.c1 / d) * m[j];          // the element-wise step size of Sec. 3.2 times the first moment
-    } else {
-      u = a.lr * m[j];
-    }
-    if (a.wd != 0.0f) wj = wj - a.wd * wj;
-    w[j] = wj - u;
-  }
-  store_state8<FMT == FMT_BF16_PLAIN, ACC>(td.w, e0, nvalid, w);
-  store_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
-  if (ADAM) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
-}
-
+// Launches of their own for unquantized tensors: a plan without quantized ones, or one whose unquantized tensors are
+// too many to ride along as one-wave units (an embedding, attention matrices).  A wave per 512-element tile.
 template <int FMT, bool STATE_BF16, bool ADAM>
 __global__ __launch_bounds__(WG_THREADS) void eco_plain_kernel(const StepArgs a) {
-  for (uint32_t tile = blockIdx.x; tile < a.num_tiles; tile += gridDim.x) {
-    const TensorDesc td = load_tensor_desc(a, load_table(a.tile_tensor, tile));
-    const uint64_t tile_off = (uint64_t)(tile - td.first_unit) * TILE_ELEMS;
-    plain_tile<FMT, STATE_BF16, ADAM, ACC_FULL>(a, td, tile_off + (uint64_t)threadIdx.x * ELEMS_PER_LANE);
-  }
+  const uint32_t tile = blockIdx.x + a.unit_base;
+  const TensorDesc td = load_tensor_desc(a, load_table(a.extra_tensor, tile));
+  const uint64_t tile_off = (uint64_t)(tile - td.first_unit) * TILE_ELEMS, e0 = tile_off + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
+  if (tile_off + TILE_ELEMS <= td.numel) plain_lane<FMT == FMT_BF16_PLAIN, STATE_BF16, ADAM, ACC_FULL>(a, td, e0, 8);
+  else plain_lane<FMT == FMT_BF16_PLAIN, STATE_BF16, ADAM, ACC_LANE>(a, td, e0, valid_from(e0, td.numel));
 }
 
-template <int FMT, bool STATE_BF16, bool ADAM>
-__global__ __launch_bounds__(WG_THREADS) void eco_plain_ragged_kernel(const StepArgs a) {
-  const TensorDesc td = load_tensor_desc(a, load_table(a.ragged_tensor, blockIdx.x + a.unit_base));
-  const uint64_t tile_off = td.numel / TILE_ELEMS * TILE_ELEMS;
-  plain_tile<FMT, STATE_BF16, ADAM, ACC_GUARDED>(a, td, tile_off + (uint64_t)threadIdx.x * ELEMS_PER_LANE);
-}
-
-hipError_t launch_step_plain(const KernelVariant &kv, const StepArgs &args, unsigned grid, hipStream_t stream) {
-#define ECO_LAUNCH(F, ST, AD)                                                                                  \
-  do {                                                                                                         \
-    if (args.num_tiles)                                                                                        \
-      ECO_LAUNCH_CHECKED((eco_plain_kernel<F, ST, AD>), dim3(capped_grid(grid, args)), dim3(WG_THREADS), 0,    \
-                         stream, args);                                                                        \
-    if (args.num_ragged)                                                                                       \
-      ECO_CHUNKS_CHECKED((eco_plain_ragged_kernel<F, ST, AD>), args.num_ragged, WG_THREADS, 0, stream, args);  \
-  } while (0)
+hipError_t launch_step_plain(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {
+#define ECO_LAUNCH(F, ST, AD) \
+  ECO_CHUNKS_CHECKED((eco_plain_kernel<F, ST, AD>), sl.args.num_extra, WG_THREADS, 0, stream, sl.args, sl.max_tile_threads)
   const int key = (kv.fmt == FMT_FP32_ID ? 4 : 0) | (kv.state_bf16 ? 2 : 0) | (algo_is_adam(kv.algo) ? 0 : 1);
   switch (key) {
     case 0: ECO_LAUNCH(FMT_BF16_PLAIN, false, true); break;
@@ -80,10 +37,10 @@ hipError_t launch_step_plain(const KernelVariant &kv, const StepArgs &args, unsi
   return hipSuccess;
 }
 
-hipError_t launch_step(const KernelVariant &kv, const StepArgs &args, unsigned grid, hipStream_t stream) {
-  if (kv.fmt == FMT_FP8) return kv.state_bf16 ? launch_step_fp8_bf16(kv, args, grid, stream) : launch_step_fp8_f32(kv, args, grid, stream);
-  if (kv.fmt == FMT_INT4) return kv.state_bf16 ? launch_step_int4_bf16(kv, args, grid, stream) : launch_step_int4_f32(kv, args, grid, stream);
-  return launch_step_plain(kv, args, grid, stream);
+hipError_t launch_step(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {
+  if (kv.fmt == FMT_FP8) return kv.state_bf16 ? launch_step_fp8_bf16(kv, sl, stream) : launch_step_fp8_f32(kv, sl, stream);
+  if (kv.fmt == FMT_INT4) return kv.state_bf16 ? launch_step_int4_bf16(kv, sl, stream) : launch_step_int4_f32(kv, sl, stream);
+  return launch_step_plain(kv, sl, stream);
 }
 
 // ------------------------------------------------------------------------ initial quantizer

@@ -2,7 +2,7 @@
 #include "eco_step_kernel.hpp"
 
 namespace eco {
-hipError_t launch_step_int4_f32(const KernelVariant &kv, const StepArgs &args, unsigned grid, hipStream_t stream) {
-  return launch_step_variants<FMT_INT4, false>(kv, args, grid, stream);
+hipError_t launch_step_int4_f32(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {
+  return launch_step_variants<FMT_INT4, false>(kv, sl, stream);
 }
 }  // namespace eco

@@ -157,6 +157,16 @@ __device__ __forceinline__ void store_codes8(void *base, uint64_t e0, int nvalid
   }
 }
 
+// x_j = value for the elements of a lane that do not exist.
+template <int ACC>
+__device__ __forceinline__ void fill_missing(float (&x)[8], int nvalid, float value) {
+  if (ACC != ACC_FULL) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j >= nvalid) x[j] = value;
+  }
+}
+
 template <int FMT, int J>
 __device__ __forceinline__ float decode_elem(const uint32_t (&c)[2]) {
   if (FMT == FMT_FP8) return e4m3_decode<(J & 3)>(c[J >> 2]);
@@ -265,29 +275,55 @@ __device__ __forceinline__ bool sqrt_plus_eps8(const float (&x)[8], float eps, f
   return false;
 }
 
+// eta_j = c1 / d_j with d_j = sqrt(x_j) + eps: the element-wise step size of Sec. 3.2, (eta / (1 - b1^k)) / (sqrt(v^) + eps).
+// After the short square root every d of the wave lies in [2^-48, 2^48 + eps], and div_mid says that eps <= 1 and c1 is
+// in the range of the short division.
+__device__ __forceinline__ void step_sizes8(const StepArgs &a, const float (&x)[8], float (&d)[8], float (&eta)[8]) {
+  if (sqrt_plus_eps8(x, a.eps, d) && a.div_mid) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) eta[j] = div_rn_midrange(a.c1, d[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) eta[j] = a.c1 / d[j];
+  }
+}
+
 // ------------------------------------------------------------------ the step of one lane
 // How the abs-max of a scale group is obtained:
 //   RED_BLOCK  the group is 2^shift elements inside one wave: DPP/swizzle all-reduce over its lanes
 //   RED_WG     the group is the whole workgroup (1..16 waves): wave all-reduce, then an LDS combine
-//   RED_WG_ROWS the workgroup holds 2..8 whole groups of more than 512 elements each (a wave meets at most two of
+//   RED_WG_ROWS the workgroup holds up to 16 whole groups of more than 512 elements each (a wave meets at most two of
 //              them): per wave one all-reduce for each of its groups, LDS atomic max into the group's entry
 //   RED_ATOMIC first pass of a group larger than a workgroup, one group at a time (the initial quantizer):
 //              wave all-reduce, one atomic max per wave into the group's slot; nothing else is written
 //   RED_TILE   first pass of the step for such groups (tensor-wise scaling): wave all-reduce, the wave's
 //              maximum goes to its tile's entry of a scratch array, which a small kernel folds into the
 //              tensor's slot (tens of thousands of atomics on one address serialize in the memory system)
+//   RED_ROWS   groups of any length up to 512, several to a wave: segmented all-reduce over the group's lanes
 //   RED_SLOT   second pass: the abs-max is read from that slot; everything is recomputed and written
 //              except the scale (a last, tiny kernel writes it once every tile has used the old one)
-enum : int { RED_BLOCK = 0, RED_WG = 1, RED_ATOMIC = 2, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS = 5 };
+enum : int { RED_BLOCK = 0, RED_WG = 1, RED_ATOMIC = 2, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS = 5, RED_ROWS = 6 };
 
-// arg: RED_BLOCK: log2(group size); RED_WG_ROWS: which of the workgroup's groups the lane belongs to.
+constexpr uint32_t WG_ROWS = 16;
+// arg: RED_BLOCK: log2(group size); RED_WG_ROWS: which of the workgroup's groups the lane belongs to; RED_ROWS: the
+// first lane of the lane's group, `lanes` the lanes of a group.
 template <int RED>
-__device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t *slot) {
+__device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t *slot, int lanes = 0) {
+  if (RED == RED_ROWS) {
+    // inclusive maximum scan within the group, doubling the distance; the group's last lane then holds its maximum
+    const int lane = (int)(threadIdx.x & 63), last = arg + lanes - 1;
+    uint32_t x = f2u(lane_max);
+    for (int off = 1; off < lanes; off <<= 1) {                // wave-uniform
+      const uint32_t o = (uint32_t)__shfl_up((int)x, off, 64);
+      if (lane - off >= arg) x = x > o ? x : o;
+    }
+    return u2f((uint32_t)__shfl((int)x, last < 64 ? last : 63, 64));
+  }
   if (RED == RED_BLOCK) return u2f(group_umax(f2u(lane_max), 1 << (arg - 3)));
   if (RED == RED_SLOT) return u2f(*slot);
   if (RED == RED_WG_ROWS) {
-    __shared__ uint32_t row_max[8];
-    if (threadIdx.x < 8) row_max[threadIdx.x] = 0;
+    __shared__ uint32_t row_max[WG_ROWS];
+    if (threadIdx.x < WG_ROWS) row_max[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t x = f2u(lane_max);
     const int first = __builtin_amdgcn_readfirstlane(arg), last = __builtin_amdgcn_readlane(arg, 63);
@@ -325,7 +361,7 @@ __device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t 
 
 // One lane's 8 consecutive elements, starting at element e0 of tensor td, of which the first nvalid exist;
 // scale group number sg; bs_shift = log2(group size) for RED_BLOCK; row = the lane's group within the workgroup for
-// RED_WG_ROWS.
+// RED_WG_ROWS, the first lane of the lane's group for RED_ROWS.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC, int RED>
 __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid,
                                           uint64_t sg, bool scale_writer, uint32_t *slot, int row = 0) {
@@ -369,15 +405,8 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
       x[j] = v[j] * a.rbc2;
     }
     if (WRITE) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);   // v is final (Alg. 3 returns it unchanged)
-    // the element-wise step size of Sec. 3.2, eta_t = (eta / (1 - b1^k)) / (sqrt(v^) + eps).  After the short square
-    // root every d of the wave lies in [2^-48, 2^48 + eps], and div_mid says that eps <= 1 and c1 is in range
-    if (sqrt_plus_eps8(x, a.eps, d) && a.div_mid) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) eta[j] = div_rn_midrange(a.c1, d[j]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) eta[j] = a.c1 / d[j];
-    }
+    fill_missing<ACC>(x, nvalid, 1.0f);                              // elements that do not exist decide nothing
+    step_sizes8(a, x, d, eta);
   }
   float u[8];
 #pragma unroll
@@ -409,14 +438,11 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
 #pragma unroll
     for (int j = 0; j < 8; ++j) th[j] = w[j] - u[j];
   }
-  if (ACC != ACC_FULL) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (j >= nvalid) th[j] = 0.0f;
-  }
+  fill_missing<ACC>(th, nvalid, 0.0f);
 
   // ECO_QUANTIZE
-  const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS ? row : (int)td.bs_shift, slot);
+  const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
+                                       RED == RED_ROWS ? (int)(td.group_size >> 3) : 0);
   if (!WRITE) return;
   if (MASTER) store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, th);
   float s_new, inv;
@@ -440,7 +466,11 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   if (FMT == FMT_FP8) {
     // the E4M3 subnormal range (|y| < 2^-6) needs a second formula; it is rare, so decide per wave
     // (multiplication by inv >= 0 is monotone, so the smallest |y| is fl(min|theta~| * inv))
-    if (wave_any(absmin8(th) * inv < 0x1p-6f)) encode8<FMT, ROUND, false>(th, inv, r, cn, qn);
+    float lo[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) lo[j] = th[j];
+    fill_missing<ACC>(lo, nvalid, __builtin_inff());
+    if (wave_any(absmin8(lo) * inv < 0x1p-6f)) encode8<FMT, ROUND, false>(th, inv, r, cn, qn);
     else encode8<FMT, ROUND, true>(th, inv, r, cn, qn);
   } else {
     encode8<FMT, ROUND, true>(th, inv, r, cn, qn);
@@ -477,8 +507,7 @@ __device__ __forceinline__ uint32_t load_table(const uint32_t *table, uint32_t i
   return p[i];
 }
 
-__device__ __forceinline__ TensorDesc load_tensor_desc(const StepArgs &a, uint32_t ti) {
-  const ECO_CONST_AS uint64_t *p = (const ECO_CONST_AS uint64_t *)(uintptr_t)(a.tensors + ti);
+__device__ __forceinline__ TensorDesc read_tensor_desc(const ECO_CONST_AS uint64_t *p) {
   TensorDesc td;
   td.w = (void *)(uintptr_t)p[0];
   td.s = (void *)(uintptr_t)p[1];
@@ -491,55 +520,130 @@ __device__ __forceinline__ TensorDesc load_tensor_desc(const StepArgs &a, uint32
   const uint64_t a8 = p[8], a9 = p[9];
   td.first_unit = (uint32_t)a8;
   td.tensor_id = (uint32_t)(a8 >> 32);
-  td.bs_shift = (uint32_t)a9;
+  td.bs_shift = (uint16_t)a9;
+  td.kind = (uint16_t)(a9 >> 16);
   td.slot = (uint32_t)(a9 >> 32);
   return td;
 }
 
-// ------------------------------------------------------------------ kernels
-// (1) Block-scaled tensors (group = 32..512 elements, a power of two): one workgroup of one wave per
-// full 512-element tile, dispatched in address order (or, when the host caps the grid, looping with
-// the grid as stride).  The tile -> tensor table and the descriptors are wave-uniform scalar loads.
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(WG_THREADS, 8) void eco_step_kernel(const StepArgs a) {
-  for (uint32_t tile = blockIdx.x; tile < a.num_tiles; tile += gridDim.x) {
-    // A wave that has not issued its loads yet goes first: its address arithmetic and load instructions
-    // are not queued behind the arithmetic of the waves that already have their data (the priority is
-    // dropped again in step_lane, once the loads are issued).  Measured: +0.3 % and a flatter optimum
-    // over the occupancy cap.
-    __builtin_amdgcn_s_setprio(3);
-    const TensorDesc td = load_tensor_desc(a, load_table(a.tile_tensor, tile));
-    const uint64_t e0 = (uint64_t)(tile - td.first_unit) * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
-    const bool writer = (threadIdx.x & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_BLOCK>(a, td, e0, 8, e0 >> td.bs_shift, writer, nullptr);
-  }
+__device__ __forceinline__ TensorDesc load_tensor_desc(const StepArgs &a, uint32_t ti) {
+  return read_tensor_desc((const ECO_CONST_AS uint64_t *)(uintptr_t)(a.tensors + ti));
 }
 
-// (2) The last, partial tile of each block-scaled tensor whose length is not a multiple of TILE_ELEMS:
-// one workgroup per such tensor, element-wise guarded accesses.  A separate kernel keeps the guards'
-// registers and branches out of the full-tile kernel.
+// How many of the 8 elements from e0 on exist before `end`.
 __device__ __forceinline__ int valid_from(uint64_t e0, uint64_t end) {
   const int64_t left = (int64_t)end - (int64_t)e0;
   return left >= 8 ? 8 : (left <= 0 ? 0 : (int)left);
 }
 
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(WG_THREADS) void eco_step_ragged_kernel(const StepArgs a) {
-  const TensorDesc td = load_tensor_desc(a, load_table(a.ragged_tensor, blockIdx.x + a.unit_base));
-  const uint64_t e0 = td.numel / TILE_ELEMS * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
-  const bool writer = (threadIdx.x & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
-  step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_GUARDED, RED_BLOCK>(a, td, e0, valid_from(e0, td.numel),
-                                                                              e0 >> td.bs_shift, writer, nullptr);
+// ------------------------------------------------------------------ plain optimizer step
+// Adam / SGDM on weights that are not quantized.  UNIT_PLAIN_BF16: bf16 weights, result rounded to nearest even, no
+// injection (the method is applied to linear layers only; norm weights take the ordinary optimizer).
+// UNIT_PLAIN_FP32: fp32 weights under the identity quantizer, for which the quantization error is zero and Alg. 2/3
+// add nothing to the momentum.
+template <bool W_BF16, bool STATE_BF16, bool ADAM, int ACC>
+__device__ __forceinline__ void plain_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid) {
+  float w[8], g[8], m[8], v[8], eta[8];
+  load_state8<W_BF16, ACC>(td.w, e0, nvalid, w);
+  load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
+  load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+  if (ADAM) {
+    float x[8], d[8];
+    load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      v[j] = fmaf(a.b2, v[j], a.omb2 * (g[j] * g[j]));
+      x[j] = v[j] * a.rbc2;
+    }
+    fill_missing<ACC>(x, nvalid, 1.0f);
+    step_sizes8(a, x, d, eta);
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float wj = w[j];
+    m[j] = fmaf(a.b1, m[j], a.omb1 * g[j]);
+    const float u = ADAM ? eta[j] * m[j] : a.lr * m[j];     // the element-wise step size of Sec. 3.2 times the first moment
+    if (a.wd != 0.0f) wj = wj - a.wd * wj;
+    w[j] = wj - u;
+  }
+  store_state8<W_BF16, ACC>(td.w, e0, nvalid, w);
+  store_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+  if (ADAM) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
 }
 
-// (3) Wide groups (any multiple of 8 up to 8192 elements: row-wise scaling, Sec. 4.1): one workgroup of
+// ------------------------------------------------------------------ kernels
+// One unit of a list of one-wave units (UNIT_*), `lane` in 0..63.  Per-lane guards throughout: what is left beside the
+// full tiles is little, and one body serves whole and partial tiles.
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+__device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDesc &td, uint32_t unit, uint32_t lane) {
+  if (td.kind == UNIT_PLAIN_BF16 || td.kind == UNIT_PLAIN_FP32) {
+    const uint64_t e0 = (uint64_t)unit * TILE_ELEMS + (uint64_t)lane * ELEMS_PER_LANE;
+    const int nvalid = valid_from(e0, td.numel);
+    if (td.kind == UNIT_PLAIN_BF16) plain_lane<true, STATE_BF16, algo_is_adam(ALGO), ACC_LANE>(a, td, e0, nvalid);
+    else plain_lane<false, STATE_BF16, algo_is_adam(ALGO), ACC_LANE>(a, td, e0, nvalid);
+    return;
+  }
+  if (td.kind == UNIT_ROWS) {
+    // td.slot groups to the wave, one after the other; the lanes beyond them have nothing
+    const uint32_t gl = (uint32_t)td.group_size >> 3;                      // lanes of a group: 1..63
+    const uint32_t row = (lane * (65536u / gl + 1u)) >> 16;                // lane / gl, exact for lane < 64
+    const uint64_t grp = (uint64_t)unit * td.slot;
+    const uint64_t e0 = grp * td.group_size + (uint64_t)lane * ELEMS_PER_LANE;
+    const uint64_t end = (grp + td.slot) * td.group_size;
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_ROWS>(
+        a, td, e0, valid_from(e0, end < td.numel ? end : td.numel), grp + row, lane == row * gl, nullptr, (int)(row * gl));
+    return;
+  }
+  const uint64_t tile = td.kind == UNIT_TAIL ? td.numel / TILE_ELEMS : unit;
+  const uint64_t e0 = tile * TILE_ELEMS + (uint64_t)lane * ELEMS_PER_LANE;
+  const bool writer = (lane & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
+  step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_BLOCK>(a, td, e0, valid_from(e0, td.numel), e0 >> td.bs_shift,
+                                                                           writer, nullptr);
+}
+
+// (1) Block-scaled tensors (group = 32..512 elements, a power of two): one workgroup of one wave per
+// full 512-element tile, dispatched in address order.  The tile -> tensor table and the descriptors are
+// wave-uniform scalar loads.
+// Behind the tiles come the plan's one-wave units: a launch of their own for the norm gains and the ragged tails would
+// cost 5-6 us of a step each, whatever they hold.  (No loop over tiles: with one around both bodies the arguments and
+// what is derived from them stay live across it and no longer fit the scalar registers.)
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+__global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const StepArgs a) {
+  // A wave that has not issued its loads yet goes first: its address arithmetic and load instructions
+  // are not queued behind the arithmetic of the waves that already have their data (the priority is
+  // dropped again in step_lane, once the loads are issued).  Measured: +0.3 % and a flatter optimum
+  // over the occupancy cap.
+  __builtin_amdgcn_s_setprio(3);
+  const uint32_t tile = blockIdx.x + a.unit_base;
+  if (tile < a.num_tiles) {
+    const TensorDesc td = load_tensor_desc(a, load_table(a.tile_tensor, tile));
+    const uint64_t e0 = (uint64_t)(tile - td.first_unit) * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
+    const bool writer = (threadIdx.x & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_BLOCK>(a, td, e0, 8, e0 >> td.bs_shift, writer, nullptr);
+  } else {
+    const TensorDesc td = load_tensor_desc(a, load_table(a.extra_tensor, tile - a.num_tiles));
+    step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, tile - a.num_tiles - td.first_unit, threadIdx.x);
+  }
+}
+
+// (2) Wide groups (any multiple of 8 from 520 to 8192 elements: row-wise scaling, Sec. 4.1): one workgroup of
 // ceil(group/512) waves per group, abs-max by wave all-reduce plus an LDS combine across the waves -- or, where the
 // plan found that 2..8 groups fill a whole number of waves exactly (TensorDesc::slot, see wide_geometry), one
-// workgroup per such bundle of groups, every lane busy.
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+// workgroup per such bundle of groups, every lane busy.  EXTRA: workgroups beyond the groups take one-wave units, one
+// to a wave (a variant of its own: with those paths in the kernel the groups run 3.6 % slower, 3 460 -> 3 590 us over
+// Gemma-3-1B shapes, so a long launch leaves them to another one).
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, bool EXTRA>
 __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);      // as in eco_step_kernel: loading waves first
   const uint32_t unit = blockIdx.x + a.unit_base;
+  if (EXTRA && unit >= a.num_units) {
+    const uint32_t x = __builtin_amdgcn_readfirstlane((unit - a.num_units) * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    if (x < a.num_extra) {
+      const TensorDesc td = load_tensor_desc(a, load_table(a.extra_tensor, x));
+      step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, x - td.first_unit, threadIdx.x & 63);
+    }
+    return;
+  }
   const TensorDesc td = load_tensor_desc(a, load_table(a.wide_tensor, unit));
   const uint32_t rows = td.slot;
   const uint64_t grp = (uint64_t)(unit - td.first_unit) * rows;       // the workgroup's first group
@@ -561,6 +665,49 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const StepArgs a) {
   else
     step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG>(a, td, e0, valid_from(e0, end), grp,
                                                                           threadIdx.x == 0, nullptr);
+}
+
+// (3) A short list of tensors, its descriptors in the kernel arguments, every class of scale group but the tensor-wise
+// one in one launch: a step of a few small tensors is bound by launches (2.6 us of host time each, 4-6 us on the device
+// with the drain between two), not by what they do.  All workgroups have the waves that the widest group asks for; a
+// workgroup finds its tensor by comparing its number with the tensors' first ones, a lane each.  Groups wider than a
+// wave are packed as many units to a workgroup as its waves hold; one-wave units take a wave each.
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+__global__ __launch_bounds__(1024) void eco_step_small_kernel(const SmallArgs args) {
+  const ECO_CONST_AS SmallArgs *ka = (const ECO_CONST_AS SmallArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  const StepArgs &a = args.step;
+  __builtin_amdgcn_s_setprio(3);
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
+  const uint32_t first = lane < args.num ? ka->first_wg[lane] : 0xFFFFFFFFu;
+  const uint32_t ti = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(first <= blockIdx.x)) - 1u;
+  const uint32_t wg = blockIdx.x - ka->first_wg[ti];
+  const TensorDesc td = read_tensor_desc((const ECO_CONST_AS uint64_t *)&ka->desc[ti]);
+  const uint32_t units = td.first_unit;
+  if (td.kind != UNIT_WIDE) {
+    const uint32_t unit = wg * nwaves + wave;
+    if (unit >= units) return;
+    const uint64_t tile_off = (uint64_t)unit * TILE_ELEMS;
+    if (td.kind == UNIT_TILES && tile_off + TILE_ELEMS <= td.numel) {
+      const uint64_t e0 = tile_off + (uint64_t)lane * ELEMS_PER_LANE;
+      const bool writer = (lane & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
+      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_BLOCK>(a, td, e0, 8, e0 >> td.bs_shift, writer, nullptr);
+    } else {
+      step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, unit, lane);
+    }
+    return;
+  }
+  const uint32_t gs = (uint32_t)td.group_size, rows = td.slot;
+  const uint32_t uw = (rows * gs + TILE_ELEMS - 1) / TILE_ELEMS, per_wg = nwaves / uw;   // waves of a unit, units of a workgroup
+  const uint32_t u = wave / uw, unit = wg * per_wg + u;
+  const uint32_t lane_elem = (wave - u * uw) * TILE_ELEMS + lane * ELEMS_PER_LANE;
+  const uint64_t start = (uint64_t)unit * rows * gs;
+  uint64_t end = start + (uint64_t)rows * gs < td.numel ? start + (uint64_t)rows * gs : td.numel;
+  if (u >= per_wg || unit >= units) end = 0;              // nothing to do, but the barriers are the workgroup's
+  uint32_t row = 0;
+  for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * gs ? 1u : 0u;
+  step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG_ROWS>(
+      a, td, start + lane_elem, valid_from(start + lane_elem, end), (uint64_t)unit * rows + row, lane_elem == row * gs, nullptr,
+      u < per_wg ? (int)(u * rows + row) : 0);
 }
 
 // (4) One scale per tensor (tensor-wise scaling, Sec. 4.4), tensors too large for one workgroup: two passes
@@ -625,8 +772,9 @@ inline unsigned lds_cap(unsigned bytes) { return bytes < 65536u ? bytes : 65536u
 // One work item per workgroup, `units` of them: as many launches as the limit on the threads of one launch asks
 // for (the runtime wants grid x block below 2^32), each told where it starts through StepArgs::unit_base.
 template <class Kernel>
-hipError_t launch_in_chunks(Kernel kernel, uint64_t units, unsigned block, unsigned lds, hipStream_t stream, StepArgs args) {
-  const uint64_t per_launch = args.max_launch_threads / block ? args.max_launch_threads / block : 1;
+hipError_t launch_in_chunks(Kernel kernel, uint64_t units, unsigned block, unsigned lds, hipStream_t stream, StepArgs args,
+                            uint64_t max_launch_threads) {
+  const uint64_t per_launch = max_launch_threads / block ? max_launch_threads / block : 1;
   for (uint64_t base = 0; base < units; base += per_launch) {
     args.unit_base = static_cast<uint32_t>(base);
     const uint64_t n = units - base < per_launch ? units - base : per_launch;
@@ -640,57 +788,63 @@ hipError_t launch_in_chunks(Kernel kernel, uint64_t units, unsigned block, unsig
     if (chunk_err_ != hipSuccess) return chunk_err_;             \
   } while (0)
 
-// The full-tile kernels loop over tiles with the grid as stride, so they take one launch with a capped grid.
-inline unsigned capped_grid(unsigned grid, const StepArgs &args) {
-  const uint64_t most = args.max_launch_threads / WG_THREADS ? args.max_launch_threads / WG_THREADS : 1;
-  return grid > most ? static_cast<unsigned>(most) : grid;
-}
-
 template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
-hipError_t launch_step_kernels(const StepArgs &args, unsigned grid, hipStream_t stream) {
-  if (args.num_tiles)
-    ECO_LAUNCH_CHECKED((eco_step_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(capped_grid(grid, args)), dim3(WG_THREADS),
-                       args.lds_bytes, stream, args);
-  if (args.num_ragged)
-    ECO_CHUNKS_CHECKED((eco_step_ragged_kernel<FMT, STATE_BF16, SC, AL, RD>), args.num_ragged, WG_THREADS, 0, stream, args);
-  for (int nw = 1; nw <= MAX_WIDE_WAVES; ++nw) {
-    if (!args.num_wide[nw]) continue;
-    StepArgs wa = args;
-    wa.wide_tensor = args.wide_base + args.wide_offset[nw];
-    ECO_CHUNKS_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD>), args.num_wide[nw], 64 * nw,
-                       lds_cap(args.lds_bytes_wave * nw), stream, wa);
+hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
+  const StepArgs &args = sl.args;
+  if (sl.small) {
+    ECO_LAUNCH_CHECKED((eco_step_small_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(sl.small_wgs), dim3(64 * sl.small_waves), 0, stream,
+                       *sl.small);
+  } else {
+    if (args.num_tiles || (args.num_extra && sl.extra_in == 0)) {
+      StepArgs ta = args;
+      if (sl.extra_in != 0) ta.num_extra = 0;
+      ECO_CHUNKS_CHECKED((eco_step_kernel<FMT, STATE_BF16, SC, AL, RD>), (uint64_t)ta.num_tiles + ta.num_extra, WG_THREADS, sl.lds_bytes,
+                         stream, ta, sl.max_tile_threads);
+    }
+    for (int nw = 1; nw <= MAX_WIDE_WAVES; ++nw) {
+      if (!sl.num_wide[nw]) continue;
+      StepArgs wa = args;
+      wa.wide_tensor = sl.wide_base + sl.wide_offset[nw];
+      wa.num_units = sl.num_wide[nw];
+      if (sl.extra_in != nw || !args.num_extra)
+        ECO_CHUNKS_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, false>), wa.num_units, 64 * nw,
+                           lds_cap(sl.lds_bytes_wave * nw), stream, wa, sl.max_launch_threads);
+      else
+        ECO_CHUNKS_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, true>), (uint64_t)wa.num_units + (wa.num_extra + nw - 1) / nw,
+                           64 * nw, lds_cap(sl.lds_bytes_wave * nw), stream, wa, sl.max_launch_threads);
+    }
   }
   if (args.num_tw_tiles) {
     ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_TILE>), args.num_tw_tiles, WG_THREADS,
-                       args.lds_bytes_tw, stream, args);
-    ECO_CHUNKS_CHECKED((eco_tensorwise_reduce_kernel<FMT>), args.num_tw_tensors, TW_REDUCE_THREADS, 0, stream, args);
+                       sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
+    ECO_CHUNKS_CHECKED((eco_tensorwise_reduce_kernel<FMT>), args.num_tw_tensors, TW_REDUCE_THREADS, 0, stream, args, sl.max_launch_threads);
     ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_SLOT>), args.num_tw_tiles, WG_THREADS,
-                       args.lds_bytes_tw, stream, args);
+                       sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
     ECO_CHUNKS_CHECKED((eco_tensorwise_scale_kernel<FMT, SC>), (args.num_tw_tensors + WG_THREADS - 1) / WG_THREADS, WG_THREADS,
-                       0, stream, args);
+                       0, stream, args, sl.max_launch_threads);
   }
   return hipSuccess;
 }
 
 template <int FMT, bool STATE_BF16, bool SC, int RD>
-hipError_t launch_step_algos(const KernelVariant &kv, const StepArgs &args, unsigned grid, hipStream_t stream) {
+hipError_t launch_step_algos(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {
   switch (kv.algo) {
-    case ALGO_ADAM: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_ADAM>(args, grid, stream);
-    case ALGO_SGDM: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_SGDM>(args, grid, stream);
-    case ALGO_SGDM_EXACT: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_SGDM_EXACT>(args, grid, stream);
-    case ALGO_ADAM_MASTER: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_ADAM_MASTER>(args, grid, stream);
-    default: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_SGDM_MASTER>(args, grid, stream);
+    case ALGO_ADAM: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_ADAM>(sl, stream);
+    case ALGO_SGDM: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_SGDM>(sl, stream);
+    case ALGO_SGDM_EXACT: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_SGDM_EXACT>(sl, stream);
+    case ALGO_ADAM_MASTER: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_ADAM_MASTER>(sl, stream);
+    default: return launch_step_kernels<FMT, STATE_BF16, SC, RD, ALGO_SGDM_MASTER>(sl, stream);
   }
 }
 
 template <int FMT, bool STATE_BF16>
-hipError_t launch_step_variants(const KernelVariant &kv, const StepArgs &args, unsigned grid, hipStream_t stream) {
+hipError_t launch_step_variants(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {
   const int key = (kv.scale_bf16 ? 2 : 0) | (kv.round == ROUND_RTN ? 1 : 0);
   switch (key) {
-    case 0: return launch_step_algos<FMT, STATE_BF16, false, ROUND_SR>(kv, args, grid, stream);
-    case 1: return launch_step_algos<FMT, STATE_BF16, false, ROUND_RTN>(kv, args, grid, stream);
-    case 2: return launch_step_algos<FMT, STATE_BF16, true, ROUND_SR>(kv, args, grid, stream);
-    default: return launch_step_algos<FMT, STATE_BF16, true, ROUND_RTN>(kv, args, grid, stream);
+    case 0: return launch_step_algos<FMT, STATE_BF16, false, ROUND_SR>(kv, sl, stream);
+    case 1: return launch_step_algos<FMT, STATE_BF16, false, ROUND_RTN>(kv, sl, stream);
+    case 2: return launch_step_algos<FMT, STATE_BF16, true, ROUND_SR>(kv, sl, stream);
+    default: return launch_step_algos<FMT, STATE_BF16, true, ROUND_RTN>(kv, sl, stream);
   }
 }
 

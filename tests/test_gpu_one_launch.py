@@ -1,0 +1,84 @@
+"""Units that share a launch: short rows, ragged tails and unquantized tensors behind full tiles, behind wide groups, and
+in the short-list kernel (at most 44 tensors, every class of group in one launch).  The comparison bar is the one of
+tests/gpu_util.py: the same fp32 sequence on both sides, so no code, scale or state bit may differ."""
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_util import bf16_bits, compare, host_copy, oracle_step, step_config
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+T = workloads.TensorSpec
+
+
+def short_rows(fmt):
+    """Groups of 8 .. 504 elements that are no power of two: one lane to 63, rows that fill a wave's last lane and that
+    do not, tensors of fewer rows than a wave takes, a ragged last unit."""
+    shapes = [(130, 8), (65, 16), (43, 24), (13, 40), (25, 96), (6, 120), (5, 168), (3, 336), (4, 384), (3, 504), (2, 248), (1, 72)]
+    return [T(f"r{c}", (r, c), fmt, grad_std=1e-3 * (1 + c % 3), granularity="row") for r, c in shapes]
+
+
+def lists(which, fmt):
+    plain = [T(f"p{n}", (n,), "bf16_plain") for n in (1, 511, 512, 1027)]
+    tails = [T(f"t{n}", (n,), fmt) for n in (1, 127, 300, 511)]
+    if which == "tiles":                   # a full-tile launch, more tensors than the short-list kernel takes
+        return short_rows(fmt) + plain + tails + [T(f"b{i}", (1024 + 8 * i + i % 3,), fmt) for i in range(40)]
+    if which == "wide":                    # no full tile: the units ride in the launch of the wide groups
+        return short_rows(fmt) + plain + tails + [T(f"w{i}", (1 + i % 5, 1408), fmt, granularity="row") for i in range(40)]
+    if which == "short":                   # several launches' worth of classes in one
+        wide = [T(f"w{c}_{r}", (r, c), fmt, granularity="row") for r, c in
+                ((8, 576), (5, 1408), (8, 1408), (3, 8192), (7, 520), (2, 6912), (33, 1024), (9, 2048))]
+        return short_rows(fmt) + plain + tails + wide + [T("b", (3, 700), fmt), T("b2", (4096,), fmt)]
+    return short_rows(fmt)                 # one-wave units alone
+
+
+@pytest.mark.parametrize("which", ["tiles", "wide", "short", "rows"])
+@pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("fp8", True, dict(mode=3, weight_decay=0.1)), ("int4", True, {}),
+                                           ("int4", False, dict(opt=1, round=1, lr=0.05)), ("fp8", False, dict(opt=1, mode=2, lr=0.05))])
+def test_units_that_share_a_launch(which, fmt, bf16, over):
+    from paper_2601_22101_amd import harness
+    o32 = oracle.get("f32")
+    wl = workloads.Workload("share_" + which, lists(which, fmt), steps=2, state_bf16=bf16, scale_bf16=bf16)
+    dw = harness.DeviceWorkload(wl, DEV, layout=over)
+    host = [host_copy(tv) for tv in dw.tensors]
+    for k in (1, 2):
+        dw.fill_gradients(k)
+        hp = dw.hparams(k)
+        for tv, h in zip(dw.tensors, host):
+            h["grad"] = bf16_bits(tv.grad)
+        dw.plan.step(hp)
+        torch.cuda.synchronize()
+        for tv, h in zip(dw.tensors, host):
+            oracle_step(o32, h, tv.spec.numel, step_config(hp, tv.tensor_id, tv.fmt, group_size=dw.group_size(tv)))
+            st = compare(host_copy(tv), h, f"{which} step {k} {tv.spec.name}", bf16)
+            assert not any(v for key, v in st.items() if key.endswith("mismatch")), (tv.spec.name, st)
+    dw.close()
+
+
+@pytest.mark.parametrize("opt", [0, 1])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_identity_weights_step_alike_alone_and_beside_quantized_tensors(opt, noalloc):
+    from paper_2601_22101_amd import binding as eco
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    n = 1500
+    arr = lambda scale: torch.randn(n, generator=gen, device=DEV) * scale  # noqa: E731
+    w, m, v, grad = arr(0.02), arr(1e-3), arr(1e-3).square(), arr(1e-3).to(torch.bfloat16)
+    hp = eco.make_hparams(opt=opt, step=7, weight_decay=0.1)
+    got = []
+    for beside in (False, True):
+        mine = [x.clone() for x in (w, m, v)]
+        ts = [eco.make_tensor(mine[0], None, grad, mine[1], mine[2], n, 0, eco.ECO_FMT_FP32_IDENTITY)]
+        if beside:
+            q = [torch.zeros(n, dtype=torch.uint8, device=DEV), torch.ones(12, device=DEV), torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)]
+            ts.append(eco.make_tensor(q[0], q[1], grad, q[2], q[3], n, 1, eco.ECO_FMT_FP8_E4M3))
+        if noalloc:
+            eco.eco_step_tensors_noalloc(ts, hp)
+        else:
+            with eco.Plan(ts, hp) as plan:
+                plan.step(hp)
+        torch.cuda.synchronize()
+        got.append(mine)
+    assert not torch.equal(got[0][0], w)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
