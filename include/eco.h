@@ -163,7 +163,7 @@ typedef struct eco_plan eco_plan_t;
  *                memory layout the descriptors are checked against)
  *   out        : receives the plan; owned by the library until eco_plan_destroy
  * Allocates device memory for the tables (80 bytes per tensor + 4 bytes per 512 elements, or per scale group
- * for groups wider than 512; for tensors with a single scale over more than 8192 elements another 4 bytes per
+ * for groups wider than 512; for tensors with a single scale over more than 8192 elements up to another 4.7 bytes per
  * 512 elements of scratch) and copies them synchronously.
  * Errors: ECO_EINVAL, ECO_EALIGN, ECO_EUNSUPPORTED, ECO_ENOMEM, ECO_EHIP.
  */
@@ -175,11 +175,13 @@ eco_status_t eco_plan_destroy(eco_plan_t *plan);
 /*
  * eco_step — one ECO step (Alg. 1 with Alg. 3 or Alg. 2) over every tensor of the plan.
  * Asynchronous on `stream`; allocates nothing.  Launches per quantized format present: one kernel over the full
- * 512-element tiles of block-scaled tensors, one per workgroup size for wide groups, and four for tensors with a single
- * scale (abs-max pass into the plan's scratch, its reduction, apply pass, scale write); ragged tails, groups of up to
- * 512 elements that are no power of two and unquantized tensors ride in one of the first two kinds (large sets of
- * unquantized tensors get a launch of their own), and up to 44 tensors of together 8 million elements are one launch
- * beside the tensor-wise ones.  A plan with more work than one launch can hold (2^32 threads: about 2^35 elements) has
+ * 512-element tiles of block-scaled tensors, one per workgroup size for wide groups, two for tensors with a single scale
+ * that the chip can hold (up to 4.7 million elements on 256 compute units; one pass over memory; a third launch if a
+ * length is no multiple of 8) and four for longer ones (abs-max pass into the plan's scratch, its reduction, apply pass,
+ * scale write); ragged tails, groups of up to 512 elements that are no power of two and unquantized tensors ride in one
+ * of the first two kinds (large sets of unquantized tensors get a launch of their own), and up to 44 tensors of together
+ * 8 million elements are one launch beside the tensor-wise ones.  A plan with more work than one launch can hold (2^32
+ * threads: about 2^35 elements) has
  * these launched in pieces.  Steps of one plan that use that scratch must not overlap each other on different streams.
  * hp->block_size, state_dtype, scale_dtype, opt and mode must equal the plan's, and the device that was current at
  * eco_plan_create must be current (ECO_EINVAL otherwise).

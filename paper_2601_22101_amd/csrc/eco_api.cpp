@@ -117,13 +117,15 @@ struct Lists {                           // the launch lists of one storage form
   std::vector<uint32_t> wide[eco::MAX_WIDE_WAVES + 1];   // wide groups, by waves per unit: one entry per unit
   std::vector<uint32_t> tw_tile;         // tensor-wise: one entry per tile (full or partial)
   std::vector<uint32_t> tw_tensor;       // tensor-wise: the tensors
+  std::vector<uint32_t> slab;            // tensor-wise in one pass: one entry per slab
+  std::vector<uint32_t> resident;        // tensor-wise in one pass: the tensors
   size_t off_tile = 0, off_extra = 0, off_wide[eco::MAX_WIDE_WAVES + 1] = {0}, off_tw_tile = 0, off_tw_tensor = 0, off_slots = 0,
-         off_tile_max = 0;
-  uint64_t tensors = 0;
+         off_tile_max = 0, off_slab = 0, off_resident = 0, off_tail_max = 0, off_slab_max = 0, off_counts = 0, off_deferred = 0;
+  uint64_t tensors = 0, most_tw_tiles = 0, tails = 0;
   std::unique_ptr<eco::SmallArgs> small; // all but the tensor-wise tensors as one launch, where that is the better way
   unsigned small_wgs = 0, small_waves = 1;
   std::vector<uint32_t> &list(int l) {
-    return l == eco::LIST_TILE ? tile : l == eco::LIST_EXTRA ? extra : l == eco::LIST_TW_TILES ? tw_tile : wide[l - eco::LIST_WIDE1 + 1];
+    return l == eco::LIST_TILE ? tile : l == eco::LIST_EXTRA ? extra : l == eco::LIST_TW_TILES ? tw_tile : l == eco::LIST_RESIDENT ? slab : wide[l - eco::LIST_WIDE1 + 1];
   }
 };
 
@@ -289,6 +291,7 @@ struct BuildArgs {
   uint32_t list_pos[BUILD_CHUNK];    // index into the tables of the first of this tensor's `units` entries
   uint32_t units[BUILD_CHUNK];       // entries (tiles or groups) the tensor adds to its launch list
   uint32_t extra_pos[BUILD_CHUNK];   // index of one more entry (a ragged tail, tensor-wise tensor list), or NO_ENTRY
+  uint32_t slot_pos[BUILD_CHUNK];    // the tensor's abs-max slot (tensor-wise scaling), or NO_ENTRY
   uint32_t first_index;              // descriptor index of desc[0]
   uint32_t count;
   unsigned char *scratch;
@@ -308,6 +311,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void eco_noalloc_build_kernel(const 
         src[threadIdx.x];
   }
   if (blockIdx.y == 0 && threadIdx.x == 0 && a.extra_pos[k] != NO_ENTRY) tables[a.extra_pos[k]] = index;
+  if (blockIdx.y == 0 && threadIdx.x == 0 && a.slot_pos[k] != NO_ENTRY) reinterpret_cast<uint32_t *>(a.scratch + OFF_SLOTS)[a.slot_pos[k]] = 0;
   const uint32_t pos = a.list_pos[k], n = a.units[k];
   for (uint32_t i = blockIdx.y * BUILD_THREADS + threadIdx.x; i < n; i += BUILD_BLOCKS_PER_TENSOR * BUILD_THREADS)
     tables[pos + i] = index;
@@ -338,7 +342,7 @@ eco::TensorDesc describe(const eco_tensor_t &t, const eco_hparams_t *layout, con
   d.tensor_id = t.tensor_id;
   const bool plain = p.kind == eco::UNIT_PLAIN_BF16 || p.kind == eco::UNIT_PLAIN_FP32;
   d.group_size = plain ? layout->block_size : p.group;
-  if (p.kind == eco::UNIT_TILES && p.list != eco::LIST_TW_TILES) d.bs_shift = static_cast<uint16_t>(eco::log2_exact(p.group));
+  if (p.kind == eco::UNIT_TILES && p.list < eco::LIST_TW_TILES) d.bs_shift = static_cast<uint16_t>(eco::log2_exact(p.group));
   d.kind = static_cast<uint16_t>(p.tail ? eco::UNIT_TAIL : p.kind);
   d.slot = p.rows;
   d.first_unit = static_cast<uint32_t>(first_unit);
@@ -477,6 +481,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
   plan->opt = layout->opt;
   plan->mode = layout->mode;
 
+  hipError_t e = hipSuccess;
   std::vector<eco::TensorDesc> descs;
   std::vector<uint32_t> host;
   try {
@@ -498,6 +503,15 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       if (in_list > 0x7FFFFFF0ull) st = fail(ECO_EUNSUPPORTED, "plan: more than 2^31 tiles in one launch");
     }
     if (st != ECO_OK) { delete plan; return st; }
+    e = hipGetDevice(&plan->device);
+    if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
+    plan->cus = num_compute_units();
+    // tensors with one scale that the chip can hold
+    const bool bf16 = layout->state_dtype == ECO_DT_BF16;
+    const uint64_t max_slabs = std::min<uint64_t>(eco::res_waves(bf16) * 64, eco::res_slabs_per_wg(bf16) * plan->cus);
+    for (size_t i = 0; i < n; ++i)
+      if (place[i].list == eco::LIST_TW_TILES)
+        place[i] = eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, tensors[i].fmt, eco::res_slab(bf16), max_slabs);
     const int plain_home = home_of_plain(tensors_of, entries_of);
 
     std::vector<SmallItem> items[4];
@@ -515,6 +529,13 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       if (p.list == eco::LIST_TW_TILES) {
         d.slot = static_cast<uint32_t>(g.tw_tensor.size());
         g.tw_tensor.push_back(idx);
+        g.most_tw_tiles = std::max(g.most_tw_tiles, p.units);
+      } else if (p.list == eco::LIST_RESIDENT) {
+        d.slot = static_cast<uint32_t>(t.numel % eco::ELEMS_PER_LANE);
+        d.numel = t.numel - d.slot;
+        d.group_size = g.resident.size();             // its place in the list
+        g.tails += d.slot != 0;
+        g.resident.push_back(idx);
       } else {
         elements[f] += t.numel;
         if (items[f].size() <= static_cast<size_t>(eco::SMALL_TENSORS)) items[f].push_back(SmallItem{&t, p});
@@ -533,7 +554,8 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       if (make_small(items[f], layout, sa.get(), &g.small_wgs, &g.small_waves)) g.small = std::move(sa);
     }
 
-    // one device buffer: per format [full tiles | one-wave units | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots | scratch]
+    // one device buffer: per format [full tiles | one-wave units | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots |
+    // tile maxima | slabs | their tensors | tail maxima | slab maxima | counts | deferred tiles]
     for (Lists &g : plan->lists) {
       const auto add = [&host](const std::vector<uint32_t> &l, size_t *off) {
         *off = host.size();
@@ -549,15 +571,22 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       host.insert(host.end(), g.tw_tensor.size() + 1, 0u);      // abs-max slots start at zero
       g.off_tile_max = host.size();
       host.insert(host.end(), g.tw_tile.size(), 0u);
+      add(g.slab, &g.off_slab);
+      add(g.resident, &g.off_resident);
+      g.off_tail_max = host.size();
+      host.insert(host.end(), g.resident.size(), 0u);
+      g.off_slab_max = host.size();
+      host.insert(host.end(), g.slab.size(), 0xFFFFFFFFu);      // no slab's maximum is known
+      g.off_counts = host.size();
+      host.insert(host.end(), 2, 0u);
+      g.off_deferred = host.size();
+      host.insert(host.end(), g.slab.size() * eco::res_waves(layout->state_dtype == ECO_DT_BF16), 0u);
     }
   } catch (const std::bad_alloc &) {
     delete plan;
     return fail(ECO_ENOMEM, "plan: host allocation failed");
   }
 
-  hipError_t e = hipGetDevice(&plan->device);
-  if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
-  plan->cus = num_compute_units();
   e = hipMalloc(reinterpret_cast<void **>(&plan->d_descs), descs.size() * sizeof(eco::TensorDesc));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&plan->d_tables), host.size() * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemcpy(plan->d_descs, descs.data(), descs.size() * sizeof(eco::TensorDesc), hipMemcpyHostToDevice);
@@ -624,6 +653,18 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     a.tile_max = plan->d_tables + g.off_tile_max;
     a.num_tw_tiles = static_cast<uint32_t>(g.tw_tile.size());
     a.num_tw_tensors = static_cast<uint32_t>(g.tw_tensor.size());
+    a.tw_reduce_wgs = eco::tw_reduce_workgroups(g.most_tw_tiles);
+    a.slab_tensor = plan->d_tables + g.off_slab;
+    a.slab_max = plan->d_tables + g.off_slab_max;
+    a.resident_counts = plan->d_tables + g.off_counts;
+    a.deferred = plan->d_tables + g.off_deferred;
+    a.resident_tensor = plan->d_tables + g.off_resident;
+    a.num_resident = static_cast<uint32_t>(g.resident.size());
+    a.resident_tails = static_cast<uint32_t>(g.tails);
+    a.tail_max = plan->d_tables + g.off_tail_max;
+    a.num_slabs = static_cast<uint32_t>(g.slab.size());
+    a.resident_tries = eco::RES_TRIES;
+    sl.resident_wgs = static_cast<unsigned>(plan->cus);
     eco::SmallArgs small;                  // a copy: steps of one plan may be enqueued by different calls
     if (g.small) { small = *g.small; sl.small_wgs = g.small_wgs; sl.small_waves = g.small_waves; }
     st = launch_format(hp, c, f, plan->cus, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
@@ -658,7 +699,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
 
   // pass 1: validate, place, count the entries of every launch list
   constexpr int L_TW_TENSORS = eco::LIST_COUNT, L_COUNT = eco::LIST_COUNT + 1;
-  uint64_t count[4][L_COUNT] = {{0}}, tensors_of[4] = {0}, entries_of[4] = {0};
+  uint64_t count[4][L_COUNT] = {{0}}, tensors_of[4] = {0}, entries_of[4] = {0}, most_tw_tiles[4] = {0};
   uint64_t total = 0, elements = 0;
   const auto place = [&](size_t i, eco::Placement *p) {
     uint64_t gsz = 0;
@@ -733,7 +774,10 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     const int f = format_of(i);
     count[f][p.list] += p.units;
     if (p.tail) count[f][eco::LIST_EXTRA] += 1;
-    if (p.list == eco::LIST_TW_TILES) count[f][L_TW_TENSORS] += 1;
+    if (p.list == eco::LIST_TW_TILES) {
+      count[f][L_TW_TENSORS] += 1;
+      most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
+    }
   }
   uint32_t start[4][L_COUNT], tw_tile_start[4], tw_tensor_start[4];
   {
@@ -765,10 +809,11 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     ba.list_pos[k] = start[f][p.list] + fill[f][p.list];
     ba.units[k] = static_cast<uint32_t>(p.units);
     fill[f][p.list] += static_cast<uint32_t>(p.units);
-    ba.extra_pos[k] = NO_ENTRY;
+    ba.extra_pos[k] = ba.slot_pos[k] = NO_ENTRY;
     if (p.tail) ba.extra_pos[k] = start[f][eco::LIST_EXTRA] + fill[f][eco::LIST_EXTRA]++;
     if (p.list == eco::LIST_TW_TILES) {
       d.slot = fill[f][L_TW_TENSORS];
+      ba.slot_pos[k] = tw_tensor_start[f] + d.slot;
       ba.extra_pos[k] = start[f][L_TW_TENSORS] + fill[f][L_TW_TENSORS]++;
     }
     if (ba.count == BUILD_CHUNK || i + 1 == n) {
@@ -804,6 +849,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     a.tile_max = reinterpret_cast<uint32_t *>(sp + OFF_TILE_MAX) + tw_tile_start[f];
     a.num_tw_tiles = static_cast<uint32_t>(count[f][eco::LIST_TW_TILES]);
     a.num_tw_tensors = static_cast<uint32_t>(count[f][L_TW_TENSORS]);
+    a.tw_reduce_wgs = eco::tw_reduce_workgroups(most_tw_tiles[f]);
     st = launch_format(hp, c, f, cus, &sl, nullptr, hs);
     if (st != ECO_OK) return st;
   }

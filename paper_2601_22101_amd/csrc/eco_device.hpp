@@ -243,4 +243,18 @@ __device__ __forceinline__ uint32_t group_umax(uint32_t x, int lanes) {
   return x;
 }
 
+// The same over the whole wave, as a wave-uniform value: the last two steps by DPP broadcasts of a row's last lane to the
+// rows behind it, so that lane 63 ends with the maximum (a cross-row swizzle is an LDS round trip).
+__device__ __forceinline__ uint32_t wave_umax(uint32_t x) {
+  x = dpp_umax<0xB1>(x);
+  x = dpp_umax<0x4E>(x);
+  x = dpp_umax<0x141>(x);
+  x = dpp_umax<0x140>(x);
+  uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  x = x > o ? x : o;
+  o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);            // row_bcast:31 into rows 2 and 3
+  x = x > o ? x : o;
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 }  // namespace eco

@@ -52,6 +52,16 @@ enum : int {
   UNIT_WIDE = 5         // groups of 520..8192 elements: a workgroup's unit, see wide_geometry
 };
 
+// Tensor-wise scaling in one pass (eco_step_resident_kernel): slabs of one 512-element tile to each wave of a workgroup,
+// `depth` of them in hand.  The waves and what they hold fill the 512 registers of a SIMD lane: 16 waves with 4 slabs in
+// hand where the next slab's loads are bf16 state (13 registers), 12 with 5 for fp32 state (22).
+constexpr int res_waves(bool state_bf16) { return state_bf16 ? 12 : 12; }
+constexpr int res_depth(bool state_bf16) { return state_bf16 ? 5 : 5; }
+constexpr uint64_t res_slab(bool state_bf16) { return static_cast<uint64_t>(res_waves(state_bf16)) * TILE_ELEMS; }
+// Slabs a tensor may have for each workgroup: the exchange of maxima takes two of the turns in hand.
+constexpr uint64_t res_slabs_per_wg(bool state_bf16) { return static_cast<uint64_t>(res_depth(state_bf16)) - 2; }
+constexpr uint32_t RES_TRIES = 64;           // reads of slab_max[] before a wait is given up, 1.5-2 us each
+
 struct TensorDesc {          // 80 bytes, device table entry
   void *w;                   // weights / codes
   void *s;                   // scales
@@ -65,7 +75,8 @@ struct TensorDesc {          // 80 bytes, device table entry
   uint32_t tensor_id;
   uint16_t bs_shift;         // log2(group_size) for power-of-two groups of 32..512 elements
   uint16_t kind;             // UNIT_*: what a unit of the list the tensor is in stands for
-  uint32_t slot;             // tensor-wise scaling: index of the tensor's abs-max slot; wide groups and UNIT_ROWS: groups per unit
+  uint32_t slot;             // tensor-wise scaling: index of the tensor's abs-max slot; in one pass: elements beyond numel, which
+                             // is a multiple of 8 there; wide groups and UNIT_ROWS: groups per unit
 };
 static_assert(sizeof(TensorDesc) == 80, "TensorDesc layout");
 
@@ -78,7 +89,14 @@ struct StepArgs {            // by-value kernel argument: everything wave-unifor
   const uint32_t *tw_tensor;       //   ... the tensors themselves
   uint32_t *slots;                 //   ... one abs-max slot (fp32 bit pattern) per such tensor
   uint32_t *tile_max;              //   ... scratch: the abs-max of every such tile, written and consumed within a step
-  uint32_t num_tiles, num_extra, num_tw_tiles, num_tw_tensors;
+  const uint32_t *slab_tensor;     // tensor-wise scaling in one pass: slab -> index into tensors
+  uint32_t *slab_max;              //   ... scratch: each slab's abs-max, all ones until it is known; empty again after the step
+  const uint32_t *resident_tensor; //   ... the tensors themselves
+  uint32_t *deferred;              //   ... scratch: tiles that are left to the finishing kernel
+  uint32_t *tail_max;              //   ... scratch: abs-max of the tensors' tails, by place in resident_tensor
+  uint32_t *resident_counts;       //   ... scratch: how many those are; workgroups through with them
+  uint32_t num_tiles, num_extra, num_tw_tiles, num_tw_tensors, num_slabs, num_resident, resident_tails, resident_tries;
+  uint32_t tw_reduce_wgs;          // tensor-wise scaling: workgroups per tensor of the reduction
   float b1, omb1, b2, omb2, rbc2, c1, eps, kappa, lr, alpha, wd, inv_lr, inv_lr_beta;
   uint32_t seed_lo, seed_hi, step_lo;
   uint32_t div_mid;                // c1 and eps allow the short division (see div_rn_midrange) after a short square root
@@ -97,6 +115,11 @@ struct SmallArgs {
 };
 static_assert(sizeof(SmallArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
+inline uint32_t tw_reduce_workgroups(uint64_t most_tiles) {
+  const uint64_t w = (most_tiles + 16383) / 16384;
+  return static_cast<uint32_t>(w < 1 ? 1 : w > 64 ? 64 : w);
+}
+
 // What one format's step launches, host side.
 struct StepLaunch {
   StepArgs args;
@@ -108,6 +131,7 @@ struct StepLaunch {
   const uint32_t *wide_base;       // wide-group lists, one per workgroup size, back to back
   uint32_t wide_offset[MAX_WIDE_WAVES + 1];
   uint32_t num_wide[MAX_WIDE_WAVES + 1];
+  unsigned resident_wgs;           // workgroups of the one-pass tensor-wise kernel: one per compute unit
   int extra_in;                    // which launch the one-wave units ride in: 0 the full-tile one, n the wide groups of n waves
   const SmallArgs *small;          // if set, one launch of the short-list kernel ...
   unsigned small_wgs, small_waves; //   ... with this geometry stands for all of the above but the tensor-wise passes
@@ -181,7 +205,7 @@ inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = 
 inline uint32_t rows_per_wave(uint64_t g) { return static_cast<uint32_t>(TILE_ELEMS / g); }
 
 // What a step does with one tensor: the launch list it enters, the kind of its units there and how many they are.
-enum : int { LIST_TILE = 0, LIST_EXTRA = 1, LIST_WIDE1 = 2, LIST_TW_TILES = LIST_WIDE1 + MAX_WIDE_WAVES, LIST_COUNT };
+enum : int { LIST_TILE = 0, LIST_EXTRA = 1, LIST_WIDE1 = 2, LIST_TW_TILES = LIST_WIDE1 + MAX_WIDE_WAVES, LIST_RESIDENT, LIST_COUNT };
 struct Placement {
   int list;              // LIST_*; LIST_WIDE1 + n - 1: groups that take a workgroup of n waves
   int kind;              // UNIT_*
@@ -191,7 +215,9 @@ struct Placement {
   uint32_t rows;         // groups per unit (wide groups, UNIT_ROWS)
   uint64_t entries;      // what the tensor counts towards the limits on launch tables: a unit per tile or per group
 };
-inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool quantized, int fmt) {
+// slab, max_slabs: the one-pass tensor-wise kernel's slab length and the most slabs of a tensor it may take (0: none).
+inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool quantized, int fmt, uint64_t slab = TILE_ELEMS,
+                              uint64_t max_slabs = 0) {
   Placement p = {LIST_TILE, UNIT_TILES, 0, false, group_size, 1, 0};
   if (cls == GROUP_BLOCK) {
     const bool rest = numel % TILE_ELEMS != 0;
@@ -224,6 +250,12 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
     p.list = LIST_TW_TILES;
     p.units = (numel + TILE_ELEMS - 1) / TILE_ELEMS;
     p.entries = p.units + 1;
+    // one pass where the chip can hold the tensor (its lanes have 8 elements or none; up to 7 last ones are a tail)
+    const uint64_t whole = numel / ELEMS_PER_LANE * ELEMS_PER_LANE, slabs = whole <= slab ? 1 : (whole + slab - 1) / slab;
+    if (slabs <= max_slabs) {
+      p.list = LIST_RESIDENT;
+      p.units = slabs;
+    }
   }
   return p;
 }

@@ -1,5 +1,5 @@
 // Instantiations of the fused ECO step kernel: FP8 codes, fp32 optimizer state.
-#include "eco_step_kernel.hpp"
+#include "eco_step_resident.hpp"
 
 namespace eco {
 hipError_t launch_step_fp8_f32(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {

@@ -38,11 +38,12 @@ template <> struct FmtTraits<FMT_INT4> { static constexpr float RHO = 7.0f; };
 //               elements read as zero and are not written (the ragged tail of a tensor)
 //   ACC_LANE    decided per lane: vector access where nvalid == 8, element-wise elsewhere (wide groups,
 //               whose last lanes may lie beyond the group)
-enum : int { ACC_FULL = 0, ACC_GUARDED = 1, ACC_LANE = 2 };
+//   ACC_WHOLE   all 8 of a lane exist or none (lengths that are multiples of 8): vector access where they do
+enum : int { ACC_FULL = 0, ACC_GUARDED = 1, ACC_LANE = 2, ACC_WHOLE = 3 };
 
 template <int ACC>
 __device__ __forceinline__ bool use_vector(int nvalid) {
-  return ACC == ACC_FULL || (ACC == ACC_LANE && nvalid == 8);
+  return ACC == ACC_FULL || ((ACC == ACC_LANE || ACC == ACC_WHOLE) && nvalid == 8);
 }
 
 template <int ACC>
@@ -54,7 +55,7 @@ __device__ __forceinline__ void load_f32x8(const float *p, int nvalid, float (&o
     out[4] = b.x; out[5] = b.y; out[6] = b.z; out[7] = b.w;
   } else {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) out[j] = j < nvalid ? p[j] : 0.0f;
+    for (int j = 0; j < 8; ++j) out[j] = ACC != ACC_WHOLE && j < nvalid ? p[j] : 0.0f;
   }
 }
 
@@ -66,7 +67,7 @@ __device__ __forceinline__ void load_bf16x8(const uint16_t *p, int nvalid, float
     out[4] = bf16_lo(q.z); out[5] = bf16_hi(q.z); out[6] = bf16_lo(q.w); out[7] = bf16_hi(q.w);
   } else {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) out[j] = j < nvalid ? u2f((uint32_t)p[j] << 16) : 0.0f;
+    for (int j = 0; j < 8; ++j) out[j] = ACC != ACC_WHOLE && j < nvalid ? u2f((uint32_t)p[j] << 16) : 0.0f;
   }
 }
 
@@ -88,7 +89,7 @@ __device__ __forceinline__ void store_f32x8(float *p, int nvalid, const float (&
   if (use_vector<ACC>(nvalid)) {
     store_vec(reinterpret_cast<eco_f32x4_t *>(p), eco_f32x4_t{x[0], x[1], x[2], x[3]});
     store_vec(reinterpret_cast<eco_f32x4_t *>(p) + 1, eco_f32x4_t{x[4], x[5], x[6], x[7]});
-  } else {
+  } else if (ACC != ACC_WHOLE) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       if (j < nvalid) p[j] = x[j];
@@ -102,7 +103,7 @@ __device__ __forceinline__ void store_bf16x8(uint16_t *p, int nvalid, const floa
   for (int j = 0; j < 4; ++j) h[j] = f32x2_to_bf16x2_rne(x[2 * j], x[2 * j + 1]);
   if (use_vector<ACC>(nvalid)) {
     store_vec(reinterpret_cast<eco_u32x4_t *>(p), eco_u32x4_t{h[0], h[1], h[2], h[3]});
-  } else {
+  } else if (ACC != ACC_WHOLE) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       if (j < nvalid) p[j] = (uint16_t)(h[j >> 1] >> (16 * (j & 1)));
@@ -138,7 +139,7 @@ __device__ __forceinline__ void load_codes8(const void *base, uint64_t e0, int n
     constexpr int MAXB = FMT == FMT_FP8 ? 8 : 4;
 #pragma unroll
     for (int k = 0; k < MAXB; ++k)
-      if (k < nbytes) c[k >> 2] |= (uint32_t)p[k] << (8 * (k & 3));
+      if (ACC != ACC_WHOLE && k < nbytes) c[k >> 2] |= (uint32_t)p[k] << (8 * (k & 3));
   }
 }
 
@@ -148,7 +149,7 @@ __device__ __forceinline__ void store_codes8(void *base, uint64_t e0, int nvalid
   if (use_vector<ACC>(nvalid)) {
     if (FMT == FMT_FP8) store_vec(reinterpret_cast<eco_u32x2_t *>(p), eco_u32x2_t{c[0], c[1]});
     else store_vec(reinterpret_cast<uint32_t *>(p), c[0]);
-  } else {
+  } else if (ACC != ACC_WHOLE) {
     const int nbytes = FMT == FMT_FP8 ? nvalid : (nvalid + 1) >> 1;
     constexpr int MAXB = FMT == FMT_FP8 ? 8 : 4;
 #pragma unroll
@@ -163,7 +164,7 @@ __device__ __forceinline__ void fill_missing(float (&x)[8], int nvalid, float va
   if (ACC != ACC_FULL) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      if (j >= nvalid) x[j] = value;
+      if (ACC == ACC_WHOLE ? nvalid == 0 : j >= nvalid) x[j] = value;
   }
 }
 
@@ -359,62 +360,41 @@ __device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t 
   return u2f(r);
 }
 
-// One lane's 8 consecutive elements, starting at element e0 of tensor td, of which the first nvalid exist;
-// scale group number sg; bs_shift = log2(group size) for RED_BLOCK; row = the lane's group within the workgroup for
-// RED_WG_ROWS, the first lane of the lane's group for RED_ROWS.
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC, int RED>
-__device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid,
-                                          uint64_t sg, bool scale_writer, uint32_t *slot, int row = 0) {
-  constexpr bool ADAM = algo_is_adam(ALGO);
-  constexpr bool MASTER = algo_is_master(ALGO);
-  constexpr bool WRITE = RED != RED_ATOMIC && RED != RED_TILE;   // the first pass of a two-pass group writes nothing
-  const bool any = ACC == ACC_FULL || nvalid > 0;
+// A bf16 scale has 8 significant bits and a decoded code at most 4, so dec(c) * s is exact in fp32 (also where it is
+// subnormal: its lowest bit is at least 2^-142) and theta~ = w - u and e = theta~ - dec(c') s' may be formed by one fused
+// multiply-add each: the same real number is rounded once either way.  Until then w holds the decoded values and sc the
+// factor.
+template <bool SCALE_BF16, int ALGO>
+constexpr bool exact_scale() { return SCALE_BF16 && !algo_is_master(ALGO); }
 
-  // A bf16 scale has 8 significant bits and a decoded code at most 4, so dec(c) * s is exact in fp32 (also where
-  // it is subnormal: its lowest bit is at least 2^-142) and theta~ = w - u and e = theta~ - dec(c') s' may be
-  // formed by one fused multiply-add each: the same real number is rounded once either way.  Until then w holds
-  // the decoded values and sc the factor.
-  constexpr bool EXACT_SCALE = SCALE_BF16 && !MASTER;
-  float g[8], m[8], v[8], w[8], sc = 1.0f;
-  load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
-  load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
-  if (ADAM) load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
-  if (MASTER) {
-    load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, w);
-  } else {
-    uint32_t c[2];
-    load_codes8<FMT, ACC>(td.w, e0, nvalid, c);
-    const float s_old = any ? load_scale<SCALE_BF16>(td.s, sg) : 0.0f;
-    sc = decode8<FMT>(c, s_old, w);
-    if (!EXACT_SCALE) {
+// m~, v~ and the argument x = v~ / (1 - b2^k) of the square root; V_FINAL: v already is v~.
+template <int ALGO, bool V_FINAL = false>
+__device__ __forceinline__ void moments_lane(const StepArgs &a, const float (&g)[8], float (&m)[8], float (&v)[8], float (&x)[8]) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) w[j] *= sc;
-    }
-  }
-
-  __builtin_amdgcn_s_setprio(0);      // loads issued: back to the default priority (see eco_step_kernel)
-
-  // OPTIM_STEP on the de-quantized (or master) weights
-  float th[8], d[8], eta[8];
-  if (ADAM) {
-    float x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      m[j] = fmaf(a.b1, m[j], a.omb1 * g[j]);
-      v[j] = fmaf(a.b2, v[j], a.omb2 * (g[j] * g[j]));
+  for (int j = 0; j < 8; ++j) {
+    m[j] = fmaf(a.b1, m[j], a.omb1 * g[j]);
+    if (algo_is_adam(ALGO)) {
+      if (!V_FINAL) v[j] = fmaf(a.b2, v[j], a.omb2 * (g[j] * g[j]));
       x[j] = v[j] * a.rbc2;
     }
-    if (WRITE) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);   // v is final (Alg. 3 returns it unchanged)
+  }
+}
+
+// OPTIM_STEP on the de-quantized (or master) weights: theta~, and d for Adam.
+template <bool SCALE_BF16, int ALGO, int ACC>
+__device__ __forceinline__ void theta_lane(const StepArgs &a, float (&x)[8], float (&w)[8], float sc, const float (&m)[8], int nvalid,
+                                           float (&d)[8], float (&th)[8]) {
+  constexpr bool ADAM = algo_is_adam(ALGO), EXACT_SCALE = exact_scale<SCALE_BF16, ALGO>();
+  float eta[8], u[8];
+  if (ADAM) {
     fill_missing<ACC>(x, nvalid, 1.0f);                              // elements that do not exist decide nothing
     step_sizes8(a, x, d, eta);
   }
-  float u[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     if (ADAM) {
       u[j] = eta[j] * m[j];
     } else {
-      m[j] = fmaf(a.b1, m[j], a.omb1 * g[j]);
       d[j] = 0.0f;
       u[j] = a.lr * m[j];
     }
@@ -439,15 +419,11 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
     for (int j = 0; j < 8; ++j) th[j] = w[j] - u[j];
   }
   fill_missing<ACC>(th, nvalid, 0.0f);
+}
 
-  // ECO_QUANTIZE
-  const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
-                                       RED == RED_ROWS ? (int)(td.group_size >> 3) : 0);
-  if (!WRITE) return;
-  if (MASTER) store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, th);
-  float s_new, inv;
-  block_scale<FMT, SCALE_BF16>(amax, s_new, inv);
-
+// The random words of a lane's 8 elements, counter e0 / 8.
+template <int ROUND>
+__device__ __forceinline__ Philox4 random_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0) {
   Philox4 r = {0, 0, 0, 0};
   if (ROUND == ROUND_SR) {
     const uint64_t q = e0 >> 3;
@@ -461,8 +437,15 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
       r = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.step_lo, td.tensor_id, a.seed_lo, a.seed_hi);
     }
   }
-  uint32_t cn[2];
-  float qn[8];
+  return r;
+}
+
+// ECO_QUANTIZE given the group's abs-max: the new codes, what they decode to and, returned, the new scale.
+template <int FMT, bool SCALE_BF16, int ROUND, int ACC>
+__device__ __forceinline__ float quantize_lane8(float amax, const Philox4 &r, int nvalid, const float (&th)[8], uint32_t (&cn)[2],
+                                                float (&qn)[8]) {
+  float s_new, inv;
+  block_scale<FMT, SCALE_BF16>(amax, s_new, inv);
   if (FMT == FMT_FP8) {
     // the E4M3 subnormal range (|y| < 2^-6) needs a second formula; it is rare, so decide per wave
     // (multiplication by inv >= 0 is monotone, so the smallest |y| is fl(min|theta~| * inv))
@@ -475,26 +458,88 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   } else {
     encode8<FMT, ROUND, true>(th, inv, r, cn, qn);
   }
-  store_codes8<FMT, ACC>(td.w, e0, nvalid, cn);
+  return s_new;
+}
 
+// The quantization error and its injection into m~; eo: the stored error of the exact variant, old in and new out.
+template <bool SCALE_BF16, int ALGO>
+__device__ __forceinline__ void inject_lane8(const StepArgs &a, float s_new, const float (&th)[8], const float (&qn)[8],
+                                             const float (&d)[8], float (&m)[8], float (&eo)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float e = SCALE_BF16 ? fmaf(-qn[j], s_new, th[j]) : th[j] - qn[j] * s_new;   // exact product, see exact_scale
+    if (ALGO == ALGO_ADAM) m[j] = fmaf(a.kappa * d[j], e, m[j]);
+    else if (ALGO == ALGO_SGDM) m[j] = fmaf(a.alpha, e, m[j]);
+    else { m[j] = fmaf(-a.inv_lr_beta, e, fmaf(a.inv_lr, eo[j], m[j])); eo[j] = e; }
+  }
+}
+
+// Both, with the stores: codes, the injected momentum (or master weights); returns the new scale.
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC>
+__device__ __forceinline__ float quantize_inject_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid, float amax,
+                                                      const Philox4 &r, const float (&th)[8], const float (&d)[8], float (&m)[8]) {
+  constexpr bool MASTER = algo_is_master(ALGO);
+  if (MASTER) store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, th);
+  uint32_t cn[2];
+  float qn[8];
+  const float s_new = quantize_lane8<FMT, SCALE_BF16, ROUND, ACC>(amax, r, nvalid, th, cn, qn);
+  store_codes8<FMT, ACC>(td.w, e0, nvalid, cn);
   if (!MASTER) {
     float eo[8];
     if (ALGO == ALGO_SGDM_EXACT) load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, eo);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float e = SCALE_BF16 ? fmaf(-qn[j], s_new, th[j]) : th[j] - qn[j] * s_new;   // exact product, see above
-      if (ALGO == ALGO_ADAM) m[j] = fmaf(a.kappa * d[j], e, m[j]);
-      else if (ALGO == ALGO_SGDM) m[j] = fmaf(a.alpha, e, m[j]);
-      else { m[j] = fmaf(-a.inv_lr_beta, e, fmaf(a.inv_lr, eo[j], m[j])); eo[j] = e; }
-    }
+    inject_lane8<SCALE_BF16, ALGO>(a, s_new, th, qn, d, m, eo);
     if (ALGO == ALGO_SGDM_EXACT) store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, eo);
   }
   store_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+  return s_new;
+}
 
-  if (RED != RED_SLOT && scale_writer && any) {
-    if (SCALE_BF16) static_cast<uint16_t *>(td.s)[sg] = (uint16_t)(f2u(s_new) >> 16);
-    else static_cast<float *>(td.s)[sg] = s_new;
+template <bool SCALE_BF16>
+__device__ __forceinline__ void store_scale(const TensorDesc &td, uint64_t sg, float s) {
+  if (SCALE_BF16) static_cast<uint16_t *>(td.s)[sg] = (uint16_t)(f2u(s) >> 16);
+  else static_cast<float *>(td.s)[sg] = s;
+}
+
+// One lane's 8 consecutive elements, starting at element e0 of tensor td, of which the first nvalid exist;
+// scale group number sg; bs_shift = log2(group size) for RED_BLOCK; row = the lane's group within the workgroup for
+// RED_WG_ROWS, the first lane of the lane's group for RED_ROWS.  LATE: an earlier kernel of the step has stored v~.
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC, int RED, bool LATE = false>
+__device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid,
+                                          uint64_t sg, bool scale_writer, uint32_t *slot, int row = 0) {
+  constexpr bool ADAM = algo_is_adam(ALGO);
+  constexpr bool MASTER = algo_is_master(ALGO);
+  constexpr bool WRITE = RED != RED_ATOMIC && RED != RED_TILE;   // the first pass of a two-pass group writes nothing
+  const bool any = ACC == ACC_FULL || nvalid > 0;
+
+  float g[8], m[8], v[8], w[8], x[8], d[8], th[8], sc = 1.0f;
+  load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
+  load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+  if (ADAM) load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
+  if (MASTER) {
+    load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, w);
+  } else {
+    uint32_t c[2];
+    load_codes8<FMT, ACC>(td.w, e0, nvalid, c);
+    const float s_old = any ? load_scale<SCALE_BF16>(td.s, sg) : 0.0f;
+    sc = decode8<FMT>(c, s_old, w);
+    if (!exact_scale<SCALE_BF16, ALGO>()) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) w[j] *= sc;
+    }
   }
+
+  __builtin_amdgcn_s_setprio(0);      // loads issued: back to the default priority (see eco_step_kernel)
+
+  moments_lane<ALGO, LATE>(a, g, m, v, x);
+  if (ADAM && WRITE && !LATE) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);   // v is final (Alg. 3 returns it unchanged)
+  theta_lane<SCALE_BF16, ALGO, ACC>(a, x, w, sc, m, nvalid, d, th);
+
+  const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
+                                       RED == RED_ROWS ? (int)(td.group_size >> 3) : 0);
+  if (!WRITE) return;
+  const Philox4 r = random_lane<ROUND>(a, td, e0);
+  const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC>(a, td, e0, nvalid, amax, r, th, d, m);
+  if (RED != RED_SLOT && scale_writer && any) store_scale<SCALE_BF16>(td, sg, s_new);
 }
 
 // The launch tables are read-only for the lifetime of a launch; reading them through the constant
@@ -729,21 +774,27 @@ __global__ __launch_bounds__(WG_THREADS) void eco_step_tensorwise_kernel(const S
     step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_GUARDED, RED>(a, td, e0, valid_from(e0, td.numel), 0, false, slot);
 }
 
+// tw_reduce_wgs workgroups per tensor (one for every 16 384 tiles of the longest), which meet in its slot (zero until
+// then; the scale kernel leaves it so): one alone took 158 us over the 409 600 tiles of an embedding, a serial read of
+// 1.6 MB; 26 take 6 us.
 constexpr int TW_REDUCE_THREADS = 1024;
 template <int FMT>   // a template only so that every translation unit may hold its own copy
 __global__ __launch_bounds__(TW_REDUCE_THREADS) void eco_tensorwise_reduce_kernel(const StepArgs a) {
-  const TensorDesc td = load_tensor_desc(a, a.tw_tensor[blockIdx.x + a.unit_base]);
+  const uint32_t unit = blockIdx.x + a.unit_base;
+  const TensorDesc td = load_tensor_desc(a, a.tw_tensor[unit / a.tw_reduce_wgs]);
   const uint64_t ntiles = (td.numel + TILE_ELEMS - 1) / TILE_ELEMS;
+  const uint64_t first = (uint64_t)(unit % a.tw_reduce_wgs) * TW_REDUCE_THREADS;
+  if (first >= ntiles) return;
   const uint32_t *tm = a.tile_max + td.first_unit;
   uint32_t r = 0;
-  for (uint64_t i = threadIdx.x; i < ntiles; i += TW_REDUCE_THREADS) { const uint32_t x = tm[i]; r = r > x ? r : x; }
+  for (uint64_t i = first + threadIdx.x; i < ntiles; i += (uint64_t)TW_REDUCE_THREADS * a.tw_reduce_wgs) { const uint32_t x = tm[i]; r = r > x ? r : x; }
   r = group_umax(r, 64);
   __shared__ uint32_t wave_max[TW_REDUCE_THREADS / 64];
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = r;
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int k = 1; k < TW_REDUCE_THREADS / 64; ++k) { const uint32_t o = wave_max[k]; r = r > o ? r : o; }
-    a.slots[td.slot] = r;
+    atomicMax(&a.slots[td.slot], r);
   }
 }
 
@@ -754,8 +805,8 @@ __global__ __launch_bounds__(WG_THREADS) void eco_tensorwise_scale_kernel(const 
   const TensorDesc td = load_tensor_desc(a, a.tw_tensor[i]);
   float s_new, inv;
   block_scale<FMT, SCALE_BF16>(u2f(a.slots[td.slot]), s_new, inv);
-  if (SCALE_BF16) static_cast<uint16_t *>(td.s)[0] = (uint16_t)(f2u(s_new) >> 16);
-  else static_cast<float *>(td.s)[0] = s_new;
+  store_scale<SCALE_BF16>(td, 0, s_new);
+  a.slots[td.slot] = 0;
 }
 
 inline unsigned lds_cap(unsigned bytes) { return bytes < 65536u ? bytes : 65536u; }   // per-workgroup request limit
@@ -789,6 +840,9 @@ hipError_t launch_in_chunks(Kernel kernel, uint64_t units, unsigned block, unsig
   } while (0)
 
 template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
+hipError_t launch_resident(const StepLaunch &sl, hipStream_t stream);      // eco_step_resident.hpp
+
+template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
 hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
   const StepArgs &args = sl.args;
   if (sl.small) {
@@ -814,10 +868,15 @@ hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
                            64 * nw, lds_cap(sl.lds_bytes_wave * nw), stream, wa, sl.max_launch_threads);
     }
   }
+  if (args.num_slabs) {
+    const hipError_t e = launch_resident<FMT, STATE_BF16, SC, RD, AL>(sl, stream);
+    if (e != hipSuccess) return e;
+  }
   if (args.num_tw_tiles) {
     ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_TILE>), args.num_tw_tiles, WG_THREADS,
                        sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
-    ECO_CHUNKS_CHECKED((eco_tensorwise_reduce_kernel<FMT>), args.num_tw_tensors, TW_REDUCE_THREADS, 0, stream, args, sl.max_launch_threads);
+    ECO_CHUNKS_CHECKED((eco_tensorwise_reduce_kernel<FMT>), (uint64_t)args.num_tw_tensors * args.tw_reduce_wgs, TW_REDUCE_THREADS, 0, stream,
+                       args, sl.max_launch_threads);
     ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_SLOT>), args.num_tw_tiles, WG_THREADS,
                        sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
     ECO_CHUNKS_CHECKED((eco_tensorwise_scale_kernel<FMT, SC>), (args.num_tw_tensors + WG_THREADS - 1) / WG_THREADS, WG_THREADS,
