@@ -217,9 +217,9 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
  *   src    : device, numel values of src_dtype (ECO_DT_FP32 or ECO_DT_BF16)
  *   weights, scales : device outputs, laid out as in eco_tensor_t
  * fmt must be ECO_FMT_FP8_E4M3 or ECO_FMT_INT4; group_size as in eco_tensor_t (not 0).  Asynchronous on `stream`.
- * With one scale for a tensor of more than 8192 elements the abs-max is kept in a library-owned slot between
- * the call's kernels; the library hands out 64 such slots in turn and makes a call wait, on its own stream, for
- * the previous user of its slot, so calls on different streams may overlap.
+ * With one scale for a tensor of more than 8192 elements up to 256 partial maxima are kept in a library-owned slot
+ * between the call's two kernels; the library hands out 64 such slots in turn and makes a call wait, on its own stream,
+ * for the previous user of its slot, so calls on different streams may overlap.
  * Size limit, for this call, eco_dequantize and eco_quantize_error alike: what one kernel launch holds (fewer than
  * 2^32 threads, one thread per 8 elements: just under 2^35 elements; less for groups of 520..8192 elements whose
  * length is far from a multiple of 512).  Larger arrays are ECO_EUNSUPPORTED: pass slices of whole scale groups.

@@ -45,20 +45,19 @@ hipError_t launch_step(const KernelVariant &kv, const StepLaunch &sl, hipStream_
 
 // ------------------------------------------------------------------------ initial quantizer
 // q(x) of Sec. 3.1 with nearest-even rounding over one flat tensor, for the three classes of scale
-// groups (in-wave blocks, one workgroup per wide group, one scale for the whole tensor in two passes).
-// The two-pass form keeps its abs-max, between its kernels, in one of QUANT_SLOTS file-scope slots; the host
+// groups (in-wave groups, wide groups, one scale for the whole tensor in two passes).
+// The two-pass form keeps its partial maxima, between its kernels, in one of QUANT_SLOTS file-scope slots; the host
 // hands the slots out in turn and makes a call wait (on its own stream) for the previous user of its slot, so
 // calls on different streams never share a slot that is in use.
-constexpr int QUANT_SLOTS = 64;
-__device__ uint32_t g_quantize_slots[QUANT_SLOTS];     // zero at load; every call leaves its slot at zero again
+constexpr int QUANT_SLOTS = 64, QUANT_PARTS = 256;
+__device__ uint32_t g_quantize_parts[QUANT_SLOTS][QUANT_PARTS];
 
 template <int FMT, bool SCALE_BF16, bool SRC_BF16, int ACC, int RED>
 __device__ __forceinline__ void quantize_lane(const void *src, void *weights, void *scales, uint64_t e0, int nvalid,
-                                              uint64_t sg, int shift, bool scale_writer, uint32_t slot = 0) {
+                                              uint64_t sg, int arg, bool scale_writer, int lanes = 0, uint32_t *slot = nullptr) {
   float x[8];
   load_state8<SRC_BF16, ACC>(src, e0, nvalid, x);
-  const float amax = group_absmax<RED>(absmax8(x), shift, &g_quantize_slots[slot]);
-  if (RED == RED_ATOMIC) return;
+  const float amax = group_absmax<RED>(absmax8(x), arg, slot, lanes);
   float s_new, inv;
   block_scale<FMT, SCALE_BF16>(amax, s_new, inv);
   uint32_t c[2];
@@ -66,7 +65,7 @@ __device__ __forceinline__ void quantize_lane(const void *src, void *weights, vo
   float q[8];
   encode8<FMT, ROUND_RTN, false>(x, inv, none, c, q);
   store_codes8<FMT, ACC>(weights, e0, nvalid, c);
-  if (RED != RED_SLOT && scale_writer && (ACC == ACC_FULL || nvalid > 0)) {
+  if (scale_writer && (ACC == ACC_FULL || nvalid > 0)) {
     if (SCALE_BF16) static_cast<uint16_t *>(scales)[sg] = (uint16_t)(f2u(s_new) >> 16);
     else static_cast<float *>(scales)[sg] = s_new;
   }
@@ -84,34 +83,95 @@ __global__ __launch_bounds__(WG_THREADS) void eco_quantize_kernel(const void *sr
                                                                      e0 >> bs_shift, (int)bs_shift, writer);
 }
 
+// Groups of up to 512 elements that are no power of two: `rows` whole groups to a wave.
 template <int FMT, bool SCALE_BF16, bool SRC_BF16>
-__global__ __launch_bounds__(1024) void eco_quantize_wide_kernel(const void *src, uint64_t numel, uint64_t group_size,
+__global__ __launch_bounds__(WG_THREADS) void eco_quantize_rows_kernel(const void *src, uint64_t numel, uint32_t group_size, uint32_t rows,
+                                                                       void *weights, void *scales) {
+  const uint32_t gl = group_size >> 3, row = (threadIdx.x * (65536u / gl + 1u)) >> 16;    // lane / lanes of a group, exact below 64
+  const uint64_t grp = (uint64_t)blockIdx.x * rows, e0 = grp * group_size + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
+  const uint64_t end = (grp + rows) * group_size;
+  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_ROWS>(src, weights, scales, e0, valid_from(e0, end < numel ? end : numel),
+                                                               grp + row, (int)(row * gl), threadIdx.x == row * gl, (int)gl);
+}
+
+// Wide groups: one to a workgroup, or as many as fill a whole number of waves (see wide_geometry).
+template <int FMT, bool SCALE_BF16, bool SRC_BF16>
+__global__ __launch_bounds__(1024) void eco_quantize_wide_kernel(const void *src, uint64_t numel, uint32_t group_size, uint32_t rows,
                                                                  void *weights, void *scales) {
-  const uint64_t start = (uint64_t)blockIdx.x * group_size;
+  const uint64_t grp = (uint64_t)blockIdx.x * rows, start = grp * group_size;
+  const uint32_t lane_elem = threadIdx.x * ELEMS_PER_LANE;
+  const uint64_t e0 = start + lane_elem;
+  if (rows > 1) {
+    uint32_t row = 0;
+    for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * group_size ? 1u : 0u;
+    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_FULL, RED_WG_ROWS>(src, weights, scales, e0, 8, grp + row, (int)row,
+                                                                    lane_elem == row * group_size);
+    return;
+  }
   const uint64_t end = start + group_size < numel ? start + group_size : numel;
-  const uint64_t e0 = start + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
-  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_WG>(src, weights, scales, e0, valid_from(e0, end), blockIdx.x, 0,
-                                                             threadIdx.x == 0);
+  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_WG>(src, weights, scales, e0, valid_from(e0, end), grp, 0, threadIdx.x == 0);
 }
 
-template <int FMT, bool SCALE_BF16, bool SRC_BF16, int RED>
-__global__ __launch_bounds__(WG_THREADS) void eco_quantize_tensorwise_kernel(const void *src, uint64_t numel, void *weights,
-                                                                             void *scales, uint32_t slot) {
-  const uint64_t e0 = (uint64_t)blockIdx.x * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
-  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED>(src, weights, scales, e0, valid_from(e0, numel), 0, 0, false, slot);
+// Tensor-wise, first pass: the maximum over each workgroup's share.  One workgroup per partial maximum, which is stored, not
+// merged: an atomic maximum per wave on one address took 220 us over 210 M bf16 elements, the read itself 68.
+constexpr int QUANT_MAX_THREADS = 1024;
+template <bool SRC_BF16>
+__global__ __launch_bounds__(QUANT_MAX_THREADS) void eco_quantize_max_kernel(const void *src, uint64_t numel, uint32_t slot) {
+  const uint64_t stride = (uint64_t)gridDim.x * QUANT_MAX_THREADS * ELEMS_PER_LANE;
+  uint64_t e0 = ((uint64_t)blockIdx.x * QUANT_MAX_THREADS + threadIdx.x) * ELEMS_PER_LANE;
+  float amax = 0.0f, x[4][8];
+  for (; e0 + 3 * stride + 8 <= numel; e0 += 4 * stride) {      // four independent loads under way
+#pragma unroll
+    for (int k = 0; k < 4; ++k) load_state8<SRC_BF16, ACC_FULL>(src, e0 + k * stride, 8, x[k]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) amax = __builtin_fmaxf(amax, absmax8(x[k]));
+  }
+  for (; e0 < numel; e0 += stride) {
+    load_state8<SRC_BF16, ACC_LANE>(src, e0, valid_from(e0, numel), x[0]);
+    amax = __builtin_fmaxf(amax, absmax8(x[0]));
+  }
+  __shared__ uint32_t wave_max[QUANT_MAX_THREADS / 64];
+  const uint32_t w = wave_umax(f2u(amax));
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = w;
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const uint32_t r = wave_umax(threadIdx.x < QUANT_MAX_THREADS / 64 ? wave_max[threadIdx.x] : 0u);
+    if (threadIdx.x == 0) g_quantize_parts[slot][blockIdx.x] = r;
+  }
 }
 
-template <int FMT, bool SCALE_BF16>
-__global__ void eco_quantize_tensorwise_scale_kernel(void *scales, uint32_t slot) {
+// Second pass: every workgroup folds the partial maxima (its loads of them and of its elements are under way together);
+// the first writes the scale.
+template <int FMT, bool SCALE_BF16, bool SRC_BF16>
+__global__ __launch_bounds__(QUANT_PARTS) void eco_quantize_tensorwise_kernel(const void *src, uint64_t numel, uint32_t parts,
+                                                                              void *weights, void *scales, uint32_t slot) {
+  const uint64_t e0 = ((uint64_t)blockIdx.x * QUANT_PARTS + threadIdx.x) * ELEMS_PER_LANE;
+  const int nvalid = valid_from(e0, numel);
+  const uint32_t part = threadIdx.x < parts ? g_quantize_parts[slot][threadIdx.x] : 0u;
+  float x[8];
+  load_state8<SRC_BF16, ACC_LANE>(src, e0, nvalid, x);
+  __shared__ uint32_t wave_max[QUANT_PARTS / 64];
+  const uint32_t w = wave_umax(part);
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = w;
+  __syncthreads();
+  uint32_t r = wave_max[0];
+#pragma unroll
+  for (int k = 1; k < QUANT_PARTS / 64; ++k) r = r > wave_max[k] ? r : wave_max[k];
   float s_new, inv;
-  block_scale<FMT, SCALE_BF16>(u2f(g_quantize_slots[slot]), s_new, inv);
-  if (SCALE_BF16) static_cast<uint16_t *>(scales)[0] = (uint16_t)(f2u(s_new) >> 16);
-  else static_cast<float *>(scales)[0] = s_new;
-  g_quantize_slots[slot] = 0;
+  block_scale<FMT, SCALE_BF16>(u2f(r), s_new, inv);
+  uint32_t c[2];
+  const Philox4 none = {0, 0, 0, 0};
+  float q[8];
+  encode8<FMT, ROUND_RTN, false>(x, inv, none, c, q);
+  store_codes8<FMT, ACC_LANE>(weights, e0, nvalid, c);
+  if (e0 == 0) {
+    if (SCALE_BF16) static_cast<uint16_t *>(scales)[0] = (uint16_t)(f2u(s_new) >> 16);
+    else static_cast<float *>(scales)[0] = s_new;
+  }
 }
 
-// Hands out the abs-max slots of the two-pass quantizer.  A slot is free again once the scale kernel of its
-// last user has run; the event recorded behind that kernel is what the next user of the slot waits for.
+// Hands out the slots of the two-pass quantizer.  A slot is free again once the second pass of its last user has run; the
+// event recorded behind that kernel is what the next user of the slot waits for.
 struct QuantSlotRing {
   static constexpr int MAX_DEVICES = 32;
   std::mutex mu;
@@ -129,10 +189,13 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
     ECO_LAUNCH_CHECKED((eco_quantize_kernel<FMT, SC, SR>), dim3((unsigned)tiles), dim3(WG_THREADS), 0, stream, src, numel,
                        (uint32_t)log2_exact(group_size), weights, scales);
   } else if (cls == GROUP_WIDE) {
-    const uint64_t g = group_size < numel ? group_size : numel;
-    const unsigned nw = (unsigned)((g + TILE_ELEMS - 1) / TILE_ELEMS);
-    ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR>), dim3((unsigned)((numel + g - 1) / g)), dim3(64 * nw), 0,
-                       stream, src, numel, g, weights, scales);
+    const Placement p = place_tensor(numel, group_size, cls, true, FMT);
+    if (p.kind == UNIT_ROWS)
+      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR>), dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel,
+                         (uint32_t)p.group, p.rows, weights, scales);
+    else
+      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR>), dim3((unsigned)p.units), dim3(64 * (p.list - LIST_WIDE1 + 1)), 0, stream,
+                         src, numel, (uint32_t)p.group, p.rows, weights, scales);
   } else {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -148,11 +211,12 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
       e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
       if (e != hipSuccess) { done = nullptr; return e; }
     }
-    ECO_LAUNCH_CHECKED((eco_quantize_tensorwise_kernel<FMT, SC, SR, RED_ATOMIC>), dim3((unsigned)tiles), dim3(WG_THREADS), 0,
-                       stream, src, numel, weights, scales, slot);
-    ECO_LAUNCH_CHECKED((eco_quantize_tensorwise_kernel<FMT, SC, SR, RED_SLOT>), dim3((unsigned)tiles), dim3(WG_THREADS), 0,
-                       stream, src, numel, weights, scales, slot);
-    ECO_LAUNCH_CHECKED((eco_quantize_tensorwise_scale_kernel<FMT, SC>), dim3(1), dim3(1), 0, stream, scales, slot);
+    constexpr uint64_t max_share = (uint64_t)QUANT_MAX_THREADS * ELEMS_PER_LANE, share = (uint64_t)QUANT_PARTS * ELEMS_PER_LANE;
+    const uint64_t want = (numel + max_share - 1) / max_share;
+    const uint32_t parts = want < QUANT_PARTS ? (uint32_t)want : QUANT_PARTS;
+    ECO_LAUNCH_CHECKED((eco_quantize_max_kernel<SR>), dim3(parts), dim3(QUANT_MAX_THREADS), 0, stream, src, numel, slot);
+    ECO_LAUNCH_CHECKED((eco_quantize_tensorwise_kernel<FMT, SC, SR>), dim3((unsigned)((numel + share - 1) / share)), dim3(QUANT_PARTS), 0,
+                       stream, src, numel, parts, weights, scales, slot);
     e = hipEventRecord(done, stream);
     if (e != hipSuccess) return e;
   }
@@ -180,28 +244,48 @@ hipError_t launch_quantize_init(const void *src, int src_bf16, uint64_t numel, i
 // quantization error e = theta - q(theta) of the notation paragraph of Sec. 3.1 (one multiplication, one
 // subtraction, each rounded to fp32).
 // A lane's 8 elements may straddle two groups when the group size is not a multiple of 8, so the scale
-// index is taken per element.
+// index is then taken per element.
+// Threads of a workgroup: one wave where the output is most of the traffic (16 M FP8 elements 14.3 us, with four waves 15.0),
+// two where a source is read beside it.
+constexpr int dequant_threads(int src) { return src == 0 ? 64 : 128; }
+// The group of a lane: a shift where the group size is a power of two, else a product with its reciprocal in double
+// precision (exact to within one for the 2^35 elements of a call, then corrected); a 64-bit division is ~150 instructions
+// and made the kernel arithmetic bound.
+struct GroupOf { uint64_t size; double reciprocal; int32_t shift; };       // shift < 0: no power of two
+
 template <int FMT, bool SCALE_BF16, int SRC>
-__global__ __launch_bounds__(WG_THREADS) void eco_dequantize_kernel(const void *weights, const void *scales,
-                                                                    uint64_t numel, uint64_t group_size, const void *src,
-                                                                    float *dst) {
-  const uint64_t e0 = (uint64_t)blockIdx.x * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
+__global__ __launch_bounds__(dequant_threads(SRC)) void eco_dequantize_kernel(const void *weights, const void *scales, uint64_t numel,
+                                                                         GroupOf group, const void *src, float *dst) {
+  const uint64_t e0 = ((uint64_t)blockIdx.x * dequant_threads(SRC) + threadIdx.x) * ELEMS_PER_LANE;
   const int nvalid = valid_from(e0, numel);
   if (nvalid == 0) return;
   uint32_t c[2];
   load_codes8<FMT, ACC_LANE>(weights, e0, nvalid, c);
-  const uint64_t sg = e0 / group_size;
-  const uint64_t boundary = (sg + 1) * group_size - e0;     // elements of this lane before the next group starts
+  float t[8];
+  if (SRC != 0) load_state8<SRC == 2, ACC_LANE>(src, e0, nvalid, t);
+  uint64_t sg;
+  if (group.shift >= 0) {
+    sg = e0 >> group.shift;
+  } else {
+    sg = (uint64_t)((double)e0 * group.reciprocal);
+    const int64_t rest = (int64_t)(e0 - sg * group.size);
+    if (rest < 0) --sg;
+    else if (rest >= (int64_t)group.size) ++sg;
+  }
   const float s0 = load_scale<SCALE_BF16>(scales, sg);
-  const float s1 = boundary < (uint64_t)nvalid ? load_scale<SCALE_BF16>(scales, sg + 1) : s0;
   float x[8];
   x[0] = decode_elem<FMT, 0>(c); x[1] = decode_elem<FMT, 1>(c); x[2] = decode_elem<FMT, 2>(c); x[3] = decode_elem<FMT, 3>(c);
   x[4] = decode_elem<FMT, 4>(c); x[5] = decode_elem<FMT, 5>(c); x[6] = decode_elem<FMT, 6>(c); x[7] = decode_elem<FMT, 7>(c);
+  if (group.size % ELEMS_PER_LANE == 0) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) x[j] *= ((uint64_t)j < boundary ? s0 : s1);
+    for (int j = 0; j < 8; ++j) x[j] *= s0;
+  } else {                                                  // the next group may start within the lane
+    const uint64_t boundary = (sg + 1) * group.size - e0;
+    const float s1 = boundary < (uint64_t)nvalid ? load_scale<SCALE_BF16>(scales, sg + 1) : s0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] *= ((uint64_t)j < boundary ? s0 : s1);
+  }
   if (SRC != 0) {
-    float t[8];
-    load_state8<SRC == 2, ACC_LANE>(src, e0, nvalid, t);
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = t[j] - x[j];
   }
@@ -211,10 +295,15 @@ __global__ __launch_bounds__(WG_THREADS) void eco_dequantize_kernel(const void *
 // src_kind: 0 = no source (plain de-quantization), 1 = fp32 source, 2 = bf16 source (dst = src - q)
 hipError_t launch_dequantize(const void *weights, const void *scales, uint64_t numel, int fmt, uint64_t group_size,
                              int scale_bf16, const void *src, int src_kind, float *dst, hipStream_t stream) {
-  const unsigned tiles = (unsigned)((numel + TILE_ELEMS - 1) / TILE_ELEMS);
-#define ECO_LAUNCH(F, SC, SK)                                                                                          \
-  ECO_LAUNCH_CHECKED((eco_dequantize_kernel<F, SC, SK>), dim3(tiles), dim3(WG_THREADS), 0, stream, weights, scales, numel, \
-                     group_size, src, dst)
+  const unsigned threads = (unsigned)dequant_threads(src_kind);
+  const uint64_t share = (uint64_t)threads * ELEMS_PER_LANE;
+  const unsigned wgs = (unsigned)((numel + share - 1) / share);
+  // a group that holds the whole tensor: any power of two beyond it does, and no lane crosses its end
+  GroupOf group = {group_size, 1.0 / (double)group_size, log2_exact(group_size)};
+  if (group_size >= numel) group = {1ull << 62, 0.0, 62};
+#define ECO_LAUNCH(F, SC, SK)                                                                                                 \
+  ECO_LAUNCH_CHECKED((eco_dequantize_kernel<F, SC, SK>), dim3(wgs), dim3(threads), 0, stream, weights, scales, numel, \
+                     group, src, dst)
 #define ECO_LAUNCH_SRC(F, SC)                                                                                          \
   do {                                                                                                                 \
     if (src_kind == 0) ECO_LAUNCH(F, SC, 0); else if (src_kind == 1) ECO_LAUNCH(F, SC, 1); else ECO_LAUNCH(F, SC, 2);  \

@@ -295,15 +295,13 @@ __device__ __forceinline__ void step_sizes8(const StepArgs &a, const float (&x)[
 //   RED_WG     the group is the whole workgroup (1..16 waves): wave all-reduce, then an LDS combine
 //   RED_WG_ROWS the workgroup holds up to 16 whole groups of more than 512 elements each (a wave meets at most two of
 //              them): per wave one all-reduce for each of its groups, LDS atomic max into the group's entry
-//   RED_ATOMIC first pass of a group larger than a workgroup, one group at a time (the initial quantizer):
-//              wave all-reduce, one atomic max per wave into the group's slot; nothing else is written
-//   RED_TILE   first pass of the step for such groups (tensor-wise scaling): wave all-reduce, the wave's
+//   RED_TILE   first pass of the step for a group larger than a workgroup (tensor-wise scaling): wave all-reduce, the wave's
 //              maximum goes to its tile's entry of a scratch array, which a small kernel folds into the
 //              tensor's slot (tens of thousands of atomics on one address serialize in the memory system)
 //   RED_ROWS   groups of any length up to 512, several to a wave: segmented all-reduce over the group's lanes
 //   RED_SLOT   second pass: the abs-max is read from that slot; everything is recomputed and written
 //              except the scale (a last, tiny kernel writes it once every tile has used the old one)
-enum : int { RED_BLOCK = 0, RED_WG = 1, RED_ATOMIC = 2, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS = 5, RED_ROWS = 6 };
+enum : int { RED_BLOCK = 0, RED_WG = 1, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS = 5, RED_ROWS = 6 };
 
 constexpr uint32_t WG_ROWS = 16;
 // arg: RED_BLOCK: log2(group size); RED_WG_ROWS: which of the workgroup's groups the lane belongs to; RED_ROWS: the
@@ -338,13 +336,6 @@ __device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t 
     return u2f(row_max[arg]);
   }
   const uint32_t wmax = group_umax(f2u(lane_max), 64);
-  if (RED == RED_ATOMIC) {
-    // the slot only grows, so a wave whose maximum does not exceed what the slot already holds has
-    // nothing to add; the read goes to the device-coherent cache level, and the atomic is what decides
-    if ((threadIdx.x & 63) == 0 && wmax > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(slot, wmax);
-    return 0.0f;
-  }
   if (RED == RED_TILE) {
     if ((threadIdx.x & 63) == 0) *slot = wmax;
     return 0.0f;
@@ -508,7 +499,7 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
                                           uint64_t sg, bool scale_writer, uint32_t *slot, int row = 0) {
   constexpr bool ADAM = algo_is_adam(ALGO);
   constexpr bool MASTER = algo_is_master(ALGO);
-  constexpr bool WRITE = RED != RED_ATOMIC && RED != RED_TILE;   // the first pass of a two-pass group writes nothing
+  constexpr bool WRITE = RED != RED_TILE;   // the first pass of a two-pass group writes nothing
   const bool any = ACC == ACC_FULL || nvalid > 0;
 
   float g[8], m[8], v[8], w[8], x[8], d[8], th[8], sc = 1.0f;

@@ -82,3 +82,45 @@ def test_identity_weights_step_alike_alone_and_beside_quantized_tensors(opt, noa
         got.append(mine)
     assert not torch.equal(got[0][0], w)
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("fmt,scale_bf16", [(0, False), (1, True)])
+@pytest.mark.parametrize("src_bf16", [False, True])
+@pytest.mark.parametrize("numel", [5, 8201, 256 * 8 * 3 + 1, 1024 * 8 * 256 + 8, 1024 * 8 * 256 * 5 + 4099])
+def test_tensor_wise_quantizer_at_the_edges_of_its_shares(fmt, scale_bf16, src_bf16, numel):
+    """One partial maximum per 8192 elements up to 256 of them, then several turns to a workgroup; the largest element in
+    the first and in the last place."""
+    import numpy as np
+
+    from paper_2601_22101_amd import binding as eco
+    o32 = oracle.get("f32")
+    gen = torch.Generator(device=DEV).manual_seed(numel)
+    for at in (0, numel - 1):
+        x = torch.randn(numel, generator=gen, device=DEV) * 0.02
+        x[at] = -0.5
+        src = x.to(torch.bfloat16) if src_bf16 else x
+        codes = torch.zeros(numel if fmt == 0 else (numel + 1) // 2, dtype=torch.uint8, device=DEV)
+        scales = torch.zeros(1, dtype=torch.bfloat16 if scale_bf16 else torch.float32, device=DEV)
+        eco.eco_quantize_init(src, int(src_bf16), numel, fmt, numel, int(scale_bf16), codes, scales)
+        rc, rs = o32.quantize_rtn(oracle.FMT_E4M3 if fmt == 0 else oracle.FMT_INT4, src.float().cpu().numpy(), numel, scale_bf16=scale_bf16)
+        assert np.array_equal(codes.cpu().numpy(), rc) and float(scales.float()[0]) == float(rs[0])
+
+
+@pytest.mark.parametrize("group", [9, 13, 100, 768, 1000, 1500, 3 * 4096])
+@pytest.mark.parametrize("fmt", [0, 1])
+def test_dequantizer_finds_the_group_of_every_element(fmt, group):
+    """Group lengths that are no power of two, multiples of 8 or not: all codes 1.0 (4 in INT4: 4.0) and scales that name
+    their group."""
+    from paper_2601_22101_amd import binding as eco
+    n = 300 * group + group // 2
+    groups = -(-n // group)
+    codes = torch.full((n if fmt == 0 else (n + 1) // 2,), 0x38 if fmt == 0 else 0x44, dtype=torch.uint8, device=DEV)
+    scales = torch.arange(1, groups + 1, device=DEV, dtype=torch.float32)
+    out = torch.zeros(n, device=DEV)
+    eco.eco_dequantize(codes, scales, n, fmt, group, 0, out)
+    ref = scales.repeat_interleave(group)[:n] * (1.0 if fmt == 0 else 4.0)
+    assert torch.equal(out, ref)
+    src = torch.randn(n, device=DEV)
+    err = torch.zeros(n, device=DEV)
+    eco.eco_quantize_error(src, 0, codes, scales, n, fmt, group, 0, err)
+    assert torch.equal(err, src - ref)
