@@ -147,10 +147,15 @@ int num_compute_units() {
 }
 
 // Resident waves per compute unit at which the full-tile step kernel measured fastest on MI355X, by bytes
-// moved per 512-element tile (fp32 state: the kernel is bound by HBM, which delivers most with roughly
-// 100-120 KB of tile traffic in flight per compute unit; bf16 state: bound by instruction issue, no cap: 0).
+// moved per 512-element tile: HBM delivers most with a certain amount of tile traffic in flight per compute unit, and
+// more waves than that only add latency.  bf16 state, Adam (us, without a cap -> with it): INT4, 1.39 G elements, 2689 ->
+// 2470 at 21 waves (2558 at 18, 2655 at 25); FP8, 0.42 G elements, 885 -> 824 at 18 (857 at 21, 855 at 16), with master weights 1423 -> 1310 at 12 (1381 at 16).
 int default_waves(const eco::KernelVariant &kv) {
-  if (kv.state_bf16 || kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) return 0;
+  if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) return 0;
+  if (kv.state_bf16) {
+    if (kv.algo == eco::ALGO_ADAM) return kv.fmt == eco::FMT_INT4 ? 21 : 18;
+    return kv.algo == eco::ALGO_ADAM_MASTER ? 12 : 0;
+  }
   switch (kv.algo) {
     case eco::ALGO_ADAM: return 12;          // 20.1 B/parameter
     case eco::ALGO_ADAM_MASTER: return 8;    // 27.0
@@ -160,8 +165,26 @@ int default_waves(const eco::KernelVariant &kv) {
   }
 }
 
-// The cap is expressed as a dynamic-LDS request the kernels never touch (160 KB of LDS per compute unit).
-// For Adam the wide-group kernel measured best at the same cap, the two tensor-wise passes with four waves more.
+// The same for the wide-group kernel, whose workgroups of 2..16 waves come and go together.  Measured (us, 33-130 M
+// elements in rows of the named length; in parentheses the waves resident): Adam with fp32 state, rows of 1000: 472 (16),
+// 497 (14), 545 (12), 527 (no cap); 768: 340 (15), 337 (12), 384 (no cap); 2048: 467 (16), 498 (8), 520 (no cap); 4096: 482
+// (16), 508 (32), 571 (8); 1152: 1027 (18), 1124 (no cap), 1205 (9); 6912: 757 (28), 868 (14).  With master weights, 768:
+// 346 (9), 361 (12), 394 (no cap).  INT4 with bf16 state, 1408: 367 (22), 397 (no cap); 2048: 345 (20), 362 (no cap).
+// SGDM ran best without a cap.
+int wide_waves(const eco::KernelVariant &kv) {
+  if (kv.algo == eco::ALGO_ADAM) return kv.state_bf16 ? 20 : 16;
+  if (kv.algo == eco::ALGO_ADAM_MASTER) return kv.state_bf16 ? 0 : 9;
+  return 0;
+}
+
+// The two tensor-wise passes over 210 M elements (us): Adam, fp32 state 1119 at 16 waves (1176 without a cap); INT4 with
+// bf16 state 623 at 21 (645); SGDM 676 at 18 (703).
+int tensorwise_waves(const eco::KernelVariant &kv) {
+  if (kv.algo == eco::ALGO_ADAM) return kv.state_bf16 ? 21 : 16;
+  return kv.algo == eco::ALGO_SGDM && !kv.state_bf16 ? 18 : 0;
+}
+
+// A cap is expressed as a dynamic-LDS request the kernels never touch (160 KB of LDS per compute unit).
 uint32_t lds_for_waves(int waves, int granule) {
   return waves > 0 ? static_cast<uint32_t>(163840 / waves / granule * granule) : 0u;
 }
@@ -234,12 +257,12 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   sl->max_launch_threads = opt_threads > 0 ? static_cast<uint64_t>(opt_threads) : eco::MAX_LAUNCH_THREADS;
   a->unit_base = 0;
   const int waves = default_waves(kv);
-  const int waves_wide = kv.algo == eco::ALGO_ADAM ? waves : 0;     // measured for Adam only; SGDM ran best uncapped
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
   sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(waves, 512);
-  sl->lds_bytes_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves_wide, 256);
-  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves_wide ? waves_wide + 4 : 0, 256);
+  sl->lds_bytes_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : eco::LDS_BY_RULE;
+  sl->wide_waves = static_cast<uint32_t>(wide_waves(kv));
+  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv), 256);
 }
 
 

@@ -120,13 +120,15 @@ inline uint32_t tw_reduce_workgroups(uint64_t most_tiles) {
   return static_cast<uint32_t>(w < 1 ? 1 : w > 64 ? 64 : w);
 }
 
+constexpr uint32_t LDS_BY_RULE = 0xFFFFFFFFu;
 // What one format's step launches, host side.
 struct StepLaunch {
   StepArgs args;
   uint64_t max_launch_threads;     // most threads one launch may have (the runtime's limit, or a smaller one set for tests)
   uint64_t max_tile_threads;       // the same for the full-tile kernel (a tuning option may cap it further)
   uint32_t lds_bytes;              // dynamic LDS per workgroup of the full-tile kernel (occupancy cap)
-  uint32_t lds_bytes_wave;         // the same per wave of the wide-group kernel
+  uint32_t lds_bytes_wave;         // the same per wave of the wide-group kernel (a tuning option), or LDS_BY_RULE
+  uint32_t wide_waves;             // waves of the wide-group kernel to have resident per compute unit (0: no cap)
   uint32_t lds_bytes_tw;           // the same per (one-wave) workgroup of the two tensor-wise passes
   const uint32_t *wide_base;       // wide-group lists, one per workgroup size, back to back
   uint32_t wide_offset[MAX_WIDE_WAVES + 1];

@@ -800,7 +800,14 @@ __global__ __launch_bounds__(WG_THREADS) void eco_tensorwise_scale_kernel(const 
   a.slots[td.slot] = 0;
 }
 
-inline unsigned lds_cap(unsigned bytes) { return bytes < 65536u ? bytes : 65536u; }   // per-workgroup request limit
+// The dynamic LDS that keeps `waves` waves of workgroups of `nw` resident per compute unit (two workgroups at least); LDS is
+// handed out in pieces of 1280 bytes, and a workgroup has up to 128 of its own beside it.
+inline unsigned lds_for_workgroups(unsigned waves, unsigned nw) {
+  if (waves == 0) return 0;
+  const unsigned k = (waves + nw / 2) / nw < 2 ? 2 : (waves + nw / 2) / nw;
+  const unsigned bytes = 163840u / k / 1280u * 1280u - 256u;
+  return bytes < 65536u ? bytes : 65536u;
+}
 
 // Every launch is followed by its own error check, so that a failed launch stops the sequence and is the
 // error that is reported.
@@ -849,14 +856,16 @@ hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
     for (int nw = 1; nw <= MAX_WIDE_WAVES; ++nw) {
       if (!sl.num_wide[nw]) continue;
       StepArgs wa = args;
+      const unsigned option = sl.lds_bytes_wave * nw;
+      const unsigned lds = sl.lds_bytes_wave == LDS_BY_RULE ? lds_for_workgroups(sl.wide_waves, nw) : option < 65536u ? option : 65536u;
       wa.wide_tensor = sl.wide_base + sl.wide_offset[nw];
       wa.num_units = sl.num_wide[nw];
       if (sl.extra_in != nw || !args.num_extra)
         ECO_CHUNKS_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, false>), wa.num_units, 64 * nw,
-                           lds_cap(sl.lds_bytes_wave * nw), stream, wa, sl.max_launch_threads);
+                           lds, stream, wa, sl.max_launch_threads);
       else
         ECO_CHUNKS_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, true>), (uint64_t)wa.num_units + (wa.num_extra + nw - 1) / nw,
-                           64 * nw, lds_cap(sl.lds_bytes_wave * nw), stream, wa, sl.max_launch_threads);
+                           64 * nw, lds, stream, wa, sl.max_launch_threads);
     }
   }
   if (args.num_slabs) {
