@@ -287,8 +287,8 @@ eco_status_t eco_step_constants(const eco_hparams_t *hp, eco_constants_t *out);
 /* Launch tuning, host only; never changes results.
  *   option 0: cap on the step kernel's grid, in workgroups per compute unit; the tiles are then launched in
  *             pieces (0 = library default: one workgroup per 512-element tile, no cap)
- *   option 1: bytes of dynamic LDS requested per workgroup of the step kernel (-1 = library default).
- *             The kernel never touches it; the request only caps resident workgroups per compute unit.
+ *   option 1: bytes of dynamic LDS requested per workgroup of the step kernel and of the kernel of unquantized
+ *             tensors (-1 = library default).  They never touch it; the request only caps resident workgroups per compute unit.
  *   option 2: the same per wave of the wide-group and tensor-wise kernels (-1 = library default)
  *   option 3: most threads one kernel launch of a step may have, in [1024, 2^32 - 1] (-1 = the runtime's limit,
  *             2^32 - 1).  A step with more work items than that launches its kernels in several pieces; a small

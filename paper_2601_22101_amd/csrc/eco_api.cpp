@@ -151,7 +151,8 @@ int num_compute_units() {
 // more waves than that only add latency.  bf16 state, Adam (us, without a cap -> with it): INT4, 1.39 G elements, 2689 ->
 // 2470 at 21 waves (2558 at 18, 2655 at 25); FP8, 0.42 G elements, 885 -> 824 at 18 (857 at 21, 855 at 16), with master weights 1423 -> 1310 at 12 (1381 at 16).
 int default_waves(const eco::KernelVariant &kv) {
-  if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) return 0;
+  // unquantized weights (22 B/parameter with fp32 state, 14 with bf16), 148 M elements: 614 -> 561 us, 374 -> 337
+  if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) return kv.state_bf16 ? 13 : 12;
   if (kv.state_bf16) {
     if (kv.algo == eco::ALGO_ADAM) return kv.fmt == eco::FMT_INT4 ? 21 : 18;
     return kv.algo == eco::ALGO_ADAM_MASTER ? 12 : 0;

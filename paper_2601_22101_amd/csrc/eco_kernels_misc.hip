@@ -21,7 +21,7 @@ __global__ __launch_bounds__(WG_THREADS) void eco_plain_kernel(const StepArgs a)
 
 hipError_t launch_step_plain(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {
 #define ECO_LAUNCH(F, ST, AD) \
-  ECO_CHUNKS_CHECKED((eco_plain_kernel<F, ST, AD>), sl.args.num_extra, WG_THREADS, 0, stream, sl.args, sl.max_tile_threads)
+  ECO_CHUNKS_CHECKED((eco_plain_kernel<F, ST, AD>), sl.args.num_extra, WG_THREADS, sl.lds_bytes, stream, sl.args, sl.max_tile_threads)
   const int key = (kv.fmt == FMT_FP32_ID ? 4 : 0) | (kv.state_bf16 ? 2 : 0) | (algo_is_adam(kv.algo) ? 0 : 1);
   switch (key) {
     case 0: ECO_LAUNCH(FMT_BF16_PLAIN, false, true); break;
