@@ -166,14 +166,14 @@ int default_waves(const eco::KernelVariant &kv) {
   }
 }
 
-// The same for the wide-group kernel, whose workgroups of 2..16 waves come and go together.  Measured (us, 33-130 M
-// elements in rows of the named length; in parentheses the waves resident): Adam with fp32 state, rows of 1000: 472 (16),
-// 497 (14), 545 (12), 527 (no cap); 768: 340 (15), 337 (12), 384 (no cap); 2048: 467 (16), 498 (8), 520 (no cap); 4096: 482
-// (16), 508 (32), 571 (8); 1152: 1027 (18), 1124 (no cap), 1205 (9); 6912: 757 (28), 868 (14).  With master weights, 768:
-// 346 (9), 361 (12), 394 (no cap).  INT4 with bf16 state, 1408: 367 (22), 397 (no cap); 2048: 345 (20), 362 (no cap).
-// SGDM ran best without a cap.
+// The same for the wide-group kernel, whose workgroups of 2..16 waves come and go together (0: no cap; us, in
+// parentheses the waves resident).  With master weights, rows of 768: 346 (9), 361 (12), 394 (no cap).  INT4 with bf16
+// state, rows of 1408: 367 (22), 397 (no cap); 2048: 345 (20), 362 (no cap).  SGDM ran best without a cap.  Adam with fp32
+// state keeps the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups of larger
+// ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 1000: 472 against 630, of 2048: 467 against
+// 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
 int wide_waves(const eco::KernelVariant &kv) {
-  if (kv.algo == eco::ALGO_ADAM) return kv.state_bf16 ? 20 : 16;
+  if (kv.algo == eco::ALGO_ADAM) return 20;          // bf16 state
   if (kv.algo == eco::ALGO_ADAM_MASTER) return kv.state_bf16 ? 0 : 9;
   return 0;
 }
@@ -261,7 +261,8 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
   sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(waves, 512);
-  sl->lds_bytes_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : eco::LDS_BY_RULE;
+  sl->lds_bytes_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave)
+                       : kv.algo == eco::ALGO_ADAM && !kv.state_bf16 ? lds_for_waves(waves, 256) : eco::LDS_BY_RULE;
   sl->wide_waves = static_cast<uint32_t>(wide_waves(kv));
   sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv), 256);
 }
