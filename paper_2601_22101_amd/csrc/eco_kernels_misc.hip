@@ -119,19 +119,23 @@ template <bool SRC_BF16>
 __global__ __launch_bounds__(QUANT_MAX_THREADS) void eco_quantize_max_kernel(const void *src, uint64_t numel, uint32_t slot) {
   const uint64_t stride = (uint64_t)gridDim.x * QUANT_MAX_THREADS * ELEMS_PER_LANE;
   uint64_t e0 = ((uint64_t)blockIdx.x * QUANT_MAX_THREADS + threadIdx.x) * ELEMS_PER_LANE;
-  float amax = 0.0f, x[4][8];
+  // The maximum is one of bit patterns, as in every other reduction of the library: the float maximum would drop the NaN
+  // of a lane all of whose elements are NaN.
+  uint32_t amax = 0;
+  float x[4][8];
+  const auto take = [&amax](const float (&y)[8]) { const uint32_t a = f2u(absmax8(y)); amax = amax > a ? amax : a; };
   for (; e0 + 3 * stride + 8 <= numel; e0 += 4 * stride) {      // four independent loads under way
 #pragma unroll
     for (int k = 0; k < 4; ++k) load_state8<SRC_BF16, ACC_FULL>(src, e0 + k * stride, 8, x[k]);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) amax = __builtin_fmaxf(amax, absmax8(x[k]));
+    for (int k = 0; k < 4; ++k) take(x[k]);
   }
   for (; e0 < numel; e0 += stride) {
     load_state8<SRC_BF16, ACC_LANE>(src, e0, valid_from(e0, numel), x[0]);
-    amax = __builtin_fmaxf(amax, absmax8(x[0]));
+    take(x[0]);
   }
   __shared__ uint32_t wave_max[QUANT_MAX_THREADS / 64];
-  const uint32_t w = wave_umax(f2u(amax));
+  const uint32_t w = wave_umax(amax);
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = w;
   __syncthreads();
   if (threadIdx.x < 64) {

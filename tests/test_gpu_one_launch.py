@@ -106,6 +106,23 @@ def test_tensor_wise_quantizer_at_the_edges_of_its_shares(fmt, scale_bf16, src_b
         assert np.array_equal(codes.cpu().numpy(), rc) and float(scales.float()[0]) == float(rs[0])
 
 
+@pytest.mark.parametrize("numel", [8200, 8201, 1024 * 8 * 256 * 4 + 8])
+def test_tensor_wise_quantizer_folds_not_a_number_as_the_groups_in_a_wave_do(numel):
+    """Eight elements of a lane: NaN among numbers is passed over, NaN alone makes the group's maximum NaN and with it the
+    scale zero; infinity is the maximum.  The same array with a scale for every 32 elements says what a group of each does."""
+    from paper_2601_22101_amd import binding as eco
+    x = torch.full((numel,), 0.25, device=DEV)
+    for at in (0, 8 * 1023, numel // 8 * 8 - 8):
+        for bad, width in ((float("nan"), 1), (float("nan"), 7), (float("nan"), 8), (float("inf"), 1)):
+            src = x.clone()
+            src[at:at + width] = bad
+            codes, one, many = torch.zeros(numel, dtype=torch.uint8, device=DEV), torch.zeros(1, device=DEV), torch.zeros(-(-numel // 32), device=DEV)
+            eco.eco_quantize_init(src, 0, numel, 0, numel, 0, codes, one)
+            eco.eco_quantize_init(src, 0, numel, 0, 32, 0, codes, many)
+            want = 0.0 if width == 8 else bad if bad == bad else float(torch.tensor(0.25) / 448)
+            assert float(one[0]) == float(many[at // 32]) == want, (at, bad, width)
+
+
 @pytest.mark.parametrize("group", [9, 13, 100, 768, 1000, 1500, 3 * 4096])
 @pytest.mark.parametrize("fmt", [0, 1])
 def test_dequantizer_finds_the_group_of_every_element(fmt, group):
