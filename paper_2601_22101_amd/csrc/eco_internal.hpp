@@ -174,6 +174,14 @@ inline bool flat_call_fits(uint64_t numel, uint64_t group_size) {
   }
   return threads <= MAX_LAUNCH_THREADS;
 }
+// A flat kernel with 8 elements to a thread: its workgroups, and how many of them one launch may have.  A helper call
+// of the largest size that flat_call_fits lets through is 2^32 - 64 threads; rounded up to whole workgroups of more than
+// 64 threads it is 2^32, one launch too many, so those kernels are told the first workgroup of each launch.
+struct FlatLaunch { uint64_t workgroups, per_launch; };
+inline FlatLaunch flat_launch(uint64_t numel, unsigned threads) {
+  const uint64_t share = static_cast<uint64_t>(threads) * ELEMS_PER_LANE;
+  return {(numel + share - 1) / share, MAX_LAUNCH_THREADS / threads};
+}
 // Wide groups (a multiple of 8 up to 8192 elements, not a power of two in [32, 512]): one workgroup of `waves` waves
 // steps `rows` consecutive groups.  One group a workgroup in general; groups of more than 512 elements whose length is
 // not a multiple of 512 leave lanes of their last wave idle, so where 2..8 of them together fill a whole number of

@@ -148,8 +148,9 @@ __global__ __launch_bounds__(QUANT_MAX_THREADS) void eco_quantize_max_kernel(con
 // the first writes the scale.
 template <int FMT, bool SCALE_BF16, bool SRC_BF16>
 __global__ __launch_bounds__(QUANT_PARTS) void eco_quantize_tensorwise_kernel(const void *src, uint64_t numel, uint32_t parts,
-                                                                              void *weights, void *scales, uint32_t slot) {
-  const uint64_t e0 = ((uint64_t)blockIdx.x * QUANT_PARTS + threadIdx.x) * ELEMS_PER_LANE;
+                                                                              void *weights, void *scales, uint32_t slot,
+                                                                              uint32_t first_wg) {
+  const uint64_t e0 = (((uint64_t)first_wg + blockIdx.x) * QUANT_PARTS + threadIdx.x) * ELEMS_PER_LANE;
   const int nvalid = valid_from(e0, numel);
   const uint32_t part = threadIdx.x < parts ? g_quantize_parts[slot][threadIdx.x] : 0u;
   float x[8];
@@ -184,6 +185,16 @@ struct QuantSlotRing {
 };
 static QuantSlotRing g_quant_ring;
 
+// Launches a kernel of `threads` threads a workgroup, whose last argument is the first workgroup of the launch.
+#define ECO_FLAT_CHECKED(flat, threads, stream, kernel, ...)                                                               \
+  do {                                                                                                                     \
+    const FlatLaunch f_ = flat;                                                                                            \
+    for (uint64_t wg_ = 0; wg_ < f_.workgroups; wg_ += f_.per_launch) {                                                    \
+      const uint64_t n_ = f_.workgroups - wg_ < f_.per_launch ? f_.workgroups - wg_ : f_.per_launch;                       \
+      ECO_LAUNCH_CHECKED(kernel, dim3((unsigned)n_), dim3(threads), 0, stream, __VA_ARGS__, (uint32_t)wg_);                \
+    }                                                                                                                      \
+  } while (0)
+
 template <int FMT, bool SC, bool SR>
 static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t group_size, void *weights, void *scales,
                                     hipStream_t stream) {
@@ -215,12 +226,12 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
       e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
       if (e != hipSuccess) { done = nullptr; return e; }
     }
-    constexpr uint64_t max_share = (uint64_t)QUANT_MAX_THREADS * ELEMS_PER_LANE, share = (uint64_t)QUANT_PARTS * ELEMS_PER_LANE;
+    constexpr uint64_t max_share = (uint64_t)QUANT_MAX_THREADS * ELEMS_PER_LANE;
     const uint64_t want = (numel + max_share - 1) / max_share;
     const uint32_t parts = want < QUANT_PARTS ? (uint32_t)want : QUANT_PARTS;
     ECO_LAUNCH_CHECKED((eco_quantize_max_kernel<SR>), dim3(parts), dim3(QUANT_MAX_THREADS), 0, stream, src, numel, slot);
-    ECO_LAUNCH_CHECKED((eco_quantize_tensorwise_kernel<FMT, SC, SR>), dim3((unsigned)((numel + share - 1) / share)), dim3(QUANT_PARTS), 0,
-                       stream, src, numel, parts, weights, scales, slot);
+    ECO_FLAT_CHECKED(flat_launch(numel, QUANT_PARTS), QUANT_PARTS, stream, (eco_quantize_tensorwise_kernel<FMT, SC, SR>), src, numel,
+                     parts, weights, scales, slot);
     e = hipEventRecord(done, stream);
     if (e != hipSuccess) return e;
   }
@@ -259,8 +270,8 @@ struct GroupOf { uint64_t size; double reciprocal; int32_t shift; };       // sh
 
 template <int FMT, bool SCALE_BF16, int SRC>
 __global__ __launch_bounds__(dequant_threads(SRC)) void eco_dequantize_kernel(const void *weights, const void *scales, uint64_t numel,
-                                                                         GroupOf group, const void *src, float *dst) {
-  const uint64_t e0 = ((uint64_t)blockIdx.x * dequant_threads(SRC) + threadIdx.x) * ELEMS_PER_LANE;
+                                                                         GroupOf group, const void *src, float *dst, uint32_t first_wg) {
+  const uint64_t e0 = (((uint64_t)first_wg + blockIdx.x) * dequant_threads(SRC) + threadIdx.x) * ELEMS_PER_LANE;
   const int nvalid = valid_from(e0, numel);
   if (nvalid == 0) return;
   uint32_t c[2];
@@ -300,14 +311,11 @@ __global__ __launch_bounds__(dequant_threads(SRC)) void eco_dequantize_kernel(co
 hipError_t launch_dequantize(const void *weights, const void *scales, uint64_t numel, int fmt, uint64_t group_size,
                              int scale_bf16, const void *src, int src_kind, float *dst, hipStream_t stream) {
   const unsigned threads = (unsigned)dequant_threads(src_kind);
-  const uint64_t share = (uint64_t)threads * ELEMS_PER_LANE;
-  const unsigned wgs = (unsigned)((numel + share - 1) / share);
   // a group that holds the whole tensor: any power of two beyond it does, and no lane crosses its end
   GroupOf group = {group_size, 1.0 / (double)group_size, log2_exact(group_size)};
   if (group_size >= numel) group = {1ull << 62, 0.0, 62};
-#define ECO_LAUNCH(F, SC, SK)                                                                                                 \
-  ECO_LAUNCH_CHECKED((eco_dequantize_kernel<F, SC, SK>), dim3(wgs), dim3(threads), 0, stream, weights, scales, numel, \
-                     group, src, dst)
+#define ECO_LAUNCH(F, SC, SK) \
+  ECO_FLAT_CHECKED(flat_launch(numel, threads), threads, stream, (eco_dequantize_kernel<F, SC, SK>), weights, scales, numel, group, src, dst)
 #define ECO_LAUNCH_SRC(F, SC)                                                                                          \
   do {                                                                                                                 \
     if (src_kind == 0) ECO_LAUNCH(F, SC, 0); else if (src_kind == 1) ECO_LAUNCH(F, SC, 1); else ECO_LAUNCH(F, SC, 2);  \

@@ -53,6 +53,21 @@ int main() {
   // what one helper launch holds
   CHECK(flat_call_fits((1ull << 35) - 512, 128) && !flat_call_fits(1ull << 35, 128) && !flat_call_fits((1ull << 40) + 1, 128));
   CHECK(flat_call_fits(1ull << 34, 520) && !flat_call_fits(1ull << 35, 520) && flat_call_fits(1ull << 30, 1ull << 31));
+  // the helper kernels with more than 64 threads to a workgroup, up to the largest call: every launch within the limit,
+  // together the whole array
+  for (uint64_t n : {1ull, 2048ull, 2049ull, (1ull << 35) - 2048, (1ull << 35) - 2047, (1ull << 35) - 1024, (1ull << 35) - 1023, (1ull << 35) - 512}) {
+    for (unsigned threads : {64u, 128u, 256u}) {
+      CHECK(flat_call_fits(n, n) && flat_call_fits(n, 128));
+      const FlatLaunch f = flat_launch(n, threads);
+      uint64_t covered = 0;
+      for (uint64_t first = 0; first < f.workgroups; first += f.per_launch) {
+        const uint64_t k = f.workgroups - first < f.per_launch ? f.workgroups - first : f.per_launch;
+        CHECK(k >= 1 && k * threads <= MAX_LAUNCH_THREADS && first <= 0xFFFFFFFFull);
+        covered += k;
+      }
+      CHECK(covered == f.workgroups && covered * threads * ELEMS_PER_LANE >= n && (covered - 1) * threads * ELEMS_PER_LANE < n);
+    }
+  }
   std::printf("geometry ok\n");
   return 0;
 }

@@ -258,3 +258,39 @@ def test_one_int4_tensor_of_more_than_2_pow_35_elements():
     n = (1 << 35) + 3 * 512 + 100
     _one_huge_tensor(eco, oracle.get("f32"), n, 1, True,
                      [(0, 6144), ((1 << 32) - 3072, (1 << 32) + 3072), ((1 << 35) - 3072, n)], seed=35)
+
+
+def test_set_up_calls_with_one_scale_at_their_largest_size():
+    """2^35 - 512 elements, the most that one helper call takes (bf16 to INT4: 80 GiB, and 128 GiB of stored error): the
+    last workgroups are more threads than one launch holds."""
+    from paper_2601_22101_amd import binding as eco
+    n = (1 << 35) - 512
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    if free < 6.5 * n + (4 << 30):
+        pytest.skip(f"needs {(6.5 * n + (4 << 30)) / 2**30:.0f} GiB of device memory, {free / 2**30:.0f} GiB are free")
+    src = torch.empty(n, dtype=torch.bfloat16, device=DEV)
+    gen = torch.Generator(device=DEV).manual_seed(2)
+    for off in range(0, n, 2 * CHUNK):
+        src[off:off + 2 * CHUNK].uniform_(-0.25, 0.25, generator=gen)
+    src[n - 1] = -0.5                                                 # the maximum is the very last element
+    codes = torch.empty(n // 2, dtype=torch.uint8, device=DEV)
+    scale = torch.zeros(1, device=DEV)
+    print(f"[huge] quantizing {n} elements with one scale", flush=True)
+    eco.eco_quantize_init(src, eco.ECO_DT_BF16, n, 1, n, eco.ECO_DT_FP32, codes, scale)
+    torch.cuda.synchronize()
+    err = torch.empty(n, device=DEV)
+    print("[huge] quantization error", flush=True)
+    eco.eco_quantize_error(src, eco.ECO_DT_BF16, codes, scale, n, 1, n, eco.ECO_DT_FP32, err)
+    torch.cuda.synchronize()
+    o32 = oracle.get("f32")
+    for e0, e1 in ((0, 4096), ((1 << 34) - 2048, (1 << 34) + 2048), (n - 8192, n)):
+        x = np.append(to_f32(src[e0:e1]), np.float32(-0.5))           # the span and the maximum: one group
+        x = np.append(x, np.float32(0.0))
+        rc, rs = o32.quantize_rtn(oracle.FMT_INT4, x, x.size, scale_bf16=False)
+        assert float(scale[0]) == float(rs[0])
+        assert np.array_equal(codes[e0 // 2:e1 // 2].cpu().numpy(), rc[:(e1 - e0) // 2]), (e0, e1)
+        back = o32.dequantize(oracle.FMT_INT4, rc, rs, x.size, x.size)
+        assert np.array_equal(err[e0:e1].cpu().numpy(), (x - back)[:e1 - e0]), (e0, e1)
+    del src, codes, err
+    torch.cuda.empty_cache()
