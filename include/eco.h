@@ -185,6 +185,8 @@ eco_status_t eco_plan_destroy(eco_plan_t *plan);
  * these launched in pieces.  Steps of one plan that use that scratch must not overlap each other on different streams.
  * hp->block_size, state_dtype, scale_dtype, opt and mode must equal the plan's, and the device that was current at
  * eco_plan_create must be current (ECO_EINVAL otherwise).
+ * After ECO_EHIP some of the step's launches may have run and others not: the plan stays usable, but the tensors hold what
+ * those launches wrote and have to be restored before the step is taken again.
  */
 eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream);
 

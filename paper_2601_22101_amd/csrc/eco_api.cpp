@@ -352,6 +352,7 @@ struct eco_plan {
   int cus = 256;
   int device = 0;    // the device that was current when the plan was created (its tables live there)
   Lists lists[4];    // indexed by eco_format_t; unquantized tensors may be in a quantized format's lists
+  bool unfinished = false;               // a step has stopped between its launches: scratch may hold what it left
   eco::TensorDesc *d_descs = nullptr;
   uint32_t *d_tables = nullptr;          // all lists, back to back, then the abs-max slots and the scratch of the tensor-wise passes
 };
@@ -372,6 +373,29 @@ eco::TensorDesc describe(const eco_tensor_t &t, const eco_hparams_t *layout, con
   d.slot = p.rows;
   d.first_unit = static_cast<uint32_t>(first_unit);
   return d;
+}
+
+// Scratch that a step expects empty and leaves empty, as eco_plan_create uploads it: abs-max slots, slab maxima, counts.
+// Only a step that stopped between its launches (ECO_EHIP) leaves it otherwise; the next one empties it first.
+constexpr int RESET_THREADS = 256, RESET_BLOCKS = 64;
+__global__ __launch_bounds__(RESET_THREADS) void eco_reset_scratch_kernel(uint32_t *slots, uint32_t num_slots, uint32_t *slab_max,
+                                                                          uint32_t num_slabs, uint32_t *counts) {
+  const uint32_t first = blockIdx.x * RESET_THREADS + threadIdx.x;
+  for (uint32_t i = first; i < num_slots; i += RESET_BLOCKS * RESET_THREADS) slots[i] = 0;
+  for (uint32_t i = first; i < num_slabs; i += RESET_BLOCKS * RESET_THREADS) slab_max[i] = 0xFFFFFFFFu;
+  if (first < 2) counts[first] = 0;
+}
+
+hipError_t reset_scratch(const eco_plan &plan, hipStream_t stream) {
+  for (const Lists &g : plan.lists) {
+    if (g.tw_tensor.empty() && g.slab.empty()) continue;
+    uint32_t *const t = plan.d_tables;
+    hipLaunchKernelGGL(eco_reset_scratch_kernel, dim3(RESET_BLOCKS), dim3(RESET_THREADS), 0, stream, t + g.off_slots,
+                       static_cast<uint32_t>(g.tw_tensor.size()), t + g.off_slab_max, static_cast<uint32_t>(g.slab.size()), t + g.off_counts);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Which format's launches the unquantized tensors ride in: their own, or a quantized format's of the same step.
@@ -653,12 +677,17 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     return fail(ECO_EINVAL, "step: the plan was created on device %d, which is not the current device (%d)", plan->device, dev);
   (void)hipGetLastError();   // an error left behind by the caller's earlier HIP work is not this call's
 
+  if (!plan->d_descs || !plan->d_tables) return fail(ECO_EINVAL, "step: the plan's device tables are missing");
   eco_constants_t c;
   derive_constants(hp, &c);
+  if (plan->unfinished) {
+    const hipError_t e = reset_scratch(*plan, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return fail_hip(e, "scratch kernel launch");
+  }
+  plan->unfinished = true;
   for (int f = 0; f < 4; ++f) {
     Lists &g = plan->lists[f];
     if (!g.tensors) continue;
-    if (!plan->d_descs || !plan->d_tables) return fail(ECO_EINVAL, "step: the plan's device tables are missing");
     eco::StepLaunch sl;
     std::memset(&sl, 0, sizeof sl);
     eco::StepArgs &a = sl.args;
@@ -695,6 +724,7 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     st = launch_format(hp, c, f, plan->cus, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
     if (st != ECO_OK) return st;
   }
+  plan->unfinished = false;
   return ECO_OK;
 }
 
