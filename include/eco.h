@@ -163,7 +163,7 @@ typedef struct eco_plan eco_plan_t;
  *                memory layout the descriptors are checked against)
  *   out        : receives the plan; owned by the library until eco_plan_destroy
  * Allocates device memory for the tables (80 bytes per tensor + 4 bytes per 512 elements, or per scale group
- * for groups wider than 512; for tensors with a single scale over more than 8192 elements up to another 4.7 bytes per
+ * for groups wider than 512; for tensors with a single scale over more than 8192 elements up to another 4 bytes per
  * 512 elements of scratch) and copies them synchronously.
  * Errors: ECO_EINVAL, ECO_EALIGN, ECO_EUNSUPPORTED, ECO_ENOMEM, ECO_EHIP.
  */

@@ -375,14 +375,14 @@ eco::TensorDesc describe(const eco_tensor_t &t, const eco_hparams_t *layout, con
   return d;
 }
 
-// Scratch that a step expects empty and leaves empty, as eco_plan_create uploads it: abs-max slots, slab maxima, counts.
+// Scratch that a step expects empty and leaves empty, as eco_plan_create uploads it: abs-max slots, slab maxima, marks, counts.
 // Only a step that stopped between its launches (ECO_EHIP) leaves it otherwise; the next one empties it first.
 constexpr int RESET_THREADS = 256, RESET_BLOCKS = 64;
 __global__ __launch_bounds__(RESET_THREADS) void eco_reset_scratch_kernel(uint32_t *slots, uint32_t num_slots, uint32_t *slab_max,
-                                                                          uint32_t num_slabs, uint32_t *counts) {
+                                                                          uint32_t *deferred, uint32_t num_slabs, uint32_t *counts) {
   const uint32_t first = blockIdx.x * RESET_THREADS + threadIdx.x;
   for (uint32_t i = first; i < num_slots; i += RESET_BLOCKS * RESET_THREADS) slots[i] = 0;
-  for (uint32_t i = first; i < num_slabs; i += RESET_BLOCKS * RESET_THREADS) slab_max[i] = 0xFFFFFFFFu;
+  for (uint32_t i = first; i < num_slabs; i += RESET_BLOCKS * RESET_THREADS) { slab_max[i] = 0xFFFFFFFFu; deferred[i] = 0; }
   if (first < 2) counts[first] = 0;
 }
 
@@ -391,7 +391,8 @@ hipError_t reset_scratch(const eco_plan &plan, hipStream_t stream) {
     if (g.tw_tensor.empty() && g.slab.empty()) continue;
     uint32_t *const t = plan.d_tables;
     hipLaunchKernelGGL(eco_reset_scratch_kernel, dim3(RESET_BLOCKS), dim3(RESET_THREADS), 0, stream, t + g.off_slots,
-                       static_cast<uint32_t>(g.tw_tensor.size()), t + g.off_slab_max, static_cast<uint32_t>(g.slab.size()), t + g.off_counts);
+                       static_cast<uint32_t>(g.tw_tensor.size()), t + g.off_slab_max, t + g.off_deferred,
+                       static_cast<uint32_t>(g.slab.size()), t + g.off_counts);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -604,7 +605,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     }
 
     // one device buffer: per format [full tiles | one-wave units | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots |
-    // tile maxima | slabs | their tensors | tail maxima | slab maxima | counts | deferred tiles]
+    // tile maxima | slabs | their tensors | tail maxima | slab maxima | counts | deferred slabs]
     for (Lists &g : plan->lists) {
       const auto add = [&host](const std::vector<uint32_t> &l, size_t *off) {
         *off = host.size();
@@ -629,7 +630,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       g.off_counts = host.size();
       host.insert(host.end(), 2, 0u);
       g.off_deferred = host.size();
-      host.insert(host.end(), g.slab.size() * eco::res_waves(layout->state_dtype == ECO_DT_BF16), 0u);
+      host.insert(host.end(), g.slab.size(), 0u);
     }
   } catch (const std::bad_alloc &) {
     delete plan;

@@ -53,6 +53,18 @@ constexpr int res_depth(bool state_bf16) { return state_bf16 ? 5 : 5; }
 constexpr uint64_t res_slab(bool state_bf16) { return static_cast<uint64_t>(res_waves(state_bf16)) * TILE_ELEMS; }
 // Slabs a tensor may have for each workgroup: the exchange of maxima takes two of the turns in hand.
 constexpr uint64_t res_slabs_per_wg(bool state_bf16) { return static_cast<uint64_t>(res_depth(state_bf16)) - 2; }
+// Workgroups of the finishing kernel: a wave to each tensor, for its scale, and where waits may be given up enough for the
+// slabs that are then marked, a workgroup to each up to four per compute unit (they return after one load where none is:
+// 12.9 us for three tensors of 40 000 elements with one workgroup and with 21, 34 us for one of 4.7 M with 1 and with 768).
+// With elementwise kernels of another stream on the chip a step of 4.7 M elements takes 0.28 ms, and took 4.0 when
+// one workgroup finished them all; of 92 M 1.17 ms, and 9.2.
+constexpr unsigned RES_FINISH_THREADS = 256;
+inline unsigned res_finish_workgroups(uint64_t tensors, uint64_t slabs, unsigned cus) {
+  constexpr uint64_t waves = RES_FINISH_THREADS / 64;
+  const uint64_t most = 4ull * cus, for_tensors = (tensors + waves - 1) / waves;
+  const uint64_t wgs = slabs > for_tensors ? slabs : for_tensors;
+  return static_cast<unsigned>(wgs < most ? wgs : most);
+}
 constexpr uint32_t RES_TRIES = 64;           // reads of slab_max[] before a wait is given up, 1.5-2 us each
 
 struct TensorDesc {          // 80 bytes, device table entry
@@ -85,9 +97,9 @@ struct StepArgs {            // by-value kernel argument: everything wave-unifor
   const uint32_t *slab_tensor;     // tensor-wise scaling in one pass: slab -> index into tensors
   uint32_t *slab_max;              //   ... scratch: each slab's abs-max, all ones until it is known; empty again after the step
   const uint32_t *resident_tensor; //   ... the tensors themselves
-  uint32_t *deferred;              //   ... scratch: tiles that are left to the finishing kernel
+  uint32_t *deferred;              //   ... scratch: which slabs are left to the finishing kernel (0 or 1 each)
   uint32_t *tail_max;              //   ... scratch: abs-max of the tensors' tails, by place in resident_tensor
-  uint32_t *resident_counts;       //   ... scratch: how many those are; workgroups through with them
+  uint32_t *resident_counts;       //   ... scratch: whether there are any; workgroups through with them
   uint32_t num_tiles, num_extra, num_tw_tiles, num_tw_tensors, num_slabs, num_resident, resident_tails, resident_tries;
   uint32_t tw_reduce_wgs;          // tensor-wise scaling: workgroups per tensor of the reduction
   float b1, omb1, b2, omb2, rbc2, c1, eps, kappa, lr, alpha, wd, inv_lr, inv_lr_beta;

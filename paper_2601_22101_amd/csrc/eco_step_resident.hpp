@@ -13,9 +13,12 @@
 // turn ahead, so neither memory nor the exchange between compute units is waited for in the steady state.
 //
 // Nothing depends on the workgroups being resident together: a wait for entries is a bounded number of reads.  A
-// workgroup that gives up lists its tile and goes on (at most fp32 v~ has been stored, everything else the tile needs is
-// still in place), and a second kernel finishes listed tiles from memory.  That kernel also writes the new scales (until
-// then the old ones are there for listed tiles) and empties slab_max[] for the next step.
+// workgroup that gives up marks its slab and goes on (at most fp32 v~ has been stored, everything else the slab needs is
+// still in place), and a second kernel finishes marked slabs from memory.  That kernel also writes the new scales (until
+// then the old ones are there for marked slabs) and empties slab_max[] for the next step.  (Giving up is no rarity: a
+// workgroup takes a whole compute unit, so with a kernel of another stream on the chip some come late.  A store to the
+// slab's own flag is all that it costs: a list with an atomic counter was 10 000 additions to one address for each 5 M
+// elements.)
 //
 // Progress and reuse inside a workgroup, without barriers: a wave contributes to an "event" (the resolution of a
 // tensor's maximum: each lane reads one of the entries) and waits for the other waves.  They never wait for it in turn:
@@ -290,7 +293,7 @@ __global__ __launch_bounds__(res_waves(STATE_BF16) * 64, res_waves(STATE_BF16) /
         }
         out_len = len_at(out, td.numel);
         if (known == NO_MAX) {
-          if (lane == 0 && out_len) a.deferred[atomicAdd(&a.resident_counts[0], 1u)] = slab * WAVES + wave;
+          if (threadIdx.x == 0) a.deferred[slab] = a.resident_counts[0] = 1;
           out_len = 0;
         }
       }
@@ -332,7 +335,6 @@ __global__ __launch_bounds__(res_waves(STATE_BF16) * 64, res_waves(STATE_BF16) /
 
 // The tail of a tensor, its last numel % 8 elements, is not in the slabs.  This kernel leaves the maximum of theta~ over it
 // for the workgroup that publishes the tensor's last slab; the finishing kernel steps it.  A wave to each tensor.
-constexpr int RES_FINISH_THREADS = 256;
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
 __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_tail_kernel(const StepArgs a) {
   const uint32_t x = a.unit_base + blockIdx.x * (RES_FINISH_THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -343,15 +345,15 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_tail_ker
                                                                              a.tail_max + x);
 }
 
-// Finishes the tiles that were listed, from memory (normally none); then writes the tensors' new scales and empties their
-// entries of slab_max[], a wave to each tensor.  Where tiles were listed, the last workgroup through with them does that
-// alone: until then the old scales are needed.
+// Finishes the slabs that were marked, from memory (normally none), a workgroup to each; then writes the tensors' new
+// scales and empties their entries of slab_max[], a wave to each tensor.  Where slabs were marked, the last workgroup
+// through with them does that alone: until then the old scales are needed.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
 __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_kernel(const StepArgs a) {
   constexpr uint32_t WAVES = res_waves(STATE_BF16), NW = RES_FINISH_THREADS / 64;
   constexpr uint64_t SLAB = res_slab(STATE_BF16);
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t listed = __builtin_amdgcn_readfirstlane(a.resident_counts[0]);
+  const uint32_t marked = __builtin_amdgcn_readfirstlane(a.resident_counts[0]);
   const auto slabs_of = [&](const TensorDesc &td) { return td.numel <= SLAB ? 1u : (uint32_t)((td.numel + SLAB - 1) / SLAB); };
   const auto max_of = [&](const TensorDesc &td) {
     uint32_t x = 0;
@@ -359,13 +361,15 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_k
     return wave_umax(x);
   };
   uint32_t first = blockIdx.x * NW + wave, stride = gridDim.x * NW;
-  if (listed) {
-    for (uint32_t x = first; x < listed; x += stride) {
-      const uint32_t it = __builtin_amdgcn_readfirstlane(a.deferred[x]), slab = it / WAVES;
+  if (marked) {
+    for (uint32_t slab = blockIdx.x; slab < a.num_slabs; slab += gridDim.x) {
+      if (!__builtin_amdgcn_readfirstlane(a.deferred[slab])) continue;
       const TensorDesc td = load_tensor_desc(a, load_table(a.slab_tensor, slab));
       uint32_t amax = max_of(td);
-      const uint64_t e0 = ((uint64_t)(slab - td.first_unit) * WAVES + it % WAVES) * TILE_ELEMS + lane * ELEMS_PER_LANE;
-      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_WHOLE, RED_SLOT, !STATE_BF16>(a, td, e0, e0 < td.numel ? 8 : 0, 0, false, &amax);
+      for (uint32_t k = wave; k < WAVES; k += NW) {
+        const uint64_t e0 = ((uint64_t)(slab - td.first_unit) * WAVES + k) * TILE_ELEMS + lane * ELEMS_PER_LANE;
+        step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_WHOLE, RED_SLOT, !STATE_BF16>(a, td, e0, e0 < td.numel ? 8 : 0, 0, false, &amax);
+      }
     }
     __shared__ uint32_t last;
     __syncthreads();
@@ -373,6 +377,7 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_k
     __syncthreads();
     if (!last) return;
     if (threadIdx.x < 2) a.resident_counts[threadIdx.x] = 0;
+    for (uint32_t i = threadIdx.x; i < a.num_slabs; i += RES_FINISH_THREADS) a.deferred[i] = 0;
     first = wave;
     stride = NW;
   }
@@ -403,7 +408,7 @@ hipError_t launch_resident(const StepLaunch &sl, hipStream_t stream) {
                        dim3(RES_FINISH_THREADS), 0, stream, ta);
   }
   ECO_LAUNCH_CHECKED((eco_step_resident_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(wgs), dim3(block), 0, stream, sl.args);
-  unsigned fin = per_tensor > 1024 ? 1024 : per_tensor;
+  unsigned fin = res_finish_workgroups(sl.args.num_resident, sl.args.num_slabs, sl.resident_wgs);
   if (fin > 2 * most) fin = 2 * most;
   ECO_LAUNCH_CHECKED((eco_step_resident_finish_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(fin), dim3(RES_FINISH_THREADS), 0, stream, sl.args);
   return hipSuccess;

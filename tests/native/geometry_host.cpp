@@ -68,6 +68,16 @@ int main() {
       CHECK(covered == f.workgroups && covered * threads * ELEMS_PER_LANE >= n && (covered - 1) * threads * ELEMS_PER_LANE < n);
     }
   }
+  // the finishing kernel of the one-pass tensor-wise step has enough workgroups for every slab it may be left with
+  for (unsigned cus : {32u, 256u}) {
+    for (uint64_t slabs : {1ull, 21ull, 768ull, 15360ull, 1000000ull}) {
+      for (uint64_t tensors : {1ull, 3ull, 1000ull, 100000ull}) {
+        const unsigned wgs = res_finish_workgroups(tensors, slabs, cus);
+        CHECK(wgs >= 1 && wgs <= 4 * cus && wgs >= (slabs < cus ? slabs : cus));
+        CHECK(slabs > tensors || static_cast<uint64_t>(wgs) * 4 >= tensors || wgs == 4 * cus);
+      }
+    }
+  }
   std::printf("geometry ok\n");
   return 0;
 }
