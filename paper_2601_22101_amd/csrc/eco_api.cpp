@@ -410,13 +410,13 @@ int home_of_plain(const uint64_t (&tensors)[4], const uint64_t (&entries)[4]) {
 
 // The short-list arguments of one format's tensors; false if they do not fit one launch of it.
 struct SmallItem { const eco_tensor_t *t; eco::Placement p; };
-bool make_small(const std::vector<SmallItem> &items, const eco_hparams_t *layout, eco::SmallArgs *sa, unsigned *wgs, unsigned *waves) {
-  if (items.empty() || items.size() > static_cast<size_t>(eco::SMALL_TENSORS)) return false;
+bool make_small(const SmallItem *items, size_t n, const eco_hparams_t *layout, eco::SmallArgs *sa, unsigned *wgs, unsigned *waves) {
+  if (n == 0 || n > static_cast<size_t>(eco::SMALL_TENSORS)) return false;
   unsigned nw = 1;
-  for (const SmallItem &it : items)
-    if (it.p.kind == eco::UNIT_WIDE) nw = std::max(nw, static_cast<unsigned>(it.p.list - eco::LIST_WIDE1 + 1));
+  for (size_t i = 0; i < n; ++i)
+    if (items[i].p.kind == eco::UNIT_WIDE) nw = std::max(nw, static_cast<unsigned>(items[i].p.list - eco::LIST_WIDE1 + 1));
   uint64_t wg = 0;
-  for (size_t i = 0; i < items.size(); ++i) {
+  for (size_t i = 0; i < n; ++i) {
     eco::Placement p = items[i].p;
     const uint64_t units = p.units + (p.tail ? 1 : 0);
     p.tail = false;                                     // whole and partial tiles in one list here
@@ -425,7 +425,7 @@ bool make_small(const std::vector<SmallItem> &items, const eco_hparams_t *layout
     const unsigned per_wg = p.kind == eco::UNIT_WIDE ? nw / static_cast<unsigned>(p.list - eco::LIST_WIDE1 + 1) : nw;
     wg += (units + per_wg - 1) / per_wg;
   }
-  sa->num = static_cast<uint32_t>(items.size());
+  sa->num = static_cast<uint32_t>(n);
   *wgs = static_cast<unsigned>(wg);
   *waves = nw;
   return true;
@@ -601,7 +601,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) launches += !g.wide[nw].empty();
       if (launches < 2 || elements[f] > SMALL_ELEMENTS) continue;
       std::unique_ptr<eco::SmallArgs> sa(new eco::SmallArgs());
-      if (make_small(items[f], layout, sa.get(), &g.small_wgs, &g.small_waves)) g.small = std::move(sa);
+      if (make_small(items[f].data(), items[f].size(), layout, sa.get(), &g.small_wgs, &g.small_waves)) g.small = std::move(sa);
     }
 
     // one device buffer: per format [full tiles | one-wave units | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots |
@@ -795,24 +795,23 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   if (!tensorwise && elements <= SMALL_ELEMENTS && (plain_home >= 0 || !(tensors_of[2] + tensors_of[3])) && tensors_of[0] + tensors_of[1]) {
     eco::SmallArgs small[2];
     eco::StepLaunch sl[2];
+    SmallItem items[2][eco::SMALL_TENSORS];             // no container: this call allocates nothing, on the host neither
+    size_t held[2] = {0, 0};
     bool fits = true;
     std::memset(sl, 0, sizeof sl);
-    try {
-      std::vector<SmallItem> items[2];
-      for (size_t i = 0; i < n && fits; ++i) {
-        eco::Placement p;
-        (void)place(i, &p);
-        items[format_of(i)].push_back(SmallItem{&tensors[i], p});
-        fits = items[format_of(i)].size() <= static_cast<size_t>(eco::SMALL_TENSORS);
-      }
-      for (int f = 0; f < 2 && fits; ++f) {
-        if (items[f].empty()) continue;
-        fits = make_small(items[f], hp, &small[f], &sl[f].small_wgs, &sl[f].small_waves);
-        const int64_t limit = g_max_launch_threads.load(std::memory_order_relaxed);
-        if (limit > 0 && static_cast<uint64_t>(sl[f].small_wgs) * sl[f].small_waves * 64 > static_cast<uint64_t>(limit)) fits = false;
-      }
-    } catch (const std::bad_alloc &) {
-      return fail(ECO_ENOMEM, "step: host allocation failed");
+    for (size_t i = 0; i < n && fits; ++i) {
+      const int f = format_of(i);
+      fits = held[f] < static_cast<size_t>(eco::SMALL_TENSORS);
+      if (!fits) break;
+      SmallItem &it = items[f][held[f]++];
+      it.t = &tensors[i];
+      (void)place(i, &it.p);
+    }
+    for (int f = 0; f < 2 && fits; ++f) {
+      if (!held[f]) continue;
+      fits = make_small(items[f], held[f], hp, &small[f], &sl[f].small_wgs, &sl[f].small_waves);
+      const int64_t limit = g_max_launch_threads.load(std::memory_order_relaxed);
+      if (limit > 0 && static_cast<uint64_t>(sl[f].small_wgs) * sl[f].small_waves * 64 > static_cast<uint64_t>(limit)) fits = false;
     }
     if (fits) {
       for (int f = 0; f < 2; ++f) {

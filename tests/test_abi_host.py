@@ -285,6 +285,21 @@ def test_launch_geometry_host_checks(tmp_path):
     assert out.returncode == 0 and "geometry ok" in out.stdout, out.stdout
 
 
+def test_the_allocation_free_step_allocates_no_host_memory(eco, tmp_path):
+    """eco_step_tensors_noalloc under a counting operator new, with launches that end in the test: tests/native/noalloc_host.c."""
+    import subprocess
+    lib = os.environ.get("ECO_LIB_PATH") or os.path.join(ROOT, "paper_2601_22101_amd", "libeco.so")
+    lib_dir = os.path.dirname(os.path.abspath(lib))
+    exe = str(tmp_path / "noalloc_host")
+    cmd = ["gcc", "-O1", "-std=gnu11", "-Wall", "-Wextra", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+           os.path.join(ROOT, "tests", "native", "noalloc_host.c"), "-o", exe, "-Wl,--export-dynamic", "-L", lib_dir,
+           "-l:" + os.path.basename(lib), f"-Wl,-rpath,{lib_dir}"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    out = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert out.returncode == 0 and "no host allocation" in out.stdout, out.stdout
+
+
 def test_a_plain_c_client_compiles_links_and_runs(eco, tmp_path):
     """include/eco.h is valid C99 (-Wall -Wextra -pedantic -Werror), libeco.so links by its C names, and the
     host-only entry points give a C caller what they give the Python binding."""
