@@ -260,24 +260,27 @@ hipError_t launch_quantize_init(const void *src, int src_bf16, uint64_t numel, i
 // subtraction, each rounded to fp32).
 // A lane's 8 elements may straddle two groups when the group size is not a multiple of 8, so the scale
 // index is then taken per element.
-// Threads of a workgroup: one wave where the output is most of the traffic (16 M FP8 elements 14.3 us, with four waves 15.0),
-// two where a source is read beside it.
-constexpr int dequant_threads(int src) { return src == 0 ? 64 : 128; }
 // The group of a lane: a shift where the group size is a power of two, else a product with its reciprocal in double
 // precision (exact to within one for the 2^35 elements of a call, then corrected); a 64-bit division is ~150 instructions
 // and made the kernel arithmetic bound.
 struct GroupOf { uint64_t size; double reciprocal; int32_t shift; };       // shift < 0: no power of two
+// With a source, workgroups of one wave that load it behind the scale; for long arrays workgroups of two waves with every
+// load of a lane under way together.  Measured, us, one wave / two -- bf16 source, INT4: 5 M elements 6.6 / 6.8, 10 M 11.1 /
+// 12.9, 100 M 109 / 114, 450 M 486 / 481 (FP8 528 / 512); fp32 source, INT4: 5 M 6.9 / 7.7, 10 M 13.6 / 14.5, 20 M 27.2 /
+// 26.5, 40 M 60.2 / 58.9, 200 M 292 / 284.  (The threads are a template parameter: a kernel that asks for blockDim is passed
+// 256 bytes of arguments more, 0.8 us of a call.)
+inline bool long_error_call(int src_kind, uint64_t numel) { return numel >= (src_kind == 1 ? 1ull << 24 : 1ull << 28); }
 
-template <int FMT, bool SCALE_BF16, int SRC>
-__global__ __launch_bounds__(dequant_threads(SRC)) void eco_dequantize_kernel(const void *weights, const void *scales, uint64_t numel,
+template <int FMT, bool SCALE_BF16, int SRC, int THREADS>
+__global__ __launch_bounds__(THREADS) void eco_dequantize_kernel(const void *weights, const void *scales, uint64_t numel,
                                                                          GroupOf group, const void *src, float *dst, uint32_t first_wg) {
-  const uint64_t e0 = (((uint64_t)first_wg + blockIdx.x) * dequant_threads(SRC) + threadIdx.x) * ELEMS_PER_LANE;
+  const uint64_t e0 = (((uint64_t)first_wg + blockIdx.x) * THREADS + threadIdx.x) * ELEMS_PER_LANE;
   const int nvalid = valid_from(e0, numel);
   if (nvalid == 0) return;
   uint32_t c[2];
   load_codes8<FMT, ACC_LANE>(weights, e0, nvalid, c);
   float t[8];
-  if (SRC != 0) load_state8<SRC == 2, ACC_LANE>(src, e0, nvalid, t);
+  if (SRC != 0 && THREADS == 128) load_state8<SRC == 2, ACC_LANE>(src, e0, nvalid, t);
   uint64_t sg;
   if (group.shift >= 0) {
     sg = e0 >> group.shift;
@@ -301,6 +304,7 @@ __global__ __launch_bounds__(dequant_threads(SRC)) void eco_dequantize_kernel(co
     for (int j = 0; j < 8; ++j) x[j] *= ((uint64_t)j < boundary ? s0 : s1);
   }
   if (SRC != 0) {
+    if (THREADS != 128) load_state8<SRC == 2, ACC_LANE>(src, e0, nvalid, t);
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = t[j] - x[j];
   }
@@ -310,15 +314,19 @@ __global__ __launch_bounds__(dequant_threads(SRC)) void eco_dequantize_kernel(co
 // src_kind: 0 = no source (plain de-quantization), 1 = fp32 source, 2 = bf16 source (dst = src - q)
 hipError_t launch_dequantize(const void *weights, const void *scales, uint64_t numel, int fmt, uint64_t group_size,
                              int scale_bf16, const void *src, int src_kind, float *dst, hipStream_t stream) {
-  const unsigned threads = (unsigned)dequant_threads(src_kind);
+  const bool longer = long_error_call(src_kind, numel);
   // a group that holds the whole tensor: any power of two beyond it does, and no lane crosses its end
   GroupOf group = {group_size, 1.0 / (double)group_size, log2_exact(group_size)};
   if (group_size >= numel) group = {1ull << 62, 0.0, 62};
-#define ECO_LAUNCH(F, SC, SK) \
-  ECO_FLAT_CHECKED(flat_launch(numel, threads), threads, stream, (eco_dequantize_kernel<F, SC, SK>), weights, scales, numel, group, src, dst)
-#define ECO_LAUNCH_SRC(F, SC)                                                                                          \
-  do {                                                                                                                 \
-    if (src_kind == 0) ECO_LAUNCH(F, SC, 0); else if (src_kind == 1) ECO_LAUNCH(F, SC, 1); else ECO_LAUNCH(F, SC, 2);  \
+#define ECO_LAUNCH(F, SC, SK, T) \
+  ECO_FLAT_CHECKED(flat_launch(numel, T), T, stream, (eco_dequantize_kernel<F, SC, SK, T>), weights, scales, numel, group, src, dst)
+#define ECO_LAUNCH_SRC(F, SC)                                        \
+  do {                                                               \
+    if (src_kind == 0) ECO_LAUNCH(F, SC, 0, 64);                     \
+    else if (src_kind == 1 && longer) ECO_LAUNCH(F, SC, 1, 128);     \
+    else if (src_kind == 1) ECO_LAUNCH(F, SC, 1, 64);                \
+    else if (longer) ECO_LAUNCH(F, SC, 2, 128);                      \
+    else ECO_LAUNCH(F, SC, 2, 64);                                   \
   } while (0)
   if (fmt == FMT_FP8) { if (scale_bf16) ECO_LAUNCH_SRC(FMT_FP8, true); else ECO_LAUNCH_SRC(FMT_FP8, false); }
   else { if (scale_bf16) ECO_LAUNCH_SRC(FMT_INT4, true); else ECO_LAUNCH_SRC(FMT_INT4, false); }

@@ -141,3 +141,16 @@ def test_dequantizer_finds_the_group_of_every_element(fmt, group):
     err = torch.zeros(n, device=DEV)
     eco.eco_quantize_error(src, 0, codes, scales, n, fmt, group, 0, err)
     assert torch.equal(err, src - ref)
+
+
+@pytest.mark.parametrize("src_bf16,numel", [(0, (1 << 24) - 8), (0, (1 << 24) + 1027), (1, (1 << 28) - 8), (1, (1 << 28) + 1027)])
+def test_quantization_error_either_side_of_its_long_form(src_bf16, numel):
+    from paper_2601_22101_amd import binding as eco
+    group = 1000
+    codes = torch.full((numel,), 0x38, dtype=torch.uint8, device=DEV)                     # 1.0
+    scales = torch.rand(-(-numel // group), device=DEV)
+    src = torch.randn(numel, device=DEV).to(torch.bfloat16 if src_bf16 else torch.float32)
+    err = torch.full((numel + 8,), 7.0, device=DEV)
+    eco.eco_quantize_error(src, src_bf16, codes, scales, numel, 0, group, 0, err)
+    assert torch.equal(err[:numel], src.float() - scales.repeat_interleave(group)[:numel])
+    assert bool((err[numel:] == 7).all())
