@@ -122,6 +122,7 @@ struct Lists {                           // the launch lists of one storage form
   size_t off_tile = 0, off_extra = 0, off_wide[eco::MAX_WIDE_WAVES + 1] = {0}, off_tw_tile = 0, off_tw_tensor = 0, off_slots = 0,
          off_tile_max = 0, off_slab = 0, off_resident = 0, off_tail_max = 0, off_slab_max = 0, off_counts = 0, off_deferred = 0;
   uint64_t tensors = 0, most_tw_tiles = 0, tails = 0;
+  uint32_t idle[eco::MAX_WIDE_WAVES + 1] = {0};          // units of the wide lists that leave lanes idle
   std::unique_ptr<eco::SmallArgs> small; // all but the tensor-wise tensors as one launch, where that is the better way
   unsigned small_wgs = 0, small_waves = 1;
   std::vector<uint32_t> &list(int l) {
@@ -164,18 +165,6 @@ int default_waves(const eco::KernelVariant &kv) {
     case eco::ALGO_SGDM_MASTER: return 8;    // 19.0
     default: return 11;                      // SGDM with a stored error: 20.1
   }
-}
-
-// The same for the wide-group kernel, whose workgroups of 2..16 waves come and go together (0: no cap; us, in
-// parentheses the waves resident).  With master weights, rows of 768: 346 (9), 361 (12), 394 (no cap).  INT4 with bf16
-// state, rows of 1408: 367 (22), 397 (no cap); 2048: 345 (20), 362 (no cap).  SGDM ran best without a cap.  Adam with fp32
-// state keeps the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups of larger
-// ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 1000: 472 against 630, of 2048: 467 against
-// 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
-int wide_waves(const eco::KernelVariant &kv) {
-  if (kv.algo == eco::ALGO_ADAM) return 20;          // bf16 state
-  if (kv.algo == eco::ALGO_ADAM_MASTER) return kv.state_bf16 ? 0 : 9;
-  return 0;
 }
 
 // The two tensor-wise passes over 210 M elements (us): Adam, fp32 state 1119 at 16 waves (1176 without a cap); INT4 with
@@ -245,8 +234,9 @@ eco::KernelVariant variant_for(const eco_hparams_t *hp, int f) {
   return kv;
 }
 
-// The scalar part of the kernel arguments: step constants, random-stream key, launch options.
-void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, eco::StepLaunch *sl) {
+// The scalar part of the kernel arguments: step constants, random-stream key, launch options.  idle: see wide_workgroups.
+typedef uint32_t IdleUnits[eco::MAX_WIDE_WAVES + 1];
+void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const IdleUnits &idle, eco::StepLaunch *sl) {
   eco::StepArgs *a = &sl->args;
   a->b1 = c.b1; a->omb1 = c.omb1; a->b2 = c.b2; a->omb2 = c.omb2; a->rbc2 = c.rbc2; a->c1 = c.c1; a->eps = c.eps;
   a->kappa = c.kappa; a->lr = c.lr; a->alpha = c.alpha; a->wd = c.wd; a->inv_lr = c.inv_lr; a->inv_lr_beta = c.inv_lr_beta;
@@ -261,9 +251,15 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
   sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(waves, 512);
-  sl->lds_bytes_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave)
-                       : kv.algo == eco::ALGO_ADAM && !kv.state_bf16 ? lds_for_waves(waves, 256) : eco::LDS_BY_RULE;
-  sl->wide_waves = static_cast<uint32_t>(wide_waves(kv));
+  for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
+    // Adam with fp32 state keeps the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
+    // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 1000: 472 against 630, of 2048: 467
+    // against 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
+    const uint32_t per_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves, 256);
+    sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (kv.algo == eco::ALGO_ADAM && !kv.state_bf16)
+                                 ? std::min(per_wave * nw, 65536u)
+                                 : eco::lds_for_workgroups(eco::wide_workgroups(kv, nw, sl->num_wide[nw], idle[nw]));
+  }
   sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv), 256);
 }
 
@@ -588,6 +584,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
         g.resident.push_back(idx);
       } else {
         elements[f] += t.numel;
+        if (p.idle) g.idle[p.list - eco::LIST_WIDE1 + 1] += static_cast<uint32_t>(p.units);
         if (items[f].size() <= static_cast<size_t>(eco::SMALL_TENSORS)) items[f].push_back(SmallItem{&t, p});
       }
       list.insert(list.end(), static_cast<size_t>(p.units), idx);
@@ -651,10 +648,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
 }
 
 // Launches the step of one format's lists (sl: everything but the scalars).
-static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, eco::StepLaunch *sl,
+static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, const IdleUnits &idle, eco::StepLaunch *sl,
                                   eco::SmallArgs *small, hipStream_t stream) {
   const eco::KernelVariant kv = variant_for(hp, f);
-  fill_step_scalars(hp, c, kv, sl);
+  fill_step_scalars(hp, c, kv, idle, sl);
   sl->extra_in = home_of_extra(sl->args.num_tiles, sl->args.num_extra, sl->num_wide);
   sl->max_tile_threads = tile_threads(sl->max_launch_threads, cus);
   // the limit on a launch's threads holds for the one launch of the short-list kernel too (without tables it is the only way)
@@ -722,7 +719,7 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     sl.resident_wgs = static_cast<unsigned>(plan->cus);
     eco::SmallArgs small;                  // a copy: steps of one plan may be enqueued by different calls
     if (g.small) { small = *g.small; sl.small_wgs = g.small_wgs; sl.small_waves = g.small_waves; }
-    st = launch_format(hp, c, f, plan->cus, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
+    st = launch_format(hp, c, f, plan->cus, g.idle, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
     if (st != ECO_OK) return st;
   }
   plan->unfinished = false;
@@ -757,6 +754,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   constexpr int L_TW_TENSORS = eco::LIST_COUNT, L_COUNT = eco::LIST_COUNT + 1;
   uint64_t count[4][L_COUNT] = {{0}}, tensors_of[4] = {0}, entries_of[4] = {0}, most_tw_tiles[4] = {0};
   uint64_t total = 0, elements = 0;
+  IdleUnits idle[4] = {{0}};
   const auto place = [&](size_t i, eco::Placement *p) {
     uint64_t gsz = 0;
     int cls = 0;
@@ -816,7 +814,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     if (fits) {
       for (int f = 0; f < 2; ++f) {
         if (!sl[f].small_wgs) continue;
-        st = launch_format(hp, c, f, cus, &sl[f], &small[f], hs);
+        st = launch_format(hp, c, f, cus, idle[f], &sl[f], &small[f], hs);
         if (st != ECO_OK) return st;
       }
       return ECO_OK;
@@ -828,6 +826,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     (void)place(i, &p);
     const int f = format_of(i);
     count[f][p.list] += p.units;
+    if (p.idle) idle[f][p.list - eco::LIST_WIDE1 + 1] += static_cast<uint32_t>(p.units);
     if (p.tail) count[f][eco::LIST_EXTRA] += 1;
     if (p.list == eco::LIST_TW_TILES) {
       count[f][L_TW_TENSORS] += 1;
@@ -905,7 +904,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     a.num_tw_tiles = static_cast<uint32_t>(count[f][eco::LIST_TW_TILES]);
     a.num_tw_tensors = static_cast<uint32_t>(count[f][L_TW_TENSORS]);
     a.tw_reduce_wgs = eco::tw_reduce_workgroups(most_tw_tiles[f]);
-    st = launch_format(hp, c, f, cus, &sl, nullptr, hs);
+    st = launch_format(hp, c, f, cus, idle[f], &sl, nullptr, hs);
     if (st != ECO_OK) return st;
   }
   return ECO_OK;

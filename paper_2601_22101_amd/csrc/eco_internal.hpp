@@ -125,15 +125,13 @@ inline uint32_t tw_reduce_workgroups(uint64_t most_tiles) {
   return static_cast<uint32_t>(w < 1 ? 1 : w > 64 ? 64 : w);
 }
 
-constexpr uint32_t LDS_BY_RULE = 0xFFFFFFFFu;
 // What one format's step launches, host side.
 struct StepLaunch {
   StepArgs args;
   uint64_t max_launch_threads;     // most threads one launch may have (the runtime's limit, or a smaller one set for tests)
   uint64_t max_tile_threads;       // the same for the full-tile kernel (a tuning option may cap it further)
   uint32_t lds_bytes;              // dynamic LDS per workgroup of the full-tile kernel (occupancy cap)
-  uint32_t lds_bytes_wave;         // the same per wave of the wide-group kernel (a tuning option), or LDS_BY_RULE
-  uint32_t wide_waves;             // waves of the wide-group kernel to have resident per compute unit (0: no cap)
+  uint32_t lds_bytes_wide[MAX_WIDE_WAVES + 1];   // the same per workgroup of the wide-group kernel, by its waves
   uint32_t lds_bytes_tw;           // the same per (one-wave) workgroup of the two tensor-wise passes
   const uint32_t *wide_base;       // wide-group lists, one per workgroup size, back to back
   uint32_t wide_offset[MAX_WIDE_WAVES + 1];
@@ -228,12 +226,13 @@ struct Placement {
   bool tail;             // one more unit, of kind UNIT_TAIL, in LIST_EXTRA
   uint64_t group;        // elements per scale group
   uint32_t rows;         // groups per unit (wide groups, UNIT_ROWS)
+  bool idle;             // wide groups: the units leave lanes of their last wave idle
   uint64_t entries;      // what the tensor counts towards the limits on launch tables: a unit per tile or per group
 };
 // slab, max_slabs: the one-pass tensor-wise kernel's slab length and the most slabs of a tensor it may take (0: none).
 inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool quantized, int fmt, uint64_t slab = TILE_ELEMS,
                               uint64_t max_slabs = 0) {
-  Placement p = {LIST_TILE, UNIT_TILES, 0, false, group_size, 1, 0};
+  Placement p = {LIST_TILE, UNIT_TILES, 0, false, group_size, 1, false, 0};
   if (cls == GROUP_BLOCK) {
     const bool rest = numel % TILE_ELEMS != 0;
     p.entries = numel / TILE_ELEMS + (rest ? 1 : 0);
@@ -259,6 +258,7 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
       p.kind = UNIT_WIDE;
       p.rows = w.rows;
       p.units = p.entries = w.units;
+      p.idle = w.rows == 1 && p.group % TILE_ELEMS != 0;
     }
   } else {
     p.group = numel;
@@ -273,6 +273,31 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
     }
   }
   return p;
+}
+// Workgroups of `nw` waves of the wide-group kernel to have resident per compute unit (0: as many as fit).  HBM delivers
+// most with a certain amount of traffic in flight, so where the lanes are busy a cap is worth 3 to 11 %; where a row
+// leaves lanes of its last wave idle, their guarded accesses need all the waves there are and a cap costs up to 47 %.
+// Measured over 150 M elements, us, capped / not --
+//   Adam, bf16 state, at least 20 waves: FP8 rows of 768 309 / 337, 1024 314 / 329, 2048 323 / 337, 4096 311 / 323 (INT4 286 /
+//   309, 294 / 305, 293 / 304, 290 / 303).  Workgroups of 5 to 7 and of 9 to 16 waves gain nothing or lose: 640 314 / 309,
+//   3072 316 / 314, 896 319 / 312, 2304 328 / 318, 1408 323 / 319, 8192 336 / 336.  Idle lanes: 1000 411 / 327, 1800 446 / 332,
+//   3000 381 / 374.
+//   Master weights, fp32 state, two or up to 10 waves: 768 701 / 789, 1024 766 / 803, 2048 724 / 793, 640 724 / 780, 4096 757 / 771,
+//   2304 761 / 782.  Idle lanes: 1800 1016 / 820, 1000 807 / 823 (4 M elements 23.1 / 18.4).
+// Adam with fp32 state has a cap of its own; the other variants ran best without one.  units, idle: the launch's units, and those
+// of them that leave lanes idle.
+inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, uint64_t units, uint64_t idle) {
+  if (idle > units / 8) return 0;
+  if (kv.algo == ALGO_ADAM && kv.state_bf16) return nw <= 4 || nw == 8 ? (20 + nw - 1) / nw : 0;
+  if (kv.algo == ALGO_ADAM_MASTER && !kv.state_bf16) return nw <= 5 ? 10 / nw : 2;
+  return 0;
+}
+// The dynamic LDS that keeps k workgroups resident per compute unit (0: no request); LDS is handed out in pieces of 1280
+// bytes, and a workgroup has up to 128 of its own beside it.
+inline uint32_t lds_for_workgroups(unsigned k) {
+  if (k == 0) return 0;
+  const uint32_t bytes = 163840u / k / 1280u * 1280u - 256u;
+  return bytes < 65536u ? bytes : 65536u;
 }
 inline int log2_exact(uint64_t x) {
   for (int s = 0; s < 64; ++s)

@@ -800,15 +800,6 @@ __global__ __launch_bounds__(WG_THREADS) void eco_tensorwise_scale_kernel(const 
   a.slots[td.slot] = 0;
 }
 
-// The dynamic LDS that keeps `waves` waves of workgroups of `nw` resident per compute unit (two workgroups at least); LDS is
-// handed out in pieces of 1280 bytes, and a workgroup has up to 128 of its own beside it.
-inline unsigned lds_for_workgroups(unsigned waves, unsigned nw) {
-  if (waves == 0) return 0;
-  const unsigned k = (waves + nw / 2) / nw < 2 ? 2 : (waves + nw / 2) / nw;
-  const unsigned bytes = 163840u / k / 1280u * 1280u - 256u;
-  return bytes < 65536u ? bytes : 65536u;
-}
-
 // Every launch is followed by its own error check, so that a failed launch stops the sequence and is the
 // error that is reported.
 #define ECO_LAUNCH_CHECKED(kernel, grid, block, lds, stream, ...)                                                 \
@@ -856,8 +847,7 @@ hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
     for (int nw = 1; nw <= MAX_WIDE_WAVES; ++nw) {
       if (!sl.num_wide[nw]) continue;
       StepArgs wa = args;
-      const unsigned option = sl.lds_bytes_wave * nw;
-      const unsigned lds = sl.lds_bytes_wave == LDS_BY_RULE ? lds_for_workgroups(sl.wide_waves, nw) : option < 65536u ? option : 65536u;
+      const unsigned lds = sl.lds_bytes_wide[nw];
       wa.wide_tensor = sl.wide_base + sl.wide_offset[nw];
       wa.num_units = sl.num_wide[nw];
       if (sl.extra_in != nw || !args.num_extra)

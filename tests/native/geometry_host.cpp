@@ -78,6 +78,22 @@ int main() {
       }
     }
   }
+  // occupancy caps of the wide-group kernel: none where rows leave lanes idle, at least 20 waves where bf16 state is capped,
+  // and a request that the hardware's LDS holds that many times
+  for (int algo : {ALGO_ADAM, ALGO_SGDM, ALGO_SGDM_EXACT, ALGO_ADAM_MASTER, ALGO_SGDM_MASTER}) {
+    for (int bf16 = 0; bf16 <= 1; ++bf16) {
+      for (unsigned nw = 2; nw <= (unsigned)MAX_WIDE_WAVES; ++nw) {
+        const KernelVariant kv = {FMT_FP8, bf16, bf16, algo, ROUND_SR};
+        CHECK(wide_workgroups(kv, nw, 1000, 1000) == 0 && wide_workgroups(kv, nw, 1000, 126) == 0);
+        const unsigned k = wide_workgroups(kv, nw, 1000, 125);
+        CHECK(k == wide_workgroups(kv, nw, 1000, 0) && (k == 0 || k >= 2));
+        if (algo == ALGO_ADAM && bf16) CHECK(k == 0 || (k * nw >= 20 && (nw <= 4 || nw == 8)));
+        CHECK(k == 0 || ((lds_for_workgroups(k) + 128 + 1279) / 1280 * 1280 * k <= 163840 && lds_for_workgroups(k) <= 65536));
+      }
+    }
+  }
+  CHECK(place_tensor(64 * 1000, 1000, GROUP_WIDE, true, FMT_FP8).idle && place_tensor(3 * 1408, 1408, GROUP_WIDE, true, FMT_FP8).idle);
+  CHECK(!place_tensor(4 * 1408, 1408, GROUP_WIDE, true, FMT_FP8).idle && !place_tensor(5 * 1024, 1024, GROUP_WIDE, true, FMT_FP8).idle);
   std::printf("geometry ok\n");
   return 0;
 }
