@@ -221,6 +221,10 @@ eco_status_t check_layout(const eco_hparams_t *layout) {
   return check_block_size(layout->block_size);
 }
 
+eco::StateLayout state_layout(const eco_hparams_t *layout) {
+  return {layout->opt == ECO_OPT_ADAM, layout->state_dtype == ECO_DT_BF16, layout->mode == ECO_MODE_EXACT || layout->mode == ECO_MODE_MASTER};
+}
+
 // The kernel variant of a step with these hyper-parameters on tensors of format f.
 eco::KernelVariant variant_for(const eco_hparams_t *hp, int f) {
   eco::KernelVariant kv;
@@ -552,12 +556,28 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     e = hipGetDevice(&plan->device);
     if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
     plan->cus = num_compute_units();
-    // tensors with one scale that the chip can hold
+    // tensors with one scale that the chip can hold: one pass, if it pays for those of the format
     const bool bf16 = layout->state_dtype == ECO_DT_BF16;
+    const eco::StateLayout state = state_layout(layout);
     const uint64_t max_slabs = std::min<uint64_t>(eco::res_waves(bf16) * 64, eco::res_slabs_per_wg(bf16) * plan->cus);
-    for (size_t i = 0; i < n; ++i)
-      if (place[i].list == eco::LIST_TW_TILES)
-        place[i] = eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, tensors[i].fmt, eco::res_slab(bf16), max_slabs);
+    for (int f = 0; f < 2; ++f) {
+      uint64_t bytes = 0, slabs = 0;
+      bool tails = false, longer = false;
+      const auto in_one_pass = [&](size_t i) {
+        return eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, tensors[i].fmt, eco::res_slab(bf16), max_slabs);
+      };
+      for (size_t i = 0; i < n; ++i) {
+        if (tensors[i].fmt != f || place[i].list != eco::LIST_TW_TILES) continue;
+        const eco::Placement p = in_one_pass(i);
+        if (p.list != eco::LIST_RESIDENT) { longer = true; continue; }
+        bytes += eco::array_bytes(tensors[i].numel, f, state);
+        slabs += p.units;
+        tails = tails || tensors[i].numel % eco::ELEMS_PER_LANE != 0;
+      }
+      if (!eco::one_pass_pays(state, bytes, slabs, static_cast<unsigned>(plan->cus), tails, longer)) continue;
+      for (size_t i = 0; i < n; ++i)
+        if (tensors[i].fmt == f && place[i].list == eco::LIST_TW_TILES) place[i] = in_one_pass(i);
+    }
     const int plain_home = home_of_plain(tensors_of, entries_of);
 
     std::vector<SmallItem> items[4];

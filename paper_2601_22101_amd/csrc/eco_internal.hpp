@@ -53,6 +53,30 @@ constexpr int res_depth(bool state_bf16) { return state_bf16 ? 5 : 5; }
 constexpr uint64_t res_slab(bool state_bf16) { return static_cast<uint64_t>(res_waves(state_bf16)) * TILE_ELEMS; }
 // Slabs a tensor may have for each workgroup: the exchange of maxima takes two of the turns in hand.
 constexpr uint64_t res_slabs_per_wg(bool state_bf16) { return static_cast<uint64_t>(res_depth(state_bf16)) - 2; }
+// Bytes of a tensor's arrays, each counted once: whether a step finds them in the 256 MB cache in front of HBM decides
+// which form of it is the faster one.
+struct StateLayout { bool adam, state_bf16, aux; };
+inline uint64_t array_bytes(uint64_t numel, int fmt, const StateLayout &l) {
+  const bool quantized = fmt == FMT_FP8 || fmt == FMT_INT4;
+  const uint64_t half = fmt == FMT_FP8 ? 2 : fmt == FMT_INT4 ? 1 : fmt == FMT_BF16_PLAIN ? 4 : 8;      // of the weights, in half bytes
+  return numel * (2 + (l.adam ? 2 : 1) * (l.state_bf16 ? 2 : 4) + (l.aux && quantized ? 4 : 0)) + numel * half / 2;
+}
+// Whether the tensor-wise tensors of one format that the chip can hold are stepped in one pass.  In favour: 35 % fewer bytes,
+// and two launches where the two-pass form has four.  Against: turns of 4 to 5 us, so that lists of few turns (but more than
+// one) are slower; a launch of 5 us more where a tensor has a tail; two launches more where longer tensors need the
+// two-pass form anyway.  The lines below are where the two forms met (us, two passes / one) --
+//   one turn: 15.1 / 12.9 (0.8 M elements); two turns 18 / 21, 20 / 25.  Then 44 MB: Adam with fp32 state 35 / 27 (4 M), 32 / 28;
+//   INT4 with bf16 state 33 / 29 (6.4 M), 31 / 29, 29 / 28; SGDM 30 / 26; master weights 39 / 31 (4 M), 36 / 33.
+//   tails: fp32 state 54 / 44 (8 M), 50 / 45, 51 / 51; bf16 state 88 / 88 (26 M), 162 / 150 (48 M).
+//   beside longer tensors: fp32 state 112 / 107 (16 M), 106 / 103, 311 / 306; bf16 state 282 / 275 (48 M), 294 / 297, 302 / 283.
+//   SGDM with bf16 state, the fewest bytes: 120 / 129 (64 M), 192 / 164 (92 M).
+inline bool one_pass_pays(const StateLayout &l, uint64_t bytes, uint64_t slabs, unsigned cus, bool tails, bool beside_longer) {
+  if (slabs <= cus && !tails && !beside_longer) return true;
+  const uint64_t MB = 1000000;
+  if (!l.state_bf16 || l.aux) return bytes >= 44 * MB + (tails ? 52 * MB : 0) + (beside_longer ? 132 * MB : 0);
+  if (!l.adam) return bytes >= 384 * MB;
+  return bytes >= (beside_longer ? (tails ? 416 * MB : 312 * MB) : tails ? 256 * MB : 44 * MB);
+}
 // Workgroups of the finishing kernel: a wave to each tensor, for its scale, and where waits may be given up enough for the
 // slabs that are then marked, a workgroup to each up to four per compute unit (they return after one load where none is:
 // 12.9 us for three tensors of 40 000 elements with one workgroup and with 21, 34 us for one of 4.7 M with 1 and with 768).

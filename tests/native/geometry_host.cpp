@@ -94,6 +94,25 @@ int main() {
   }
   CHECK(place_tensor(64 * 1000, 1000, GROUP_WIDE, true, FMT_FP8).idle && place_tensor(3 * 1408, 1408, GROUP_WIDE, true, FMT_FP8).idle);
   CHECK(!place_tensor(4 * 1408, 1408, GROUP_WIDE, true, FMT_FP8).idle && !place_tensor(5 * 1024, 1024, GROUP_WIDE, true, FMT_FP8).idle);
+  // tensor-wise scaling: one pass where it was measured to pay, and more readily with fewer launches in its way
+  for (int opt = 0; opt < 8; ++opt) {
+    const StateLayout l = {(opt & 1) != 0, (opt & 2) != 0, (opt & 4) != 0};
+    CHECK(one_pass_pays(l, 1, 1, 256, false, false) && one_pass_pays(l, 1, 256, 256, false, false));
+    CHECK(!one_pass_pays(l, 17000000, 257, 256, false, false) && !one_pass_pays(l, 1, 1, 256, true, false) && !one_pass_pays(l, 1, 1, 256, false, true));
+    bool before[4] = {false, false, false, false};
+    for (uint64_t bytes = 1 << 20; bytes < 1ull << 31; bytes += bytes / 8) {
+      for (int k = 0; k < 4; ++k) {
+        const bool now = one_pass_pays(l, bytes, 1000, 256, (k & 1) != 0, (k & 2) != 0);
+        CHECK(now || !before[k]);
+        CHECK(!now || ((!(k & 1) || before[k - 1] || one_pass_pays(l, bytes, 1000, 256, false, (k & 2) != 0)) &&
+                       (!(k & 2) || one_pass_pays(l, bytes, 1000, 256, (k & 1) != 0, false))));
+        before[k] = now;
+      }
+    }
+    CHECK(before[0] && before[1] && before[2] && before[3]);
+  }
+  CHECK(array_bytes(1000, FMT_FP8, {true, false, false}) == 11000 && array_bytes(1000, FMT_INT4, {true, true, false}) == 6500);
+  CHECK(array_bytes(1000, FMT_FP8, {false, false, true}) == 11000 && array_bytes(1000, FMT_BF16_PLAIN, {true, true, true}) == 8000);
   std::printf("geometry ok\n");
   return 0;
 }

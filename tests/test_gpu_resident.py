@@ -83,6 +83,46 @@ def test_tiles_whose_wait_is_given_up_are_finished_from_memory(fmt, bf16, over):
     dw.close()
 
 
+def beside_enough(wl, bf16, over):
+    """The workload with tensors behind it that make one pass the faster form of its list (small lists, and those beside a
+    longer tensor, are stepped in two): how many there are, 4.7 M elements each, goes by the bytes of a parameter."""
+    few = not bf16 or over.get("mode", 1) >= 2                       # fp32 state or an fp32 array beside it
+    wl.tensors = wl.tensors + [T(f"fill{i}", (4_700_000,), wl.tensors[0].fmt, granularity="tensor") for i in range(7 if few else 14)]
+    return wl
+
+
+@pytest.mark.parametrize("which", ["edges", "long"])
+@pytest.mark.parametrize("fmt,bf16,over", VARIANTS)
+def test_one_pass_matches_the_oracle_in_a_list_that_it_pays_for(fmt, bf16, over, which):
+    from paper_2601_22101_amd import harness
+    wl = workload(fmt, bf16, which)
+    n = len(wl.tensors)
+    dw = harness.DeviceWorkload(beside_enough(wl, bf16, over), DEV, layout=over)
+    host = [host_copy(tv) for tv in dw.tensors[:n]]
+    for k in (1, 2) if which == "edges" else (1,):
+        dw.fill_gradients(k)
+        check(dw, host, k, bf16)
+    dw.close()
+
+
+@pytest.mark.parametrize("fmt,bf16,over", VARIANTS)
+def test_slabs_whose_wait_is_given_up_in_a_list_that_one_pass_pays_for(fmt, bf16, over):
+    from paper_2601_22101_amd import binding as eco
+    from paper_2601_22101_amd import harness
+    ts = [T(f"t{i}", (n,), fmt, grad_std=1e-3, granularity="tensor") for i, n in enumerate((SLAB * 30 + 13, 8200, SLAB * 11 + 512 + 8, 60000, SLAB * 25))]
+    wl = workloads.Workload("given_up_long", ts, steps=4, state_bf16=bf16, scale_bf16=bf16)
+    dw = harness.DeviceWorkload(beside_enough(wl, bf16, over), DEV, layout=over)
+    host = [host_copy(tv) for tv in dw.tensors[:len(ts)]]
+    try:
+        for k, limit in ((1, 2048), (2, -1), (3, 100_000), (4, 1024)):
+            eco.eco_set_option(3, limit)
+            dw.fill_gradients(k)
+            check(dw, host, k, bf16)
+    finally:
+        eco.eco_set_option(3, -1)
+    dw.close()
+
+
 def test_two_plans_on_two_streams_share_the_chip():
     """Neither kernel has all its workgroups resident; each plan has scratch of its own."""
     from paper_2601_22101_amd import harness
