@@ -140,6 +140,14 @@ constexpr uint64_t RIDE_ALONG_WAVES = 65536;   // largest wide-group launch that
 // short-list kernel instead.
 constexpr uint64_t SMALL_ELEMENTS = 1ull << 23;
 
+// How much of a step's arrays comes from HBM and not from the 256 MB cache before it, by the bytes of the arrays, each
+// counted once: the caps on resident waves were measured against none over 1 to 256 M elements, and the two met between
+// 340 and 420 MB where the traffic in flight is little (bf16 state), between 60 and 120 MB elsewhere.
+struct HbmBound {
+  bool half, fully;
+  explicit HbmBound(uint64_t bytes) : half(bytes >= 96000000), fully(bytes >= 384000000) {}
+};
+
 int num_compute_units() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
@@ -151,10 +159,18 @@ int num_compute_units() {
 // moved per 512-element tile: HBM delivers most with a certain amount of tile traffic in flight per compute unit, and
 // more waves than that only add latency.  bf16 state, Adam (us, without a cap -> with it): INT4, 1.39 G elements, 2689 ->
 // 2470 at 21 waves (2558 at 18, 2655 at 25); FP8, 0.42 G elements, 885 -> 824 at 18 (857 at 21, 855 at 16), with master weights 1423 -> 1310 at 12 (1381 at 16).
-int default_waves(const eco::KernelVariant &kv) {
-  // unquantized weights (22 B/parameter with fp32 state, 14 with bf16), 148 M elements: 614 -> 561 us, 374 -> 337
-  if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) return kv.state_bf16 ? 13 : 12;
+// Unquantized weights (22 B/parameter with fp32 state, 14 with bf16), 148 M elements: 614 -> 561 us, 374 -> 337.
+// That holds for arrays that come from HBM (see HbmBound): where a step finds them in the cache before it, a cap costs up
+// to 24 % (bf16 state, us, without / with: FP8 4 M elements 9.3 / 10.4, 32 M 61.1 / 60.3, 64 M 142 / 137; INT4 32 M 56.2 / 56.3,
+// 48 M 85.0 / 88.2, 64 M 129.4 / 127.5; master weights 4 M 14.0 / 15.7, 32 M 105.1 / 107.7, 64 M 226 / 213; unquantized 4 M 8.6 / 10.4,
+// 16 M 38.9 / 37.8).  The caps of fp32 state have no such line.
+int default_waves(const eco::KernelVariant &kv, const HbmBound &hbm) {
+  if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) {
+    if (kv.state_bf16) return (eco::algo_is_adam(kv.algo) ? hbm.half : hbm.fully) ? 13 : 0;
+    return hbm.half ? 12 : 0;
+  }
   if (kv.state_bf16) {
+    if (!hbm.fully) return 0;
     if (kv.algo == eco::ALGO_ADAM) return kv.fmt == eco::FMT_INT4 ? 21 : 18;
     return kv.algo == eco::ALGO_ADAM_MASTER ? 12 : 0;
   }
@@ -168,9 +184,12 @@ int default_waves(const eco::KernelVariant &kv) {
 }
 
 // The two tensor-wise passes over 210 M elements (us): Adam, fp32 state 1119 at 16 waves (1176 without a cap); INT4 with
-// bf16 state 623 at 21 (645); SGDM 676 at 18 (703).
-int tensorwise_waves(const eco::KernelVariant &kv) {
-  if (kv.algo == eco::ALGO_ADAM) return kv.state_bf16 ? 21 : 16;
+// bf16 state 623 at 21 (645); SGDM 676 at 18 (703).  The last two for arrays from HBM only (one tensor of 4.7 M elements:
+// SGDM 22.6 without a cap, 24.8 with it).
+int tensorwise_waves(const eco::KernelVariant &kv, const HbmBound &hbm) {
+  if (kv.algo == eco::ALGO_ADAM && !kv.state_bf16) return 16;
+  if (!hbm.fully) return 0;
+  if (kv.algo == eco::ALGO_ADAM) return 21;
   return kv.algo == eco::ALGO_SGDM && !kv.state_bf16 ? 18 : 0;
 }
 
@@ -240,7 +259,8 @@ eco::KernelVariant variant_for(const eco_hparams_t *hp, int f) {
 
 // The scalar part of the kernel arguments: step constants, random-stream key, launch options.  idle: see wide_workgroups.
 typedef uint32_t IdleUnits[eco::MAX_WIDE_WAVES + 1];
-void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const IdleUnits &idle, eco::StepLaunch *sl) {
+void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const IdleUnits &idle, uint64_t bytes,
+                       eco::StepLaunch *sl) {
   eco::StepArgs *a = &sl->args;
   a->b1 = c.b1; a->omb1 = c.omb1; a->b2 = c.b2; a->omb2 = c.omb2; a->rbc2 = c.rbc2; a->c1 = c.c1; a->eps = c.eps;
   a->kappa = c.kappa; a->lr = c.lr; a->alpha = c.alpha; a->wd = c.wd; a->inv_lr = c.inv_lr; a->inv_lr_beta = c.inv_lr_beta;
@@ -251,20 +271,24 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   const int64_t opt_threads = g_max_launch_threads.load(std::memory_order_relaxed);
   sl->max_launch_threads = opt_threads > 0 ? static_cast<uint64_t>(opt_threads) : eco::MAX_LAUNCH_THREADS;
   a->unit_base = 0;
-  const int waves = default_waves(kv);
+  const HbmBound hbm(bytes);
+  const int waves = default_waves(kv, hbm);
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
   sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
+    // (workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too: 4 M elements 9.7 against 10.2 us)
+    const bool worth = kv.state_bf16 ? hbm.fully || nw == 4 || nw == 8 : hbm.half;
+    const unsigned k = worth ? eco::wide_workgroups(kv, nw, sl->num_wide[nw], idle[nw]) : 0;
     // Adam with fp32 state keeps the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
     // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 1000: 472 against 630, of 2048: 467
     // against 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
     const uint32_t per_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves, 256);
     sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (kv.algo == eco::ALGO_ADAM && !kv.state_bf16)
                                  ? std::min(per_wave * nw, 65536u)
-                                 : eco::lds_for_workgroups(eco::wide_workgroups(kv, nw, sl->num_wide[nw], idle[nw]));
+                                 : eco::lds_for_workgroups(k);
   }
-  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv), 256);
+  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv, hbm), 256);
 }
 
 
@@ -352,6 +376,7 @@ struct eco_plan {
   int cus = 256;
   int device = 0;    // the device that was current when the plan was created (its tables live there)
   Lists lists[4];    // indexed by eco_format_t; unquantized tensors may be in a quantized format's lists
+  uint64_t bytes = 0;                    // of all arrays
   bool unfinished = false;               // a step has stopped between its launches: scratch may hold what it left
   eco::TensorDesc *d_descs = nullptr;
   uint32_t *d_tables = nullptr;          // all lists, back to back, then the abs-max slots and the scratch of the tensor-wise passes
@@ -537,6 +562,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
   try {
     // validation and placement; how much there is of every list
     std::vector<eco::Placement> place(n);
+    const eco::StateLayout state = state_layout(layout);
     uint64_t tensors_of[4] = {0}, entries_of[4] = {0}, list_entries[4][eco::LIST_COUNT] = {{0}};
     for (size_t i = 0; i < n && st == ECO_OK; ++i) {
       const eco_tensor_t &t = tensors[i];
@@ -548,6 +574,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       place[i] = eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt);
       tensors_of[t.fmt] += 1;
       entries_of[t.fmt] += place[i].entries;
+      plan->bytes += eco::array_bytes(t.numel, t.fmt, state);
       uint64_t &in_list = list_entries[t.fmt][place[i].list];
       in_list += place[i].entries;
       if (in_list > 0x7FFFFFF0ull) st = fail(ECO_EUNSUPPORTED, "plan: more than 2^31 tiles in one launch");
@@ -558,7 +585,6 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     plan->cus = num_compute_units();
     // tensors with one scale that the chip can hold: one pass, if it pays for those of the format
     const bool bf16 = layout->state_dtype == ECO_DT_BF16;
-    const eco::StateLayout state = state_layout(layout);
     const uint64_t max_slabs = std::min<uint64_t>(eco::res_waves(bf16) * 64, eco::res_slabs_per_wg(bf16) * plan->cus);
     for (int f = 0; f < 2; ++f) {
       uint64_t bytes = 0, slabs = 0;
@@ -668,10 +694,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
 }
 
 // Launches the step of one format's lists (sl: everything but the scalars).
-static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, const IdleUnits &idle, eco::StepLaunch *sl,
-                                  eco::SmallArgs *small, hipStream_t stream) {
+static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, const IdleUnits &idle, uint64_t bytes,
+                                  eco::StepLaunch *sl, eco::SmallArgs *small, hipStream_t stream) {
   const eco::KernelVariant kv = variant_for(hp, f);
-  fill_step_scalars(hp, c, kv, idle, sl);
+  fill_step_scalars(hp, c, kv, idle, bytes, sl);
   sl->extra_in = home_of_extra(sl->args.num_tiles, sl->args.num_extra, sl->num_wide);
   sl->max_tile_threads = tile_threads(sl->max_launch_threads, cus);
   // the limit on a launch's threads holds for the one launch of the short-list kernel too (without tables it is the only way)
@@ -739,7 +765,7 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     sl.resident_wgs = static_cast<unsigned>(plan->cus);
     eco::SmallArgs small;                  // a copy: steps of one plan may be enqueued by different calls
     if (g.small) { small = *g.small; sl.small_wgs = g.small_wgs; sl.small_waves = g.small_waves; }
-    st = launch_format(hp, c, f, plan->cus, g.idle, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
+    st = launch_format(hp, c, f, plan->cus, g.idle, plan->bytes, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
     if (st != ECO_OK) return st;
   }
   plan->unfinished = false;
@@ -773,7 +799,8 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   // pass 1: validate, place, count the entries of every launch list
   constexpr int L_TW_TENSORS = eco::LIST_COUNT, L_COUNT = eco::LIST_COUNT + 1;
   uint64_t count[4][L_COUNT] = {{0}}, tensors_of[4] = {0}, entries_of[4] = {0}, most_tw_tiles[4] = {0};
-  uint64_t total = 0, elements = 0;
+  uint64_t total = 0, elements = 0, bytes = 0;
+  const eco::StateLayout state = state_layout(hp);
   IdleUnits idle[4] = {{0}};
   const auto place = [&](size_t i, eco::Placement *p) {
     uint64_t gsz = 0;
@@ -792,6 +819,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     tensors_of[tensors[i].fmt] += 1;
     entries_of[tensors[i].fmt] += p.entries;
     elements += tensors[i].numel;
+    bytes += eco::array_bytes(tensors[i].numel, tensors[i].fmt, state);
     tensorwise = tensorwise || p.list == eco::LIST_TW_TILES;
     total += p.entries;
     if (total > MAX_UNITS)
@@ -834,7 +862,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     if (fits) {
       for (int f = 0; f < 2; ++f) {
         if (!sl[f].small_wgs) continue;
-        st = launch_format(hp, c, f, cus, idle[f], &sl[f], &small[f], hs);
+        st = launch_format(hp, c, f, cus, idle[f], bytes, &sl[f], &small[f], hs);
         if (st != ECO_OK) return st;
       }
       return ECO_OK;
@@ -924,7 +952,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     a.num_tw_tiles = static_cast<uint32_t>(count[f][eco::LIST_TW_TILES]);
     a.num_tw_tensors = static_cast<uint32_t>(count[f][L_TW_TENSORS]);
     a.tw_reduce_wgs = eco::tw_reduce_workgroups(most_tw_tiles[f]);
-    st = launch_format(hp, c, f, cus, idle[f], &sl, nullptr, hs);
+    st = launch_format(hp, c, f, cus, idle[f], bytes, &sl, nullptr, hs);
     if (st != ECO_OK) return st;
   }
   return ECO_OK;
@@ -1001,7 +1029,7 @@ eco_status_t eco_bandwidth_probe(int32_t kind, void *codes, void *scales, const 
   eco::KernelVariant kv;
   kv.fmt = eco::FMT_FP8; kv.state_bf16 = 0; kv.scale_bf16 = 0; kv.algo = eco::ALGO_ADAM; kv.round = eco::ROUND_SR;
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
-  const uint32_t lds = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(default_waves(kv), 512);
+  const uint32_t lds = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(default_waves(kv, HbmBound(0)), 512);
   (void)hipGetLastError();
   const hipError_t e = eco::launch_bandwidth_probe(kind, codes, scales, grad, m, v, numel, lds, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? ECO_OK : fail_hip(e, "probe kernel launch");

@@ -75,7 +75,7 @@ inline bool one_pass_pays(const StateLayout &l, uint64_t bytes, uint64_t slabs, 
   const uint64_t MB = 1000000;
   if (!l.state_bf16 || l.aux) return bytes >= 44 * MB + (tails ? 52 * MB : 0) + (beside_longer ? 132 * MB : 0);
   if (!l.adam) return bytes >= 384 * MB;
-  return bytes >= (beside_longer ? (tails ? 416 * MB : 312 * MB) : tails ? 256 * MB : 44 * MB);
+  return bytes >= (beside_longer ? (tails ? 416 * MB : 280 * MB) : tails ? 256 * MB : 44 * MB);
 }
 // Workgroups of the finishing kernel: a wave to each tensor, for its scale, and where waits may be given up enough for the
 // slabs that are then marked, a workgroup to each up to four per compute unit (they return after one load where none is:

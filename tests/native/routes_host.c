@@ -1,0 +1,125 @@
+/* What a step launches, without a GPU: this program's runtime calls stand before HIP's, record every launch and let it pass.
+ * Each case says how many launches a plan's step makes and which of them ask for LDS, the request that caps resident waves. */
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <hip/hip_runtime_api.h>
+
+#include "eco.h"
+
+enum { MOST = 64 };
+static int launches;
+static size_t lds_of[MOST], pushed_lds;
+
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream) {
+  (void)f; (void)grid; (void)block; (void)args; (void)stream;
+  if (launches < MOST) lds_of[launches] = lds;
+  ++launches;
+  return hipSuccess;
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+  (void)grid; (void)block; (void)stream;
+  pushed_lds = lds;
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *stream) {
+  grid->x = grid->y = grid->z = block->x = block->y = block->z = 1;
+  *lds = pushed_lds;
+  *stream = NULL;
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetDevice(int *device) { *device = 0; return hipSuccess; }
+hipError_t hipSetDevice(int device) { (void)device; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *x, hipDeviceAttribute_t a, int device) { (void)a; (void)device; *x = 256; return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) { *p = malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind k) { (void)k; memcpy(d, s, n); return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *symbol) { (void)symbol; *p = (void *)0x100000; return hipSuccess; }
+
+enum { ROW = -1, TENSOR = -2, PLAIN = -3 };
+enum { FP8 = ECO_FMT_FP8_E4M3, INT4 = ECO_FMT_INT4, F32 = ECO_DT_FP32, BF16 = ECO_DT_BF16, ADAM = ECO_OPT_ADAM, SGDM = ECO_OPT_SGDM };
+typedef struct {
+  const char *what;
+  int fmt, state, opt, mode;
+  struct { int count, scale; uint64_t rows, cols; } t[3];    /* scale: elements, or ROW, TENSOR, PLAIN */
+  int launches;
+  int capped;                                                /* bit i: launch i asks for LDS */
+} Case;
+
+static const Case cases[] = {
+    /* full tiles: the caps of bf16 state for arrays beyond the cache, those of fp32 state always */
+    {"block bf16, 16 M", FP8, BF16, ADAM, ECO_MODE_ECO, {{16, 128, 1024, 1024}}, 1, 0},
+    {"block bf16, 64 M", FP8, BF16, ADAM, ECO_MODE_ECO, {{64, 128, 1024, 1024}}, 1, 1},
+    {"block bf16 INT4, 48 M", INT4, BF16, ADAM, ECO_MODE_ECO, {{48, 128, 1024, 1024}}, 1, 0},
+    {"block bf16 INT4, 64 M", INT4, BF16, ADAM, ECO_MODE_NAIVE, {{64, 128, 1024, 1024}}, 1, 1},
+    {"block bf16 master, 24 M", FP8, BF16, ADAM, ECO_MODE_MASTER, {{24, 128, 1024, 1024}}, 1, 0},
+    {"block bf16 master, 48 M", FP8, BF16, ADAM, ECO_MODE_MASTER, {{48, 128, 1024, 1024}}, 1, 1},
+    {"block fp32, 1 M", FP8, F32, ADAM, ECO_MODE_ECO, {{1, 128, 1024, 1024}}, 1, 1},
+    {"block bf16 SGDM", FP8, BF16, SGDM, ECO_MODE_ECO, {{128, 128, 1024, 1024}}, 1, 0},
+    /* unquantized */
+    {"plain, 4 M", FP8, F32, ADAM, ECO_MODE_ECO, {{4, PLAIN, 1024, 1024}}, 1, 0},
+    {"plain, 16 M", FP8, F32, ADAM, ECO_MODE_ECO, {{16, PLAIN, 1024, 1024}}, 1, 1},
+    {"plain bf16 SGDM, 48 M", FP8, BF16, SGDM, ECO_MODE_ECO, {{48, PLAIN, 1024, 1024}}, 1, 0},
+    {"plain bf16 SGDM, 96 M", FP8, BF16, SGDM, ECO_MODE_ECO, {{96, PLAIN, 1024, 1024}}, 1, 1},
+    /* rows */
+    {"rows of 768, bf16, 16 M", FP8, BF16, ADAM, ECO_MODE_ECO, {{20, ROW, 1024, 768}}, 1, 0},
+    {"rows of 768, bf16, 63 M", FP8, BF16, ADAM, ECO_MODE_ECO, {{80, ROW, 1024, 768}}, 1, 1},
+    {"rows of 1000, bf16", FP8, BF16, ADAM, ECO_MODE_ECO, {{80, ROW, 1024, 1000}}, 1, 0},
+    {"rows of 2304, bf16", FP8, BF16, ADAM, ECO_MODE_ECO, {{40, ROW, 1024, 2304}}, 1, 0},
+    {"rows of 1000 and of 1024, bf16, a tenth idle", FP8, BF16, ADAM, ECO_MODE_ECO, {{9, ROW, 1024, 1000}, {81, ROW, 1024, 1024}}, 1, 1},
+    {"rows of 1800, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{20, ROW, 1024, 1800}}, 1, 0},
+    {"rows of 768, master, 4 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{5, ROW, 1024, 768}}, 1, 0},
+    {"rows of 768, master, 8 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{10, ROW, 1024, 768}}, 1, 1},
+    /* tensor-wise: two launches in one pass (three with a tail), four in two passes, and which of these are capped */
+    {"three small tensors", FP8, F32, ADAM, ECO_MODE_ECO, {{3, TENSOR, 1, 40000}}, 2, 0},
+    {"three small tensors with tails", FP8, F32, ADAM, ECO_MODE_ECO, {{3, TENSOR, 1, 40001}}, 4, 5},
+    {"two turns", INT4, BF16, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1, 200000}}, 4, 0},
+    {"many turns", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}}, 2, 0},
+    {"many turns with tails", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}, {1, TENSOR, 1, 8193}}, 3, 0},
+    {"beside a long one", INT4, BF16, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1, 870000}, {1, TENSOR, 1, 7000000}}, 4, 0},
+    {"more beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1408, 2048}, {1, TENSOR, 1, 7000000}}, 6, 20},
+    {"a long one, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{1, TENSOR, 1, 7000000}}, 4, 0},
+    {"a longer one, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{1, TENSOR, 1, 70000000}}, 4, 5},
+};
+
+int main(void) {
+  static eco_tensor_t list[128];
+  int bad = 0;
+  for (size_t c = 0; c < sizeof cases / sizeof *cases; ++c) {
+    const Case *k = &cases[c];
+    size_t n = 0;
+    memset(list, 0, sizeof list);
+    for (int g = 0; g < 3; ++g)
+      for (int i = 0; i < k->t[g].count; ++i, ++n) {
+        eco_tensor_t *t = &list[n];
+        t->weights = (void *)0x1000; t->scales = (void *)0x2000; t->grad = (void *)0x3000; t->m = (void *)0x4000; t->v = (void *)0x5000; t->aux = (void *)0x6000;
+        t->numel = k->t[g].rows * k->t[g].cols;
+        t->group_size = k->t[g].scale == ROW ? k->t[g].cols : k->t[g].scale == TENSOR ? t->numel : k->t[g].scale == PLAIN ? 0 : (uint64_t)k->t[g].scale;
+        t->tensor_id = (uint32_t)n;
+        t->fmt = k->t[g].scale == PLAIN ? ECO_FMT_BF16_PLAIN : k->fmt;
+      }
+    eco_hparams_t hp;
+    memset(&hp, 0, sizeof hp);
+    hp.opt = k->opt; hp.mode = k->mode; hp.block_size = 128; hp.state_dtype = hp.scale_dtype = k->state;
+    hp.lr = 1e-3; hp.beta1 = 0.9; hp.beta2 = 0.999; hp.eps = 1e-8; hp.step = 1;
+    eco_plan_t *plan = NULL;
+    if (eco_plan_create(list, n, &hp, &plan) != ECO_OK) { printf("FAILED: %s: %s\n", k->what, eco_last_error()); return 1; }
+    for (int again = 0; again < 2; ++again) {
+      launches = 0;
+      if (eco_step(plan, &hp, NULL) != ECO_OK) { printf("FAILED: %s: %s\n", k->what, eco_last_error()); return 1; }
+      int capped = 0;
+      for (int i = 0; i < launches && i < MOST; ++i) capped |= (lds_of[i] != 0) << i;
+      if (launches != k->launches || capped != k->capped) {
+        printf("%s: %d launches, capped %d; expected %d, %d\n", k->what, launches, capped, k->launches, k->capped);
+        ++bad;
+      }
+    }
+    (void)eco_plan_destroy(plan);
+  }
+  if (bad) return 1;
+  printf("routes ok\n");
+  return 0;
+}

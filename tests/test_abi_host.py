@@ -285,19 +285,30 @@ def test_launch_geometry_host_checks(tmp_path):
     assert out.returncode == 0 and "geometry ok" in out.stdout, out.stdout
 
 
-def test_the_allocation_free_step_allocates_no_host_memory(eco, tmp_path):
-    """eco_step_tensors_noalloc under a counting operator new, with launches that end in the test: tests/native/noalloc_host.c."""
+def run_with_stand_in_runtime(tmp_path, name):
+    """Output of tests/native/<name>.c, a program whose own HIP calls stand before the runtime's: no GPU is needed."""
     import subprocess
     lib = os.environ.get("ECO_LIB_PATH") or os.path.join(ROOT, "paper_2601_22101_amd", "libeco.so")
     lib_dir = os.path.dirname(os.path.abspath(lib))
-    exe = str(tmp_path / "noalloc_host")
+    exe = str(tmp_path / name)
     cmd = ["gcc", "-O1", "-std=gnu11", "-Wall", "-Wextra", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
-           os.path.join(ROOT, "tests", "native", "noalloc_host.c"), "-o", exe, "-Wl,--export-dynamic", "-L", lib_dir,
+           os.path.join(ROOT, "tests", "native", name + ".c"), "-o", exe, "-Wl,--export-dynamic", "-L", lib_dir,
            "-l:" + os.path.basename(lib), f"-Wl,-rpath,{lib_dir}"]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
     out = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
-    assert out.returncode == 0 and "no host allocation" in out.stdout, out.stdout
+    assert out.returncode == 0, out.stdout
+    return out.stdout
+
+
+def test_the_allocation_free_step_allocates_no_host_memory(eco, tmp_path):
+    """eco_step_tensors_noalloc under a counting operator new."""
+    assert "no host allocation" in run_with_stand_in_runtime(tmp_path, "noalloc_host")
+
+
+def test_what_a_step_launches(eco, tmp_path):
+    """The launches of plans either side of every line of the dispatch, and which of them cap resident waves."""
+    assert "routes ok" in run_with_stand_in_runtime(tmp_path, "routes_host")
 
 
 def test_a_plain_c_client_compiles_links_and_runs(eco, tmp_path):
