@@ -802,35 +802,47 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   uint64_t total = 0, elements = 0, bytes = 0;
   const eco::StateLayout state = state_layout(hp);
   IdleUnits idle[4] = {{0}};
-  const auto place = [&](size_t i, eco::Placement *p) {
-    uint64_t gsz = 0;
-    int cls = 0;
-    const eco_status_t s = check_tensor(tensors[i], i, hp, &gsz, &cls);
-    const int32_t fmt = tensors[i].fmt;
-    if (s == ECO_OK) *p = eco::place_tensor(tensors[i].numel, gsz, cls, fmt == ECO_FMT_FP8_E4M3 || fmt == ECO_FMT_INT4, fmt);
-    return s;
+  // the placement of a tensor that check_tensor has let through
+  const auto place = [&](const eco_tensor_t &t) {
+    const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
+    const uint64_t gsz = t.group_size ? t.group_size : hp->block_size;
+    return eco::place_tensor(t.numel, gsz, quantized ? eco::classify_group(gsz, t.numel) : eco::GROUP_BLOCK, quantized, t.fmt);
   };
   bool tensorwise = false;
   for (size_t i = 0; i < n; ++i) {
-    eco::Placement p;
-    st = place(i, &p);
+    const int f = tensors[i].fmt;
+    uint64_t gsz = 0;
+    int cls = 0;
+    st = check_tensor(tensors[i], i, hp, &gsz, &cls);
     if (st != ECO_OK) return st;
+    const eco::Placement p = place(tensors[i]);
     if (p.entries > MAX_UNITS) return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: tensor %zu alone exceeds the static scratch", i);
-    tensors_of[tensors[i].fmt] += 1;
-    entries_of[tensors[i].fmt] += p.entries;
+    tensors_of[f] += 1;
+    entries_of[f] += p.entries;
     elements += tensors[i].numel;
-    bytes += eco::array_bytes(tensors[i].numel, tensors[i].fmt, state);
-    tensorwise = tensorwise || p.list == eco::LIST_TW_TILES;
+    bytes += eco::array_bytes(tensors[i].numel, f, state);
     total += p.entries;
     if (total > MAX_UNITS)
       return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: more than %u launch-table entries (512-element tiles, or scale "
                   "groups wider than 512): the static scratch does not hold them (use a plan)", MAX_UNITS);
+    count[f][p.list] += p.units;
+    if (p.idle) idle[f][p.list - eco::LIST_WIDE1 + 1] += static_cast<uint32_t>(p.units);
+    if (p.tail) count[f][eco::LIST_EXTRA] += 1;
+    if (p.list == eco::LIST_TW_TILES) {
+      tensorwise = true;
+      count[f][L_TW_TENSORS] += 1;
+      most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
+    }
   }
   const int plain_home = home_of_plain(tensors_of, entries_of);
   const auto format_of = [&](size_t i) {
     const int32_t fmt = tensors[i].fmt;
     return fmt == ECO_FMT_FP8_E4M3 || fmt == ECO_FMT_INT4 || plain_home < 0 ? fmt : plain_home;
   };
+  for (int f = eco::FMT_BF16_PLAIN; f <= eco::FMT_FP32_ID && plain_home >= 0; ++f) {
+    count[plain_home][eco::LIST_EXTRA] += count[f][eco::LIST_EXTRA];
+    count[f][eco::LIST_EXTRA] = 0;
+  }
   (void)hipGetLastError();
   hipStream_t hs = static_cast<hipStream_t>(stream);
   eco_constants_t c;
@@ -851,7 +863,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       if (!fits) break;
       SmallItem &it = items[f][held[f]++];
       it.t = &tensors[i];
-      (void)place(i, &it.p);
+      it.p = place(tensors[i]);
     }
     for (int f = 0; f < 2 && fits; ++f) {
       if (!held[f]) continue;
@@ -869,18 +881,6 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     }
   }
 
-  for (size_t i = 0; i < n; ++i) {
-    eco::Placement p;
-    (void)place(i, &p);
-    const int f = format_of(i);
-    count[f][p.list] += p.units;
-    if (p.idle) idle[f][p.list - eco::LIST_WIDE1 + 1] += static_cast<uint32_t>(p.units);
-    if (p.tail) count[f][eco::LIST_EXTRA] += 1;
-    if (p.list == eco::LIST_TW_TILES) {
-      count[f][L_TW_TENSORS] += 1;
-      most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
-    }
-  }
   uint32_t start[4][L_COUNT], tw_tile_start[4], tw_tensor_start[4];
   {
     uint32_t pos = 0, tw_tiles = 0, tw_tensors = 0;
@@ -901,8 +901,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   std::memset(&ba, 0, sizeof ba);
   ba.scratch = sp;
   for (size_t i = 0; i < n; ++i) {
-    eco::Placement p;
-    (void)place(i, &p);
+    const eco::Placement p = place(tensors[i]);
     const int f = format_of(i);
     const uint32_t k = ba.count++;
     if (k == 0) ba.first_index = static_cast<uint32_t>(i);
