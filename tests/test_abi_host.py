@@ -285,6 +285,43 @@ def test_launch_geometry_host_checks(tmp_path):
     assert out.returncode == 0 and "geometry ok" in out.stdout, out.stdout
 
 
+class _FakeTorch:
+    """The part of torch that the binding asks for the current stream, with a choice of raw lookup."""
+
+    def __init__(self, raw):
+        from types import SimpleNamespace as NS
+        self.current = 0
+        outer = self
+
+        class On:
+            def __init__(self, s): self.s = s
+            def __enter__(self): self.before, outer.current = outer.current, self.s.cuda_stream
+            def __exit__(self, *exc): outer.current = self.before
+
+        self.cuda = NS(current_stream=lambda: NS(cuda_stream=self.current), stream=On, ExternalStream=lambda p: NS(cuda_stream=p))
+        self._C = NS(_cuda_getDevice=lambda: 0)
+        if raw:
+            self._C._cuda_getCurrentRawStream = lambda device: raw(self)
+
+
+def test_the_raw_stream_lookup_is_used_only_if_it_follows_the_current_stream(eco):
+    """A lookup that answers with the default stream, or with whichever stream came first, agrees with the Stream object as
+    long as that stream is current."""
+    right = _FakeTorch(lambda t: t.current)
+    found = eco._find_raw_stream(right)
+    assert found is not None and found() == 0
+    right.current = 4096
+    assert found() == 4096 and eco._find_raw_stream(right)() == 4096
+    first = []
+    for wrong in (lambda t: 0, lambda t: first.append(t.current) or first[0], None, lambda t: None):
+        fake = _FakeTorch(wrong)
+        assert eco._find_raw_stream(fake) is None and fake.current == 0
+
+    def fails(t):
+        raise RuntimeError("no such device")
+    assert eco._find_raw_stream(_FakeTorch(fails)) is None
+
+
 def run_with_stand_in_runtime(tmp_path, name):
     """Output of tests/native/<name>.c, a program whose own HIP calls stand before the runtime's: no GPU is needed."""
     import subprocess
