@@ -69,9 +69,11 @@ constexpr uint32_t SQRT_MID_HI = 0x6F800000u;   // 2^96
 // Newton step on the reciprocal, the quotient and one residual correction, every step a fused multiply-add.  The sequence
 // the compiler emits for `/` pre-scales its operands, corrects twice, scales back and fixes special cases up.  In the
 // stated ranges neither operand needs scaling (no denormal, the exponents less than 96 apart, reciprocal and quotient
-// normal) and nothing is special, and the second correction never changes the result: compared on the device for all
-// 2^46 pairs of significands (the sequence commutes with scaling by powers of two inside the ranges), and, by the
-// library's self-test entry, for every d of the range against `/`.  `/` covers everything outside.
+// normal) and nothing is special, and the second correction never changes the result: the sum before the last rounding is
+// within 2^-22 units of n / d, which leaves one pair of significands in a million to look at; on all of those the sequence
+// is right for any reciprocal estimate within 2 units, but for two pairs that depend on it and are right on the device
+// (tests/native/division_proof.c; the sequence commutes with scaling by powers of two inside the ranges).  The library's
+// self-test entry compares with `/` for every d of the range.  `/` covers everything outside.
 __device__ __forceinline__ float div_rn_midrange(float n, float d) {
   const float y0 = __builtin_amdgcn_rcpf(d);
   const float e0 = fmaf(-d, y0, 1.0f);

@@ -348,6 +348,22 @@ def test_what_a_step_launches(eco, tmp_path):
     assert "routes ok" in run_with_stand_in_runtime(tmp_path, "routes_host")
 
 
+def test_the_short_division_is_correctly_rounded_but_for_pairs_that_the_device_settles(tmp_path):
+    """tests/native/division_proof.c: of all 2^46 pairs of significands only those near the middle between two floats can
+    fail, and of these only two do for some reciprocal estimate within its error; test_gpu_parity.py runs those."""
+    import subprocess
+    exe = str(tmp_path / "division_proof")
+    cmd = ["gcc", "-O2", "-std=gnu11", "-Wall", "-Wextra", "-Werror", "-ffp-contract=off", "-fopenmp", "-march=native",
+           os.path.join(ROOT, "tests", "native", "division_proof.c"), "-o", exe, "-lm"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    out = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert out.returncode == 0, out.stdout
+    pairs = {tuple(map(int, line.split()[1:])) for line in out.stdout.splitlines() if line.startswith("open")}
+    from test_gpu_parity import OPEN_DIVISIONS
+    assert pairs == set(OPEN_DIVISIONS), out.stdout
+
+
 def test_a_plain_c_client_compiles_links_and_runs(eco, tmp_path):
     """include/eco.h is valid C99 (-Wall -Wextra -pedantic -Werror), libeco.so links by its C names, and the
     host-only entry points give a C caller what they give the Python binding."""

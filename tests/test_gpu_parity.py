@@ -69,6 +69,23 @@ def test_the_step_uses_every_bit_of_seed_step_and_tensor_id(eco, o32, fmt):
         assert st["code_mismatch"] == 0 and st["m_bit_mismatch"] == 0, st
 
 
+# significands (numerator, denominator) for which the short division's rounding depends on the reciprocal estimate, see
+# tests/native/division_proof.c
+OPEN_DIVISIONS = ((8388608, 16777215), (13981011, 16777213))
+
+
+def test_short_division_of_many_numerators(eco):
+    """The pairs that the proof on the host leaves open, and 200 numerators over a binade of denominators each (2^23; the
+    sequence commutes with scaling by powers of two)."""
+    bad = torch.zeros(1, dtype=torch.int64, device=DEV)
+    rng = np.random.default_rng(46)
+    numerators = [n for n, _ in OPEN_DIVISIONS] + [int(x) for x in rng.integers(1 << 23, 1 << 24, 200)]
+    for n in numerators:
+        eco.eco_arith_selftest(1, n * 2.0 ** -23, 0x3F800000, 0x40000000, bad)
+    torch.cuda.synchronize()
+    assert int(bad.item()) == 0
+
+
 def test_short_square_root_and_division_are_correctly_rounded(eco):
     """The step kernels use shorter sequences than sqrtf() and `/` inside stated operand ranges; the library's self-test
     compares short and long form on the device: every fp32 argument of the square root's range (1.6e9 patterns), and
