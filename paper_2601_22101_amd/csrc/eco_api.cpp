@@ -584,13 +584,12 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
     plan->cus = num_compute_units();
     // tensors with one scale that the chip can hold: one pass, if it pays for those of the format
-    const bool bf16 = layout->state_dtype == ECO_DT_BF16;
-    const uint64_t max_slabs = std::min<uint64_t>(eco::res_waves(bf16) * 64, eco::res_slabs_per_wg(bf16) * plan->cus);
+    const uint64_t max_slabs = std::min<uint64_t>(eco::RES_WAVES * 64, eco::RES_SLABS_PER_WG * plan->cus);
     for (int f = 0; f < 2; ++f) {
       uint64_t bytes = 0, slabs = 0;
       bool tails = false, longer = false;
       const auto in_one_pass = [&](size_t i) {
-        return eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, tensors[i].fmt, eco::res_slab(bf16), max_slabs);
+        return eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, tensors[i].fmt, eco::RES_SLAB, max_slabs);
       };
       for (size_t i = 0; i < n; ++i) {
         if (tensors[i].fmt != f || place[i].list != eco::LIST_TW_TILES) continue;

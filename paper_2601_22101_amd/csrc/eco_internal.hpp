@@ -45,14 +45,13 @@ enum : int {
   UNIT_WIDE = 5         // groups of 520..8192 elements: a workgroup's unit, see wide_geometry
 };
 
-// Tensor-wise scaling in one pass (eco_step_resident_kernel): slabs of one 512-element tile to each wave of a workgroup,
-// `depth` of them in hand.  The waves and what they hold fill the 512 registers of a SIMD lane: 16 waves with 4 slabs in
-// hand where the next slab's loads are bf16 state (13 registers), 12 with 5 for fp32 state (22).
-constexpr int res_waves(bool state_bf16) { return state_bf16 ? 12 : 12; }
-constexpr int res_depth(bool state_bf16) { return state_bf16 ? 5 : 5; }
-constexpr uint64_t res_slab(bool state_bf16) { return static_cast<uint64_t>(res_waves(state_bf16)) * TILE_ELEMS; }
+// Tensor-wise scaling in one pass (eco_step_resident_kernel): slabs of one 512-element tile to each of a workgroup's 12
+// waves, five of them in hand.  Three waves of 168 registers fill a SIMD's 512 (INT4, 369 M elements, us: 12 waves 940 and 16 with
+// four slabs of 128 registers 957; an earlier form 1000, and 8 with eight of 256 registers 1290).
+constexpr int RES_WAVES = 12, RES_DEPTH = 5;
+constexpr uint64_t RES_SLAB = static_cast<uint64_t>(RES_WAVES) * TILE_ELEMS;
 // Slabs a tensor may have for each workgroup: the exchange of maxima takes two of the turns in hand.
-constexpr uint64_t res_slabs_per_wg(bool state_bf16) { return static_cast<uint64_t>(res_depth(state_bf16)) - 2; }
+constexpr uint64_t RES_SLABS_PER_WG = RES_DEPTH - 2;
 // Bytes of a tensor's arrays, each counted once: whether a step finds them in the 256 MB cache in front of HBM decides
 // which form of it is the faster one.
 struct StateLayout { bool adam, state_bf16, aux; };

@@ -292,7 +292,7 @@ __device__ __forceinline__ void step_sizes8(const StepArgs &a, const float (&x)[
 // ------------------------------------------------------------------ the step of one lane
 // How the abs-max of a scale group is obtained:
 //   RED_BLOCK  the group is 2^shift elements inside one wave: DPP/swizzle all-reduce over its lanes
-//   RED_WG     the group is the whole workgroup (1..16 waves): wave all-reduce, then an LDS combine
+//   RED_WG     the group is the whole workgroup (2..16 waves): wave all-reduce, then an LDS combine
 //   RED_WG_ROWS the workgroup holds up to 16 whole groups of more than 512 elements each (a wave meets at most two of
 //              them): per wave one all-reduce for each of its groups, LDS atomic max into the group's entry
 //   RED_TILE   first pass of the step for a group larger than a workgroup (tensor-wise scaling): wave all-reduce, the wave's
@@ -343,7 +343,6 @@ __device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t 
   // RED_WG
   __shared__ uint32_t wave_max[16];
   const int nwaves = (int)(blockDim.x >> 6);
-  if (nwaves == 1) return u2f(wmax);
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = wmax;
   __syncthreads();
   uint32_t r = wave_max[0];
@@ -748,7 +747,7 @@ __global__ __launch_bounds__(1024) void eco_step_small_kernel(const SmallArgs ar
 
 // (4) One scale per tensor (tensor-wise scaling, Sec. 4.4), tensors too large for one workgroup: two passes
 // over 512-element tiles.  Pass 1 recomputes theta~ and leaves each tile's abs-max in a scratch array, which
-// a reduction kernel (one workgroup per tensor) folds into the tensor's slot; pass 2 recomputes theta~ again
+// a reduction kernel (see eco_tensorwise_reduce_kernel) folds into the tensor's slot; pass 2 recomputes theta~ again
 // (the inputs are untouched so far), quantizes against the slot's value and writes codes and state; a last
 // kernel writes the new scales.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int RED>

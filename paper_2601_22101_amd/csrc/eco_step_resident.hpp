@@ -27,18 +27,20 @@
 // event every turn, so waves are never RES_RING turns apart and an entry of the rings is not reused before all have
 // left it.
 //
-// What bounds it: memory for fp32 state (5.2 of the 6.1 TB/s of the block-scaled form), vector-ALU issue for INT4 with
-// bf16 state.  Measured, two-pass form -> this one, 369 M elements in tensors of 1408 x 2048: FP8, fp32 state 1964 ->
-// 1430 us; INT4, bf16 state 1112 -> 872 us; three tensors of 40 000 elements 14.2 -> 12.8 us.  What it took: 12 waves of
-// 168 registers rather than 8 of 256 (INT4 1290 -> 1000 us), no memory access inside a branch (1000 -> 940), an event's
-// contributions half a turn before the result is wanted (940 -> 890).
+// What bounds it: memory for fp32 state (5.2 of the 6.1 TB/s of the block-scaled form); for INT4 with bf16 state the
+// vector ALU's issue beside it (see the counters in profiles/).  Measured, two-pass form -> this one, 369 M elements in
+// tensors of 1408 x 2048: FP8, fp32 state 1964 -> 1430 us; INT4, bf16 state 1112 -> 872 us; three tensors of 40 000
+// elements 14.2 -> 12.8 us; where a list is too short for it or has company that costs launches, see one_pass_pays.  What
+// it took: 12 waves of 168 registers rather than 8 of 256 (INT4 1290 -> 1000 us), no memory access inside a branch (1000 ->
+// 940), an event's contributions half a turn before the result is wanted (940 -> 890).  17 of the 80 variants, among them
+// Adam with bf16 state and stochastic rounding, do not quite fit 168 registers and keep 2 to 11 values in scratch memory.
 #pragma once
 #include "eco_step_kernel.hpp"
 
 namespace eco {
 
 constexpr int RES_RING = 16;           // LDS entries for slabs whose maximum is being collected
-static_assert(RES_RING >= 2 * res_depth(false) && RES_RING >= 2 * res_depth(true), "resident step rings");
+static_assert(RES_RING >= 2 * RES_DEPTH, "resident step rings");
 constexpr uint32_t NO_MAX = 0xFFFFFFFFu;       // an entry of slab_max[] that has not been published (no maximum has the sign bit)
 
 // Memory access of a wave's tile: buffer instructions, whose hardware bound drops what lies beyond the tensor's end -- or
@@ -139,14 +141,14 @@ __device__ __forceinline__ uint32_t lds_add1(uint32_t *p) {
 }
 
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(res_waves(STATE_BF16) * 64, res_waves(STATE_BF16) / 4) void eco_step_resident_kernel(const StepArgs a) {
+__global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_resident_kernel(const StepArgs a) {
   constexpr bool ADAM = algo_is_adam(ALGO), MASTER = algo_is_master(ALGO);
   constexpr bool KEEP_D = ALGO == ALGO_ADAM;                       // the injection of the other variants does not use d
   // fp32 v~ is stored at once; a bf16 one, rounded, could not stand in for the exact value in a tile that is finished from
   // memory, so it waits with the rest
   constexpr bool KEEP_V = ADAM && STATE_BF16;
-  constexpr int D = res_depth(STATE_BF16), WAVES = res_waves(STATE_BF16);
-  constexpr uint64_t SLAB = res_slab(STATE_BF16);
+  constexpr int D = RES_DEPTH, WAVES = RES_WAVES;
+  constexpr uint64_t SLAB = RES_SLAB;
   __shared__ float4 d_ring[KEEP_D ? D * WAVES * 128 : 1];          // [slot][wave][half of the 8 values][lane]
   __shared__ uint32_t part_max[RES_RING], part_count[RES_RING], event_max[4], event_count[4];
   if (threadIdx.x < RES_RING) { part_max[threadIdx.x] = 0; part_count[threadIdx.x] = 0; }
@@ -350,8 +352,8 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_tail_ker
 // through with them does that alone: until then the old scales are needed.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
 __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_kernel(const StepArgs a) {
-  constexpr uint32_t WAVES = res_waves(STATE_BF16), NW = RES_FINISH_THREADS / 64;
-  constexpr uint64_t SLAB = res_slab(STATE_BF16);
+  constexpr uint32_t WAVES = RES_WAVES, NW = RES_FINISH_THREADS / 64;
+  constexpr uint64_t SLAB = RES_SLAB;
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t marked = __builtin_amdgcn_readfirstlane(a.resident_counts[0]);
   const auto slabs_of = [&](const TensorDesc &td) { return td.numel <= SLAB ? 1u : (uint32_t)((td.numel + SLAB - 1) / SLAB); };
@@ -395,7 +397,7 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_k
 
 template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
 hipError_t launch_resident(const StepLaunch &sl, hipStream_t stream) {
-  const unsigned block = res_waves(STATE_BF16) * 64;
+  const unsigned block = RES_WAVES * 64;
   const uint64_t fit = sl.max_launch_threads / block;
   const unsigned most = fit < 1 ? 1 : fit > 65536 ? 65536 : static_cast<unsigned>(fit);
   unsigned wgs = sl.resident_wgs < sl.args.num_slabs ? sl.resident_wgs : sl.args.num_slabs;
