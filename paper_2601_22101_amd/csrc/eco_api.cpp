@@ -275,7 +275,10 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   const int waves = default_waves(kv, hbm);
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
-  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(waves, 512);
+  // a launch of one-wave units beside few tiles or none has no cap: their guarded accesses want all the waves there are (60 M
+  // elements in rows of 264, us, with the cap / without: FP8 Adam 494 / 236, SGDM 310 / 163; in rows of 160 294 / 224, 183 / 133)
+  const bool units = (kv.fmt == eco::FMT_FP8 || kv.fmt == eco::FMT_INT4) && a->num_extra > a->num_tiles / 8;
+  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? 0 : lds_for_waves(waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
     // (workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too: 4 M elements 9.7 against 10.2 us)
     const bool worth = kv.state_bf16 ? hbm.fully || nw == 4 || nw == 8 : hbm.half;
@@ -394,6 +397,7 @@ eco::TensorDesc describe(const eco_tensor_t &t, const eco_hparams_t *layout, con
   const bool plain = p.kind == eco::UNIT_PLAIN_BF16 || p.kind == eco::UNIT_PLAIN_FP32;
   d.group_size = plain ? layout->block_size : p.group;
   if (p.kind == eco::UNIT_TILES && p.list < eco::LIST_TW_TILES) d.bs_shift = static_cast<uint16_t>(eco::log2_exact(p.group));
+  if (p.kind == eco::UNIT_ROW) d.bs_shift = 9;                   // reduced over the whole wave
   d.kind = static_cast<uint16_t>(p.tail ? eco::UNIT_TAIL : p.kind);
   d.slot = p.rows;
   d.first_unit = static_cast<uint32_t>(first_unit);

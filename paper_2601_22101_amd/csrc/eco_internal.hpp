@@ -39,9 +39,10 @@ constexpr uint64_t MAX_WIDE_GROUP = 8192;
 enum : int {
   UNIT_TILES = 0,       // block-scaled: unit u is tile u
   UNIT_TAIL = 1,        // block-scaled, full tiles elsewhere: the one unit is the partial last tile
-  UNIT_ROWS = 2,        // groups of 8..504 elements, no power of two >= 32: unit u is the groups u * slot .. u * slot + slot - 1
+  UNIT_ROWS = 2,        // groups of 8..256 elements, no power of two >= 32: unit u is the groups u * slot .. u * slot + slot - 1
   UNIT_PLAIN_BF16 = 3,  // unquantized: unit u is tile u
   UNIT_PLAIN_FP32 = 4,
+  UNIT_ROW = 6,         // groups of 264..512 elements of that kind: unit u is group u
   UNIT_WIDE = 5         // groups of 520..8192 elements: a workgroup's unit, see wide_geometry
 };
 
@@ -271,8 +272,8 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
     p.group = group_size < numel ? group_size : numel;
     if (p.group <= static_cast<uint64_t>(TILE_ELEMS)) {
       p.list = LIST_EXTRA;
-      p.kind = UNIT_ROWS;
       p.rows = rows_per_wave(p.group);
+      p.kind = p.rows > 1 ? UNIT_ROWS : UNIT_ROW;
       p.entries = (numel + p.group - 1) / p.group;
       p.units = (p.entries + p.rows - 1) / p.rows;
     } else {

@@ -83,10 +83,17 @@ __global__ __launch_bounds__(WG_THREADS) void eco_quantize_kernel(const void *sr
                                                                      e0 >> bs_shift, (int)bs_shift, writer);
 }
 
-// Groups of up to 512 elements that are no power of two: `rows` whole groups to a wave.
-template <int FMT, bool SCALE_BF16, bool SRC_BF16>
+// Groups of up to 512 elements that are no power of two: `rows` whole groups to a wave; ONE: one of more than 256 elements,
+// reduced over the whole wave (13 M bf16 elements in rows of 264: 17.1 us with the segmented reduction).
+template <int FMT, bool SCALE_BF16, bool SRC_BF16, bool ONE>
 __global__ __launch_bounds__(WG_THREADS) void eco_quantize_rows_kernel(const void *src, uint64_t numel, uint32_t group_size, uint32_t rows,
                                                                        void *weights, void *scales) {
+  if (ONE) {
+    const uint64_t e0 = (uint64_t)blockIdx.x * group_size + (uint64_t)threadIdx.x * ELEMS_PER_LANE, end = (uint64_t)(blockIdx.x + 1) * group_size;
+    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_BLOCK>(src, weights, scales, e0, valid_from(e0, end < numel ? end : numel), blockIdx.x, 9,
+                                                                  threadIdx.x == 0);
+    return;
+  }
   const uint32_t gl = group_size >> 3, row = (threadIdx.x * (65536u / gl + 1u)) >> 16;    // lane / lanes of a group, exact below 64
   const uint64_t grp = (uint64_t)blockIdx.x * rows, e0 = grp * group_size + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
   const uint64_t end = (grp + rows) * group_size;
@@ -206,8 +213,11 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
                        (uint32_t)log2_exact(group_size), weights, scales);
   } else if (cls == GROUP_WIDE) {
     const Placement p = place_tensor(numel, group_size, cls, true, FMT);
-    if (p.kind == UNIT_ROWS)
-      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR>), dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel,
+    if (p.kind == UNIT_ROW)
+      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR, true>), dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel,
+                         (uint32_t)p.group, p.rows, weights, scales);
+    else if (p.kind == UNIT_ROWS)
+      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR, false>), dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel,
                          (uint32_t)p.group, p.rows, weights, scales);
     else
       ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR>), dim3((unsigned)p.units), dim3(64 * (p.list - LIST_WIDE1 + 1)), 0, stream,

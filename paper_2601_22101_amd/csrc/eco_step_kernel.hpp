@@ -620,7 +620,7 @@ __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDe
   }
   if (td.kind == UNIT_ROWS) {
     // td.slot groups to the wave, one after the other; the lanes beyond them have nothing
-    const uint32_t gl = (uint32_t)td.group_size >> 3;                      // lanes of a group: 1..63
+    const uint32_t gl = (uint32_t)td.group_size >> 3;                      // lanes of a group: 1..32
     const uint32_t row = (lane * (65536u / gl + 1u)) >> 16;                // lane / gl, exact for lane < 64
     const uint64_t grp = (uint64_t)unit * td.slot;
     const uint64_t e0 = grp * td.group_size + (uint64_t)lane * ELEMS_PER_LANE;
@@ -629,10 +629,14 @@ __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDe
         a, td, e0, valid_from(e0, end < td.numel ? end : td.numel), grp + row, lane == row * gl, nullptr, (int)(row * gl));
     return;
   }
-  const uint64_t tile = td.kind == UNIT_TAIL ? td.numel / TILE_ELEMS : unit;
-  const uint64_t e0 = tile * TILE_ELEMS + (uint64_t)lane * ELEMS_PER_LANE;
+  // a tile, or one group that is reduced like a tile of 512 (bs_shift 9): the segmented reduction above takes six exchanges
+  // across lanes, and a wave with one group spends more on them than on its 264 to 504 elements
+  const bool row = td.kind == UNIT_ROW;
+  const uint64_t start = row ? (uint64_t)unit * td.group_size : (td.kind == UNIT_TAIL ? td.numel / TILE_ELEMS : unit) * TILE_ELEMS;
+  const uint64_t end = row && start + td.group_size < td.numel ? start + td.group_size : td.numel;
+  const uint64_t e0 = start + (uint64_t)lane * ELEMS_PER_LANE;
   const bool writer = (lane & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
-  step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_BLOCK>(a, td, e0, valid_from(e0, td.numel), e0 >> td.bs_shift,
+  step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_BLOCK>(a, td, e0, valid_from(e0, end), row ? unit : e0 >> td.bs_shift,
                                                                            writer, nullptr);
 }
 

@@ -73,6 +73,10 @@ static const Case cases[] = {
     {"rows of 1800, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{20, ROW, 1024, 1800}}, 1, 0},
     {"rows of 768, master, 4 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{5, ROW, 1024, 768}}, 1, 0},
     {"rows of 768, master, 8 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{10, ROW, 1024, 768}}, 1, 1},
+    /* short rows: a launch of one-wave units alone has no cap, a few beside full tiles ride under theirs */
+    {"rows of 400, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{40, ROW, 1024, 400}}, 1, 0},
+    {"rows of 160, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{60, ROW, 1024, 160}}, 1, 0},
+    {"a few rows of 400 beside blocks", FP8, F32, ADAM, ECO_MODE_ECO, {{60, 128, 1024, 1024}, {4, ROW, 1024, 400}}, 1, 1},
     /* tensor-wise: two launches in one pass (three with a tail), four in two passes, and which of these are capped */
     {"three small tensors", FP8, F32, ADAM, ECO_MODE_ECO, {{3, TENSOR, 1, 40000}}, 2, 0},
     {"three small tensors with tails", FP8, F32, ADAM, ECO_MODE_ECO, {{3, TENSOR, 1, 40001}}, 4, 5},

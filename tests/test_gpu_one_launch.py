@@ -123,6 +123,34 @@ def test_tensor_wise_quantizer_folds_not_a_number_as_the_groups_in_a_wave_do(num
             assert float(one[0]) == float(many[at // 32]) == want, (at, bad, width)
 
 
+@pytest.mark.parametrize("group", [8, 48, 248, 256, 264, 400, 504, 512])
+@pytest.mark.parametrize("fmt,scale_bf16,src_bf16", [(0, False, False), (1, True, True)])
+def test_quantizer_of_rows_of_up_to_a_wave(group, fmt, scale_bf16, src_bf16):
+    """One group to a wave from 264 elements on, several below; the last one ragged, the only one ragged."""
+    import numpy as np
+
+    from paper_2601_22101_amd import binding as eco
+    o32 = oracle.get("f32")
+    gen = torch.Generator(device=DEV).manual_seed(group)
+    for numel in (group * 37, group * 37 + 8, group * 3 + group // 2 + 3, group - 3):
+        if eco_group_is_whole(group, numel):
+            continue
+        x = torch.randn(numel, generator=gen, device=DEV) * torch.logspace(-3, 0, numel, device=DEV)
+        src = x.to(torch.bfloat16) if src_bf16 else x
+        n_scales = -(-numel // group)
+        codes = torch.zeros(numel if fmt == 0 else (numel + 1) // 2, dtype=torch.uint8, device=DEV)
+        scales = torch.full((n_scales + 8,), 7.0, dtype=torch.bfloat16 if scale_bf16 else torch.float32, device=DEV)
+        eco.eco_quantize_init(src, int(src_bf16), numel, fmt, group, int(scale_bf16), codes, scales)
+        rc, rs = o32.quantize_rtn(oracle.FMT_E4M3 if fmt == 0 else oracle.FMT_INT4, src.float().cpu().numpy(), group, scale_bf16=scale_bf16)
+        assert np.array_equal(codes.cpu().numpy(), rc), numel
+        assert np.array_equal(scales.float().cpu().numpy()[:n_scales], rs.astype(np.float32)) and bool((scales[n_scales:] == 7).all()), numel
+
+
+def eco_group_is_whole(group, numel):
+    """A tensor shorter than its group, of a length that is no multiple of 8, has one scale and no groups."""
+    return numel < group and numel % 8 != 0
+
+
 @pytest.mark.parametrize("group", [9, 13, 100, 768, 1000, 1500, 3 * 4096])
 @pytest.mark.parametrize("fmt", [0, 1])
 def test_dequantizer_finds_the_group_of_every_element(fmt, group):
