@@ -237,6 +237,15 @@ inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = 
   }
   return w;
 }
+// Whether the initial quantizer takes the bundle too.  It moves a third of the step's bytes and is the sooner bound by the
+// longer workgroup's waves coming and going together: four rows or more to a workgroup pay where a row alone leaves at least an
+// eighth of its lanes idle, with INT4 codes a fifth (100 M elements, us, one row / the bundle: FP8 rows of 1152 126 / 121, 1664
+// 121 / 118, 1408 117 / 123, 1920 117 / 123; INT4 from bf16 1152 103 / 98, 1664 94 / 96, 1408 87 / 96, 1920 84 / 88), two rows always
+// (2816 127 / 120 and 102 / 92).
+inline bool quantizer_takes_bundle(uint32_t rows, uint64_t g, int fmt) {
+  const uint64_t lanes = (g + TILE_ELEMS - 1) / TILE_ELEMS * TILE_ELEMS;
+  return rows == 2 || (rows > 2 && (lanes - g) * (fmt == FMT_INT4 ? 5 : 8) >= lanes);
+}
 // Groups of up to 512 elements that are no power of two in [32, 512] (rows of 48, 96, 384, ...): as many whole groups to
 // a wave as its 512 elements hold, instead of one.
 inline uint32_t rows_per_wave(uint64_t g) { return static_cast<uint32_t>(TILE_ELEMS / g); }

@@ -101,14 +101,15 @@ __global__ __launch_bounds__(WG_THREADS) void eco_quantize_rows_kernel(const voi
                                                                grp + row, (int)(row * gl), threadIdx.x == row * gl, (int)gl);
 }
 
-// Wide groups: one to a workgroup, or as many as fill a whole number of waves (see wide_geometry).
-template <int FMT, bool SCALE_BF16, bool SRC_BF16>
+// Wide groups: one to a workgroup, or (BUNDLE) as many as fill a whole number of waves (see quantizer_takes_bundle; two
+// kernels, because the other form's code alone cost rows of 6912 up to 4 %).
+template <int FMT, bool SCALE_BF16, bool SRC_BF16, bool BUNDLE>
 __global__ __launch_bounds__(1024) void eco_quantize_wide_kernel(const void *src, uint64_t numel, uint32_t group_size, uint32_t rows,
                                                                  void *weights, void *scales) {
-  const uint64_t grp = (uint64_t)blockIdx.x * rows, start = grp * group_size;
+  const uint64_t grp = (uint64_t)blockIdx.x * (BUNDLE ? rows : 1), start = grp * group_size;
   const uint32_t lane_elem = threadIdx.x * ELEMS_PER_LANE;
   const uint64_t e0 = start + lane_elem;
-  if (rows > 1) {
+  if (BUNDLE) {
     uint32_t row = 0;
     for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * group_size ? 1u : 0u;
     quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_FULL, RED_WG_ROWS>(src, weights, scales, e0, 8, grp + row, (int)row,
@@ -219,9 +220,12 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
     else if (p.kind == UNIT_ROWS)
       ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR, false>), dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel,
                          (uint32_t)p.group, p.rows, weights, scales);
-    else
-      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR>), dim3((unsigned)p.units), dim3(64 * (p.list - LIST_WIDE1 + 1)), 0, stream,
+    else if (quantizer_takes_bundle(p.rows, p.group, FMT))
+      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, true>), dim3((unsigned)p.units), dim3(64 * (p.list - LIST_WIDE1 + 1)), 0, stream,
                          src, numel, (uint32_t)p.group, p.rows, weights, scales);
+    else
+      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, false>), dim3((unsigned)((numel + p.group - 1) / p.group)),
+                         dim3((unsigned)((p.group + TILE_ELEMS - 1) / TILE_ELEMS) * 64), 0, stream, src, numel, (uint32_t)p.group, 1u, weights, scales);
   } else {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);

@@ -113,6 +113,14 @@ int main() {
   }
   CHECK(array_bytes(1000, FMT_FP8, {true, false, false}) == 11000 && array_bytes(1000, FMT_INT4, {true, true, false}) == 6500);
   CHECK(array_bytes(1000, FMT_FP8, {false, false, true}) == 11000 && array_bytes(1000, FMT_BF16_PLAIN, {true, true, true}) == 8000);
+  // rows that the quantizer bundles, and rows that it leaves alone though the step bundles them
+  for (uint64_t g : {576ull, 640ull, 768ull, 1152ull, 1280ull, 1792ull, 2304ull, 2816ull, 3840ull}) {
+    const WideGeometry w = wide_geometry(64 * g, g);
+    CHECK(w.rows > 1 && quantizer_takes_bundle(w.rows, g, FMT_FP8) && quantizer_takes_bundle(w.rows, g, FMT_INT4));
+  }
+  for (uint64_t g : {1408ull, 1920ull}) CHECK(!quantizer_takes_bundle(4, g, FMT_FP8) && !quantizer_takes_bundle(4, g, FMT_INT4));
+  CHECK(quantizer_takes_bundle(4, 1664, FMT_FP8) && !quantizer_takes_bundle(4, 1664, FMT_INT4) && !quantizer_takes_bundle(4, 896, FMT_INT4));
+  for (uint64_t g = 520; g <= MAX_WIDE_GROUP; g += 8) CHECK(!quantizer_takes_bundle(1, g, FMT_FP8) && !quantizer_takes_bundle(1, g, FMT_INT4));
   std::printf("geometry ok\n");
   return 0;
 }

@@ -123,16 +123,17 @@ def test_tensor_wise_quantizer_folds_not_a_number_as_the_groups_in_a_wave_do(num
             assert float(one[0]) == float(many[at // 32]) == want, (at, bad, width)
 
 
-@pytest.mark.parametrize("group", [8, 48, 248, 256, 264, 400, 504, 512])
+@pytest.mark.parametrize("group", [8, 48, 248, 256, 264, 400, 504, 512, 520, 576, 768, 896, 1024, 1152, 1408, 1664, 1920, 2304, 6912, 8192])
 @pytest.mark.parametrize("fmt,scale_bf16,src_bf16", [(0, False, False), (1, True, True)])
-def test_quantizer_of_rows_of_up_to_a_wave(group, fmt, scale_bf16, src_bf16):
-    """One group to a wave from 264 elements on, several below; the last one ragged, the only one ragged."""
+def test_quantizer_of_rows(group, fmt, scale_bf16, src_bf16):
+    """One group to a wave from 264 elements on, several below; one to a workgroup from 520 on, or several that fill a whole
+    number of waves; numbers of rows that are and are not whole bundles, the last one ragged, the only one ragged."""
     import numpy as np
 
     from paper_2601_22101_amd import binding as eco
     o32 = oracle.get("f32")
     gen = torch.Generator(device=DEV).manual_seed(group)
-    for numel in (group * 37, group * 37 + 8, group * 3 + group // 2 + 3, group - 3):
+    for numel in (group * 40, group * 37, group * 37 + 8, group * 3 + group // 2 + 3, group - 3):
         if eco_group_is_whole(group, numel):
             continue
         x = torch.randn(numel, generator=gen, device=DEV) * torch.logspace(-3, 0, numel, device=DEV)
