@@ -247,7 +247,7 @@ inline bool quantizer_takes_bundle(uint32_t rows, uint64_t g, int fmt) {
   return rows == 2 || (rows > 2 && (lanes - g) * (fmt == FMT_INT4 ? 5 : 8) >= lanes);
 }
 // Groups of up to 512 elements that are no power of two in [32, 512] (rows of 48, 96, 384, ...): as many whole groups to
-// a wave as its 512 elements hold, instead of one.
+// a wave as its 512 elements hold (one from 264 on).
 inline uint32_t rows_per_wave(uint64_t g) { return static_cast<uint32_t>(TILE_ELEMS / g); }
 
 // What a step does with one tensor: the launch list it enters, the kind of its units there and how many they are.

@@ -298,7 +298,7 @@ __device__ __forceinline__ void step_sizes8(const StepArgs &a, const float (&x)[
 //   RED_TILE   first pass of the step for a group larger than a workgroup (tensor-wise scaling): wave all-reduce, the wave's
 //              maximum goes to its tile's entry of a scratch array, which a small kernel folds into the
 //              tensor's slot (tens of thousands of atomics on one address serialize in the memory system)
-//   RED_ROWS   groups of any length up to 512, several to a wave: segmented all-reduce over the group's lanes
+//   RED_ROWS   groups of up to 256 elements of any length, several to a wave: segmented all-reduce over the group's lanes
 //   RED_SLOT   second pass: the abs-max is read from that slot; everything is recomputed and written
 //              except the scale (a last, tiny kernel writes it once every tile has used the old one)
 enum : int { RED_BLOCK = 0, RED_WG = 1, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS = 5, RED_ROWS = 6 };
