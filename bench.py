@@ -529,7 +529,7 @@ def main() -> int:
                    "optimizer": args.variant,
                    "static_bytes_per_param": round(static_bytes_per_param(wl, args.variant), 4),
                    "launches_per_step": {"block": 1 if args.config != 2 else 2, "row": "one per row length",
-                                         "tensor": "two passes, a reduction and a scale kernel"}[args.granularity]},
+                                         "tensor": "one pass and a finishing kernel; for tensors that the chip does not hold two passes, a reduction and a scale kernel"}[args.granularity]},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic, "traffic_source": traffic_source,
