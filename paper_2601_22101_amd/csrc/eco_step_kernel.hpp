@@ -37,7 +37,7 @@ template <> struct FmtTraits<FMT_INT4> { static constexpr float RHO = 7.0f; };
 //   ACC_GUARDED only the first `nvalid` (possibly <= 0) exist: element-wise access in every lane; missing
 //               elements read as zero and are not written (the ragged tail of a tensor)
 //   ACC_LANE    decided per lane: vector access where nvalid == 8, element-wise elsewhere (wide groups,
-//               whose last lanes may lie beyond the group)
+//               whose last lanes may lie beyond the group); the step kernels load as WavePieces says
 //   ACC_WHOLE   all 8 of a lane exist or none (lengths that are multiples of 8): vector access where they do
 enum : int { ACC_FULL = 0, ACC_GUARDED = 1, ACC_LANE = 2, ACC_WHOLE = 3 };
 
@@ -158,14 +158,65 @@ __device__ __forceinline__ void store_codes8(void *base, uint64_t e0, int nvalid
   }
 }
 
-// x_j = value for the elements of a lane that do not exist.
+// x_j = value for the elements of a lane that do not exist.  (ACC_LANE: seldom anything to do, so a wave-uniform branch.)
 template <int ACC>
 __device__ __forceinline__ void fill_missing(float (&x)[8], int nvalid, float value) {
-  if (ACC != ACC_FULL) {
+  if (ACC == ACC_FULL || (ACC == ACC_LANE && !wave_any(nvalid < 8))) return;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (ACC == ACC_WHOLE ? nvalid == 0 : j >= nvalid) x[j] = value;
+  for (int j = 0; j < 8; ++j)
+    if (ACC == ACC_WHOLE ? nvalid == 0 : j >= nvalid) x[j] = value;
+}
+
+// Eight elements of a lane as they come from memory: one 16-byte vector of bf16, or two of fp32.
+template <bool BF16>
+__device__ __forceinline__ void load_raw8(const void *base, uint64_t e, eco_u32x4_t (&q)[2]) {
+  const eco_u32x4_t *p = reinterpret_cast<const eco_u32x4_t *>(static_cast<const char *>(base) + e * (BF16 ? 2 : 4));
+  q[0] = p[0];
+  if (!BF16) q[1] = p[1];
+}
+template <bool BF16>
+__device__ __forceinline__ void load_ragged8(const void *base, uint64_t e, int nvalid, eco_u32x4_t (&q)[2]) {
+  q[0] = q[1] = eco_u32x4_t{0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 7; ++j) {
+    if (j >= nvalid) continue;
+    if (BF16) q[0][j >> 1] |= (uint32_t)static_cast<const uint16_t *>(base)[e + j] << (16 * (j & 1));
+    else q[j >> 2][j & 3] = static_cast<const uint32_t *>(base)[e + j];
   }
+}
+template <bool BF16>
+__device__ __forceinline__ void unpack8(const eco_u32x4_t (&q)[2], float (&x)[8]) {
+  if (BF16) {
+    x[0] = bf16_lo(q[0].x); x[1] = bf16_hi(q[0].x); x[2] = bf16_lo(q[0].y); x[3] = bf16_hi(q[0].y);
+    x[4] = bf16_lo(q[0].z); x[5] = bf16_hi(q[0].z); x[6] = bf16_lo(q[0].w); x[7] = bf16_hi(q[0].w);
+  } else {
+    x[0] = u2f(q[0].x); x[1] = u2f(q[0].y); x[2] = u2f(q[0].z); x[3] = u2f(q[0].w);
+    x[4] = u2f(q[1].x); x[5] = u2f(q[1].y); x[6] = u2f(q[1].z); x[7] = u2f(q[1].w);
+  }
+}
+
+// What a wave whose last lanes may lie beyond the end reads (ACC_LANE; its lanes' pieces of 8 elements are consecutive).  A
+// load inside a branch of its own is waited for there, one array after the other, which is what bounded such waves.  So all
+// loads of all lanes are vectors and issued together: a lane beyond the end reads the wave's last whole piece once more (no
+// traffic, and nothing that a maximum would notice), and writes nothing.  Only the one lane whose piece is cut off reads
+// element by element, over what it has been given, in a branch that waves without one skip.  Measured (us, five loads waited for in
+// turn / this): Adam, fp32 state, 44 tensors of 1001 rows of 2304 538 / 403, 30 750 rows of 1152 in INT4 180 / 133.
+struct WavePieces {
+  bool any_whole, any_cut;       // wave-uniform
+  int last;                      // the lane with the last whole piece
+  uint64_t from;                 // where the lane reads its vectors
+  int fill;                      // how many of the lane's 8 elements stand for something
+};
+__device__ __forceinline__ WavePieces wave_pieces(uint64_t e0, int nvalid) {
+  const int lane = (int)(threadIdx.x & 63);
+  const uint64_t whole = __builtin_amdgcn_ballot_w64(nvalid == 8);
+  WavePieces p;
+  p.any_whole = whole != 0;
+  p.any_cut = wave_any((nvalid & 7) != 0);
+  p.last = 63 - __builtin_clzll(whole | 1);
+  p.from = e0 - (uint64_t)(lane > p.last ? lane - p.last : 0) * ELEMS_PER_LANE;
+  p.fill = p.any_cut || !p.any_whole ? nvalid : 8;
+  return p;
 }
 
 template <int FMT, int J>
@@ -466,13 +517,14 @@ __device__ __forceinline__ void inject_lane8(const StepArgs &a, float s_new, con
 
 // Both, with the stores: codes, the injected momentum (or master weights); returns the new scale.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC>
-__device__ __forceinline__ float quantize_inject_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid, float amax,
-                                                      const Philox4 &r, const float (&th)[8], const float (&d)[8], float (&m)[8]) {
+__device__ __forceinline__ float quantize_inject_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid, int fill,
+                                                      float amax, const Philox4 &r, const float (&th)[8], const float (&d)[8],
+                                                      float (&m)[8]) {
   constexpr bool MASTER = algo_is_master(ALGO);
   if (MASTER) store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, th);
   uint32_t cn[2];
   float qn[8];
-  const float s_new = quantize_lane8<FMT, SCALE_BF16, ROUND, ACC>(amax, r, nvalid, th, cn, qn);
+  const float s_new = quantize_lane8<FMT, SCALE_BF16, ROUND, ACC>(amax, r, fill, th, cn, qn);
   store_codes8<FMT, ACC>(td.w, e0, nvalid, cn);
   if (!MASTER) {
     float eo[8];
@@ -502,15 +554,59 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   const bool any = ACC == ACC_FULL || nvalid > 0;
 
   float g[8], m[8], v[8], w[8], x[8], d[8], th[8], sc = 1.0f;
-  load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
-  load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
-  if (ADAM) load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
-  if (MASTER) {
-    load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, w);
+  int fill = nvalid;
+  uint32_t c[2] = {0, 0};
+  float s_old = 0.0f;
+  if (ACC == ACC_LANE) {
+    const WavePieces wp = wave_pieces(e0, nvalid);
+    fill = wp.fill;
+    eco_u32x4_t gq[2] = {}, mq[2] = {}, vq[2] = {}, wq[2] = {};
+    if (wp.any_whole) {
+      load_raw8<true>(td.g, wp.from, gq);
+      load_raw8<STATE_BF16>(td.m, wp.from, mq);
+      if (ADAM) load_raw8<STATE_BF16>(td.v, wp.from, vq);
+      if (MASTER) {
+        load_raw8<false>(td.aux, wp.from, wq);
+      } else {
+        load_codes8<FMT, ACC_FULL>(td.w, wp.from, 8, c);
+        uint64_t sl = sg;
+        if (RED == RED_BLOCK || RED == RED_ROWS || RED == RED_WG_ROWS) {
+          const uint64_t of_last = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sg, wp.last) |
+                                   (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(sg >> 32), wp.last) << 32;
+          sl = any ? sg : of_last;
+        }
+        s_old = load_scale<SCALE_BF16>(td.s, sl);
+      }
+    }
+    if (wp.any_cut) {
+      if (nvalid & 7) {
+        load_ragged8<true>(td.g, e0, nvalid, gq);
+        load_ragged8<STATE_BF16>(td.m, e0, nvalid, mq);
+        if (ADAM) load_ragged8<STATE_BF16>(td.v, e0, nvalid, vq);
+        if (MASTER) {
+          load_ragged8<false>(td.aux, e0, nvalid, wq);
+        } else {
+          load_codes8<FMT, ACC_GUARDED>(td.w, e0, nvalid, c);
+          s_old = load_scale<SCALE_BF16>(td.s, sg);
+        }
+      }
+    }
+    unpack8<true>(gq, g);
+    unpack8<STATE_BF16>(mq, m);
+    if (ADAM) unpack8<STATE_BF16>(vq, v);
+    if (MASTER) unpack8<false>(wq, w);
   } else {
-    uint32_t c[2];
-    load_codes8<FMT, ACC>(td.w, e0, nvalid, c);
-    const float s_old = any ? load_scale<SCALE_BF16>(td.s, sg) : 0.0f;
+    load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
+    load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+    if (ADAM) load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
+    if (MASTER) {
+      load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, w);
+    } else {
+      load_codes8<FMT, ACC>(td.w, e0, nvalid, c);
+      s_old = any ? load_scale<SCALE_BF16>(td.s, sg) : 0.0f;
+    }
+  }
+  if (!MASTER) {
     sc = decode8<FMT>(c, s_old, w);
     if (!exact_scale<SCALE_BF16, ALGO>()) {
 #pragma unroll
@@ -522,13 +618,13 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
 
   moments_lane<ALGO, LATE>(a, g, m, v, x);
   if (ADAM && WRITE && !LATE) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);   // v is final (Alg. 3 returns it unchanged)
-  theta_lane<SCALE_BF16, ALGO, ACC>(a, x, w, sc, m, nvalid, d, th);
+  theta_lane<SCALE_BF16, ALGO, ACC>(a, x, w, sc, m, fill, d, th);
 
   const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
                                        RED == RED_ROWS ? (int)(td.group_size >> 3) : 0);
   if (!WRITE) return;
   const Philox4 r = random_lane<ROUND>(a, td, e0);
-  const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC>(a, td, e0, nvalid, amax, r, th, d, m);
+  const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC>(a, td, e0, nvalid, fill, amax, r, th, d, m);
   if (RED != RED_SLOT && scale_writer && any) store_scale<SCALE_BF16>(td, sg, s_new);
 }
 
@@ -579,18 +675,43 @@ __device__ __forceinline__ int valid_from(uint64_t e0, uint64_t end) {
 template <bool W_BF16, bool STATE_BF16, bool ADAM, int ACC>
 __device__ __forceinline__ void plain_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid) {
   float w[8], g[8], m[8], v[8], eta[8];
-  load_state8<W_BF16, ACC>(td.w, e0, nvalid, w);
-  load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
-  load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+  int fill = nvalid;
+  if (ACC == ACC_LANE) {
+    const WavePieces wp = wave_pieces(e0, nvalid);
+    fill = wp.fill;
+    eco_u32x4_t wq[2] = {}, gq[2] = {}, mq[2] = {}, vq[2] = {};
+    if (wp.any_whole) {
+      load_raw8<W_BF16>(td.w, wp.from, wq);
+      load_raw8<true>(td.g, wp.from, gq);
+      load_raw8<STATE_BF16>(td.m, wp.from, mq);
+      if (ADAM) load_raw8<STATE_BF16>(td.v, wp.from, vq);
+    }
+    if (wp.any_cut) {
+      if (nvalid & 7) {
+        load_ragged8<W_BF16>(td.w, e0, nvalid, wq);
+        load_ragged8<true>(td.g, e0, nvalid, gq);
+        load_ragged8<STATE_BF16>(td.m, e0, nvalid, mq);
+        if (ADAM) load_ragged8<STATE_BF16>(td.v, e0, nvalid, vq);
+      }
+    }
+    unpack8<W_BF16>(wq, w);
+    unpack8<true>(gq, g);
+    unpack8<STATE_BF16>(mq, m);
+    if (ADAM) unpack8<STATE_BF16>(vq, v);
+  } else {
+    load_state8<W_BF16, ACC>(td.w, e0, nvalid, w);
+    load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
+    load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+    if (ADAM) load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
+  }
   if (ADAM) {
     float x[8], d[8];
-    load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       v[j] = fmaf(a.b2, v[j], a.omb2 * (g[j] * g[j]));
       x[j] = v[j] * a.rbc2;
     }
-    fill_missing<ACC>(x, nvalid, 1.0f);
+    fill_missing<ACC>(x, fill, 1.0f);
     step_sizes8(a, x, d, eta);
   }
 #pragma unroll
@@ -689,15 +810,19 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const StepArgs a) {
   const uint64_t start = grp * td.group_size;
   const uint32_t lane_elem = threadIdx.x * ELEMS_PER_LANE;
   const uint64_t e0 = start + lane_elem;
+  const uint64_t end = start + rows * td.group_size < td.numel ? start + rows * td.group_size : td.numel;
   if (rows > 1) {
     const uint32_t gs = (uint32_t)td.group_size;
     uint32_t row = 0;
     for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * gs ? 1u : 0u;
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG_ROWS>(a, td, e0, 8, grp + row, lane_elem == row * gs, nullptr,
-                                                                               (int)row);
+    if (ALGO == ALGO_ADAM_MASTER || end - start == (uint64_t)blockDim.x * ELEMS_PER_LANE)      // master weights: see step_geometry
+      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG_ROWS>(a, td, e0, 8, grp + row, lane_elem == row * gs, nullptr,
+                                                                                 (int)row);
+    else
+      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG_ROWS>(a, td, e0, valid_from(e0, end), grp + row,
+                                                                                 lane_elem == row * gs, nullptr, (int)row);
     return;
   }
-  const uint64_t end = start + td.group_size < td.numel ? start + td.group_size : td.numel;
   // a group that fills every lane of the workgroup (e.g. rows of 1024, 2048, 4096) needs no per-lane guards
   if (end - start == (uint64_t)blockDim.x * ELEMS_PER_LANE)
     step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG>(a, td, e0, 8, grp, threadIdx.x == 0, nullptr);

@@ -111,17 +111,6 @@ __device__ __forceinline__ void load_raw(const TensorDesc &td, uint64_t tile, ui
   }
 }
 
-template <bool BF16>
-__device__ __forceinline__ void unpack8(const eco_u32x4_t (&q)[2], float (&x)[8]) {
-  if (BF16) {
-    x[0] = bf16_lo(q[0].x); x[1] = bf16_hi(q[0].x); x[2] = bf16_lo(q[0].y); x[3] = bf16_hi(q[0].y);
-    x[4] = bf16_lo(q[0].z); x[5] = bf16_hi(q[0].z); x[6] = bf16_lo(q[0].w); x[7] = bf16_hi(q[0].w);
-  } else {
-    x[0] = u2f(q[0].x); x[1] = u2f(q[0].y); x[2] = u2f(q[0].z); x[3] = u2f(q[0].w);
-    x[4] = u2f(q[1].x); x[5] = u2f(q[1].y); x[6] = u2f(q[1].z); x[7] = u2f(q[1].w);
-  }
-}
-
 // LDS words shared by the waves of a workgroup.  The hardware executes a compute unit's LDS operations of one wave in
 // order; the empty asm statements keep the compiler to it.
 __device__ __forceinline__ uint32_t lds_read(const uint32_t *p) {

@@ -57,6 +57,42 @@ def test_units_that_share_a_launch(which, fmt, bf16, over):
     dw.close()
 
 
+def grouped(numel, group, fmt):
+    """A tensor of any length in scale groups of any length: the last one may be cut off, within a lane's 8 elements too."""
+    t = T(f"g{group}_{numel}", (numel,), fmt, grad_std=1e-3 * (1 + numel % 3), granularity="row")
+    t.group_size = lambda block_size: group
+    return t
+
+
+@pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("fp8", True, dict(mode=3, weight_decay=0.1)), ("int4", True, {}),
+                                           ("int4", False, dict(opt=1, round=1, lr=0.05)), ("fp8", False, dict(opt=1, mode=2, lr=0.05)),
+                                           ("fp8", False, dict(eps=0.0))])
+@pytest.mark.parametrize("few", [False, True])
+def test_rows_that_leave_lanes_idle(few, fmt, bf16, over):
+    """Rows of which several share a workgroup and rows that have one to themselves, their last waves part idle: numbers of rows
+    that fill the last workgroup and that do not, a last row that is cut off behind a whole piece of 8 elements and within one.
+    few: in the short-list kernel."""
+    from paper_2601_22101_amd import harness
+    o32 = oracle.get("f32")
+    specs = [grouped(n, g, fmt) for g in ((640, 1000, 1152) if few else (520, 576, 664, 720, 800, 896, 1000, 1152, 1280, 1408, 1800, 2304, 2816, 8000))
+             for n in (g, 2 * g, 4 * g, 7 * g, 3 * g + 8, 2 * g + 5, 5 * g - 3)]
+    wl = workloads.Workload("idle_lanes", specs, steps=2, state_bf16=bf16, scale_bf16=bf16)
+    dw = harness.DeviceWorkload(wl, DEV, layout=over)
+    host = [host_copy(tv) for tv in dw.tensors]
+    for k in (1, 2):
+        dw.fill_gradients(k)
+        hp = dw.hparams(k)
+        for tv, h in zip(dw.tensors, host):
+            h["grad"] = bf16_bits(tv.grad)
+        dw.plan.step(hp)
+        torch.cuda.synchronize()
+        for tv, h in zip(dw.tensors, host):
+            oracle_step(o32, h, tv.spec.numel, step_config(hp, tv.tensor_id, tv.fmt, group_size=dw.group_size(tv)))
+            st = compare(host_copy(tv), h, f"step {k} {tv.spec.name}", bf16)
+            assert not any(v for key, v in st.items() if key.endswith("mismatch")), (tv.spec.name, st)
+    dw.close()
+
+
 @pytest.mark.parametrize("opt", [0, 1])
 @pytest.mark.parametrize("noalloc", [False, True])
 def test_identity_weights_step_alike_alone_and_beside_quantized_tensors(opt, noalloc):
