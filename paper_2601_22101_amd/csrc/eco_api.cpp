@@ -122,7 +122,8 @@ struct Lists {                           // the launch lists of one storage form
   size_t off_tile = 0, off_extra = 0, off_wide[eco::MAX_WIDE_WAVES + 1] = {0}, off_tw_tile = 0, off_tw_tensor = 0, off_slots = 0,
          off_tile_max = 0, off_slab = 0, off_resident = 0, off_tail_max = 0, off_slab_max = 0, off_counts = 0, off_deferred = 0;
   uint64_t tensors = 0, most_tw_tiles = 0, tails = 0;
-  uint32_t idle[eco::MAX_WIDE_WAVES + 1] = {0};          // units of the wide lists that leave lanes idle
+  struct WideLoad { uint64_t idle, elements; };          // of a wide list: units that leave lanes idle; elements
+  WideLoad load[eco::MAX_WIDE_WAVES + 1] = {};
   std::unique_ptr<eco::SmallArgs> small; // all but the tensor-wise tensors as one launch, where that is the better way
   unsigned small_wgs = 0, small_waves = 1;
   std::vector<uint32_t> &list(int l) {
@@ -147,6 +148,15 @@ struct HbmBound {
   bool half, fully;
   explicit HbmBound(uint64_t bytes) : half(bytes >= 96000000), fully(bytes >= 384000000) {}
 };
+
+// Bytes of all arrays of a list.  From HbmBound::half on the step groups rows in its own way (see step_geometry); in shorter
+// steps the exact bundles, which leave most rows in few launches, are the better way (3.5 M elements in rows of 1024 and of 768, SGDM
+// with a stored error: 6.0 us in one launch, 6.8 in two).
+uint64_t bytes_of(const eco_tensor_t *tensors, size_t n, const eco::StateLayout &l) {
+  uint64_t sum = 0;
+  for (size_t i = 0; i < n; ++i) sum += eco::array_bytes(tensors[i].numel, tensors[i].fmt, l);
+  return sum;
+}
 
 int num_compute_units() {
   int dev = 0, cus = 0;
@@ -257,9 +267,9 @@ eco::KernelVariant variant_for(const eco_hparams_t *hp, int f) {
   return kv;
 }
 
-// The scalar part of the kernel arguments: step constants, random-stream key, launch options.  idle: see wide_workgroups.
-typedef uint32_t IdleUnits[eco::MAX_WIDE_WAVES + 1];
-void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const IdleUnits &idle, uint64_t bytes,
+// The scalar part of the kernel arguments: step constants, random-stream key, launch options.
+typedef Lists::WideLoad WideLoads[eco::MAX_WIDE_WAVES + 1];
+void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const WideLoads &load, uint64_t bytes,
                        eco::StepLaunch *sl) {
   eco::StepArgs *a = &sl->args;
   a->b1 = c.b1; a->omb1 = c.omb1; a->b2 = c.b2; a->omb2 = c.omb2; a->rbc2 = c.rbc2; a->c1 = c.c1; a->eps = c.eps;
@@ -280,16 +290,20 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   const bool units = (kv.fmt == eco::FMT_FP8 || kv.fmt == eco::FMT_INT4) && a->num_extra > a->num_tiles / 8;
   sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? 0 : lds_for_waves(waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
-    // (workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too: 4 M elements 9.7 against 10.2 us)
-    const bool worth = kv.state_bf16 ? hbm.fully || nw == 4 || nw == 8 : hbm.half;
-    const unsigned k = worth ? eco::wide_workgroups(kv, nw, sl->num_wide[nw], idle[nw]) : 0;
-    // Adam with fp32 state keeps the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
-    // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 1000: 472 against 630, of 2048: 467
+    const uint64_t units = sl->num_wide[nw];
+    const bool idle = load[nw].idle > units / 8, adam32 = kv.algo == eco::ALGO_ADAM && !kv.state_bf16;
+    // Workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too (4 M elements 9.7 against 10.2 us); master weights
+    // with fp32 state in full rows, and Adam with fp32 state in rows with idle lanes, from 96 MB on (us, with / without: rows of 1000 88 MB
+    // 28.8 / 29.5, 33 MB 12.1 / 10.7; 1800 28.4 / 29.2, 12.1 / 11.4); the others from 384 MB on (master weights, rows of 1152, 300 MB 89 / 87; SGDM,
+    // rows of 1000, 315 MB 91 / 89).
+    const bool worth = hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && (idle ? adam32 : kv.algo == eco::ALGO_ADAM_MASTER));
+    const unsigned k = !units || !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, units, load[nw].elements)
+                                                   : eco::wide_workgroups(kv, nw, units, load[nw].idle);
+    // Adam with fp32 state in full rows has the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
+    // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 2048: 467
     // against 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
     const uint32_t per_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves, 256);
-    sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (kv.algo == eco::ALGO_ADAM && !kv.state_bf16)
-                                 ? std::min(per_wave * nw, 65536u)
-                                 : eco::lds_for_workgroups(k);
+    sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (adam32 && !idle) ? std::min(per_wave * nw, 65536u) : eco::lds_for_workgroups(k);
   }
   sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv, hbm), 256);
 }
@@ -568,6 +582,8 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     std::vector<eco::Placement> place(n);
     const eco::StateLayout state = state_layout(layout);
     uint64_t tensors_of[4] = {0}, entries_of[4] = {0}, list_entries[4][eco::LIST_COUNT] = {{0}};
+    plan->bytes = bytes_of(tensors, n, state);
+    const eco::StateLayout *const grouping = HbmBound(plan->bytes).half ? &state : nullptr;
     for (size_t i = 0; i < n && st == ECO_OK; ++i) {
       const eco_tensor_t &t = tensors[i];
       uint64_t gsz = 0;
@@ -575,10 +591,9 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       st = check_tensor(t, i, layout, &gsz, &cls);
       if (st != ECO_OK) break;
       const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
-      place[i] = eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt);
+      place[i] = eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt, eco::TILE_ELEMS, 0, grouping);
       tensors_of[t.fmt] += 1;
       entries_of[t.fmt] += place[i].entries;
-      plan->bytes += eco::array_bytes(t.numel, t.fmt, state);
       uint64_t &in_list = list_entries[t.fmt][place[i].list];
       in_list += place[i].entries;
       if (in_list > 0x7FFFFFF0ull) st = fail(ECO_EUNSUPPORTED, "plan: more than 2^31 tiles in one launch");
@@ -633,7 +648,11 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
         g.resident.push_back(idx);
       } else {
         elements[f] += t.numel;
-        if (p.idle) g.idle[p.list - eco::LIST_WIDE1 + 1] += static_cast<uint32_t>(p.units);
+        if (p.kind == eco::UNIT_WIDE) {
+          Lists::WideLoad &w = g.load[p.list - eco::LIST_WIDE1 + 1];
+          w.idle += p.idle ? p.units : 0;
+          w.elements += t.numel;
+        }
         if (items[f].size() <= static_cast<size_t>(eco::SMALL_TENSORS)) items[f].push_back(SmallItem{&t, p});
       }
       list.insert(list.end(), static_cast<size_t>(p.units), idx);
@@ -697,10 +716,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
 }
 
 // Launches the step of one format's lists (sl: everything but the scalars).
-static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, const IdleUnits &idle, uint64_t bytes,
+static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, const WideLoads &load, uint64_t bytes,
                                   eco::StepLaunch *sl, eco::SmallArgs *small, hipStream_t stream) {
   const eco::KernelVariant kv = variant_for(hp, f);
-  fill_step_scalars(hp, c, kv, idle, bytes, sl);
+  fill_step_scalars(hp, c, kv, load, bytes, sl);
   sl->extra_in = home_of_extra(sl->args.num_tiles, sl->args.num_extra, sl->num_wide);
   sl->max_tile_threads = tile_threads(sl->max_launch_threads, cus);
   // the limit on a launch's threads holds for the one launch of the short-list kernel too (without tables it is the only way)
@@ -768,7 +787,7 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     sl.resident_wgs = static_cast<unsigned>(plan->cus);
     eco::SmallArgs small;                  // a copy: steps of one plan may be enqueued by different calls
     if (g.small) { small = *g.small; sl.small_wgs = g.small_wgs; sl.small_waves = g.small_waves; }
-    st = launch_format(hp, c, f, plan->cus, g.idle, plan->bytes, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
+    st = launch_format(hp, c, f, plan->cus, g.load, plan->bytes, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
     if (st != ECO_OK) return st;
   }
   plan->unfinished = false;
@@ -802,16 +821,21 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   // pass 1: validate, place, count the entries of every launch list
   constexpr int L_TW_TENSORS = eco::LIST_COUNT, L_COUNT = eco::LIST_COUNT + 1;
   uint64_t count[4][L_COUNT] = {{0}}, tensors_of[4] = {0}, entries_of[4] = {0}, most_tw_tiles[4] = {0};
-  uint64_t total = 0, elements = 0, bytes = 0;
+  uint64_t total = 0, elements = 0;
   const eco::StateLayout state = state_layout(hp);
-  IdleUnits idle[4] = {{0}};
-  // the placement of a tensor that check_tensor has let through
+  const uint64_t bytes = bytes_of(tensors, n, state);
+  WideLoads load[4] = {};
+  // The placement of a tensor that check_tensor has let through; where the static tables do not hold the units of the step's own
+  // grouping of rows, with the one that their limit is stated in.
+  const eco::StateLayout *grouping = HbmBound(bytes).half ? &state : nullptr;
   const auto place = [&](const eco_tensor_t &t) {
     const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
     const uint64_t gsz = t.group_size ? t.group_size : hp->block_size;
-    return eco::place_tensor(t.numel, gsz, quantized ? eco::classify_group(gsz, t.numel) : eco::GROUP_BLOCK, quantized, t.fmt);
+    return eco::place_tensor(t.numel, gsz, quantized ? eco::classify_group(gsz, t.numel) : eco::GROUP_BLOCK, quantized, t.fmt, eco::TILE_ELEMS, 0,
+                             grouping);
   };
   bool tensorwise = false;
+  uint64_t units = 0;
   for (size_t i = 0; i < n; ++i) {
     const int f = tensors[i].fmt;
     uint64_t gsz = 0;
@@ -823,18 +847,37 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     tensors_of[f] += 1;
     entries_of[f] += p.entries;
     elements += tensors[i].numel;
-    bytes += eco::array_bytes(tensors[i].numel, f, state);
     total += p.entries;
     if (total > MAX_UNITS)
       return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: more than %u launch-table entries (512-element tiles, or scale "
                   "groups wider than 512): the static scratch does not hold them (use a plan)", MAX_UNITS);
     count[f][p.list] += p.units;
-    if (p.idle) idle[f][p.list - eco::LIST_WIDE1 + 1] += static_cast<uint32_t>(p.units);
-    if (p.tail) count[f][eco::LIST_EXTRA] += 1;
+    units += p.units;
+    if (p.kind == eco::UNIT_WIDE) {
+      Lists::WideLoad &w = load[f][p.list - eco::LIST_WIDE1 + 1];
+      w.idle += p.idle ? p.units : 0;
+      w.elements += tensors[i].numel;
+    }
+    if (p.tail) { count[f][eco::LIST_EXTRA] += 1; units += 1; }
     if (p.list == eco::LIST_TW_TILES) {
       tensorwise = true;
       count[f][L_TW_TENSORS] += 1;
+      units += 1;
       most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
+    }
+  }
+  if (units > MAX_UNITS) {               // the wide lists again, as the limit counts them
+    grouping = nullptr;
+    std::memset(load, 0, sizeof load);
+    for (int f = 0; f < 4; ++f)
+      for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) count[f][eco::LIST_WIDE1 + nw - 1] = 0;
+    for (size_t i = 0; i < n; ++i) {
+      const eco::Placement p = place(tensors[i]);
+      if (p.kind != eco::UNIT_WIDE) continue;
+      Lists::WideLoad &w = load[tensors[i].fmt][p.list - eco::LIST_WIDE1 + 1];
+      count[tensors[i].fmt][p.list] += p.units;
+      w.idle += p.idle ? p.units : 0;
+      w.elements += tensors[i].numel;
     }
   }
   const int plain_home = home_of_plain(tensors_of, entries_of);
@@ -877,7 +920,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     if (fits) {
       for (int f = 0; f < 2; ++f) {
         if (!sl[f].small_wgs) continue;
-        st = launch_format(hp, c, f, cus, idle[f], bytes, &sl[f], &small[f], hs);
+        st = launch_format(hp, c, f, cus, load[f], bytes, &sl[f], &small[f], hs);
         if (st != ECO_OK) return st;
       }
       return ECO_OK;
@@ -954,7 +997,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     a.num_tw_tiles = static_cast<uint32_t>(count[f][eco::LIST_TW_TILES]);
     a.num_tw_tensors = static_cast<uint32_t>(count[f][L_TW_TENSORS]);
     a.tw_reduce_wgs = eco::tw_reduce_workgroups(most_tw_tiles[f]);
-    st = launch_format(hp, c, f, cus, idle[f], bytes, &sl, nullptr, hs);
+    st = launch_format(hp, c, f, cus, load[f], bytes, &sl, nullptr, hs);
     if (st != ECO_OK) return st;
   }
   return ECO_OK;

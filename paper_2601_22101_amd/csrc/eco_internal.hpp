@@ -217,10 +217,10 @@ inline FlatLaunch flat_launch(uint64_t numel, unsigned threads) {
   return {(numel + share - 1) / share, MAX_LAUNCH_THREADS / threads};
 }
 // Wide groups (a multiple of 8 up to 8192 elements, not a power of two in [32, 512]): one workgroup of `waves` waves
-// steps `rows` consecutive groups.  One group a workgroup in general; groups of more than 512 elements whose length is
+// takes `rows` consecutive groups.  One group a workgroup in general; groups of more than 512 elements whose length is
 // not a multiple of 512 leave lanes of their last wave idle, so where 2..8 of them together fill a whole number of
 // waves exactly (1408 = 2.75 waves: four rows in 11 waves; 576: eight rows in 9 waves) and the tensor is a whole number
-// of such bundles, a workgroup takes the bundle.
+// of such bundles, a workgroup takes the bundle.  This is the initial quantizer's grouping; the step has one of its own.
 struct WideGeometry { uint32_t rows; uint32_t waves; uint64_t units; };
 inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = min(group size, numel)
   const uint64_t ngroups = (numel + g - 1) / g;
@@ -236,6 +236,31 @@ inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = 
     }
   }
   return w;
+}
+// How the step groups them.  Its waves tolerate idle lanes (see WavePieces), and what a large workgroup costs is more: its waves
+// wait for the slowest, and come and go together.  So few waves, most of their lanes busy.  Measured over 150 M elements, each
+// with the best number of resident waves, us: one row / this / the bundle that fills its waves exactly --
+//   fp32 state, Adam: 576 543 / 510 / 513 (3 rows in 4 waves), 640 561 / 510 / 515, 896 544 / 519 (4 in 7), 1152 513 / 512 / 516 (2
+//   in 5), 1408 507 (one) / 548, 2304 513 (one) / 517, 2816 512 (one) / 555; SGDM: 576 327 / 305 / 308, 1152 305 / 302 / 307, 1408 303
+//   (one) / 311; SGDM with master weights 1152 509 / 490 / 522.
+//   bf16 state, Adam, INT4: 576 389 / 307 / 312, 640 357 / 295 / 294, 896 303 / 293.  Without a cap on resident waves, which rows with
+//   idle lanes of this kind do not have, the exact bundle otherwise: 1408 315 / 313 (FP8 344 / 322), 2304 310 / 303, 2816 315 / 307;
+//   longer ones lose (1664 304 / 330 in 13 waves).
+//   Adam with master weights, without such a cap: the exact bundle (576 790 / 764, 640 785 / 740, 1152 752 / 762, 2304 767 / 770).
+// Where it is all but as good and of up to 9 waves the exact bundle stays: row lengths that share a number of waves share a launch
+// (510 M elements in rows of 576 and of 2304, all in 9 waves 1833 us, in 4 and in 5 1843).
+inline WideGeometry step_geometry(uint64_t numel, uint64_t g, const StateLayout &l) {        // g = min(group size, numel)
+  const uint64_t ngroups = (numel + g - 1) / g;
+  const WideGeometry exact = wide_geometry(numel, g);
+  const bool pair = !l.state_bf16 && g > 2 * TILE_ELEMS && 2 * g <= 5 * TILE_ELEMS;
+  if ((l.aux && l.adam) || (exact.rows > 1 && !pair && exact.waves <= (l.state_bf16 ? 11 : 9))) return exact;
+  uint64_t k = 1;
+  if (g <= TILE_ELEMS) k = 1;
+  else if (3 * g <= 4 * TILE_ELEMS) k = 3;
+  else if (pair || 2 * g <= 3 * TILE_ELEMS) k = 2;
+  else if (4 * g <= 7 * TILE_ELEMS) k = 4;
+  if (k > ngroups) k = ngroups;
+  return {static_cast<uint32_t>(k), static_cast<uint32_t>((k * g + TILE_ELEMS - 1) / TILE_ELEMS), (ngroups + k - 1) / k};
 }
 // Whether the initial quantizer takes the bundle too.  It moves a third of the step's bytes and is the sooner bound by the
 // longer workgroup's waves coming and going together: four rows or more to a workgroup pay where a row alone leaves at least an
@@ -263,8 +288,9 @@ struct Placement {
   uint64_t entries;      // what the tensor counts towards the limits on launch tables: a unit per tile or per group
 };
 // slab, max_slabs: the one-pass tensor-wise kernel's slab length and the most slabs of a tensor it may take (0: none).
+// step: group rows as the step does (null: as the initial quantizer does).
 inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool quantized, int fmt, uint64_t slab = TILE_ELEMS,
-                              uint64_t max_slabs = 0) {
+                              uint64_t max_slabs = 0, const StateLayout *step = nullptr) {
   Placement p = {LIST_TILE, UNIT_TILES, 0, false, group_size, 1, false, 0};
   if (cls == GROUP_BLOCK) {
     const bool rest = numel % TILE_ELEMS != 0;
@@ -286,12 +312,14 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
       p.entries = (numel + p.group - 1) / p.group;
       p.units = (p.entries + p.rows - 1) / p.rows;
     } else {
-      const WideGeometry w = wide_geometry(numel, p.group);
+      WideGeometry w = wide_geometry(numel, p.group);
+      p.entries = w.units;
+      if (step) w = step_geometry(numel, p.group, *step);
       p.list = LIST_WIDE1 + static_cast<int>(w.waves) - 1;
       p.kind = UNIT_WIDE;
       p.rows = w.rows;
-      p.units = p.entries = w.units;
-      p.idle = w.rows == 1 && p.group % TILE_ELEMS != 0;
+      p.units = w.units;
+      p.idle = w.rows * p.group % TILE_ELEMS != 0;
     }
   } else {
     p.group = numel;
@@ -307,23 +335,42 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
   }
   return p;
 }
-// Workgroups of `nw` waves of the wide-group kernel to have resident per compute unit (0: as many as fit).  HBM delivers
-// most with a certain amount of traffic in flight, so where the lanes are busy a cap is worth 3 to 11 %; where a row
-// leaves lanes of its last wave idle, their guarded accesses need all the waves there are and a cap costs up to 47 %.
-// Measured over 150 M elements, us, capped / not --
-//   Adam, bf16 state, at least 20 waves: FP8 rows of 768 309 / 337, 1024 314 / 329, 2048 323 / 337, 4096 311 / 323 (INT4 286 /
-//   309, 294 / 305, 293 / 304, 290 / 303).  Workgroups of 5 to 7 and of 9 to 16 waves gain nothing or lose: 640 314 / 309,
-//   3072 316 / 314, 896 319 / 312, 2304 328 / 318, 1408 323 / 319, 8192 336 / 336.  Idle lanes: 1000 411 / 327, 1800 446 / 332,
-//   3000 381 / 374.
-//   Master weights, fp32 state, two or up to 10 waves: 768 701 / 789, 1024 766 / 803, 2048 724 / 793, 640 724 / 780, 4096 757 / 771,
-//   2304 761 / 782.  Idle lanes: 1800 1016 / 820, 1000 807 / 823 (4 M elements 23.1 / 18.4).
-// Adam with fp32 state has a cap of its own; the other variants ran best without one.  units, idle: the launch's units, and those
-// of them that leave lanes idle.
+// Workgroups of `nw` waves of the wide-group kernel to have resident per compute unit (0: as many as fit), for arrays that
+// come from HBM (see HbmBound).  HBM delivers most with a certain amount of traffic in flight; more waves only add latency.
+// So the smallest number of workgroups with at least that many waves' worth of busy lanes --
+// (a) where the lanes are busy, us, 150 M elements, with / without:
+//   Adam, fp32 state: 12 waves, as the full-tile kernel (fill_step_scalars).
+//   Adam, bf16 state, 20: FP8 rows of 768 309 / 337, 1024 314 / 329, 2048 323 / 337, 4096 311 / 323 (INT4 286 / 309, 294 / 305, 293 /
+//   304, 290 / 303).  Workgroups of 5 to 7 and of 9 to 16 waves gain nothing or lose: 640 314 / 309, 3072 316 / 314, 8192 336 / 336.
+//   Master weights, fp32 state, two or up to 10 waves: 768 701 / 789, 1024 766 / 803, 2048 724 / 793, 640 724 / 780, 4096 757 / 771.
+//   Master weights, bf16 state, 12: 1024 478 / 519, 2048 505 / 546, 3072 505 / 533.
+//   SGDM, fp32 state, 14.5: 768 304 / 328, 1024 310 / 319, 2048 299 / 332, 3072 301 / 332, 3584 302 / 338, 4096 314 / 332, 6144 305 /
+//   314; with a stored error, 11.5: 768 510 / 551, 1024 511 / 525, 2048 501 / 527, 4096 531 / 537; with master weights, 8.5: 768 489 /
+//   529, 1024 507 / 521, 2048 511 / 541, 4096 515 / 532.
 inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, uint64_t units, uint64_t idle) {
   if (idle > units / 8) return 0;
-  if (kv.algo == ALGO_ADAM && kv.state_bf16) return nw <= 4 || nw == 8 ? (20 + nw - 1) / nw : 0;
-  if (kv.algo == ALGO_ADAM_MASTER && !kv.state_bf16) return nw <= 5 ? 10 / nw : 2;
-  return 0;
+  const auto at_least = [nw](unsigned tenths) { const unsigned k = (tenths + 10 * nw - 1) / (10 * nw); return k < 2 ? 2 : k; };
+  if (kv.algo == ALGO_ADAM) return kv.state_bf16 && (nw <= 4 || nw == 8) ? at_least(200) : 0;
+  if (kv.algo == ALGO_ADAM_MASTER) return kv.state_bf16 ? at_least(115) : nw <= 5 ? 10 / nw : 2;
+  if (kv.state_bf16) return 0;
+  return at_least(kv.algo == ALGO_SGDM ? 145 : kv.algo == ALGO_SGDM_EXACT ? 115 : 85);
+}
+// (b) where rows leave lanes idle, `elements` in the launch's `units` workgroups:
+//   Adam, fp32 state, 13.6: 520 523 / 590, 640 510 / 577, 1000 522 / 629, 1152 512 / 520, 1408 510 / 575, 1800 515 / 608, 2304 513 /
+//   527, 2816 512 / 545, 3000 519 / 596, 3328 521 / 557, 4000 511 / 612 (INT4 1000 510 / 586, 1800 485 / 566, 3000 490 / 567).
+//   Master weights, bf16 state, 11.5: 1000 529 / 641, 1408 494 / 541, 1800 531 / 600, 2816 494 / 529.
+//   SGDM, fp32 state, 22: 640 302 / 338, 1000 308 / 345, 1152 302 / 305, 1408 306 / 321, 1800 308 / 318, 4000 310 / 346; with a stored error,
+//   16.5: 640 531 / 545, 1000 523 / 589, 1152 529 / 547, 1408 540 / 568, 1800 521 / 570, 3000 546 / 571; with master weights, 9.7: 640 486 /
+//   538, 1000 514 / 631, 1152 490 / 534, 1408 496 / 525, 1800 506 / 607, 2304 494 / 538, 3000 527 / 609.
+inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t units, uint64_t elements) {
+  const auto at_least = [=](uint64_t tenths) {
+    const uint64_t k = (tenths * units * TILE_ELEMS + 10 * elements - 1) / (10 * elements);
+    return static_cast<unsigned>(k < 2 ? 2 : k);
+  };
+  if (kv.state_bf16) return kv.algo == ALGO_ADAM_MASTER ? at_least(115) : 0;
+  if (kv.algo == ALGO_ADAM) return at_least(136);
+  if (kv.algo == ALGO_ADAM_MASTER) return 0;
+  return at_least(kv.algo == ALGO_SGDM ? 220 : kv.algo == ALGO_SGDM_EXACT ? 165 : 97);
 }
 // The dynamic LDS that keeps k workgroups resident per compute unit (0: no request); LDS is handed out in pieces of 1280
 // bytes, and a workgroup has up to 128 of its own beside it.
