@@ -464,7 +464,7 @@ __device__ __forceinline__ void theta_lane(const StepArgs &a, float (&x)[8], flo
 
 // The random words of a lane's 8 elements, counter e0 / 8.
 template <int ROUND>
-__device__ __forceinline__ Philox4 random_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0) {
+__device__ __forceinline__ Philox4 random_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, uint32_t seed_lo, uint32_t seed_hi) {
   Philox4 r = {0, 0, 0, 0};
   if (ROUND == ROUND_SR) {
     const uint64_t q = e0 >> 3;
@@ -472,10 +472,10 @@ __device__ __forceinline__ Philox4 random_lane(const StepArgs &a, const TensorDe
     // that enter the first two rounds beside q are all wave-uniform and their products are scalar work (the
     // empty asm statement keeps the two calls apart: merged, the zero would become a per-lane select)
     if (td.numel <= (1ull << 35)) {
-      r = philox4x32_10((uint32_t)q, 0u, a.step_lo, td.tensor_id, a.seed_lo, a.seed_hi);
+      r = philox4x32_10((uint32_t)q, 0u, a.step_lo, td.tensor_id, seed_lo, seed_hi);
       asm volatile("" ::: "memory");
     } else {
-      r = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.step_lo, td.tensor_id, a.seed_lo, a.seed_hi);
+      r = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.step_lo, td.tensor_id, seed_lo, seed_hi);
     }
   }
   return r;
@@ -623,7 +623,7 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
                                        RED == RED_ROWS ? (int)(td.group_size >> 3) : 0);
   if (!WRITE) return;
-  const Philox4 r = random_lane<ROUND>(a, td, e0);
+  const Philox4 r = random_lane<ROUND>(a, td, e0, a.seed_lo, a.seed_hi);
   const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC>(a, td, e0, nvalid, fill, amax, r, th, d, m);
   if (RED != RED_SLOT && scale_writer && any) store_scale<SCALE_BF16>(td, sg, s_new);
 }

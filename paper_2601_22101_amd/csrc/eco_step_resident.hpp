@@ -243,7 +243,10 @@ __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_reside
       const TensorDesc td = load_tensor_desc(a, finish ? ti[o] : ti_next);
       const uint64_t out = tile_at(td, slab);
       Philox4 r = {0, 0, 0, 0};
-      if (finish) r = random_lane<ROUND>(a, td, out + lane * ELEMS_PER_LANE);
+      // (the key schedule is derived from the seed anew each time: kept across the loop it takes 20 scalar registers)
+      uint32_t seed_lo = a.seed_lo, seed_hi = a.seed_hi;
+      asm volatile("" : "+s"(seed_lo), "+s"(seed_hi));
+      if (finish) r = random_lane<ROUND>(a, td, out + lane * ELEMS_PER_LANE, seed_lo, seed_hi);
 
       // the workgroup's last wave at slab i publishes the slab's maximum
       const bool last = begin && arrived == (i / RES_RING + 1) * WAVES;            // in lane 0
