@@ -173,8 +173,17 @@ def eco_step_constants(hp: eco_hparams_t) -> eco_constants_t:
     return out
 
 
+def _tensor_array(tensors: Sequence[eco_tensor_t]):
+    """The descriptors as one C array.  ctypes takes 0.2 us for each element it is given, which bounded calls with long lists; where
+    all are descriptors (anything else is left to ctypes) their bytes are joined: 25 tensors 5.2 -> 1.6 us, 336 76 -> 14."""
+    array = eco_tensor_t * len(tensors)
+    if set(map(type, tensors)) == {eco_tensor_t}:
+        return array.from_buffer_copy(b"".join(tensors))
+    return array(*tensors)
+
+
 def eco_plan_create(tensors: Sequence[eco_tensor_t], layout: eco_hparams_t) -> int:
-    arr = (eco_tensor_t * len(tensors))(*tensors)
+    arr = _tensor_array(tensors)
     plan = C.c_void_p()
     _check(lib.eco_plan_create(arr, len(tensors), C.byref(layout), C.byref(plan)))
     return plan.value
@@ -189,12 +198,12 @@ def eco_step(plan: int, hp: eco_hparams_t, stream=None) -> None:
 
 
 def eco_step_tensors(tensors: Sequence[eco_tensor_t], hp: eco_hparams_t, stream=None) -> None:
-    arr = (eco_tensor_t * len(tensors))(*tensors)
+    arr = _tensor_array(tensors)
     _check(lib.eco_step_tensors(arr, len(tensors), C.byref(hp), _stream(stream)))
 
 
 def eco_step_tensors_noalloc(tensors: Sequence[eco_tensor_t], hp: eco_hparams_t, stream=None) -> None:
-    arr = (eco_tensor_t * len(tensors))(*tensors)
+    arr = _tensor_array(tensors)
     _check(lib.eco_step_tensors_noalloc(arr, len(tensors), C.byref(hp), _stream(stream)))
 
 

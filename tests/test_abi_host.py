@@ -388,3 +388,15 @@ def test_a_plain_c_client_compiles_links_and_runs(eco, tmp_path):
     assert [np.float32(float(x)) for x in vals[1:]] == [np.float32(x) for x in ref]
     assert lines["step0"].startswith(f"{eco.ECO_EINVAL} invalid argument |") and "1-based" in lines["step0"]
     assert lines["nullplan"] == str(eco.ECO_EINVAL) and lines["destroynull"] == "0"
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 45, 300])
+def test_descriptor_array_is_what_ctypes_would_build(eco, n):
+    """Lists of descriptors are joined as bytes; whatever else a caller passes goes to ctypes, which takes or refuses it as before."""
+    ts = [eco.make_tensor(16 * i, 32, 48, 64, 80, 100 + i, i, i % 4, aux=None, group_size=8 * i) for i in range(n)]
+    assert bytes(eco._tensor_array(ts)) == bytes((eco.eco_tensor_t * n)(*ts)) == bytes(eco._tensor_array(tuple(ts)))
+    as_tuples = [tuple(getattr(t, f) for f, _ in t._fields_) for t in ts]
+    assert bytes(eco._tensor_array(as_tuples)) == bytes(eco._tensor_array(ts))
+    for bad in (None, 7, "x", object()):
+        with pytest.raises(TypeError):
+            eco._tensor_array(ts + [bad])
