@@ -124,8 +124,9 @@ struct Lists {                           // the launch lists of one storage form
   uint64_t tensors = 0, most_tw_tiles = 0, tails = 0;
   struct WideLoad { uint64_t idle, elements; };          // of a wide list: units that leave lanes idle; elements
   WideLoad load[eco::MAX_WIDE_WAVES + 1] = {};
-  std::unique_ptr<eco::SmallArgs> small; // all but the tensor-wise tensors as one launch, where that is the better way
-  unsigned small_wgs = 0, small_waves = 1;
+  std::vector<uint32_t> one;             // all but the tensor-wise tensors as one launch, where that is the better way: workgroup -> tensor
+  size_t off_one = 0;
+  unsigned one_waves = 1;
   std::vector<uint32_t> &list(int l) {
     return l == eco::LIST_TILE ? tile : l == eco::LIST_EXTRA ? extra : l == eco::LIST_TW_TILES ? tw_tile : l == eco::LIST_RESIDENT ? slab : wide[l - eco::LIST_WIDE1 + 1];
   }
@@ -137,8 +138,7 @@ struct Lists {                           // the launch lists of one storage form
 constexpr uint64_t RIDE_ALONG_TILES = 8192;
 constexpr uint64_t RIDE_ALONG_WAVES = 65536;   // largest wide-group launch that takes them, see home_of_extra
 
-// A step of at most SMALL_TENSORS tensors and this many elements that would be several launches is one launch of the
-// short-list kernel instead.
+// A step of at most this many elements that would be several launches is one launch of the list kernel instead.
 constexpr uint64_t SMALL_ELEMENTS = 1ull << 23;
 
 // How much of a step's arrays comes from HBM and not from the 256 MB cache before it, by the bytes of the arrays, each
@@ -451,27 +451,31 @@ int home_of_plain(const uint64_t (&tensors)[4], const uint64_t (&entries)[4]) {
   return -1;
 }
 
-// The short-list arguments of one format's tensors; false if they do not fit one launch of it.
+// A tensor in a list launch (step_list_workgroup) of workgroups of nw waves: the waves of its units, and its workgroups.
+unsigned unit_waves(const eco::Placement &p) { return p.kind == eco::UNIT_WIDE ? static_cast<unsigned>(p.list - eco::LIST_WIDE1 + 1) : 1u; }
+uint64_t list_workgroups(const eco::Placement &p, unsigned nw) {
+  const uint64_t units = p.units + (p.tail ? 1 : 0), per_wg = nw / unit_waves(p);
+  return (units + per_wg - 1) / per_wg;
+}
+eco::TensorDesc describe_in_list(const eco_tensor_t &t, const eco_hparams_t *layout, eco::Placement p, uint64_t first_wg) {
+  p.tail = false;                                       // whole and partial tiles alike there
+  return describe(t, layout, p, first_wg);
+}
+
+// The short-list arguments of up to SMALL_TENSORS tensors.
 struct SmallItem { const eco_tensor_t *t; eco::Placement p; };
-bool make_small(const SmallItem *items, size_t n, const eco_hparams_t *layout, eco::SmallArgs *sa, unsigned *wgs, unsigned *waves) {
-  if (n == 0 || n > static_cast<size_t>(eco::SMALL_TENSORS)) return false;
+void make_small(const SmallItem *items, size_t n, const eco_hparams_t *layout, eco::SmallArgs *sa, uint64_t *wgs, unsigned *waves) {
   unsigned nw = 1;
-  for (size_t i = 0; i < n; ++i)
-    if (items[i].p.kind == eco::UNIT_WIDE) nw = std::max(nw, static_cast<unsigned>(items[i].p.list - eco::LIST_WIDE1 + 1));
+  for (size_t i = 0; i < n; ++i) nw = std::max(nw, unit_waves(items[i].p));
   uint64_t wg = 0;
   for (size_t i = 0; i < n; ++i) {
-    eco::Placement p = items[i].p;
-    const uint64_t units = p.units + (p.tail ? 1 : 0);
-    p.tail = false;                                     // whole and partial tiles in one list here
     sa->first_wg[i] = static_cast<uint32_t>(wg);
-    sa->desc[i] = describe(*items[i].t, layout, p, units);
-    const unsigned per_wg = p.kind == eco::UNIT_WIDE ? nw / static_cast<unsigned>(p.list - eco::LIST_WIDE1 + 1) : nw;
-    wg += (units + per_wg - 1) / per_wg;
+    sa->desc[i] = describe_in_list(*items[i].t, layout, items[i].p, wg);
+    wg += list_workgroups(items[i].p, nw);
   }
   sa->num = static_cast<uint32_t>(n);
-  *wgs = static_cast<unsigned>(wg);
+  *wgs = wg;
   *waves = nw;
-  return true;
 }
 
 // Which launch the one-wave units of a format ride in: the full-tile one (0) where there is one, they are many or every
@@ -583,7 +587,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     const eco::StateLayout state = state_layout(layout);
     uint64_t tensors_of[4] = {0}, entries_of[4] = {0}, list_entries[4][eco::LIST_COUNT] = {{0}};
     plan->bytes = bytes_of(tensors, n, state);
-    const eco::StateLayout *const grouping = HbmBound(plan->bytes).half ? &state : nullptr;
+    const eco::StepRows rows = {state, HbmBound(plan->bytes).half};
     for (size_t i = 0; i < n && st == ECO_OK; ++i) {
       const eco_tensor_t &t = tensors[i];
       uint64_t gsz = 0;
@@ -591,7 +595,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       st = check_tensor(t, i, layout, &gsz, &cls);
       if (st != ECO_OK) break;
       const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
-      place[i] = eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt, eco::TILE_ELEMS, 0, grouping);
+      place[i] = eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt, eco::TILE_ELEMS, 0, &rows);
       tensors_of[t.fmt] += 1;
       entries_of[t.fmt] += place[i].entries;
       uint64_t &in_list = list_entries[t.fmt][place[i].list];
@@ -624,14 +628,16 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     }
     const int plain_home = home_of_plain(tensors_of, entries_of);
 
-    std::vector<SmallItem> items[4];
     uint64_t elements[4] = {0};
+    const auto home = [&](size_t i) {
+      const int f = tensors[i].fmt;
+      return f == ECO_FMT_FP8_E4M3 || f == ECO_FMT_INT4 || plain_home < 0 ? f : plain_home;
+    };
     descs.reserve(n);
     for (size_t i = 0; i < n; ++i) {
       const eco_tensor_t &t = tensors[i];
       const eco::Placement &p = place[i];
-      const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
-      const int f = quantized || plain_home < 0 ? t.fmt : plain_home;
+      const int f = home(i);
       Lists &g = plan->lists[f];
       const uint32_t idx = static_cast<uint32_t>(i);
       std::vector<uint32_t> &list = g.list(p.list);
@@ -653,7 +659,6 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
           w.idle += p.idle ? p.units : 0;
           w.elements += t.numel;
         }
-        if (items[f].size() <= static_cast<size_t>(eco::SMALL_TENSORS)) items[f].push_back(SmallItem{&t, p});
       }
       list.insert(list.end(), static_cast<size_t>(p.units), idx);
       if (p.tail) g.extra.push_back(idx);
@@ -665,11 +670,18 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       int launches = g.tile.empty() ? 0 : 1;
       for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) launches += !g.wide[nw].empty();
       if (launches < 2 || elements[f] > SMALL_ELEMENTS) continue;
-      std::unique_ptr<eco::SmallArgs> sa(new eco::SmallArgs());
-      if (make_small(items[f].data(), items[f].size(), layout, sa.get(), &g.small_wgs, &g.small_waves)) g.small = std::move(sa);
+      const auto listed = [&](size_t i) { return home(i) == f && place[i].list != eco::LIST_TW_TILES && place[i].list != eco::LIST_RESIDENT; };
+      for (size_t i = 0; i < n; ++i)
+        if (listed(i)) g.one_waves = std::max(g.one_waves, unit_waves(place[i]));
+      for (size_t i = 0; i < n; ++i) {
+        if (!listed(i)) continue;
+        const uint32_t idx = static_cast<uint32_t>(descs.size());
+        descs.push_back(describe_in_list(tensors[i], layout, place[i], g.one.size()));
+        g.one.insert(g.one.end(), static_cast<size_t>(list_workgroups(place[i], g.one_waves)), idx);
+      }
     }
 
-    // one device buffer: per format [full tiles | one-wave units | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots |
+    // one device buffer: per format [full tiles | one-wave units | all of a list launch | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots |
     // tile maxima | slabs | their tensors | tail maxima | slab maxima | counts | deferred slabs]
     for (Lists &g : plan->lists) {
       const auto add = [&host](const std::vector<uint32_t> &l, size_t *off) {
@@ -679,6 +691,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       if (!g.tensors) continue;
       add(g.tile, &g.off_tile);
       add(g.extra, &g.off_extra);
+      add(g.one, &g.off_one);
       for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) add(g.wide[nw], &g.off_wide[nw]);
       add(g.tw_tile, &g.off_tw_tile);
       add(g.tw_tensor, &g.off_tw_tensor);
@@ -722,8 +735,8 @@ static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t
   fill_step_scalars(hp, c, kv, load, bytes, sl);
   sl->extra_in = home_of_extra(sl->args.num_tiles, sl->args.num_extra, sl->num_wide);
   sl->max_tile_threads = tile_threads(sl->max_launch_threads, cus);
-  // the limit on a launch's threads holds for the one launch of the short-list kernel too (without tables it is the only way)
-  if (small && (!sl->args.tensors || static_cast<uint64_t>(sl->small_wgs) * sl->small_waves * 64 <= sl->max_launch_threads)) {
+  if (small) {
+    sl->args.wg_waves = sl->list_waves;
     small->step = sl->args;
     sl->small = small;
   }
@@ -785,9 +798,10 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     a.num_slabs = static_cast<uint32_t>(g.slab.size());
     a.resident_tries = eco::RES_TRIES;
     sl.resident_wgs = static_cast<unsigned>(plan->cus);
-    eco::SmallArgs small;                  // a copy: steps of one plan may be enqueued by different calls
-    if (g.small) { small = *g.small; sl.small_wgs = g.small_wgs; sl.small_waves = g.small_waves; }
-    st = launch_format(hp, c, f, plan->cus, g.load, plan->bytes, &sl, g.small ? &small : nullptr, static_cast<hipStream_t>(stream));
+    a.list_tensor = plan->d_tables + g.off_one;
+    sl.list_wgs = g.one.size();
+    sl.list_waves = g.one_waves;
+    st = launch_format(hp, c, f, plan->cus, g.load, plan->bytes, &sl, nullptr, static_cast<hipStream_t>(stream));
     if (st != ECO_OK) return st;
   }
   plan->unfinished = false;
@@ -827,12 +841,12 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   WideLoads load[4] = {};
   // The placement of a tensor that check_tensor has let through; where the static tables do not hold the units of the step's own
   // grouping of rows, with the one that their limit is stated in.
-  const eco::StateLayout *grouping = HbmBound(bytes).half ? &state : nullptr;
+  eco::StepRows rows = {state, HbmBound(bytes).half};
   const auto place = [&](const eco_tensor_t &t) {
     const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
     const uint64_t gsz = t.group_size ? t.group_size : hp->block_size;
     return eco::place_tensor(t.numel, gsz, quantized ? eco::classify_group(gsz, t.numel) : eco::GROUP_BLOCK, quantized, t.fmt, eco::TILE_ELEMS, 0,
-                             grouping);
+                             &rows);
   };
   bool tensorwise = false;
   uint64_t units = 0;
@@ -867,7 +881,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     }
   }
   if (units > MAX_UNITS) {               // the wide lists again, as the limit counts them
-    grouping = nullptr;
+    rows.own_rows = false;
     std::memset(load, 0, sizeof load);
     for (int f = 0; f < 4; ++f)
       for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) count[f][eco::LIST_WIDE1 + nw - 1] = 0;
@@ -895,36 +909,33 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   derive_constants(hp, &c);
   const int cus = num_compute_units();
 
-  // a short list of small tensors needs no tables: its descriptors go as kernel arguments, one launch per quantized format
+  // lists of small tensors need no tables: their descriptors go as kernel arguments, SMALL_TENSORS to a launch (205 tensors, us: with
+  // tables, which take seven launches to write, 35.6; in five launches 23.6)
   if (!tensorwise && elements <= SMALL_ELEMENTS && (plain_home >= 0 || !(tensors_of[2] + tensors_of[3])) && tensors_of[0] + tensors_of[1]) {
-    eco::SmallArgs small[2];
-    eco::StepLaunch sl[2];
-    SmallItem items[2][eco::SMALL_TENSORS];             // no container: this call allocates nothing, on the host neither
-    size_t held[2] = {0, 0};
+    SmallItem items[eco::SMALL_TENSORS];                // no container: this call allocates nothing, on the host neither
+    eco::SmallArgs small;
+    eco::StepLaunch sl;
+    const int64_t limit = g_max_launch_threads.load(std::memory_order_relaxed);
+    // (a limit on a launch's threads holds here too: a first round without launching, if there is one)
     bool fits = true;
-    std::memset(sl, 0, sizeof sl);
-    for (size_t i = 0; i < n && fits; ++i) {
-      const int f = format_of(i);
-      fits = held[f] < static_cast<size_t>(eco::SMALL_TENSORS);
-      if (!fits) break;
-      SmallItem &it = items[f][held[f]++];
-      it.t = &tensors[i];
-      it.p = place(tensors[i]);
-    }
-    for (int f = 0; f < 2 && fits; ++f) {
-      if (!held[f]) continue;
-      fits = make_small(items[f], held[f], hp, &small[f], &sl[f].small_wgs, &sl[f].small_waves);
-      const int64_t limit = g_max_launch_threads.load(std::memory_order_relaxed);
-      if (limit > 0 && static_cast<uint64_t>(sl[f].small_wgs) * sl[f].small_waves * 64 > static_cast<uint64_t>(limit)) fits = false;
-    }
-    if (fits) {
+    for (int round = limit > 0 ? 0 : 1; round < 2 && fits; ++round)
       for (int f = 0; f < 2; ++f) {
-        if (!sl[f].small_wgs) continue;
-        st = launch_format(hp, c, f, cus, load[f], bytes, &sl[f], &small[f], hs);
-        if (st != ECO_OK) return st;
+        size_t held = 0;
+        for (size_t i = 0; i <= n && fits; ++i) {
+          if (i < n && format_of(i) == f) {
+            items[held].t = &tensors[i];
+            items[held++].p = place(tensors[i]);
+          }
+          if (!held || (held < static_cast<size_t>(eco::SMALL_TENSORS) && i < n)) continue;
+          std::memset(&sl, 0, sizeof sl);
+          make_small(items, held, hp, &small, &sl.list_wgs, &sl.list_waves);
+          held = 0;
+          if (round == 0) { fits = sl.list_wgs * sl.list_waves * 64 <= static_cast<uint64_t>(limit); continue; }
+          st = launch_format(hp, c, f, cus, load[f], bytes, &sl, &small, hs);
+          if (st != ECO_OK) return st;
+        }
       }
-      return ECO_OK;
-    }
+    if (fits) return ECO_OK;
   }
 
   uint32_t start[4][L_COUNT], tw_tile_start[4], tw_tensor_start[4];

@@ -124,6 +124,7 @@ struct StepArgs {            // by-value kernel argument: everything wave-unifor
   uint32_t *deferred;              //   ... scratch: which slabs are left to the finishing kernel (0 or 1 each)
   uint32_t *tail_max;              //   ... scratch: abs-max of the tensors' tails, by place in resident_tensor
   uint32_t *resident_counts;       //   ... scratch: whether there are any; workgroups through with them
+  uint32_t resident_wgs;           //   ... workgroups of the launch in flight
   uint32_t num_tiles, num_extra, num_tw_tiles, num_tw_tensors, num_slabs, num_resident, resident_tails, resident_tries;
   uint32_t tw_reduce_wgs;          // tensor-wise scaling: workgroups per tensor of the reduction
   float b1, omb1, b2, omb2, rbc2, c1, eps, kappa, lr, alpha, wd, inv_lr, inv_lr_beta;
@@ -131,16 +132,19 @@ struct StepArgs {            // by-value kernel argument: everything wave-unifor
   uint32_t div_mid;                // c1 and eps allow the short division (see div_rn_midrange) after a short square root
   uint32_t unit_base;              // first work item (group, tile, tensor) of the launch in flight, see launch_in_chunks
   uint32_t num_units;              // wide-group launch: work items before the extra ones
+  uint32_t wg_waves;               // waves of a workgroup of the launch in flight (a kernel that asks the runtime for its geometry is
+                                   // passed 256 bytes of arguments more, 0.7 to 1 us of a call)
+  const uint32_t *list_tensor;     // the list kernel: workgroup -> index into tensors
 };
 
-// A list of at most SMALL_TENSORS tensors, carried by value in the kernel arguments (4 KB): the step of a short list
-// needs no table in device memory and is one launch whatever classes of scale group it holds.
+// A list of at most SMALL_TENSORS tensors, carried by value in the kernel arguments (4 KB): the allocation-free step of a short
+// list needs no table in device memory and is one launch whatever classes of scale group it holds.
 constexpr int SMALL_TENSORS = 44;
 struct SmallArgs {
   StepArgs step;
   uint32_t num;                        // tensors
   uint32_t first_wg[SMALL_TENSORS];    // the first workgroup of each
-  TensorDesc desc[SMALL_TENSORS];      // first_unit: the number of the tensor's units here
+  TensorDesc desc[SMALL_TENSORS];
 };
 static_assert(sizeof(SmallArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
@@ -162,8 +166,9 @@ struct StepLaunch {
   uint32_t num_wide[MAX_WIDE_WAVES + 1];
   unsigned resident_wgs;           // workgroups of the one-pass tensor-wise kernel: one per compute unit
   int extra_in;                    // which launch the one-wave units ride in: 0 the full-tile one, n the wide groups of n waves
-  const SmallArgs *small;          // if set, one launch of the short-list kernel ...
-  unsigned small_wgs, small_waves; //   ... with this geometry stands for all of the above but the tensor-wise passes
+  const SmallArgs *small;          // if set, one launch of the short-list kernel,
+  uint64_t list_wgs;               // or if not 0, of the list kernel,
+  unsigned list_waves;             //   with workgroups of so many waves, stands for all of the above but the tensor-wise passes
 };
 
 struct KernelVariant {
@@ -288,9 +293,10 @@ struct Placement {
   uint64_t entries;      // what the tensor counts towards the limits on launch tables: a unit per tile or per group
 };
 // slab, max_slabs: the one-pass tensor-wise kernel's slab length and the most slabs of a tensor it may take (0: none).
-// step: group rows as the step does (null: as the initial quantizer does).
+// step: of a step (null: for the initial quantizer, which shares the grouping of rows); own_rows: with the step's own grouping.
+struct StepRows { StateLayout layout; bool own_rows; };
 inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool quantized, int fmt, uint64_t slab = TILE_ELEMS,
-                              uint64_t max_slabs = 0, const StateLayout *step = nullptr) {
+                              uint64_t max_slabs = 0, const StepRows *step = nullptr) {
   Placement p = {LIST_TILE, UNIT_TILES, 0, false, group_size, 1, false, 0};
   if (cls == GROUP_BLOCK) {
     const bool rest = numel % TILE_ELEMS != 0;
@@ -314,7 +320,7 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
     } else {
       WideGeometry w = wide_geometry(numel, p.group);
       p.entries = w.units;
-      if (step) w = step_geometry(numel, p.group, *step);
+      if (step && step->own_rows) w = step_geometry(numel, p.group, step->layout);
       p.list = LIST_WIDE1 + static_cast<int>(w.waves) - 1;
       p.kind = UNIT_WIDE;
       p.rows = w.rows;

@@ -57,7 +57,7 @@ __device__ __forceinline__ void quantize_lane(const void *src, void *weights, vo
                                               uint64_t sg, int arg, bool scale_writer, int lanes = 0, uint32_t *slot = nullptr) {
   float x[8];
   load_state8<SRC_BF16, ACC>(src, e0, nvalid, x);
-  const float amax = group_absmax<RED>(absmax8(x), arg, slot, lanes);
+  const float amax = group_absmax<RED>(absmax8(x), arg, slot, lanes);        // lanes: see there
   float s_new, inv;
   block_scale<FMT, SCALE_BF16>(amax, s_new, inv);
   uint32_t c[2];
@@ -117,7 +117,8 @@ __global__ __launch_bounds__(1024) void eco_quantize_wide_kernel(const void *src
     return;
   }
   const uint64_t end = start + group_size < numel ? start + group_size : numel;
-  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_WG>(src, weights, scales, e0, valid_from(e0, end), grp, 0, threadIdx.x == 0);
+  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_WG>(src, weights, scales, e0, valid_from(e0, end), grp, 0, threadIdx.x == 0,
+                                                             (int)((group_size + TILE_ELEMS - 1) / TILE_ELEMS));
 }
 
 // Tensor-wise, first pass: the maximum over each workgroup's share.  One workgroup per partial maximum, which is stored, not
@@ -125,8 +126,8 @@ __global__ __launch_bounds__(1024) void eco_quantize_wide_kernel(const void *src
 // at the rate of a large copy would be 68 (one workgroup per compute unit, four loads of a lane under way).
 constexpr int QUANT_MAX_THREADS = 1024;
 template <bool SRC_BF16>
-__global__ __launch_bounds__(QUANT_MAX_THREADS) void eco_quantize_max_kernel(const void *src, uint64_t numel, uint32_t slot) {
-  const uint64_t stride = (uint64_t)gridDim.x * QUANT_MAX_THREADS * ELEMS_PER_LANE;
+__global__ __launch_bounds__(QUANT_MAX_THREADS) void eco_quantize_max_kernel(const void *src, uint64_t numel, uint32_t slot, uint32_t parts) {
+  const uint64_t stride = (uint64_t)parts * QUANT_MAX_THREADS * ELEMS_PER_LANE;
   uint64_t e0 = ((uint64_t)blockIdx.x * QUANT_MAX_THREADS + threadIdx.x) * ELEMS_PER_LANE;
   // The maximum is one of bit patterns, as in every other reduction of the library: the float maximum would drop the NaN
   // of a lane all of whose elements are NaN.
@@ -244,7 +245,7 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
     constexpr uint64_t max_share = (uint64_t)QUANT_MAX_THREADS * ELEMS_PER_LANE;
     const uint64_t want = (numel + max_share - 1) / max_share;
     const uint32_t parts = want < QUANT_PARTS ? (uint32_t)want : QUANT_PARTS;
-    ECO_LAUNCH_CHECKED((eco_quantize_max_kernel<SR>), dim3(parts), dim3(QUANT_MAX_THREADS), 0, stream, src, numel, slot);
+    ECO_LAUNCH_CHECKED((eco_quantize_max_kernel<SR>), dim3(parts), dim3(QUANT_MAX_THREADS), 0, stream, src, numel, slot, parts);
     ECO_FLAT_CHECKED(flat_launch(numel, QUANT_PARTS), QUANT_PARTS, stream, (eco_quantize_tensorwise_kernel<FMT, SC, SR>), src, numel,
                      parts, weights, scales, slot);
     e = hipEventRecord(done, stream);

@@ -356,7 +356,7 @@ enum : int { RED_BLOCK = 0, RED_WG = 1, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS 
 
 constexpr uint32_t WG_ROWS = 16;
 // arg: RED_BLOCK: log2(group size); RED_WG_ROWS: which of the workgroup's groups the lane belongs to; RED_ROWS: the
-// first lane of the lane's group, `lanes` the lanes of a group.
+// first lane of the lane's group.  lanes: RED_ROWS: the lanes of a group; RED_WG: the waves of the workgroup.
 template <int RED>
 __device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t *slot, int lanes = 0) {
   if (RED == RED_ROWS) {
@@ -393,7 +393,7 @@ __device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t 
   }
   // RED_WG
   __shared__ uint32_t wave_max[16];
-  const int nwaves = (int)(blockDim.x >> 6);
+  const int nwaves = lanes;
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = wmax;
   __syncthreads();
   uint32_t r = wave_max[0];
@@ -621,7 +621,7 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   theta_lane<SCALE_BF16, ALGO, ACC>(a, x, w, sc, m, fill, d, th);
 
   const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
-                                       RED == RED_ROWS ? (int)(td.group_size >> 3) : 0);
+                                       RED == RED_ROWS ? (int)(td.group_size >> 3) : RED == RED_WG ? (int)a.wg_waves : 0);
   if (!WRITE) return;
   const Philox4 r = random_lane<ROUND>(a, td, e0, a.seed_lo, a.seed_hi);
   const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC>(a, td, e0, nvalid, fill, amax, r, th, d, m);
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);      // as in eco_step_kernel: loading waves first
   const uint32_t unit = blockIdx.x + a.unit_base;
   if (EXTRA && unit >= a.num_units) {
-    const uint32_t x = __builtin_amdgcn_readfirstlane((unit - a.num_units) * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    const uint32_t x = __builtin_amdgcn_readfirstlane((unit - a.num_units) * a.wg_waves + (threadIdx.x >> 6));
     if (x < a.num_extra) {
       const TensorDesc td = load_tensor_desc(a, load_table(a.extra_tensor, x));
       step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, x - td.first_unit, threadIdx.x & 63);
@@ -815,7 +815,7 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const StepArgs a) {
     const uint32_t gs = (uint32_t)td.group_size;
     uint32_t row = 0;
     for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * gs ? 1u : 0u;
-    if (ALGO == ALGO_ADAM_MASTER || end - start == (uint64_t)blockDim.x * ELEMS_PER_LANE)      // master weights: see step_geometry
+    if (ALGO == ALGO_ADAM_MASTER || end - start == (uint64_t)a.wg_waves * TILE_ELEMS)      // master weights: see step_geometry
       step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG_ROWS>(a, td, e0, 8, grp + row, lane_elem == row * gs, nullptr,
                                                                                  (int)row);
     else
@@ -824,32 +824,24 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const StepArgs a) {
     return;
   }
   // a group that fills every lane of the workgroup (e.g. rows of 1024, 2048, 4096) needs no per-lane guards
-  if (end - start == (uint64_t)blockDim.x * ELEMS_PER_LANE)
+  if (end - start == (uint64_t)a.wg_waves * TILE_ELEMS)
     step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG>(a, td, e0, 8, grp, threadIdx.x == 0, nullptr);
   else
     step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG>(a, td, e0, valid_from(e0, end), grp,
                                                                           threadIdx.x == 0, nullptr);
 }
 
-// (3) A short list of tensors, its descriptors in the kernel arguments, every class of scale group but the tensor-wise
-// one in one launch: a step of a few small tensors is bound by launches (2.6 us of host time each, 4-6 us on the device
-// with the drain between two), not by what they do.  All workgroups have the waves that the widest group asks for; a
-// workgroup finds its tensor by comparing its number with the tensors' first ones, a lane each.  Groups wider than a
-// wave are packed as many units to a workgroup as its waves hold; one-wave units take a wave each.
+// (3) Lists of little work, every class of scale group but the long tensor-wise one in one launch: a step of small tensors is
+// bound by launches (2.6 us of host time each, 4-6 us on the device with the drain between two), not by what they do.  All
+// workgroups have the waves that the widest group asks for (wg_waves).  Groups wider than a wave are packed as many units to a
+// workgroup as its waves hold; one-wave units take a wave each.  wg: the workgroup's number within its tensor.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(1024) void eco_step_small_kernel(const SmallArgs args) {
-  const ECO_CONST_AS SmallArgs *ka = (const ECO_CONST_AS SmallArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-  const StepArgs &a = args.step;
-  __builtin_amdgcn_s_setprio(3);
-  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
-  const uint32_t first = lane < args.num ? ka->first_wg[lane] : 0xFFFFFFFFu;
-  const uint32_t ti = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(first <= blockIdx.x)) - 1u;
-  const uint32_t wg = blockIdx.x - ka->first_wg[ti];
-  const TensorDesc td = read_tensor_desc((const ECO_CONST_AS uint64_t *)&ka->desc[ti]);
-  const uint32_t units = td.first_unit;
+__device__ __forceinline__ void step_list_workgroup(const StepArgs &a, const TensorDesc &td, uint32_t wg) {
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = a.wg_waves;
+  const uint32_t gs = (uint32_t)td.group_size, rows = td.slot;
   if (td.kind != UNIT_WIDE) {
     const uint32_t unit = wg * nwaves + wave;
-    if (unit >= units) return;
+    if ((uint64_t)unit * (td.kind == UNIT_ROWS ? rows * gs : td.kind == UNIT_ROW ? gs : (uint32_t)TILE_ELEMS) >= td.numel) return;
     const uint64_t tile_off = (uint64_t)unit * TILE_ELEMS;
     if (td.kind == UNIT_TILES && tile_off + TILE_ELEMS <= td.numel) {
       const uint64_t e0 = tile_off + (uint64_t)lane * ELEMS_PER_LANE;
@@ -860,18 +852,40 @@ __global__ __launch_bounds__(1024) void eco_step_small_kernel(const SmallArgs ar
     }
     return;
   }
-  const uint32_t gs = (uint32_t)td.group_size, rows = td.slot;
   const uint32_t uw = (rows * gs + TILE_ELEMS - 1) / TILE_ELEMS, per_wg = nwaves / uw;   // waves of a unit, units of a workgroup
   const uint32_t u = wave / uw, unit = wg * per_wg + u;
   const uint32_t lane_elem = (wave - u * uw) * TILE_ELEMS + lane * ELEMS_PER_LANE;
   const uint64_t start = (uint64_t)unit * rows * gs;
   uint64_t end = start + (uint64_t)rows * gs < td.numel ? start + (uint64_t)rows * gs : td.numel;
-  if (u >= per_wg || unit >= units) end = 0;              // nothing to do, but the barriers are the workgroup's
+  if (u >= per_wg || start >= td.numel) end = 0;          // nothing to do, but the barriers are the workgroup's
   uint32_t row = 0;
   for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * gs ? 1u : 0u;
   step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG_ROWS>(
       a, td, start + lane_elem, valid_from(start + lane_elem, end), (uint64_t)unit * rows + row, lane_elem == row * gs, nullptr,
       u < per_wg ? (int)(u * rows + row) : 0);
+}
+
+// With the descriptors in the kernel arguments (no table in device memory); a workgroup finds its tensor by comparing its number
+// with the tensors' first ones, a lane each.
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+__global__ __launch_bounds__(1024) void eco_step_small_kernel(const SmallArgs args) {
+  const ECO_CONST_AS SmallArgs *ka = (const ECO_CONST_AS SmallArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  __builtin_amdgcn_s_setprio(3);
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t first = lane < args.num ? ka->first_wg[lane] : 0xFFFFFFFFu;
+  const uint32_t ti = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(first <= blockIdx.x)) - 1u;
+  const TensorDesc td = read_tensor_desc((const ECO_CONST_AS uint64_t *)&ka->desc[ti]);
+  step_list_workgroup<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(args.step, td, blockIdx.x - ka->first_wg[ti]);
+}
+
+// With a plan's tables: any number of tensors (415 of them in rows of 984, 3024, 1120 and 4856 elements, us: a launch for each number of
+// waves 19.7, this 7.9; 142 in rows of 2304 and 108 in rows of 512 20.3 / 12.3).
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+__global__ __launch_bounds__(1024) void eco_step_list_kernel(const StepArgs a) {
+  __builtin_amdgcn_s_setprio(3);
+  const uint32_t wg = blockIdx.x + a.unit_base;
+  const TensorDesc td = load_tensor_desc(a, load_table(a.list_tensor, wg));
+  step_list_workgroup<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, wg - td.first_unit);
 }
 
 // (4) One scale per tensor (tensor-wise scaling, Sec. 4.4), tensors too large for one workgroup: two passes
@@ -963,8 +977,12 @@ template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
 hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
   const StepArgs &args = sl.args;
   if (sl.small) {
-    ECO_LAUNCH_CHECKED((eco_step_small_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(sl.small_wgs), dim3(64 * sl.small_waves), 0, stream,
+    ECO_LAUNCH_CHECKED((eco_step_small_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3((unsigned)sl.list_wgs), dim3(64 * sl.list_waves), 0, stream,
                        *sl.small);
+  } else if (sl.list_wgs) {
+    StepArgs la = args;
+    la.wg_waves = sl.list_waves;
+    ECO_CHUNKS_CHECKED((eco_step_list_kernel<FMT, STATE_BF16, SC, AL, RD>), sl.list_wgs, 64 * sl.list_waves, 0, stream, la, sl.max_launch_threads);
   } else {
     if (args.num_tiles || (args.num_extra && sl.extra_in == 0)) {
       StepArgs ta = args;
@@ -978,6 +996,7 @@ hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
       const unsigned lds = sl.lds_bytes_wide[nw];
       wa.wide_tensor = sl.wide_base + sl.wide_offset[nw];
       wa.num_units = sl.num_wide[nw];
+      wa.wg_waves = static_cast<uint32_t>(nw);
       if (sl.extra_in != nw || !args.num_extra)
         ECO_CHUNKS_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, false>), wa.num_units, 64 * nw,
                            lds, stream, wa, sl.max_launch_threads);

@@ -6,7 +6,7 @@
 // 12 bytes (theta~, m~, d) for 8 million elements, so here they wait on the chip for the tensor's maximum instead:
 //
 // The tensors of the list, one after the other, are cut into slabs of 6144 elements (one 512-element tile to each of a
-// workgroup's 12 waves).  One workgroup per compute unit takes every gridDim-th slab.  In turn i a wave computes theta~ of
+// workgroup's 12 waves).  One workgroup per compute unit takes every resident_wgs-th slab.  In turn i a wave computes theta~ of
 // its tile of slab i, keeps it, and the workgroup publishes the slab's maximum in slab_max[]; then it quantizes and
 // writes its tile of slab i - 4, whose tensor's last slab has been published by some workgroup a turn or more ago.  The
 // loads of slab i + 1 are in flight all the while, and the entries of slab_max[] that the next turn needs are loaded a
@@ -145,8 +145,8 @@ __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_reside
   __syncthreads();
 
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t n = (a.num_slabs - blockIdx.x + gridDim.x - 1) / gridDim.x;      // slabs of this workgroup
-  const auto slab_of = [&](uint32_t i) { return blockIdx.x + i * gridDim.x; };
+  const uint32_t n = (a.num_slabs - blockIdx.x + a.resident_wgs - 1) / a.resident_wgs;      // slabs of this workgroup
+  const auto slab_of = [&](uint32_t i) { return blockIdx.x + i * a.resident_wgs; };
   // element offset of the wave's tile in its tensor
   const auto tile_at = [&](const TensorDesc &td, uint32_t slab) { return ((uint64_t)(slab - td.first_unit) * WAVES + wave) * TILE_ELEMS; };
   const auto tensor_of = [&](uint32_t i) { return load_table(a.slab_tensor, slab_of(i < n ? i : n - 1)); };
@@ -354,9 +354,9 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_k
     for (uint32_t k = lane; k < slabs_of(td); k += 64) { const uint32_t y = a.slab_max[td.first_unit + k]; x = x > y ? x : y; }
     return wave_umax(x);
   };
-  uint32_t first = blockIdx.x * NW + wave, stride = gridDim.x * NW;
+  uint32_t first = blockIdx.x * NW + wave, stride = a.resident_wgs * NW;
   if (marked) {
-    for (uint32_t slab = blockIdx.x; slab < a.num_slabs; slab += gridDim.x) {
+    for (uint32_t slab = blockIdx.x; slab < a.num_slabs; slab += a.resident_wgs) {
       if (!__builtin_amdgcn_readfirstlane(a.deferred[slab])) continue;
       const TensorDesc td = load_tensor_desc(a, load_table(a.slab_tensor, slab));
       uint32_t amax = max_of(td);
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_k
     }
     __shared__ uint32_t last;
     __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(&a.resident_counts[1], 1u) == gridDim.x - 1;
+    if (threadIdx.x == 0) last = atomicAdd(&a.resident_counts[1], 1u) == a.resident_wgs - 1;
     __syncthreads();
     if (!last) return;
     if (threadIdx.x < 2) a.resident_counts[threadIdx.x] = 0;
@@ -401,10 +401,13 @@ hipError_t launch_resident(const StepLaunch &sl, hipStream_t stream) {
     ECO_LAUNCH_CHECKED((eco_step_resident_tail_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(per_tensor - done < 2 * most ? per_tensor - done : 2 * most),
                        dim3(RES_FINISH_THREADS), 0, stream, ta);
   }
-  ECO_LAUNCH_CHECKED((eco_step_resident_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(wgs), dim3(block), 0, stream, sl.args);
+  ta = sl.args;
+  ta.resident_wgs = wgs;
+  ECO_LAUNCH_CHECKED((eco_step_resident_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(wgs), dim3(block), 0, stream, ta);
   unsigned fin = res_finish_workgroups(sl.args.num_resident, sl.args.num_slabs, sl.resident_wgs);
   if (fin > 2 * most) fin = 2 * most;
-  ECO_LAUNCH_CHECKED((eco_step_resident_finish_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(fin), dim3(RES_FINISH_THREADS), 0, stream, sl.args);
+  ta.resident_wgs = fin;
+  ECO_LAUNCH_CHECKED((eco_step_resident_finish_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(fin), dim3(RES_FINISH_THREADS), 0, stream, ta);
   return hipSuccess;
 }
 

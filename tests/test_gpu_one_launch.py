@@ -67,15 +67,21 @@ def grouped(numel, group, fmt):
 @pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("fp8", True, dict(mode=3, weight_decay=0.1)), ("int4", True, {}),
                                            ("int4", False, dict(opt=1, round=1, lr=0.05)), ("fp8", False, dict(opt=1, mode=2, lr=0.05)),
                                            ("fp8", False, dict(eps=0.0))])
-@pytest.mark.parametrize("few", [False, True])
-def test_rows_that_leave_lanes_idle(few, fmt, bf16, over):
+@pytest.mark.parametrize("path", ["classes", "list", "noalloc"])
+def test_rows_that_leave_lanes_idle(path, fmt, bf16, over):
     """Rows of which several share a workgroup and rows that have one to themselves, their last waves part idle: numbers of rows
-    that fill the last workgroup and that do not, a last row that is cut off behind a whole piece of 8 elements and within one.
-    few: in the short-list kernel."""
+    that fill the last workgroup and that do not, a last row that is cut off behind a whole piece of 8 elements and within one;
+    and tensors of any length with one scale that are one group.  In a launch for each class of group (a large tensor beside
+    them), in one launch with a plan's tables, and in launches of 44 with the descriptors as arguments."""
+    from paper_2601_22101_amd import binding as eco
     from paper_2601_22101_amd import harness
     o32 = oracle.get("f32")
-    specs = [grouped(n, g, fmt) for g in ((640, 1000, 1152) if few else (520, 576, 664, 720, 800, 896, 1000, 1152, 1280, 1408, 1800, 2304, 2816, 8000))
+    specs = [grouped(n, g, fmt) for g in (520, 576, 664, 720, 800, 896, 1000, 1152, 1280, 1408, 1800, 2304, 2816, 8000)
              for n in (g, 2 * g, 4 * g, 7 * g, 3 * g + 8, 2 * g + 5, 5 * g - 3)]
+    specs += [grouped(n, n, fmt) for n in (1, 5, 100, 511, 513, 1001, 4097, 8191)] + [T(f"p{n}", (n,), "bf16_plain") for n in (7, 1027)]
+    specs += [grouped(1000, 24, fmt), grouped(700, 336, fmt), grouped(1500, 128, fmt)]
+    if path == "classes":
+        specs.append(T("large", (9000, 1024), fmt, granularity="row"))
     wl = workloads.Workload("idle_lanes", specs, steps=2, state_bf16=bf16, scale_bf16=bf16)
     dw = harness.DeviceWorkload(wl, DEV, layout=over)
     host = [host_copy(tv) for tv in dw.tensors]
@@ -83,8 +89,12 @@ def test_rows_that_leave_lanes_idle(few, fmt, bf16, over):
         dw.fill_gradients(k)
         hp = dw.hparams(k)
         for tv, h in zip(dw.tensors, host):
+            tv.grad[tv.grad == 0] = 1e-4              # (with eps = 0 a gradient of zero in the first step is 0 / 0)
             h["grad"] = bf16_bits(tv.grad)
-        dw.plan.step(hp)
+        if path == "noalloc":
+            eco.eco_step_tensors_noalloc([dw.descriptor(tv) for tv in dw.tensors], hp)
+        else:
+            dw.plan.step(hp)
         torch.cuda.synchronize()
         for tv, h in zip(dw.tensors, host):
             oracle_step(o32, h, tv.spec.numel, step_config(hp, tv.tensor_id, tv.fmt, group_size=dw.group_size(tv)))
@@ -122,7 +132,7 @@ def test_identity_weights_step_alike_alone_and_beside_quantized_tensors(opt, noa
 
 @pytest.mark.parametrize("fmt,scale_bf16", [(0, False), (1, True)])
 @pytest.mark.parametrize("src_bf16", [False, True])
-@pytest.mark.parametrize("numel", [5, 8201, 256 * 8 * 3 + 1, 1024 * 8 * 256 + 8, 1024 * 8 * 256 * 5 + 4099])
+@pytest.mark.parametrize("numel", [5, 509, 513, 8191, 8201, 256 * 8 * 3 + 1, 1024 * 8 * 256 + 8, 1024 * 8 * 256 * 5 + 4099])
 def test_tensor_wise_quantizer_at_the_edges_of_its_shares(fmt, scale_bf16, src_bf16, numel):
     """One partial maximum per 8192 elements up to 256 of them, then several turns to a workgroup; the largest element in
     the first and in the last place."""
