@@ -309,11 +309,13 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
       p.units = numel / TILE_ELEMS;
       p.tail = rest;
     }
-  } else if (cls == GROUP_WIDE) {
+  } else if (cls == GROUP_WIDE || (step && numel <= MAX_WIDE_GROUP)) {
+    // (one scale for a whole tensor of up to 8192 elements is one group, of any length: its last piece of 8 elements is cut off; 282
+    // tensors of 64, 318 and 2650 elements, us: those of odd length in slabs, with a launch for their tails, 17.0, so 6.2)
     p.group = group_size < numel ? group_size : numel;
     if (p.group <= static_cast<uint64_t>(TILE_ELEMS)) {
       p.list = LIST_EXTRA;
-      p.rows = rows_per_wave(p.group);
+      p.rows = cls == GROUP_WIDE ? rows_per_wave(p.group) : 1;
       p.kind = p.rows > 1 ? UNIT_ROWS : UNIT_ROW;
       p.entries = (numel + p.group - 1) / p.group;
       p.units = (p.entries + p.rows - 1) / p.rows;
@@ -327,6 +329,7 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
       p.units = w.units;
       p.idle = w.rows * p.group % TILE_ELEMS != 0;
     }
+    if (cls == GROUP_TENSOR) p.entries = (numel + TILE_ELEMS - 1) / TILE_ELEMS + 1;
   } else {
     p.group = numel;
     p.list = LIST_TW_TILES;

@@ -227,6 +227,14 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
     else
       ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, false>), dim3((unsigned)((numel + p.group - 1) / p.group)),
                          dim3((unsigned)((p.group + TILE_ELEMS - 1) / TILE_ELEMS) * 64), 0, stream, src, numel, (uint32_t)p.group, 1u, weights, scales);
+  } else if (numel <= MAX_WIDE_GROUP) {
+    // one scale for a tensor that one workgroup holds: one group (4001 elements, us: in two passes, with their event, 8.9, so 4.3)
+    if (numel <= static_cast<uint64_t>(TILE_ELEMS))
+      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR, true>), dim3(1), dim3(WG_THREADS), 0, stream, src, numel, (uint32_t)numel, 1u,
+                         weights, scales);
+    else
+      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, false>), dim3(1), dim3((unsigned)tiles * 64), 0, stream, src, numel, (uint32_t)numel,
+                         1u, weights, scales);
   } else {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
