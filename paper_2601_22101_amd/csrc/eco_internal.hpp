@@ -353,8 +353,8 @@ inline Placement place_tensor(uint64_t numel, uint64_t group_size, int cls, bool
 //   304, 290 / 303).  Workgroups of 5 to 7 and of 9 to 16 waves gain nothing or lose: 640 314 / 309, 3072 316 / 314, 8192 336 / 336.
 //   Master weights, fp32 state, two or up to 10 waves: 768 701 / 789, 1024 766 / 803, 2048 724 / 793, 640 724 / 780, 4096 757 / 771.
 //   Master weights, bf16 state, 12: 1024 478 / 519, 2048 505 / 546, 3072 505 / 533.
-//   SGDM, fp32 state, 14.5: 768 304 / 328, 1024 310 / 319, 2048 299 / 332, 3072 301 / 332, 3584 302 / 338, 4096 314 / 332, 6144 305 /
-//   314; with a stored error, 11.5: 768 510 / 551, 1024 511 / 525, 2048 501 / 527, 4096 531 / 537; with master weights, 8.5: 768 489 /
+//   SGDM, fp32 state, 14.5: 768 304 / 328, 1024 310 / 319, 2048 299 / 332, 3072 301 / 332, 3584 302 / 338, 4096 314 / 332 (larger
+//   workgroups lose: 2304, two of 9 waves, 332 / 309); with a stored error, 11.5: 768 510 / 551, 1024 511 / 525, 2048 501 / 527, 4096 531 / 537; with master weights, 8.5: 768 489 /
 //   529, 1024 507 / 521, 2048 511 / 541, 4096 515 / 532.
 inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, uint64_t units, uint64_t idle) {
   if (idle > units / 8) return 0;
@@ -362,7 +362,8 @@ inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, uint64_t u
   if (kv.algo == ALGO_ADAM) return kv.state_bf16 && (nw <= 4 || nw == 8) ? at_least(200) : 0;
   if (kv.algo == ALGO_ADAM_MASTER) return kv.state_bf16 ? at_least(115) : nw <= 5 ? 10 / nw : 2;
   if (kv.state_bf16) return 0;
-  return at_least(kv.algo == ALGO_SGDM ? 145 : kv.algo == ALGO_SGDM_EXACT ? 115 : 85);
+  if (kv.algo == ALGO_SGDM) return nw <= 8 ? at_least(145) : 0;
+  return at_least(kv.algo == ALGO_SGDM_EXACT ? 115 : 85);
 }
 // (b) where rows leave lanes idle, `elements` in the launch's `units` workgroups:
 //   Adam, fp32 state, 13.6: 520 523 / 590, 640 510 / 577, 1000 522 / 629, 1152 512 / 520, 1408 510 / 575, 1800 515 / 608, 2304 513 /
