@@ -122,7 +122,7 @@ struct Lists {                           // the launch lists of one storage form
   size_t off_tile = 0, off_extra = 0, off_wide[eco::MAX_WIDE_WAVES + 1] = {0}, off_tw_tile = 0, off_tw_tensor = 0, off_slots = 0,
          off_tile_max = 0, off_slab = 0, off_resident = 0, off_tail_max = 0, off_slab_max = 0, off_counts = 0, off_deferred = 0;
   uint64_t tensors = 0, most_tw_tiles = 0, tails = 0;
-  struct WideLoad { uint64_t idle, elements; };          // of a wide list: units that leave lanes idle; elements
+  struct WideLoad { uint64_t idle, elements; };          // of a wide list: units that leave lanes idle; elements (0: the one-wave units')
   WideLoad load[eco::MAX_WIDE_WAVES + 1] = {};
   std::vector<uint32_t> one;             // all but the tensor-wise tensors as one launch, where that is the better way: workgroup -> tensor
   size_t off_one = 0;
@@ -285,10 +285,11 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   const int waves = default_waves(kv, hbm);
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
-  // a launch of one-wave units beside few tiles or none has no cap: their guarded accesses want all the waves there are (60 M
-  // elements in rows of 264, us, with the cap / without: FP8 Adam 494 / 236, SGDM 310 / 163; in rows of 160 294 / 224, 183 / 133)
+  // a launch of one-wave units beside few tiles does not have the tiles' cap, which counts on every lane; short rows alone have
+  // one of their own
   const bool units = (kv.fmt == eco::FMT_FP8 || kv.fmt == eco::FMT_INT4) && a->num_extra > a->num_tiles / 8;
-  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? 0 : lds_for_waves(waves, 512);
+  const unsigned resident = units && !a->num_tiles && load[0].elements ? eco::unit_workgroups(kv, hbm.fully, a->num_extra, load[0].elements) : 0;
+  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? eco::lds_for_workgroups(resident) : lds_for_waves(waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
     const uint64_t units = sl->num_wide[nw];
     const bool idle = load[nw].idle > units / 8, adam32 = kv.algo == eco::ALGO_ADAM && !kv.state_bf16;
@@ -654,6 +655,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
         g.resident.push_back(idx);
       } else {
         elements[f] += t.numel;
+        if (p.list == eco::LIST_EXTRA) g.load[0].elements += t.numel;
         if (p.kind == eco::UNIT_WIDE) {
           Lists::WideLoad &w = g.load[p.list - eco::LIST_WIDE1 + 1];
           w.idle += p.idle ? p.units : 0;
@@ -867,6 +869,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
                   "groups wider than 512): the static scratch does not hold them (use a plan)", MAX_UNITS);
     count[f][p.list] += p.units;
     units += p.units;
+    if (p.list == eco::LIST_EXTRA) load[f][0].elements += tensors[i].numel;
     if (p.kind == eco::UNIT_WIDE) {
       Lists::WideLoad &w = load[f][p.list - eco::LIST_WIDE1 + 1];
       w.idle += p.idle ? p.units : 0;
@@ -882,9 +885,11 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   }
   if (units > MAX_UNITS) {               // the wide lists again, as the limit counts them
     rows.own_rows = false;
-    std::memset(load, 0, sizeof load);
     for (int f = 0; f < 4; ++f)
-      for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) count[f][eco::LIST_WIDE1 + nw - 1] = 0;
+      for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
+        count[f][eco::LIST_WIDE1 + nw - 1] = 0;
+        load[f][nw] = Lists::WideLoad{0, 0};
+      }
     for (size_t i = 0; i < n; ++i) {
       const eco::Placement p = place(tensors[i]);
       if (p.kind != eco::UNIT_WIDE) continue;
@@ -901,6 +906,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   };
   for (int f = eco::FMT_BF16_PLAIN; f <= eco::FMT_FP32_ID && plain_home >= 0; ++f) {
     count[plain_home][eco::LIST_EXTRA] += count[f][eco::LIST_EXTRA];
+    load[plain_home][0].elements += load[f][0].elements;
     count[f][eco::LIST_EXTRA] = 0;
   }
   (void)hipGetLastError();

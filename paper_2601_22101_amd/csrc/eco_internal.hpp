@@ -382,6 +382,32 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t units, ui
   if (kv.algo == ALGO_ADAM_MASTER) return 0;
   return at_least(kv.algo == ALGO_SGDM ? 220 : kv.algo == ALGO_SGDM_EXACT ? 165 : 97);
 }
+// Waves per compute unit of a launch of one-wave units alone (short rows), `elements` in `units` of them; 0: as many as fit.
+// Again the smallest number with a certain number of waves' worth of busy lanes.  For arrays that come from HBM, 100 M elements,
+// us, with / without --
+//   Adam, fp32 state, 10.3: rows of 48 369 / 389, 160 368 / 393, 200 365 / 391, 328 378 / 395, 400 362 / 406, 504 393 / 415 (INT4 354 / 368,
+//   353 / 372, 359 / 370, 361 / 373, 355 / 383, 366 / 395); bf16 state, 20.5, where nine lanes in ten are busy: INT4 48 214 / 219, 160
+//   217 / 225, 504 211 / 229 (FP8 227 / 238, 234 / 245, 223 / 252), others none (400 243 / 222).
+//   Master weights, fp32 state, 7: 96 506 / 559, 160 517 / 551, 200 544 / 590, 264 583 / 612, 328 532 / 589, 400 533 / 586, 504 535 / 599.
+//   SGDM, fp32 state, 15.5, where three in four are: 48 215 / 234, 400 217 / 232, 504 214 / 247, others none (328 241 / 226); with a stored
+//   error, 13.4: 48 352 / 394, 200 364 / 399, 328 369 / 405, 400 366 / 404, 504 362 / 417; with master weights, 8.2: 48 376 / 394, 160 380 / 389,
+//   200 381 / 404, 264 386 / 416, 328 372 / 399, 400 369 / 408, 504 361 / 408.
+// For arrays in the cache before it only Adam with fp32 state, 16, where three lanes in four are busy (8 M elements: 96 28.9 / 30.0, 400
+// 29.8 / 30.6; 25 M 87.8 / 90.3, 91.5 / 93.1).
+inline unsigned unit_workgroups(const KernelVariant &kv, bool from_hbm, uint64_t units, uint64_t elements) {
+  const uint64_t lanes = units * TILE_ELEMS;
+  const auto at_least = [=](uint64_t tenths) { return static_cast<unsigned>((tenths * lanes + 10 * elements - 1) / (10 * elements)); };
+  const bool most = elements * 4 >= lanes * 3;
+  if (!from_hbm) return kv.algo == ALGO_ADAM && !kv.state_bf16 && most ? at_least(160) : 0;
+  if (kv.state_bf16) return kv.algo == ALGO_ADAM && elements * 10 >= lanes * 9 ? at_least(205) : 0;
+  switch (kv.algo) {
+    case ALGO_ADAM: return at_least(103);
+    case ALGO_ADAM_MASTER: return at_least(70);
+    case ALGO_SGDM: return most ? at_least(155) : 0;
+    case ALGO_SGDM_EXACT: return at_least(134);
+    default: return at_least(82);
+  }
+}
 // The dynamic LDS that keeps k workgroups resident per compute unit (0: no request); LDS is handed out in pieces of 1280
 // bytes, and a workgroup has up to 128 of its own beside it.
 inline uint32_t lds_for_workgroups(unsigned k) {
