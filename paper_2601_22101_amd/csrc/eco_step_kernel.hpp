@@ -349,10 +349,11 @@ __device__ __forceinline__ void step_sizes8(const StepArgs &a, const float (&x)[
 //   RED_TILE   first pass of the step for a group larger than a workgroup (tensor-wise scaling): wave all-reduce, the wave's
 //              maximum goes to its tile's entry of a scratch array, which a small kernel folds into the
 //              tensor's slot (tens of thousands of atomics on one address serialize in the memory system)
+//   RED_TILE_KEEP the same with master weights, whose new values, and the moments, are final before the scale is known: they are stored
 //   RED_ROWS   groups of up to 256 elements of any length, several to a wave: segmented all-reduce over the group's lanes
 //   RED_SLOT   second pass: the abs-max is read from that slot; everything is recomputed and written
 //              except the scale (a last, tiny kernel writes it once every tile has used the old one)
-enum : int { RED_BLOCK = 0, RED_WG = 1, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS = 5, RED_ROWS = 6 };
+enum : int { RED_BLOCK = 0, RED_WG = 1, RED_TILE_KEEP = 2, RED_SLOT = 3, RED_TILE = 4, RED_WG_ROWS = 5, RED_ROWS = 6 };
 
 constexpr uint32_t WG_ROWS = 16;
 // arg: RED_BLOCK: log2(group size); RED_WG_ROWS: which of the workgroup's groups the lane belongs to; RED_ROWS: the
@@ -387,7 +388,7 @@ __device__ __forceinline__ float group_absmax(float lane_max, int arg, uint32_t 
     return u2f(row_max[arg]);
   }
   const uint32_t wmax = group_umax(f2u(lane_max), 64);
-  if (RED == RED_TILE) {
+  if (RED == RED_TILE || RED == RED_TILE_KEEP) {
     if ((threadIdx.x & 63) == 0) *slot = wmax;
     return 0.0f;
   }
@@ -550,7 +551,8 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
                                           uint64_t sg, bool scale_writer, uint32_t *slot, int row = 0) {
   constexpr bool ADAM = algo_is_adam(ALGO);
   constexpr bool MASTER = algo_is_master(ALGO);
-  constexpr bool WRITE = RED != RED_TILE;   // the first pass of a two-pass group writes nothing
+  constexpr bool KEEP = RED == RED_TILE_KEEP;
+  constexpr bool WRITE = RED != RED_TILE && !KEEP;   // the first pass of a two-pass group writes nothing but what is final
   const bool any = ACC == ACC_FULL || nvalid > 0;
 
   float g[8], m[8], v[8], w[8], x[8], d[8], th[8], sc = 1.0f;
@@ -617,8 +619,12 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   __builtin_amdgcn_s_setprio(0);      // loads issued: back to the default priority (see eco_step_kernel)
 
   moments_lane<ALGO, LATE>(a, g, m, v, x);
-  if (ADAM && WRITE && !LATE) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);   // v is final (Alg. 3 returns it unchanged)
+  if (ADAM && (WRITE || KEEP) && !LATE) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);   // v is final (Alg. 3 returns it unchanged)
   theta_lane<SCALE_BF16, ALGO, ACC>(a, x, w, sc, m, fill, d, th);
+  if (KEEP) {
+    store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, th);
+    store_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+  }
 
   const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
                                        RED == RED_ROWS ? (int)(td.group_size >> 3) : RED == RED_WG ? (int)a.wg_waves : 0);
@@ -626,6 +632,17 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   const Philox4 r = random_lane<ROUND>(a, td, e0, a.seed_lo, a.seed_hi);
   const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC>(a, td, e0, nvalid, fill, amax, r, th, d, m);
   if (RED != RED_SLOT && scale_writer && any) store_scale<SCALE_BF16>(td, sg, s_new);
+}
+
+// The second pass with master weights: they hold theta~, only the codes are left to write.
+template <int FMT, bool SCALE_BF16, int ROUND, int ACC>
+__device__ __forceinline__ void quantize_master_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid, const uint32_t *slot) {
+  float th[8], qn[8];
+  uint32_t cn[2];
+  load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, th);
+  const Philox4 r = random_lane<ROUND>(a, td, e0, a.seed_lo, a.seed_hi);
+  (void)quantize_lane8<FMT, SCALE_BF16, ROUND, ACC>(u2f(*slot), r, nvalid, th, cn, qn);
+  store_codes8<FMT, ACC>(td.w, e0, nvalid, cn);
 }
 
 // The launch tables are read-only for the lifetime of a launch; reading them through the constant
@@ -892,7 +909,9 @@ __global__ __launch_bounds__(1024) void eco_step_list_kernel(const StepArgs a) {
 // over 512-element tiles.  Pass 1 recomputes theta~ and leaves each tile's abs-max in a scratch array, which
 // a reduction kernel (see eco_tensorwise_reduce_kernel) folds into the tensor's slot; pass 2 recomputes theta~ again
 // (the inputs are untouched so far), quantizes against the slot's value and writes codes and state; a last
-// kernel writes the new scales.
+// kernel writes the new scales.  With master weights nothing but the codes waits for the scale: pass 1 stores them and the
+// moments, pass 2 reads them alone (31 bytes a parameter with Adam and fp32 state where recomputing takes 41: six tensors of 64 M
+// elements in INT4 2817 -> 2164 us; SGDM 324 M 1644 -> 1295; Adam with bf16 state two of 51 M 544 -> 415).
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int RED>
 __global__ __launch_bounds__(WG_THREADS) void eco_step_tensorwise_kernel(const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);      // as in eco_step_kernel: loading waves first
@@ -903,10 +922,17 @@ __global__ __launch_bounds__(WG_THREADS) void eco_step_tensorwise_kernel(const S
   const uint64_t tile_off = (uint64_t)(unit - td.first_unit) * TILE_ELEMS;
   const uint64_t e0 = tile_off + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
   uint32_t *slot = RED == RED_TILE ? a.tile_max + unit : a.slots + td.slot;
-  if (tile_off + TILE_ELEMS <= td.numel)
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED>(a, td, e0, 8, 0, false, slot);
-  else
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_GUARDED, RED>(a, td, e0, valid_from(e0, td.numel), 0, false, slot);
+  constexpr int R = algo_is_master(ALGO) && RED == RED_TILE ? RED_TILE_KEEP : RED;
+  const bool whole = tile_off + TILE_ELEMS <= td.numel;
+  const int nvalid = valid_from(e0, td.numel);
+  if (algo_is_master(ALGO) && RED == RED_SLOT) {
+    if (whole) quantize_master_lane<FMT, SCALE_BF16, ROUND, ACC_FULL>(a, td, e0, 8, slot);
+    else quantize_master_lane<FMT, SCALE_BF16, ROUND, ACC_GUARDED>(a, td, e0, nvalid, slot);
+  } else if (whole) {
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, R>(a, td, e0, 8, 0, false, slot);
+  } else {
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_GUARDED, R>(a, td, e0, nvalid, 0, false, slot);
+  }
 }
 
 // tw_reduce_wgs workgroups per tensor (one for every 16 384 tiles of the longest), which meet in its slot (zero until

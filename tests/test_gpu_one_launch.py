@@ -104,6 +104,31 @@ def test_rows_that_leave_lanes_idle(path, fmt, bf16, over):
 
 
 @pytest.mark.parametrize("opt", [0, 1])
+@pytest.mark.parametrize("fmt,bf16", [("fp8", False), ("int4", True), ("int4", False)])
+def test_master_weights_with_one_scale_in_two_passes(fmt, bf16, opt):
+    """Pass 1 stores the master weights and the moments, pass 2 reads the former alone: whole and partial last tiles, a last piece of 8
+    elements that is cut off (such a tail keeps the list, a short one, out of the one-pass form)."""
+    from paper_2601_22101_amd import harness
+    o32 = oracle.get("f32")
+    specs = [grouped(n, n, fmt) for n in (8193, 8200, 512 * 17, 512 * 17 + 5, 100003)]
+    wl = workloads.Workload("master_two_passes", specs, steps=2, state_bf16=bf16, scale_bf16=bf16, lr=1e-3 if opt == 0 else 0.05)
+    dw = harness.DeviceWorkload(wl, DEV, layout=dict(opt=opt, mode=3, weight_decay=0.1))
+    host = [host_copy(tv) for tv in dw.tensors]
+    for k in (1, 2):
+        dw.fill_gradients(k)
+        hp = dw.hparams(k)
+        for tv, h in zip(dw.tensors, host):
+            h["grad"] = bf16_bits(tv.grad)
+        dw.plan.step(hp)
+        torch.cuda.synchronize()
+        for tv, h in zip(dw.tensors, host):
+            oracle_step(o32, h, tv.spec.numel, step_config(hp, tv.tensor_id, tv.fmt, group_size=dw.group_size(tv)))
+            st = compare(host_copy(tv), h, f"step {k} {tv.spec.name}", bf16)
+            assert not any(v for key, v in st.items() if key.endswith("mismatch")), (tv.spec.name, st)
+    dw.close()
+
+
+@pytest.mark.parametrize("opt", [0, 1])
 @pytest.mark.parametrize("noalloc", [False, True])
 def test_identity_weights_step_alike_alone_and_beside_quantized_tensors(opt, noalloc):
     from paper_2601_22101_amd import binding as eco
