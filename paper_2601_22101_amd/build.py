@@ -26,10 +26,11 @@ SOURCES = [
 ]
 
 # -ffp-contract=off: the kernels spell every fused multiply-add explicitly, so that their fp32
-# results can be reproduced operation by operation.  Packed fp32 instructions are disabled.
+# results can be reproduced operation by operation.  Packed fp32 instructions are disabled.  The first 16 dwords of a kernel's
+# arguments are in scalar registers when its waves start (members of a struct stay in memory).
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
-    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes",
 ]
 

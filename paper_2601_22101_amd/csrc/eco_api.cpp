@@ -683,7 +683,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       }
     }
 
-    // one device buffer: per format [full tiles | one-wave units | all of a list launch | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots |
+    // one device buffer: per format [full tiles | one-wave units (right behind: see eco_step_kernel) | all of a list launch | wide lists 1..16 | tensor-wise tiles | tensor-wise tensors | slots |
     // tile maxima | slabs | their tensors | tail maxima | slab maxima | counts | deferred slabs]
     for (Lists &g : plan->lists) {
       const auto add = [&host](const std::vector<uint32_t> &l, size_t *off) {
@@ -773,7 +773,7 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     std::memset(&sl, 0, sizeof sl);
     eco::StepArgs &a = sl.args;
     a.tensors = plan->d_descs;
-    a.tile_tensor = plan->d_tables + g.off_tile;
+    sl.tile_tensor = plan->d_tables + g.off_tile;
     a.extra_tensor = plan->d_tables + g.off_extra;
     a.num_tiles = static_cast<uint32_t>(g.tile.size());
     a.num_extra = static_cast<uint32_t>(g.extra.size());
@@ -800,7 +800,7 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     a.num_slabs = static_cast<uint32_t>(g.slab.size());
     a.resident_tries = eco::RES_TRIES;
     sl.resident_wgs = static_cast<unsigned>(plan->cus);
-    a.list_tensor = plan->d_tables + g.off_one;
+    sl.list_tensor = plan->d_tables + g.off_one;
     sl.list_wgs = g.one.size();
     sl.list_waves = g.one_waves;
     st = launch_format(hp, c, f, plan->cus, g.load, plan->bytes, &sl, nullptr, static_cast<hipStream_t>(stream));
@@ -998,7 +998,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     std::memset(&sl, 0, sizeof sl);
     eco::StepArgs &a = sl.args;
     a.tensors = descs;
-    a.tile_tensor = tables + start[f][eco::LIST_TILE];
+    sl.tile_tensor = tables + start[f][eco::LIST_TILE];
     a.extra_tensor = tables + start[f][eco::LIST_EXTRA];
     a.num_tiles = static_cast<uint32_t>(count[f][eco::LIST_TILE]);
     a.num_extra = static_cast<uint32_t>(count[f][eco::LIST_EXTRA]);

@@ -111,9 +111,7 @@ static_assert(sizeof(TensorDesc) == 80, "TensorDesc layout");
 
 struct StepArgs {            // by-value kernel argument: everything wave-uniform
   const TensorDesc *tensors;
-  const uint32_t *tile_tensor;     // block-scaled tensors: full tile -> index into tensors
   const uint32_t *extra_tensor;    // one-wave units that ride in this launch: unit -> index into tensors
-  const uint32_t *wide_tensor;     // wide groups of the launch in flight: group -> index into tensors
   const uint32_t *tw_tile_tensor;  // tensor-wise scaling: tile (full or partial) -> index into tensors
   const uint32_t *tw_tensor;       //   ... the tensors themselves
   uint32_t *slots;                 //   ... one abs-max slot (fp32 bit pattern) per such tensor
@@ -134,7 +132,6 @@ struct StepArgs {            // by-value kernel argument: everything wave-unifor
   uint32_t num_units;              // wide-group launch: work items before the extra ones
   uint32_t wg_waves;               // waves of a workgroup of the launch in flight (a kernel that asks the runtime for its geometry is
                                    // passed 256 bytes of arguments more, 0.7 to 1 us of a call)
-  const uint32_t *list_tensor;     // the list kernel: workgroup -> index into tensors
 };
 
 // A list of at most SMALL_TENSORS tensors, carried by value in the kernel arguments (4 KB): the allocation-free step of a short
@@ -161,7 +158,9 @@ struct StepLaunch {
   uint32_t lds_bytes;              // dynamic LDS per workgroup of the full-tile kernel (occupancy cap)
   uint32_t lds_bytes_wide[MAX_WIDE_WAVES + 1];   // the same per workgroup of the wide-group kernel, by its waves
   uint32_t lds_bytes_tw;           // the same per (one-wave) workgroup of the two tensor-wise passes
-  const uint32_t *wide_base;       // wide-group lists, one per workgroup size, back to back
+  const uint32_t *tile_tensor;     // block-scaled tensors: full tile -> index into the descriptors; args.extra_tensor lies behind it
+  const uint32_t *list_tensor;     // the list kernel: workgroup -> index into the descriptors
+  const uint32_t *wide_base;       // group -> index into the descriptors: wide-group lists, one per workgroup size, back to back
   uint32_t wide_offset[MAX_WIDE_WAVES + 1];
   uint32_t num_wide[MAX_WIDE_WAVES + 1];
   unsigned resident_wgs;           // workgroups of the one-pass tensor-wise kernel: one per compute unit
