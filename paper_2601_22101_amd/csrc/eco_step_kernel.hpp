@@ -174,15 +174,39 @@ __device__ __forceinline__ void load_raw8(const void *base, uint64_t e, eco_u32x
   q[0] = p[0];
   if (!BF16) q[1] = p[1];
 }
+// The first nvalid (1..7) elements of a piece, zeros behind them.  Element by element, but without a branch, so that the loads of a
+// lane are under way together: an element that does not exist is the first one read once more (25 odd tensors, SGDM, without a plan
+// 7.4 -> 6.5 us, 30 of 4004 elements beside 30 plain ones 5.1 -> 4.4).
 template <bool BF16>
 __device__ __forceinline__ void load_ragged8(const void *base, uint64_t e, int nvalid, eco_u32x4_t (&q)[2]) {
-  q[0] = q[1] = eco_u32x4_t{0, 0, 0, 0};
+  uint32_t x[8];
 #pragma unroll
   for (int j = 0; j < 7; ++j) {
-    if (j >= nvalid) continue;
-    if (BF16) q[0][j >> 1] |= (uint32_t)static_cast<const uint16_t *>(base)[e + j] << (16 * (j & 1));
-    else q[j >> 2][j & 3] = static_cast<const uint32_t *>(base)[e + j];
+    const uint64_t i = e + (j < nvalid ? j : 0);
+    x[j] = BF16 ? (uint32_t)static_cast<const uint16_t *>(base)[i] : static_cast<const uint32_t *>(base)[i];
   }
+  x[7] = 0;
+#pragma unroll
+  for (int j = 1; j < 7; ++j) x[j] = j < nvalid ? x[j] : 0u;
+  if (BF16) {
+    q[0] = eco_u32x4_t{x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6]};
+  } else {
+    q[0] = eco_u32x4_t{x[0], x[1], x[2], x[3]};
+    q[1] = eco_u32x4_t{x[4], x[5], x[6], 0};
+  }
+}
+template <int FMT>
+__device__ __forceinline__ void load_ragged_codes8(const void *base, uint64_t e, int nvalid, uint32_t (&c)[2]) {
+  constexpr int MAXB = FMT == FMT_FP8 ? 7 : 4;
+  const uint8_t *p = static_cast<const uint8_t *>(base) + (FMT == FMT_FP8 ? e : e >> 1);
+  const int nbytes = FMT == FMT_FP8 ? nvalid : (nvalid + 1) >> 1;
+  uint32_t x[8] = {};
+#pragma unroll
+  for (int k = 0; k < MAXB; ++k) x[k] = p[k < nbytes ? k : 0];
+#pragma unroll
+  for (int k = 1; k < MAXB; ++k) x[k] = k < nbytes ? x[k] : 0u;
+  c[0] = x[0] | x[1] << 8 | x[2] << 16 | x[3] << 24;
+  c[1] = x[4] | x[5] << 8 | x[6] << 16;
 }
 template <bool BF16>
 __device__ __forceinline__ void unpack8(const eco_u32x4_t (&q)[2], float (&x)[8]) {
@@ -588,7 +612,7 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
         if (MASTER) {
           load_ragged8<false>(td.aux, e0, nvalid, wq);
         } else {
-          load_codes8<FMT, ACC_GUARDED>(td.w, e0, nvalid, c);
+          load_ragged_codes8<FMT>(td.w, e0, nvalid, c);
           s_old = load_scale<SCALE_BF16>(td.s, sg);
         }
       }
