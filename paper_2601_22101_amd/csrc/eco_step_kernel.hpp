@@ -46,17 +46,6 @@ __device__ __forceinline__ bool use_vector(int nvalid) {
   return ACC == ACC_FULL || ((ACC == ACC_LANE || ACC == ACC_WHOLE) && nvalid == 8);
 }
 
-// The first nvalid (1..8) elements at p, zeros behind them: without a branch, so that the loads are under way together; an element
-// that does not exist is the first one read once more (51 tensors of 3425 and two of 87 345 elements with one scale each, whose tails
-// are launches of one lane, 20.5 us with a branch around each load, 19.7 so).
-template <class T, int N>
-__device__ __forceinline__ void load_first(const T *p, int nvalid, uint32_t (&x)[N]) {
-#pragma unroll
-  for (int j = 0; j < N; ++j) x[j] = (uint32_t)p[j < nvalid ? j : 0];
-#pragma unroll
-  for (int j = 1; j < N; ++j) x[j] = j < nvalid ? x[j] : 0u;
-}
-
 template <int ACC>
 __device__ __forceinline__ void load_f32x8(const float *p, int nvalid, float (&out)[8]) {
   if (use_vector<ACC>(nvalid)) {
@@ -65,10 +54,8 @@ __device__ __forceinline__ void load_f32x8(const float *p, int nvalid, float (&o
     out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
     out[4] = b.x; out[5] = b.y; out[6] = b.z; out[7] = b.w;
   } else {
-    uint32_t x[8] = {};
-    if (ACC != ACC_WHOLE && nvalid > 0) load_first(reinterpret_cast<const uint32_t *>(p), nvalid, x);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) out[j] = u2f(x[j]);
+    for (int j = 0; j < 8; ++j) out[j] = ACC != ACC_WHOLE && j < nvalid ? p[j] : 0.0f;
   }
 }
 
@@ -79,10 +66,8 @@ __device__ __forceinline__ void load_bf16x8(const uint16_t *p, int nvalid, float
     out[0] = bf16_lo(q.x); out[1] = bf16_hi(q.x); out[2] = bf16_lo(q.y); out[3] = bf16_hi(q.y);
     out[4] = bf16_lo(q.z); out[5] = bf16_hi(q.z); out[6] = bf16_lo(q.w); out[7] = bf16_hi(q.w);
   } else {
-    uint32_t x[8] = {};
-    if (ACC != ACC_WHOLE && nvalid > 0) load_first(p, nvalid, x);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) out[j] = u2f(x[j] << 16);
+    for (int j = 0; j < 8; ++j) out[j] = ACC != ACC_WHOLE && j < nvalid ? u2f((uint32_t)p[j] << 16) : 0.0f;
   }
 }
 
@@ -149,11 +134,12 @@ __device__ __forceinline__ void load_codes8(const void *base, uint64_t e0, int n
       c[0] = *reinterpret_cast<const uint32_t *>(p); c[1] = 0;
     }
   } else {
+    c[0] = 0; c[1] = 0;
+    const int nbytes = FMT == FMT_FP8 ? nvalid : (nvalid + 1) >> 1;
     constexpr int MAXB = FMT == FMT_FP8 ? 8 : 4;
-    uint32_t x[MAXB] = {};
-    if (ACC != ACC_WHOLE && nvalid > 0) load_first(p, FMT == FMT_FP8 ? nvalid : (nvalid + 1) >> 1, x);
-    c[0] = x[0] | x[1] << 8 | x[2] << 16 | x[3] << 24;
-    c[1] = MAXB == 8 ? x[4 % MAXB] | x[5 % MAXB] << 8 | x[6 % MAXB] << 16 | x[7 % MAXB] << 24 : 0;
+#pragma unroll
+    for (int k = 0; k < MAXB; ++k)
+      if (ACC != ACC_WHOLE && k < nbytes) c[k >> 2] |= (uint32_t)p[k] << (8 * (k & 3));
   }
 }
 
@@ -193,15 +179,34 @@ __device__ __forceinline__ void load_raw8(const void *base, uint64_t e, eco_u32x
 // 7.4 -> 6.5 us, 30 of 4004 elements beside 30 plain ones 5.1 -> 4.4).
 template <bool BF16>
 __device__ __forceinline__ void load_ragged8(const void *base, uint64_t e, int nvalid, eco_u32x4_t (&q)[2]) {
-  uint32_t x[7];
-  if (BF16) load_first(static_cast<const uint16_t *>(base) + e, nvalid, x);
-  else load_first(static_cast<const uint32_t *>(base) + e, nvalid, x);
+  uint32_t x[8];
+#pragma unroll
+  for (int j = 0; j < 7; ++j) {
+    const uint64_t i = e + (j < nvalid ? j : 0);
+    x[j] = BF16 ? (uint32_t)static_cast<const uint16_t *>(base)[i] : static_cast<const uint32_t *>(base)[i];
+  }
+  x[7] = 0;
+#pragma unroll
+  for (int j = 1; j < 7; ++j) x[j] = j < nvalid ? x[j] : 0u;
   if (BF16) {
     q[0] = eco_u32x4_t{x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6]};
   } else {
     q[0] = eco_u32x4_t{x[0], x[1], x[2], x[3]};
     q[1] = eco_u32x4_t{x[4], x[5], x[6], 0};
   }
+}
+template <int FMT>
+__device__ __forceinline__ void load_ragged_codes8(const void *base, uint64_t e, int nvalid, uint32_t (&c)[2]) {
+  constexpr int MAXB = FMT == FMT_FP8 ? 7 : 4;
+  const uint8_t *p = static_cast<const uint8_t *>(base) + (FMT == FMT_FP8 ? e : e >> 1);
+  const int nbytes = FMT == FMT_FP8 ? nvalid : (nvalid + 1) >> 1;
+  uint32_t x[8] = {};
+#pragma unroll
+  for (int k = 0; k < MAXB; ++k) x[k] = p[k < nbytes ? k : 0];
+#pragma unroll
+  for (int k = 1; k < MAXB; ++k) x[k] = k < nbytes ? x[k] : 0u;
+  c[0] = x[0] | x[1] << 8 | x[2] << 16 | x[3] << 24;
+  c[1] = x[4] | x[5] << 8 | x[6] << 16;
 }
 template <bool BF16>
 __device__ __forceinline__ void unpack8(const eco_u32x4_t (&q)[2], float (&x)[8]) {
@@ -607,7 +612,7 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
         if (MASTER) {
           load_ragged8<false>(td.aux, e0, nvalid, wq);
         } else {
-          load_codes8<FMT, ACC_GUARDED>(td.w, e0, nvalid, c);
+          load_ragged_codes8<FMT>(td.w, e0, nvalid, c);
           s_old = load_scale<SCALE_BF16>(td.s, sg);
         }
       }
