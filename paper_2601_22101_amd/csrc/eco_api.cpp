@@ -463,7 +463,7 @@ eco::TensorDesc describe_in_list(const eco_tensor_t &t, const eco_hparams_t *lay
   return describe(t, layout, p, first_wg);
 }
 
-// The short-list arguments of up to SMALL_TENSORS tensors.
+// The arguments by value of up to SMALL_TENSORS tensors.
 struct SmallItem { const eco_tensor_t *t; eco::Placement p; };
 void make_small(const SmallItem *items, size_t n, const eco_hparams_t *layout, eco::SmallArgs *sa, uint64_t *wgs, unsigned *waves) {
   unsigned nw = 1;

@@ -165,7 +165,7 @@ struct StepLaunch {
   uint32_t num_wide[MAX_WIDE_WAVES + 1];
   unsigned resident_wgs;           // workgroups of the one-pass tensor-wise kernel: one per compute unit
   int extra_in;                    // which launch the one-wave units ride in: 0 the full-tile one, n the wide groups of n waves
-  const SmallArgs *small;          // if set, one launch of the short-list kernel,
+  const SmallArgs *small;          // if set, one launch of eco_step_small_kernel (arguments by value),
   uint64_t list_wgs;               // or if not 0, of the list kernel,
   unsigned list_waves;             //   with workgroups of so many waves, stands for all of the above but the tensor-wise passes
 };

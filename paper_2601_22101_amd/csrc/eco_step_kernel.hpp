@@ -770,8 +770,8 @@ __device__ __forceinline__ void plain_lane(const StepArgs &a, const TensorDesc &
 }
 
 // ------------------------------------------------------------------ kernels
-// One unit of a list of one-wave units (UNIT_*), `lane` in 0..63.  Per-lane guards throughout: what is left beside the
-// full tiles is little, and one body serves whole and partial tiles.
+// One unit of a list of one-wave units (UNIT_*), `lane` in 0..63: what is left beside the full tiles.  One body serves whole
+// and partial tiles.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
 __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDesc &td, uint32_t unit, uint32_t lane) {
   if (td.kind == UNIT_PLAIN_BF16 || td.kind == UNIT_PLAIN_FP32) {

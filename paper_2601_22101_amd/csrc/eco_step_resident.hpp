@@ -32,7 +32,7 @@
 // tensors of 1408 x 2048: FP8, fp32 state 1964 -> 1430 us; INT4, bf16 state 1112 -> 872 us; three tensors of 40 000
 // elements 14.2 -> 12.8 us; where a list is too short for it or has company that costs launches, see one_pass_pays.  What
 // it took: 12 waves of 168 registers rather than 8 of 256 (INT4 1290 -> 1000 us), no memory access inside a branch (1000 ->
-// 940), an event's contributions half a turn before the result is wanted (940 -> 890).  17 of the 80 variants, among them
+// 940), an event's contributions half a turn before the result is wanted (940 -> 890).  19 of the 80 variants, among them
 // Adam with bf16 state and stochastic rounding, do not quite fit 168 registers and keep 2 to 11 values in scratch memory.
 #pragma once
 #include "eco_step_kernel.hpp"
