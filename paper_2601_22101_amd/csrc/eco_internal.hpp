@@ -414,6 +414,14 @@ inline uint32_t lds_for_workgroups(unsigned k) {
   const uint32_t bytes = 163840u / k / 1280u * 1280u - 256u;
   return bytes < 65536u ? bytes : 65536u;
 }
+// The nth piece of `pieces` where a second pass takes what a first pass left in the caches, the last pieces first.  The hardware
+// hands workgroups to the eight XCDs in turn and each XCD has an L2 of its own, so a piece keeps its place among eight: the XCD that read
+// it in the first pass reads it in the second.
+constexpr uint32_t backwards_on_the_same_xcd(uint32_t nth, uint32_t pieces) {
+  constexpr uint32_t XCDS = 8;
+  const uint32_t whole = pieces / XCDS * XCDS;
+  return nth < whole ? whole - XCDS - nth / XCDS * XCDS + nth % XCDS : nth;
+}
 inline int log2_exact(uint64_t x) {
   for (int s = 0; s < 64; ++s)
     if ((1ull << s) == x) return s;

@@ -942,9 +942,11 @@ __global__ __launch_bounds__(1024) void eco_step_list_kernel(const uint32_t *tab
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int RED>
 __global__ __launch_bounds__(WG_THREADS) void eco_step_tensorwise_kernel(const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);      // as in eco_step_kernel: loading waves first
-  // Pass 2 goes through the tiles backwards: the cache before HBM still holds the last ones of pass 1 (us, forwards / backwards: 210 M
-  // elements in INT4 with bf16 state 628 / 605, eight tensors of 12 M 307 / 286, FP8 with fp32 state 8 M 51.2 / 49.4, two of 60 M 668 / 653).
-  const uint32_t nth = blockIdx.x + a.unit_base, unit = RED == RED_SLOT ? a.num_tw_tiles - 1 - nth : nth;
+  // Pass 2 goes through the tiles backwards, each on the XCD that has it in its L2 from pass 1 (us, forwards / backwards by single tiles,
+  // which takes every tile to another XCD / this: FP8 with fp32 state 1 M elements 14.7 / 17.6 / 14.4, 4 M 32.6 / 31.4 / 27.7, 8 M 51.7 /
+  // 49.8 / 45.4, two of 60 M 660 / 639 / 634; INT4 with bf16 state 2.2 M in seven tensors 16.0 / 20.0 / 16.1, 7 M 34.2 / 34.1 / 30.1, 210 M
+  // 622 / 600 / 599).
+  const uint32_t nth = blockIdx.x + a.unit_base, unit = RED == RED_SLOT ? backwards_on_the_same_xcd(nth, a.num_tw_tiles) : nth;
   const TensorDesc td = load_tensor_desc(a, load_table(a.tw_tile_tensor, unit));
   const uint64_t tile_off = (uint64_t)(unit - td.first_unit) * TILE_ELEMS;
   const uint64_t e0 = tile_off + (uint64_t)threadIdx.x * ELEMS_PER_LANE;

@@ -2,6 +2,7 @@
 // steps it, how many rows a workgroup of the wide-group kernel takes, and what one helper launch can hold.
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
 #include "eco_internal.hpp"
 
@@ -66,6 +67,16 @@ int main() {
         covered += k;
       }
       CHECK(covered == f.workgroups && covered * threads * ELEMS_PER_LANE >= n && (covered - 1) * threads * ELEMS_PER_LANE < n);
+    }
+  }
+  // the second tensor-wise pass: every tile once, on the XCD of the first pass (workgroups go to eight in turn), the last ones first
+  for (uint32_t n : {1u, 7u, 8u, 9u, 15u, 16u, 17u, 4099u}) {
+    std::vector<bool> seen(n, false);
+    for (uint32_t i = 0; i < n; ++i) {
+      const uint32_t u = backwards_on_the_same_xcd(i, n);
+      CHECK(u < n && !seen[u] && u % 8 == i % 8);
+      CHECK(i < 8 || i >= n / 8 * 8 || backwards_on_the_same_xcd(i - 8, n) == u + 8);
+      seen[u] = true;
     }
   }
   // the finishing kernel of the one-pass tensor-wise step has enough workgroups for every slab it may be left with
