@@ -910,10 +910,12 @@ __device__ __forceinline__ void step_list_workgroup(const StepArgs &a, const Ten
       u < per_wg ? (int)(u * rows + row) : 0);
 }
 
+// 64 registers at most, for eight waves a SIMD: with 65, FP8 with Adam, a workgroup of nine waves was resident twice and not three times
+// (us, 65 / 64: rows of 576, 5.5 M elements with fp32 state 26.6 / 24.3, with bf16 state 22.6 / 19.7).
 // With the descriptors in the kernel arguments (no table in device memory); a workgroup finds its tensor by comparing its number
 // with the tensors' first ones, a lane each.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(1024) void eco_step_small_kernel(const SmallArgs args) {
+__global__ __launch_bounds__(1024, 8) void eco_step_small_kernel(const SmallArgs args) {
   const ECO_CONST_AS SmallArgs *ka = (const ECO_CONST_AS SmallArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   __builtin_amdgcn_s_setprio(3);
   const uint32_t lane = threadIdx.x & 63;
@@ -926,7 +928,7 @@ __global__ __launch_bounds__(1024) void eco_step_small_kernel(const SmallArgs ar
 // With a plan's tables: any number of tensors (415 of them in rows of 984, 3024, 1120 and 4856 elements, us: a launch for each number of
 // waves 19.7, this 7.9; 142 in rows of 2304 and 108 in rows of 512 20.3 / 12.3).
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(1024) void eco_step_list_kernel(const uint32_t *table, const TensorDesc *tensors, const StepArgs a) {
+__global__ __launch_bounds__(1024, 8) void eco_step_list_kernel(const uint32_t *table, const TensorDesc *tensors, const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);
   const TensorDesc td = load_tensor_desc(tensors, load_table(table, blockIdx.x));
   step_list_workgroup<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, blockIdx.x + a.unit_base - td.first_unit);

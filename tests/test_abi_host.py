@@ -348,6 +348,30 @@ def test_what_a_step_launches(eco, tmp_path):
     assert "routes ok" in run_with_stand_in_runtime(tmp_path, "routes_host")
 
 
+def kernel_metadata(tmp_path):
+    """{kernel's name: its entry of the code objects' metadata} of the built library."""
+    import shutil
+    import subprocess
+    import yaml
+    lib = os.environ.get("ECO_LIB_PATH") or os.path.join(ROOT, "paper_2601_22101_amd", "libeco.so")
+    llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+    shutil.copy(lib, tmp_path / "lib.so")
+    subprocess.run([os.path.join(llvm, "llvm-objdump"), "--offloading", "lib.so"], cwd=tmp_path, stdout=subprocess.DEVNULL, check=True)
+    kernels = {}
+    for obj in sorted(tmp_path.glob("lib.so.*gfx950*")):
+        text = subprocess.run([os.path.join(llvm, "llvm-readelf"), "--notes", str(obj)], stdout=subprocess.PIPE, text=True, check=True).stdout
+        doc = text[text.index("---"):]
+        kernels.update({k[".name"]: k for k in yaml.load(doc[:doc.index("...")], Loader=getattr(yaml, "CSafeLoader", yaml.SafeLoader))["amdhsa.kernels"]})
+    return kernels
+
+
+def test_list_kernels_leave_room_for_eight_waves_a_simd(tmp_path):
+    """64 registers of a SIMD's 512: with 65 a workgroup of nine waves is resident twice and not three times."""
+    lists = {n: k for n, k in kernel_metadata(tmp_path).items() if "eco_step_list_kernel" in n or "eco_step_small_kernel" in n}
+    assert len(lists) == 160
+    assert {n: k[".vgpr_count"] for n, k in lists.items() if k[".vgpr_count"] > 64 or k[".private_segment_fixed_size"]} == {}
+
+
 def test_the_short_division_is_correctly_rounded_but_for_pairs_that_the_device_settles(tmp_path):
     """tests/native/division_proof.c: of all 2^46 pairs of significands only those near the middle between two floats can
     fail, and of these only two do for some reciprocal estimate within its error; test_gpu_parity.py runs those."""
