@@ -811,16 +811,17 @@ __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDe
 // what is derived from them stay live across it and no longer fit the scalar registers.)
 // What a wave's way to its data begins with -- the launch's table and the descriptors -- are arguments of their own, in front, here and in
 // the kernels below: they are in scalar registers when the wave starts (the build asks for that; members of a struct are not), one
-// memory access fewer in a chain of four (one matrix of 1 M elements 5.2 -> 5.0 us, of 4 M 16.9 -> 16.7).  `table` also covers the
-// one-wave units, whose list lies behind the tiles'.
+// memory access fewer in a chain of four (one matrix of 1 M elements 5.2 -> 5.0 us, of 4 M 16.9 -> 16.7).  As integers: for every argument
+// of pointer type the runtime looks up the allocation behind it, 0.03 us of a call each.  `table` also covers the one-wave units, whose list
+// lies behind the tiles'.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint32_t *table, const TensorDesc *tensors, const StepArgs a) {
+__global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint64_t table, const uint64_t tensors, const StepArgs a) {
   // A wave that has not issued its loads yet goes first: its address arithmetic and load instructions
   // are not queued behind the arithmetic of the waves that already have their data (the priority is
   // dropped again in step_lane, once the loads are issued).  Measured: +0.3 % and a flatter optimum
   // over the occupancy cap.
   __builtin_amdgcn_s_setprio(3);
-  const TensorDesc td = load_tensor_desc(tensors, load_table(table, blockIdx.x));
+  const TensorDesc td = load_tensor_desc((const TensorDesc *)tensors, load_table((const uint32_t *)table, blockIdx.x));
   const uint32_t tile = blockIdx.x + a.unit_base;
   if (tile < a.num_tiles) {
     const uint64_t e0 = (uint64_t)(tile - td.first_unit) * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
@@ -838,7 +839,7 @@ __global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint32_t *ta
 // to a wave (a variant of its own: with those paths in the kernel the groups run 3.6 % slower, 3 460 -> 3 590 us over
 // Gemma-3-1B shapes, so a long launch leaves them to another one).
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, bool EXTRA>
-__global__ __launch_bounds__(1024) void eco_step_wide_kernel(const uint32_t *table, const TensorDesc *tensors, const StepArgs a) {
+__global__ __launch_bounds__(1024) void eco_step_wide_kernel(const uint64_t table, const uint64_t tensors, const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);      // as in eco_step_kernel: loading waves first
   const uint32_t unit = blockIdx.x + a.unit_base;
   if (EXTRA && unit >= a.num_units) {
@@ -849,7 +850,7 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const uint32_t *tab
     }
     return;
   }
-  const TensorDesc td = load_tensor_desc(tensors, load_table(table, blockIdx.x));
+  const TensorDesc td = load_tensor_desc((const TensorDesc *)tensors, load_table((const uint32_t *)table, blockIdx.x));
   const uint32_t rows = td.slot;
   const uint64_t grp = (uint64_t)(unit - td.first_unit) * rows;       // the workgroup's first group
   const uint64_t start = grp * td.group_size;
@@ -910,8 +911,8 @@ __device__ __forceinline__ void step_list_workgroup(const StepArgs &a, const Ten
       u < per_wg ? (int)(u * rows + row) : 0);
 }
 
-// 64 registers at most, for eight waves a SIMD: with 65, FP8 with Adam, a workgroup of nine waves was resident twice and not three times
-// (us, 65 / 64: rows of 576, 5.5 M elements with fp32 state 26.6 / 24.3, with bf16 state 22.6 / 19.7).
+// 64 registers at most, for eight waves a SIMD: with 65, as FP8 with Adam had, seven (us, 65 / 64: rows of 576, 5.5 M elements with fp32
+// state 26.6 / 24.3, with bf16 state 22.6 / 19.7).
 // With the descriptors in the kernel arguments (no table in device memory); a workgroup finds its tensor by comparing its number
 // with the tensors' first ones, a lane each.
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
@@ -928,9 +929,9 @@ __global__ __launch_bounds__(1024, 8) void eco_step_small_kernel(const SmallArgs
 // With a plan's tables: any number of tensors (415 of them in rows of 984, 3024, 1120 and 4856 elements, us: a launch for each number of
 // waves 19.7, this 7.9; 142 in rows of 2304 and 108 in rows of 512 20.3 / 12.3).
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
-__global__ __launch_bounds__(1024, 8) void eco_step_list_kernel(const uint32_t *table, const TensorDesc *tensors, const StepArgs a) {
+__global__ __launch_bounds__(1024, 8) void eco_step_list_kernel(const uint64_t table, const uint64_t tensors, const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);
-  const TensorDesc td = load_tensor_desc(tensors, load_table(table, blockIdx.x));
+  const TensorDesc td = load_tensor_desc((const TensorDesc *)tensors, load_table((const uint32_t *)table, blockIdx.x));
   step_list_workgroup<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, blockIdx.x + a.unit_base - td.first_unit);
 }
 
@@ -1031,7 +1032,8 @@ hipError_t launch_listed_in_chunks(Kernel kernel, const uint32_t *table, uint64_
   for (uint64_t base = 0; base < units; base += per_launch) {
     const uint64_t n = units - base < per_launch ? units - base : per_launch;
     args.unit_base = static_cast<uint32_t>(base);
-    ECO_LAUNCH_CHECKED(kernel, dim3(static_cast<unsigned>(n)), dim3(block), lds, stream, table + base, args.tensors, args);
+    ECO_LAUNCH_CHECKED(kernel, dim3(static_cast<unsigned>(n)), dim3(block), lds, stream, reinterpret_cast<uint64_t>(table + base),
+                       reinterpret_cast<uint64_t>(args.tensors), args);
   }
   return hipSuccess;
 }

@@ -366,10 +366,17 @@ def kernel_metadata(tmp_path):
 
 
 def test_list_kernels_leave_room_for_eight_waves_a_simd(tmp_path):
-    """64 registers of a SIMD's 512: with 65 a workgroup of nine waves is resident twice and not three times."""
+    """64 registers of a SIMD's 512 each; with 65 it holds seven."""
     lists = {n: k for n, k in kernel_metadata(tmp_path).items() if "eco_step_list_kernel" in n or "eco_step_small_kernel" in n}
     assert len(lists) == 160
     assert {n: k[".vgpr_count"] for n, k in lists.items() if k[".vgpr_count"] > 64 or k[".private_segment_fixed_size"]} == {}
+
+
+def test_step_kernels_take_addresses_as_integers(tmp_path):
+    """The runtime looks up the allocation behind every argument of pointer type, host time that a step would pay for each."""
+    step = {n: k for n, k in kernel_metadata(tmp_path).items() if "eco_step_" in n}
+    assert len(step) > 600
+    assert [n for n, k in step.items() if any(a[".value_kind"] != "by_value" for a in k[".args"])] == []
 
 
 def test_the_short_division_is_correctly_rounded_but_for_pairs_that_the_device_settles(tmp_path):
