@@ -292,13 +292,14 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? eco::lds_for_workgroups(resident) : lds_for_waves(waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
     const uint64_t units = sl->num_wide[nw];
+    if (!units) continue;
     const bool idle = load[nw].idle > units / 8, adam32 = kv.algo == eco::ALGO_ADAM && !kv.state_bf16;
     // Workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too (4 M elements 9.7 against 10.2 us); master weights
     // with fp32 state in full rows, and Adam with fp32 state in rows with idle lanes, from 96 MB on (us, with / without: rows of 1000 88 MB
     // 28.8 / 29.5, 33 MB 12.1 / 10.7; 1800 28.4 / 29.2, 12.1 / 11.4); the others from 384 MB on (master weights, rows of 1152, 300 MB 89 / 87; SGDM,
     // rows of 1000, 315 MB 91 / 89).
     const bool worth = hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && (idle ? adam32 : kv.algo == eco::ALGO_ADAM_MASTER));
-    const unsigned k = !units || !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, units, load[nw].elements)
+    const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, units, load[nw].elements)
                                                    : eco::wide_workgroups(kv, nw, units, load[nw].idle);
     // Adam with fp32 state in full rows has the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
     // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 2048: 467
