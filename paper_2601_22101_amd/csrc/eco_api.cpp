@@ -456,8 +456,9 @@ int home_of_plain(const uint64_t (&tensors)[4], const uint64_t (&entries)[4]) {
 // A tensor in a list launch (step_list_workgroup) of workgroups of nw waves: the waves of its units, and its workgroups.
 unsigned unit_waves(const eco::Placement &p) { return p.kind == eco::UNIT_WIDE ? static_cast<unsigned>(p.list - eco::LIST_WIDE1 + 1) : 1u; }
 uint64_t list_workgroups(const eco::Placement &p, unsigned nw) {
-  const uint64_t units = p.units + (p.tail ? 1 : 0), per_wg = nw / unit_waves(p);
-  return (units + per_wg - 1) / per_wg;
+  const uint64_t units = p.units + (p.tail ? 1 : 0);
+  const unsigned waves = unit_waves(p), per_wg = waves == 1 ? nw : nw / waves;      // (without the divisions that can be spared)
+  return per_wg == 1 ? units : (units + per_wg - 1) / per_wg;
 }
 eco::TensorDesc describe_in_list(const eco_tensor_t &t, const eco_hparams_t *layout, eco::Placement p, uint64_t first_wg) {
   p.tail = false;                                       // whole and partial tiles alike there
@@ -838,21 +839,26 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   // pass 1: validate, place, count the entries of every launch list
   constexpr int L_TW_TENSORS = eco::LIST_COUNT, L_COUNT = eco::LIST_COUNT + 1;
   uint64_t count[4][L_COUNT] = {{0}}, tensors_of[4] = {0}, entries_of[4] = {0}, most_tw_tiles[4] = {0};
-  uint64_t total = 0, elements = 0;
+  uint64_t total = 0, elements = 0, bytes = 0;
   const eco::StateLayout state = state_layout(hp);
-  const uint64_t bytes = bytes_of(tensors, n, state);
   WideLoads load[4] = {};
-  // The placement of a tensor that check_tensor has let through; where the static tables do not hold the units of the step's own
-  // grouping of rows, with the one that their limit is stated in.
-  eco::StepRows rows = {state, HbmBound(bytes).half};
+  // The placement of a tensor that check_tensor has let through: rows first as the limit on launch tables counts them.
+  eco::StepRows rows = {state, false};
   const auto place = [&](const eco_tensor_t &t) {
     const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
     const uint64_t gsz = t.group_size ? t.group_size : hp->block_size;
     return eco::place_tensor(t.numel, gsz, quantized ? eco::classify_group(gsz, t.numel) : eco::GROUP_BLOCK, quantized, t.fmt, eco::TILE_ELEMS, 0,
                              &rows);
   };
-  bool tensorwise = false;
   uint64_t units = 0;
+  const auto count_wide = [&](const eco_tensor_t &t, const eco::Placement &p) {
+    Lists::WideLoad &w = load[t.fmt][p.list - eco::LIST_WIDE1 + 1];
+    count[t.fmt][p.list] += p.units;
+    units += p.units;
+    w.idle += p.idle ? p.units : 0;
+    w.elements += t.numel;
+  };
+  bool tensorwise = false, wide = false;
   for (size_t i = 0; i < n; ++i) {
     const int f = tensors[i].fmt;
     uint64_t gsz = 0;
@@ -864,18 +870,19 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     tensors_of[f] += 1;
     entries_of[f] += p.entries;
     elements += tensors[i].numel;
+    bytes += eco::array_bytes(tensors[i].numel, f, state);
     total += p.entries;
     if (total > MAX_UNITS)
       return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: more than %u launch-table entries (512-element tiles, or scale "
                   "groups wider than 512): the static scratch does not hold them (use a plan)", MAX_UNITS);
+    if (p.kind == eco::UNIT_WIDE) {
+      wide = true;
+      count_wide(tensors[i], p);
+      continue;
+    }
     count[f][p.list] += p.units;
     units += p.units;
     if (p.list == eco::LIST_EXTRA) load[f][0].elements += tensors[i].numel;
-    if (p.kind == eco::UNIT_WIDE) {
-      Lists::WideLoad &w = load[f][p.list - eco::LIST_WIDE1 + 1];
-      w.idle += p.idle ? p.units : 0;
-      w.elements += tensors[i].numel;
-    }
     if (p.tail) { count[f][eco::LIST_EXTRA] += 1; units += 1; }
     if (p.list == eco::LIST_TW_TILES) {
       tensorwise = true;
@@ -884,21 +891,22 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
     }
   }
-  if (units > MAX_UNITS) {               // the wide lists again, as the limit counts them
-    rows.own_rows = false;
+  // The wide lists again with the step's own grouping of rows, where it is the better one (see bytes_of) and the static tables hold
+  // its units; back to the other one if they do not.
+  const bool own = wide && HbmBound(bytes).half;
+  for (int round = 0; own && round < 2; ++round) {
+    rows.own_rows = round == 0;
     for (int f = 0; f < 4; ++f)
       for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
+        units -= count[f][eco::LIST_WIDE1 + nw - 1];
         count[f][eco::LIST_WIDE1 + nw - 1] = 0;
         load[f][nw] = Lists::WideLoad{0, 0};
       }
     for (size_t i = 0; i < n; ++i) {
       const eco::Placement p = place(tensors[i]);
-      if (p.kind != eco::UNIT_WIDE) continue;
-      Lists::WideLoad &w = load[tensors[i].fmt][p.list - eco::LIST_WIDE1 + 1];
-      count[tensors[i].fmt][p.list] += p.units;
-      w.idle += p.idle ? p.units : 0;
-      w.elements += tensors[i].numel;
+      if (p.kind == eco::UNIT_WIDE) count_wide(tensors[i], p);
     }
+    if (units <= MAX_UNITS) break;
   }
   const int plain_home = home_of_plain(tensors_of, entries_of);
   const auto format_of = [&](size_t i) {
@@ -930,8 +938,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
         size_t held = 0;
         for (size_t i = 0; i <= n && fits; ++i) {
           if (i < n && format_of(i) == f) {
-            items[held].t = &tensors[i];
-            items[held++].p = place(tensors[i]);
+            ::new (&items[held++]) SmallItem{&tensors[i], place(tensors[i])};      // (built where it lies: a copy is 5 ns)
           }
           if (!held || (held < static_cast<size_t>(eco::SMALL_TENSORS) && i < n)) continue;
           std::memset(&sl, 0, sizeof sl);
