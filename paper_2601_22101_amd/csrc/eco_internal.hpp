@@ -409,9 +409,9 @@ inline unsigned unit_workgroups(const KernelVariant &kv, bool from_hbm, uint64_t
   }
 }
 // The dynamic LDS that keeps k workgroups resident per compute unit (0: no request); LDS is handed out in pieces of 1280
-// bytes, and a workgroup has up to 128 of its own beside it.
+// bytes, and a workgroup has up to 128 of its own beside it.  A compute unit holds 32 waves, so 32 workgroups and more are no cap.
 inline uint32_t lds_for_workgroups(unsigned k) {
-  if (k == 0) return 0;
+  if (k == 0 || k >= 32) return 0;
   const uint32_t bytes = 163840u / k / 1280u * 1280u - 256u;
   return bytes < 65536u ? bytes : 65536u;
 }

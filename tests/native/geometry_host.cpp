@@ -89,6 +89,12 @@ int main() {
       }
     }
   }
+  // an LDS request that the hardware's LDS holds k times, and none where k is no less than the waves of a compute unit
+  for (unsigned k = 0; k <= 2000; ++k) {
+    const uint32_t lds = lds_for_workgroups(k);
+    CHECK(k == 0 || k >= 32 ? lds == 0 : lds > 0 && lds <= 65536 && (lds + 128 + 1279) / 1280 * 1280 * k <= 163840);
+    if (k > 2 && k < 32) CHECK((lds + 1279) / 1280 * 1280 * (k + k / 4 + 1) > 163840);
+  }
   // occupancy caps of the wide-group kernel: none where rows leave lanes idle, at least 20 waves where bf16 state is capped,
   // and a request that the hardware's LDS holds that many times
   for (int algo : {ALGO_ADAM, ALGO_SGDM, ALGO_SGDM_EXACT, ALGO_ADAM_MASTER, ALGO_SGDM_MASTER}) {
