@@ -665,7 +665,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
         }
       }
       list.insert(list.end(), static_cast<size_t>(p.units), idx);
-      if (p.tail) g.extra.push_back(idx);
+      if (p.tail) {
+        g.extra.push_back(idx);
+        g.load[0].elements += t.numel % eco::TILE_ELEMS;
+      }
       g.tensors += 1;
       descs.push_back(d);
     }
@@ -883,7 +886,11 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     count[f][p.list] += p.units;
     units += p.units;
     if (p.list == eco::LIST_EXTRA) load[f][0].elements += tensors[i].numel;
-    if (p.tail) { count[f][eco::LIST_EXTRA] += 1; units += 1; }
+    if (p.tail) {
+      count[f][eco::LIST_EXTRA] += 1;
+      units += 1;
+      load[f][0].elements += tensors[i].numel % eco::TILE_ELEMS;
+    }
     if (p.list == eco::LIST_TW_TILES) {
       tensorwise = true;
       count[f][L_TW_TENSORS] += 1;

@@ -80,6 +80,8 @@ static const Case cases[] = {
     /* one-wave units with few busy lanes beside arrays from HBM: as many waves as want to */
     {"100 norms of 32 beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 70000000}, {100, PLAIN, 1, 32}}, 5, 10},
     {"100 tensors of 40 beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 70000000}, {100, TENSOR, 1, 40}}, 5, 10},
+    /* partial last tiles are one-wave units too, and count with the lanes they keep busy */
+    {"tails and a few short rows beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 70000000}, {1, ROW, 16, 400}, {1000, 128, 1, 500}}, 5, 11},
     /* tensor-wise: two launches in one pass (three with a tail), four in two passes, and which of these are capped */
     {"three small tensors", FP8, F32, ADAM, ECO_MODE_ECO, {{3, TENSOR, 1, 40000}}, 2, 0},
     {"three small tensors with tails", FP8, F32, ADAM, ECO_MODE_ECO, {{3, TENSOR, 1, 40001}}, 4, 5},
@@ -93,7 +95,7 @@ static const Case cases[] = {
 };
 
 int main(void) {
-  static eco_tensor_t list[128];
+  static eco_tensor_t list[1024];
   int bad = 0;
   for (size_t c = 0; c < sizeof cases / sizeof *cases; ++c) {
     const Case *k = &cases[c];
