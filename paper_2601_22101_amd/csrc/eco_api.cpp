@@ -453,6 +453,19 @@ int home_of_plain(const uint64_t (&tensors)[4], const uint64_t (&entries)[4]) {
   return -1;
 }
 
+// One scale for a tensor of up to 8192 elements whose length is no multiple of 8: one group of a row or list launch, or, beside longer
+// tensors with one scale, one more tensor of their launches.  The second is a launch fewer where nothing else needs one, the first
+// less work: it wins from 1600 tiles and tensors on (us, in a launch of their own / along with one of 9000 elements: FP8 300 of 770
+// 16.8 / 14.7, 600 16.8 / 17.1, 1200 18.3 / 23.6, 200 of 2627 17.5 / 14.6, 60 of 8001 18.6 / 15.1, 120 18.9 / 20.2, 300 of 101 16.6 / 14.7, 1500
+// 17.2 / 17.8; INT4 with bf16 state 770 16.2 / 15.1, 16.3 / 16.3, 17.6 / 19.4), and where the longer ones are stepped in one pass of
+// several turns, which odd lengths cost a launch.
+constexpr uint64_t ODD_ALONG_ENTRIES = 1600;
+bool short_odd(const eco_tensor_t &t, const eco_hparams_t *layout) {
+  const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
+  return quantized && t.numel <= eco::MAX_WIDE_GROUP && t.numel % eco::ELEMS_PER_LANE != 0 &&
+         eco::classify_group(t.group_size ? t.group_size : layout->block_size, t.numel) == eco::GROUP_TENSOR;
+}
+
 // A tensor in a list launch (step_list_workgroup) of workgroups of nw waves: the waves of its units, and its workgroups.
 unsigned unit_waves(const eco::Placement &p) { return p.kind == eco::UNIT_WIDE ? static_cast<unsigned>(p.list - eco::LIST_WIDE1 + 1) : 1u; }
 uint64_t list_workgroups(const eco::Placement &p, unsigned nw) {
@@ -609,33 +622,47 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     e = hipGetDevice(&plan->device);
     if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
     plan->cus = num_compute_units();
-    // tensors with one scale that the chip can hold: one pass, if it pays for those of the format
-    const uint64_t max_slabs = std::min<uint64_t>(eco::RES_WAVES * 64, eco::RES_SLABS_PER_WG * plan->cus);
-    for (int f = 0; f < 2; ++f) {
-      uint64_t bytes = 0, slabs = 0;
-      bool tails = false, longer = false;
-      const auto in_one_pass = [&](size_t i) {
-        return eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, tensors[i].fmt, eco::RES_SLAB, max_slabs);
-      };
-      for (size_t i = 0; i < n; ++i) {
-        if (tensors[i].fmt != f || place[i].list != eco::LIST_TW_TILES) continue;
-        const eco::Placement p = in_one_pass(i);
-        if (p.list != eco::LIST_RESIDENT) { longer = true; continue; }
-        bytes += eco::array_bytes(tensors[i].numel, f, state);
-        slabs += p.units;
-        tails = tails || tensors[i].numel % eco::ELEMS_PER_LANE != 0;
-      }
-      if (!eco::one_pass_pays(state, bytes, slabs, static_cast<unsigned>(plan->cus), tails, longer)) continue;
-      for (size_t i = 0; i < n; ++i)
-        if (tensors[i].fmt == f && place[i].list == eco::LIST_TW_TILES) place[i] = in_one_pass(i);
-    }
     const int plain_home = home_of_plain(tensors_of, entries_of);
-
-    uint64_t elements[4] = {0};
     const auto home = [&](size_t i) {
       const int f = tensors[i].fmt;
       return f == ECO_FMT_FP8_E4M3 || f == ECO_FMT_INT4 || plain_home < 0 ? f : plain_home;
     };
+    // tensors with one scale that the chip can hold: one pass, if it pays for those of the format
+    const uint64_t max_slabs = std::min<uint64_t>(eco::RES_WAVES * 64, eco::RES_SLABS_PER_WG * plan->cus);
+    for (int f = 0; f < 2; ++f) {
+      uint64_t bytes = 0, slabs = 0;
+      uint64_t odd = 0;
+      bool any = false, tails = false, longer = false, listed = false;
+      const auto in_one_pass = [&](size_t i) {
+        return eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, tensors[i].fmt, eco::RES_SLAB, max_slabs);
+      };
+      const auto count = [&](size_t i) {
+        const eco::Placement p = in_one_pass(i);
+        any = true;
+        if (p.list != eco::LIST_RESIDENT) { longer = true; return; }
+        bytes += eco::array_bytes(tensors[i].numel, f, state);
+        slabs += p.units;
+        tails = tails || tensors[i].numel % eco::ELEMS_PER_LANE != 0;
+      };
+      for (size_t i = 0; i < n; ++i) {
+        if (home(i) != f) continue;
+        if (place[i].list == eco::LIST_TW_TILES) count(i);
+        else if (short_odd(tensors[i], layout)) odd += place[i].entries;
+        else listed = true;
+      }
+      const unsigned cus = static_cast<unsigned>(plan->cus);
+      if (any && odd && odd <= ODD_ALONG_ENTRIES && !listed && (slabs <= cus || tails || !eco::one_pass_pays(state, bytes, slabs, cus, tails, longer)))
+        for (size_t i = 0; i < n; ++i)
+          if (tensors[i].fmt == f && short_odd(tensors[i], layout)) {
+            place[i] = eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, f);
+            count(i);
+          }
+      if (!eco::one_pass_pays(state, bytes, slabs, cus, tails, longer)) continue;
+      for (size_t i = 0; i < n; ++i)
+        if (tensors[i].fmt == f && place[i].list == eco::LIST_TW_TILES) place[i] = in_one_pass(i);
+    }
+
+    uint64_t elements[4] = {0};
     descs.reserve(n);
     for (size_t i = 0; i < n; ++i) {
       const eco_tensor_t &t = tensors[i];
@@ -847,11 +874,12 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   WideLoads load[4] = {};
   // The placement of a tensor that check_tensor has let through: rows first as the limit on launch tables counts them.
   eco::StepRows rows = {state, false};
+  bool odd_along[2] = {false, false};      // see short_odd: along with the longer ones of the format
   const auto place = [&](const eco_tensor_t &t) {
     const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
     const uint64_t gsz = t.group_size ? t.group_size : hp->block_size;
-    return eco::place_tensor(t.numel, gsz, quantized ? eco::classify_group(gsz, t.numel) : eco::GROUP_BLOCK, quantized, t.fmt, eco::TILE_ELEMS, 0,
-                             &rows);
+    const int cls = quantized ? eco::classify_group(gsz, t.numel) : eco::GROUP_BLOCK;
+    return eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt, eco::TILE_ELEMS, 0, cls == eco::GROUP_TENSOR && odd_along[t.fmt] ? nullptr : &rows);
   };
   uint64_t units = 0;
   const auto count_wide = [&](const eco_tensor_t &t, const eco::Placement &p) {
@@ -861,7 +889,14 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     w.idle += p.idle ? p.units : 0;
     w.elements += t.numel;
   };
+  const auto count_tensorwise = [&](int f, const eco::Placement &p) {
+    count[f][eco::LIST_TW_TILES] += p.units;
+    count[f][L_TW_TENSORS] += 1;
+    units += p.units + 1;
+    most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
+  };
   bool tensorwise = false, wide = false;
+  uint64_t odd[4] = {0}, odd_entries[4] = {0};
   for (size_t i = 0; i < n; ++i) {
     const int f = tensors[i].fmt;
     uint64_t gsz = 0;
@@ -878,6 +913,12 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     if (total > MAX_UNITS)
       return fail(ECO_EUNSUPPORTED, "eco_step_tensors_noalloc: more than %u launch-table entries (512-element tiles, or scale "
                   "groups wider than 512): the static scratch does not hold them (use a plan)", MAX_UNITS);
+    if (p.list == eco::LIST_TW_TILES) {
+      tensorwise = true;
+      count_tensorwise(f, p);
+      continue;
+    }
+    if (cls == eco::GROUP_TENSOR) { odd[f] += 1; odd_entries[f] += p.entries; }
     if (p.kind == eco::UNIT_WIDE) {
       wide = true;
       count_wide(tensors[i], p);
@@ -891,12 +932,19 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       units += 1;
       load[f][0].elements += tensors[i].numel % eco::TILE_ELEMS;
     }
-    if (p.list == eco::LIST_TW_TILES) {
-      tensorwise = true;
-      count[f][L_TW_TENSORS] += 1;
-      units += 1;
-      most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
-    }
+  }
+  const int plain_home = home_of_plain(tensors_of, entries_of);
+  for (int f = 0; f < 2; ++f) {
+    if (!odd[f] || odd_entries[f] > ODD_ALONG_ENTRIES || !count[f][L_TW_TENSORS]) continue;
+    uint64_t listed = plain_home == f ? tensors_of[eco::FMT_BF16_PLAIN] + tensors_of[eco::FMT_FP32_ID] : 0;
+    for (int l = 0; l < eco::LIST_TW_TILES; ++l) listed += count[f][l];
+    if (listed != odd[f]) continue;
+    odd_along[f] = true;                    // the launch lists hold them alone, a unit each
+    for (int l = 0; l < eco::LIST_TW_TILES; ++l) count[f][l] = 0;
+    for (Lists::WideLoad &w : load[f]) w = Lists::WideLoad{0, 0};
+    units -= odd[f];
+    for (size_t i = 0; i < n; ++i)
+      if (tensors[i].fmt == f && short_odd(tensors[i], hp)) count_tensorwise(f, place(tensors[i]));
   }
   // The wide lists again with the step's own grouping of rows, where it is the better one (see bytes_of) and the static tables hold
   // its units; back to the other one if they do not.
@@ -915,7 +963,6 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     }
     if (units <= MAX_UNITS) break;
   }
-  const int plain_home = home_of_plain(tensors_of, entries_of);
   const auto format_of = [&](size_t i) {
     const int32_t fmt = tensors[i].fmt;
     return fmt == ECO_FMT_FP8_E4M3 || fmt == ECO_FMT_INT4 || plain_home < 0 ? fmt : plain_home;

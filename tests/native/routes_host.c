@@ -88,6 +88,14 @@ static const Case cases[] = {
     {"two turns", INT4, BF16, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1, 200000}}, 4, 0},
     {"many turns", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}}, 2, 0},
     {"many turns with tails", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}, {1, TENSOR, 1, 8193}}, 3, 0},
+    /* ... and short ones of a length that is no multiple of 8: along with longer ones, unless a launch takes them for nothing */
+    {"short odd ones beside longer ones", INT4, BF16, ADAM, ECO_MODE_ECO, {{2, TENSOR, 1, 11942}, {31, TENSOR, 1, 770}}, 4, 0},
+    {"short odd ones beside one turn", INT4, BF16, ADAM, ECO_MODE_NAIVE, {{5, TENSOR, 18, 2048}, {29, TENSOR, 1, 2627}}, 4, 0},
+    {"short odd ones beside longer ones and norms", INT4, BF16, ADAM, ECO_MODE_ECO, {{2, TENSOR, 1, 11942}, {31, TENSOR, 1, 770}, {1, PLAIN, 1, 512}}, 5, 0},
+    {"short odd ones beside many turns", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}, {29, TENSOR, 1, 2627}}, 3, 0},
+    {"short odd ones beside many turns with tails", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}, {1, TENSOR, 1, 8193}, {29, TENSOR, 1, 2627}}, 3, 0},
+    {"many short odd ones beside a longer one", INT4, BF16, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 9000}, {540, TENSOR, 1, 770}}, 3, 0},
+    {"short odd ones alone", INT4, BF16, ADAM, ECO_MODE_ECO, {{31, TENSOR, 1, 770}}, 1, 0},
     {"beside a long one", INT4, BF16, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1, 870000}, {1, TENSOR, 1, 7000000}}, 4, 0},
     {"more beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1408, 2048}, {1, TENSOR, 1, 7000000}}, 6, 20},
     {"a long one, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{1, TENSOR, 1, 7000000}}, 4, 0},

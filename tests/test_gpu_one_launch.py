@@ -103,6 +103,35 @@ def test_rows_that_leave_lanes_idle(path, fmt, bf16, over):
     dw.close()
 
 
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("int4", True, dict(round=1)), ("fp8", False, dict(mode=3)), ("int4", False, dict(opt=1, lr=0.05))])
+def test_short_tensors_of_odd_length_along_with_longer_ones(fmt, bf16, over, noalloc):
+    """One scale each: lengths from 1 to 8191 that are no multiple of 8, in the launches of tensors beyond 8192 elements; no tensor
+    of another kind in the list."""
+    from paper_2601_22101_amd import binding as eco
+    from paper_2601_22101_amd import harness
+    o32 = oracle.get("f32")
+    specs = [grouped(n, n, fmt) for n in (1, 5, 7, 9, 511, 513, 770, 2627, 8191, 8193, 11942, 100003)]
+    wl = workloads.Workload("odd_along", specs, steps=2, state_bf16=bf16, scale_bf16=bf16)
+    dw = harness.DeviceWorkload(wl, DEV, layout=over)
+    host = [host_copy(tv) for tv in dw.tensors]
+    for k in (1, 2):
+        dw.fill_gradients(k)
+        hp = dw.hparams(k)
+        for tv, h in zip(dw.tensors, host):
+            h["grad"] = bf16_bits(tv.grad)
+        if noalloc:
+            eco.eco_step_tensors_noalloc([dw.descriptor(tv) for tv in dw.tensors], hp)
+        else:
+            dw.plan.step(hp)
+        torch.cuda.synchronize()
+        for tv, h in zip(dw.tensors, host):
+            oracle_step(o32, h, tv.spec.numel, step_config(hp, tv.tensor_id, tv.fmt, group_size=dw.group_size(tv)))
+            st = compare(host_copy(tv), h, f"step {k} {tv.spec.name}", bf16)
+            assert not any(v for key, v in st.items() if key.endswith("mismatch")), (tv.spec.name, st)
+    dw.close()
+
+
 @pytest.mark.parametrize("opt", [0, 1])
 @pytest.mark.parametrize("fmt,bf16", [("fp8", False), ("int4", True), ("int4", False)])
 def test_master_weights_with_one_scale_in_two_passes(fmt, bf16, opt):
