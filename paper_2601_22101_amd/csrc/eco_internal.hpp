@@ -392,13 +392,18 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t units, ui
 //   SGDM, fp32 state, 15.5, where three in four are: 48 215 / 234, 400 217 / 232, 504 214 / 247, others none (328 241 / 226); with a stored
 //   error, 13.4: 48 352 / 394, 200 364 / 399, 328 369 / 405, 400 366 / 404, 504 362 / 417; with master weights, 8.2: 48 376 / 394, 160 380 / 389,
 //   200 381 / 404, 264 386 / 416, 328 372 / 399, 400 369 / 408, 504 361 / 408.
-// For arrays in the cache before it only Adam with fp32 state, 16, where three lanes in four are busy (8 M elements: 96 28.9 / 30.0, 400
-// 29.8 / 30.6; 25 M 87.8 / 90.3, 91.5 / 93.1).
-inline unsigned unit_workgroups(const KernelVariant &kv, bool from_hbm, uint64_t units, uint64_t elements) {
+// For arrays in the cache before it only Adam with fp32 state: 16 where three lanes in four are busy (8 M elements: 96 28.9 / 30.0, 400
+// 29.8 / 30.6; 25 M 87.8 / 90.3, 91.5 / 93.1), with master weights 14 from 192 MB on (16 M: 48 68.4 / 71.4, 96 66.9 / 68.6, 200 69.8 / 71.5, 264
+// 73.1 / 72.9, 400 68.9 / 70.2, 504 68.7 / 70.7; 23 M: 96 111.3 / 114.0, 400 115.0 / 116.3, 504 113.6 / 117.9; below no difference, 9.6 M: 96
+// 42.3 / 42.6, 200 43.9 / 43.9, 400 44.2 / 44.1).
+inline unsigned unit_workgroups(const KernelVariant &kv, bool mostly_hbm, bool from_hbm, uint64_t units, uint64_t elements) {
   const uint64_t lanes = units * TILE_ELEMS;
   const auto at_least = [=](uint64_t tenths) { return static_cast<unsigned>((tenths * lanes + 10 * elements - 1) / (10 * elements)); };
   const bool most = elements * 4 >= lanes * 3;
-  if (!from_hbm) return kv.algo == ALGO_ADAM && !kv.state_bf16 && most ? at_least(160) : 0;
+  if (!from_hbm) {
+    if (kv.state_bf16) return 0;
+    return kv.algo == ALGO_ADAM ? (most ? at_least(160) : 0) : kv.algo == ALGO_ADAM_MASTER && mostly_hbm ? at_least(140) : 0;
+  }
   if (kv.state_bf16) return kv.algo == ALGO_ADAM && elements * 10 >= lanes * 9 ? at_least(205) : 0;
   switch (kv.algo) {
     case ALGO_ADAM: return at_least(103);
