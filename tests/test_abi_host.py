@@ -421,7 +421,7 @@ def test_a_plain_c_client_compiles_links_and_runs(eco, tmp_path):
     assert lines["nullplan"] == str(eco.ECO_EINVAL) and lines["destroynull"] == "0"
 
 
-@pytest.mark.parametrize("n", [0, 1, 2, 45, 300])
+@pytest.mark.parametrize("n", [0, 1, 2, 3, 45, 300])
 def test_descriptor_array_is_what_ctypes_would_build(eco, n):
     """Lists of descriptors are joined as bytes; whatever else a caller passes goes to ctypes, which takes or refuses it as before."""
     ts = [eco.make_tensor(16 * i, 32, 48, 64, 80, 100 + i, i, i % 4, aux=None, group_size=8 * i) for i in range(n)]
