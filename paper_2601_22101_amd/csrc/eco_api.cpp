@@ -251,7 +251,8 @@ eco_status_t check_layout(const eco_hparams_t *layout) {
 }
 
 eco::StateLayout state_layout(const eco_hparams_t *layout) {
-  return {layout->opt == ECO_OPT_ADAM, layout->state_dtype == ECO_DT_BF16, layout->mode == ECO_MODE_EXACT || layout->mode == ECO_MODE_MASTER};
+  return {layout->opt == ECO_OPT_ADAM, layout->state_dtype == ECO_DT_BF16, layout->mode == ECO_MODE_EXACT || layout->mode == ECO_MODE_MASTER,
+          layout->mode == ECO_MODE_MASTER};
 }
 
 // The kernel variant of a step with these hyper-parameters on tensors of format f.

@@ -55,27 +55,34 @@ constexpr uint64_t RES_SLAB = static_cast<uint64_t>(RES_WAVES) * TILE_ELEMS;
 constexpr uint64_t RES_SLABS_PER_WG = RES_DEPTH - 2;
 // Bytes of a tensor's arrays, each counted once: whether a step finds them in the 256 MB cache in front of HBM decides
 // which form of it is the faster one.
-struct StateLayout { bool adam, state_bf16, aux; };
+struct StateLayout { bool adam, state_bf16, aux, master = false; };      // aux: a stored error or master weights
 inline uint64_t array_bytes(uint64_t numel, int fmt, const StateLayout &l) {
   const bool quantized = fmt == FMT_FP8 || fmt == FMT_INT4;
   const uint64_t half = fmt == FMT_FP8 ? 2 : fmt == FMT_INT4 ? 1 : fmt == FMT_BF16_PLAIN ? 4 : 8;      // of the weights, in half bytes
   return numel * (2 + (l.adam ? 2 : 1) * (l.state_bf16 ? 2 : 4) + (l.aux && quantized ? 4 : 0)) + numel * half / 2;
 }
-// Whether the tensor-wise tensors of one format that the chip can hold are stepped in one pass.  In favour: 35 % fewer bytes,
-// and two launches where the two-pass form has four.  Against: turns of 4 to 5 us, so that lists of few turns (but more than
-// one) are slower; a launch of 5 us more where a tensor has a tail; two launches more where longer tensors need the
-// two-pass form anyway.  The lines below are where the two forms met (us, two passes / one) --
-//   one turn: 15.1 / 12.9 (0.8 M elements); two turns 18 / 21, 20 / 25.  Then 44 MB: Adam with fp32 state 35 / 27 (4 M), 32 / 28;
-//   INT4 with bf16 state 33 / 29 (6.4 M), 31 / 29, 29 / 28; SGDM 30 / 26; master weights 39 / 31 (4 M), 36 / 33.
-//   tails: fp32 state 54 / 44 (8 M), 50 / 45, 51 / 51; bf16 state 88 / 88 (26 M), 162 / 150 (48 M).
-//   beside longer tensors: fp32 state 112 / 107 (16 M), 106 / 103, 311 / 306; bf16 state 282 / 275 (48 M), 294 / 297, 302 / 283.
-//   SGDM with bf16 state, the fewest bytes: 120 / 129 (64 M), 192 / 164 (92 M).
+// Whether the tensor-wise tensors of one format that the chip can hold are stepped in one pass.  In favour: 35 % fewer bytes (10 to 15 %
+// with master weights, whose second pass reads them alone), and two launches where the two-pass form has four.  Against: turns of 4 to 5 us, so
+// that lists of few turns (but more than one) are slower; a launch of 5 us more where a tensor has a tail; two launches more where longer
+// tensors need the two-pass form anyway.  The lines are where the two forms met, by the bytes of the tensors that one pass would take (tensors
+// of 300 000 elements; us, two passes / one) --
+//   one turn: Adam, fp32 state 15.4 / 13.3 (1.2 M elements).
+//   fp32 state and a stored error: Adam 30.6 / 31.6 (53 MB), 42.2 / 35.2 (79); SGDM 20.9 / 21.8 (34), 27.5 / 26.6 (50), 33.2 / 35.0 (67), 59.8 / 49.6.
+//     Tails: Adam 41.7 / 41.3 (79), 52.7 / 52.3 (106), 92.5 / 76.6; SGDM 33.0 / 39.1 (67), 59.9 / 54.7 (134).  Beside a longer tensor: Adam 124.8 /
+//     128.3 (211), 233.8 / 212.5 (422); SGDM 76.1 / 78.5 (134), 134.8 / 118.7 (269); stored error 111 / 113 (211), 208 / 200 (422).
+//   bf16 state, Adam: INT4 35.3 / 38.6 (62), 59.1 / 57.9 (125); FP8 36.6 / 39.1 (67), 62.9 / 58.0 (134).  Tails: 59.0 / 64.2 (125), 104.2 / 101.8
+//     (250); FP8 62.4 / 64.3 (134), 114.3 / 106.5 (269).  Beside a longer one: 123.5 / 133.1 (250), 249 / 224 (499); FP8 134.7 / 136.4 (269).
+//   bf16 state, SGDM, the fewest bytes: 71.0 / 73.8 (173), 140.1 / 137.3 (346), with tails 139.8 / 145.0.
+//   master weights, Adam, fp32 state: 32.2 / 33.6 (72), 43.3 / 38.5 (108), bf16 state 25.5 / 29.7 (50), 34.2 / 33.3 (76).  Tails 111.8 / 112.1 (288),
+//     215.6 / 223.4 (576), 434 / 422 (1152).  Beside a longer one 248 / 264 (576), 466 / 462 (1152).  SGDM 24.9 / 26.6 (53), 33.9 / 30.3 (79); tails
+//     42.2 / 43.4 (106), 72.8 / 66.5 (211), 146 / 158 (422), 317 / 299 (845); beside a longer one 173 / 193 (422), 332 / 330 (845).
 inline bool one_pass_pays(const StateLayout &l, uint64_t bytes, uint64_t slabs, unsigned cus, bool tails, bool beside_longer) {
   if (slabs <= cus && !tails && !beside_longer) return true;
-  const uint64_t MB = 1000000;
-  if (!l.state_bf16 || l.aux) return bytes >= 44 * MB + (tails ? 52 * MB : 0) + (beside_longer ? 132 * MB : 0);
-  if (!l.adam) return bytes >= 384 * MB;
-  return bytes >= (beside_longer ? (tails ? 416 * MB : 280 * MB) : tails ? 256 * MB : 44 * MB);
+  enum { F32_ADAM, F32_SGDM, BF16_ADAM, BF16_SGDM, MASTER_ADAM, MASTER_SGDM };
+  constexpr uint64_t from_mb[][4] = {{56, 96, 224, 260}, {48, 96, 224, 260}, {100, 208, 320, 416}, {384, 384, 384, 384}, {80, 800, 1100, 1100},
+                                     {64, 130, 1000, 1000}};
+  const int row = l.master ? (l.adam ? MASTER_ADAM : MASTER_SGDM) : !l.state_bf16 || l.aux ? (l.adam ? F32_ADAM : F32_SGDM) : l.adam ? BF16_ADAM : BF16_SGDM;
+  return bytes >= 1000000 * from_mb[row][(tails ? 1 : 0) + (beside_longer ? 2 : 0)];
 }
 // Workgroups of the finishing kernel: a wave to each tensor, for its scale, and where waits may be given up enough for the
 // slabs that are then marked, a workgroup to each up to four per compute unit (they return after one load where none is:

@@ -112,8 +112,8 @@ int main() {
   CHECK(place_tensor(64 * 1000, 1000, GROUP_WIDE, true, FMT_FP8).idle && place_tensor(3 * 1408, 1408, GROUP_WIDE, true, FMT_FP8).idle);
   CHECK(!place_tensor(4 * 1408, 1408, GROUP_WIDE, true, FMT_FP8).idle && !place_tensor(5 * 1024, 1024, GROUP_WIDE, true, FMT_FP8).idle);
   // tensor-wise scaling: one pass where it was measured to pay, and more readily with fewer launches in its way
-  for (int opt = 0; opt < 8; ++opt) {
-    const StateLayout l = {(opt & 1) != 0, (opt & 2) != 0, (opt & 4) != 0};
+  for (int opt = 0; opt < 16; ++opt) {
+    const StateLayout l = {(opt & 1) != 0, (opt & 2) != 0, (opt & 4) != 0, (opt & 8) != 0};
     CHECK(one_pass_pays(l, 1, 1, 256, false, false) && one_pass_pays(l, 1, 256, 256, false, false));
     CHECK(!one_pass_pays(l, 17000000, 257, 256, false, false) && !one_pass_pays(l, 1, 1, 256, true, false) && !one_pass_pays(l, 1, 1, 256, false, true));
     bool before[4] = {false, false, false, false};

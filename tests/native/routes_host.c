@@ -97,6 +97,17 @@ static const Case cases[] = {
     {"short odd ones beside many turns with tails", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}, {1, TENSOR, 1, 8193}, {29, TENSOR, 1, 2627}}, 3, 0},
     {"many short odd ones beside a longer one", INT4, BF16, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 9000}, {540, TENSOR, 1, 770}}, 3, 0},
     {"short odd ones alone", INT4, BF16, ADAM, ECO_MODE_ECO, {{31, TENSOR, 1, 770}}, 1, 0},
+    /* ... either side of where one pass and two met, again with the second pass on the XCDs of the first */
+    {"9.6 M, INT4 bf16", INT4, BF16, ADAM, ECO_MODE_ECO, {{32, TENSOR, 1, 300000}}, 4, 0},
+    {"19 M, INT4 bf16", INT4, BF16, ADAM, ECO_MODE_ECO, {{64, TENSOR, 1, 300000}}, 2, 0},
+    {"4.8 M, fp32", FP8, F32, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1, 300000}}, 4, 5},
+    {"7.2 M, fp32", FP8, F32, ADAM, ECO_MODE_ECO, {{24, TENSOR, 1, 300000}}, 2, 0},
+    {"4.8 M, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{16, TENSOR, 1, 300000}}, 4, 0},
+    {"7.2 M, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{24, TENSOR, 1, 300000}}, 2, 0},
+    {"38 M with tails, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{128, TENSOR, 1, 300001}}, 4, 0},
+    {"38 M beside a long one, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 4, 0},
+    {"38 M beside a long one, SGDM, master", FP8, F32, SGDM, ECO_MODE_MASTER, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 4, 0},
+    {"38 M beside a long one, stored error", FP8, F32, SGDM, ECO_MODE_EXACT, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 6, 0},
     {"beside a long one", INT4, BF16, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1, 870000}, {1, TENSOR, 1, 7000000}}, 4, 0},
     {"more beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1408, 2048}, {1, TENSOR, 1, 7000000}}, 6, 20},
     {"a long one, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{1, TENSOR, 1, 7000000}}, 4, 0},
