@@ -58,8 +58,8 @@
  *    in it); per-tensor calls pay a launch each, 2.6 us of host time and 4-6 us on the device.
  *  - Tensor lengths that are multiples of 512 keep every tile on the unguarded fast path.
  *  - Row-wise scale groups (group_size = the row length) of more than 512 elements run with every lane busy when the
- *    row is a multiple of 512 elements, or when 2, 4 or 8 rows together are (576, 640, 768, 1408, 2304, ...) and the
- *    tensor has a multiple of that many rows; other lengths leave part of each row's last wave idle.
+ *    row is a multiple of 512 elements; of other rows two to eight share a workgroup where that keeps most lanes
+ *    busy (576, 640, 768, 1152, 1408, 2304, ...), and the lanes left idle cost no memory traffic.
  */
 #ifndef ECO_H
 #define ECO_H
@@ -180,7 +180,7 @@ eco_status_t eco_plan_destroy(eco_plan_t *plan);
  * hold (up to 4.7 million elements on 256 compute units) where one pass over memory is the faster form of the list (a
  * third launch if a length is no multiple of 8).  Ragged tails, groups of up to 512 elements that are no power of two and
  * unquantized tensors ride in one of the first two kinds (large sets of unquantized tensors get a launch of their own),
- * and up to 44 tensors of together 8 million elements are one launch beside the tensor-wise ones.  A plan with more work
+ * and tensors of together 8 million elements are one launch beside the tensor-wise ones.  A plan with more work
  * than one launch can hold (2^32 threads: about 2^35 elements) has these launched in pieces.
  * The one-pass form wants whole compute units: with kernels of other streams on the chip it waits for them to end (a
  * step of 4.7 million elements beside elementwise kernels of 0.35 ms: 0.28 ms).
@@ -205,8 +205,8 @@ eco_status_t eco_step_tensors(const eco_tensor_t *tensors, size_t n, const eco_h
  * host-to-device copy or other allocating routine: the tensor descriptors, the launch tables and the abs-max
  * scratch of tensors with a single scale live in one static device array of 8.7 MB (8 732 672 bytes) per GPU,
  * held until the process ends, and the tables are written by a kernel from descriptors passed as kernel arguments (a
- * list of up to 44 tensors and 8 million elements without tensor-wise scales needs no tables: its descriptors are
- * arguments of the step kernel itself).
+ * list of up to 8 million elements without a single scale over more than 8192 of them needs no tables: its descriptors
+ * are arguments of the step kernel itself, 44 tensors to a launch).
  * Limits: at most 4096 tensors per call and at most 2^20 launch-table entries in total (one per 512 elements of a
  * tensor, rounded up, plus one per tensor with a ragged tail or a single scale; one per scale group for groups
  * wider than 512 elements) -- about 5.3e8 elements per call; beyond that ECO_EUNSUPPORTED, before anything is

@@ -301,7 +301,7 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
     // rows of 1000, 315 MB 91 / 89).
     const bool worth = hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && (idle ? adam32 : kv.algo == eco::ALGO_ADAM_MASTER));
     const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, units, load[nw].elements)
-                                                   : eco::wide_workgroups(kv, nw, units, load[nw].idle);
+                                                   : eco::wide_workgroups(kv, nw);
     // Adam with fp32 state in full rows has the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
     // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 2048: 467
     // against 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).

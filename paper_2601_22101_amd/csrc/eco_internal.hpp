@@ -231,7 +231,8 @@ inline FlatLaunch flat_launch(uint64_t numel, unsigned threads) {
 // takes `rows` consecutive groups.  One group a workgroup in general; groups of more than 512 elements whose length is
 // not a multiple of 512 leave lanes of their last wave idle, so where 2..8 of them together fill a whole number of
 // waves exactly (1408 = 2.75 waves: four rows in 11 waves; 576: eight rows in 9 waves) and the tensor is a whole number
-// of such bundles, a workgroup takes the bundle.  This is the initial quantizer's grouping; the step has one of its own.
+// of such bundles, a workgroup takes the bundle.  This is the initial quantizer's grouping, that of steps of less than 96 MB of arrays, of
+// steps of Adam with master weights, and of allocation-free calls whose tables hold no other; for the others see step_geometry.
 struct WideGeometry { uint32_t rows; uint32_t waves; uint64_t units; };
 inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = min(group size, numel)
   const uint64_t ngroups = (numel + g - 1) / g;
@@ -248,8 +249,9 @@ inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = 
   }
   return w;
 }
-// How the step groups them.  Its waves tolerate idle lanes (see WavePieces), and what a large workgroup costs is more: its waves
-// wait for the slowest, and come and go together.  So few waves, most of their lanes busy.  Measured over 150 M elements, each
+// How steps of 96 MB of arrays and more group them.  A step's waves tolerate idle lanes (see WavePieces), and what a large workgroup costs
+// is more: its waves wait for the slowest, and come and go together.  So few waves, most of their lanes busy: two to four rows whose
+// last wave may be part idle, the last workgroup of a tensor with what rows there are.  Measured over 150 M elements, each
 // with the best number of resident waves, us: one row / this / the bundle that fills its waves exactly --
 //   fp32 state, Adam: 576 543 / 510 / 513 (3 rows in 4 waves), 640 561 / 510 / 515, 896 544 / 519 (4 in 7), 1152 513 / 512 / 516 (2
 //   in 5), 1408 507 (one) / 548, 2304 513 (one) / 517, 2816 512 (one) / 555; SGDM: 576 327 / 305 / 308, 1152 305 / 302 / 307, 1408 303
@@ -257,7 +259,8 @@ inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = 
 //   bf16 state, Adam, INT4: 576 389 / 307 / 312, 640 357 / 295 / 294, 896 303 / 293.  Without a cap on resident waves, which rows with
 //   idle lanes of this kind do not have, the exact bundle otherwise: 1408 315 / 313 (FP8 344 / 322), 2304 310 / 303, 2816 315 / 307;
 //   longer ones lose (1664 304 / 330 in 13 waves).
-//   Adam with master weights, without such a cap: the exact bundle (576 790 / 764, 640 785 / 740, 1152 752 / 762, 2304 767 / 770).
+//   Adam with master weights, without such a cap, which it does not have either: the exact bundle (576 790 / 764, 640 785 / 740, 1152 752 /
+//   762, 2304 767 / 770).  (With one, see wide_workgroups_idle, one row and other bundles are faster still; not taken up yet.)
 // Where it is all but as good and of up to 9 waves the exact bundle stays: row lengths that share a number of waves share a launch
 // (510 M elements in rows of 576 and of 2304, all in 9 waves 1833 us, in 4 and in 5 1843).
 inline WideGeometry step_geometry(uint64_t numel, uint64_t g, const StateLayout &l) {        // g = min(group size, numel)
@@ -363,8 +366,7 @@ __attribute__((always_inline)) inline Placement place_tensor(uint64_t numel, uin
 //   SGDM, fp32 state, 14.5: 768 304 / 328, 1024 310 / 319, 2048 299 / 332, 3072 301 / 332, 3584 302 / 338, 4096 314 / 332 (larger
 //   workgroups lose: 2304, two of 9 waves, 332 / 309); with a stored error, 11.5: 768 510 / 551, 1024 511 / 525, 2048 501 / 527, 4096 531 / 537; with master weights, 8.5: 768 489 /
 //   529, 1024 507 / 521, 2048 511 / 541, 4096 515 / 532.
-inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, uint64_t units, uint64_t idle) {
-  if (idle > units / 8) return 0;
+inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw) {
   const auto at_least = [nw](unsigned tenths) { const unsigned k = (tenths + 10 * nw - 1) / (10 * nw); return k < 2 ? 2 : k; };
   if (kv.algo == ALGO_ADAM) return kv.state_bf16 && (nw <= 4 || nw == 8) ? at_least(200) : 0;
   if (kv.algo == ALGO_ADAM_MASTER) return kv.state_bf16 ? at_least(115) : nw <= 5 ? 10 / nw : 2;
@@ -379,6 +381,9 @@ inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, uint64_t u
 //   SGDM, fp32 state, 22: 640 302 / 338, 1000 308 / 345, 1152 302 / 305, 1408 306 / 321, 1800 308 / 318, 4000 310 / 346; with a stored error,
 //   16.5: 640 531 / 545, 1000 523 / 589, 1152 529 / 547, 1408 540 / 568, 1800 521 / 570, 3000 546 / 571; with master weights, 9.7: 640 486 /
 //   538, 1000 514 / 631, 1152 490 / 534, 1408 496 / 525, 1800 506 / 607, 2304 494 / 538, 3000 527 / 609.
+//   None, though 150 M elements are faster with one -- other sizes are not measured: Adam with master weights and fp32 state (best cap / none:
+//   1000 744 / 924, 1800 742 / 891, 3000 733 / 887; in other bundles 1152 706 / 751, 1408 691 / 773, 2816 705 / 776), Adam with bf16 state (1000 INT4
+//   297 / 334, FP8 318 / 360).
 inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t units, uint64_t elements) {
   const auto at_least = [=](uint64_t tenths) {
     const uint64_t k = (tenths * units * TILE_ELEMS + 10 * elements - 1) / (10 * elements);

@@ -176,7 +176,7 @@ __device__ __forceinline__ void load_raw8(const void *base, uint64_t e, eco_u32x
 }
 // The first nvalid (1..7) elements of a piece, zeros behind them.  Element by element, but without a branch, so that the loads of a
 // lane are under way together: an element that does not exist is the first one read once more (25 odd tensors, SGDM, without a plan
-// 7.4 -> 6.5 us, 30 of 4004 elements beside 30 plain ones 5.1 -> 4.4).
+// 7.6 -> 6.5 us, 30 of 4004 elements beside 30 plain ones 5.1 -> 4.4).
 template <bool BF16>
 __device__ __forceinline__ void load_ragged8(const void *base, uint64_t e, int nvalid, eco_u32x4_t (&q)[2]) {
   uint32_t x[8];
@@ -833,9 +833,9 @@ __global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint64_t tab
 }
 
 // (2) Wide groups (any multiple of 8 from 520 to 8192 elements: row-wise scaling, Sec. 4.1): one workgroup of
-// ceil(group/512) waves per group, abs-max by wave all-reduce plus an LDS combine across the waves -- or, where the
-// plan found that 2..8 groups fill a whole number of waves exactly (TensorDesc::slot, see wide_geometry), one
-// workgroup per such bundle of groups, every lane busy.  EXTRA: workgroups beyond the groups take one-wave units, one
+// ceil(group/512) waves per group, abs-max by wave all-reduce plus an LDS combine across the waves -- or one workgroup
+// per bundle of 2..8 groups (TensorDesc::slot), which fill a whole number of waves exactly (wide_geometry) or leave
+// lanes of the last one idle (step_geometry).  EXTRA: workgroups beyond the groups take one-wave units, one
 // to a wave (a variant of its own: with those paths in the kernel the groups run 3.6 % slower, 3 460 -> 3 590 us over
 // Gemma-3-1B shapes, so a long launch leaves them to another one).
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, bool EXTRA>

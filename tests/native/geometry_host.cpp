@@ -95,18 +95,71 @@ int main() {
     CHECK(k == 0 || k >= 32 ? lds == 0 : lds > 0 && lds <= 65536 && (lds + 128 + 1279) / 1280 * 1280 * k <= 163840);
     if (k > 2 && k < 32) CHECK((lds + 1279) / 1280 * 1280 * (k + k / 4 + 1) > 163840);
   }
-  // occupancy caps of the wide-group kernel: none where rows leave lanes idle, at least 20 waves where bf16 state is capped,
-  // and a request that the hardware's LDS holds that many times
+  // how many workgroups are to be resident, 0 for no wish.  Full rows: at least two, at least 20 waves where bf16 state is capped.
+  // Rows with idle lanes, and units of one wave: the fewest with a certain number of waves' worth of busy lanes, whatever their share
   for (int algo : {ALGO_ADAM, ALGO_SGDM, ALGO_SGDM_EXACT, ALGO_ADAM_MASTER, ALGO_SGDM_MASTER}) {
     for (int bf16 = 0; bf16 <= 1; ++bf16) {
+      const KernelVariant kv = {FMT_FP8, bf16, bf16, algo, ROUND_SR};
       for (unsigned nw = 2; nw <= (unsigned)MAX_WIDE_WAVES; ++nw) {
-        const KernelVariant kv = {FMT_FP8, bf16, bf16, algo, ROUND_SR};
-        CHECK(wide_workgroups(kv, nw, 1000, 1000) == 0 && wide_workgroups(kv, nw, 1000, 126) == 0);
-        const unsigned k = wide_workgroups(kv, nw, 1000, 125);
-        CHECK(k == wide_workgroups(kv, nw, 1000, 0) && (k == 0 || k >= 2));
+        const unsigned k = wide_workgroups(kv, nw);
+        CHECK(k == 0 || (k >= 2 && k * nw <= 32));
         if (algo == ALGO_ADAM && bf16) CHECK(k == 0 || (k * nw >= 20 && (nw <= 4 || nw == 8)));
-        CHECK(k == 0 || ((lds_for_workgroups(k) + 128 + 1279) / 1280 * 1280 * k <= 163840 && lds_for_workgroups(k) <= 65536));
       }
+      const bool capped = bf16 ? algo == ALGO_ADAM_MASTER : algo != ALGO_ADAM_MASTER;
+      for (uint64_t g = 520; g < MAX_WIDE_GROUP; g += 8) {
+        if (g % TILE_ELEMS == 0) continue;
+        const uint64_t nw = (g + TILE_ELEMS - 1) / TILE_ELEMS;
+        const unsigned k = wide_workgroups_idle(kv, 1000, 1000 * g), half = wide_workgroups_idle(kv, 1000, 500 * g);
+        CHECK(capped ? k >= 2 && k <= 22 && half >= k && half <= 2 * k : k == 0 && half == 0);
+        if (k > 2) CHECK(k * g * 10 >= 97 * TILE_ELEMS && (k - 1) * g * 10 < 220 * TILE_ELEMS && k * nw <= 44);
+      }
+      for (uint64_t busy = 1; busy <= (uint64_t)TILE_ELEMS; ++busy) {
+        for (int where = 0; where <= 2; ++where) {
+          const unsigned k = unit_workgroups(kv, where >= 1, where == 2, 1000, 1000 * busy);
+          CHECK(k == 0 || (k * busy * 10 >= 70 * TILE_ELEMS && (k - 1) * busy * 10 < 205 * TILE_ELEMS));
+          CHECK(k == 0 || where == 2 || (!bf16 && (algo == ALGO_ADAM || algo == ALGO_ADAM_MASTER)));
+          CHECK(lds_for_workgroups(k) == 0 || (k < 32 && (lds_for_workgroups(k) + 1279) / 1280 * 1280 * k <= 163840));
+        }
+      }
+    }
+  }
+  // the step's own grouping of rows, every group length, a ragged last row among the numbers of rows: what the kernels rely on.  At
+  // most 16 groups in a workgroup's LDS, also where a list launch packs several units into one of any number of waves; a wave meets at
+  // most two groups; units of Adam with master weights of several rows have no idle lane, in the last workgroup neither
+  for (int opt = 0; opt < 8; ++opt) {
+    const StateLayout l = {(opt & 1) != 0, (opt & 2) != 0, (opt & 4) != 0};
+    for (uint64_t g = 520; g <= MAX_WIDE_GROUP; g += 8) {
+      for (uint64_t n : {1ull, 2ull, 3ull, 4ull, 5ull, 7ull, 8ull, 15ull, 16ull, 24ull, 1000ull}) {
+        for (uint64_t cut : {0ull, 8ull, 3ull, 515ull}) {
+          const uint64_t numel = n * g - cut;
+          const WideGeometry w = step_geometry(numel, g < numel ? g : numel, l);
+          const uint64_t group = g < numel ? g : numel, groups = (numel + group - 1) / group;
+          CHECK(w.rows >= 1 && w.rows <= 8 && w.waves >= 1 && w.waves <= (uint32_t)MAX_WIDE_WAVES);
+          CHECK(w.waves == (w.rows * group + TILE_ELEMS - 1) / TILE_ELEMS && w.rows <= groups);
+          CHECK(w.units * w.rows >= groups && (w.units - 1) * w.rows < groups);
+          if (w.rows > 1) CHECK(group > (uint64_t)TILE_ELEMS);
+          for (uint32_t nw = w.waves; nw <= (uint32_t)MAX_WIDE_WAVES; ++nw) CHECK(nw / w.waves * w.rows <= 16);
+          if (l.aux && l.adam && w.rows > 1) CHECK(w.rows * group == (uint64_t)w.waves * TILE_ELEMS && w.units * w.rows * group == numel);
+          const StepRows rows = {l, true};
+          const Placement p = place_tensor(numel, g, GROUP_WIDE, true, FMT_FP8, TILE_ELEMS, 0, &rows);
+          if (group > (uint64_t)TILE_ELEMS) {
+            CHECK(p.kind == UNIT_WIDE && p.list == LIST_WIDE1 + (int)w.waves - 1 && p.units == w.units && p.rows == w.rows);
+            CHECK(p.entries == wide_geometry(numel, group).units && p.idle == (w.rows * group % TILE_ELEMS != 0));
+          }
+        }
+      }
+    }
+  }
+  struct { uint64_t n, g; bool adam, bf16, aux; uint32_t rows, waves; } own[] = {
+      {2304, 576, true, false, false, 8, 9}, {1001, 576, true, false, false, 3, 4}, {2, 576, true, false, false, 2, 3}, {1000, 1152, true, false, false, 2, 5},
+      {1000, 1152, true, true, false, 4, 9}, {2048, 1408, true, false, false, 1, 3}, {2048, 1408, true, true, false, 4, 11},
+      {2048, 1408, true, false, true, 4, 11}, {1001, 896, false, false, false, 4, 7}, {1001, 760, true, false, false, 2, 3}, {1001, 1000, true, false, false, 1, 2},
+      {1001, 1152, false, false, true, 2, 5}, {1001, 1152, true, false, true, 1, 3}};
+  for (const auto &k : own) {
+    const WideGeometry w = step_geometry(k.n * k.g, k.g, {k.adam, k.bf16, k.aux});
+    if (w.rows != k.rows || w.waves != k.waves) {
+      std::printf("FAILED: step, %llu rows of %llu: got %u rows, %u waves\n", (unsigned long long)k.n, (unsigned long long)k.g, w.rows, w.waves);
+      return 1;
     }
   }
   CHECK(place_tensor(64 * 1000, 1000, GROUP_WIDE, true, FMT_FP8).idle && place_tensor(3 * 1408, 1408, GROUP_WIDE, true, FMT_FP8).idle);

@@ -11,16 +11,17 @@
 enum { MOST = 64 };
 static int launches;
 static size_t lds_of[MOST], pushed_lds;
+static unsigned grid_of[MOST], block_of[MOST], pushed_grid, pushed_block;
 
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream) {
   (void)f; (void)grid; (void)block; (void)args; (void)stream;
-  if (launches < MOST) lds_of[launches] = lds;
+  if (launches < MOST) { lds_of[launches] = lds; grid_of[launches] = pushed_grid; block_of[launches] = pushed_block; }
   ++launches;
   return hipSuccess;
 }
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
-  (void)grid; (void)block; (void)stream;
-  pushed_lds = lds;
+  (void)stream;
+  pushed_lds = lds; pushed_grid = grid.x; pushed_block = block.x;
   return hipSuccess;
 }
 hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *stream) {
@@ -73,7 +74,21 @@ static const Case cases[] = {
     {"rows of 1800, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{20, ROW, 1024, 1800}}, 1, 0},
     {"rows of 768, master, 4 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{5, ROW, 1024, 768}}, 1, 0},
     {"rows of 768, master, 8 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{10, ROW, 1024, 768}}, 1, 1},
-    /* short rows: a launch of one-wave units alone has no cap, a few beside full tiles ride under theirs */
+    {"rows of 1000, 7 M, in the cache", FP8, F32, ADAM, ECO_MODE_ECO, {{7, ROW, 1024, 1000}}, 1, 0},
+    {"rows of 1000, 10 M", FP8, F32, ADAM, ECO_MODE_ECO, {{10, ROW, 1024, 1000}}, 1, 1},
+    {"rows of 1000, SGDM, 40 M", FP8, F32, SGDM, ECO_MODE_ECO, {{40, ROW, 1024, 1000}}, 1, 0},
+    {"rows of 1000, SGDM, 60 M", FP8, F32, SGDM, ECO_MODE_ECO, {{60, ROW, 1024, 1000}}, 1, 1},
+    {"rows of 1000, SGDM with a stored error, 30 M", FP8, F32, SGDM, ECO_MODE_EXACT, {{30, ROW, 1024, 1000}}, 1, 0},
+    {"rows of 1000, SGDM with a stored error, 40 M", FP8, F32, SGDM, ECO_MODE_EXACT, {{40, ROW, 1024, 1000}}, 1, 1},
+    {"rows of 1000, bf16 master, 40 M", FP8, BF16, ADAM, ECO_MODE_MASTER, {{40, ROW, 1024, 1000}}, 1, 1},
+    /* short rows: a launch of one-wave units alone has caps of its own, a few beside full tiles ride under theirs */
+    {"rows of 400, SGDM, 57 M", FP8, F32, SGDM, ECO_MODE_ECO, {{140, ROW, 1024, 400}}, 1, 1},
+    {"rows of 328, SGDM, 57 M, too few lanes busy", FP8, F32, SGDM, ECO_MODE_ECO, {{170, ROW, 1024, 328}}, 1, 0},
+    {"rows of 400, 10 M, in part in the cache", FP8, F32, ADAM, ECO_MODE_ECO, {{25, ROW, 1024, 400}}, 1, 1},
+    {"rows of 328, 10 M, in part in the cache", FP8, F32, ADAM, ECO_MODE_ECO, {{30, ROW, 1024, 328}}, 1, 0},
+    {"rows of 328, 37 M", FP8, F32, ADAM, ECO_MODE_ECO, {{110, ROW, 1024, 328}}, 1, 1},
+    {"rows of 504, bf16 INT4, 62 M", INT4, BF16, ADAM, ECO_MODE_ECO, {{120, ROW, 1024, 504}}, 1, 1},
+    {"rows of 400, bf16 INT4, 62 M, too few lanes busy", INT4, BF16, ADAM, ECO_MODE_ECO, {{150, ROW, 1024, 400}}, 1, 0},
     {"rows of 400, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{40, ROW, 1024, 400}}, 1, 0},
     {"rows of 160, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{60, ROW, 1024, 160}}, 1, 0},
     {"rows of 160, master, 15 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{94, ROW, 1024, 160}}, 1, 1},
@@ -147,6 +162,33 @@ int main(void) {
       }
     }
     (void)eco_plan_destroy(plan);
+  }
+  /* Without a plan: rows of 1408 are a workgroup of three waves each from 96 MB on, and four to one of eleven where the static tables
+   * hold no more.  Short tensors of odd length with one scale are along with longer ones. */
+  eco_hparams_t hp;
+  memset(&hp, 0, sizeof hp);
+  hp.opt = ADAM; hp.mode = ECO_MODE_ECO; hp.block_size = 128; hp.lr = 1e-3; hp.beta1 = 0.9; hp.beta2 = 0.999; hp.eps = 1e-8; hp.step = 1;
+  for (int wide = 0; wide < 2; ++wide) {
+    memset(list, 0, sizeof list);
+    list[0].weights = (void *)0x1000; list[0].scales = (void *)0x2000; list[0].grad = (void *)0x3000; list[0].m = (void *)0x4000; list[0].v = (void *)0x5000;
+    list[0].numel = (wide ? 1ull << 21 : 1ull << 19) * 1408;
+    list[0].group_size = 1408;
+    launches = 0;
+    if (eco_step_tensors_noalloc(list, 1, &hp, NULL) != ECO_OK) { printf("FAILED: no plan: %s\n", eco_last_error()); return 1; }
+    if (launches != 2 || grid_of[1] != 1u << 19 || block_of[1] != (wide ? 704u : 192u)) {
+      printf("no plan, rows of 1408: %d launches, %u workgroups of %u threads\n", launches, grid_of[1], block_of[1]);
+      ++bad;
+    }
+  }
+  for (int i = 0; i < 12; ++i) {
+    list[i] = list[0];
+    list[i].numel = list[i].group_size = i < 2 ? 11942 : 770;
+    list[i].tensor_id = (uint32_t)i;
+  }
+  launches = 0;
+  if (eco_step_tensors_noalloc(list, 12, &hp, NULL) != ECO_OK || launches != 5 || grid_of[1] != 2 * 24 + 10 * 2) {
+    printf("no plan, short tensors of odd length: %d launches, %u tiles\n", launches, grid_of[1]);
+    ++bad;
   }
   if (bad) return 1;
   printf("routes ok\n");

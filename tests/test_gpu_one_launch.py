@@ -64,15 +64,21 @@ def grouped(numel, group, fmt):
     return t
 
 
+def bytes_per_element(fmt, bf16, over):
+    aux = over.get("mode", 1) in (2, 3)
+    return (1 if fmt == "fp8" else 0.5) + 2 + (2 if bf16 else 4) * (1 if over.get("opt") else 2) + (4 if aux else 0)
+
+
 @pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("fp8", True, dict(mode=3, weight_decay=0.1)), ("int4", True, {}),
                                            ("int4", False, dict(opt=1, round=1, lr=0.05)), ("fp8", False, dict(opt=1, mode=2, lr=0.05)),
-                                           ("fp8", False, dict(eps=0.0))])
-@pytest.mark.parametrize("path", ["classes", "list", "noalloc"])
+                                           ("fp8", False, dict(eps=0.0)), ("fp8", True, {}), ("int4", False, dict(opt=1, mode=3, lr=0.05))])
+@pytest.mark.parametrize("path", ["classes", "list", "own_list", "noalloc"])
 def test_rows_that_leave_lanes_idle(path, fmt, bf16, over):
     """Rows of which several share a workgroup and rows that have one to themselves, their last waves part idle: numbers of rows
     that fill the last workgroup and that do not, a last row that is cut off behind a whole piece of 8 elements and within one;
     and tensors of any length with one scale that are one group.  In a launch for each class of group (a large tensor beside
-    them), in one launch with a plan's tables, and in launches of 44 with the descriptors as arguments."""
+    them), in one launch with a plan's tables, and in launches of 44 with the descriptors as arguments.  From 96 MB of arrays on rows
+    are grouped in another way, with idle lanes: in a launch for each class, and in one launch beside a large tensor of the other format."""
     from paper_2601_22101_amd import binding as eco
     from paper_2601_22101_amd import harness
     o32 = oracle.get("f32")
@@ -80,8 +86,12 @@ def test_rows_that_leave_lanes_idle(path, fmt, bf16, over):
              for n in (g, 2 * g, 4 * g, 7 * g, 3 * g + 8, 2 * g + 5, 5 * g - 3)]
     specs += [grouped(n, n, fmt) for n in (1, 5, 100, 511, 513, 1001, 4097, 8191)] + [T(f"p{n}", (n,), "bf16_plain") for n in (7, 1027)]
     specs += [grouped(1000, 24, fmt), grouped(700, 336, fmt), grouped(1500, 128, fmt)]
-    if path == "classes":
-        specs.append(T("large", (9000, 1024), fmt, granularity="row"))
+    other = "int4" if fmt == "fp8" else "fp8"
+    if path in ("classes", "own_list"):
+        which = fmt if path == "classes" else other
+        rows = max(9000, int(100e6 / bytes_per_element(which, bf16, over) / 1024) + 1)
+        specs.append(T("large", (rows, 1024), which, granularity="row"))
+        assert rows * 1024 > 1 << 23 and rows * 1024 * bytes_per_element(which, bf16, over) > 96e6
     wl = workloads.Workload("idle_lanes", specs, steps=2, state_bf16=bf16, scale_bf16=bf16)
     dw = harness.DeviceWorkload(wl, DEV, layout=over)
     host = [host_copy(tv) for tv in dw.tensors]
