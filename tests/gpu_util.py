@@ -110,3 +110,9 @@ def step_config(hp, tensor_id: int, fmt: int, elem_offset: int = 0, group_size: 
                       block_size=group_size or hp.block_size, state_bf16=bool(hp.state_dtype), scale_bf16=bool(hp.scale_dtype),
                       lr=hp.lr, beta1=hp.beta1, beta2=hp.beta2, eps=hp.eps, weight_decay=hp.weight_decay,
                       step=hp.step, seed=hp.seed, elem_offset=elem_offset, tensor_id=tensor_id)
+
+
+def bytes_per_element(fmt, bf16, over):
+    """Of a quantized tensor's arrays, each counted once; over: the layout's opt and mode as tests state them."""
+    aux = over.get("mode", 1) in (2, 3)
+    return (1 if fmt == "fp8" else 0.5) + 2 + (2 if bf16 else 4) * (1 if over.get("opt") else 2) + (4 if aux else 0)

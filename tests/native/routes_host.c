@@ -123,6 +123,13 @@ static const Case cases[] = {
     {"38 M beside a long one, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 4, 0},
     {"38 M beside a long one, SGDM, master", FP8, F32, SGDM, ECO_MODE_MASTER, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 4, 0},
     {"38 M beside a long one, stored error", FP8, F32, SGDM, ECO_MODE_EXACT, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 6, 0},
+    /* ... and what makes one pass of a list with tails beside a longer tensor, by the kind of state */
+    {"420 MB", FP8, F32, ADAM, ECO_MODE_ECO, {{9, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 40},
+    {"420 MB, INT4 bf16", INT4, BF16, ADAM, ECO_MODE_ECO, {{14, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 40},
+    {"420 MB, SGDM INT4", INT4, F32, SGDM, ECO_MODE_ECO, {{14, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 40},
+    {"420 MB, stored error, bf16", FP8, BF16, SGDM, ECO_MODE_EXACT, {{10, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 0},
+    {"1.1 GB, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{16, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 0},
+    {"1.1 GB, master INT4 bf16", INT4, BF16, ADAM, ECO_MODE_MASTER, {{23, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 0},
     {"beside a long one", INT4, BF16, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1, 870000}, {1, TENSOR, 1, 7000000}}, 4, 0},
     {"more beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{8, TENSOR, 1408, 2048}, {1, TENSOR, 1, 7000000}}, 6, 20},
     {"a long one, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{1, TENSOR, 1, 7000000}}, 4, 0},

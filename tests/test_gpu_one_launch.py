@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import workloads
-from gpu_util import bf16_bits, compare, host_copy, oracle_step, step_config
+from gpu_util import bf16_bits, bytes_per_element, compare, host_copy, oracle_step, step_config
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -62,11 +62,6 @@ def grouped(numel, group, fmt):
     t = T(f"g{group}_{numel}", (numel,), fmt, grad_std=1e-3 * (1 + numel % 3), granularity="row")
     t.group_size = lambda block_size: group
     return t
-
-
-def bytes_per_element(fmt, bf16, over):
-    aux = over.get("mode", 1) in (2, 3)
-    return (1 if fmt == "fp8" else 0.5) + 2 + (2 if bf16 else 4) * (1 if over.get("opt") else 2) + (4 if aux else 0)
 
 
 @pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("fp8", True, dict(mode=3, weight_decay=0.1)), ("int4", True, {}),

@@ -5,7 +5,7 @@ import torch
 
 import oracle
 import workloads
-from gpu_util import bf16_bits, compare, host_copy, oracle_step, step_config
+from gpu_util import bf16_bits, bytes_per_element, compare, host_copy, oracle_step, step_config
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -85,9 +85,11 @@ def test_tiles_whose_wait_is_given_up_are_finished_from_memory(fmt, bf16, over):
 
 def beside_enough(wl, bf16, over):
     """The workload with tensors behind it that make one pass the faster form of its list (small lists, and those beside a
-    longer tensor, are stepped in two): how many there are, 4.7 M elements each, goes by the bytes of a parameter."""
-    few = not bf16 or over.get("mode", 1) >= 2                       # fp32 state or an fp32 array beside it
-    wl.tensors = wl.tensors + [T(f"fill{i}", (4_700_000,), wl.tensors[0].fmt, granularity="tensor") for i in range(7 if few else 14)]
+    longer tensor, are stepped in two): as many of 4.7 M elements as have 420 MB of arrays, 1.1 GB with master weights, whose
+    second pass is a short one."""
+    fmt = wl.tensors[0].fmt
+    n = int((1100e6 if over.get("mode", 1) == 3 else 420e6) / (4_700_000 * bytes_per_element(fmt, bf16, over))) + 1
+    wl.tensors = wl.tensors + [T(f"fill{i}", (4_700_000,), fmt, granularity="tensor") for i in range(n)]
     return wl
 
 
