@@ -455,11 +455,12 @@ int home_of_plain(const uint64_t (&tensors)[4], const uint64_t (&entries)[4]) {
 }
 
 // One scale for a tensor of up to 8192 elements whose length is no multiple of 8: one group of a row or list launch, or, beside longer
-// tensors with one scale, one more tensor of their launches.  The second is a launch fewer where nothing else needs one, the first
+// tensors with one scale, one more tensor of their launches.  The second is less of a launch or a launch fewer, the first
 // less work: it wins from 1600 tiles and tensors on (us, in a launch of their own / along with one of 9000 elements: FP8 300 of 770
 // 16.8 / 14.7, 600 16.8 / 17.1, 1200 18.3 / 23.6, 200 of 2627 17.5 / 14.6, 60 of 8001 18.6 / 15.1, 120 18.9 / 20.2, 300 of 101 16.6 / 14.7, 1500
-// 17.2 / 17.8; INT4 with bf16 state 770 16.2 / 15.1, 16.3 / 16.3, 17.6 / 19.4), and where the longer ones are stepped in one pass of
-// several turns, which odd lengths cost a launch.
+// 17.2 / 17.8; INT4 with bf16 state 770 16.2 / 15.1, 16.3 / 16.3, 17.6 / 19.4; where norms are stepped in that launch anyway, beside two of
+// 11 942, 31 of 770 19.5 / 19.0, 60 of 8001 20.9 / 19.5), and where the longer ones are stepped in one pass, which odd lengths cost a launch
+// or take from one turn to two passes, unless two passes for all are a launch fewer.
 constexpr uint64_t ODD_ALONG_ENTRIES = 1600;
 bool short_odd(const eco_tensor_t &t, const eco_hparams_t *layout) {
   const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
@@ -652,7 +653,8 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
         else listed = true;
       }
       const unsigned cus = static_cast<unsigned>(plan->cus);
-      if (any && odd && odd <= ODD_ALONG_ENTRIES && !listed && (slabs <= cus || tails || !eco::one_pass_pays(state, bytes, slabs, cus, tails, longer)))
+      if (any && odd && odd <= ODD_ALONG_ENTRIES &&
+          (tails || !eco::one_pass_pays(state, bytes, slabs, cus, tails, longer) || (!listed && slabs <= cus)))
         for (size_t i = 0; i < n; ++i)
           if (tensors[i].fmt == f && short_odd(tensors[i], layout)) {
             place[i] = eco::place_tensor(tensors[i].numel, tensors[i].numel, eco::GROUP_TENSOR, true, f);
@@ -897,7 +899,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
   };
   bool tensorwise = false, wide = false;
-  uint64_t odd[4] = {0}, odd_entries[4] = {0};
+  uint64_t odd_entries[4] = {0};
   for (size_t i = 0; i < n; ++i) {
     const int f = tensors[i].fmt;
     uint64_t gsz = 0;
@@ -919,7 +921,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       count_tensorwise(f, p);
       continue;
     }
-    if (cls == eco::GROUP_TENSOR) { odd[f] += 1; odd_entries[f] += p.entries; }
+    if (cls == eco::GROUP_TENSOR) odd_entries[f] += p.entries;
     if (p.kind == eco::UNIT_WIDE) {
       wide = true;
       count_wide(tensors[i], p);
@@ -936,14 +938,17 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   }
   const int plain_home = home_of_plain(tensors_of, entries_of);
   for (int f = 0; f < 2; ++f) {
-    if (!odd[f] || odd_entries[f] > ODD_ALONG_ENTRIES || !count[f][L_TW_TENSORS]) continue;
-    uint64_t listed = plain_home == f ? tensors_of[eco::FMT_BF16_PLAIN] + tensors_of[eco::FMT_FP32_ID] : 0;
-    for (int l = 0; l < eco::LIST_TW_TILES; ++l) listed += count[f][l];
-    if (listed != odd[f]) continue;
-    odd_along[f] = true;                    // the launch lists hold them alone, a unit each
-    for (int l = 0; l < eco::LIST_TW_TILES; ++l) count[f][l] = 0;
-    for (Lists::WideLoad &w : load[f]) w = Lists::WideLoad{0, 0};
-    units -= odd[f];
+    if (!odd_entries[f] || odd_entries[f] > ODD_ALONG_ENTRIES || !count[f][L_TW_TENSORS]) continue;
+    for (size_t i = 0; i < n; ++i) {
+      if (tensors[i].fmt != f || !short_odd(tensors[i], hp)) continue;
+      const eco::Placement p = place(tensors[i]);
+      count[f][p.list] -= p.units;
+      units -= p.units;
+      Lists::WideLoad &w = load[f][p.kind == eco::UNIT_WIDE ? p.list - eco::LIST_WIDE1 + 1 : 0];
+      w.idle -= p.idle ? p.units : 0;
+      w.elements -= tensors[i].numel;
+    }
+    odd_along[f] = true;
     for (size_t i = 0; i < n; ++i)
       if (tensors[i].fmt == f && short_odd(tensors[i], hp)) count_tensorwise(f, place(tensors[i]));
   }

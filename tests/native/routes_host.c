@@ -108,6 +108,7 @@ static const Case cases[] = {
     {"short odd ones beside longer ones", INT4, BF16, ADAM, ECO_MODE_ECO, {{2, TENSOR, 1, 11942}, {31, TENSOR, 1, 770}}, 4, 0},
     {"short odd ones beside one turn", INT4, BF16, ADAM, ECO_MODE_NAIVE, {{5, TENSOR, 18, 2048}, {29, TENSOR, 1, 2627}}, 4, 0},
     {"short odd ones beside longer ones and norms", INT4, BF16, ADAM, ECO_MODE_ECO, {{2, TENSOR, 1, 11942}, {31, TENSOR, 1, 770}, {1, PLAIN, 1, 512}}, 5, 0},
+    {"short odd ones and norms beside one turn", INT4, BF16, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 9000}, {31, TENSOR, 1, 770}, {1, PLAIN, 1, 512}}, 3, 0},
     {"short odd ones beside many turns", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}, {29, TENSOR, 1, 2627}}, 3, 0},
     {"short odd ones beside many turns with tails", INT4, BF16, ADAM, ECO_MODE_ECO, {{16, TENSOR, 1408, 2048}, {1, TENSOR, 1, 8193}, {29, TENSOR, 1, 2627}}, 3, 0},
     {"many short odd ones beside a longer one", INT4, BF16, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 9000}, {540, TENSOR, 1, 770}}, 3, 0},
@@ -192,10 +193,16 @@ int main(void) {
     list[i].numel = list[i].group_size = i < 2 ? 11942 : 770;
     list[i].tensor_id = (uint32_t)i;
   }
-  launches = 0;
-  if (eco_step_tensors_noalloc(list, 12, &hp, NULL) != ECO_OK || launches != 5 || grid_of[1] != 2 * 24 + 10 * 2) {
-    printf("no plan, short tensors of odd length: %d launches, %u tiles\n", launches, grid_of[1]);
-    ++bad;
+  list[12] = list[13] = list[0];
+  list[12].numel = 512; list[12].fmt = ECO_FMT_BF16_PLAIN;
+  list[13].numel = list[13].group_size = 1152;
+  for (int n = 12; n <= 14; ++n) {
+    launches = 0;
+    const int tensorwise = n == 12 ? 1 : n == 13 ? 2 : 2;             /* behind the tables' launch and that of the norm and the row */
+    if (eco_step_tensors_noalloc(list, (size_t)n, &hp, NULL) != ECO_OK || launches != 4 + tensorwise || grid_of[tensorwise] != 2 * 24 + 10 * 2) {
+      printf("no plan, short tensors of odd length, %d: %d launches, %u tiles\n", n, launches, grid_of[tensorwise]);
+      ++bad;
+    }
   }
   if (bad) return 1;
   printf("routes ok\n");

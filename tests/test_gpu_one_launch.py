@@ -109,14 +109,17 @@ def test_rows_that_leave_lanes_idle(path, fmt, bf16, over):
 
 
 @pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("others", [False, True])
 @pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("int4", True, dict(round=1)), ("fp8", False, dict(mode=3)), ("int4", False, dict(opt=1, lr=0.05))])
-def test_short_tensors_of_odd_length_along_with_longer_ones(fmt, bf16, over, noalloc):
-    """One scale each: lengths from 1 to 8191 that are no multiple of 8, in the launches of tensors beyond 8192 elements; no tensor
-    of another kind in the list."""
+def test_short_tensors_of_odd_length_along_with_longer_ones(fmt, bf16, over, others, noalloc):
+    """One scale each: lengths from 1 to 8191 that are no multiple of 8, in the launches of tensors beyond 8192 elements; tensors of
+    other kinds in the list or none."""
     from paper_2601_22101_amd import binding as eco
     from paper_2601_22101_amd import harness
     o32 = oracle.get("f32")
     specs = [grouped(n, n, fmt) for n in (1, 5, 7, 9, 511, 513, 770, 2627, 8191, 8193, 11942, 100003)]
+    if others:
+        specs += [T("p", (700,), "bf16_plain"), grouped(2304, 1152, fmt), grouped(800, 800, fmt), grouped(3000, 1000, fmt)]
     wl = workloads.Workload("odd_along", specs, steps=2, state_bf16=bf16, scale_bf16=bf16)
     dw = harness.DeviceWorkload(wl, DEV, layout=over)
     host = [host_copy(tv) for tv in dw.tensors]
