@@ -381,6 +381,9 @@ inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw) {
 //   SGDM, fp32 state, 22: 640 302 / 338, 1000 308 / 345, 1152 302 / 305, 1408 306 / 321, 1800 308 / 318, 4000 310 / 346; with a stored error,
 //   16.5: 640 531 / 545, 1000 523 / 589, 1152 529 / 547, 1408 540 / 568, 1800 521 / 570, 3000 546 / 571; with master weights, 9.7: 640 486 /
 //   538, 1000 514 / 631, 1152 490 / 534, 1408 496 / 525, 1800 506 / 607, 2304 494 / 538, 3000 527 / 609.
+//   SGDM, bf16 state, with master weights 13.6, INT4 1.2 GB (FP8 alike): 520 355 / 385, 576 368 / 397, 640 356 / 390, 760 360 / 401, 1000 377 /
+//   449, 1496 387 / 423, 1800 360 / 399, 2304 354 / 372, 3000 353 / 397, 4000 366 / 398, 6912 370 / 370 (390 MB: 520 126 / 114, 1000 113 / 115, 3000
+//   113 / 118); with a stored error 20.4: 576 364 / 365, 760 359 / 380, 1000 371 / 403, 1408 368 / 377, 1496 377 / 405, 1800 362 / 373, 2304 371 / 371.
 //   None, though 150 M elements are faster with one -- other sizes are not measured: Adam with master weights and fp32 state (best cap / none:
 //   1000 744 / 924, 1800 742 / 891, 3000 733 / 887; in other bundles 1152 706 / 751, 1408 691 / 773, 2816 705 / 776), Adam with bf16 state (1000 INT4
 //   297 / 334, FP8 318 / 360).
@@ -389,7 +392,8 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t units, ui
     const uint64_t k = (tenths * units * TILE_ELEMS + 10 * elements - 1) / (10 * elements);
     return static_cast<unsigned>(k < 2 ? 2 : k);
   };
-  if (kv.state_bf16) return kv.algo == ALGO_ADAM_MASTER ? at_least(115) : 0;
+  if (kv.state_bf16)
+    return kv.algo == ALGO_ADAM_MASTER ? at_least(115) : kv.algo == ALGO_SGDM_MASTER ? at_least(136) : kv.algo == ALGO_SGDM_EXACT ? at_least(204) : 0;
   if (kv.algo == ALGO_ADAM) return at_least(136);
   if (kv.algo == ALGO_ADAM_MASTER) return 0;
   return at_least(kv.algo == ALGO_SGDM ? 220 : kv.algo == ALGO_SGDM_EXACT ? 165 : 97);

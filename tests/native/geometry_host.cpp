@@ -105,7 +105,7 @@ int main() {
         CHECK(k == 0 || (k >= 2 && k * nw <= 32));
         if (algo == ALGO_ADAM && bf16) CHECK(k == 0 || (k * nw >= 20 && (nw <= 4 || nw == 8)));
       }
-      const bool capped = bf16 ? algo == ALGO_ADAM_MASTER : algo != ALGO_ADAM_MASTER;
+      const bool capped = bf16 ? algo != ALGO_ADAM && algo != ALGO_SGDM : algo != ALGO_ADAM_MASTER;
       for (uint64_t g = 520; g < MAX_WIDE_GROUP; g += 8) {
         if (g % TILE_ELEMS == 0) continue;
         const uint64_t nw = (g + TILE_ELEMS - 1) / TILE_ELEMS;

@@ -81,6 +81,10 @@ static const Case cases[] = {
     {"rows of 1000, SGDM with a stored error, 30 M", FP8, F32, SGDM, ECO_MODE_EXACT, {{30, ROW, 1024, 1000}}, 1, 0},
     {"rows of 1000, SGDM with a stored error, 40 M", FP8, F32, SGDM, ECO_MODE_EXACT, {{40, ROW, 1024, 1000}}, 1, 1},
     {"rows of 1000, bf16 master, 40 M", FP8, BF16, ADAM, ECO_MODE_MASTER, {{40, ROW, 1024, 1000}}, 1, 1},
+    {"rows of 1000, bf16 SGDM master, 40 M", INT4, BF16, SGDM, ECO_MODE_MASTER, {{40, ROW, 1024, 1000}}, 1, 0},
+    {"rows of 1000, bf16 SGDM master, 50 M", INT4, BF16, SGDM, ECO_MODE_MASTER, {{50, ROW, 1024, 1000}}, 1, 1},
+    {"rows of 1000, bf16 stored error, 50 M", INT4, BF16, SGDM, ECO_MODE_EXACT, {{50, ROW, 1024, 1000}}, 1, 1},
+    {"rows of 1000, bf16 SGDM, 90 M", INT4, BF16, SGDM, ECO_MODE_ECO, {{90, ROW, 1024, 1000}}, 1, 0},
     /* short rows: a launch of one-wave units alone has caps of its own, a few beside full tiles ride under theirs */
     {"rows of 400, SGDM, 57 M", FP8, F32, SGDM, ECO_MODE_ECO, {{140, ROW, 1024, 400}}, 1, 1},
     {"rows of 328, SGDM, 57 M, too few lanes busy", FP8, F32, SGDM, ECO_MODE_ECO, {{170, ROW, 1024, 328}}, 1, 0},
