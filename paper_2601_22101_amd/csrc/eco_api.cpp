@@ -145,8 +145,8 @@ constexpr uint64_t SMALL_ELEMENTS = 1ull << 23;
 // counted once: the caps on resident waves were measured against none over 1 to 256 M elements, and the two met between
 // 340 and 420 MB where the traffic in flight is little (bf16 state), between 60 and 120 MB elsewhere.
 struct HbmBound {
-  bool half, mostly, fully;
-  explicit HbmBound(uint64_t bytes) : half(bytes >= 96000000), mostly(bytes >= 192000000), fully(bytes >= 384000000) {}
+  bool half, fully;
+  explicit HbmBound(uint64_t bytes) : half(bytes >= 96000000), fully(bytes >= 384000000) {}
 };
 
 // Bytes of all arrays of a list.  From HbmBound::half on the step groups rows in its own way (see step_geometry); in shorter
@@ -289,7 +289,7 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   // a launch of one-wave units beside few tiles does not have the tiles' cap, which counts on every lane; short rows alone have
   // one of their own
   const bool units = (kv.fmt == eco::FMT_FP8 || kv.fmt == eco::FMT_INT4) && a->num_extra > a->num_tiles / 8;
-  const unsigned resident = units && !a->num_tiles && load[0].elements ? eco::unit_workgroups(kv, hbm.mostly, hbm.fully, a->num_extra, load[0].elements) : 0;
+  const unsigned resident = units && !a->num_tiles && load[0].elements ? eco::unit_workgroups(kv, bytes, a->num_extra, load[0].elements) : 0;
   sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? eco::lds_for_workgroups(resident) : lds_for_waves(waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
     const uint64_t units = sl->num_wide[nw];

@@ -408,19 +408,30 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t units, ui
 //   SGDM, fp32 state, 15.5, where three in four are: 48 215 / 234, 400 217 / 232, 504 214 / 247, others none (328 241 / 226); with a stored
 //   error, 13.4: 48 352 / 394, 200 364 / 399, 328 369 / 405, 400 366 / 404, 504 362 / 417; with master weights, 8.2: 48 376 / 394, 160 380 / 389,
 //   200 381 / 404, 264 386 / 416, 328 372 / 399, 400 369 / 408, 504 361 / 408.
+//   bf16 state beside an fp32 array, where three in four are: with master weights 12.4 (1.5 GB of arrays, Adam, FP8 / INT4: 48 518 / 557 and 556 /
+//   585, 96 508 / 555 and 549 / 582, 200 502 / 550 and 538 / 552, 504 531 / 559 and 556 / 583; SGDM 96 464 / 526 and 485 / 560, 400 477 / 516 and 499 / 530,
+//   504 503 / 532 and 519 / 563; 328 gains nothing), with a stored error 17.2 (96 472 / 524 and 476 / 514, 200 481 / 519 and 488 / 506, 504 490 / 547 and
+//   488 / 549).  SGDM, bf16 state, from 768 MB on and where nineteen lanes in twenty are busy 21.5 (504: 437 / 488, 2.6 GB 755 / 879; 390 MB 116 / 114).
 // For arrays in the cache before it only Adam with fp32 state: 16 where three lanes in four are busy (8 M elements: 96 28.9 / 30.0, 400
 // 29.8 / 30.6; 25 M 87.8 / 90.3, 91.5 / 93.1), with master weights 14 from 192 MB on (16 M: 48 68.4 / 71.4, 96 66.9 / 68.6, 200 69.8 / 71.5, 264
 // 73.1 / 72.9, 400 68.9 / 70.2, 504 68.7 / 70.7; 23 M: 96 111.3 / 114.0, 400 115.0 / 116.3, 504 113.6 / 117.9; below no difference, 9.6 M: 96
 // 42.3 / 42.6, 200 43.9 / 43.9, 400 44.2 / 44.1).
-inline unsigned unit_workgroups(const KernelVariant &kv, bool mostly_hbm, bool from_hbm, uint64_t units, uint64_t elements) {
-  const uint64_t lanes = units * TILE_ELEMS;
+inline unsigned unit_workgroups(const KernelVariant &kv, uint64_t bytes, uint64_t units, uint64_t elements) {
+  const uint64_t lanes = units * TILE_ELEMS, MB = 1000000;
   const auto at_least = [=](uint64_t tenths) { return static_cast<unsigned>((tenths * lanes + 10 * elements - 1) / (10 * elements)); };
   const bool most = elements * 4 >= lanes * 3;
-  if (!from_hbm) {
+  if (bytes < 384 * MB) {
     if (kv.state_bf16) return 0;
-    return kv.algo == ALGO_ADAM ? (most ? at_least(160) : 0) : kv.algo == ALGO_ADAM_MASTER && mostly_hbm ? at_least(140) : 0;
+    return kv.algo == ALGO_ADAM ? (most ? at_least(160) : 0) : kv.algo == ALGO_ADAM_MASTER && bytes >= 192 * MB ? at_least(140) : 0;
   }
-  if (kv.state_bf16) return kv.algo == ALGO_ADAM && elements * 10 >= lanes * 9 ? at_least(205) : 0;
+  if (kv.state_bf16) {
+    switch (kv.algo) {
+      case ALGO_ADAM: return elements * 10 >= lanes * 9 ? at_least(205) : 0;
+      case ALGO_SGDM: return elements * 20 >= lanes * 19 && bytes >= 768 * MB ? at_least(215) : 0;
+      case ALGO_SGDM_EXACT: return most ? at_least(172) : 0;
+      default: return most ? at_least(124) : 0;
+    }
+  }
   switch (kv.algo) {
     case ALGO_ADAM: return at_least(103);
     case ALGO_ADAM_MASTER: return at_least(70);

@@ -114,10 +114,10 @@ int main() {
         if (k > 2) CHECK(k * g * 10 >= 97 * TILE_ELEMS && (k - 1) * g * 10 < 220 * TILE_ELEMS && k * nw <= 44);
       }
       for (uint64_t busy = 1; busy <= (uint64_t)TILE_ELEMS; ++busy) {
-        for (int where = 0; where <= 2; ++where) {
-          const unsigned k = unit_workgroups(kv, where >= 1, where == 2, 1000, 1000 * busy);
-          CHECK(k == 0 || (k * busy * 10 >= 70 * TILE_ELEMS && (k - 1) * busy * 10 < 205 * TILE_ELEMS));
-          CHECK(k == 0 || where == 2 || (!bf16 && (algo == ALGO_ADAM || algo == ALGO_ADAM_MASTER)));
+        for (uint64_t mb : {1ull, 100ull, 191ull, 192ull, 383ull, 384ull, 767ull, 768ull, 5000ull}) {
+          const unsigned k = unit_workgroups(kv, mb * 1000000, 1000, 1000 * busy);
+          CHECK(k == 0 || (k * busy * 10 >= 70 * TILE_ELEMS && (k - 1) * busy * 10 < 215 * TILE_ELEMS));
+          CHECK(k == 0 || mb >= 384 || (!bf16 && (algo == ALGO_ADAM || (algo == ALGO_ADAM_MASTER && mb >= 192))));
           CHECK(lds_for_workgroups(k) == 0 || (k < 32 && (lds_for_workgroups(k) + 1279) / 1280 * 1280 * k <= 163840));
         }
       }

@@ -96,6 +96,12 @@ static const Case cases[] = {
     {"rows of 400, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{40, ROW, 1024, 400}}, 1, 0},
     {"rows of 160, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{60, ROW, 1024, 160}}, 1, 0},
     {"rows of 160, master, 15 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{94, ROW, 1024, 160}}, 1, 1},
+    {"rows of 160, bf16 SGDM master, 30 M", FP8, BF16, SGDM, ECO_MODE_MASTER, {{190, ROW, 1024, 160}}, 1, 0},
+    {"rows of 160, bf16 SGDM master, 50 M", FP8, BF16, SGDM, ECO_MODE_MASTER, {{310, ROW, 1024, 160}}, 1, 1},
+    {"rows of 328, bf16 SGDM master, 50 M, too few lanes busy", FP8, BF16, SGDM, ECO_MODE_MASTER, {{150, ROW, 1024, 328}}, 1, 0},
+    {"rows of 160, bf16 stored error, 50 M", FP8, BF16, SGDM, ECO_MODE_EXACT, {{310, ROW, 1024, 160}}, 1, 1},
+    {"rows of 504, bf16 SGDM, 120 M", FP8, BF16, SGDM, ECO_MODE_ECO, {{235, ROW, 1024, 504}}, 1, 0},
+    {"rows of 504, bf16 SGDM, 170 M", FP8, BF16, SGDM, ECO_MODE_ECO, {{330, ROW, 1024, 504}}, 1, 1},
     {"a few rows of 400 beside blocks", FP8, F32, ADAM, ECO_MODE_ECO, {{60, 128, 1024, 1024}, {4, ROW, 1024, 400}}, 1, 1},
     /* one-wave units with few busy lanes beside arrays from HBM: as many waves as want to */
     {"100 norms of 32 beside a long one", FP8, F32, ADAM, ECO_MODE_ECO, {{1, TENSOR, 1, 70000000}, {100, PLAIN, 1, 32}}, 5, 10},
