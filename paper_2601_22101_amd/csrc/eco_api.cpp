@@ -158,6 +158,16 @@ uint64_t bytes_of(const eco_tensor_t *tensors, size_t n, const eco::StateLayout 
   return sum;
 }
 
+// The step's own grouping of rows has a launch for each size of workgroup, which may be more of them than the other grouping's: 4-6 us
+// that it has to make up for (us, other / own, with a launch more: 16.9 M elements in rows of 4096, 1024 and an odd number of 768, FP8 with bf16
+// state 41.2 / 45.8; rows of 768, 2304 and 576, 11 M, FP8 60.6 / 66.3; INT4 SGDM 39 M in rows of 1024, 768 and 1816 102.9 / 109.1; 160 M in rows of
+// 576 and 1024, INT4 with bf16 state 550 / 475).  So from 384 MB on, and below where it takes no launch more.
+bool own_grouping_pays(uint64_t bytes, const uint32_t (&own_sizes)[4], const uint32_t (&sizes)[4]) {
+  int more = 0;
+  for (int f = 0; f < 4; ++f) more += __builtin_popcount(own_sizes[f]) - __builtin_popcount(sizes[f]);
+  return HbmBound(bytes).fully || more <= 0;
+}
+
 int num_compute_units() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
@@ -605,7 +615,8 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     const eco::StateLayout state = state_layout(layout);
     uint64_t tensors_of[4] = {0}, entries_of[4] = {0}, list_entries[4][eco::LIST_COUNT] = {{0}};
     plan->bytes = bytes_of(tensors, n, state);
-    const eco::StepRows rows = {state, HbmBound(plan->bytes).half};
+    eco::StepRows rows = {state, HbmBound(plan->bytes).half};
+    uint32_t own_sizes[4] = {0}, sizes[4] = {0};          // of workgroups, a bit each: with the step's own grouping of rows, and without
     for (size_t i = 0; i < n && st == ECO_OK; ++i) {
       const eco_tensor_t &t = tensors[i];
       uint64_t gsz = 0;
@@ -614,6 +625,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       if (st != ECO_OK) break;
       const bool quantized = t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4;
       place[i] = eco::place_tensor(t.numel, gsz, cls, quantized, t.fmt, eco::TILE_ELEMS, 0, &rows);
+      if (rows.own_rows && place[i].kind == eco::UNIT_WIDE) {
+        own_sizes[t.fmt] |= 1u << (place[i].list - eco::LIST_WIDE1);
+        sizes[t.fmt] |= 1u << (eco::wide_geometry(t.numel, place[i].group).waves - 1);
+      }
       tensors_of[t.fmt] += 1;
       entries_of[t.fmt] += place[i].entries;
       uint64_t &in_list = list_entries[t.fmt][place[i].list];
@@ -621,6 +636,12 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       if (in_list > 0x7FFFFFF0ull) st = fail(ECO_EUNSUPPORTED, "plan: more than 2^31 tiles in one launch");
     }
     if (st != ECO_OK) { delete plan; return st; }
+    if (rows.own_rows && !own_grouping_pays(plan->bytes, own_sizes, sizes)) {
+      rows.own_rows = false;
+      for (size_t i = 0; i < n; ++i)
+        if (place[i].kind == eco::UNIT_WIDE)
+          place[i] = eco::place_tensor(tensors[i].numel, place[i].group, eco::GROUP_WIDE, true, tensors[i].fmt, eco::TILE_ELEMS, 0, &rows);
+    }
     e = hipGetDevice(&plan->device);
     if (e != hipSuccess) { delete plan; return fail_hip(e, "hipGetDevice"); }
     plan->cus = num_compute_units();
@@ -952,9 +973,15 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     for (size_t i = 0; i < n; ++i)
       if (tensors[i].fmt == f && short_odd(tensors[i], hp)) count_tensorwise(f, place(tensors[i]));
   }
-  // The wide lists again with the step's own grouping of rows, where it is the better one (see bytes_of) and the static tables hold
-  // its units; back to the other one if they do not.
+  // The wide lists again with the step's own grouping of rows, where it is the better one (see bytes_of, own_grouping_pays) and the
+  // static tables hold its units; back to the other one if not.
   const bool own = wide && HbmBound(bytes).half;
+  uint32_t sizes[2][4] = {{0}};
+  const auto used = [&](uint32_t (&bits)[4]) {
+    for (int f = 0; f < 4; ++f)
+      for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) bits[f] |= (count[f][eco::LIST_WIDE1 + nw - 1] ? 1u : 0u) << (nw - 1);
+  };
+  if (own) used(sizes[0]);
   for (int round = 0; own && round < 2; ++round) {
     rows.own_rows = round == 0;
     for (int f = 0; f < 4; ++f)
@@ -967,7 +994,8 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       const eco::Placement p = place(tensors[i]);
       if (p.kind == eco::UNIT_WIDE) count_wide(tensors[i], p);
     }
-    if (units <= MAX_UNITS) break;
+    if (round == 0) used(sizes[1]);
+    if (units <= MAX_UNITS && own_grouping_pays(bytes, sizes[1], sizes[0])) break;
   }
   const auto format_of = [&](size_t i) {
     const int32_t fmt = tensors[i].fmt;

@@ -231,8 +231,9 @@ inline FlatLaunch flat_launch(uint64_t numel, unsigned threads) {
 // takes `rows` consecutive groups.  One group a workgroup in general; groups of more than 512 elements whose length is
 // not a multiple of 512 leave lanes of their last wave idle, so where 2..8 of them together fill a whole number of
 // waves exactly (1408 = 2.75 waves: four rows in 11 waves; 576: eight rows in 9 waves) and the tensor is a whole number
-// of such bundles, a workgroup takes the bundle.  This is the initial quantizer's grouping, that of steps of less than 96 MB of arrays, of
-// steps of Adam with master weights, and of allocation-free calls whose tables hold no other; for the others see step_geometry.
+// of such bundles, a workgroup takes the bundle.  This is the initial quantizer's grouping, that of steps of less than 96 MB of arrays (of
+// less than 384 MB where the other takes more launches), of steps of Adam with master weights, and of allocation-free calls whose tables hold no
+// other; for the others see step_geometry.
 struct WideGeometry { uint32_t rows; uint32_t waves; uint64_t units; };
 inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = min(group size, numel)
   const uint64_t ngroups = (numel + g - 1) / g;

@@ -74,6 +74,10 @@ static const Case cases[] = {
     {"rows of 1800, master", FP8, F32, ADAM, ECO_MODE_MASTER, {{20, ROW, 1024, 1800}}, 1, 0},
     {"rows of 768, master, 4 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{5, ROW, 1024, 768}}, 1, 0},
     {"rows of 768, master, 8 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{10, ROW, 1024, 768}}, 1, 1},
+    /* the step's own grouping of rows takes a launch more than the other only from 384 MB on */
+    {"rows of 1024 and an odd number of 768, 110 MB", FP8, BF16, ADAM, ECO_MODE_ECO, {{10, ROW, 1024, 1024}, {10, ROW, 687, 768}}, 1, 0},
+    {"rows of 1024 and an odd number of 768, 440 MB", FP8, BF16, ADAM, ECO_MODE_ECO, {{40, ROW, 1024, 1024}, {40, ROW, 687, 768}}, 2, 3},
+    {"rows of 2048 and an odd number of 576, 110 MB", FP8, BF16, ADAM, ECO_MODE_ECO, {{5, ROW, 1024, 2048}, {10, ROW, 915, 576}}, 1, 0},
     {"rows of 1000, 7 M, in the cache", FP8, F32, ADAM, ECO_MODE_ECO, {{7, ROW, 1024, 1000}}, 1, 0},
     {"rows of 1000, 10 M", FP8, F32, ADAM, ECO_MODE_ECO, {{10, ROW, 1024, 1000}}, 1, 1},
     {"rows of 1000, SGDM, 40 M", FP8, F32, SGDM, ECO_MODE_ECO, {{40, ROW, 1024, 1000}}, 1, 0},
@@ -197,6 +201,14 @@ int main(void) {
       printf("no plan, rows of 1408: %d launches, %u workgroups of %u threads\n", launches, grid_of[1], block_of[1]);
       ++bad;
     }
+  }
+  list[1] = list[0];
+  list[0].numel = 10240 * 1024; list[0].group_size = 1024;
+  list[1].numel = 6871 * 768; list[1].group_size = 768;
+  launches = 0;
+  if (eco_step_tensors_noalloc(list, 2, &hp, NULL) != ECO_OK || launches != 2 || grid_of[1] != 10240 + 6871 || block_of[1] != 128) {
+    printf("no plan, rows of 1024 and of 768: %d launches, %u workgroups of %u threads\n", launches, grid_of[1], block_of[1]);
+    ++bad;
   }
   for (int i = 0; i < 12; ++i) {
     list[i] = list[0];
