@@ -310,7 +310,7 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
     // 28.8 / 29.5, 33 MB 12.1 / 10.7; 1800 28.4 / 29.2, 12.1 / 11.4); the others from 384 MB on (master weights, rows of 1152, 300 MB 89 / 87; SGDM,
     // rows of 1000, 315 MB 91 / 89).
     const bool worth = hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && (idle ? adam32 : kv.algo == eco::ALGO_ADAM_MASTER));
-    const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, units, load[nw].elements)
+    const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, bytes, nw, units, load[nw].elements)
                                                    : eco::wide_workgroups(kv, nw);
     // Adam with fp32 state in full rows has the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
     // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 2048: 467

@@ -257,11 +257,11 @@ inline WideGeometry wide_geometry(uint64_t numel, uint64_t g) {          // g = 
 //   fp32 state, Adam: 576 543 / 510 / 513 (3 rows in 4 waves), 640 561 / 510 / 515, 896 544 / 519 (4 in 7), 1152 513 / 512 / 516 (2
 //   in 5), 1408 507 (one) / 548, 2304 513 (one) / 517, 2816 512 (one) / 555; SGDM: 576 327 / 305 / 308, 1152 305 / 302 / 307, 1408 303
 //   (one) / 311; SGDM with master weights 1152 509 / 490 / 522.
-//   bf16 state, Adam, INT4: 576 389 / 307 / 312, 640 357 / 295 / 294, 896 303 / 293.  Without a cap on resident waves, which rows with
+//   bf16 state, Adam, INT4: 576 389 / 307 / 312, 640 357 / 295 / 294, 896 303 / 293.  Without a cap on resident waves, which most rows with
 //   idle lanes of this kind do not have, the exact bundle otherwise: 1408 315 / 313 (FP8 344 / 322), 2304 310 / 303, 2816 315 / 307;
 //   longer ones lose (1664 304 / 330 in 13 waves).
-//   Adam with master weights, without such a cap, which it does not have either: the exact bundle (576 790 / 764, 640 785 / 740, 1152 752 /
-//   762, 2304 767 / 770).  (With one, see wide_workgroups_idle, one row and other bundles are faster still; not taken up yet.)
+//   Adam with master weights, without such a cap: the exact bundle (576 790 / 764, 640 785 / 740, 1152 752 /
+//   762, 2304 767 / 770).  (With the cap that longer steps have, see wide_workgroups_idle, other bundles may be the better ones; not measured.)
 // Where it is all but as good and of up to 9 waves the exact bundle stays: row lengths that share a number of waves share a launch
 // (510 M elements in rows of 576 and of 2304, all in 9 waves 1833 us, in 4 and in 5 1843).
 inline WideGeometry step_geometry(uint64_t numel, uint64_t g, const StateLayout &l) {        // g = min(group size, numel)
@@ -375,29 +375,38 @@ inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw) {
   if (kv.algo == ALGO_SGDM) return nw <= 8 ? at_least(145) : 0;
   return at_least(kv.algo == ALGO_SGDM_EXACT ? 115 : 85);
 }
-// (b) where rows leave lanes idle, `elements` in the launch's `units` workgroups:
+// (b) where rows leave lanes idle, `elements` in the launch's `units` workgroups of `nw` waves (150 M elements, with / without, if not said
+// otherwise):
 //   Adam, fp32 state, 13.6: 520 523 / 590, 640 510 / 577, 1000 522 / 629, 1152 512 / 520, 1408 510 / 575, 1800 515 / 608, 2304 513 /
 //   527, 2816 512 / 545, 3000 519 / 596, 3328 521 / 557, 4000 511 / 612 (INT4 1000 510 / 586, 1800 485 / 566, 3000 490 / 567).
+//   Adam, bf16 state, workgroups of up to 4 and of 8 waves of which nineteen lanes in twenty are busy, from 600 MB on, in INT4 from 1 GB, 19.5:
+//   FP8 620 MB 1000 203 / 212, 1480 197 / 205, 2000 193 / 201, 2.8 GB 760 879 / 973, 1000 865 / 1012, 2000 854 / 982, 4000 850 / 905; INT4 1.4 GB 760 449 /
+//   464, 1000 446 / 477, 2000 433 / 459 (620 MB 760 212 / 199, 1000 200 / 208).  Others lose: 2528 in workgroups of 5 891 / 857, rows with
+//   fewer lanes busy (1344, INT4 620 MB) 197 / 188.
+//   Master weights, fp32 state, from 600 MB on, 9.5: FP8 620 MB 1000 204 / 221, 1344 198 / 216, 1800 203 / 226, 3000 208 / 218, 2.8 GB 966 /
+//   1179, 867 / 1056, 916 / 1131, 920 / 1107, 1152 872 / 941, 1408 876 / 960; of 4000 and longer two workgroups are more than that already.
 //   Master weights, bf16 state, 11.5: 1000 529 / 641, 1408 494 / 541, 1800 531 / 600, 2816 494 / 529.
-//   SGDM, fp32 state, 22: 640 302 / 338, 1000 308 / 345, 1152 302 / 305, 1408 306 / 321, 1800 308 / 318, 4000 310 / 346; with a stored error,
-//   16.5: 640 531 / 545, 1000 523 / 589, 1152 529 / 547, 1408 540 / 568, 1800 521 / 570, 3000 546 / 571; with master weights, 9.7: 640 486 /
-//   538, 1000 514 / 631, 1152 490 / 534, 1408 496 / 525, 1800 506 / 607, 2304 494 / 538, 3000 527 / 609.
+//   SGDM, fp32 state, 19.6: 640 302 / 338, 1152 302 / 305, 1408 306 / 321; FP8 1.4 GB (22 waves' worth / this) 760 441 / 426, 1000 467 / 452, 1344
+//   443 / 422, 1800 458 / 413, 5000 412 / 412; with a stored error, 15.6: 640 531 / 545, 1152 529 / 547, 1408 540 / 568, 3000 546 / 571; 1.4 GB
+//   (16.5 waves' worth / this) 1000 466 / 443, 1344 461 / 440, 4000 488 / 448; with master weights, 9.7: 640 486 / 538, 1000 514 / 631, 1152
+//   490 / 534, 1408 496 / 525, 1800 506 / 607, 2304 494 / 538, 3000 527 / 609.
 //   SGDM, bf16 state, with master weights 13.6, INT4 1.2 GB (FP8 alike): 520 355 / 385, 576 368 / 397, 640 356 / 390, 760 360 / 401, 1000 377 /
 //   449, 1496 387 / 423, 1800 360 / 399, 2304 354 / 372, 3000 353 / 397, 4000 366 / 398, 6912 370 / 370 (390 MB: 520 126 / 114, 1000 113 / 115, 3000
 //   113 / 118); with a stored error 20.4: 576 364 / 365, 760 359 / 380, 1000 371 / 403, 1408 368 / 377, 1496 377 / 405, 1800 362 / 373, 2304 371 / 371.
-//   None, though 150 M elements are faster with one -- other sizes are not measured: Adam with master weights and fp32 state (best cap / none:
-//   1000 744 / 924, 1800 742 / 891, 3000 733 / 887; in other bundles 1152 706 / 751, 1408 691 / 773, 2816 705 / 776), Adam with bf16 state (1000 INT4
-//   297 / 334, FP8 318 / 360).
-inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t units, uint64_t elements) {
+inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, unsigned nw, uint64_t units, uint64_t elements) {
   const auto at_least = [=](uint64_t tenths) {
     const uint64_t k = (tenths * units * TILE_ELEMS + 10 * elements - 1) / (10 * elements);
     return static_cast<unsigned>(k < 2 ? 2 : k);
   };
-  if (kv.state_bf16)
-    return kv.algo == ALGO_ADAM_MASTER ? at_least(115) : kv.algo == ALGO_SGDM_MASTER ? at_least(136) : kv.algo == ALGO_SGDM_EXACT ? at_least(204) : 0;
-  if (kv.algo == ALGO_ADAM) return at_least(136);
-  if (kv.algo == ALGO_ADAM_MASTER) return 0;
-  return at_least(kv.algo == ALGO_SGDM ? 220 : kv.algo == ALGO_SGDM_EXACT ? 165 : 97);
+  const uint64_t MB = 1000000;
+  const bool long_step = bytes >= 600 * MB, nearly_all = (nw <= 4 || nw == 8) && elements * 20 >= units * nw * TILE_ELEMS * 19;
+  switch (kv.algo) {
+    case ALGO_ADAM: return !kv.state_bf16 ? at_least(136) : nearly_all && bytes >= (kv.fmt == FMT_FP8 ? 600 : 1000) * MB ? at_least(195) : 0;
+    case ALGO_ADAM_MASTER: return kv.state_bf16 ? at_least(115) : long_step ? at_least(95) : 0;
+    case ALGO_SGDM: return kv.state_bf16 ? 0 : at_least(196);
+    case ALGO_SGDM_EXACT: return at_least(kv.state_bf16 ? 204 : 156);
+    default: return at_least(kv.state_bf16 ? 136 : 97);
+  }
 }
 // Waves per compute unit of a launch of one-wave units alone (short rows), `elements` in `units` of them; 0: as many as fit.
 // Again the smallest number with a certain number of waves' worth of busy lanes.  For arrays that come from HBM, 100 M elements,

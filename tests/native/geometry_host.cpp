@@ -105,13 +105,20 @@ int main() {
         CHECK(k == 0 || (k >= 2 && k * nw <= 32));
         if (algo == ALGO_ADAM && bf16) CHECK(k == 0 || (k * nw >= 20 && (nw <= 4 || nw == 8)));
       }
-      const bool capped = bf16 ? algo != ALGO_ADAM && algo != ALGO_SGDM : algo != ALGO_ADAM_MASTER;
       for (uint64_t g = 520; g < MAX_WIDE_GROUP; g += 8) {
         if (g % TILE_ELEMS == 0) continue;
         const uint64_t nw = (g + TILE_ELEMS - 1) / TILE_ELEMS;
-        const unsigned k = wide_workgroups_idle(kv, 1000, 1000 * g), half = wide_workgroups_idle(kv, 1000, 500 * g);
-        CHECK(capped ? k >= 2 && k <= 22 && half >= k && half <= 2 * k : k == 0 && half == 0);
-        if (k > 2) CHECK(k * g * 10 >= 97 * TILE_ELEMS && (k - 1) * g * 10 < 220 * TILE_ELEMS && k * nw <= 44);
+        const bool nearly_all = (nw <= 4 || nw == 8) && g * 20 >= nw * TILE_ELEMS * 19;
+        for (uint64_t mb : {100ull, 599ull, 600ull, 5000ull}) {
+          const bool capped = algo == ALGO_ADAM          ? !bf16 || (mb >= 600 && nearly_all)
+                              : algo == ALGO_ADAM_MASTER ? bf16 || mb >= 600
+                                                         : !(algo == ALGO_SGDM && bf16);
+          const unsigned k = wide_workgroups_idle(kv, mb * 1000000, (unsigned)nw, 1000, 1000 * g);
+          const unsigned half = wide_workgroups_idle(kv, mb * 1000000, (unsigned)nw, 1000, 500 * g);
+          CHECK(capped ? k >= 2 && k <= 22 : k == 0);
+          CHECK(half == 0 || (half >= k && half <= 2 * k));
+          if (k > 2) CHECK(k * g * 10 >= 95 * TILE_ELEMS && (k - 1) * g * 10 < 204 * TILE_ELEMS && k * nw <= 44);
+        }
       }
       for (uint64_t busy = 1; busy <= (uint64_t)TILE_ELEMS; ++busy) {
         for (uint64_t mb : {1ull, 100ull, 191ull, 192ull, 383ull, 384ull, 767ull, 768ull, 5000ull}) {

@@ -89,6 +89,9 @@ static const Case cases[] = {
     {"rows of 1000, bf16 SGDM master, 50 M", INT4, BF16, SGDM, ECO_MODE_MASTER, {{50, ROW, 1024, 1000}}, 1, 1},
     {"rows of 1000, bf16 stored error, 50 M", INT4, BF16, SGDM, ECO_MODE_EXACT, {{50, ROW, 1024, 1000}}, 1, 1},
     {"rows of 1000, bf16 SGDM, 90 M", INT4, BF16, SGDM, ECO_MODE_ECO, {{90, ROW, 1024, 1000}}, 1, 0},
+    {"rows of 1000, bf16, 90 M", FP8, BF16, ADAM, ECO_MODE_ECO, {{90, ROW, 1024, 1000}}, 1, 1},
+    {"rows of 1800, bf16, 90 M, too few lanes busy", FP8, BF16, ADAM, ECO_MODE_ECO, {{50, ROW, 1024, 1800}}, 1, 0},
+    {"rows of 1800, master, 44 M", FP8, F32, ADAM, ECO_MODE_MASTER, {{24, ROW, 1024, 1800}}, 1, 1},
     /* short rows: a launch of one-wave units alone has caps of its own, a few beside full tiles ride under theirs */
     {"rows of 400, SGDM, 57 M", FP8, F32, SGDM, ECO_MODE_ECO, {{140, ROW, 1024, 400}}, 1, 1},
     {"rows of 328, SGDM, 57 M, too few lanes busy", FP8, F32, SGDM, ECO_MODE_ECO, {{170, ROW, 1024, 328}}, 1, 0},
