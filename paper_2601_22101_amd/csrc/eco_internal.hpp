@@ -79,7 +79,7 @@ inline uint64_t array_bytes(uint64_t numel, int fmt, const StateLayout &l) {
 inline bool one_pass_pays(const StateLayout &l, uint64_t bytes, uint64_t slabs, unsigned cus, bool tails, bool beside_longer) {
   if (slabs <= cus && !tails && !beside_longer) return true;
   enum { F32_ADAM, F32_SGDM, BF16_ADAM, BF16_SGDM, MASTER_ADAM, MASTER_SGDM };
-  constexpr uint64_t from_mb[][4] = {{56, 96, 224, 260}, {48, 96, 224, 260}, {100, 208, 320, 416}, {384, 384, 384, 384}, {80, 800, 1100, 1100},
+  constexpr uint64_t from_mb[][4] = {{56, 96, 224, 260}, {48, 96, 200, 228}, {100, 208, 320, 416}, {384, 384, 384, 384}, {80, 800, 1100, 1100},
                                      {64, 130, 1000, 1000}};
   const int row = l.master ? (l.adam ? MASTER_ADAM : MASTER_SGDM) : !l.state_bf16 || l.aux ? (l.adam ? F32_ADAM : F32_SGDM) : l.adam ? BF16_ADAM : BF16_SGDM;
   return bytes >= 1000000 * from_mb[row][(tails ? 1 : 0) + (beside_longer ? 2 : 0)];

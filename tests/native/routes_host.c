@@ -142,6 +142,7 @@ static const Case cases[] = {
     {"38 M beside a long one, SGDM, master", FP8, F32, SGDM, ECO_MODE_MASTER, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 4, 0},
     {"38 M beside a long one, stored error", FP8, F32, SGDM, ECO_MODE_EXACT, {{128, TENSOR, 1, 300000}, {1, TENSOR, 1, 6000000}}, 6, 0},
     /* ... and what makes one pass of a list with tails beside a longer tensor, by the kind of state */
+    {"230 MB, SGDM", FP8, F32, SGDM, ECO_MODE_ECO, {{7, TENSOR, 1, 4700000}, {1, TENSOR, 1, 300007}, {1, TENSOR, 1, 5000000}}, 7, 0},
     {"420 MB", FP8, F32, ADAM, ECO_MODE_ECO, {{9, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 40},
     {"420 MB, INT4 bf16", INT4, BF16, ADAM, ECO_MODE_ECO, {{14, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 40},
     {"420 MB, SGDM INT4", INT4, F32, SGDM, ECO_MODE_ECO, {{14, TENSOR, 1, 4700000}, {1, TENSOR, 1, 8193}, {1, TENSOR, 1, 6000000}}, 7, 40},
