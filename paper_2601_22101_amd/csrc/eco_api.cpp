@@ -308,7 +308,7 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
     // Workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too (4 M elements 9.7 against 10.2 us); master weights
     // with fp32 state in full rows, and Adam with fp32 state in rows with idle lanes, from 96 MB on (us, with / without: rows of 1000 88 MB
     // 28.8 / 29.5, 33 MB 12.1 / 10.7; 1800 28.4 / 29.2, 12.1 / 11.4); the others from 384 MB on (master weights, rows of 1152, 300 MB 89 / 87; SGDM,
-    // rows of 1000, 315 MB 91 / 89).
+    // rows of 1000, 315 MB 91 / 89), of rows with idle lanes some later still (see wide_workgroups_idle).
     const bool worth = hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && (idle ? adam32 : kv.algo == eco::ALGO_ADAM_MASTER));
     const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, bytes, nw, units, load[nw].elements)
                                                    : eco::wide_workgroups(kv, nw);
