@@ -122,7 +122,8 @@ struct Lists {                           // the launch lists of one storage form
   size_t off_tile = 0, off_extra = 0, off_wide[eco::MAX_WIDE_WAVES + 1] = {0}, off_tw_tile = 0, off_tw_tensor = 0, off_slots = 0,
          off_tile_max = 0, off_slab = 0, off_resident = 0, off_tail_max = 0, off_slab_max = 0, off_counts = 0, off_deferred = 0;
   uint64_t tensors = 0, most_tw_tiles = 0, tails = 0;
-  struct WideLoad { uint64_t idle, elements; };          // of a wide list: units that leave lanes idle; elements (0: the one-wave units')
+  struct WideLoad { uint64_t idle, elements, off_lines; };   // of a wide list: units that leave lanes idle; elements (0: the one-wave units'); those
+                                                         // whose waves start off the lines of memory (0: of the full tiles as well)
   WideLoad load[eco::MAX_WIDE_WAVES + 1] = {};
   std::vector<uint32_t> one;             // all but the tensor-wise tensors as one launch, where that is the better way: workgroup -> tensor
   size_t off_one = 0;
@@ -183,7 +184,10 @@ int num_compute_units() {
 // That holds for arrays that come from HBM (see HbmBound): where a step finds them in the cache before it, a cap costs up
 // to 24 % (bf16 state, us, without / with: FP8 4 M elements 9.3 / 10.4, 32 M 61.1 / 60.3, 64 M 142 / 137; INT4 32 M 56.2 / 56.3,
 // 48 M 85.0 / 88.2, 64 M 129.4 / 127.5; master weights 4 M 14.0 / 15.7, 32 M 105.1 / 107.7, 64 M 226 / 213; unquantized 4 M 8.6 / 10.4,
-// 16 M 38.9 / 37.8).  The caps of fp32 state have no such line.
+// 16 M 38.9 / 37.8).  The caps of fp32 state
+// as well, since waves take whole lines (see exchange_chunks; us, with / without): Adam 40 MB 15.2 / 13.4, 120 MB 37.0 / 35.6 (35.2 at 20 waves),
+// master weights 40 MB 15.2 / 13.1, 120 MB 35.0 / 32.1, 240 MB 65.6 / 66.2, SGDM 14.4 / 12.2, 32.8 / 31.9, 62.6 / 61.8, with a stored error 13.5 /
+// 11.5, 33.9 / 32.9, 64.6 / 63.2, with master weights 12.7 / 10.2, 33.3 / 32.0, 64.1 / 60.7.
 int default_waves(const eco::KernelVariant &kv, const HbmBound &hbm) {
   if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) {
     if (kv.state_bf16) return (eco::algo_is_adam(kv.algo) ? hbm.half : hbm.fully) ? 13 : 0;
@@ -195,11 +199,25 @@ int default_waves(const eco::KernelVariant &kv, const HbmBound &hbm) {
     return kv.algo == eco::ALGO_ADAM_MASTER ? 12 : 0;
   }
   switch (kv.algo) {
-    case eco::ALGO_ADAM: return 12;          // 20.1 B/parameter
-    case eco::ALGO_ADAM_MASTER: return 8;    // 27.0
-    case eco::ALGO_SGDM: return 14;          // 12.1
-    case eco::ALGO_SGDM_MASTER: return 8;    // 19.0
-    default: return 11;                      // SGDM with a stored error: 20.1
+    case eco::ALGO_ADAM: return hbm.fully ? 12 : hbm.half ? 20 : 0;          // 20.1 B/parameter
+    case eco::ALGO_ADAM_MASTER: return hbm.fully ? 8 : 0;    // 27.0
+    case eco::ALGO_SGDM: return hbm.fully ? 14 : 0;          // 12.1
+    case eco::ALGO_SGDM_MASTER: return hbm.fully ? 8 : 0;    // 19.0
+    default: return hbm.fully ? 11 : 0;                      // SGDM with a stored error: 20.1
+  }
+}
+
+// The same for launches that pass the caches by.  Adam with fp32 state wants more waves as long as part of the arrays is still in the cache (us,
+// 12 / 20 waves: 29 M elements 117 / 112, 54 M 175 / 173, 137 M 439 / 438, 870 M 2734 / 2857).  2.8 GB of traffic, default_waves' / this: SGDM 430 /
+// 421, with a stored error 442 / 430, with master weights 453 / 436.
+int streaming_waves(const eco::KernelVariant &kv, uint64_t bytes) {
+  if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID || kv.state_bf16) return default_waves(kv, HbmBound(UINT64_MAX));
+  switch (kv.algo) {
+    case eco::ALGO_ADAM: return bytes < 600000000 ? 20 : 12;
+    case eco::ALGO_ADAM_MASTER: return 8;
+    case eco::ALGO_SGDM: return 16;
+    case eco::ALGO_SGDM_MASTER: return 13;
+    default: return 14;
   }
 }
 
@@ -278,6 +296,28 @@ eco::KernelVariant variant_for(const eco_hparams_t *hp, int f) {
   return kv;
 }
 
+// Whether the waves that step a tensor start off the 128-byte lines of its arrays: its units are no multiple of 64 elements, the line of a
+// bf16 array, or an array does not begin on a line.
+bool off_lines(const eco_tensor_t &t, const eco::Placement &p) {
+  const uintptr_t arrays = reinterpret_cast<uintptr_t>(t.weights) | reinterpret_cast<uintptr_t>(t.grad) | reinterpret_cast<uintptr_t>(t.m) |
+                           reinterpret_cast<uintptr_t>(t.v) | reinterpret_cast<uintptr_t>(t.aux);
+  const bool units_of_rows = p.kind == eco::UNIT_WIDE || p.kind == eco::UNIT_ROWS || p.kind == eco::UNIT_ROW;
+  return (arrays & 127) != 0 || (units_of_rows && p.units > 1 && p.rows * p.group % 64 != 0);
+}
+
+// Which launches of a step pass the caches by (CACHED and the others beside it in the kernels say what that is worth), a bit each: 0 the
+// full-tile one, n the wide groups of n waves.  Arrays that the 256 MB cache before HBM still holds from the step before lose by it, and so do
+// waves that start off the lines of memory, whose instructions then write parts of two (us, us usual / streamed) -- by bytes of the arrays, groups
+// of 128: fp32 state, Adam 250 MB 71 / 74, 280 89 / 82, 340 103 / 99, master weights 69 / 74, 91 / 82, 107 / 97, SGDM 65 / 69, 82 / 77; bf16
+// state, INT4, Adam 310 MB 82 / 83, 340 90 / 90, 420 99 / 97, 640 187 / 168, SGDM (FP8) 310 75 / 78, 340 84 / 85, 420 101 / 95.  Rows of 1.6 GB, fp32
+// state: 1120 (pairs: 35 lines) 491 / 451, 2016 517 / 507, 544 532 / 555, 1000 527 / 654, 6944 545 / 554; bf16 state 1120 528 / 620, 320 590 / 576.
+uint32_t stream_launches(uint64_t bytes, bool f32, uint64_t tiles, const Lists::WideLoad (&load)[eco::MAX_WIDE_WAVES + 1]) {
+  if (bytes < (f32 ? 280000000u : 384000000u)) return 0;
+  uint32_t launches = load[0].off_lines * 8 <= load[0].elements + tiles * eco::TILE_ELEMS ? 1 : 0;
+  for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) launches |= (load[nw].off_lines * 8 <= load[nw].elements ? 1u : 0u) << nw;
+  return launches;
+}
+
 // The scalar part of the kernel arguments: step constants, random-stream key, launch options.
 typedef Lists::WideLoad WideLoads[eco::MAX_WIDE_WAVES + 1];
 void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const WideLoads &load, uint64_t bytes,
@@ -293,30 +333,33 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
   sl->max_launch_threads = opt_threads > 0 ? static_cast<uint64_t>(opt_threads) : eco::MAX_LAUNCH_THREADS;
   a->unit_base = 0;
   const HbmBound hbm(bytes);
-  const int waves = default_waves(kv, hbm);
+  sl->stream = stream_launches(bytes, !kv.state_bf16, a->num_tiles, load);
+  const int waves = default_waves(kv, hbm), tile_waves = sl->stream & 1u ? streaming_waves(kv, bytes) : waves;
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
   const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
   // a launch of one-wave units beside few tiles does not have the tiles' cap, which counts on every lane; short rows alone have
   // one of their own
   const bool units = (kv.fmt == eco::FMT_FP8 || kv.fmt == eco::FMT_INT4) && a->num_extra > a->num_tiles / 8;
   const unsigned resident = units && !a->num_tiles && load[0].elements ? eco::unit_workgroups(kv, bytes, a->num_extra, load[0].elements) : 0;
-  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? eco::lds_for_workgroups(resident) : lds_for_waves(waves, 512);
+  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? eco::lds_for_workgroups(resident) : lds_for_waves(tile_waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
     const uint64_t units = sl->num_wide[nw];
     if (!units) continue;
     const bool idle = load[nw].idle > units / 8, adam32 = kv.algo == eco::ALGO_ADAM && !kv.state_bf16;
-    // Workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too (4 M elements 9.7 against 10.2 us); master weights
-    // with fp32 state in full rows, and Adam with fp32 state in rows with idle lanes, from 96 MB on (us, with / without: rows of 1000 88 MB
-    // 28.8 / 29.5, 33 MB 12.1 / 10.7; 1800 28.4 / 29.2, 12.1 / 11.4); the others from 384 MB on (master weights, rows of 1152, 300 MB 89 / 87; SGDM,
-    // rows of 1000, 315 MB 91 / 89), of rows with idle lanes some later still (see wide_workgroups_idle).
-    const bool worth = hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && (idle ? adam32 : kv.algo == eco::ALGO_ADAM_MASTER));
-    const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, bytes, nw, units, load[nw].elements)
-                                                   : eco::wide_workgroups(kv, nw);
+    // Workgroups of 4 and 8 waves with bf16 state gain by their cap in the cache too (4 M elements 9.7 against 10.2 us); Adam with fp32 state in
+    // rows with idle lanes from 96 MB on (us, with / without: rows of 1000 88 MB 28.8 / 29.5, 33 MB 12.1 / 10.7; 1800 28.4 / 29.2, 12.1 / 11.4); the
+    // others from 384 MB on (master weights, rows of 1152, 300 MB 89 / 87, of 2048 120 MB 35.9 / 33.1; SGDM, rows of 1000, 315 MB 91 / 89), of rows
+    // with idle lanes some later still (see wide_workgroups_idle).  Launches that pass the caches by from 450 MB on (Adam, fp32 state, rows of 2048
+    // 340 MB 95 / 90, 590 MB 174 / 191, 4096 330 MB 91.7 / 88.9, 500 MB 147 / 161).
+    const bool streamed = (sl->stream >> nw & 1u) != 0;
+    const bool worth = streamed ? bytes >= 450000000 : hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && idle && adam32);
+    const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, bytes, nw, units, load[nw].elements, streamed)
+                                                   : eco::wide_workgroups(kv, nw, streamed);
     // Adam with fp32 state in full rows has the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
     // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 2048: 467
     // against 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
     const uint32_t per_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves, 256);
-    sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (adam32 && !idle) ? std::min(per_wave * nw, 65536u) : eco::lds_for_workgroups(k);
+    sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (adam32 && !idle && !streamed) ? std::min(per_wave * nw, 65536u) : eco::lds_for_workgroups(k);
   }
   sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv, hbm), 256);
 }
@@ -708,12 +751,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
         g.resident.push_back(idx);
       } else {
         elements[f] += t.numel;
-        if (p.list == eco::LIST_EXTRA) g.load[0].elements += t.numel;
-        if (p.kind == eco::UNIT_WIDE) {
-          Lists::WideLoad &w = g.load[p.list - eco::LIST_WIDE1 + 1];
-          w.idle += p.idle ? p.units : 0;
-          w.elements += t.numel;
-        }
+        Lists::WideLoad &w = g.load[p.kind == eco::UNIT_WIDE ? p.list - eco::LIST_WIDE1 + 1 : 0];
+        if (p.kind == eco::UNIT_WIDE) w.idle += p.idle ? p.units : 0;
+        if (p.list != eco::LIST_TILE) w.elements += t.numel;
+        if (off_lines(t, p)) w.off_lines += t.numel;
       }
       list.insert(list.end(), static_cast<size_t>(p.units), idx);
       if (p.tail) {
@@ -912,6 +953,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     units += p.units;
     w.idle += p.idle ? p.units : 0;
     w.elements += t.numel;
+    w.off_lines += off_lines(t, p) ? t.numel : 0;
   };
   const auto count_tensorwise = [&](int f, const eco::Placement &p) {
     count[f][eco::LIST_TW_TILES] += p.units;
@@ -951,6 +993,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     count[f][p.list] += p.units;
     units += p.units;
     if (p.list == eco::LIST_EXTRA) load[f][0].elements += tensors[i].numel;
+    load[f][0].off_lines += off_lines(tensors[i], p) ? tensors[i].numel : 0;
     if (p.tail) {
       count[f][eco::LIST_EXTRA] += 1;
       units += 1;
@@ -968,6 +1011,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       Lists::WideLoad &w = load[f][p.kind == eco::UNIT_WIDE ? p.list - eco::LIST_WIDE1 + 1 : 0];
       w.idle -= p.idle ? p.units : 0;
       w.elements -= tensors[i].numel;
+      w.off_lines -= off_lines(tensors[i], p) ? tensors[i].numel : 0;
     }
     odd_along[f] = true;
     for (size_t i = 0; i < n; ++i)
@@ -988,7 +1032,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
         units -= count[f][eco::LIST_WIDE1 + nw - 1];
         count[f][eco::LIST_WIDE1 + nw - 1] = 0;
-        load[f][nw] = Lists::WideLoad{0, 0};
+        load[f][nw] = Lists::WideLoad{0, 0, 0};
       }
     for (size_t i = 0; i < n; ++i) {
       const eco::Placement p = place(tensors[i]);
@@ -1004,6 +1048,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   for (int f = eco::FMT_BF16_PLAIN; f <= eco::FMT_FP32_ID && plain_home >= 0; ++f) {
     count[plain_home][eco::LIST_EXTRA] += count[f][eco::LIST_EXTRA];
     load[plain_home][0].elements += load[f][0].elements;
+    load[plain_home][0].off_lines += load[f][0].off_lines;
     count[f][eco::LIST_EXTRA] = 0;
   }
   (void)hipGetLastError();
@@ -1187,7 +1232,7 @@ eco_status_t eco_bandwidth_probe(int32_t kind, void *codes, void *scales, const 
   eco::KernelVariant kv;
   kv.fmt = eco::FMT_FP8; kv.state_bf16 = 0; kv.scale_bf16 = 0; kv.algo = eco::ALGO_ADAM; kv.round = eco::ROUND_SR;
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
-  const uint32_t lds = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(default_waves(kv, HbmBound(0)), 512);
+  const uint32_t lds = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(default_waves(kv, HbmBound(UINT64_MAX)), 512);
   (void)hipGetLastError();
   const hipError_t e = eco::launch_bandwidth_probe(kind, codes, scales, grad, m, v, numel, lds, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? ECO_OK : fail_hip(e, "probe kernel launch");

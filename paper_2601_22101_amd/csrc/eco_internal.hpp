@@ -171,6 +171,7 @@ struct StepLaunch {
   uint32_t wide_offset[MAX_WIDE_WAVES + 1];
   uint32_t num_wide[MAX_WIDE_WAVES + 1];
   unsigned resident_wgs;           // workgroups of the one-pass tensor-wise kernel: one per compute unit
+  uint32_t stream;                 // which launches pass the caches by (see stream_pays), a bit each: 0 the full-tile one, n the wide groups of n waves
   int extra_in;                    // which launch the one-wave units ride in: 0 the full-tile one, n the wide groups of n waves
   const SmallArgs *small;          // if set, one launch of eco_step_small_kernel (arguments by value),
   uint64_t list_wgs;               // or if not 0, of the list kernel,
@@ -367,8 +368,11 @@ __attribute__((always_inline)) inline Placement place_tensor(uint64_t numel, uin
 //   SGDM, fp32 state, 14.5: 768 304 / 328, 1024 310 / 319, 2048 299 / 332, 3072 301 / 332, 3584 302 / 338, 4096 314 / 332 (larger
 //   workgroups lose: 2304, two of 9 waves, 332 / 309); with a stored error, 11.5: 768 510 / 551, 1024 511 / 525, 2048 501 / 527, 4096 531 / 537; with master weights, 8.5: 768 489 /
 //   529, 1024 507 / 521, 2048 511 / 541, 4096 515 / 532.
-inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw) {
+// streamed: where the launch passes the caches by (us, the others' / these: Adam, fp32 state, rows of 1024 180 / 174, 2048 544 / 470; with master
+// weights 1024 466 / 446).
+inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, bool streamed = false) {
   const auto at_least = [nw](unsigned tenths) { const unsigned k = (tenths + 10 * nw - 1) / (10 * nw); return k < 2 ? 2 : k; };
+  if (streamed && !kv.state_bf16 && algo_is_adam(kv.algo)) return at_least(kv.algo == ALGO_ADAM ? 120 : 80);
   if (kv.algo == ALGO_ADAM) return kv.state_bf16 && (nw <= 4 || nw == 8) ? at_least(200) : 0;
   if (kv.algo == ALGO_ADAM_MASTER) return kv.state_bf16 ? at_least(115) : nw <= 5 ? 10 / nw : 2;
   if (kv.state_bf16) return 0;
@@ -393,7 +397,10 @@ inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw) {
 //   SGDM, bf16 state, with master weights 13.6, INT4 1.2 GB (FP8 alike): 520 355 / 385, 576 368 / 397, 640 356 / 390, 760 360 / 401, 1000 377 /
 //   449, 1496 387 / 423, 1800 360 / 399, 2304 354 / 372, 3000 353 / 397, 4000 366 / 398, 6912 370 / 370 (390 MB: 520 126 / 114, 1000 113 / 115, 3000
 //   113 / 118); with a stored error 20.4: 576 364 / 365, 760 359 / 380, 1000 371 / 403, 1408 368 / 377, 1496 377 / 405, 1800 362 / 373, 2304 371 / 371.
-inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, unsigned nw, uint64_t units, uint64_t elements) {
+// Adam with fp32 state and SGDM with a stored error, where rows start off the lines of memory and are not streamed (1.6 GB of arrays, 13.6 and
+// 15.6 / this): 11.5 544 532 / 498, 560 556 / 512, 1000 524 / 501, 2016 517 / 490, in the cache 1152 66.4 / 64.8; 11.8 1000 552 / 500, 2016 514 / 505.
+inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, unsigned nw, uint64_t units, uint64_t elements,
+                                     bool streamed = false) {
   const auto at_least = [=](uint64_t tenths) {
     const uint64_t k = (tenths * units * TILE_ELEMS + 10 * elements - 1) / (10 * elements);
     return static_cast<unsigned>(k < 2 ? 2 : k);
@@ -401,16 +408,19 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, un
   const uint64_t MB = 1000000;
   const bool long_step = bytes >= 600 * MB, nearly_all = (nw <= 4 || nw == 8) && elements * 20 >= units * nw * TILE_ELEMS * 19;
   switch (kv.algo) {
-    case ALGO_ADAM: return !kv.state_bf16 ? at_least(136) : nearly_all && bytes >= (kv.fmt == FMT_FP8 ? 600 : 1000) * MB ? at_least(195) : 0;
+    case ALGO_ADAM: return !kv.state_bf16 ? at_least(streamed ? 136 : 115) : nearly_all && bytes >= (kv.fmt == FMT_FP8 ? 600 : 1000) * MB ? at_least(195) : 0;
     case ALGO_ADAM_MASTER: return kv.state_bf16 ? at_least(115) : long_step ? at_least(95) : 0;
     case ALGO_SGDM: return kv.state_bf16 ? 0 : at_least(196);
-    case ALGO_SGDM_EXACT: return at_least(kv.state_bf16 ? 204 : 156);
+    case ALGO_SGDM_EXACT: return at_least(kv.state_bf16 ? 204 : streamed ? 156 : 118);
     default: return at_least(kv.state_bf16 ? 136 : 97);
   }
 }
 // Waves per compute unit of a launch of one-wave units alone (short rows), `elements` in `units` of them; 0: as many as fit.
 // Again the smallest number with a certain number of waves' worth of busy lanes.  For arrays that come from HBM, 100 M elements,
 // us, with / without --
+//   (Before waves took whole lines at a time, see exchange_chunks: since then fp32 state 13.4 instead of 10.3, 1.6 GB 200 540 / 518, streamed 192
+//   510 / 471, 384 500 / 476; master weights 9 instead of 7, 200 582 / 544, streamed 192 508 / 479, 384 498 / 481; a stored error 12 instead of
+//   13.4, 200 583 / 495, streamed 384 485 / 462.)
 //   Adam, fp32 state, 10.3: rows of 48 369 / 389, 160 368 / 393, 200 365 / 391, 328 378 / 395, 400 362 / 406, 504 393 / 415 (INT4 354 / 368,
 //   353 / 372, 359 / 370, 361 / 373, 355 / 383, 366 / 395); bf16 state, 20.5, where nine lanes in ten are busy: INT4 48 214 / 219, 160
 //   217 / 225, 504 211 / 229 (FP8 227 / 238, 234 / 245, 223 / 252), others none (400 243 / 222).
@@ -443,10 +453,10 @@ inline unsigned unit_workgroups(const KernelVariant &kv, uint64_t bytes, uint64_
     }
   }
   switch (kv.algo) {
-    case ALGO_ADAM: return at_least(103);
-    case ALGO_ADAM_MASTER: return at_least(70);
+    case ALGO_ADAM: return at_least(134);
+    case ALGO_ADAM_MASTER: return at_least(90);
     case ALGO_SGDM: return most ? at_least(155) : 0;
-    case ALGO_SGDM_EXACT: return at_least(134);
+    case ALGO_SGDM_EXACT: return at_least(120);
     default: return at_least(82);
   }
 }

@@ -10,18 +10,23 @@ namespace eco {
 // ------------------------------------------------------------------------ plain optimizer step
 // Launches of their own for unquantized tensors: a plan without quantized ones, or one whose unquantized tensors are
 // too many to ride along as one-wave units (an embedding, attention matrices).  A wave per 512-element tile.
-template <int FMT, bool STATE_BF16, bool ADAM>
+template <int FMT, bool STATE_BF16, bool ADAM, int CP>
 __global__ __launch_bounds__(WG_THREADS) void eco_plain_kernel(const StepArgs a) {
   const uint32_t tile = blockIdx.x + a.unit_base;
   const TensorDesc td = load_tensor_desc(a, load_table(a.extra_tensor, tile));
   const uint64_t tile_off = (uint64_t)(tile - td.first_unit) * TILE_ELEMS, e0 = tile_off + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
-  if (tile_off + TILE_ELEMS <= td.numel) plain_lane<FMT == FMT_BF16_PLAIN, STATE_BF16, ADAM, ACC_FULL>(a, td, e0, 8);
-  else plain_lane<FMT == FMT_BF16_PLAIN, STATE_BF16, ADAM, ACC_LANE>(a, td, e0, valid_from(e0, td.numel));
+  if (tile_off + TILE_ELEMS <= td.numel) plain_lane<FMT == FMT_BF16_PLAIN, STATE_BF16, ADAM, ACC_FULL, CP>(a, td, e0, 8);
+  else plain_lane<FMT == FMT_BF16_PLAIN, STATE_BF16, ADAM, ACC_LANE, CP>(a, td, e0, valid_from(e0, td.numel));
 }
 
 hipError_t launch_step_plain(const KernelVariant &kv, const StepLaunch &sl, hipStream_t stream) {
-#define ECO_LAUNCH(F, ST, AD) \
-  ECO_CHUNKS_CHECKED((eco_plain_kernel<F, ST, AD>), sl.args.num_extra, WG_THREADS, sl.lds_bytes, stream, sl.args, sl.max_tile_threads)
+#define ECO_LAUNCH(F, ST, AD)                                                                                                               \
+  do {                                                                                                                                      \
+    if (sl.stream & 1u)                                                                                                                          \
+      ECO_CHUNKS_CHECKED((eco_plain_kernel<F, ST, AD, STREAM_WAVE>), sl.args.num_extra, WG_THREADS, sl.lds_bytes, stream, sl.args, sl.max_tile_threads); \
+    else                                                                                                                                    \
+      ECO_CHUNKS_CHECKED((eco_plain_kernel<F, ST, AD, CACHED>), sl.args.num_extra, WG_THREADS, sl.lds_bytes, stream, sl.args, sl.max_tile_threads); \
+  } while (0)
   const int key = (kv.fmt == FMT_FP32_ID ? 4 : 0) | (kv.state_bf16 ? 2 : 0) | (algo_is_adam(kv.algo) ? 0 : 1);
   switch (key) {
     case 0: ECO_LAUNCH(FMT_BF16_PLAIN, false, true); break;

@@ -46,6 +46,19 @@ __device__ __forceinline__ bool use_vector(int nvalid) {
   return ACC == ACC_FULL || ((ACC == ACC_LANE || ACC == ACC_WHOLE) && nvalid == 8);
 }
 
+typedef float eco_f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t eco_u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t eco_u32x2_t __attribute__((ext_vector_type(2)));
+// How a kernel's vector accesses treat the caches.  CACHED: as usual.  The others are for arrays that come from HBM (see stream_pays): loads
+// with the non-temporal hint, and stores with the given bits of the instruction, of which sc1 writes through the L2.  Neither half alone
+// helps, and neither where an instruction covers halves of lines (see exchange_chunks): a copy of the FP8 Adam step's byte mix, 268 M
+// elements, us: 985; instructions over whole lines 944; with loads nt 1008, stores nt 945, both 865, loads nt and stores sc1 nt 837.
+// STREAM_WAVE, of independent waves: 700 M elements in groups of 128 2390 -> 2195 (sc1 alone 2230).  STREAM_GROUP, of workgroups that store
+// behind a barrier: rows of 1152 2303 -> 2118 (with nt 2473), 2304 2342 -> 2142 (2443), 3072 2384 -> 2176 (2270).
+enum : int { CACHED = 0, STREAM_GROUP = 16, STREAM_WAVE = 16 | 2 };          // sc1; sc1 and nt
+template <int CP, class V>
+__device__ __forceinline__ V load_vec(const V *p) { return CP != CACHED ? __builtin_nontemporal_load(p) : *p; }
+
 template <int ACC>
 __device__ __forceinline__ void load_f32x8(const float *p, int nvalid, float (&out)[8]) {
   if (use_vector<ACC>(nvalid)) {
@@ -59,10 +72,10 @@ __device__ __forceinline__ void load_f32x8(const float *p, int nvalid, float (&o
   }
 }
 
-template <int ACC>
+template <int ACC, int CP = CACHED>
 __device__ __forceinline__ void load_bf16x8(const uint16_t *p, int nvalid, float (&out)[8]) {
   if (use_vector<ACC>(nvalid)) {
-    const uint4 q = *reinterpret_cast<const uint4 *>(p);
+    const eco_u32x4_t q = load_vec<CP>(reinterpret_cast<const eco_u32x4_t *>(p));
     out[0] = bf16_lo(q.x); out[1] = bf16_hi(q.x); out[2] = bf16_lo(q.y); out[3] = bf16_hi(q.y);
     out[4] = bf16_lo(q.z); out[5] = bf16_hi(q.z); out[6] = bf16_lo(q.w); out[7] = bf16_hi(q.w);
   } else {
@@ -71,24 +84,11 @@ __device__ __forceinline__ void load_bf16x8(const uint16_t *p, int nvalid, float
   }
 }
 
-// Tuning builds only (-DECO_NT_STORES): full-tile vector stores carry the non-temporal hint.
-typedef float eco_f32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t eco_u32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t eco_u32x2_t __attribute__((ext_vector_type(2)));
-template <class V>
-__device__ __forceinline__ void store_vec(V *p, V x) {
-#ifdef ECO_NT_STORES
-  __builtin_nontemporal_store(x, p);
-#else
-  *p = x;
-#endif
-}
-
 template <int ACC>
 __device__ __forceinline__ void store_f32x8(float *p, int nvalid, const float (&x)[8]) {
   if (use_vector<ACC>(nvalid)) {
-    store_vec(reinterpret_cast<eco_f32x4_t *>(p), eco_f32x4_t{x[0], x[1], x[2], x[3]});
-    store_vec(reinterpret_cast<eco_f32x4_t *>(p) + 1, eco_f32x4_t{x[4], x[5], x[6], x[7]});
+    reinterpret_cast<eco_f32x4_t *>(p)[0] = eco_f32x4_t{x[0], x[1], x[2], x[3]};
+    reinterpret_cast<eco_f32x4_t *>(p)[1] = eco_f32x4_t{x[4], x[5], x[6], x[7]};
   } else if (ACC != ACC_WHOLE) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
@@ -102,7 +102,7 @@ __device__ __forceinline__ void store_bf16x8(uint16_t *p, int nvalid, const floa
 #pragma unroll
   for (int j = 0; j < 4; ++j) h[j] = f32x2_to_bf16x2_rne(x[2 * j], x[2 * j + 1]);
   if (use_vector<ACC>(nvalid)) {
-    store_vec(reinterpret_cast<eco_u32x4_t *>(p), eco_u32x4_t{h[0], h[1], h[2], h[3]});
+    *reinterpret_cast<eco_u32x4_t *>(p) = eco_u32x4_t{h[0], h[1], h[2], h[3]};
   } else if (ACC != ACC_WHOLE) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
@@ -123,15 +123,15 @@ __device__ __forceinline__ void store_state8(void *base, uint64_t e0, int nvalid
 }
 
 // 8 codes of one lane: two dwords of E4M3 bytes, or one dword of INT4 nibbles (in c[0]).
-template <int FMT, int ACC>
+template <int FMT, int ACC, int CP = CACHED>
 __device__ __forceinline__ void load_codes8(const void *base, uint64_t e0, int nvalid, uint32_t (&c)[2]) {
   const uint8_t *p = static_cast<const uint8_t *>(base) + (FMT == FMT_FP8 ? e0 : (e0 >> 1));
   if (use_vector<ACC>(nvalid)) {
     if (FMT == FMT_FP8) {
-      const uint2 q = *reinterpret_cast<const uint2 *>(p);
+      const eco_u32x2_t q = load_vec<CP>(reinterpret_cast<const eco_u32x2_t *>(p));
       c[0] = q.x; c[1] = q.y;
     } else {
-      c[0] = *reinterpret_cast<const uint32_t *>(p); c[1] = 0;
+      c[0] = load_vec<CP>(reinterpret_cast<const uint32_t *>(p)); c[1] = 0;
     }
   } else {
     c[0] = 0; c[1] = 0;
@@ -147,8 +147,8 @@ template <int FMT, int ACC>
 __device__ __forceinline__ void store_codes8(void *base, uint64_t e0, int nvalid, const uint32_t (&c)[2]) {
   uint8_t *p = static_cast<uint8_t *>(base) + (FMT == FMT_FP8 ? e0 : (e0 >> 1));
   if (use_vector<ACC>(nvalid)) {
-    if (FMT == FMT_FP8) store_vec(reinterpret_cast<eco_u32x2_t *>(p), eco_u32x2_t{c[0], c[1]});
-    else store_vec(reinterpret_cast<uint32_t *>(p), c[0]);
+    if (FMT == FMT_FP8) *reinterpret_cast<eco_u32x2_t *>(p) = eco_u32x2_t{c[0], c[1]};
+    else *reinterpret_cast<uint32_t *>(p) = c[0];
   } else if (ACC != ACC_WHOLE) {
     const int nbytes = FMT == FMT_FP8 ? nvalid : (nvalid + 1) >> 1;
     constexpr int MAXB = FMT == FMT_FP8 ? 8 : 4;
@@ -167,12 +167,41 @@ __device__ __forceinline__ void fill_missing(float (&x)[8], int nvalid, float va
     if (ACC == ACC_WHOLE ? nvalid == 0 : j >= nvalid) x[j] = value;
 }
 
-// Eight elements of a lane as they come from memory: one 16-byte vector of bf16, or two of fp32.
-template <bool BF16>
-__device__ __forceinline__ void load_raw8(const void *base, uint64_t e, eco_u32x4_t (&q)[2]) {
-  const eco_u32x4_t *p = reinterpret_cast<const eco_u32x4_t *>(static_cast<const char *>(base) + e * (BF16 ? 2 : 4));
-  q[0] = p[0];
-  if (!BF16) q[1] = p[1];
+// Eight fp32 elements of each lane of a wave, the lanes' pieces one behind the other: 32 bytes to a lane, which two instructions of 16
+// bytes would take in halves of every 64-byte request.  So each takes 1 KB of consecutive bytes: lane l has chunk 2 l (l < 32) or
+// 2 (l - 32) + 1 of the 64 and the same of the next 64, and an exchange between the halves of the wave brings a lane's two chunks
+// together (four instructions; its own inverse, so stores take the same way back).
+__device__ __forceinline__ uint32_t lane_chunk() { return 2 * (threadIdx.x & 31) + ((threadIdx.x >> 5) & 1); }
+__device__ __forceinline__ void exchange_chunks(eco_u32x4_t (&q)[2]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(q[0][i], q[1][i], false, false);
+    q[0][i] = r[0];
+    q[1][i] = r[1];
+  }
+}
+// The element at which the wave's first piece starts; e0: the lane's.
+__device__ __forceinline__ uint64_t wave_start(uint64_t e0) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e0) |
+         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(e0 >> 32)) << 32;
+}
+// Stores of a wave go through a buffer that ends with its last whole piece, so lanes beyond it need no branch.
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ __forceinline__ buffer_t buffer_at(const void *base, uint64_t byte, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(base)) + byte, 0, (int)bytes, 0x00020000);
+}
+// whole: the lanes, from the first on, whose pieces exist; the others read the last of those once more, and write nothing.
+template <bool FULL, int CP>
+__device__ __forceinline__ void load_f32_wave(const void *base, uint64_t wave, int whole, eco_u32x4_t (&q)[2]) {
+  const char *p = static_cast<const char *>(base) + wave * 4;
+  const uint32_t c = lane_chunk(), last = 2 * (uint32_t)whole - 2 + (c & 1), c0 = FULL || c < last ? c : last, c1 = FULL || c + 64 < last ? c + 64 : last;
+  q[0] = load_vec<CP>(reinterpret_cast<const eco_u32x4_t *>(p + c0 * 16));
+  q[1] = load_vec<CP>(reinterpret_cast<const eco_u32x4_t *>(p + c1 * 16));
+  exchange_chunks(q);
+}
+__device__ __forceinline__ eco_u32x4_t pack_bf16x8(const float (&x)[8]) {
+  return eco_u32x4_t{f32x2_to_bf16x2_rne(x[0], x[1]), f32x2_to_bf16x2_rne(x[2], x[3]), f32x2_to_bf16x2_rne(x[4], x[5]),
+                     f32x2_to_bf16x2_rne(x[6], x[7])};
 }
 // The first nvalid (1..7) elements of a piece, zeros behind them.  Element by element, but without a branch, so that the loads of a
 // lane are under way together: an element that does not exist is the first one read once more (25 odd tensors, SGDM, without a plan
@@ -230,6 +259,8 @@ struct WavePieces {
   int last;                      // the lane with the last whole piece
   uint64_t from;                 // where the lane reads its vectors
   int fill;                      // how many of the lane's 8 elements stand for something
+  uint64_t wave;                 // where the wave's pieces start
+  int whole;                     // whole pieces
 };
 __device__ __forceinline__ WavePieces wave_pieces(uint64_t e0, int nvalid) {
   const int lane = (int)(threadIdx.x & 63);
@@ -240,7 +271,52 @@ __device__ __forceinline__ WavePieces wave_pieces(uint64_t e0, int nvalid) {
   p.last = 63 - __builtin_clzll(whole | 1);
   p.from = e0 - (uint64_t)(lane > p.last ? lane - p.last : 0) * ELEMS_PER_LANE;
   p.fill = p.any_cut || !p.any_whole ? nvalid : 8;
+  p.wave = wave_start(e0);
+  p.whole = p.any_whole ? p.last + 1 : 0;
   return p;
+}
+__device__ __forceinline__ WavePieces full_wave(uint64_t e0) { return WavePieces{true, false, 63, e0, 8, wave_start(e0), 64}; }
+
+// Optimizer state, master weights (fp32) or the stored error of the wave's lanes.
+template <bool BF16, bool FULL, int CP>
+__device__ __forceinline__ void load_wave8(const void *base, const WavePieces &wp, eco_u32x4_t (&q)[2]) {
+  if (BF16) q[0] = load_vec<CP>(reinterpret_cast<const eco_u32x4_t *>(static_cast<const uint16_t *>(base) + wp.from));
+  else load_f32_wave<FULL, CP>(base, wp.wave, wp.whole, q);
+}
+template <bool BF16, int ACC, int CP>
+__device__ __forceinline__ void store_wave8(void *base, uint64_t e0, int nvalid, const WavePieces &wp, const float (&x)[8]) {
+  if (ACC != ACC_FULL && ACC != ACC_LANE) {
+    if (BF16) store_bf16x8<ACC>(static_cast<uint16_t *>(base) + e0, nvalid, x);
+    else store_f32x8<ACC>(static_cast<float *>(base) + e0, nvalid, x);
+    return;
+  }
+  constexpr uint32_t ES = BF16 ? 2 : 4;
+  const buffer_t b = buffer_at(base, wp.wave * ES, (uint32_t)wp.whole * (8 * ES));
+  if (BF16) {
+    __builtin_amdgcn_raw_buffer_store_b128(pack_bf16x8(x), b, (threadIdx.x & 63) * 16, 0, CP);
+  } else {
+    eco_u32x4_t q[2] = {{f2u(x[0]), f2u(x[1]), f2u(x[2]), f2u(x[3])}, {f2u(x[4]), f2u(x[5]), f2u(x[6]), f2u(x[7])}};
+    exchange_chunks(q);
+    __builtin_amdgcn_raw_buffer_store_b128(q[0], b, lane_chunk() * 16, 0, CP);
+    __builtin_amdgcn_raw_buffer_store_b128(q[1], b, lane_chunk() * 16 + 1024, 0, CP);
+  }
+  if (ACC == ACC_LANE && wp.any_cut && nvalid < 8) {
+    if (BF16) store_bf16x8<ACC_GUARDED>(static_cast<uint16_t *>(base) + e0, nvalid, x);
+    else store_f32x8<ACC_GUARDED>(static_cast<float *>(base) + e0, nvalid, x);
+  }
+}
+template <int FMT, int ACC, int CP>
+__device__ __forceinline__ void store_wave_codes8(void *base, uint64_t e0, int nvalid, const WavePieces &wp, const uint32_t (&c)[2]) {
+  if (ACC != ACC_FULL && ACC != ACC_LANE) {
+    store_codes8<FMT, ACC>(base, e0, nvalid, c);
+    return;
+  }
+  if (FMT == FMT_FP8)
+    __builtin_amdgcn_raw_buffer_store_b64(eco_u32x2_t{c[0], c[1]}, buffer_at(base, wp.wave, (uint32_t)wp.whole * 8), (threadIdx.x & 63) * 8, 0,
+                                          CP);
+  else
+    __builtin_amdgcn_raw_buffer_store_b32(c[0], buffer_at(base, wp.wave >> 1, (uint32_t)wp.whole * 4), (threadIdx.x & 63) * 4, 0, CP);
+  if (ACC == ACC_LANE && wp.any_cut && nvalid < 8) store_codes8<FMT, ACC_GUARDED>(base, e0, nvalid, c);
 }
 
 template <int FMT, int J>
@@ -541,23 +617,34 @@ __device__ __forceinline__ void inject_lane8(const StepArgs &a, float s_new, con
 }
 
 // Both, with the stores: codes, the injected momentum (or master weights); returns the new scale.
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC>
-__device__ __forceinline__ float quantize_inject_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid, int fill,
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC, int CP>
+__device__ __forceinline__ float quantize_inject_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid, const WavePieces &wp,
                                                       float amax, const Philox4 &r, const float (&th)[8], const float (&d)[8],
                                                       float (&m)[8]) {
   constexpr bool MASTER = algo_is_master(ALGO);
-  if (MASTER) store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, th);
   uint32_t cn[2];
   float qn[8];
-  const float s_new = quantize_lane8<FMT, SCALE_BF16, ROUND, ACC>(amax, r, fill, th, cn, qn);
-  store_codes8<FMT, ACC>(td.w, e0, nvalid, cn);
+  const float s_new = quantize_lane8<FMT, SCALE_BF16, ROUND, ACC>(amax, r, wp.fill, th, cn, qn);
+  store_wave_codes8<FMT, ACC, CP>(td.w, e0, nvalid, wp, cn);
+  if (MASTER) store_wave8<false, ACC, CP>(td.aux, e0, nvalid, wp, th);
   if (!MASTER) {
     float eo[8];
-    if (ALGO == ALGO_SGDM_EXACT) load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, eo);
+    if (ALGO == ALGO_SGDM_EXACT) {
+      if (ACC == ACC_FULL || ACC == ACC_LANE) {
+        eco_u32x4_t q[2] = {};
+        if (wp.any_whole) load_wave8<false, ACC == ACC_FULL, CP>(td.aux, wp, q);
+        if (wp.any_cut) {
+          if (nvalid & 7) load_ragged8<false>(td.aux, e0, nvalid, q);
+        }
+        unpack8<false>(q, eo);
+      } else {
+        load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, eo);
+      }
+    }
     inject_lane8<SCALE_BF16, ALGO>(a, s_new, th, qn, d, m, eo);
-    if (ALGO == ALGO_SGDM_EXACT) store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, eo);
+    if (ALGO == ALGO_SGDM_EXACT) store_wave8<false, ACC, CP>(td.aux, e0, nvalid, wp, eo);
   }
-  store_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+  store_wave8<STATE_BF16, ACC, CP>(td.m, e0, nvalid, wp, m);
   return s_new;
 }
 
@@ -570,7 +657,7 @@ __device__ __forceinline__ void store_scale(const TensorDesc &td, uint64_t sg, f
 // One lane's 8 consecutive elements, starting at element e0 of tensor td, of which the first nvalid exist;
 // scale group number sg; bs_shift = log2(group size) for RED_BLOCK; row = the lane's group within the workgroup for
 // RED_WG_ROWS, the first lane of the lane's group for RED_ROWS.  LATE: an earlier kernel of the step has stored v~.
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC, int RED, bool LATE = false>
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int ACC, int RED, int CP = CACHED, bool LATE = false>
 __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid,
                                           uint64_t sg, bool scale_writer, uint32_t *slot, int row = 0) {
   constexpr bool ADAM = algo_is_adam(ALGO);
@@ -580,23 +667,23 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   const bool any = ACC == ACC_FULL || nvalid > 0;
 
   float g[8], m[8], v[8], w[8], x[8], d[8], th[8], sc = 1.0f;
-  int fill = nvalid;
+  WavePieces wp = {false, false, 0, e0, nvalid, 0, 0};
   uint32_t c[2] = {0, 0};
   float s_old = 0.0f;
-  if (ACC == ACC_LANE) {
-    const WavePieces wp = wave_pieces(e0, nvalid);
-    fill = wp.fill;
+  if (ACC == ACC_FULL || ACC == ACC_LANE) {
+    constexpr bool FULL = ACC == ACC_FULL;
+    wp = FULL ? full_wave(e0) : wave_pieces(e0, nvalid);
     eco_u32x4_t gq[2] = {}, mq[2] = {}, vq[2] = {}, wq[2] = {};
     if (wp.any_whole) {
-      load_raw8<true>(td.g, wp.from, gq);
-      load_raw8<STATE_BF16>(td.m, wp.from, mq);
-      if (ADAM) load_raw8<STATE_BF16>(td.v, wp.from, vq);
+      load_wave8<true, FULL, CP>(td.g, wp, gq);
+      load_wave8<STATE_BF16, FULL, CP>(td.m, wp, mq);
+      if (ADAM) load_wave8<STATE_BF16, FULL, CP>(td.v, wp, vq);
       if (MASTER) {
-        load_raw8<false>(td.aux, wp.from, wq);
+        load_wave8<false, FULL, CP>(td.aux, wp, wq);
       } else {
-        load_codes8<FMT, ACC_FULL>(td.w, wp.from, 8, c);
+        load_codes8<FMT, ACC_FULL, CP>(td.w, wp.from, 8, c);
         uint64_t sl = sg;
-        if (RED == RED_BLOCK || RED == RED_ROWS || RED == RED_WG_ROWS) {
+        if (!FULL && (RED == RED_BLOCK || RED == RED_ROWS || RED == RED_WG_ROWS)) {
           const uint64_t of_last = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sg, wp.last) |
                                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(sg >> 32), wp.last) << 32;
           sl = any ? sg : of_last;
@@ -643,30 +730,37 @@ __device__ __forceinline__ void step_lane(const StepArgs &a, const TensorDesc &t
   __builtin_amdgcn_s_setprio(0);      // loads issued: back to the default priority (see eco_step_kernel)
 
   moments_lane<ALGO, LATE>(a, g, m, v, x);
-  if (ADAM && (WRITE || KEEP) && !LATE) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);   // v is final (Alg. 3 returns it unchanged)
-  theta_lane<SCALE_BF16, ALGO, ACC>(a, x, w, sc, m, fill, d, th);
+  if (ADAM && (WRITE || KEEP) && !LATE) store_wave8<STATE_BF16, ACC, CP>(td.v, e0, nvalid, wp, v);   // v is final (Alg. 3 returns it unchanged)
+  theta_lane<SCALE_BF16, ALGO, ACC>(a, x, w, sc, m, wp.fill, d, th);
   if (KEEP) {
-    store_f32x8<ACC>(static_cast<float *>(td.aux) + e0, nvalid, th);
-    store_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
+    store_wave8<false, ACC, CP>(td.aux, e0, nvalid, wp, th);
+    store_wave8<STATE_BF16, ACC, CP>(td.m, e0, nvalid, wp, m);
   }
 
   const float amax = group_absmax<RED>(absmax8(th), RED == RED_WG_ROWS || RED == RED_ROWS ? row : (int)td.bs_shift, slot,
                                        RED == RED_ROWS ? (int)(td.group_size >> 3) : RED == RED_WG ? (int)a.wg_waves : 0);
   if (!WRITE) return;
   const Philox4 r = random_lane<ROUND>(a, td, e0, a.seed_lo, a.seed_hi);
-  const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC>(a, td, e0, nvalid, fill, amax, r, th, d, m);
+  const float s_new = quantize_inject_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC, CP>(a, td, e0, nvalid, wp, amax, r, th, d, m);
   if (RED != RED_SLOT && scale_writer && any) store_scale<SCALE_BF16>(td, sg, s_new);
 }
 
 // The second pass with master weights: they hold theta~, only the codes are left to write.
-template <int FMT, bool SCALE_BF16, int ROUND, int ACC>
+template <int FMT, bool SCALE_BF16, int ROUND, int ACC, int CP>
 __device__ __forceinline__ void quantize_master_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid, const uint32_t *slot) {
   float th[8], qn[8];
   uint32_t cn[2];
-  load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, th);
+  const WavePieces wp = full_wave(e0);                    // ACC_FULL alone
+  if (ACC == ACC_FULL) {
+    eco_u32x4_t q[2];
+    load_wave8<false, true, CP>(td.aux, wp, q);
+    unpack8<false>(q, th);
+  } else {
+    load_f32x8<ACC>(static_cast<const float *>(td.aux) + e0, nvalid, th);
+  }
   const Philox4 r = random_lane<ROUND>(a, td, e0, a.seed_lo, a.seed_hi);
   (void)quantize_lane8<FMT, SCALE_BF16, ROUND, ACC>(u2f(*slot), r, nvalid, th, cn, qn);
-  store_codes8<FMT, ACC>(td.w, e0, nvalid, cn);
+  store_wave_codes8<FMT, ACC, CP>(td.w, e0, nvalid, wp, cn);
 }
 
 // The launch tables are read-only for the lifetime of a launch; reading them through the constant
@@ -714,38 +808,30 @@ __device__ __forceinline__ int valid_from(uint64_t e0, uint64_t end) {
 // injection (the method is applied to linear layers only; norm weights take the ordinary optimizer).
 // UNIT_PLAIN_FP32: fp32 weights under the identity quantizer, for which the quantization error is zero and Alg. 2/3
 // add nothing to the momentum.
-template <bool W_BF16, bool STATE_BF16, bool ADAM, int ACC>
+template <bool W_BF16, bool STATE_BF16, bool ADAM, int ACC, int CP>
 __device__ __forceinline__ void plain_lane(const StepArgs &a, const TensorDesc &td, uint64_t e0, int nvalid) {
+  constexpr bool FULL = ACC == ACC_FULL;
   float w[8], g[8], m[8], v[8], eta[8];
-  int fill = nvalid;
-  if (ACC == ACC_LANE) {
-    const WavePieces wp = wave_pieces(e0, nvalid);
-    fill = wp.fill;
-    eco_u32x4_t wq[2] = {}, gq[2] = {}, mq[2] = {}, vq[2] = {};
-    if (wp.any_whole) {
-      load_raw8<W_BF16>(td.w, wp.from, wq);
-      load_raw8<true>(td.g, wp.from, gq);
-      load_raw8<STATE_BF16>(td.m, wp.from, mq);
-      if (ADAM) load_raw8<STATE_BF16>(td.v, wp.from, vq);
-    }
-    if (wp.any_cut) {
-      if (nvalid & 7) {
-        load_ragged8<W_BF16>(td.w, e0, nvalid, wq);
-        load_ragged8<true>(td.g, e0, nvalid, gq);
-        load_ragged8<STATE_BF16>(td.m, e0, nvalid, mq);
-        if (ADAM) load_ragged8<STATE_BF16>(td.v, e0, nvalid, vq);
-      }
-    }
-    unpack8<W_BF16>(wq, w);
-    unpack8<true>(gq, g);
-    unpack8<STATE_BF16>(mq, m);
-    if (ADAM) unpack8<STATE_BF16>(vq, v);
-  } else {
-    load_state8<W_BF16, ACC>(td.w, e0, nvalid, w);
-    load_bf16x8<ACC>(static_cast<const uint16_t *>(td.g) + e0, nvalid, g);
-    load_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
-    if (ADAM) load_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
+  const WavePieces wp = FULL ? full_wave(e0) : wave_pieces(e0, nvalid);
+  eco_u32x4_t wq[2] = {}, gq[2] = {}, mq[2] = {}, vq[2] = {};
+  if (wp.any_whole) {
+    load_wave8<W_BF16, FULL, CP>(td.w, wp, wq);
+    load_wave8<true, FULL, CP>(td.g, wp, gq);
+    load_wave8<STATE_BF16, FULL, CP>(td.m, wp, mq);
+    if (ADAM) load_wave8<STATE_BF16, FULL, CP>(td.v, wp, vq);
   }
+  if (wp.any_cut) {
+    if (nvalid & 7) {
+      load_ragged8<W_BF16>(td.w, e0, nvalid, wq);
+      load_ragged8<true>(td.g, e0, nvalid, gq);
+      load_ragged8<STATE_BF16>(td.m, e0, nvalid, mq);
+      if (ADAM) load_ragged8<STATE_BF16>(td.v, e0, nvalid, vq);
+    }
+  }
+  unpack8<W_BF16>(wq, w);
+  unpack8<true>(gq, g);
+  unpack8<STATE_BF16>(mq, m);
+  if (ADAM) unpack8<STATE_BF16>(vq, v);
   if (ADAM) {
     float x[8], d[8];
 #pragma unroll
@@ -753,7 +839,7 @@ __device__ __forceinline__ void plain_lane(const StepArgs &a, const TensorDesc &
       v[j] = fmaf(a.b2, v[j], a.omb2 * (g[j] * g[j]));
       x[j] = v[j] * a.rbc2;
     }
-    fill_missing<ACC>(x, fill, 1.0f);
+    fill_missing<ACC>(x, wp.fill, 1.0f);
     step_sizes8(a, x, d, eta);
   }
 #pragma unroll
@@ -764,21 +850,21 @@ __device__ __forceinline__ void plain_lane(const StepArgs &a, const TensorDesc &
     if (a.wd != 0.0f) wj = wj - a.wd * wj;
     w[j] = wj - u;
   }
-  store_state8<W_BF16, ACC>(td.w, e0, nvalid, w);
-  store_state8<STATE_BF16, ACC>(td.m, e0, nvalid, m);
-  if (ADAM) store_state8<STATE_BF16, ACC>(td.v, e0, nvalid, v);
+  store_wave8<W_BF16, ACC, CP>(td.w, e0, nvalid, wp, w);
+  store_wave8<STATE_BF16, ACC, CP>(td.m, e0, nvalid, wp, m);
+  if (ADAM) store_wave8<STATE_BF16, ACC, CP>(td.v, e0, nvalid, wp, v);
 }
 
 // ------------------------------------------------------------------ kernels
 // One unit of a list of one-wave units (UNIT_*), `lane` in 0..63: what is left beside the full tiles.  One body serves whole
 // and partial tiles.
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int CP>
 __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDesc &td, uint32_t unit, uint32_t lane) {
   if (td.kind == UNIT_PLAIN_BF16 || td.kind == UNIT_PLAIN_FP32) {
     const uint64_t e0 = (uint64_t)unit * TILE_ELEMS + (uint64_t)lane * ELEMS_PER_LANE;
     const int nvalid = valid_from(e0, td.numel);
-    if (td.kind == UNIT_PLAIN_BF16) plain_lane<true, STATE_BF16, algo_is_adam(ALGO), ACC_LANE>(a, td, e0, nvalid);
-    else plain_lane<false, STATE_BF16, algo_is_adam(ALGO), ACC_LANE>(a, td, e0, nvalid);
+    if (td.kind == UNIT_PLAIN_BF16) plain_lane<true, STATE_BF16, algo_is_adam(ALGO), ACC_LANE, CP>(a, td, e0, nvalid);
+    else plain_lane<false, STATE_BF16, algo_is_adam(ALGO), ACC_LANE, CP>(a, td, e0, nvalid);
     return;
   }
   if (td.kind == UNIT_ROWS) {
@@ -788,7 +874,7 @@ __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDe
     const uint64_t grp = (uint64_t)unit * td.slot;
     const uint64_t e0 = grp * td.group_size + (uint64_t)lane * ELEMS_PER_LANE;
     const uint64_t end = (grp + td.slot) * td.group_size;
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_ROWS>(
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_ROWS, CP>(
         a, td, e0, valid_from(e0, end < td.numel ? end : td.numel), grp + row, lane == row * gl, nullptr, (int)(row * gl));
     return;
   }
@@ -799,7 +885,7 @@ __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDe
   const uint64_t end = row && start + td.group_size < td.numel ? start + td.group_size : td.numel;
   const uint64_t e0 = start + (uint64_t)lane * ELEMS_PER_LANE;
   const bool writer = (lane & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
-  step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_BLOCK>(a, td, e0, valid_from(e0, end), row ? unit : e0 >> td.bs_shift,
+  step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_BLOCK, CP>(a, td, e0, valid_from(e0, end), row ? unit : e0 >> td.bs_shift,
                                                                            writer, nullptr);
 }
 
@@ -814,7 +900,7 @@ __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDe
 // memory access fewer in a chain of four (one matrix of 1 M elements 5.2 -> 5.0 us, of 4 M 16.9 -> 16.7).  As integers: for every argument
 // of pointer type the runtime looks up the allocation behind it, 0.03 us of a call each.  `table` also covers the one-wave units, whose list
 // lies behind the tiles'.
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int CP>
 __global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint64_t table, const uint64_t tensors, const StepArgs a) {
   // A wave that has not issued its loads yet goes first: its address arithmetic and load instructions
   // are not queued behind the arithmetic of the waves that already have their data (the priority is
@@ -826,9 +912,9 @@ __global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint64_t tab
   if (tile < a.num_tiles) {
     const uint64_t e0 = (uint64_t)(tile - td.first_unit) * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
     const bool writer = (threadIdx.x & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_BLOCK>(a, td, e0, 8, e0 >> td.bs_shift, writer, nullptr);
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_BLOCK, CP>(a, td, e0, 8, e0 >> td.bs_shift, writer, nullptr);
   } else {
-    step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, tile - a.num_tiles - td.first_unit, threadIdx.x);
+    step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, CP>(a, td, tile - a.num_tiles - td.first_unit, threadIdx.x);
   }
 }
 
@@ -838,7 +924,7 @@ __global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint64_t tab
 // lanes of the last one idle (step_geometry).  EXTRA: workgroups beyond the groups take one-wave units, one
 // to a wave (a variant of its own: with those paths in the kernel the groups run 3.6 % slower, 3 460 -> 3 590 us over
 // Gemma-3-1B shapes, so a long launch leaves them to another one).
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, bool EXTRA>
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, bool EXTRA, int CP>
 __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const uint64_t table, const uint64_t tensors, const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);      // as in eco_step_kernel: loading waves first
   const uint32_t unit = blockIdx.x + a.unit_base;
@@ -846,7 +932,7 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const uint64_t tabl
     const uint32_t x = __builtin_amdgcn_readfirstlane((unit - a.num_units) * a.wg_waves + (threadIdx.x >> 6));
     if (x < a.num_extra) {
       const TensorDesc td = load_tensor_desc(a, load_table(a.extra_tensor, x));
-      step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, x - td.first_unit, threadIdx.x & 63);
+      step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, CP>(a, td, x - td.first_unit, threadIdx.x & 63);
     }
     return;
   }
@@ -862,18 +948,18 @@ __global__ __launch_bounds__(1024) void eco_step_wide_kernel(const uint64_t tabl
     uint32_t row = 0;
     for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * gs ? 1u : 0u;
     if (ALGO == ALGO_ADAM_MASTER || end - start == (uint64_t)a.wg_waves * TILE_ELEMS)      // master weights: see step_geometry
-      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG_ROWS>(a, td, e0, 8, grp + row, lane_elem == row * gs, nullptr,
+      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG_ROWS, CP>(a, td, e0, 8, grp + row, lane_elem == row * gs, nullptr,
                                                                                  (int)row);
     else
-      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG_ROWS>(a, td, e0, valid_from(e0, end), grp + row,
+      step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG_ROWS, CP>(a, td, e0, valid_from(e0, end), grp + row,
                                                                                  lane_elem == row * gs, nullptr, (int)row);
     return;
   }
   // a group that fills every lane of the workgroup (e.g. rows of 1024, 2048, 4096) needs no per-lane guards
   if (end - start == (uint64_t)a.wg_waves * TILE_ELEMS)
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG>(a, td, e0, 8, grp, threadIdx.x == 0, nullptr);
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_WG, CP>(a, td, e0, 8, grp, threadIdx.x == 0, nullptr);
   else
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG>(a, td, e0, valid_from(e0, end), grp,
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_LANE, RED_WG, CP>(a, td, e0, valid_from(e0, end), grp,
                                                                           threadIdx.x == 0, nullptr);
 }
 
@@ -894,7 +980,7 @@ __device__ __forceinline__ void step_list_workgroup(const StepArgs &a, const Ten
       const bool writer = (lane & ((1u << (td.bs_shift - 3)) - 1u)) == 0;
       step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, RED_BLOCK>(a, td, e0, 8, e0 >> td.bs_shift, writer, nullptr);
     } else {
-      step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND>(a, td, unit, lane);
+      step_wave_unit<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, CACHED>(a, td, unit, lane);
     }
     return;
   }
@@ -942,7 +1028,7 @@ __global__ __launch_bounds__(1024, 8) void eco_step_list_kernel(const uint64_t t
 // kernel writes the new scales.  With master weights nothing but the codes waits for the scale: pass 1 stores them and the
 // moments, pass 2 reads them alone (31 bytes a parameter with Adam and fp32 state where recomputing takes 41: six tensors of 64 M
 // elements in INT4 2817 -> 2164 us; SGDM 324 M 1644 -> 1295; Adam with bf16 state two of 51 M 544 -> 415).
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int RED>
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int RED, int CP>
 __global__ __launch_bounds__(WG_THREADS) void eco_step_tensorwise_kernel(const StepArgs a) {
   __builtin_amdgcn_s_setprio(3);      // as in eco_step_kernel: loading waves first
   // Pass 2 goes through the tiles backwards, each on the XCD that has it in its L2 from pass 1 (us, forwards / backwards by single tiles,
@@ -958,10 +1044,10 @@ __global__ __launch_bounds__(WG_THREADS) void eco_step_tensorwise_kernel(const S
   const bool whole = tile_off + TILE_ELEMS <= td.numel;
   const int nvalid = valid_from(e0, td.numel);
   if (algo_is_master(ALGO) && RED == RED_SLOT) {
-    if (whole) quantize_master_lane<FMT, SCALE_BF16, ROUND, ACC_FULL>(a, td, e0, 8, slot);
-    else quantize_master_lane<FMT, SCALE_BF16, ROUND, ACC_GUARDED>(a, td, e0, nvalid, slot);
+    if (whole) quantize_master_lane<FMT, SCALE_BF16, ROUND, ACC_FULL, CP>(a, td, e0, 8, slot);
+    else quantize_master_lane<FMT, SCALE_BF16, ROUND, ACC_GUARDED, CACHED>(a, td, e0, nvalid, slot);
   } else if (whole) {
-    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, R>(a, td, e0, 8, 0, false, slot);
+    step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_FULL, R, CP>(a, td, e0, 8, 0, false, slot);
   } else {
     step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_GUARDED, R>(a, td, e0, nvalid, 0, false, slot);
   }
@@ -1051,6 +1137,32 @@ hipError_t launch_listed_in_chunks(Kernel kernel, const uint32_t *table, uint64_
 template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
 hipError_t launch_resident(const StepLaunch &sl, hipStream_t stream);      // eco_step_resident.hpp
 
+// Full tiles and one-wave units.
+template <int FMT, bool STATE_BF16, bool SC, int RD, int AL, int CP>
+hipError_t launch_tiles(const StepLaunch &sl, hipStream_t stream) {
+  StepArgs ta = sl.args;
+  if (sl.extra_in != 0) ta.num_extra = 0;
+  ECO_LISTED_CHECKED((eco_step_kernel<FMT, STATE_BF16, SC, AL, RD, CP>), sl.tile_tensor, (uint64_t)ta.num_tiles + ta.num_extra, WG_THREADS,
+                     sl.lds_bytes, stream, ta, sl.max_tile_threads);
+  return hipSuccess;
+}
+// The wide groups whose workgroups have nw waves.
+template <int FMT, bool STATE_BF16, bool SC, int RD, int AL, int CP>
+hipError_t launch_wide(const StepLaunch &sl, int nw, hipStream_t stream) {
+  StepArgs wa = sl.args;
+  const unsigned lds = sl.lds_bytes_wide[nw];
+  const uint32_t *const table = sl.wide_base + sl.wide_offset[nw];
+  const uint32_t units = wa.num_units = sl.num_wide[nw];
+  wa.wg_waves = static_cast<uint32_t>(nw);
+  if (sl.extra_in != nw || !wa.num_extra)
+    ECO_LISTED_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, false, CP>), table, units, 64 * nw, lds, stream, wa,
+                       sl.max_launch_threads);
+  else
+    ECO_LISTED_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, true, CP>), table, (uint64_t)units + (wa.num_extra + nw - 1) / nw,
+                       64 * nw, lds, stream, wa, sl.max_launch_threads);
+  return hipSuccess;
+}
+
 template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
 hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
   const StepArgs &args = sl.args;
@@ -1064,24 +1176,15 @@ hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
                        sl.max_launch_threads);
   } else {
     if (args.num_tiles || (args.num_extra && sl.extra_in == 0)) {
-      StepArgs ta = args;
-      if (sl.extra_in != 0) ta.num_extra = 0;
-      ECO_LISTED_CHECKED((eco_step_kernel<FMT, STATE_BF16, SC, AL, RD>), sl.tile_tensor, (uint64_t)ta.num_tiles + ta.num_extra, WG_THREADS,
-                         sl.lds_bytes, stream, ta, sl.max_tile_threads);
+      const hipError_t e = sl.stream & 1u ? launch_tiles<FMT, STATE_BF16, SC, RD, AL, STREAM_WAVE>(sl, stream)
+                                          : launch_tiles<FMT, STATE_BF16, SC, RD, AL, CACHED>(sl, stream);
+      if (e != hipSuccess) return e;
     }
     for (int nw = 1; nw <= MAX_WIDE_WAVES; ++nw) {
       if (!sl.num_wide[nw]) continue;
-      StepArgs wa = args;
-      const unsigned lds = sl.lds_bytes_wide[nw];
-      const uint32_t *const table = sl.wide_base + sl.wide_offset[nw];
-      const uint32_t units = wa.num_units = sl.num_wide[nw];
-      wa.wg_waves = static_cast<uint32_t>(nw);
-      if (sl.extra_in != nw || !args.num_extra)
-        ECO_LISTED_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, false>), table, units, 64 * nw, lds, stream, wa,
-                           sl.max_launch_threads);
-      else
-        ECO_LISTED_CHECKED((eco_step_wide_kernel<FMT, STATE_BF16, SC, AL, RD, true>), table, (uint64_t)units + (wa.num_extra + nw - 1) / nw,
-                           64 * nw, lds, stream, wa, sl.max_launch_threads);
+      const hipError_t e = sl.stream >> nw & 1u ? launch_wide<FMT, STATE_BF16, SC, RD, AL, STREAM_GROUP>(sl, nw, stream)
+                                                : launch_wide<FMT, STATE_BF16, SC, RD, AL, CACHED>(sl, nw, stream);
+      if (e != hipSuccess) return e;
     }
   }
   if (args.num_slabs) {
@@ -1089,11 +1192,11 @@ hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   if (args.num_tw_tiles) {
-    ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_TILE>), args.num_tw_tiles, WG_THREADS,
+    ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_TILE, CACHED>), args.num_tw_tiles, WG_THREADS,
                        sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
     ECO_CHUNKS_CHECKED((eco_tensorwise_reduce_kernel<FMT>), (uint64_t)args.num_tw_tensors * args.tw_reduce_wgs, TW_REDUCE_THREADS, 0, stream,
                        args, sl.max_launch_threads);
-    ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_SLOT>), args.num_tw_tiles, WG_THREADS,
+    ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_SLOT, CACHED>), args.num_tw_tiles, WG_THREADS,
                        sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
     ECO_CHUNKS_CHECKED((eco_tensorwise_scale_kernel<FMT, SC>), (args.num_tw_tensors + WG_THREADS - 1) / WG_THREADS, WG_THREADS,
                        0, stream, args, sl.max_launch_threads);

@@ -48,7 +48,6 @@ constexpr uint32_t NO_MAX = 0xFFFFFFFFu;       // an entry of slab_max[] that ha
 // stores count in one counter, in order, and a wait for loads whose number of younger stores depends on the path taken
 // has to drain the stores as well, about 1.5 us a turn.  (Nor are they FLAT instructions, which count as LDS operations
 // too, so that every wait for an LDS result or a scalar load would wait for the tile in flight.)
-typedef __amdgpu_buffer_rsrc_t buffer_t;
 __device__ __forceinline__ buffer_t tile_buffer(const void *array, uint64_t tile, uint32_t len, uint32_t elem_bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(array)) + tile * elem_bytes, 0,
                                            (int)(len * elem_bytes), 0x00020000);
@@ -58,10 +57,6 @@ __device__ __forceinline__ void store16(buffer_t b, uint32_t off, eco_u32x4_t x)
 __device__ __forceinline__ eco_u32x4_t bits4(const float *x) { return eco_u32x4_t{f2u(x[0]), f2u(x[1]), f2u(x[2]), f2u(x[3])}; }
 constexpr int SCOPE_AGENT = 16;        // cache policy: coherent between the XCDs
 
-__device__ __forceinline__ eco_u32x4_t pack_bf16x8(const float (&x)[8]) {
-  return eco_u32x4_t{f32x2_to_bf16x2_rne(x[0], x[1]), f32x2_to_bf16x2_rne(x[2], x[3]), f32x2_to_bf16x2_rne(x[4], x[5]),
-                     f32x2_to_bf16x2_rne(x[6], x[7])};
-}
 __device__ __forceinline__ void store_f32_tile(buffer_t b, uint32_t lane, const float (&x)[8]) {
   store16(b, lane * 32, bits4(x));
   store16(b, lane * 32 + 16, bits4(x + 4));
@@ -362,7 +357,7 @@ __global__ __launch_bounds__(RES_FINISH_THREADS) void eco_step_resident_finish_k
       uint32_t amax = max_of(td);
       for (uint32_t k = wave; k < WAVES; k += NW) {
         const uint64_t e0 = ((uint64_t)(slab - td.first_unit) * WAVES + k) * TILE_ELEMS + lane * ELEMS_PER_LANE;
-        step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_WHOLE, RED_SLOT, !STATE_BF16>(a, td, e0, e0 < td.numel ? 8 : 0, 0, false, &amax);
+        step_lane<FMT, STATE_BF16, SCALE_BF16, ALGO, ROUND, ACC_WHOLE, RED_SLOT, CACHED, !STATE_BF16>(a, td, e0, e0 < td.numel ? 8 : 0, 0, false, &amax);
       }
     }
     __shared__ uint32_t last;

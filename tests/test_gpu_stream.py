@@ -1,0 +1,82 @@
+"""Steps whose arrays come from HBM (280 MB and more with fp32 state, 384 MB with bf16) load and store past the caches, and waves exchange
+halves of their fp32 pieces to do it: every class of scale group and of unit, whole and partial waves, pieces that are cut off, beside
+a large tensor that takes the step over the line.  The comparison bar is the one of tests/gpu_util.py, and no bit may differ."""
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_util import bf16_bits, bytes_per_element, compare, host_copy, oracle_step, step_config
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+T = workloads.TensorSpec
+
+
+def grouped(numel, group, fmt):
+    t = T(f"g{group}_{numel}", (numel,), fmt, grad_std=1e-3 * (1 + numel % 3), granularity="row")
+    t.group_size = lambda block_size: group
+    return t
+
+
+def small(fmt):
+    """Full tiles and every cut of the last one that matters: within a lane's piece, at a lane's end, in the wave's first and second half."""
+    tiles = [T(f"t{n}", (n,), fmt) for n in (512, 1024 + 8, 512 + 255, 512 + 256, 512 + 257, 2048 + 509, 3, 5 * 512 + 264)]
+    # units of whole lines and of parts of lines; last rows that are cut off
+    rows = [grouped(n * g - cut, g, fmt) for g in (64, 192, 200, 320, 384, 576, 1024, 1056, 1152, 1408, 2048, 2304, 4096, 6912)
+            for n, cut in ((5, 0), (9, 3), (4, 8))]
+    plain = [T(f"p{n}", (n,), "bf16_plain") for n in (1, 511, 512, 1027)]
+    return tiles + rows + plain
+
+
+@pytest.mark.parametrize("home", ["tiles", "rows", "plain"])
+@pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("fp8", False, dict(mode=3, weight_decay=0.1)), ("int4", True, {}),
+                                           ("fp8", True, dict(opt=1, mode=3, lr=0.05)), ("int4", False, dict(opt=1, round=1, lr=0.05)),
+                                           ("fp8", False, dict(opt=1, mode=2, lr=0.05))])
+def test_steps_past_the_caches(home, fmt, bf16, over):
+    """home: what the large tensor is, and with it which launch the one-wave units ride in."""
+    from paper_2601_22101_amd import harness
+    o32 = oracle.get("f32")
+    state = (2 if bf16 else 4) * (1 if over.get("opt") else 2)
+    n = int(400e6 / (state + 4 if home == "plain" else bytes_per_element(fmt, bf16, over)))
+    big = T("big", (n,), "bf16_plain") if home == "plain" else T("big", (n,), fmt) if home == "tiles" else grouped(n // 2048 * 2048, 2048, fmt)
+    specs = [t for t in small(fmt) if home != "rows" or not t.name.startswith("t")]
+    wl = workloads.Workload("stream_" + home, specs + [big], steps=2, state_bf16=bf16, scale_bf16=bf16)
+    dw = harness.DeviceWorkload(wl, DEV, layout=over)
+    views = dw.tensors if home != "plain" else dw.tensors[:-1]
+    host = [host_copy(tv) for tv in views]
+    for k in (1, 2):
+        dw.fill_gradients(k)
+        hp = dw.hparams(k)
+        for tv, h in zip(views, host):
+            h["grad"] = bf16_bits(tv.grad)
+        dw.plan.step(hp)
+        torch.cuda.synchronize()
+        for tv, h in zip(views, host):
+            if k == 2 and tv.spec.name == "big":
+                continue
+            oracle_step(o32, h, tv.spec.numel, step_config(hp, tv.tensor_id, tv.fmt, group_size=dw.group_size(tv) if h.get("codes") is not None else 0))
+            st = compare(host_copy(tv), h, f"{home} step {k} {tv.spec.name}", bf16)
+            assert not any(v for key, v in st.items() if key.endswith("mismatch")), (tv.spec.name, st)
+    dw.close()
+
+
+@pytest.mark.parametrize("off", [8, 32])
+def test_arrays_that_begin_off_a_line(off):
+    """Arrays at 16 and 64 bytes past a line, without a plan: stepped the usual way, with the same results as arrays on lines."""
+    from paper_2601_22101_amd import binding as eco
+    n = 27_000_001
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    base = {"w": torch.randint(0, 120, (n,), generator=gen, device=DEV, dtype=torch.uint8), "s": torch.full((n // 128 + 1,), 1e-4, device=DEV),
+            "g": (torch.randn(n, generator=gen, device=DEV) * 1e-3).to(torch.bfloat16), "m": torch.randn(n, generator=gen, device=DEV) * 1e-3,
+            "v": torch.rand(n, generator=gen, device=DEV) * 1e-6 + 1e-9}
+    out = []
+    for shift in (0, off):
+        x = {k: torch.cat([t.new_zeros(shift * 2 if k == "w" else shift), t])[shift * 2 if k == "w" else shift:] for k, t in base.items()}
+        t = eco.make_tensor(x["w"], x["s"], x["g"], x["m"], x["v"], n, 7, eco.ECO_FMT_FP8_E4M3)
+        eco.eco_step_tensors_noalloc([t], eco.make_hparams(step=3, seed=11))
+        torch.cuda.synchronize()
+        out.append(x)
+    for k in base:
+        assert torch.equal(out[0][k].contiguous().view(torch.uint8), out[1][k].contiguous().view(torch.uint8)), k
