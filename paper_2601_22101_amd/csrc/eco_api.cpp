@@ -124,7 +124,7 @@ struct Lists {                           // the launch lists of one storage form
   uint64_t tensors = 0, most_tw_tiles = 0, tails = 0;
   struct WideLoad { uint64_t idle, elements, off_lines; };   // of a wide list: units that leave lanes idle; elements (0: the one-wave units'); those
                                                          // whose waves start off the lines of memory (0: of the full tiles as well)
-  WideLoad load[eco::MAX_WIDE_WAVES + 1] = {};
+  WideLoad load[eco::MAX_WIDE_WAVES + 2] = {};           // the last: long tensors with one scale
   std::vector<uint32_t> one;             // all but the tensor-wise tensors as one launch, where that is the better way: workgroup -> tensor
   size_t off_one = 0;
   unsigned one_waves = 1;
@@ -224,10 +224,11 @@ int streaming_waves(const eco::KernelVariant &kv, uint64_t bytes) {
 // The two tensor-wise passes over 210 M elements (us): Adam, fp32 state 1119 at 16 waves (1176 without a cap); INT4 with
 // bf16 state 623 at 21 (645); SGDM 676 at 18 (703).  The last two for arrays from HBM only (one tensor of 4.7 M elements:
 // SGDM 22.6 without a cap, 24.8 with it).
-int tensorwise_waves(const eco::KernelVariant &kv, const HbmBound &hbm) {
+// Past the caches INT4 572 at 21 and 555 at 25.
+int tensorwise_waves(const eco::KernelVariant &kv, const HbmBound &hbm, bool streamed) {
   if (kv.algo == eco::ALGO_ADAM && !kv.state_bf16) return 16;
   if (!hbm.fully) return 0;
-  if (kv.algo == eco::ALGO_ADAM) return 21;
+  if (kv.algo == eco::ALGO_ADAM) return streamed ? 25 : 21;
   return kv.algo == eco::ALGO_SGDM && !kv.state_bf16 ? 18 : 0;
 }
 
@@ -306,20 +307,20 @@ bool off_lines(const eco_tensor_t &t, const eco::Placement &p) {
 }
 
 // Which launches of a step pass the caches by (CACHED and the others beside it in the kernels say what that is worth), a bit each: 0 the
-// full-tile one, n the wide groups of n waves.  Arrays that the 256 MB cache before HBM still holds from the step before lose by it, and so do
+// full-tile one, n the wide groups of n waves, STREAM_TENSORWISE the others.  Arrays that the 256 MB cache before HBM still holds from the step before lose by it, and so do
 // waves that start off the lines of memory, whose instructions then write parts of two (us, us usual / streamed) -- by bytes of the arrays, groups
 // of 128: fp32 state, Adam 250 MB 71 / 74, 280 89 / 82, 340 103 / 99, master weights 69 / 74, 91 / 82, 107 / 97, SGDM 65 / 69, 82 / 77; bf16
 // state, INT4, Adam 310 MB 82 / 83, 340 90 / 90, 420 99 / 97, 640 187 / 168, SGDM (FP8) 310 75 / 78, 340 84 / 85, 420 101 / 95.  Rows of 1.6 GB, fp32
 // state: 1120 (pairs: 35 lines) 491 / 451, 2016 517 / 507, 544 532 / 555, 1000 527 / 654, 6944 545 / 554; bf16 state 1120 528 / 620, 320 590 / 576.
-uint32_t stream_launches(uint64_t bytes, bool f32, uint64_t tiles, const Lists::WideLoad (&load)[eco::MAX_WIDE_WAVES + 1]) {
+uint32_t stream_launches(uint64_t bytes, bool f32, uint64_t tiles, const Lists::WideLoad (&load)[eco::MAX_WIDE_WAVES + 2]) {
   if (bytes < (f32 ? 280000000u : 384000000u)) return 0;
   uint32_t launches = load[0].off_lines * 8 <= load[0].elements + tiles * eco::TILE_ELEMS ? 1 : 0;
-  for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) launches |= (load[nw].off_lines * 8 <= load[nw].elements ? 1u : 0u) << nw;
+  for (int nw = 1; nw <= eco::STREAM_TENSORWISE; ++nw) launches |= (load[nw].off_lines * 8 <= load[nw].elements ? 1u : 0u) << nw;
   return launches;
 }
 
 // The scalar part of the kernel arguments: step constants, random-stream key, launch options.
-typedef Lists::WideLoad WideLoads[eco::MAX_WIDE_WAVES + 1];
+typedef Lists::WideLoad WideLoads[eco::MAX_WIDE_WAVES + 2];
 void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const WideLoads &load, uint64_t bytes,
                        eco::StepLaunch *sl) {
   eco::StepArgs *a = &sl->args;
@@ -361,7 +362,7 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
     const uint32_t per_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves, 256);
     sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (adam32 && !idle && !streamed) ? std::min(per_wave * nw, 65536u) : eco::lds_for_workgroups(k);
   }
-  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv, hbm), 256);
+  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv, hbm, sl->stream >> eco::STREAM_TENSORWISE & 1u), 256);
 }
 
 
@@ -739,6 +740,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       const uint32_t idx = static_cast<uint32_t>(i);
       std::vector<uint32_t> &list = g.list(p.list);
       eco::TensorDesc d = describe(t, layout, p, list.size());
+      if (p.list == eco::LIST_TW_TILES || p.list == eco::LIST_RESIDENT) {
+        g.load[eco::STREAM_TENSORWISE].elements += t.numel;
+        g.load[eco::STREAM_TENSORWISE].off_lines += off_lines(t, p) ? t.numel : 0;
+      }
       if (p.list == eco::LIST_TW_TILES) {
         d.slot = static_cast<uint32_t>(g.tw_tensor.size());
         g.tw_tensor.push_back(idx);
@@ -955,9 +960,11 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     w.elements += t.numel;
     w.off_lines += off_lines(t, p) ? t.numel : 0;
   };
-  const auto count_tensorwise = [&](int f, const eco::Placement &p) {
+  const auto count_tensorwise = [&](int f, const eco_tensor_t &t, const eco::Placement &p) {
     count[f][eco::LIST_TW_TILES] += p.units;
     count[f][L_TW_TENSORS] += 1;
+    load[f][eco::STREAM_TENSORWISE].elements += t.numel;
+    load[f][eco::STREAM_TENSORWISE].off_lines += off_lines(t, p) ? t.numel : 0;
     units += p.units + 1;
     most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
   };
@@ -981,7 +988,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
                   "groups wider than 512): the static scratch does not hold them (use a plan)", MAX_UNITS);
     if (p.list == eco::LIST_TW_TILES) {
       tensorwise = true;
-      count_tensorwise(f, p);
+      count_tensorwise(f, tensors[i], p);
       continue;
     }
     if (cls == eco::GROUP_TENSOR) odd_entries[f] += p.entries;
@@ -1015,7 +1022,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     }
     odd_along[f] = true;
     for (size_t i = 0; i < n; ++i)
-      if (tensors[i].fmt == f && short_odd(tensors[i], hp)) count_tensorwise(f, place(tensors[i]));
+      if (tensors[i].fmt == f && short_odd(tensors[i], hp)) count_tensorwise(f, tensors[i], place(tensors[i]));
   }
   // The wide lists again with the step's own grouping of rows, where it is the better one (see bytes_of, own_grouping_pays) and the
   // static tables hold its units; back to the other one if not.

@@ -157,6 +157,8 @@ inline uint32_t tw_reduce_workgroups(uint64_t most_tiles) {
   return static_cast<uint32_t>(w < 1 ? 1 : w > 64 ? 64 : w);
 }
 
+constexpr int STREAM_TENSORWISE = MAX_WIDE_WAVES + 1;
+
 // What one format's step launches, host side.
 struct StepLaunch {
   StepArgs args;
@@ -171,7 +173,8 @@ struct StepLaunch {
   uint32_t wide_offset[MAX_WIDE_WAVES + 1];
   uint32_t num_wide[MAX_WIDE_WAVES + 1];
   unsigned resident_wgs;           // workgroups of the one-pass tensor-wise kernel: one per compute unit
-  uint32_t stream;                 // which launches pass the caches by (see stream_pays), a bit each: 0 the full-tile one, n the wide groups of n waves
+  uint32_t stream;                 // which launches pass the caches by (see stream_launches), a bit each: 0 the full-tile one, n the wide groups of n
+                                   // waves, STREAM_TENSORWISE the long tensors with one scale
   int extra_in;                    // which launch the one-wave units ride in: 0 the full-tile one, n the wide groups of n waves
   const SmallArgs *small;          // if set, one launch of eco_step_small_kernel (arguments by value),
   uint64_t list_wgs;               // or if not 0, of the list kernel,

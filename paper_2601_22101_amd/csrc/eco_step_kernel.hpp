@@ -49,13 +49,14 @@ __device__ __forceinline__ bool use_vector(int nvalid) {
 typedef float eco_f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t eco_u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t eco_u32x2_t __attribute__((ext_vector_type(2)));
-// How a kernel's vector accesses treat the caches.  CACHED: as usual.  The others are for arrays that come from HBM (see stream_pays): loads
+// How a kernel's vector accesses treat the caches.  CACHED: as usual.  The others are for arrays that come from HBM (see stream_launches): loads
 // with the non-temporal hint, and stores with the given bits of the instruction, of which sc1 writes through the L2.  Neither half alone
 // helps, and neither where an instruction covers halves of lines (see exchange_chunks): a copy of the FP8 Adam step's byte mix, 268 M
 // elements, us: 985; instructions over whole lines 944; with loads nt 1008, stores nt 945, both 865, loads nt and stores sc1 nt 837.
 // STREAM_WAVE, of independent waves: 700 M elements in groups of 128 2390 -> 2195 (sc1 alone 2230).  STREAM_GROUP, of workgroups that store
 // behind a barrier: rows of 1152 2303 -> 2118 (with nt 2473), 2304 2342 -> 2142 (2443), 3072 2384 -> 2176 (2270).
 enum : int { CACHED = 0, STREAM_GROUP = 16, STREAM_WAVE = 16 | 2 };          // sc1; sc1 and nt
+constexpr int POLICY_NT = 2;                       // the non-temporal hint, in a buffer instruction
 template <int CP, class V>
 __device__ __forceinline__ V load_vec(const V *p) { return CP != CACHED ? __builtin_nontemporal_load(p) : *p; }
 
@@ -1163,6 +1164,20 @@ hipError_t launch_wide(const StepLaunch &sl, int nw, hipStream_t stream) {
   return hipSuccess;
 }
 
+// The two passes of tensor-wise scaling with the reduction between them.  Past the caches (us): 210 M elements, INT4 601 -> 572, FP8 1109 -> 1020,
+// with master weights 1204 -> 1099; 20 M (220 MB in FP8) would lose, 95 -> 104.
+template <int FMT, bool STATE_BF16, bool SC, int RD, int AL, int CP>
+hipError_t launch_two_passes(const StepLaunch &sl, hipStream_t stream) {
+  const StepArgs &args = sl.args;
+  ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_TILE, CP>), args.num_tw_tiles, WG_THREADS,
+                     sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
+  ECO_CHUNKS_CHECKED((eco_tensorwise_reduce_kernel<FMT>), (uint64_t)args.num_tw_tensors * args.tw_reduce_wgs, TW_REDUCE_THREADS, 0, stream,
+                     args, sl.max_launch_threads);
+  ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_SLOT, CP>), args.num_tw_tiles, WG_THREADS,
+                     sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
+  return hipSuccess;
+}
+
 template <int FMT, bool STATE_BF16, bool SC, int RD, int AL>
 hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
   const StepArgs &args = sl.args;
@@ -1192,12 +1207,9 @@ hipError_t launch_step_kernels(const StepLaunch &sl, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   if (args.num_tw_tiles) {
-    ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_TILE, CACHED>), args.num_tw_tiles, WG_THREADS,
-                       sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
-    ECO_CHUNKS_CHECKED((eco_tensorwise_reduce_kernel<FMT>), (uint64_t)args.num_tw_tensors * args.tw_reduce_wgs, TW_REDUCE_THREADS, 0, stream,
-                       args, sl.max_launch_threads);
-    ECO_CHUNKS_CHECKED((eco_step_tensorwise_kernel<FMT, STATE_BF16, SC, AL, RD, RED_SLOT, CACHED>), args.num_tw_tiles, WG_THREADS,
-                       sl.lds_bytes_tw, stream, args, sl.max_launch_threads);
+    const hipError_t e = sl.stream >> STREAM_TENSORWISE & 1u ? launch_two_passes<FMT, STATE_BF16, SC, RD, AL, STREAM_GROUP>(sl, stream)
+                                                             : launch_two_passes<FMT, STATE_BF16, SC, RD, AL, CACHED>(sl, stream);
+    if (e != hipSuccess) return e;
     ECO_CHUNKS_CHECKED((eco_tensorwise_scale_kernel<FMT, SC>), (args.num_tw_tensors + WG_THREADS - 1) / WG_THREADS, WG_THREADS,
                        0, stream, args, sl.max_launch_threads);
   }

@@ -30,7 +30,7 @@
 // What bounds it: memory for fp32 state (5.2 of the 6.1 TB/s of the block-scaled form); for INT4 with bf16 state the
 // vector ALU's issue beside it (see the counters in profiles/).  Measured, two-pass form -> this one, 369 M elements in
 // tensors of 1408 x 2048: FP8, fp32 state 1964 -> 1430 us; INT4, bf16 state 1112 -> 872 us; three tensors of 40 000
-// elements 14.2 -> 12.8 us; where a list is too short for it or has company that costs launches, see one_pass_pays.  What
+// elements 14.2 -> 12.8 us; past the caches (CP, see there) 1153 M in tensors of that kind FP8 4378 -> 3820 and INT4 2492 -> 2412; where a list is too short for it or has company that costs launches, see one_pass_pays.  What
 // it took: 12 waves of 168 registers rather than 8 of 256 (INT4 1290 -> 1000 us), no memory access inside a branch (1000 ->
 // 940), an event's contributions half a turn before the result is wanted (940 -> 890).  19 of the 80 variants, among them
 // Adam with bf16 state and stochastic rounding, do not quite fit 168 registers and keep 2 to 11 values in scratch memory.
@@ -52,20 +52,39 @@ __device__ __forceinline__ buffer_t tile_buffer(const void *array, uint64_t tile
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(array)) + tile * elem_bytes, 0,
                                            (int)(len * elem_bytes), 0x00020000);
 }
-__device__ __forceinline__ eco_u32x4_t load16(buffer_t b, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0); }
-__device__ __forceinline__ void store16(buffer_t b, uint32_t off, eco_u32x4_t x) { __builtin_amdgcn_raw_buffer_store_b128(x, b, off, 0, 0); }
+template <int CP>
+__device__ __forceinline__ eco_u32x4_t load16(buffer_t b, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, CP != CACHED ? POLICY_NT : 0);
+}
+template <int CP>
+__device__ __forceinline__ void store16(buffer_t b, uint32_t off, eco_u32x4_t x) { __builtin_amdgcn_raw_buffer_store_b128(x, b, off, 0, CP); }
 __device__ __forceinline__ eco_u32x4_t bits4(const float *x) { return eco_u32x4_t{f2u(x[0]), f2u(x[1]), f2u(x[2]), f2u(x[3])}; }
 constexpr int SCOPE_AGENT = 16;        // cache policy: coherent between the XCDs
 
-__device__ __forceinline__ void store_f32_tile(buffer_t b, uint32_t lane, const float (&x)[8]) {
-  store16(b, lane * 32, bits4(x));
-  store16(b, lane * 32 + 16, bits4(x + 4));
+// Eight fp32 of each lane: past the caches in whole lines to an instruction (see exchange_chunks, which a load still needs once it has
+// arrived); from the cache 32 bytes to a lane, without the exchange on a short step's way (1 M elements 13.4 us, with it 14.0).
+template <int CP>
+__device__ __forceinline__ void load_f32_tile(buffer_t b, eco_u32x4_t (&q)[2]) {
+  q[0] = load16<CP>(b, CP != CACHED ? lane_chunk() * 16 : (threadIdx.x & 63) * 32);
+  q[1] = load16<CP>(b, CP != CACHED ? lane_chunk() * 16 + 1024 : (threadIdx.x & 63) * 32 + 16);
 }
-template <bool BF16>
+template <int CP>
+__device__ __forceinline__ void store_f32_tile(buffer_t b, const float (&x)[8]) {
+  eco_u32x4_t q[2] = {bits4(x), bits4(x + 4)};
+  if (CP != CACHED) exchange_chunks(q);
+  store16<CP>(b, CP != CACHED ? lane_chunk() * 16 : (threadIdx.x & 63) * 32, q[0]);
+  store16<CP>(b, CP != CACHED ? lane_chunk() * 16 + 1024 : (threadIdx.x & 63) * 32 + 16, q[1]);
+}
+template <bool BF16, int CP>
+__device__ __forceinline__ void unpack_tile(eco_u32x4_t (&q)[2], float (&x)[8]) {
+  if (!BF16 && CP != CACHED) exchange_chunks(q);
+  unpack8<BF16>(q, x);
+}
+template <bool BF16, int CP>
 __device__ __forceinline__ void store_state_tile(void *array, uint64_t tile, uint32_t len, uint32_t lane, const float (&x)[8]) {
   const buffer_t b = tile_buffer(array, tile, len, BF16 ? 2 : 4);
-  if (BF16) store16(b, lane * 16, pack_bf16x8(x));
-  else store_f32_tile(b, lane, x);
+  if (BF16) store16<CP>(b, lane * 16, pack_bf16x8(x));
+  else store_f32_tile<CP>(b, x);
 }
 
 // What a lane loads for a tile, as it comes from memory.
@@ -76,29 +95,27 @@ struct RawLane {
   eco_u32x4_t g, m[2], v[2], w[2];
 };
 
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO>
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int CP>
 __device__ __forceinline__ void load_raw(const TensorDesc &td, uint64_t tile, uint32_t len, uint32_t lane, RawLane<FMT, STATE_BF16, ALGO> &r) {
   constexpr uint32_t ES = STATE_BF16 ? 2 : 4;
-  r.g = load16(tile_buffer(td.g, tile, len, 2), lane * 16);
+  r.g = load16<CP>(tile_buffer(td.g, tile, len, 2), lane * 16);
   const buffer_t bm = tile_buffer(td.m, tile, len, ES);
-  r.m[0] = load16(bm, lane * (8 * ES));
-  if (!STATE_BF16) r.m[1] = load16(bm, lane * 32 + 16);
+  if (STATE_BF16) r.m[0] = load16<CP>(bm, lane * 16);
+  else load_f32_tile<CP>(bm, r.m);
   if (algo_is_adam(ALGO)) {
     const buffer_t bv = tile_buffer(td.v, tile, len, ES);
-    r.v[0] = load16(bv, lane * (8 * ES));
-    if (!STATE_BF16) r.v[1] = load16(bv, lane * 32 + 16);
+    if (STATE_BF16) r.v[0] = load16<CP>(bv, lane * 16);
+    else load_f32_tile<CP>(bv, r.v);
   }
   if (algo_is_master(ALGO)) {
-    const buffer_t bw = tile_buffer(td.aux, tile, len, 4);
-    r.w[0] = load16(bw, lane * 32);
-    r.w[1] = load16(bw, lane * 32 + 16);
+    load_f32_tile<CP>(tile_buffer(td.aux, tile, len, 4), r.w);
     r.s = 0.0f;
   } else {
     if (FMT == FMT_FP8) {
-      const eco_u32x2_t c = __builtin_amdgcn_raw_buffer_load_b64(tile_buffer(td.w, tile, len, 1), lane * 8, 0, 0);
+      const eco_u32x2_t c = __builtin_amdgcn_raw_buffer_load_b64(tile_buffer(td.w, tile, len, 1), lane * 8, 0, CP != CACHED ? POLICY_NT : 0);
       r.c[0] = c.x; r.c[1] = c.y;
     } else {
-      r.c[0] = __builtin_amdgcn_raw_buffer_load_b32(tile_buffer(td.w, tile >> 1, len >> 1, 1), lane * 4, 0, 0);
+      r.c[0] = __builtin_amdgcn_raw_buffer_load_b32(tile_buffer(td.w, tile >> 1, len >> 1, 1), lane * 4, 0, CP != CACHED ? POLICY_NT : 0);
       r.c[1] = 0;
     }
     r.s = SCALE_BF16 ? u2f((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(tile_buffer(td.s, 0, 1, 2), 0, 0, 0) << 16)
@@ -124,7 +141,7 @@ __device__ __forceinline__ uint32_t lds_add1(uint32_t *p) {
   return old;
 }
 
-template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND>
+template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int CP>
 __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_resident_kernel(const StepArgs a) {
   constexpr bool ADAM = algo_is_adam(ALGO), MASTER = algo_is_master(ALGO);
   constexpr bool KEEP_D = ALGO == ALGO_ADAM;                       // the injection of the other variants does not use d
@@ -164,7 +181,7 @@ __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_reside
     next_tile = tile_at(td, slab);
     next_len = any ? len_at(next_tile, td.numel) : 0;
     next_v = td.v;
-    load_raw<FMT, STATE_BF16, SCALE_BF16, ALGO>(td, next_tile, next_len, lane, raw);
+    load_raw<FMT, STATE_BF16, SCALE_BF16, ALGO, CP>(td, next_tile, next_len, lane, raw);
   };
   start_loads(load_tensor_desc(a, ti_next), slab_of(0), true);
 
@@ -197,10 +214,10 @@ __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_reside
       ti[s] = ti_next;
       const eco_u32x4_t graw[2] = {raw.g, raw.g};
       unpack8<true>(graw, g);
-      unpack8<STATE_BF16>(raw.m, m[s]);
-      if (ADAM) unpack8<STATE_BF16>(raw.v, v);
+      unpack_tile<STATE_BF16, CP>(raw.m, m[s]);
+      if (ADAM) unpack_tile<STATE_BF16, CP>(raw.v, v);
       if (MASTER) {
-        unpack8<false>(raw.w, w);
+        unpack_tile<false, CP>(raw.w, w);
       } else {
         sc = decode8<FMT>(raw.c, raw.s, w);
         if (!exact_scale<SCALE_BF16, ALGO>()) {
@@ -213,7 +230,7 @@ __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_reside
       start_loads(tn, slab_of(i + 1 < n ? i + 1 : n - 1), i + 1 < n);
       ti_after = tensor_of(i + 2);
       if (KEEP_V) v_kept[KEEP_V ? s : 0] = pack_bf16x8(v);
-      else if (ADAM) store_f32_tile(tile_buffer(v_out, tile, len, 4), lane, v);
+      else if (ADAM) store_f32_tile<CP>(tile_buffer(v_out, tile, len, 4), v);
       // the entries loaded at the end of the last turn, normally complete: half a turn before the sum of them is wanted
       const bool early = wanted && wave_all(entry != NO_MAX);
       if (early) contribute(wave_umax(entry));
@@ -287,9 +304,9 @@ __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_reside
         }
       }
       if (ALGO == ALGO_SGDM_EXACT) {
-        const buffer_t b = tile_buffer(td.aux, out, out_len, 4);
-        const eco_u32x4_t q[2] = {load16(b, lane * 32), load16(b, lane * 32 + 16)};
-        unpack8<false>(q, eo);
+        eco_u32x4_t q[2];
+        load_f32_tile<CP>(tile_buffer(td.aux, out, out_len, 4), q);
+        unpack_tile<false, CP>(q, eo);
       }
       if (out_len) {
         if (KEEP_D) {
@@ -303,13 +320,13 @@ __global__ __launch_bounds__(RES_WAVES * 64, RES_WAVES / 4) void eco_step_reside
         if (!MASTER) inject_lane8<SCALE_BF16, ALGO>(a, s_new, th[o], qn, d, m[o], eo);
       }
       if (FMT == FMT_FP8)
-        __builtin_amdgcn_raw_buffer_store_b64(eco_u32x2_t{cn[0], cn[1]}, tile_buffer(td.w, out, out_len, 1), lane * 8, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(eco_u32x2_t{cn[0], cn[1]}, tile_buffer(td.w, out, out_len, 1), lane * 8, 0, CP);
       else
-        __builtin_amdgcn_raw_buffer_store_b32(cn[0], tile_buffer(td.w, out >> 1, out_len >> 1, 1), lane * 4, 0, 0);
-      if (MASTER) store_f32_tile(tile_buffer(td.aux, out, out_len, 4), lane, th[o]);
-      if (ALGO == ALGO_SGDM_EXACT) store_f32_tile(tile_buffer(td.aux, out, out_len, 4), lane, eo);
-      store_state_tile<STATE_BF16>(td.m, out, out_len, lane, m[o]);
-      if (KEEP_V) store16(tile_buffer(td.v, out, out_len, 2), lane * 16, v_kept[KEEP_V ? o : 0]);
+        __builtin_amdgcn_raw_buffer_store_b32(cn[0], tile_buffer(td.w, out >> 1, out_len >> 1, 1), lane * 4, 0, CP);
+      if (MASTER) store_f32_tile<CP>(tile_buffer(td.aux, out, out_len, 4), th[o]);
+      if (ALGO == ALGO_SGDM_EXACT) store_f32_tile<CP>(tile_buffer(td.aux, out, out_len, 4), eo);
+      store_state_tile<STATE_BF16, CP>(td.m, out, out_len, lane, m[o]);
+      if (KEEP_V) store16<CP>(tile_buffer(td.v, out, out_len, 2), lane * 16, v_kept[KEEP_V ? o : 0]);
 
       // the entries the next turn's event wants, if there is one
       const uint32_t t = ti[(s + 2) % D];
@@ -398,7 +415,10 @@ hipError_t launch_resident(const StepLaunch &sl, hipStream_t stream) {
   }
   ta = sl.args;
   ta.resident_wgs = wgs;
-  ECO_LAUNCH_CHECKED((eco_step_resident_kernel<FMT, STATE_BF16, SC, AL, RD>), dim3(wgs), dim3(block), 0, stream, ta);
+  if (sl.stream >> STREAM_TENSORWISE & 1u)
+    ECO_LAUNCH_CHECKED((eco_step_resident_kernel<FMT, STATE_BF16, SC, AL, RD, STREAM_WAVE>), dim3(wgs), dim3(block), 0, stream, ta);
+  else
+    ECO_LAUNCH_CHECKED((eco_step_resident_kernel<FMT, STATE_BF16, SC, AL, RD, CACHED>), dim3(wgs), dim3(block), 0, stream, ta);
   unsigned fin = res_finish_workgroups(sl.args.num_resident, sl.args.num_slabs, sl.resident_wgs);
   if (fin > 2 * most) fin = 2 * most;
   ta.resident_wgs = fin;

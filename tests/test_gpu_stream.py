@@ -80,3 +80,29 @@ def test_arrays_that_begin_off_a_line(off):
         out.append(x)
     for k in base:
         assert torch.equal(out[0][k].contiguous().view(torch.uint8), out[1][k].contiguous().view(torch.uint8)), k
+
+
+@pytest.mark.parametrize("longer", [False, True])
+@pytest.mark.parametrize("fmt,bf16,over", [("fp8", False, {}), ("fp8", False, dict(mode=3, weight_decay=0.1)), ("int4", True, {}),
+                                           ("fp8", False, dict(opt=1, mode=2, lr=0.05))])
+def test_one_scale_per_tensor_past_the_caches(longer, fmt, bf16, over):
+    """In one pass and in two: tensors that end within a slab, within a wave's tile and within a lane's piece."""
+    from paper_2601_22101_amd import harness
+    o32 = oracle.get("f32")
+    n = int(420e6 / bytes_per_element(fmt, bf16, over))
+    sizes = [n] if longer else [n // 16 + d for d in (0, 8, 256, 264, -8, 1)] + [n // 16 // 6144 * 6144] * 10
+    specs = [T(f"l{k}_{m}", (m,), fmt, granularity="tensor") for k, m in enumerate(sizes + [6144, 300_000, 300_003, 70_000])]
+    wl = workloads.Workload("stream_tensorwise", specs, steps=1, state_bf16=bf16, scale_bf16=bf16)
+    dw = harness.DeviceWorkload(wl, DEV, layout=over)
+    host = [host_copy(tv) for tv in dw.tensors]
+    dw.fill_gradients(1)
+    hp = dw.hparams(1)
+    for tv, h in zip(dw.tensors, host):
+        h["grad"] = bf16_bits(tv.grad)
+    dw.plan.step(hp)
+    torch.cuda.synchronize()
+    for tv, h in zip(dw.tensors, host):
+        oracle_step(o32, h, tv.spec.numel, step_config(hp, tv.tensor_id, tv.fmt, group_size=dw.group_size(tv)))
+        st = compare(host_copy(tv), h, f"{tv.spec.name}", bf16)
+        assert not any(v for key, v in st.items() if key.endswith("mismatch")), (tv.spec.name, st)
+    dw.close()
