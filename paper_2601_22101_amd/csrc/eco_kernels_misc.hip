@@ -54,14 +54,31 @@ hipError_t launch_step(const KernelVariant &kv, const StepLaunch &sl, hipStream_
 // The two-pass form keeps its partial maxima, between its kernels, in one of QUANT_SLOTS file-scope slots; the host
 // hands the slots out in turn and makes a call wait (on its own stream) for the previous user of its slot, so
 // calls on different streams never share a slot that is in use.
+constexpr uint64_t STREAM_BYTES = 280000000;       // from here on arrays come from HBM and go past the caches
 constexpr int QUANT_SLOTS = 64, QUANT_PARTS = 256;
 __device__ uint32_t g_quantize_parts[QUANT_SLOTS][QUANT_PARTS];
 
-template <int FMT, bool SCALE_BF16, bool SRC_BF16, int ACC, int RED>
+// Eight elements of each lane of a wave, with the cut piece if there is one: ACC_FULL or ACC_LANE (see WavePieces).
+template <bool BF16, int ACC, int CP>
+__device__ __forceinline__ void load_wave(const void *base, uint64_t e0, int nvalid, const WavePieces &wp, float (&x)[8]) {
+  eco_u32x4_t q[2] = {};
+  if (wp.any_whole) load_wave8<BF16, ACC == ACC_FULL, CP>(base, wp, q);
+  if (wp.any_cut) {
+    if (nvalid & 7) load_ragged8<BF16>(base, e0, nvalid, q);
+  }
+  unpack8<BF16>(q, x);
+}
+
+// How the quantizer's kernels load and store beside CACHED and STREAM_GROUP: a lane by itself, 32 bytes of fp32 to each.
+constexpr int PER_LANE = -1;
+
+template <int FMT, bool SCALE_BF16, bool SRC_BF16, int ACC, int RED, int CP>
 __device__ __forceinline__ void quantize_lane(const void *src, void *weights, void *scales, uint64_t e0, int nvalid,
                                               uint64_t sg, int arg, bool scale_writer, int lanes = 0, uint32_t *slot = nullptr) {
+  [[maybe_unused]] const WavePieces wp = ACC == ACC_FULL ? full_wave(e0) : wave_pieces(e0, nvalid);
   float x[8];
-  load_state8<SRC_BF16, ACC>(src, e0, nvalid, x);
+  if constexpr (CP == PER_LANE) load_state8<SRC_BF16, ACC>(src, e0, nvalid, x);
+  else load_wave<SRC_BF16, ACC, CP>(src, e0, nvalid, wp, x);
   const float amax = group_absmax<RED>(absmax8(x), arg, slot, lanes);        // lanes: see there
   float s_new, inv;
   block_scale<FMT, SCALE_BF16>(amax, s_new, inv);
@@ -69,46 +86,47 @@ __device__ __forceinline__ void quantize_lane(const void *src, void *weights, vo
   const Philox4 none = {0, 0, 0, 0};
   float q[8];
   encode8<FMT, ROUND_RTN, false>(x, inv, none, c, q);
-  store_codes8<FMT, ACC>(weights, e0, nvalid, c);
+  if constexpr (CP == PER_LANE) store_codes8<FMT, ACC>(weights, e0, nvalid, c);
+  else store_wave_codes8<FMT, ACC, CP>(weights, e0, nvalid, wp, c);
   if (scale_writer && (ACC == ACC_FULL || nvalid > 0)) {
     if (SCALE_BF16) static_cast<uint16_t *>(scales)[sg] = (uint16_t)(f2u(s_new) >> 16);
     else static_cast<float *>(scales)[sg] = s_new;
   }
 }
 
-template <int FMT, bool SCALE_BF16, bool SRC_BF16>
+template <int FMT, bool SCALE_BF16, bool SRC_BF16, int CP>
 __global__ __launch_bounds__(WG_THREADS) void eco_quantize_kernel(const void *src, uint64_t numel, uint32_t bs_shift,
                                                                   void *weights, void *scales) {
   const uint64_t e0 = (uint64_t)blockIdx.x * TILE_ELEMS + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
   const bool writer = (threadIdx.x & ((1u << (bs_shift - 3)) - 1u)) == 0;
   if ((uint64_t)(blockIdx.x + 1) * TILE_ELEMS <= numel)
-    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_FULL, RED_BLOCK>(src, weights, scales, e0, 8, e0 >> bs_shift, (int)bs_shift, writer);
+    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_FULL, RED_BLOCK, CP>(src, weights, scales, e0, 8, e0 >> bs_shift, (int)bs_shift, writer);
   else
-    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_GUARDED, RED_BLOCK>(src, weights, scales, e0, valid_from(e0, numel),
-                                                                     e0 >> bs_shift, (int)bs_shift, writer);
+    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_BLOCK, CP>(src, weights, scales, e0, valid_from(e0, numel),
+                                                                      e0 >> bs_shift, (int)bs_shift, writer);
 }
 
 // Groups of up to 512 elements that are no power of two: `rows` whole groups to a wave; ONE: one of more than 256 elements,
 // reduced over the whole wave (13 M bf16 elements in rows of 264: 17.1 us with the segmented reduction).
-template <int FMT, bool SCALE_BF16, bool SRC_BF16, bool ONE>
+template <int FMT, bool SCALE_BF16, bool SRC_BF16, bool ONE, int CP>
 __global__ __launch_bounds__(WG_THREADS) void eco_quantize_rows_kernel(const void *src, uint64_t numel, uint32_t group_size, uint32_t rows,
                                                                        void *weights, void *scales) {
   if (ONE) {
     const uint64_t e0 = (uint64_t)blockIdx.x * group_size + (uint64_t)threadIdx.x * ELEMS_PER_LANE, end = (uint64_t)(blockIdx.x + 1) * group_size;
-    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_BLOCK>(src, weights, scales, e0, valid_from(e0, end < numel ? end : numel), blockIdx.x, 9,
+    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_BLOCK, CP>(src, weights, scales, e0, valid_from(e0, end < numel ? end : numel), blockIdx.x, 9,
                                                                   threadIdx.x == 0);
     return;
   }
   const uint32_t gl = group_size >> 3, row = (threadIdx.x * (65536u / gl + 1u)) >> 16;    // lane / lanes of a group, exact below 64
   const uint64_t grp = (uint64_t)blockIdx.x * rows, e0 = grp * group_size + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
   const uint64_t end = (grp + rows) * group_size;
-  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_ROWS>(src, weights, scales, e0, valid_from(e0, end < numel ? end : numel),
+  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_ROWS, CP>(src, weights, scales, e0, valid_from(e0, end < numel ? end : numel),
                                                                grp + row, (int)(row * gl), threadIdx.x == row * gl, (int)gl);
 }
 
 // Wide groups: one to a workgroup, or (BUNDLE) as many as fill a whole number of waves (see quantizer_takes_bundle; two
 // kernels, because the other form's code alone cost rows of 6912 up to 4 %).
-template <int FMT, bool SCALE_BF16, bool SRC_BF16, bool BUNDLE>
+template <int FMT, bool SCALE_BF16, bool SRC_BF16, bool BUNDLE, int CP>
 __global__ __launch_bounds__(1024) void eco_quantize_wide_kernel(const void *src, uint64_t numel, uint32_t group_size, uint32_t rows,
                                                                  void *weights, void *scales) {
   const uint64_t grp = (uint64_t)blockIdx.x * (BUNDLE ? rows : 1), start = grp * group_size;
@@ -117,37 +135,66 @@ __global__ __launch_bounds__(1024) void eco_quantize_wide_kernel(const void *src
   if (BUNDLE) {
     uint32_t row = 0;
     for (uint32_t k = 1; k < rows; ++k) row += lane_elem >= k * group_size ? 1u : 0u;
-    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_FULL, RED_WG_ROWS>(src, weights, scales, e0, 8, grp + row, (int)row,
+    quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_FULL, RED_WG_ROWS, CP>(src, weights, scales, e0, 8, grp + row, (int)row,
                                                                     lane_elem == row * group_size);
     return;
   }
   const uint64_t end = start + group_size < numel ? start + group_size : numel;
-  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_WG>(src, weights, scales, e0, valid_from(e0, end), grp, 0, threadIdx.x == 0,
+  quantize_lane<FMT, SCALE_BF16, SRC_BF16, ACC_LANE, RED_WG, CP>(src, weights, scales, e0, valid_from(e0, end), grp, 0, threadIdx.x == 0,
                                                              (int)((group_size + TILE_ELEMS - 1) / TILE_ELEMS));
 }
 
 // Tensor-wise, first pass: the maximum over each workgroup's share.  One workgroup per partial maximum, which is stored, not
-// merged: an atomic maximum per wave on one address took 220 us over 210 M bf16 elements; this takes 103, of which the read
-// at the rate of a large copy would be 68 (one workgroup per compute unit, four loads of a lane under way).
+// merged: an atomic maximum per wave on one address took 220 us over 210 M bf16 elements.  What bounds it is the reads under way: a workgroup of
+// 16 waves to a compute unit, two tiles of each wave under way, a tile's loads out again as soon as it is taken (waiting for four together, then
+// loading again: 103 us; both passes of the quantizer over 250 M elements 210 -> 188, with four tiles 192, with eight more).
 constexpr int QUANT_MAX_THREADS = 1024;
-template <bool SRC_BF16>
+constexpr uint32_t QUANT_MAX_TILES = 2;
+template <bool SRC_BF16, int CP>
 __global__ __launch_bounds__(QUANT_MAX_THREADS) void eco_quantize_max_kernel(const void *src, uint64_t numel, uint32_t slot, uint32_t parts) {
-  const uint64_t stride = (uint64_t)parts * QUANT_MAX_THREADS * ELEMS_PER_LANE;
-  uint64_t e0 = ((uint64_t)blockIdx.x * QUANT_MAX_THREADS + threadIdx.x) * ELEMS_PER_LANE;
+  constexpr uint32_t WAVES = QUANT_MAX_THREADS / 64, UNDER_WAY = QUANT_MAX_TILES, CHUNKS = SRC_BF16 ? 1 : 2;
+  const uint32_t stride = parts * WAVES;
+  const uint64_t whole = numel / TILE_ELEMS, tiles = (numel + TILE_ELEMS - 1) / TILE_ELEMS;
+  uint64_t tile = blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Chunk k of a lane's share of a tile; fp32 needs exchange_chunks once it has arrived.
+  const auto load = [&](uint64_t t, uint32_t k) {
+    const eco_u32x4_t *p = static_cast<const eco_u32x4_t *>(src) + t * (64 * CHUNKS);
+    return load_vec<CP>(p + (SRC_BF16 ? threadIdx.x & 63 : lane_chunk() + 64 * k));
+  };
   // The maximum is one of bit patterns, as in every other reduction of the library: the float maximum would drop the NaN
   // of a lane all of whose elements are NaN.
   uint32_t amax = 0;
-  float x[4][8];
   const auto take = [&amax](const float (&y)[8]) { const uint32_t a = f2u(absmax8(y)); amax = amax > a ? amax : a; };
-  for (; e0 + 3 * stride + 8 <= numel; e0 += 4 * stride) {      // four independent loads under way
+  const auto take_raw = [&take](eco_u32x4_t (&q)[2]) {
+    float x[8];
+    if (!SRC_BF16) exchange_chunks(q);
+    unpack8<SRC_BF16>(q, x);
+    take(x);
+  };
+  eco_u32x4_t q[UNDER_WAY][2] = {};
+  const uint64_t ahead = (uint64_t)(UNDER_WAY - 1) * stride;
+  if (tile + ahead < whole) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) load_state8<SRC_BF16, ACC_FULL>(src, e0 + k * stride, 8, x[k]);
+    for (uint32_t u = 0; u < UNDER_WAY; ++u)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) take(x[k]);
+      for (uint32_t k = 0; k < CHUNKS; ++k) q[u][k] = load(tile + (uint64_t)u * stride, k);
+    for (tile += ahead + stride; tile + ahead < whole; tile += ahead + stride) {
+#pragma unroll
+      for (uint32_t u = 0; u < UNDER_WAY; ++u) {           // a tile's loads go out as soon as the one before it in its registers is taken
+        take_raw(q[u]);
+#pragma unroll
+        for (uint32_t k = 0; k < CHUNKS; ++k) q[u][k] = load(tile + (uint64_t)u * stride, k);
+      }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < UNDER_WAY; ++u) take_raw(q[u]);
   }
-  for (; e0 < numel; e0 += stride) {
-    load_state8<SRC_BF16, ACC_LANE>(src, e0, valid_from(e0, numel), x[0]);
-    take(x[0]);
+  for (; tile < tiles; tile += stride) {
+    const uint64_t e0 = tile * TILE_ELEMS + (threadIdx.x & 63) * ELEMS_PER_LANE;
+    const int nvalid = valid_from(e0, numel);
+    float x[8];
+    load_wave<SRC_BF16, ACC_LANE, CP>(src, e0, nvalid, wave_pieces(e0, nvalid), x);
+    take(x);
   }
   __shared__ uint32_t wave_max[QUANT_MAX_THREADS / 64];
   const uint32_t w = wave_umax(amax);
@@ -163,7 +210,7 @@ __global__ __launch_bounds__(QUANT_MAX_THREADS) void eco_quantize_max_kernel(con
 // the one with the first element writes the scale.  fp32 sources backwards: the cache before HBM still holds the end of the first pass's
 // reads (INT4, 80 M elements 113 us forwards, 106 backwards, 100 M 146 / 138, and with the quantization error behind it 235 / 231; up
 // to 240 MB no difference).  bf16 sources forwards: 200 M elements 189 / 178, but with the error behind it 210 M 417 / 421.
-template <int FMT, bool SCALE_BF16, bool SRC_BF16>
+template <int FMT, bool SCALE_BF16, bool SRC_BF16, int CP>
 __global__ __launch_bounds__(QUANT_PARTS) void eco_quantize_tensorwise_kernel(const void *src, uint64_t numel, uint32_t parts,
                                                                               void *weights, void *scales, uint32_t slot,
                                                                               uint32_t first_wg) {
@@ -172,8 +219,10 @@ __global__ __launch_bounds__(QUANT_PARTS) void eco_quantize_tensorwise_kernel(co
   const uint64_t e0 = wg * SHARE + (uint64_t)threadIdx.x * ELEMS_PER_LANE;
   const int nvalid = valid_from(e0, numel);
   const uint32_t part = threadIdx.x < parts ? g_quantize_parts[slot][threadIdx.x] : 0u;
+  [[maybe_unused]] const WavePieces wp = wave_pieces(e0, nvalid);
   float x[8];
-  load_state8<SRC_BF16, ACC_LANE>(src, e0, nvalid, x);
+  if constexpr (CP == PER_LANE) load_state8<SRC_BF16, ACC_LANE>(src, e0, nvalid, x);
+  else load_wave<SRC_BF16, ACC_LANE, CP>(src, e0, nvalid, wp, x);
   __shared__ uint32_t wave_max[QUANT_PARTS / 64];
   const uint32_t w = wave_umax(part);
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = w;
@@ -187,7 +236,8 @@ __global__ __launch_bounds__(QUANT_PARTS) void eco_quantize_tensorwise_kernel(co
   const Philox4 none = {0, 0, 0, 0};
   float q[8];
   encode8<FMT, ROUND_RTN, false>(x, inv, none, c, q);
-  store_codes8<FMT, ACC_LANE>(weights, e0, nvalid, c);
+  if constexpr (CP == PER_LANE) store_codes8<FMT, ACC_LANE>(weights, e0, nvalid, c);
+  else store_wave_codes8<FMT, ACC_LANE, CP>(weights, e0, nvalid, wp, c);
   if (e0 == 0) {
     if (SCALE_BF16) static_cast<uint16_t *>(scales)[0] = (uint16_t)(f2u(s_new) >> 16);
     else static_cast<float *>(scales)[0] = s_new;
@@ -214,36 +264,50 @@ static QuantSlotRing g_quant_ring;
     }                                                                                                                      \
   } while (0)
 
+// Which form the quantizer's kernels take (CP).  From 280 MB of source and codes on, in one pass, or of source, in two (the second finds
+// less in the cache before HBM), they go past the caches; not in groups of more than 4096 elements, nor from bf16 where groups fill their waves or share them.
+// us, per lane / past the caches: FP8 from fp32, groups of 128, 225 MB 32.0 / 34.3, 300 46.9 / 44.0, 600 102 / 86; rows of 4096 350 MB 57.6 / 54.1,
+// 1 GB 164 / 149, 1000 56.9 / 52.5, 176 / 146, 2304 59.7 / 58.6, 170 / 164, 6912 61.1 / 62.9, 169 / 175; from bf16 2304 300 MB 75.4 / 74.0, 1000 64.8 /
+// 59.9, 4096 61.9 / 63.1, 576 91.0 / 95.3.  One scale, from fp32 240 MB 76.2 / 79.7, 320 106.7 / 103.4, 520 184 / 163, from bf16 200 MB 71.7 / 79.5, 280 111.6 /
+// 108.3, 500 210 / 188; with the error behind it 210 M elements from bf16 415 / 361.  What is left goes by whole pieces of a wave in rows with idle
+// lanes (CACHED; from bf16, rows of 192 70 M elements 61.7 / 55.7, 1000 41.7 / 38.5), per lane elsewhere (4 M elements 4.1 / 4.2, 1152 26.5 / 27.4).
 template <int FMT, bool SC, bool SR>
 static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t group_size, void *weights, void *scales,
                                     hipStream_t stream) {
+  const uint64_t src_bytes = numel * (SR ? 2 : 4), bytes = src_bytes + (FMT == FMT_INT4 ? numel / 2 : numel);
+  const bool streamed = bytes >= STREAM_BYTES;
   const uint64_t tiles = (numel + TILE_ELEMS - 1) / TILE_ELEMS;
   const int cls = classify_group(group_size, numel);
+  const auto row = streamed ? eco_quantize_rows_kernel<FMT, SC, SR, true, STREAM_GROUP> : eco_quantize_rows_kernel<FMT, SC, SR, true, CACHED>;
   if (cls == GROUP_BLOCK) {
-    ECO_LAUNCH_CHECKED((eco_quantize_kernel<FMT, SC, SR>), dim3((unsigned)tiles), dim3(WG_THREADS), 0, stream, src, numel,
-                       (uint32_t)log2_exact(group_size), weights, scales);
+    const auto kernel = streamed ? eco_quantize_kernel<FMT, SC, SR, STREAM_GROUP> : eco_quantize_kernel<FMT, SC, SR, PER_LANE>;
+    ECO_LAUNCH_CHECKED(kernel, dim3((unsigned)tiles), dim3(WG_THREADS), 0, stream, src, numel, (uint32_t)log2_exact(group_size), weights, scales);
   } else if (cls == GROUP_WIDE) {
     const Placement p = place_tensor(numel, group_size, cls, true, FMT);
-    if (p.kind == UNIT_ROW)
-      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR, true>), dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel,
-                         (uint32_t)p.group, p.rows, weights, scales);
-    else if (p.kind == UNIT_ROWS)
-      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR, false>), dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel,
-                         (uint32_t)p.group, p.rows, weights, scales);
-    else if (quantizer_takes_bundle(p.rows, p.group, FMT))
-      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, true>), dim3((unsigned)p.units), dim3(64 * (p.list - LIST_WIDE1 + 1)), 0, stream,
-                         src, numel, (uint32_t)p.group, p.rows, weights, scales);
-    else
-      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, false>), dim3((unsigned)((numel + p.group - 1) / p.group)),
-                         dim3((unsigned)((p.group + TILE_ELEMS - 1) / TILE_ELEMS) * 64), 0, stream, src, numel, (uint32_t)p.group, 1u, weights, scales);
+    if (p.kind == UNIT_ROW) {
+      ECO_LAUNCH_CHECKED(row, dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel, (uint32_t)p.group, p.rows, weights, scales);
+    } else if (p.kind == UNIT_ROWS) {
+      const auto rows = streamed ? eco_quantize_rows_kernel<FMT, SC, SR, false, STREAM_GROUP> : eco_quantize_rows_kernel<FMT, SC, SR, false, CACHED>;
+      ECO_LAUNCH_CHECKED(rows, dim3((unsigned)p.units), dim3(WG_THREADS), 0, stream, src, numel, (uint32_t)p.group, p.rows, weights, scales);
+    } else if (quantizer_takes_bundle(p.rows, p.group, FMT)) {
+      const auto bundle = streamed && !SR ? eco_quantize_wide_kernel<FMT, SC, SR, true, STREAM_GROUP> : eco_quantize_wide_kernel<FMT, SC, SR, true, PER_LANE>;
+      ECO_LAUNCH_CHECKED(bundle, dim3((unsigned)p.units), dim3(64 * (p.list - LIST_WIDE1 + 1)), 0, stream, src, numel, (uint32_t)p.group, p.rows,
+                         weights, scales);
+    } else {
+      const bool fills = p.group % TILE_ELEMS == 0;
+      const auto wide = streamed && p.group <= 4096 && !(fills && SR) ? eco_quantize_wide_kernel<FMT, SC, SR, false, STREAM_GROUP>
+                        : fills                                       ? eco_quantize_wide_kernel<FMT, SC, SR, false, PER_LANE>
+                                                                      : eco_quantize_wide_kernel<FMT, SC, SR, false, CACHED>;
+      ECO_LAUNCH_CHECKED(wide, dim3((unsigned)((numel + p.group - 1) / p.group)), dim3((unsigned)((p.group + TILE_ELEMS - 1) / TILE_ELEMS) * 64), 0,
+                         stream, src, numel, (uint32_t)p.group, 1u, weights, scales);
+    }
   } else if (numel <= MAX_WIDE_GROUP) {
     // one scale for a tensor that one workgroup holds: one group (4001 elements, us: in two passes, with their event, 8.9, so 4.3)
     if (numel <= static_cast<uint64_t>(TILE_ELEMS))
-      ECO_LAUNCH_CHECKED((eco_quantize_rows_kernel<FMT, SC, SR, true>), dim3(1), dim3(WG_THREADS), 0, stream, src, numel, (uint32_t)numel, 1u,
-                         weights, scales);
+      ECO_LAUNCH_CHECKED(row, dim3(1), dim3(WG_THREADS), 0, stream, src, numel, (uint32_t)numel, 1u, weights, scales);
     else
-      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, false>), dim3(1), dim3((unsigned)tiles * 64), 0, stream, src, numel, (uint32_t)numel,
-                         1u, weights, scales);
+      ECO_LAUNCH_CHECKED((eco_quantize_wide_kernel<FMT, SC, SR, false, CACHED>), dim3(1), dim3((unsigned)tiles * 64), 0, stream, src, numel,
+                         (uint32_t)numel, 1u, weights, scales);
   } else {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -262,8 +326,11 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
     constexpr uint64_t max_share = (uint64_t)QUANT_MAX_THREADS * ELEMS_PER_LANE;
     const uint64_t want = (numel + max_share - 1) / max_share;
     const uint32_t parts = want < QUANT_PARTS ? (uint32_t)want : QUANT_PARTS;
-    ECO_LAUNCH_CHECKED((eco_quantize_max_kernel<SR>), dim3(parts), dim3(QUANT_MAX_THREADS), 0, stream, src, numel, slot, parts);
-    ECO_FLAT_CHECKED(flat_launch(numel, QUANT_PARTS), QUANT_PARTS, stream, (eco_quantize_tensorwise_kernel<FMT, SC, SR>), src, numel,
+    const bool past = src_bytes >= STREAM_BYTES;
+    const auto maximum = past ? eco_quantize_max_kernel<SR, STREAM_GROUP> : eco_quantize_max_kernel<SR, CACHED>;
+    const auto second = past ? eco_quantize_tensorwise_kernel<FMT, SC, SR, STREAM_GROUP> : eco_quantize_tensorwise_kernel<FMT, SC, SR, PER_LANE>;
+    ECO_LAUNCH_CHECKED(maximum, dim3(parts), dim3(QUANT_MAX_THREADS), 0, stream, src, numel, slot, parts);
+    ECO_FLAT_CHECKED(flat_launch(numel, QUANT_PARTS), QUANT_PARTS, stream, second, src, numel,
                      parts, weights, scales, slot);
     e = hipEventRecord(done, stream);
     if (e != hipSuccess) return e;
@@ -302,18 +369,25 @@ struct GroupOf { uint64_t size; double reciprocal; int32_t shift; };       // sh
 // 12.9, 100 M 109 / 114, 450 M 486 / 481 (FP8 528 / 512); fp32 source, INT4: 5 M 6.9 / 7.7, 10 M 13.6 / 14.5, 20 M 27.2 /
 // 26.5, 40 M 60.2 / 58.9, 200 M 292 / 284.  (The threads are a template parameter: a kernel that asks for blockDim is passed
 // 256 bytes of arguments more, 0.8 us of a call.)
+// Stores of fp32 cover whole lines (see exchange_chunks: INT4, 2.9 M elements 4.9 -> 4.3 us, FP8 12 M in groups of 1000 11.3 -> 10.2), and from
+// 280 MB of arrays on they and the loads go past the caches.  us, before / so, usual: FP8 70 M 61.4 / 50.8, 59.4, INT4 70 M 62.4 / 54.5, 62.8, 200 M
+// 167 / 155, 170 (below, 225 MB: 34.3 / 41.1, 34.4); with a source FP8 from fp32 35 M 54.1 / 50.6, 51.8, 150 M 229 / 209, 228, INT4 from bf16
+// 60 M 68.0 / 60.6, 65.3, 200 M 215 / 199, 214.  Without the hint on the stores (STREAM_GROUP) errors of up to 700 MB alone take 8 % less, but they
+// push the source out of the cache before HBM: with the quantizer before them 60 M from bf16 119 instead of 103.
 inline bool long_error_call(int src_kind, uint64_t numel) { return numel >= (src_kind == 1 ? 1ull << 24 : 1ull << 28); }
 
-template <int FMT, bool SCALE_BF16, int SRC, int THREADS>
-__global__ __launch_bounds__(THREADS) void eco_dequantize_kernel(const void *weights, const void *scales, uint64_t numel,
-                                                                         GroupOf group, const void *src, float *dst, uint32_t first_wg) {
-  const uint64_t e0 = (((uint64_t)first_wg + blockIdx.x) * THREADS + threadIdx.x) * ELEMS_PER_LANE;
-  const int nvalid = valid_from(e0, numel);
-  if (nvalid == 0) return;
-  uint32_t c[2];
-  load_codes8<FMT, ACC_LANE>(weights, e0, nvalid, c);
+template <int FMT, bool SCALE_BF16, int SRC, int THREADS, int ACC, int CP>
+__device__ __forceinline__ void dequantize_lane(const void *weights, const void *scales, uint64_t first, int nvalid, const GroupOf &group,
+                                                const void *src, float *dst) {
+  const WavePieces wp = ACC == ACC_FULL ? full_wave(first) : wave_pieces(first, nvalid);
+  uint32_t c[2] = {0, 0};
+  if (wp.any_whole) load_codes8<FMT, ACC_FULL, CP>(weights, wp.from, 8, c);
+  if (wp.any_cut) {
+    if (nvalid & 7) load_ragged_codes8<FMT>(weights, first, nvalid, c);
+  }
   float t[8];
-  if (SRC != 0 && THREADS == 128) load_state8<SRC == 2, ACC_LANE>(src, e0, nvalid, t);
+  if (SRC != 0 && THREADS == 128) load_wave<SRC == 2, ACC, CP>(src, first, nvalid, wp, t);
+  const uint64_t e0 = ACC == ACC_FULL || nvalid > 0 ? first : 0;          // lanes beyond the end read the first scale
   uint64_t sg;
   if (group.shift >= 0) {
     sg = e0 >> group.shift;
@@ -337,11 +411,21 @@ __global__ __launch_bounds__(THREADS) void eco_dequantize_kernel(const void *wei
     for (int j = 0; j < 8; ++j) x[j] *= ((uint64_t)j < boundary ? s0 : s1);
   }
   if (SRC != 0) {
-    if (THREADS != 128) load_state8<SRC == 2, ACC_LANE>(src, e0, nvalid, t);
+    if (THREADS != 128) load_wave<SRC == 2, ACC, CP>(src, first, nvalid, wp, t);
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = t[j] - x[j];
   }
-  store_f32x8<ACC_LANE>(dst + e0, nvalid, x);
+  store_wave8<false, ACC, CP>(dst, first, nvalid, wp, x);
+}
+
+template <int FMT, bool SCALE_BF16, int SRC, int THREADS, int CP>
+__global__ __launch_bounds__(THREADS) void eco_dequantize_kernel(const void *weights, const void *scales, uint64_t numel,
+                                                                         GroupOf group, const void *src, float *dst, uint32_t first_wg) {
+  const uint64_t first = ((uint64_t)first_wg + blockIdx.x) * (THREADS * ELEMS_PER_LANE), e0 = first + threadIdx.x * ELEMS_PER_LANE;
+  if (first + THREADS * ELEMS_PER_LANE <= numel)
+    dequantize_lane<FMT, SCALE_BF16, SRC, THREADS, ACC_FULL, CP>(weights, scales, e0, 8, group, src, dst);
+  else
+    dequantize_lane<FMT, SCALE_BF16, SRC, THREADS, ACC_LANE, CP>(weights, scales, e0, valid_from(e0, numel), group, src, dst);
 }
 
 // src_kind: 0 = no source (plain de-quantization), 1 = fp32 source, 2 = bf16 source (dst = src - q)
@@ -351,8 +435,12 @@ hipError_t launch_dequantize(const void *weights, const void *scales, uint64_t n
   // a group that holds the whole tensor: any power of two beyond it does, and no lane crosses its end
   GroupOf group = {group_size, 1.0 / (double)group_size, log2_exact(group_size)};
   if (group_size >= numel) group = {1ull << 62, 0.0, 62};
-#define ECO_LAUNCH(F, SC, SK, T) \
-  ECO_FLAT_CHECKED(flat_launch(numel, T), T, stream, (eco_dequantize_kernel<F, SC, SK, T>), weights, scales, numel, group, src, dst)
+  const bool streamed = numel * (src_kind == 0 ? 4 : src_kind == 1 ? 8 : 6) + (fmt == FMT_INT4 ? numel / 2 : numel) >= STREAM_BYTES;
+#define ECO_LAUNCH(F, SC, SK, T)                                                                                                              \
+  do {                                                                                                                                        \
+    if (streamed) ECO_FLAT_CHECKED(flat_launch(numel, T), T, stream, (eco_dequantize_kernel<F, SC, SK, T, (SK == 0 ? STREAM_GROUP : STREAM_WAVE)>), weights, scales, numel, group, src, dst); \
+    else ECO_FLAT_CHECKED(flat_launch(numel, T), T, stream, (eco_dequantize_kernel<F, SC, SK, T, CACHED>), weights, scales, numel, group, src, dst); \
+  } while (0)
 #define ECO_LAUNCH_SRC(F, SC)                                        \
   do {                                                               \
     if (src_kind == 0) ECO_LAUNCH(F, SC, 0, 64);                     \

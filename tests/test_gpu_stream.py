@@ -106,3 +106,68 @@ def test_one_scale_per_tensor_past_the_caches(longer, fmt, bf16, over):
         st = compare(host_copy(tv), h, f"{tv.spec.name}", bf16)
         assert not any(v for key, v in st.items() if key.endswith("mismatch")), (tv.spec.name, st)
     dw.close()
+
+
+def _quantized(eco, src, fmt, group, scale_dtype, step):
+    """Codes, scales, errors and de-quantized values of src, in calls of `step` elements."""
+    n, per = src.numel(), 1 if fmt == eco.ECO_FMT_FP8_E4M3 else 2
+    sd, dt = (eco.ECO_DT_BF16, torch.bfloat16) if scale_dtype else (eco.ECO_DT_FP32, torch.float32)
+    out = {"w": torch.zeros(-(-n // per), dtype=torch.uint8, device=DEV), "s": torch.zeros(-(-n // group), dtype=dt, device=DEV),
+           "e": torch.zeros(n, device=DEV), "d": torch.zeros(n, device=DEV)}
+    kind = eco.ECO_DT_BF16 if src.dtype == torch.bfloat16 else eco.ECO_DT_FP32
+    for at in range(0, n, step):
+        m = min(step, n - at)
+        w, s = out["w"][at // per:], torch.zeros(-(-m // group), dtype=dt, device=DEV)
+        eco.eco_quantize_init(src[at:], kind, m, fmt, group, sd, w, s)
+        eco.eco_quantize_error(src[at:], kind, w, s, m, fmt, group, sd, out["e"][at:])
+        eco.eco_dequantize(w, s, m, fmt, group, sd, out["d"][at:])
+        out["s"][at // group:at // group + s.numel()] = s
+    return out
+
+
+@pytest.mark.parametrize("src_bf16", [False, True])
+@pytest.mark.parametrize("fmt,scale_bf16", [(0, False), (1, True)])
+@pytest.mark.parametrize("group", [32, 512, 200, 320, 576, 1000, 1152, 2048, 6912])
+def test_quantizer_past_the_caches(group, fmt, scale_bf16, src_bf16):
+    """Whole arrays, past the caches, against the same in slices, the usual way: no bit may differ, infinities and NaN among the values."""
+    from paper_2601_22101_amd import binding as eco
+    step = 20_000_000 // (group * 32) * (group * 32)                 # slices of whole groups that begin on 16 bytes
+    n = int(300e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) // group * group + (5 if group in (32, 512, 1152) else 0)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(group)
+    src = torch.randn(n, generator=gen, device=DEV) * 0.02
+    src[torch.randint(0, n, (50,), generator=gen, device=DEV)] = float("nan")
+    src[torch.randint(0, n, (50,), generator=gen, device=DEV)] = float("inf")
+    src[group * 7:group * 8] = float("nan")
+    src = src.to(torch.bfloat16) if src_bf16 else src
+    a, b = (_quantized(eco, src, eco.ECO_FMT_INT4 if fmt else eco.ECO_FMT_FP8_E4M3, group, scale_bf16, k) for k in (n, step))
+    for key in a:
+        assert torch.equal(a[key].view(torch.uint8), b[key].view(torch.uint8)), key
+
+
+@pytest.mark.parametrize("src_bf16", [False, True])
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("tail", [0, 5, 264])
+def test_one_scale_quantizer_past_the_caches(tail, fmt, src_bf16):
+    """The same with one scale: every slice ends with the maximum of the whole, wherever that lies, and a NaN beside numbers is no maximum."""
+    from paper_2601_22101_amd import binding as eco
+    f, step, per = eco.ECO_FMT_INT4 if fmt else eco.ECO_FMT_FP8_E4M3, 8_192_008, 2 if fmt else 1
+    n = 290_000_000 // (2 if src_bf16 else 4) // 512 * 512 + tail
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(tail)
+    x = torch.rand(n, generator=gen, device=DEV) * 0.02 - 0.01
+    x[12345] = float("nan")
+    for peak in (0, n // 2 + 77, n - 1):
+        src = x.clone()
+        src[peak] = -0.5
+        src = src.to(torch.bfloat16) if src_bf16 else src
+        got = _quantized(eco, src, f, n, False, n)
+        for at in (0, n // 3 // 32 * 32, (n - step) // 32 * 32):
+            part = src[at:at + step].clone()
+            part[-1] = -0.5
+            want = _quantized(eco, part, f, part.numel(), False, part.numel())
+            m = (part.numel() - 1) // 2 * 2
+            assert torch.equal(got["s"], want["s"])
+            assert torch.equal(got["w"][at // per:(at + m) // per], want["w"][:m // per])
+            for key in ("e", "d"):
+                assert torch.equal(got[key][at:at + m].view(torch.int32), want[key][:m].view(torch.int32)), key
