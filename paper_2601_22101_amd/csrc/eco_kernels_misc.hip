@@ -58,13 +58,15 @@ constexpr uint64_t STREAM_BYTES = 280000000;       // from here on arrays come f
 constexpr int QUANT_SLOTS = 64, QUANT_PARTS = 256;
 __device__ uint32_t g_quantize_parts[QUANT_SLOTS][QUANT_PARTS];
 
-// Eight elements of each lane of a wave, with the cut piece if there is one: ACC_FULL or ACC_LANE (see WavePieces).
+// Eight elements of each lane of a wave, with the cut piece if there is one: ACC_FULL or ACC_LANE (see WavePieces).  The lanes behind a
+// cut piece get zeros: it may be the first of its group, and the last whole piece then one of another group's.
 template <bool BF16, int ACC, int CP>
 __device__ __forceinline__ void load_wave(const void *base, uint64_t e0, int nvalid, const WavePieces &wp, float (&x)[8]) {
   eco_u32x4_t q[2] = {};
   if (wp.any_whole) load_wave8<BF16, ACC == ACC_FULL, CP>(base, wp, q);
   if (wp.any_cut) {
     if (nvalid & 7) load_ragged8<BF16>(base, e0, nvalid, q);
+    else if (nvalid == 0) q[0] = q[1] = eco_u32x4_t{};
   }
   unpack8<BF16>(q, x);
 }

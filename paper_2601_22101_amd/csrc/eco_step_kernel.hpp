@@ -252,7 +252,8 @@ __device__ __forceinline__ void unpack8(const eco_u32x4_t (&q)[2], float (&x)[8]
 // What a wave whose last lanes may lie beyond the end reads (ACC_LANE; its lanes' pieces of 8 elements are consecutive).  A
 // load inside a branch of its own is waited for there, one array after the other, which is what bounded such waves.  So all
 // loads of all lanes are vectors and issued together: a lane beyond the end reads the wave's last whole piece once more (no
-// traffic, and nothing that a maximum would notice), and writes nothing.  Only the one lane whose piece is cut off reads
+// traffic, and nothing that a maximum would notice, as long as no piece is cut off: a cut one may begin a group, whose other lanes then
+// hold another group's elements and have to be cleared, see `fill`), and writes nothing.  Only the one lane whose piece is cut off reads
 // element by element, over what it has been given, in a branch that waves without one skip.  Measured (us, five loads waited for in
 // turn / this): Adam, fp32 state, 44 tensors of 1001 rows of 2304 538 / 403, 30 750 rows of 1152 in INT4 180 / 133.
 struct WavePieces {

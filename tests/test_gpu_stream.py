@@ -1,6 +1,7 @@
 """Steps whose arrays come from HBM (280 MB and more with fp32 state, 384 MB with bf16) load and store past the caches, and waves exchange
 halves of their fp32 pieces to do it: every class of scale group and of unit, whole and partial waves, pieces that are cut off, beside
 a large tensor that takes the step over the line.  The comparison bar is the one of tests/gpu_util.py, and no bit may differ."""
+import numpy as np
 import pytest
 import torch
 
@@ -129,20 +130,56 @@ def _quantized(eco, src, fmt, group, scale_dtype, step):
 @pytest.mark.parametrize("fmt,scale_bf16", [(0, False), (1, True)])
 @pytest.mark.parametrize("group", [32, 512, 200, 320, 576, 1000, 1152, 2048, 6912])
 def test_quantizer_past_the_caches(group, fmt, scale_bf16, src_bf16):
-    """Whole arrays, past the caches, against the same in slices, the usual way: no bit may differ, infinities and NaN among the values."""
+    """Whole arrays, past the caches, against the same in slices, the usual way: no bit may differ, infinities and NaN among the values.
+    The last group has 5 elements, a hundredth of those before them, and it and its neighbours are also compared with the oracle."""
     from paper_2601_22101_amd import binding as eco
     step = 20_000_000 // (group * 32) * (group * 32)                 # slices of whole groups that begin on 16 bytes
-    n = int(300e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) // group * group + (5 if group in (32, 512, 1152) else 0)
+    n = int(300e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) // group * group + 5
     gen = torch.Generator(device=DEV)
     gen.manual_seed(group)
     src = torch.randn(n, generator=gen, device=DEV) * 0.02
-    src[torch.randint(0, n, (50,), generator=gen, device=DEV)] = float("nan")
-    src[torch.randint(0, n, (50,), generator=gen, device=DEV)] = float("inf")
+    src[torch.randint(0, n - 8 * group, (50,), generator=gen, device=DEV)] = float("nan")
+    src[torch.randint(0, n - 8 * group, (50,), generator=gen, device=DEV)] = float("inf")
     src[group * 7:group * 8] = float("nan")
+    src[-5:] *= 0.01
     src = src.to(torch.bfloat16) if src_bf16 else src
     a, b = (_quantized(eco, src, eco.ECO_FMT_INT4 if fmt else eco.ECO_FMT_FP8_E4M3, group, scale_bf16, k) for k in (n, step))
     for key in a:
         assert torch.equal(a[key].view(torch.uint8), b[key].view(torch.uint8)), key
+    rc, rs = oracle.get("f32").quantize_rtn(oracle.FMT_INT4 if fmt else oracle.FMT_E4M3, src[-5 - 4 * group:].float().cpu().numpy(), group, scale_bf16=scale_bf16)
+    assert np.array_equal(a["w"][-rc.size:].cpu().numpy(), rc)
+    assert np.array_equal(a["s"][-5:].float().cpu().numpy(), rs.astype(np.float32))
+
+
+@pytest.mark.parametrize("src_bf16", [False, True])
+@pytest.mark.parametrize("fmt,scale_bf16", [(0, False), (1, True)])
+@pytest.mark.parametrize("streamed", [False, True])
+def test_last_group_of_less_than_a_lane(streamed, fmt, scale_bf16, src_bf16):
+    """1 to 7 elements over, behind groups of a thousand times their size in the same wave or workgroup: the last scale is that of
+    the last elements alone.  Every group below 512 that has several lanes, some above, and those that go past the caches."""
+    from paper_2601_22101_amd import binding as eco
+    o32 = oracle.get("f32")
+    f, of, per = (eco.ECO_FMT_INT4, oracle.FMT_INT4, 2) if fmt else (eco.ECO_FMT_FP8_E4M3, oracle.FMT_E4M3, 1)
+    groups = [16, 32, 64, 96, 128, 200, 256] if streamed else [*range(16, 512, 8), 512, 520, 576, 1000, 1152]
+    most = int(300e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) if streamed else 8 * 1152
+    big = torch.randn(most + 2000, generator=torch.Generator(device=DEV).manual_seed(5), device=DEV)
+    big = big.to(torch.bfloat16) if src_bf16 else big
+    codes = torch.zeros(big.numel() // per, dtype=torch.uint8, device=DEV)
+    for group in groups:
+        scales = torch.zeros(big.numel() // group + 2, dtype=torch.bfloat16 if scale_bf16 else torch.float32, device=DEV)
+        whole = [most // (512 * group) * 512 + k for k in (1, 2, 3, 5)] if streamed else [1, 2, 3, 5, 7]
+        for k in whole:
+            for rest in range(1, 8):
+                n = k * group + rest
+                src = big[:n]
+                kept = src[-rest:].clone()
+                src[-rest:] *= 1e-3
+                eco.eco_quantize_init(src, int(src_bf16), n, f, group, int(scale_bf16), codes, scales)
+                first = max(0, k - 8)                           # (an even number of elements in)
+                rc, rs = o32.quantize_rtn(of, src[first * group:].float().cpu().numpy(), group, scale_bf16=scale_bf16)
+                src[-rest:] = kept
+                assert np.array_equal(codes[first * group // per:][:rc.size].cpu().numpy(), rc), (group, n)
+                assert np.array_equal(scales[first:k + 1].float().cpu().numpy(), rs.astype(np.float32)), (group, n)
 
 
 @pytest.mark.parametrize("src_bf16", [False, True])
