@@ -299,10 +299,11 @@ eco::KernelVariant variant_for(const eco_hparams_t *hp, int f) {
 }
 
 // Whether the waves that step a tensor start off the 128-byte lines of its arrays: its units are no multiple of 64 elements, the line of a
-// bf16 array, or an array does not begin on a line.
-bool off_lines(const eco_tensor_t &t, const eco::Placement &p) {
-  const uintptr_t arrays = reinterpret_cast<uintptr_t>(t.weights) | reinterpret_cast<uintptr_t>(t.grad) | reinterpret_cast<uintptr_t>(t.m) |
-                           reinterpret_cast<uintptr_t>(t.v) | reinterpret_cast<uintptr_t>(t.aux);
+// bf16 array, or an array does not begin on a line.  Of the arrays that the step uses: the others' pointers may be anything.
+bool off_lines(const eco_tensor_t &t, const eco::Placement &p, const eco::StateLayout &l) {
+  uintptr_t arrays = reinterpret_cast<uintptr_t>(t.weights) | reinterpret_cast<uintptr_t>(t.grad) | reinterpret_cast<uintptr_t>(t.m);
+  if (l.adam) arrays |= reinterpret_cast<uintptr_t>(t.v);
+  if (l.aux && (t.fmt == ECO_FMT_FP8_E4M3 || t.fmt == ECO_FMT_INT4)) arrays |= reinterpret_cast<uintptr_t>(t.aux);
   const bool units_of_rows = p.kind == eco::UNIT_WIDE || p.kind == eco::UNIT_ROWS || p.kind == eco::UNIT_ROW;
   return (arrays & 127) != 0 || (units_of_rows && p.units > 1 && p.rows * p.group % 64 != 0);
 }
@@ -750,7 +751,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       eco::TensorDesc d = describe(t, layout, p, list.size());
       if (p.list == eco::LIST_TW_TILES || p.list == eco::LIST_RESIDENT) {
         g.load[eco::STREAM_TENSORWISE].elements += t.numel;
-        g.load[eco::STREAM_TENSORWISE].off_lines += off_lines(t, p) ? t.numel : 0;
+        g.load[eco::STREAM_TENSORWISE].off_lines += off_lines(t, p, state) ? t.numel : 0;
       }
       if (p.list == eco::LIST_TW_TILES) {
         d.slot = static_cast<uint32_t>(g.tw_tensor.size());
@@ -767,7 +768,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
         Lists::WideLoad &w = g.load[p.kind == eco::UNIT_WIDE ? p.list - eco::LIST_WIDE1 + 1 : 0];
         if (p.kind == eco::UNIT_WIDE) w.idle += p.idle ? p.units : 0;
         if (p.list != eco::LIST_TILE) w.elements += t.numel;
-        if (off_lines(t, p)) w.off_lines += t.numel;
+        if (off_lines(t, p, state)) w.off_lines += t.numel;
       }
       list.insert(list.end(), static_cast<size_t>(p.units), idx);
       if (p.tail) {
@@ -966,13 +967,13 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     units += p.units;
     w.idle += p.idle ? p.units : 0;
     w.elements += t.numel;
-    w.off_lines += off_lines(t, p) ? t.numel : 0;
+    w.off_lines += off_lines(t, p, state) ? t.numel : 0;
   };
   const auto count_tensorwise = [&](int f, const eco_tensor_t &t, const eco::Placement &p) {
     count[f][eco::LIST_TW_TILES] += p.units;
     count[f][L_TW_TENSORS] += 1;
     load[f][eco::STREAM_TENSORWISE].elements += t.numel;
-    load[f][eco::STREAM_TENSORWISE].off_lines += off_lines(t, p) ? t.numel : 0;
+    load[f][eco::STREAM_TENSORWISE].off_lines += off_lines(t, p, state) ? t.numel : 0;
     units += p.units + 1;
     most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
   };
@@ -1008,7 +1009,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     count[f][p.list] += p.units;
     units += p.units;
     if (p.list == eco::LIST_EXTRA) load[f][0].elements += tensors[i].numel;
-    load[f][0].off_lines += off_lines(tensors[i], p) ? tensors[i].numel : 0;
+    load[f][0].off_lines += off_lines(tensors[i], p, state) ? tensors[i].numel : 0;
     if (p.tail) {
       count[f][eco::LIST_EXTRA] += 1;
       units += 1;
@@ -1026,7 +1027,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       Lists::WideLoad &w = load[f][p.kind == eco::UNIT_WIDE ? p.list - eco::LIST_WIDE1 + 1 : 0];
       w.idle -= p.idle ? p.units : 0;
       w.elements -= tensors[i].numel;
-      w.off_lines -= off_lines(tensors[i], p) ? tensors[i].numel : 0;
+      w.off_lines -= off_lines(tensors[i], p, state) ? tensors[i].numel : 0;
     }
     odd_along[f] = true;
     for (size_t i = 0; i < n; ++i)

@@ -12,10 +12,11 @@ enum { MOST = 64 };
 static int launches;
 static size_t lds_of[MOST], pushed_lds;
 static unsigned grid_of[MOST], block_of[MOST], pushed_grid, pushed_block;
+static const void *kernel_of[MOST];
 
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream) {
-  (void)f; (void)grid; (void)block; (void)args; (void)stream;
-  if (launches < MOST) { lds_of[launches] = lds; grid_of[launches] = pushed_grid; block_of[launches] = pushed_block; }
+  (void)grid; (void)block; (void)args; (void)stream;
+  if (launches < MOST) { kernel_of[launches] = f; lds_of[launches] = lds; grid_of[launches] = pushed_grid; block_of[launches] = pushed_block; }
   ++launches;
   return hipSuccess;
 }
@@ -230,6 +231,34 @@ int main(void) {
       ++bad;
     }
   }
+  /* Arrays past the caches, all beginning on lines of memory: an array off a line, of those that the step uses, takes it the usual way;
+   * what stands in the place of an array that it does not use changes nothing. */
+  static const struct { int fmt, opt, mode, v, aux; } uses[] = {{FP8, SGDM, ECO_MODE_ECO, 0, 0}, {FP8, ADAM, ECO_MODE_ECO, 1, 0}, {FP8, SGDM, ECO_MODE_EXACT, 0, 1},
+      {FP8, ADAM, ECO_MODE_MASTER, 1, 1}, {ECO_FMT_BF16_PLAIN, ADAM, ECO_MODE_MASTER, 1, 0}, {ECO_FMT_BF16_PLAIN, SGDM, ECO_MODE_EXACT, 0, 0}};
+  for (size_t c = 0; c < sizeof uses / sizeof *uses; ++c)
+    for (int group = 128; group <= 1024; group += 896)
+      for (int planned = 0; planned < 2; ++planned) {
+        const void *kernels[4];
+        for (int off = 0; off < 4; ++off) {                      /* none, grad, v, aux */
+          eco_plan_t *plan = NULL;
+          memset(list, 0, sizeof *list);
+          list[0].weights = (void *)0x1000; list[0].scales = (void *)0x2000; list[0].m = (void *)0x4000;
+          list[0].grad = (void *)(uintptr_t)(off == 1 ? 0x3010 : 0x3000);
+          list[0].v = (void *)(uintptr_t)(off == 2 ? (uses[c].v ? 0x5010 : 0x5001) : 0x5000);
+          list[0].aux = (void *)(uintptr_t)(off == 3 ? (uses[c].aux ? 0x6010 : 0x6001) : 0x6000);
+          list[0].numel = 1 << 26; list[0].group_size = (uint64_t)group; list[0].fmt = uses[c].fmt;
+          hp.opt = uses[c].opt; hp.mode = uses[c].mode;
+          launches = 0;
+          if (planned && eco_plan_create(list, 1, &hp, &plan) != ECO_OK) { printf("FAILED: lines: %s\n", eco_last_error()); return 1; }
+          if ((planned ? eco_step(plan, &hp, NULL) : eco_step_tensors_noalloc(list, 1, &hp, NULL)) != ECO_OK) { printf("FAILED: lines: %s\n", eco_last_error()); return 1; }
+          kernels[off] = kernel_of[launches - 1];
+          if (plan) (void)eco_plan_destroy(plan);
+        }
+        if (kernels[1] == kernels[0] || (kernels[2] == kernels[0]) != !uses[c].v || (kernels[3] == kernels[0]) != !uses[c].aux) {
+          printf("lines of memory, case %zu, groups of %d, %s plan: v %d, aux %d\n", c, group, planned ? "with" : "without", kernels[2] == kernels[0], kernels[3] == kernels[0]);
+          ++bad;
+        }
+      }
   if (bad) return 1;
   printf("routes ok\n");
   return 0;
