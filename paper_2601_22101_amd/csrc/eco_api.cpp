@@ -146,8 +146,8 @@ constexpr uint64_t SMALL_ELEMENTS = 1ull << 23;
 // counted once: the caps on resident waves were measured against none over 1 to 256 M elements, and the two met between
 // 340 and 420 MB where the traffic in flight is little (bf16 state), between 60 and 120 MB elsewhere.
 struct HbmBound {
-  bool few, half, fully;
-  explicit HbmBound(uint64_t bytes) : few(bytes < 24000000), half(bytes >= 96000000), fully(bytes >= 384000000) {}
+  bool half, fully;
+  explicit HbmBound(uint64_t bytes) : half(bytes >= 96000000), fully(bytes >= 384000000) {}
 };
 
 // Bytes of all arrays of a list.  From HbmBound::half on the step groups rows in its own way (see step_geometry); in shorter
@@ -184,11 +184,13 @@ int num_compute_units() {
 // That holds for arrays that come from HBM (see HbmBound): where a step finds them in the cache before it, a cap costs up
 // to 24 % (bf16 state, us, without / with: FP8 4 M elements 9.3 / 10.4, 32 M 61.1 / 60.3, 64 M 142 / 137; INT4 32 M 56.2 / 56.3,
 // 48 M 85.0 / 88.2, 64 M 129.4 / 127.5; master weights 4 M 14.0 / 15.7, 32 M 105.1 / 107.7, 64 M 226 / 213; unquantized 4 M 8.6 / 10.4,
-// 16 M 38.9 / 37.8).  The caps of fp32 state
-// as well, since waves take whole lines (see exchange_chunks; us, with / without): Adam 40 MB 15.2 / 13.4, 120 MB 37.0 / 35.6 (35.2 at 20 waves),
-// master weights 40 MB 15.2 / 13.1, 120 MB 35.0 / 32.1, 240 MB 65.6 / 66.2, SGDM 14.4 / 12.2, 32.8 / 31.9, 62.6 / 61.8, with a stored error 13.5 /
-// 11.5, 33.9 / 32.9, 64.6 / 63.2, with master weights 12.7 / 10.2, 33.3 / 32.0, 64.1 / 60.7.  Adam has one of 28 waves up to 24 MB (2 M elements, at 12 /
-// 28 waves / none 7.93 / 6.90 / 6.93, 1 M 5.01 / 4.98 / 4.97, but 4 M 17.51 / 15.39 / 15.33 and 8 M 29.80 / 28.19 / 27.66).
+// 16 M 38.9 / 37.8).  The caps of fp32 state as well, since waves take
+// whole lines (see exchange_chunks; us, with / without): Adam 40 MB 15.2 / 13.4, 120 MB 37.0 / 35.6 (35.2 at 20 waves), master weights 40 MB 15.2 /
+// 13.1, 120 MB 35.0 / 32.1, 240 MB 65.6 / 66.2, SGDM 14.4 / 12.2, 32.8 / 31.9, 62.6 / 61.8, with a stored error 13.5 / 11.5, 33.9 / 32.9, 64.6 / 63.2,
+// with master weights 12.7 / 10.2, 33.3 / 32.0, 64.1 / 60.7.  Adam's of 20 waves against none: 16 to 24 M elements 0.5 to 1.7 % less time
+// (17 M 54.2 / 54.6, 21 M 67.5 / 68.2, 23 M 74.0 / 75.2).  Caps of 28 waves are worth nothing anywhere (28 / none: 1 M 5.25 / 5.27, 2 M 6.98 / 7.01, rows
+// of 2048 5.44 / 5.43, 7.45 / 7.45; those of the wide groups 290 MB of master weights 85.3 / 85.3, 85.7 / 85.6, 79.1 / 79.2, bf16 state at 390 and
+// 430 MB 97.5 / 97.1, 116.8 / 116.2, INT4 99.9 / 99.3, 115.8 / 113.0).
 int default_waves(const eco::KernelVariant &kv, const HbmBound &hbm) {
   if (kv.fmt == eco::FMT_BF16_PLAIN || kv.fmt == eco::FMT_FP32_ID) {
     if (kv.state_bf16) return (eco::algo_is_adam(kv.algo) ? hbm.half : hbm.fully) ? 13 : 0;
@@ -200,7 +202,7 @@ int default_waves(const eco::KernelVariant &kv, const HbmBound &hbm) {
     return kv.algo == eco::ALGO_ADAM_MASTER ? 12 : 0;
   }
   switch (kv.algo) {
-    case eco::ALGO_ADAM: return hbm.fully ? 12 : hbm.half ? 20 : hbm.few ? 28 : 0;          // 20.1 B/parameter
+    case eco::ALGO_ADAM: return hbm.fully ? 12 : hbm.half ? 20 : 0;           // 20.1 B/parameter
     case eco::ALGO_ADAM_MASTER: return hbm.fully ? 8 : 0;    // 27.0
     case eco::ALGO_SGDM: return hbm.fully ? 14 : 0;          // 12.1
     case eco::ALGO_SGDM_MASTER: return hbm.fully ? 8 : 0;    // 19.0
@@ -357,14 +359,8 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
     const bool streamed = (sl->stream >> nw & 1u) != 0;
     const bool worth = streamed ? bytes >= 450000000
                                 : hbm.fully || (kv.state_bf16 ? !idle && (nw == 4 || nw == 8) : hbm.half && idle && adam32);
-    // Full rows with master weights in fp32, in part in the cache: 28 waves (us, none / 28 / 12: 768 150 MB 42.1 / 42.1 / 41.9, 270 MB 85.2 / 84.3 /
-    // 87.4, 1024 42.7 / 42.7 / 43.1, 86.3 / 86.0 / 86.1, 2048 42.8 / 42.9 / 43.3, 79.4 / 79.6 / 86.4).
-    // And those of Adam with bf16 state that only just pass the caches by (none / 28 / 20: FP8 of 768 390 MB 97.6 / 97.6 / 102.4, INT4 430 MB 114.6 /
-    // 114.7 / 123.0).
-    const bool full28 = !idle && (streamed ? kv.algo == eco::ALGO_ADAM && kv.state_bf16 && !worth && (nw <= 4 || nw == 8)
-                                           : kv.algo == eco::ALGO_ADAM_MASTER && !kv.state_bf16 && hbm.half && !hbm.fully);
-    const unsigned k = full28 ? (27 + nw) / nw : !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, bytes, nw, units, load[nw].elements, streamed)
-                                                   : eco::wide_workgroups(kv, nw, streamed);
+    const unsigned k = !worth ? 0 : idle ? eco::wide_workgroups_idle(kv, bytes, nw, units, load[nw].elements, streamed)
+                                         : eco::wide_workgroups(kv, nw, streamed);
     // Adam with fp32 state in full rows has the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
     // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 2048: 467
     // against 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
