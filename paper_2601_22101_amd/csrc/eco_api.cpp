@@ -128,6 +128,7 @@ struct Lists {                           // the launch lists of one storage form
   std::vector<uint32_t> one;             // all but the tensor-wise tensors as one launch, where that is the better way: workgroup -> tensor
   size_t off_one = 0;
   unsigned one_waves = 1;
+  eco::StepLaunch launch = {};           // what the step launches, but for the scalars of a call
   std::vector<uint32_t> &list(int l) {
     return l == eco::LIST_TILE ? tile : l == eco::LIST_EXTRA ? extra : l == eco::LIST_TW_TILES ? tw_tile : l == eco::LIST_RESIDENT ? slab : wide[l - eco::LIST_WIDE1 + 1];
   }
@@ -316,37 +317,41 @@ bool off_lines(const eco_tensor_t &t, const eco::Placement &p, const eco::StateL
 // of 128: fp32 state, Adam 250 MB 71 / 74, 280 89 / 82, 340 103 / 99, master weights 69 / 74, 91 / 82, 107 / 97, SGDM 65 / 69, 82 / 77; bf16
 // state, INT4, Adam 310 MB 82 / 83, 340 90 / 90, 420 99 / 97, 640 187 / 168, SGDM (FP8) 310 75 / 78, 340 84 / 85, 420 101 / 95.  Rows of 1.6 GB, fp32
 // state: 1120 (pairs: 35 lines) 491 / 451, 2016 517 / 507, 544 532 / 555, 1000 527 / 654, 6944 545 / 554; bf16 state 1120 528 / 620, 320 590 / 576.
+constexpr uint64_t stream_from(bool f32) { return f32 ? 280000000 : 384000000; }
 uint32_t stream_launches(uint64_t bytes, bool f32, uint64_t tiles, const Lists::WideLoad (&load)[eco::MAX_WIDE_WAVES + 2]) {
-  if (bytes < (f32 ? 280000000u : 384000000u)) return 0;
+  if (bytes < stream_from(f32)) return 0;
   uint32_t launches = load[0].off_lines * 8 <= load[0].elements + tiles * eco::TILE_ELEMS ? 1 : 0;
   for (int nw = 1; nw <= eco::STREAM_TENSORWISE; ++nw) launches |= (load[nw].off_lines * 8 <= load[nw].elements ? 1u : 0u) << nw;
   return launches;
 }
 
-// The scalar part of the kernel arguments: step constants, random-stream key, launch options.
+// Which launch the one-wave units of a format ride in: the full-tile one (0) where there is one, they are many or every
+// wide-group launch is long, else the wide-group one with the most units.  Riding in a wide-group launch costs 3.6 % of
+// it, a launch of their own 5 us: the two meet at about 35 million elements.
+int home_of_extra(uint64_t tiles, uint64_t extra, const uint32_t (&num_wide)[eco::MAX_WIDE_WAVES + 1]) {
+  int best = 0;
+  uint64_t most = 0;
+  if (tiles || extra > RIDE_ALONG_TILES) return 0;
+  for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
+    const uint64_t waves = static_cast<uint64_t>(num_wide[nw]) * nw;
+    if (waves > most && waves <= RIDE_ALONG_WAVES) { best = nw; most = waves; }
+  }
+  return best;
+}
+
+// What the lists decide about their launches: which pass the caches by, the caps on resident waves, where the one-wave units ride.  A plan
+// has it worked out once (host time of a step of one matrix in C, us: on every step 3.16, so 3.13).
 typedef Lists::WideLoad WideLoads[eco::MAX_WIDE_WAVES + 2];
-void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, const WideLoads &load, uint64_t bytes,
-                       eco::StepLaunch *sl) {
-  eco::StepArgs *a = &sl->args;
-  a->b1 = c.b1; a->omb1 = c.omb1; a->b2 = c.b2; a->omb2 = c.omb2; a->rbc2 = c.rbc2; a->c1 = c.c1; a->eps = c.eps;
-  a->kappa = c.kappa; a->lr = c.lr; a->alpha = c.alpha; a->wd = c.wd; a->inv_lr = c.inv_lr; a->inv_lr_beta = c.inv_lr_beta;
-  a->seed_lo = static_cast<uint32_t>(hp->seed);
-  a->seed_hi = static_cast<uint32_t>(hp->seed >> 32);
-  a->step_lo = static_cast<uint32_t>(hp->step);
-  a->div_mid = (c.c1 >= 0x1p-40f && c.c1 <= 0x1p40f && c.eps <= 1.0f) ? 1u : 0u;
-  const int64_t opt_threads = g_max_launch_threads.load(std::memory_order_relaxed);
-  sl->max_launch_threads = opt_threads > 0 ? static_cast<uint64_t>(opt_threads) : eco::MAX_LAUNCH_THREADS;
-  a->unit_base = 0;
+void choose_launches(const eco::KernelVariant &kv, const WideLoads &load, uint64_t bytes, eco::StepLaunch *sl) {
+  const eco::StepArgs *a = &sl->args;
   const HbmBound hbm(bytes);
   sl->stream = stream_launches(bytes, !kv.state_bf16, a->num_tiles, load);
   const int waves = default_waves(kv, hbm), tile_waves = sl->stream & 1u ? streaming_waves(kv, bytes) : waves;
-  const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
-  const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
   // a launch of one-wave units beside few tiles does not have the tiles' cap, which counts on every lane; short rows alone have
   // one of their own
   const bool units = (kv.fmt == eco::FMT_FP8 || kv.fmt == eco::FMT_INT4) && a->num_extra > a->num_tiles / 8;
   const unsigned resident = units && !a->num_tiles && load[0].elements ? eco::unit_workgroups(kv, bytes, a->num_extra, load[0].elements) : 0;
-  sl->lds_bytes = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : units ? eco::lds_for_workgroups(resident) : lds_for_waves(tile_waves, 512);
+  sl->lds_bytes = units ? eco::lds_for_workgroups(resident) : lds_for_waves(tile_waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
     const uint64_t units = sl->num_wide[nw];
     if (!units) continue;
@@ -364,10 +369,32 @@ void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, const 
     // Adam with fp32 state in full rows has the full-tile kernel's LDS per wave (8 to 12 waves for workgroups of up to 4, two workgroups
     // of larger ones): 16 waves are 3-25 % faster where the arrays lie well (rows of 2048: 467
     // against 498) but 20 % slower where memory is the slower kind (rows of 2048 and 1408, 185 M elements: 922 against 765).
-    const uint32_t per_wave = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(waves, 256);
-    sl->lds_bytes_wide[nw] = opt_lds_wave >= 0 || (adam32 && !idle && !streamed) ? std::min(per_wave * nw, 65536u) : eco::lds_for_workgroups(k);
+    sl->lds_bytes_wide[nw] = adam32 && !idle && !streamed ? std::min(lds_for_waves(waves, 256) * nw, 65536u) : eco::lds_for_workgroups(k);
   }
-  sl->lds_bytes_tw = opt_lds_wave >= 0 ? static_cast<uint32_t>(opt_lds_wave) : lds_for_waves(tensorwise_waves(kv, hbm, sl->stream >> eco::STREAM_TENSORWISE & 1u), 256);
+  sl->lds_bytes_tw = lds_for_waves(tensorwise_waves(kv, hbm, sl->stream >> eco::STREAM_TENSORWISE & 1u), 256);
+  sl->extra_in = home_of_extra(a->num_tiles, a->num_extra, sl->num_wide);
+}
+
+// The scalar part of the kernel arguments: step constants, random-stream key; and the launch options that are set.
+void fill_step_scalars(const eco_hparams_t *hp, const eco_constants_t &c, eco::StepLaunch *sl) {
+  eco::StepArgs *a = &sl->args;
+  a->b1 = c.b1; a->omb1 = c.omb1; a->b2 = c.b2; a->omb2 = c.omb2; a->rbc2 = c.rbc2; a->c1 = c.c1; a->eps = c.eps;
+  a->kappa = c.kappa; a->lr = c.lr; a->alpha = c.alpha; a->wd = c.wd; a->inv_lr = c.inv_lr; a->inv_lr_beta = c.inv_lr_beta;
+  a->seed_lo = static_cast<uint32_t>(hp->seed);
+  a->seed_hi = static_cast<uint32_t>(hp->seed >> 32);
+  a->step_lo = static_cast<uint32_t>(hp->step);
+  a->div_mid = (c.c1 >= 0x1p-40f && c.c1 <= 0x1p40f && c.eps <= 1.0f) ? 1u : 0u;
+  const int64_t opt_threads = g_max_launch_threads.load(std::memory_order_relaxed);
+  sl->max_launch_threads = opt_threads > 0 ? static_cast<uint64_t>(opt_threads) : eco::MAX_LAUNCH_THREADS;
+  a->unit_base = 0;
+  const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
+  const int64_t opt_lds_wave = g_lds_bytes_wave.load(std::memory_order_relaxed);
+  if (opt_lds >= 0) sl->lds_bytes = static_cast<uint32_t>(opt_lds);
+  if (opt_lds_wave >= 0) {
+    for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw)
+      sl->lds_bytes_wide[nw] = std::min(static_cast<uint32_t>(opt_lds_wave) * nw, 65536u);
+    sl->lds_bytes_tw = static_cast<uint32_t>(opt_lds_wave);
+  }
 }
 
 
@@ -455,7 +482,6 @@ struct eco_plan {
   int cus = 256;
   int device = 0;    // the device that was current when the plan was created (its tables live there)
   Lists lists[4];    // indexed by eco_format_t; unquantized tensors may be in a quantized format's lists
-  uint64_t bytes = 0;                    // of all arrays
   bool unfinished = false;               // a step has stopped between its launches: scratch may hold what it left
   eco::TensorDesc *d_descs = nullptr;
   uint32_t *d_tables = nullptr;          // all lists, back to back, then the abs-max slots and the scratch of the tensor-wise passes
@@ -555,20 +581,6 @@ void make_small(const SmallItem *items, size_t n, const eco_hparams_t *layout, e
   *waves = nw;
 }
 
-// Which launch the one-wave units of a format ride in: the full-tile one (0) where there is one, they are many or every
-// wide-group launch is long, else the wide-group one with the most units.  Riding in a wide-group launch costs 3.6 % of
-// it, a launch of their own 5 us: the two meet at about 35 million elements.
-int home_of_extra(uint64_t tiles, uint64_t extra, const uint32_t (&num_wide)[eco::MAX_WIDE_WAVES + 1]) {
-  int best = 0;
-  uint64_t most = 0;
-  if (tiles || extra > RIDE_ALONG_TILES) return 0;
-  for (int nw = 1; nw <= eco::MAX_WIDE_WAVES; ++nw) {
-    const uint64_t waves = static_cast<uint64_t>(num_wide[nw]) * nw;
-    if (waves > most && waves <= RIDE_ALONG_WAVES) { best = nw; most = waves; }
-  }
-  return best;
-}
-
 }  // namespace
 
 extern "C" {
@@ -656,6 +668,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
   plan->mode = layout->mode;
 
   hipError_t e = hipSuccess;
+  uint64_t bytes = 0;
   std::vector<eco::TensorDesc> descs;
   std::vector<uint32_t> host;
   try {
@@ -663,8 +676,8 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     std::vector<eco::Placement> place(n);
     const eco::StateLayout state = state_layout(layout);
     uint64_t tensors_of[4] = {0}, entries_of[4] = {0}, list_entries[4][eco::LIST_COUNT] = {{0}};
-    plan->bytes = bytes_of(tensors, n, state);
-    eco::StepRows rows = {state, HbmBound(plan->bytes).half};
+    bytes = bytes_of(tensors, n, state);           // of all arrays
+    eco::StepRows rows = {state, HbmBound(bytes).half};
     uint32_t own_sizes[4] = {0}, sizes[4] = {0};          // of workgroups, a bit each: with the step's own grouping of rows, and without
     for (size_t i = 0; i < n && st == ECO_OK; ++i) {
       const eco_tensor_t &t = tensors[i];
@@ -685,7 +698,7 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
       if (in_list > 0x7FFFFFF0ull) st = fail(ECO_EUNSUPPORTED, "plan: more than 2^31 tiles in one launch");
     }
     if (st != ECO_OK) { delete plan; return st; }
-    if (rows.own_rows && !own_grouping_pays(plan->bytes, own_sizes, sizes)) {
+    if (rows.own_rows && !own_grouping_pays(bytes, own_sizes, sizes)) {
       rows.own_rows = false;
       for (size_t i = 0; i < n; ++i)
         if (place[i].kind == eco::UNIT_WIDE)
@@ -833,51 +846,10 @@ eco_status_t eco_plan_create(const eco_tensor_t *tensors, size_t n, const eco_hp
     (void)eco_plan_destroy(plan);
     return st;
   }
-  *out = plan;
-  return ECO_OK;
-}
-
-// Launches the step of one format's lists (sl: everything but the scalars).
-static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, int f, int cus, const WideLoads &load, uint64_t bytes,
-                                  eco::StepLaunch *sl, eco::SmallArgs *small, hipStream_t stream) {
-  const eco::KernelVariant kv = variant_for(hp, f);
-  fill_step_scalars(hp, c, kv, load, bytes, sl);
-  sl->extra_in = home_of_extra(sl->args.num_tiles, sl->args.num_extra, sl->num_wide);
-  sl->max_tile_threads = tile_threads(sl->max_launch_threads, cus);
-  if (small) {
-    sl->args.wg_waves = sl->list_waves;
-    small->step = sl->args;
-    sl->small = small;
-  }
-  const hipError_t e = eco::launch_step(kv, *sl, stream);
-  return e == hipSuccess ? ECO_OK : fail_hip(e, "step kernel launch");
-}
-
-eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
-  if (!plan) return fail(ECO_EINVAL, "step: null plan");
-  eco_status_t st = check_hparams(hp);
-  if (st != ECO_OK) return st;
-  if (hp->block_size != plan->block_size || hp->state_dtype != plan->state_dtype || hp->scale_dtype != plan->scale_dtype ||
-      hp->opt != plan->opt || hp->mode != plan->mode)
-    return fail(ECO_EINVAL, "step: block_size, state_dtype, scale_dtype, opt and mode must equal the plan's");
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev != plan->device)
-    return fail(ECO_EINVAL, "step: the plan was created on device %d, which is not the current device (%d)", plan->device, dev);
-  (void)hipGetLastError();   // an error left behind by the caller's earlier HIP work is not this call's
-
-  if (!plan->d_descs || !plan->d_tables) return fail(ECO_EINVAL, "step: the plan's device tables are missing");
-  eco_constants_t c;
-  derive_constants(hp, &c);
-  if (plan->unfinished) {
-    const hipError_t e = reset_scratch(*plan, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return fail_hip(e, "scratch kernel launch");
-  }
-  plan->unfinished = true;
   for (int f = 0; f < 4; ++f) {
     Lists &g = plan->lists[f];
     if (!g.tensors) continue;
-    eco::StepLaunch sl;
-    std::memset(&sl, 0, sizeof sl);
+    eco::StepLaunch &sl = g.launch;
     eco::StepArgs &a = sl.args;
     a.tensors = plan->d_descs;
     sl.tile_tensor = plan->d_tables + g.off_tile;
@@ -910,7 +882,51 @@ eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
     sl.list_tensor = plan->d_tables + g.off_one;
     sl.list_wgs = g.one.size();
     sl.list_waves = g.one_waves;
-    st = launch_format(hp, c, f, plan->cus, g.load, plan->bytes, &sl, nullptr, static_cast<hipStream_t>(stream));
+    choose_launches(variant_for(layout, f), g.load, bytes, &sl);
+  }
+  *out = plan;
+  return ECO_OK;
+}
+
+// Launches the step of one format's lists (sl: everything but the scalars).
+static eco_status_t launch_format(const eco_hparams_t *hp, const eco_constants_t &c, const eco::KernelVariant &kv, int cus, eco::StepLaunch *sl,
+                                  eco::SmallArgs *small, hipStream_t stream) {
+  fill_step_scalars(hp, c, sl);
+  sl->max_tile_threads = tile_threads(sl->max_launch_threads, cus);
+  if (small) {
+    sl->args.wg_waves = sl->list_waves;
+    small->step = sl->args;
+    sl->small = small;
+  }
+  const hipError_t e = eco::launch_step(kv, *sl, stream);
+  return e == hipSuccess ? ECO_OK : fail_hip(e, "step kernel launch");
+}
+
+eco_status_t eco_step(eco_plan_t *plan, const eco_hparams_t *hp, void *stream) {
+  if (!plan) return fail(ECO_EINVAL, "step: null plan");
+  eco_status_t st = check_hparams(hp);
+  if (st != ECO_OK) return st;
+  if (hp->block_size != plan->block_size || hp->state_dtype != plan->state_dtype || hp->scale_dtype != plan->scale_dtype ||
+      hp->opt != plan->opt || hp->mode != plan->mode)
+    return fail(ECO_EINVAL, "step: block_size, state_dtype, scale_dtype, opt and mode must equal the plan's");
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev != plan->device)
+    return fail(ECO_EINVAL, "step: the plan was created on device %d, which is not the current device (%d)", plan->device, dev);
+  (void)hipGetLastError();   // an error left behind by the caller's earlier HIP work is not this call's
+
+  if (!plan->d_descs || !plan->d_tables) return fail(ECO_EINVAL, "step: the plan's device tables are missing");
+  eco_constants_t c;
+  derive_constants(hp, &c);
+  if (plan->unfinished) {
+    const hipError_t e = reset_scratch(*plan, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return fail_hip(e, "scratch kernel launch");
+  }
+  plan->unfinished = true;
+  for (int f = 0; f < 4; ++f) {
+    const Lists &g = plan->lists[f];
+    if (!g.tensors) continue;
+    eco::StepLaunch sl = g.launch;
+    st = launch_format(hp, c, variant_for(hp, f), plan->cus, &sl, nullptr, static_cast<hipStream_t>(stream));
     if (st != ECO_OK) return st;
   }
   plan->unfinished = false;
@@ -963,13 +979,11 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     units += p.units;
     w.idle += p.idle ? p.units : 0;
     w.elements += t.numel;
-    w.off_lines += off_lines(t, p, state) ? t.numel : 0;
   };
   const auto count_tensorwise = [&](int f, const eco_tensor_t &t, const eco::Placement &p) {
     count[f][eco::LIST_TW_TILES] += p.units;
     count[f][L_TW_TENSORS] += 1;
     load[f][eco::STREAM_TENSORWISE].elements += t.numel;
-    load[f][eco::STREAM_TENSORWISE].off_lines += off_lines(t, p, state) ? t.numel : 0;
     units += p.units + 1;
     most_tw_tiles[f] = std::max(most_tw_tiles[f], p.units);
   };
@@ -1005,7 +1019,6 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     count[f][p.list] += p.units;
     units += p.units;
     if (p.list == eco::LIST_EXTRA) load[f][0].elements += tensors[i].numel;
-    load[f][0].off_lines += off_lines(tensors[i], p, state) ? tensors[i].numel : 0;
     if (p.tail) {
       count[f][eco::LIST_EXTRA] += 1;
       units += 1;
@@ -1023,7 +1036,6 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
       Lists::WideLoad &w = load[f][p.kind == eco::UNIT_WIDE ? p.list - eco::LIST_WIDE1 + 1 : 0];
       w.idle -= p.idle ? p.units : 0;
       w.elements -= tensors[i].numel;
-      w.off_lines -= off_lines(tensors[i], p, state) ? tensors[i].numel : 0;
     }
     odd_along[f] = true;
     for (size_t i = 0; i < n; ++i)
@@ -1060,9 +1072,14 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
   for (int f = eco::FMT_BF16_PLAIN; f <= eco::FMT_FP32_ID && plain_home >= 0; ++f) {
     count[plain_home][eco::LIST_EXTRA] += count[f][eco::LIST_EXTRA];
     load[plain_home][0].elements += load[f][0].elements;
-    load[plain_home][0].off_lines += load[f][0].off_lines;
     count[f][eco::LIST_EXTRA] = 0;
   }
+  if (bytes >= stream_from(!state.state_bf16))
+    for (size_t i = 0; i < n; ++i) {
+      const eco::Placement p = place(tensors[i]);
+      const int l = p.list == eco::LIST_TW_TILES ? eco::STREAM_TENSORWISE : p.kind == eco::UNIT_WIDE ? p.list - eco::LIST_WIDE1 + 1 : 0;
+      if (off_lines(tensors[i], p, state)) load[format_of(i)][l].off_lines += tensors[i].numel;
+    }
   (void)hipGetLastError();
   hipStream_t hs = static_cast<hipStream_t>(stream);
   eco_constants_t c;
@@ -1090,7 +1107,7 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
           make_small(items, held, hp, &small, &sl.list_wgs, &sl.list_waves);
           held = 0;
           if (round == 0) { fits = sl.list_wgs * sl.list_waves * 64 <= static_cast<uint64_t>(limit); continue; }
-          st = launch_format(hp, c, f, cus, load[f], bytes, &sl, &small, hs);
+          st = launch_format(hp, c, variant_for(hp, f), cus, &sl, &small, hs);
           if (st != ECO_OK) return st;
         }
       }
@@ -1167,7 +1184,9 @@ eco_status_t eco_step_tensors_noalloc(const eco_tensor_t *tensors, size_t n, con
     a.num_tw_tiles = static_cast<uint32_t>(count[f][eco::LIST_TW_TILES]);
     a.num_tw_tensors = static_cast<uint32_t>(count[f][L_TW_TENSORS]);
     a.tw_reduce_wgs = eco::tw_reduce_workgroups(most_tw_tiles[f]);
-    st = launch_format(hp, c, f, cus, load[f], bytes, &sl, nullptr, hs);
+    const eco::KernelVariant kv = variant_for(hp, f);
+    choose_launches(kv, load[f], bytes, &sl);
+    st = launch_format(hp, c, kv, cus, &sl, nullptr, hs);
     if (st != ECO_OK) return st;
   }
   return ECO_OK;

@@ -265,6 +265,27 @@ int main(void) {
           ++bad;
         }
       }
+  /* Launch options hold for the next step of a plan made before they were set, and no longer than they are set. */
+  hp.opt = ADAM; hp.mode = ECO_MODE_ECO;
+  for (int group = 128; group <= 1024; group += 896) {
+    eco_plan_t *plan = NULL;
+    memset(list, 0, sizeof *list);
+    list[0].weights = (void *)0x1000; list[0].scales = (void *)0x2000; list[0].grad = (void *)0x3000; list[0].m = (void *)0x4000; list[0].v = (void *)0x5000;
+    list[0].numel = 1 << 27; list[0].group_size = (uint64_t)group;
+    if (eco_plan_create(list, 1, &hp, &plan) != ECO_OK) { printf("FAILED: options: %s\n", eco_last_error()); return 1; }
+    size_t lds[3] = {0};
+    for (int k = 0; k < 3; ++k) {
+      if (eco_set_option(1, k == 1 ? 1536 : -1) != ECO_OK || eco_set_option(2, k == 1 ? 768 : -1) != ECO_OK) return 1;
+      launches = 0;
+      if (eco_step(plan, &hp, NULL) != ECO_OK) { printf("FAILED: options: %s\n", eco_last_error()); return 1; }
+      lds[k] = launches == 1 ? lds_of[0] : 0;
+    }
+    (void)eco_plan_destroy(plan);
+    if (lds[1] != 1536 || lds[0] == 1536 || lds[0] == 0 || lds[2] != lds[0]) {
+      printf("options, groups of %d: %zu, %zu, %zu bytes of LDS\n", group, lds[0], lds[1], lds[2]);
+      ++bad;
+    }
+  }
   if (bad) return 1;
   printf("routes ok\n");
   return 0;
