@@ -266,21 +266,28 @@ static QuantSlotRing g_quant_ring;
     }                                                                                                                      \
   } while (0)
 
-// Which form the quantizer's kernels take (CP).  From 280 MB of source and codes on, in one pass, or of source, in two (the second finds
-// less in the cache before HBM), they go past the caches; not in groups of more than 4096 elements, nor from bf16 where groups fill their waves or share them.
-// us, per lane / past the caches: FP8 from fp32, groups of 128, 225 MB 32.0 / 34.3, 300 46.9 / 44.0, 600 102 / 86; rows of 4096 350 MB 57.6 / 54.1,
-// 1 GB 164 / 149, 1000 56.9 / 52.5, 176 / 146, 2304 59.7 / 58.6, 170 / 164, 6912 61.1 / 62.9, 169 / 175; from bf16 2304 300 MB 75.4 / 74.0, 1000 64.8 /
-// 59.9, 4096 61.9 / 63.1, 576 91.0 / 95.3.  One scale, from fp32 240 MB 76.2 / 79.7, 320 106.7 / 103.4, 520 184 / 163, from bf16 200 MB 71.7 / 79.5, 280 111.6 /
+// Which form the quantizer's kernels take (CP).  From 280 MB of source and codes on (from fp32 320), in one pass, or from 280 MB of source on, in two
+// (the second finds less in the cache before HBM), they go past the caches; not in groups of more than 4096 elements, nor from bf16 where groups fill
+// their waves or share them, nor from fp32 to INT4 in rows that leave nearly half of their lanes idle.
+// us, per lane / past the caches: FP8 from fp32, groups of 128, 225 MB 32.0 / 34.3, 290 42.6 / 43.0, 350 59.4 / 51.7, 600 102 / 86; rows of 1000 290 MB
+// 42.9 / 44.2, 350 58.4 / 52.6, 1 GB 180 / 147, 4096 350 57.6 / 54.1, 2304 59.7 / 58.6, 170 / 164, 6912 61.1 / 62.9, 169 / 175; INT4 from fp32 760 290 MB
+// 49.3 / 51.8, 350 61.8 / 61.8, 1000 43.6 / 45.3, 58.9 / 54.8, 520 77.8 / 80.9, 420 94.5 / 96.4; from bf16 2304 300 MB 75.4 / 74.0, 1000 64.8 / 59.9, 4096
+// 61.9 / 63.1, 576 91.0 / 95.3.  One scale, from fp32 240 MB 76.2 / 79.7, 320 106.7 / 103.4, 520 184 / 163, from bf16 200 MB 71.7 / 79.5, 280 111.6 /
 // 108.3, 500 210 / 188; with the error behind it 210 M elements from bf16 415 / 361.  What is left goes by whole pieces of a wave in rows with idle
 // lanes (CACHED; from bf16, rows of 192 70 M elements 61.7 / 55.7, 1000 41.7 / 38.5), per lane elsewhere (4 M elements 4.1 / 4.2, 1152 26.5 / 27.4).
+// From fp32 to INT4 also per lane in rows with a wave or up to three to themselves, and in longer ones below 40 MB (us, per lane / whole pieces: 264
+// 140 MB 27.9 / 28.7, 504 22.2 / 22.7, 520 27.8 / 29.1, 576 25.4 / 26.3, 760 21.6 / 22.1, 1480 20.9 / 20.9, 6912 20 MB 4.90 / 5.14, but 60 MB 11.9 / 11.5,
+// 2304 11.6 / 11.3, 4008 240 MB 36.0 / 33.6).
 template <int FMT, bool SC, bool SR>
 static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t group_size, void *weights, void *scales,
                                     hipStream_t stream) {
   const uint64_t src_bytes = numel * (SR ? 2 : 4), bytes = src_bytes + (FMT == FMT_INT4 ? numel / 2 : numel);
-  const bool streamed = bytes >= STREAM_BYTES;
+  const bool streamed = bytes >= (SR ? STREAM_BYTES : 320000000);
+  constexpr bool INT4_F32 = FMT == FMT_INT4 && !SR;
   const uint64_t tiles = (numel + TILE_ELEMS - 1) / TILE_ELEMS;
   const int cls = classify_group(group_size, numel);
-  const auto row = streamed ? eco_quantize_rows_kernel<FMT, SC, SR, true, STREAM_GROUP> : eco_quantize_rows_kernel<FMT, SC, SR, true, CACHED>;
+  const auto row = streamed ? eco_quantize_rows_kernel<FMT, SC, SR, true, STREAM_GROUP>
+                            : eco_quantize_rows_kernel<FMT, SC, SR, true, INT4_F32 ? PER_LANE : CACHED>;
   if (cls == GROUP_BLOCK) {
     const auto kernel = streamed ? eco_quantize_kernel<FMT, SC, SR, STREAM_GROUP> : eco_quantize_kernel<FMT, SC, SR, PER_LANE>;
     ECO_LAUNCH_CHECKED(kernel, dim3((unsigned)tiles), dim3(WG_THREADS), 0, stream, src, numel, (uint32_t)log2_exact(group_size), weights, scales);
@@ -296,10 +303,12 @@ static hipError_t launch_quantize_t(const void *src, uint64_t numel, uint64_t gr
       ECO_LAUNCH_CHECKED(bundle, dim3((unsigned)p.units), dim3(64 * (p.list - LIST_WIDE1 + 1)), 0, stream, src, numel, (uint32_t)p.group, p.rows,
                          weights, scales);
     } else {
-      const bool fills = p.group % TILE_ELEMS == 0;
-      const auto wide = streamed && p.group <= 4096 && !(fills && SR) ? eco_quantize_wide_kernel<FMT, SC, SR, false, STREAM_GROUP>
-                        : fills                                       ? eco_quantize_wide_kernel<FMT, SC, SR, false, PER_LANE>
-                                                                      : eco_quantize_wide_kernel<FMT, SC, SR, false, CACHED>;
+      const bool fills = p.group % TILE_ELEMS == 0, half_idle = p.group < 6 * TILE_ELEMS / 5;
+      const bool past = streamed && p.group <= 4096 && !(fills && SR) && !(half_idle && INT4_F32);
+      const bool per_lane = fills || (INT4_F32 && (p.group <= 3 * TILE_ELEMS || bytes < 40000000));
+      const auto wide = past       ? eco_quantize_wide_kernel<FMT, SC, SR, false, STREAM_GROUP>
+                        : per_lane ? eco_quantize_wide_kernel<FMT, SC, SR, false, PER_LANE>
+                                   : eco_quantize_wide_kernel<FMT, SC, SR, false, CACHED>;
       ECO_LAUNCH_CHECKED(wide, dim3((unsigned)((numel + p.group - 1) / p.group)), dim3((unsigned)((p.group + TILE_ELEMS - 1) / TILE_ELEMS) * 64), 0,
                          stream, src, numel, (uint32_t)p.group, 1u, weights, scales);
     }
