@@ -350,7 +350,7 @@ void choose_launches(const eco::KernelVariant &kv, const WideLoads &load, uint64
   // a launch of one-wave units beside few tiles does not have the tiles' cap, which counts on every lane; short rows alone have
   // one of their own
   const bool units = (kv.fmt == eco::FMT_FP8 || kv.fmt == eco::FMT_INT4) && a->num_extra > a->num_tiles / 8;
-  const unsigned resident = units && !a->num_tiles && load[0].elements ? eco::unit_workgroups(kv, bytes, a->num_extra, load[0].elements) : 0;
+  const unsigned resident = units && !a->num_tiles && load[0].elements ? eco::unit_workgroups(kv, bytes, a->num_extra, load[0].elements, sl->stream & 1u) : 0;
   sl->lds_bytes = units ? eco::lds_for_workgroups(resident) : lds_for_waves(tile_waves, 512);
   for (unsigned nw = 1; nw <= static_cast<unsigned>(eco::MAX_WIDE_WAVES); ++nw) {
     const uint64_t units = sl->num_wide[nw];

@@ -402,6 +402,11 @@ inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, bool strea
 //   113 / 118); with a stored error 20.4: 576 364 / 365, 760 359 / 380, 1000 371 / 403, 1408 368 / 377, 1496 377 / 405, 1800 362 / 373, 2304 371 / 371.
 // Adam with fp32 state and SGDM with a stored error, where rows start off the lines of memory and are not streamed (1.6 GB of arrays, 13.6 and
 // 15.6 / this): 11.5 544 532 / 498, 560 556 / 512, 1000 524 / 501, 2016 517 / 490, in the cache 1152 66.4 / 64.8; 11.8 1000 552 / 500, 2016 514 / 505.
+// The other figures are from before waves took whole lines at a time (see exchange_chunks).  Since then, rows that start off the lines of memory,
+// 460 MB and 1.4 GB of arrays, us, as above / as now: SGDM, bf16 state, with a stored error (20.4 / 15) FP8 1000 149 / 134, 501 / 421, 3000 145 / 137,
+// 477 / 421, INT4 2024 148 / 133, 502 / 417; fp32 state, FP8, where fewer than nine lanes in ten are busy (19.6 / 17) 544 141 / 134, 507 / 460; INT4 with
+// a stored error from 1 GB (11.8 / 11.2) 1480 0.95, 3000 490 / 441, 460 MB 1000 loses 2 %; with master weights (9.7 / 10.6) 1000 147 / 140, 514 / 493;
+// Adam, master weights (9.5 / 8.5) 1.4 GB 760 453 / 411, 1480 474 / 442; Adam, in part in the cache (11.5 / 13) 1480 330 MB 101.9 / 98.5.
 inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, unsigned nw, uint64_t units, uint64_t elements,
                                      bool streamed = false) {
   const auto at_least = [=](uint64_t tenths) {
@@ -409,21 +414,28 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, un
     return static_cast<unsigned>(k < 2 ? 2 : k);
   };
   const uint64_t MB = 1000000;
-  const bool long_step = bytes >= 600 * MB, nearly_all = (nw <= 4 || nw == 8) && elements * 20 >= units * nw * TILE_ELEMS * 19;
+  const bool fp8 = kv.fmt == FMT_FP8, long_step = bytes >= 600 * MB, nearly_all = (nw <= 4 || nw == 8) && elements * 20 >= units * nw * TILE_ELEMS * 19;
   switch (kv.algo) {
-    case ALGO_ADAM: return !kv.state_bf16 ? at_least(streamed ? 136 : 115) : nearly_all && bytes >= (kv.fmt == FMT_FP8 ? 600 : 1000) * MB ? at_least(195) : 0;
-    case ALGO_ADAM_MASTER: return kv.state_bf16 ? at_least(115) : long_step ? at_least(95) : 0;
-    case ALGO_SGDM: return kv.state_bf16 ? 0 : at_least(196);
-    case ALGO_SGDM_EXACT: return at_least(kv.state_bf16 ? 204 : streamed ? 156 : 118);
-    default: return at_least(kv.state_bf16 ? 136 : 97);
+    case ALGO_ADAM:
+      if (!kv.state_bf16) return at_least(streamed ? 136 : bytes >= 384 * MB ? 115 : 130);
+      return nearly_all && bytes >= (fp8 ? 600 : 1000) * MB ? at_least(195) : 0;
+    case ALGO_ADAM_MASTER: return kv.state_bf16 ? at_least(115) : long_step ? at_least(streamed ? 95 : 85) : 0;
+    case ALGO_SGDM: return kv.state_bf16 ? 0 : at_least(fp8 && !streamed && elements * 10 < units * nw * TILE_ELEMS * 9 ? 170 : 196);
+    case ALGO_SGDM_EXACT: return at_least(kv.state_bf16 ? 150 : streamed ? 156 : fp8 || bytes < 1000 * MB ? 118 : 112);
+    default: return at_least(kv.state_bf16 ? 136 : 106);
   }
 }
 // Waves per compute unit of a launch of one-wave units alone (short rows), `elements` in `units` of them; 0: as many as fit.
 // Again the smallest number with a certain number of waves' worth of busy lanes.  For arrays that come from HBM, 100 M elements,
 // us, with / without --
-//   (Before waves took whole lines at a time, see exchange_chunks: since then fp32 state 13.4 instead of 10.3, 1.6 GB 200 540 / 518, streamed 192
-//   510 / 471, 384 500 / 476; master weights 9 instead of 7, 200 582 / 544, streamed 192 508 / 479, 384 498 / 481; a stored error 12 instead of
-//   13.4, 200 583 / 495, streamed 384 485 / 462.)
+//   (Before waves took whole lines at a time, see exchange_chunks.  Since then those that pass the caches by, fp32 state, Adam 13.4 instead of 10.3,
+//   1.6 GB 192 510 / 471, 384 500 / 476; master weights 9 instead of 7, 192 508 / 479, 384 498 / 481; a stored error 12 instead of 13.4, 384 485 / 462;
+//   SGDM with master weights 10.5 instead of 8.2, 460 MB 192 145 / 126.  And those off the lines, 460 MB and 1.4 GB, the caps of the former / as now:
+//   fp32 state, Adam FP8 12 264 165 / 153, 524 / 481, INT4 11 40 152 / 140, 503 / 439; master weights, where fewer than three lanes in four are busy, 8.5
+//   328 1.4 GB 545 / 488; a stored error 11 504 FP8 153 / 144, 535 / 470; SGDM FP8 17.5 200 149 / 143, 492 / 469, where fewer are busy 15 from 768 MB, 328
+//   485 / 443; with master weights 10.5 48 163 / 146, 530 / 477.  bf16 state, Adam 19 40 INT4 1.4 GB 503 / 457, FP8 from 600 MB, 499 / 448 (460 MB 48
+//   loses 3 %); with master weights where fewer than three in four are busy 10.5 328 173 / 157, 580 / 489, in FP8 from 600 MB for all, 48 545 / 491 (INT4
+//   136 490 / 509); SGDM with master weights 12 for all, 328 161 / 147, 527 / 440; with a stored error 16, INT4 14 40 158 / 145, 505 / 430.)
 //   Adam, fp32 state, 10.3: rows of 48 369 / 389, 160 368 / 393, 200 365 / 391, 328 378 / 395, 400 362 / 406, 504 393 / 415 (INT4 354 / 368,
 //   353 / 372, 359 / 370, 361 / 373, 355 / 383, 366 / 395); bf16 state, 20.5, where nine lanes in ten are busy: INT4 48 214 / 219, 160
 //   217 / 225, 504 211 / 229 (FP8 227 / 238, 234 / 245, 223 / 252), others none (400 243 / 222).
@@ -435,32 +447,36 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, un
 //   585, 96 508 / 555 and 549 / 582, 200 502 / 550 and 538 / 552, 504 531 / 559 and 556 / 583; SGDM 96 464 / 526 and 485 / 560, 400 477 / 516 and 499 / 530,
 //   504 503 / 532 and 519 / 563; 328 gains nothing), with a stored error 17.2 (96 472 / 524 and 476 / 514, 200 481 / 519 and 488 / 506, 504 490 / 547 and
 //   488 / 549).  SGDM, bf16 state, from 768 MB on and where nineteen lanes in twenty are busy 21.5 (504: 437 / 488, 2.6 GB 755 / 879; 390 MB 116 / 114).
-// For arrays in the cache before it only Adam with fp32 state: 16 where three lanes in four are busy (8 M elements: 96 28.9 / 30.0, 400
+// For arrays in the cache before it only Adam with fp32 state: from 96 MB on 16 where three lanes in four are busy (8 M elements: 96 28.9 / 30.0, 400
 // 29.8 / 30.6; 25 M 87.8 / 90.3, 91.5 / 93.1), with master weights 14 from 192 MB on (16 M: 48 68.4 / 71.4, 96 66.9 / 68.6, 200 69.8 / 71.5, 264
 // 73.1 / 72.9, 400 68.9 / 70.2, 504 68.7 / 70.7; 23 M: 96 111.3 / 114.0, 400 115.0 / 116.3, 504 113.6 / 117.9; below no difference, 9.6 M: 96
-// 42.3 / 42.6, 200 43.9 / 43.9, 400 44.2 / 44.1).
-inline unsigned unit_workgroups(const KernelVariant &kv, uint64_t bytes, uint64_t units, uint64_t elements) {
+// 42.3 / 42.6, 200 43.9 / 43.9, 400 44.2 / 44.1; Adam below 96 MB lost by it, 200 2.7 M elements 11.6 / 11.2).
+inline unsigned unit_workgroups(const KernelVariant &kv, uint64_t bytes, uint64_t units, uint64_t elements, bool streamed = false) {
   const uint64_t lanes = units * TILE_ELEMS, MB = 1000000;
   const auto at_least = [=](uint64_t tenths) { return static_cast<unsigned>((tenths * lanes + 10 * elements - 1) / (10 * elements)); };
-  const bool most = elements * 4 >= lanes * 3;
+  const bool fp8 = kv.fmt == FMT_FP8, long_step = bytes >= 600 * MB, most = elements * 4 >= lanes * 3, nearly_all = elements * 20 >= lanes * 19;
   if (bytes < 384 * MB) {
     if (kv.state_bf16) return 0;
-    return kv.algo == ALGO_ADAM ? (most ? at_least(160) : 0) : kv.algo == ALGO_ADAM_MASTER && bytes >= 192 * MB ? at_least(140) : 0;
+    return kv.algo == ALGO_ADAM ? (most && bytes >= 96 * MB ? at_least(160) : 0)
+                                : kv.algo == ALGO_ADAM_MASTER && bytes >= 192 * MB ? at_least(140) : 0;
   }
   if (kv.state_bf16) {
     switch (kv.algo) {
-      case ALGO_ADAM: return elements * 10 >= lanes * 9 ? at_least(205) : 0;
-      case ALGO_SGDM: return elements * 20 >= lanes * 19 && bytes >= 768 * MB ? at_least(215) : 0;
-      case ALGO_SGDM_EXACT: return most ? at_least(172) : 0;
-      default: return most ? at_least(124) : 0;
+      case ALGO_ADAM: return elements * 10 >= lanes * 9 ? at_least(streamed || (fp8 && !long_step) ? 205 : 190) : 0;
+      case ALGO_ADAM_MASTER: return !streamed && (!most || (fp8 && long_step)) ? at_least(105) : most ? at_least(124) : 0;
+      case ALGO_SGDM: return nearly_all && bytes >= 768 * MB ? at_least(215) : 0;
+      case ALGO_SGDM_EXACT: return !streamed ? at_least(fp8 ? 160 : 140) : most ? at_least(172) : 0;
+      default: return !streamed ? at_least(120) : most ? at_least(124) : 0;
     }
   }
   switch (kv.algo) {
-    case ALGO_ADAM: return at_least(134);
-    case ALGO_ADAM_MASTER: return at_least(90);
-    case ALGO_SGDM: return most ? at_least(155) : 0;
-    case ALGO_SGDM_EXACT: return at_least(120);
-    default: return at_least(82);
+    case ALGO_ADAM: return at_least(streamed ? 134 : fp8 ? 120 : 110);
+    case ALGO_ADAM_MASTER: return at_least(streamed || most ? 90 : 85);
+    case ALGO_SGDM:
+      if (!streamed && fp8 && !nearly_all) return most ? at_least(175) : bytes >= 768 * MB ? at_least(150) : 0;
+      return most ? at_least(155) : 0;
+    case ALGO_SGDM_EXACT: return at_least(!streamed && (fp8 || nearly_all) ? 110 : 120);
+    default: return at_least(105);
   }
 }
 // The dynamic LDS that keeps k workgroups resident per compute unit (0: no request); LDS is handed out in pieces of 1280

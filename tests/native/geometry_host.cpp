@@ -117,7 +117,7 @@ int main() {
           const unsigned half = wide_workgroups_idle(kv, mb * 1000000, (unsigned)nw, 1000, 500 * g);
           CHECK(capped ? k >= 2 && k <= 22 : k == 0);
           CHECK(half == 0 || (half >= k && half <= 2 * k));
-          if (k > 2) CHECK(k * g * 10 >= 95 * TILE_ELEMS && (k - 1) * g * 10 < 204 * TILE_ELEMS && k * nw <= 44);
+          if (k > 2) CHECK(k * g * 10 >= 85 * TILE_ELEMS && (k - 1) * g * 10 < 204 * TILE_ELEMS && k * nw <= 44);
         }
       }
       for (uint64_t busy = 1; busy <= (uint64_t)TILE_ELEMS; ++busy) {
