@@ -317,7 +317,11 @@ bool off_lines(const eco_tensor_t &t, const eco::Placement &p, const eco::StateL
 // of 128: fp32 state, Adam 250 MB 71 / 74, 280 89 / 82, 340 103 / 99, master weights 69 / 74, 91 / 82, 107 / 97, SGDM 65 / 69, 82 / 77; bf16
 // state, INT4, Adam 310 MB 82 / 83, 340 90 / 90, 420 99 / 97, 640 187 / 168, SGDM (FP8) 310 75 / 78, 340 84 / 85, 420 101 / 95.  Rows of 1.6 GB, fp32
 // state: 1120 (pairs: 35 lines) 491 / 451, 2016 517 / 507, 544 532 / 555, 1000 527 / 654, 6944 545 / 554; bf16 state 1120 528 / 620, 320 590 / 576.
-constexpr uint64_t stream_from(bool f32) { return f32 ? 280000000 : 384000000; }
+// The line of fp32 state among the forms, 285 / 300 / 320 / 340 MB, streamed in hundredths of usual: Adam groups of 128 104 / 105 / 101 / 98, rows of
+// 1024 100 / 99 / 94 / 89, 1088 106 / 110 / 101 / 94, 192 104 / 107 / 106 / 103; with master weights 128 98 / 105 / 103 / 94, rows of 1024 109 / 108 / 95 / 90;
+// SGDM 128 102 / 103 / 103 / 98, rows of 1024 96 / 97 / 96 / 91.  All of these are of steps back to back on the same arrays.  What a training loop does
+// between two steps takes the place of the arrays in the cache, and the two would meet at less there; no rule here is measured for that.
+constexpr uint64_t stream_from(bool f32) { return f32 ? 310000000 : 384000000; }
 uint32_t stream_launches(uint64_t bytes, bool f32, uint64_t tiles, const Lists::WideLoad (&load)[eco::MAX_WIDE_WAVES + 2]) {
   if (bytes < stream_from(f32)) return 0;
   uint32_t launches = load[0].off_lines * 8 <= load[0].elements + tiles * eco::TILE_ELEMS ? 1 : 0;

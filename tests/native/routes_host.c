@@ -271,6 +271,25 @@ int main(void) {
           ++bad;
         }
       }
+  /* Where the streamed kernels begin: steps of fp32 state on either side of 310 MB, of bf16 state of 384 MB. */
+  for (int bf16 = 0; bf16 < 2; ++bf16)
+    for (int group = 128; group <= 1024; group += 896) {
+      const void *kernels[3];
+      for (int k = 0; k < 3; ++k) {
+        eco_plan_t *plan = NULL;
+        memset(list, 0, sizeof *list);
+        list[0].weights = (void *)0x1000; list[0].scales = (void *)0x2000; list[0].grad = (void *)0x3000; list[0].m = (void *)0x4000; list[0].v = (void *)0x5000;
+        list[0].group_size = (uint64_t)group; list[0].fmt = FP8;
+        list[0].numel = (uint64_t)((bf16 ? 384e6 / 7 : 310e6 / 11) * (k == 0 ? 0.5 : k == 1 ? 0.97 : 1.01)) / 16384 * 16384;
+        hp.opt = ADAM; hp.mode = ECO_MODE_ECO; hp.state_dtype = bf16;
+        launches = 0;
+        if (eco_plan_create(list, 1, &hp, &plan) != ECO_OK || eco_step(plan, &hp, NULL) != ECO_OK) { printf("FAILED: line: %s\n", eco_last_error()); return 1; }
+        kernels[k] = kernel_of[launches - 1];
+        (void)eco_plan_destroy(plan);
+      }
+      hp.state_dtype = 0;
+      if (kernels[0] != kernels[1] || kernels[1] == kernels[2]) { printf("where streaming begins, groups of %d, %s state\n", group, bf16 ? "bf16" : "fp32"); ++bad; }
+    }
   /* Launch options hold for the next step of a plan made before they were set, and no longer than they are set. */
   hp.opt = ADAM; hp.mode = ECO_MODE_ECO;
   for (int group = 128; group <= 1024; group += 896) {

@@ -1,4 +1,4 @@
-"""Steps whose arrays come from HBM (280 MB and more with fp32 state, 384 MB with bf16) load and store past the caches, and waves exchange
+"""Steps whose arrays come from HBM (310 MB and more with fp32 state, 384 MB with bf16) load and store past the caches, and waves exchange
 halves of their fp32 pieces to do it: every class of scale group and of unit, whole and partial waves, pieces that are cut off, beside
 a large tensor that takes the step over the line.  The comparison bar is the one of tests/gpu_util.py, and no bit may differ."""
 import numpy as np
