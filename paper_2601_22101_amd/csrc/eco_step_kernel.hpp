@@ -73,10 +73,10 @@ __device__ __forceinline__ void load_f32x8(const float *p, int nvalid, float (&o
   }
 }
 
-template <int ACC, int CP = CACHED>
+template <int ACC>
 __device__ __forceinline__ void load_bf16x8(const uint16_t *p, int nvalid, float (&out)[8]) {
   if (use_vector<ACC>(nvalid)) {
-    const eco_u32x4_t q = load_vec<CP>(reinterpret_cast<const eco_u32x4_t *>(p));
+    const eco_u32x4_t q = *reinterpret_cast<const eco_u32x4_t *>(p);
     out[0] = bf16_lo(q.x); out[1] = bf16_hi(q.x); out[2] = bf16_lo(q.y); out[3] = bf16_hi(q.y);
     out[4] = bf16_lo(q.z); out[5] = bf16_hi(q.z); out[6] = bf16_lo(q.w); out[7] = bf16_hi(q.w);
   } else {
@@ -115,12 +115,6 @@ template <bool BF16, int ACC>
 __device__ __forceinline__ void load_state8(const void *base, uint64_t e0, int nvalid, float (&out)[8]) {
   if (BF16) load_bf16x8<ACC>(static_cast<const uint16_t *>(base) + e0, nvalid, out);
   else load_f32x8<ACC>(static_cast<const float *>(base) + e0, nvalid, out);
-}
-
-template <bool BF16, int ACC>
-__device__ __forceinline__ void store_state8(void *base, uint64_t e0, int nvalid, const float (&x)[8]) {
-  if (BF16) store_bf16x8<ACC>(static_cast<uint16_t *>(base) + e0, nvalid, x);
-  else store_f32x8<ACC>(static_cast<float *>(base) + e0, nvalid, x);
 }
 
 // 8 codes of one lane: two dwords of E4M3 bytes, or one dword of INT4 nibbles (in c[0]).
@@ -901,7 +895,9 @@ __device__ __forceinline__ void step_wave_unit(const StepArgs &a, const TensorDe
 // the kernels below: they are in scalar registers when the wave starts (the build asks for that; members of a struct are not), one
 // memory access fewer in a chain of four (one matrix of 1 M elements 5.2 -> 5.0 us, of 4 M 16.9 -> 16.7).  As integers: for every argument
 // of pointer type the runtime looks up the allocation behind it, 0.03 us of a call each.  `table` also covers the one-wave units, whose list
-// lies behind the tiles'.
+// lies behind the tiles'.  FP8, bf16 state, fp32 scales, Adam and nearest rounding take 65 registers, here and in the wide kernel with one-wave units,
+// so seven waves a SIMD; held to 64 they run eight, which is no faster (us, 65 / 64: 4 M elements 8.70 / 8.79, 8 M 18.69 / 19.01, 16 M 30.7 / 31.0,
+// 21 M 40.3 / 40.7; rows of 200 12.04 / 12.05; 5.7 M 13.16 / 12.94).
 template <int FMT, bool STATE_BF16, bool SCALE_BF16, int ALGO, int ROUND, int CP>
 __global__ __launch_bounds__(WG_THREADS) void eco_step_kernel(const uint64_t table, const uint64_t tensors, const StepArgs a) {
   // A wave that has not issued its loads yet goes first: its address arithmetic and load instructions

@@ -33,7 +33,9 @@
 // elements 14.2 -> 12.8 us; past the caches (CP, see there) 1153 M in tensors of that kind FP8 4378 -> 3820 and INT4 2492 -> 2412; where a list is too short for it or has company that costs launches, see one_pass_pays.  What
 // it took: 12 waves of 168 registers rather than 8 of 256 (INT4 1290 -> 1000 us), no memory access inside a branch (1000 ->
 // 940), an event's contributions half a turn before the result is wanted (940 -> 890).  19 of the 80 variants, among them
-// Adam with bf16 state and stochastic rounding, do not quite fit 168 registers and keep 2 to 11 values in scratch memory.
+// Adam with bf16 state and stochastic rounding, do not quite fit 168 registers and keep 2 to 11 values in scratch memory, and so do 15 of the 80 that pass the
+// caches by; all of these are as fast as the two forms before them or faster (721 M elements in tensors of 1408 x 2048, one each, through the
+// caches before waves took whole lines / past them: FP8, Adam with master weights 3774 / 3287, INT4, bf16 state, Adam 1569 / 1529, SGDM 1123 / 1125).
 #pragma once
 #include "eco_step_kernel.hpp"
 
