@@ -402,8 +402,8 @@ def main() -> int:
                     help="where the harness puts the arenas in HBM: one allocation per arena (packed); one allocation without "
                          "gaps, m first and v last with codes, scales and gradients between them (dense) or in the order codes, "
                          "scales, gradients, m, v (dense-default); one allocation without gaps, m first and v after as many of "
-                         "the other arenas as the library's bandwidth probe finds fastest at set-up (probed; auto = probed for "
-                         "FP8 / fp32-state Adam workloads of 8 GiB and more, dense for other large ones); one allocation with the "
+                         "the other arenas as the library's bandwidth probe finds fastest at set-up (probed; auto = dense for "
+                         "workloads of 8 GiB and more); one allocation with the "
                          "codes+gradient, m and v arenas tens of GiB of unused memory apart (spread)")
     ap.add_argument("--spread-gap-gib", type=int, default=0, help="distance between the arena groups of the spread placement (0 = default)")
     ap.add_argument("--calibrate-gaps", type=int, default=3,
@@ -549,14 +549,15 @@ def main() -> int:
         out["roofline"]["ceiling_gbs"] = n * 20.0625 / (mix[0] * 1e-3) / 1e9
         out["roofline"]["plain_copy_gbs"] = n * 8.0 / (cpy[0] * 1e-3) / 1e9
         out["roofline"]["ceiling_what"] = ("eco_bandwidth_probe on the same arrays: ceiling_gbs = the step's loads and stores "
-                                           "(11.03 B read, 9.03 B written per element, same tiles and occupancy cap) without "
-                                           "arithmetic; plain_copy_gbs = float4 copy m -> v; averages of 5 launches")
+                                           "(11.03 B read, 9.03 B written per element, same tiles and occupancy cap, past the caches as "
+                                           "the step goes) without arithmetic; plain_copy_gbs = copy m -> v, 16 bytes to a lane, past "
+                                           "the caches; averages of 5 launches")
     placement_used = dw.placement
     dw.close()
     del dw
     torch.cuda.empty_cache()
     if args.compare_placements is None:
-        args.compare_placements = "dense,packed,spread" if headline else ""
+        args.compare_placements = "probed,packed,spread" if headline else ""
     others = [p for p in args.compare_placements.split(",") if p] if args.config == 4 else []
     for other in others:
         bulk_ok = over.get("mode", eco.ECO_MODE_ECO) in (eco.ECO_MODE_ECO, eco.ECO_MODE_NAIVE)

@@ -1266,10 +1266,13 @@ eco_status_t eco_bandwidth_probe(int32_t kind, void *codes, void *scales, const 
     return fail(ECO_EINVAL, "numel must be a positive multiple of 1024 below 2^35");
   eco::KernelVariant kv;
   kv.fmt = eco::FMT_FP8; kv.state_bf16 = 0; kv.scale_bf16 = 0; kv.algo = eco::ALGO_ADAM; kv.round = eco::ROUND_SR;
+  const uint64_t bytes = numel * (kind == 0 ? 11 : 8);
+  const bool streamed = bytes >= stream_from(true);
   const int64_t opt_lds = g_lds_bytes.load(std::memory_order_relaxed);
-  const uint32_t lds = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds) : lds_for_waves(default_waves(kv, HbmBound(UINT64_MAX)), 512);
+  const uint32_t lds = opt_lds >= 0 ? static_cast<uint32_t>(opt_lds)
+                                    : lds_for_waves(streamed ? streaming_waves(kv, bytes) : default_waves(kv, HbmBound(bytes)), 512);
   (void)hipGetLastError();
-  const hipError_t e = eco::launch_bandwidth_probe(kind, codes, scales, grad, m, v, numel, lds, static_cast<hipStream_t>(stream));
+  const hipError_t e = eco::launch_bandwidth_probe(kind, codes, scales, grad, m, v, numel, streamed, lds, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? ECO_OK : fail_hip(e, "probe kernel launch");
 }
 

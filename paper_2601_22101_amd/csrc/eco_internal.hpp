@@ -196,7 +196,7 @@ hipError_t launch_quantize_init(const void *src, int src_bf16, uint64_t numel, i
 hipError_t launch_dequantize(const void *weights, const void *scales, uint64_t numel, int fmt, uint64_t group_size,
                              int scale_bf16, const void *src, int src_kind, float *dst, hipStream_t stream);
 
-hipError_t launch_bandwidth_probe(int kind, void *codes, void *scales, const void *grad, void *m, void *v, uint64_t numel,
+hipError_t launch_bandwidth_probe(int kind, void *codes, void *scales, const void *grad, void *m, void *v, uint64_t numel, bool streamed,
                                   uint32_t lds_bytes, hipStream_t stream);
 
 hipError_t launch_arith_selftest(int kind, float numerator, uint32_t bits_lo, uint32_t bits_hi, unsigned long long *mismatches,

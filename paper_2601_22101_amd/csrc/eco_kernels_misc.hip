@@ -471,39 +471,51 @@ hipError_t launch_dequantize(const void *weights, const void *scales, uint64_t n
 // Measurement aids: what the memory system delivers for the step's own access pattern with the arithmetic
 // taken out.  MIX: every lane loads what a lane of the FP8 / fp32-state Adam step loads for its 8 elements
 // (8 B codes, 16 B gradient, 2 x 16 B m, 2 x 16 B v, the block's scale) and stores what it stores (codes, m, v,
-// scale), in the same tile geometry and under the same occupancy cap: 11.03 bytes read and 9.03 written per
-// element.  COPY: the plain two-stream copy, 16 B per lane and instruction (4 B read, 4 B written per element).
-__global__ __launch_bounds__(WG_THREADS, 8) void eco_probe_mix_kernel(const uint2 *codes, float *scales, const uint4 *grad,
-                                                                      float4 *m, float4 *v, uint2 *codes_out) {
-  const uint64_t i = (uint64_t)blockIdx.x * WG_THREADS + threadIdx.x;        // the lane's 8-element piece
+// scale), in the same tile geometry, whole lines to an instruction, past the caches where the step passes them by, and under the same
+// occupancy cap: 11.03 bytes read and 9.03 written per element.  COPY: the plain two-stream copy, 16 B per lane and instruction (4 B read, 4 B
+// written per element).  In 32 bytes to a lane and through the caches, as the step once went, MIX was no ceiling of it: GB/s, so / now, 40 M
+// elements 5298 / 6497, 1 G 5587 / 6751, 5 G 5334 / 6532; COPY through the caches / past them 6040 / 6630, 6239 / 6698, 6241 / 6708.
+template <int CP>
+__global__ __launch_bounds__(WG_THREADS, 8) void eco_probe_mix_kernel(void *codes, float *scales, const void *grad, void *m, void *v) {
+  const uint64_t i = (uint64_t)blockIdx.x * WG_THREADS + threadIdx.x, e0 = i * ELEMS_PER_LANE;        // the lane's 8-element piece
+  const WavePieces wp = full_wave(e0);
   __builtin_amdgcn_s_setprio(3);
-  const uint4 g = grad[i];
-  float4 m0 = m[2 * i], m1 = m[2 * i + 1], v0 = v[2 * i], v1 = v[2 * i + 1];
-  uint2 c = codes[i];
+  eco_u32x4_t g[2], mq[2], vq[2];
+  uint32_t c[2];
+  load_wave8<true, true, CP>(grad, wp, g);
+  load_wave8<false, true, CP>(m, wp, mq);
+  load_wave8<false, true, CP>(v, wp, vq);
+  load_codes8<FMT_FP8, ACC_FULL, CP>(codes, e0, 8, c);
   const float s = scales[i >> 4];
   __builtin_amdgcn_s_setprio(0);
   // every loaded value reaches a store, so that no load can be dropped
-  c.x ^= g.x ^ g.z; c.y ^= g.y ^ g.w;
-  m0.x += s * 0.0f;
-  codes_out[i] = c;
-  m[2 * i] = v0; m[2 * i + 1] = v1; v[2 * i] = m0; v[2 * i + 1] = m1;
+  c[0] ^= g[0].x ^ g[0].z;
+  c[1] ^= g[0].y ^ g[0].w;
+  float mx[8], vx[8];
+  unpack8<false>(mq, mx);
+  unpack8<false>(vq, vx);
+  mx[0] += s * 0.0f;
+  store_wave_codes8<FMT_FP8, ACC_FULL, CP>(codes, e0, 8, wp, c);
+  store_wave8<false, ACC_FULL, CP>(m, e0, 8, wp, vx);
+  store_wave8<false, ACC_FULL, CP>(v, e0, 8, wp, mx);
   if ((threadIdx.x & 15) == 0) scales[i >> 4] = s;
 }
 
-__global__ __launch_bounds__(256) void eco_probe_copy_kernel(const float4 *src, float4 *dst) {
-  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  dst[i] = src[i];
+template <int CP>
+__global__ __launch_bounds__(256) void eco_probe_copy_kernel(const eco_u32x4_t *src, void *dst) {
+  const eco_u32x4_t x = load_vec<CP>(src + (uint64_t)blockIdx.x * 256 + threadIdx.x);
+  __builtin_amdgcn_raw_buffer_store_b128(x, buffer_at(dst, (uint64_t)blockIdx.x * 4096, 4096), threadIdx.x * 16, 0, CP);
 }
 
-hipError_t launch_bandwidth_probe(int kind, void *codes, void *scales, const void *grad, void *m, void *v, uint64_t numel,
+hipError_t launch_bandwidth_probe(int kind, void *codes, void *scales, const void *grad, void *m, void *v, uint64_t numel, bool streamed,
                                   uint32_t lds_bytes, hipStream_t stream) {
   if (kind == 0) {
-    ECO_LAUNCH_CHECKED(eco_probe_mix_kernel, dim3((unsigned)(numel / TILE_ELEMS)), dim3(WG_THREADS), lds_bytes, stream,
-                       static_cast<const uint2 *>(codes), static_cast<float *>(scales), static_cast<const uint4 *>(grad),
-                       static_cast<float4 *>(m), static_cast<float4 *>(v), static_cast<uint2 *>(codes));
+    const auto kernel = streamed ? eco_probe_mix_kernel<STREAM_WAVE> : eco_probe_mix_kernel<CACHED>;
+    ECO_LAUNCH_CHECKED(kernel, dim3((unsigned)(numel / TILE_ELEMS)), dim3(WG_THREADS), lds_bytes, stream, codes, static_cast<float *>(scales), grad,
+                       m, v);
   } else {
-    ECO_LAUNCH_CHECKED(eco_probe_copy_kernel, dim3((unsigned)(numel / 1024)), dim3(256), 0, stream,
-                       static_cast<const float4 *>(m), static_cast<float4 *>(v));
+    const auto kernel = streamed ? eco_probe_copy_kernel<STREAM_WAVE> : eco_probe_copy_kernel<CACHED>;
+    ECO_LAUNCH_CHECKED(kernel, dim3((unsigned)(numel / 1024)), dim3(256), 0, stream, static_cast<const eco_u32x4_t *>(m), v);
   }
   return hipSuccess;
 }

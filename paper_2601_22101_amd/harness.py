@@ -41,20 +41,21 @@ class DeviceWorkload:
     kind) so that a multi-thousand-tensor model costs a handful of allocations; each tensor still
     has its own descriptor in the plan and its own, 256-byte aligned, slices."""
 
-    # Where the arrays lie in device memory matters on MI355X: measured with the arrays placed by hand inside one
-    # 244 GiB allocation, the address space falls into 32 GiB regions of three kinds, and the step (nine streams
-    # that advance in lock-step) runs 3 % faster, its loads and stores alone 9 % faster, when the m or the v
-    # array lies in a region of another kind than the rest; a plain two-stream copy does not care.  Which region
-    # is of which kind is a property of the physical addresses an allocation happens to get.  Placements:
+    # Where the arrays lie in device memory: measured with the arrays placed by hand inside one 244 GiB allocation, the
+    # address space falls into 32 GiB regions of three kinds, and a step whose nine streams go through the caches runs 3 %
+    # faster, its loads and stores alone 9 % faster, when the m or the v array lies in a region of another kind than the
+    # rest.  Past the caches, as steps from HBM go, the orders of the arenas differ by 2-3 % in loads and stores alone
+    # (33 of them: 6.50 to 6.67 TB/s), and the order found fastest does not make the faster step (ms per step of 3.34 G
+    # parameters, two processes each: dense 10.51 and 10.61, probed 10.57 and 10.63, packed 10.73).  Placements:
     #   "packed"  one allocation per arena, wherever the allocator puts them;
     #   "dense"   one allocation, no byte unused, order m | codes, scales, gradients | v;
     #   "probed"  one allocation, no byte unused; m first, and v after as many of the other arenas (codes and scales,
     #             then the gradient arenas) as the library's bandwidth probe, run on the candidate addresses before
-    #             anything is initialised, finds fastest;
+    #             anything is initialised, finds fastest (kept for comparison);
     #   "spread"  one allocation with the arena groups SPREAD_GAP bytes apart: the gaps are memory the benchmark
     #             does not use (kept for comparison).
     SPREAD_GAP = 48 << 30
-    SPREAD_MIN_BYTES = 8 << 30          # "auto" spreads workloads of at least this footprint
+    SPREAD_MIN_BYTES = 8 << 30          # from this footprint on "auto" makes one allocation
 
     def __init__(self, wl: Workload, device: str = "cuda:0", base_seed: int = workloads.BASE_SEED,
                  init=True, layout: Optional[dict] = None, skew_bytes: Optional[dict] = None,
@@ -63,9 +64,9 @@ class DeviceWorkload:
         """`layout`: hyper-parameter overrides that are fixed for the life of the plan (opt, mode, ...).
         In the master-weight mode the fp32 initial weights are kept as the master copy; in the
         exact-injection mode the aux buffer starts as e_0 = theta_0 - q(theta_0) (Appendix A).
-        `placement`: "packed", "dense", "probed" or "spread" (see the class comment); "auto" = probed for large
-        workloads the probe's arrays fit (FP8 codes, fp32 state, Adam, with or without master weights), dense for other
-        large ones, packed for small ones.  `skew_bytes` / `single_allocation` place arenas by hand (probes).
+        `placement`: "packed", "dense", "probed" or "spread" (see the class comment); "auto" = dense for large
+        workloads, packed for small ones; "probed" is dense where the probe's arrays do not fit (they are FP8 codes, fp32 state,
+        Adam, with or without master weights).  `skew_bytes` / `single_allocation` place arenas by hand (probes).
         `order`: "default" lays the arenas out as codes, scales, gradients, m, v; "state-apart" (one allocation only)
         puts m first and v last with everything else between them, no byte unused.
         `grad_sets`: number of gradient arenas (each with a plan of its own over the same weights and state),
@@ -92,7 +93,7 @@ class DeviceWorkload:
         self.probe_results = None
         large = self.pool_bytes(wl, self.mode, grad_sets) >= self.SPREAD_MIN_BYTES and dev.type == "cuda"
         if placement == "auto":
-            placement = ("probed" if self._probe_fits() else "dense") if large else "packed"
+            placement = "dense" if large else "packed"
         if placement == "probed" and not (dev.type == "cuda" and self._probe_fits()):
             placement = "dense"
         if placement == "spread" and not skew and single_allocation is False and dev.type == "cuda":
@@ -180,37 +181,11 @@ class DeviceWorkload:
 
         self.calibration = None
         if probe_order:
-            # Which orders are fast depends on the physical memory the allocation got; one whose candidates all time
-            # alike (a v array in another kind of region is worth 9 % to the probe; less than 7 % between the fastest and
-            # the slowest candidate is noise) offers no choice: all of it lies in regions of one kind.  Then another allocation is made while
-            # this one is still held, so that it gets other memory, up to three in all and only while the device has
-            # room; the allocation with the fastest candidate is kept and the others are returned to the device.
-            need = pool_buf.numel()
             best = self._probe_orders(pool_buf, pool_pos, off, soff, code_bytes, woff, grad_sets)
-            losers, tried = [], 1
-            while (best is not None and best["contrast"] < 1.07 and tried < 3 and
-                   torch.cuda.mem_get_info(dev)[0] >= need + (8 << 30)):
-                try:
-                    other_buf = torch.zeros(need, dtype=torch.uint8, device=dev)
-                except torch.cuda.OutOfMemoryError:
-                    break
-                other_pos = (-other_buf.data_ptr()) % (1 << 21)
-                other = self._probe_orders(other_buf, other_pos, off, soff, code_bytes, woff, grad_sets)
-                tried += 1
-                if other["gbs"] > best["gbs"]:
-                    losers.append(pool_buf)
-                    pool_buf, pool_pos, best = other_buf, other_pos, other
-                else:
-                    losers.append(other_buf)
-                del other_buf
-            if losers:
-                losers.clear()
-                torch.cuda.empty_cache()
             if best is not None:
                 self._arena_order, self.probe_results = best["order"], best["results"]
                 self.placement = (f"one allocation, no gaps, order chosen at set-up by the library's bandwidth probe among "
-                                  f"{best['orders']} orders" + (f" (in the best of {tried} allocations)" if tried > 1 else "") +
-                                  f": {best['text']}")
+                                  f"{best['orders']} orders: {best['text']}")
         if calibrate_gaps > 1 and pool_buf is not None and not external and "GiB apart" in self.placement:
             skew = self._calibrate(build_views, pool_buf, skew, calibrate_gaps)
         build_views(skew, zero=external or self.calibration is not None or self.probe_results is not None)
@@ -247,7 +222,7 @@ class DeviceWorkload:
         other arenas (codes + scales + unquantized weights as one unit, then the gradient arenas, then the master
         weights if the mode keeps them), k = 1 .. all of them; and, mirrored, v last and m before the last k.  The probe is timed on each candidate's addresses in the
         still uninitialised allocation.  Returns the fastest order with its figures (None if the workload is too small
-        to probe); "contrast" = fastest / slowest candidate."""
+        to probe)."""
         scale_bytes = (2 if self.wl.scale_bf16 else 4) * max(soff, 1)
         sizes = {"codes": max(code_bytes, 1), "scales": scale_bytes, "plain": 2 * max(woff, 1), "m": 4 * off, "v": 4 * off}
         grads = ["grad"] + [f"grad_extra{k}" for k in range(1, grad_sets)]
@@ -292,8 +267,7 @@ class DeviceWorkload:
             else:
                 runs.append([u, 1])
         text = " | ".join(f"{c} gradient arena{'s' if c > 1 else ''}" if u == "g" else u for u, c in runs)
-        return {"order": orders[best], "results": figures, "gbs": numel * 20.0625 / best_ms / 1e6,
-                "contrast": max(r[0] for r in results) / best_ms, "orders": len(orders), "text": text}
+        return {"order": orders[best], "results": figures, "orders": len(orders), "text": text}
 
     def _calibrate(self, build_views, pool_buf, skew, n_candidates):
         """Times the step for the default gap and for smaller ones (steps of 8 GiB, not below 24 GiB) inside

@@ -208,3 +208,29 @@ def test_one_scale_quantizer_past_the_caches(tail, fmt, src_bf16):
             assert torch.equal(got["w"][at // per:(at + m) // per], want["w"][:m // per])
             for key in ("e", "d"):
                 assert torch.equal(got[key][at:at + m].view(torch.int32), want[key][:m].view(torch.int32)), key
+
+
+def test_bandwidth_probe_past_the_caches():
+    """In calls that pass the caches by (40 M elements, 440 and 320 MB): every byte as it has to be, the guards around the arrays among them."""
+    from paper_2601_22101_amd import binding as eco
+    n, guard = 39_063 * 1024, 1024
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(9)
+    full = {k: torch.randint(-2**31, 2**31, (words + 2 * guard,), generator=gen, device=DEV, dtype=torch.int32)
+            for k, words in (("codes", n // 4), ("scales", n // 128), ("grad", n // 2), ("m", n), ("v", n))}
+    for k in ("scales", "m"):                                       # finite values: one of m's passes through an addition of zero
+        full[k] &= 0x3FFFFFFF
+    was = {k: t.clone() for k, t in full.items()}
+    x, b = ({k: t[guard:-guard] for k, t in d.items()} for d in (full, was))
+    eco.eco_bandwidth_probe(0, x["codes"], x["scales"], x["grad"], x["m"], x["v"], n)
+    torch.cuda.synchronize()
+    g = b["grad"].view(-1, 4)
+    assert torch.equal(x["m"], b["v"]) and torch.equal(x["v"], b["m"])
+    assert torch.equal(x["codes"].view(-1, 2), b["codes"].view(-1, 2) ^ torch.stack([g[:, 0] ^ g[:, 2], g[:, 1] ^ g[:, 3]], dim=1))
+    for k in full:
+        assert torch.equal(full[k][:guard], was[k][:guard]) and torch.equal(full[k][-guard:], was[k][-guard:]), k
+        assert k not in ("scales", "grad") or torch.equal(full[k], was[k]), k
+    eco.eco_bandwidth_probe(1, None, None, None, x["m"], x["v"], n)
+    torch.cuda.synchronize()
+    assert torch.equal(x["v"], b["v"]) and torch.equal(x["m"], b["v"])
+    assert torch.equal(full["v"][:guard], was["v"][:guard]) and torch.equal(full["v"][-guard:], was["v"][-guard:])
