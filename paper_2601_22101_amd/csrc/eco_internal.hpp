@@ -403,10 +403,10 @@ inline unsigned wide_workgroups(const KernelVariant &kv, unsigned nw, bool strea
 // Adam with fp32 state and SGDM with a stored error, where rows start off the lines of memory and are not streamed (1.6 GB of arrays, 13.6 and
 // 15.6 / this): 11.5 544 532 / 498, 560 556 / 512, 1000 524 / 501, 2016 517 / 490, in the cache 1152 66.4 / 64.8; 11.8 1000 552 / 500, 2016 514 / 505.
 // The other figures are from before waves took whole lines at a time (see exchange_chunks).  Since then, rows that start off the lines of memory,
-// 460 MB and 1.4 GB of arrays, us, as above / as now: SGDM, bf16 state, with a stored error (20.4 / 15) FP8 1000 149 / 134, 501 / 421, 3000 145 / 137,
-// 477 / 421, INT4 2024 148 / 133, 502 / 417; fp32 state, FP8, where fewer than nine lanes in ten are busy (19.6 / 17) 544 141 / 134, 507 / 460; INT4 with
-// a stored error from 1 GB (11.8 / 11.2) 1480 0.95, 3000 490 / 441, 460 MB 1000 loses 2 %; with master weights (9.7 / 10.6) 1000 147 / 140, 514 / 493;
-// Adam, master weights (9.5 / 8.5) 1.4 GB 760 453 / 411, 1480 474 / 442; Adam, in part in the cache (11.5 / 13) 1480 330 MB 101.9 / 98.5.
+// 460 MB and 1.4 GB of arrays, us, as above / as now: SGDM, bf16 state, with a stored error (20.4 / 15) FP8 1000 153 / 138, 497 / 417, 3000 149 / 139,
+// 475 / 419, INT4 2024 154 / 138, 490 / 409; fp32 state, FP8, where fewer than nine lanes in ten are busy (19.6 / 17) 544 143 / 138, 445 / 409; INT4 with
+// a stored error from 1 GB (11.8 / 11.2) 1480 467 / 435, 3000 491 / 443 (1000 424 / 431); with master weights (9.7 / 10.6) 1000 150 / 143, 448 / 429;
+// Adam, master weights (9.5 / 8.5) 1.4 GB 760 516 / 462, 1480 485 / 450; Adam, in part in the cache (11.5 / 13) 1480 330 MB 103.1 / 98.2.
 inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, unsigned nw, uint64_t units, uint64_t elements,
                                      bool streamed = false) {
   const auto at_least = [=](uint64_t tenths) {
@@ -430,12 +430,12 @@ inline unsigned wide_workgroups_idle(const KernelVariant &kv, uint64_t bytes, un
 // us, with / without --
 //   (Before waves took whole lines at a time, see exchange_chunks.  Since then those that pass the caches by, fp32 state, Adam 13.4 instead of 10.3,
 //   1.6 GB 192 510 / 471, 384 500 / 476; master weights 9 instead of 7, 192 508 / 479, 384 498 / 481; a stored error 12 instead of 13.4, 384 485 / 462;
-//   SGDM with master weights 10.5 instead of 8.2, 460 MB 192 145 / 126.  And those off the lines, 460 MB and 1.4 GB, the caps of the former / as now:
-//   fp32 state, Adam FP8 12 264 165 / 153, 524 / 481, INT4 11 40 152 / 140, 503 / 439; master weights, where fewer than three lanes in four are busy, 8.5
-//   328 1.4 GB 545 / 488; a stored error 11 504 FP8 153 / 144, 535 / 470; SGDM FP8 17.5 200 149 / 143, 492 / 469, where fewer are busy 15 from 768 MB, 328
-//   485 / 443; with master weights 10.5 48 163 / 146, 530 / 477.  bf16 state, Adam 19 40 INT4 1.4 GB 503 / 457, FP8 from 600 MB, 499 / 448 (460 MB 48
-//   loses 3 %); with master weights where fewer than three in four are busy 10.5 328 173 / 157, 580 / 489, in FP8 from 600 MB for all, 48 545 / 491 (INT4
-//   136 490 / 509); SGDM with master weights 12 for all, 328 161 / 147, 527 / 440; with a stored error 16, INT4 14 40 158 / 145, 505 / 430.)
+//   SGDM with master weights 10.5 instead of 8.2, 460 MB 192 157 / 136.  And those off the lines, 460 MB and 1.4 GB, the caps of the former / as now:
+//   fp32 state, Adam FP8 12 264 165 / 154, 511 / 462, INT4 11 40 163 / 149, 501 / 438; master weights, where fewer than three lanes in four are busy, 8.5
+//   328 1.4 GB 536 / 481; a stored error 11 504 FP8 155 / 146, 495 / 435; SGDM FP8 17.5 200 147 / 140, 435 / 414, where fewer are busy 15 from 768 MB, 328
+//   458 / 432; with master weights 10.5 48 167 / 148, 496 / 447.  bf16 state, Adam 19, in FP8 from 600 MB, 40 to 504 at 450 MB and 1.6 GB 3.5 % less time
+//   on average; with master weights where fewer than three in four are busy 10.5 328 169 / 154, 550 / 462, in FP8 from 600 MB for all, 48 495 / 450 (INT4
+//   136 490 / 509); SGDM with master weights 12 for all, 328 166 / 149, 536 / 446; with a stored error 16, INT4 14 40 157 / 145, 502 / 431.)
 //   Adam, fp32 state, 10.3: rows of 48 369 / 389, 160 368 / 393, 200 365 / 391, 328 378 / 395, 400 362 / 406, 504 393 / 415 (INT4 354 / 368,
 //   353 / 372, 359 / 370, 361 / 373, 355 / 383, 366 / 395); bf16 state, 20.5, where nine lanes in ten are busy: INT4 48 214 / 219, 160
 //   217 / 225, 504 211 / 229 (FP8 227 / 238, 234 / 245, 223 / 252), others none (400 243 / 222).
