@@ -46,7 +46,7 @@ class DeviceWorkload:
     # faster, its loads and stores alone 9 % faster, when the m or the v array lies in a region of another kind than the
     # rest.  Past the caches, as steps from HBM go, the orders of the arenas differ by 2-3 % in loads and stores alone
     # (33 of them: 6.50 to 6.67 TB/s), and the order found fastest does not make the faster step (ms per step of 3.34 G
-    # parameters, two processes each: dense 10.51 and 10.61, probed 10.57 and 10.63, packed 10.73).  Placements:
+    # parameters, six processes each: dense 10.51 to 10.65, probed 10.55 to 10.70; packed, one process, 10.73).  Placements:
     #   "packed"  one allocation per arena, wherever the allocator puts them;
     #   "dense"   one allocation, no byte unused, order m | codes, scales, gradients | v;
     #   "probed"  one allocation, no byte unused; m first, and v after as many of the other arenas (codes and scales,

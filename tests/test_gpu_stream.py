@@ -66,7 +66,7 @@ def test_steps_past_the_caches(home, fmt, bf16, over):
 def test_arrays_that_begin_off_a_line(off):
     """Arrays at 16 and 64 bytes past a line, without a plan: stepped the usual way, with the same results as arrays on lines."""
     from paper_2601_22101_amd import binding as eco
-    n = 27_000_001
+    n = 29_000_001
     gen = torch.Generator(device=DEV)
     gen.manual_seed(3)
     base = {"w": torch.randint(0, 120, (n,), generator=gen, device=DEV, dtype=torch.uint8), "s": torch.full((n // 128 + 1,), 1e-4, device=DEV),
@@ -134,7 +134,7 @@ def test_quantizer_past_the_caches(group, fmt, scale_bf16, src_bf16):
     The last group has 5 elements, a hundredth of those before them, and it and its neighbours are also compared with the oracle."""
     from paper_2601_22101_amd import binding as eco
     step = 20_000_000 // (group * 32) * (group * 32)                 # slices of whole groups that begin on 16 bytes
-    n = int(300e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) // group * group + 5
+    n = int(340e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) // group * group + 5
     gen = torch.Generator(device=DEV)
     gen.manual_seed(group)
     src = torch.randn(n, generator=gen, device=DEV) * 0.02
@@ -161,7 +161,7 @@ def test_last_group_of_less_than_a_lane(streamed, fmt, scale_bf16, src_bf16):
     o32 = oracle.get("f32")
     f, of, per = (eco.ECO_FMT_INT4, oracle.FMT_INT4, 2) if fmt else (eco.ECO_FMT_FP8_E4M3, oracle.FMT_E4M3, 1)
     groups = [16, 32, 64, 96, 128, 200, 256] if streamed else [*range(16, 512, 8), 512, 520, 576, 1000, 1152]
-    most = int(300e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) if streamed else 8 * 1152
+    most = int(340e6 / ((2 if src_bf16 else 4) + (0.5 if fmt else 1))) if streamed else 8 * 1152
     big = torch.randn(most + 2000, generator=torch.Generator(device=DEV).manual_seed(5), device=DEV)
     big = big.to(torch.bfloat16) if src_bf16 else big
     codes = torch.zeros(big.numel() // per, dtype=torch.uint8, device=DEV)
